@@ -168,7 +168,8 @@ int gws_sample_fwd_mx(const gws_tensor* t, const gws_mx_out* o, int n, int fmt, 
  * Two ways to the same bytes (w_hat, scale and Y are bit-identical between them):
  *   GWS_LINEAR_IN_OPERAND   one kernel; the sampling sits in the weight operand load of every
  *                           output tile (no w_hat round trip; each block is resampled once per
- *                           128 rows of X).  Any shape; w_hat/scale optional.
+ *                           tile of rows of X: 16 to 64 where the plain GEMM splits K over
+ *                           wavefronts, else 128).  Any shape; w_hat/scale optional.
  *   GWS_LINEAR_TWO_KERNELS  the sampling kernel of gws_sample_fwd, then the plain GEMM on w_hat.
  *                           Needs w_hat/scale (GWS_ERR_NULL otherwise).
  *   GWS_LINEAR_AUTO         two kernels when w_hat/scale are given (the faster choice at every M

@@ -41,7 +41,8 @@ int gws_sample_fwd_tuned(const gws_tensor* t, int n, int fmt, uint64_t step, int
  * grid by `extra_workgroups` (1 .. 4096) workgroups that sample `next` (rows a multiple of 32, columns of 64),
  * whatever the library's own estimate of whether the sampling fits beside the GEMM's last round says.
  * rider: 0 = the riding loop for any such weight, 1 = the loop for weights of whole 32 x 256 tiles (falls back
- * to 0 for other weights).  Same bytes as gws_gemm_bf16_sample_next.                                        */
+ * to 0 for other weights).  Same w_hat and scale bytes as gws_gemm_bf16_sample_next; Y is the 256-tile GEMM's,
+ * whichever GEMM that call would choose.                                                                    */
 int gws_gemm_bf16_ride_probe(const void* x, int64_t M, int64_t K, int64_t ldx, const void* w, int64_t N, int64_t ldw,
                              int w_is_nk, void* y, int64_t ldy, const gws_tensor* next, int fmt, uint64_t step,
                              int extra_workgroups, int rider, void* stream);

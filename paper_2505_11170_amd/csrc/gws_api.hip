@@ -606,7 +606,10 @@ static int plan_ride(const GemmArgs& g, bool gemm_empty, int64_t K, const gws_te
   memset(&r, 0, sizeof r);
   idle = 0;
   use_rider = 1;
-  const bool gemm_rides = force_extra >= 0 ? (gemm_empty || gemm256_applicable(g)) : (!gemm_empty && gemm256_applicable(g));
+  // few tiles are left to the kernel that splits K (the layout does not matter to the route of whole 256-row tiles)
+  StreamPlan plan;
+  const bool gemm_rides = force_extra >= 0 ? (gemm_empty || gemm256_applicable(g))
+                                           : (!gemm_empty && gemm_route(g, 0, plan) == GemmRoute::kLarge);
   if (!gemm_rides) return 0;
   const int cus = compute_units();
   const uint64_t tiles = gemm_empty ? 0 : (uint64_t)(g.M / 256) * (uint64_t)(g.N / 256);

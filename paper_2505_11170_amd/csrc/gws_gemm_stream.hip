@@ -1,0 +1,363 @@
+// BF16 GEMM for few rows of X on gfx950: Y[M x N] = X[M x K] * W (W stored [K x N] or [N x K]), plain or with the
+// GaussWS sampling of W on its way in (paper Eq. 3 + cast).
+//
+// What bounds it: the weight's bytes.  A tile of the output that walks all of K alone waits for memory K / 64 times, and
+// a few rows of X make a few tiles.  So a workgroup owns a small piece of Y (16 MT rows x 16 NT columns) and its
+// wavefronts split K: wavefront w takes a contiguous range of 64-deep units of K, keeps several blocks of loads in
+// flight, and needs neither barrier nor LDS until the partial sums meet in LDS, where they are added in the order of
+// the wavefronts (one defined order; the plain and the sampling kernel split K alike, so their Y is the same bits).
+// Operands go from global memory straight to the MFMA's registers: a lane of v_mfma_f32_16x16x32_bf16 holds 8
+// consecutive k of one output.  [N x K] weights and X are stored like that; of a [K x N] weight a lane loads the same
+// NT outputs of 8 rows and turns the 8 x NT piece with byte permutes.
+#include "gws_gemm256_core.h"
+#include "gws_launch.h"
+
+namespace gws {
+
+namespace stream {
+constexpr uint32_t kMaxLd = 1u << 24;   // leading dimensions the 32-bit lane offsets reach (63 rows x 2 bytes)
+
+__device__ __forceinline__ uint32_t umin(uint32_t a, uint32_t b) { return a < b ? a : b; }
+
+// The units of 64 k that wavefront w of P takes, as even as they go (the last unit of K may be half a one).
+__device__ __forceinline__ void unit_range(uint32_t K, uint32_t w, uint32_t P, uint32_t& u0, uint32_t& u1) {
+  const uint32_t nu = (K + 63) >> 6;
+  u0 = nu * w / P;
+  u1 = nu * (w + 1) / P;
+}
+
+// Tiles in bands of eight row tiles, row tiles first.  Workgroups are dealt round-robin to the 8 XCDs: tiles that share a
+// piece of the weight, and with narrow [K x N] tiles the two that share its cache lines, go to one XCD (its L2) as a
+// group, and the groups round-robin over the XCDs (a contiguous range per XCD would put the columns of one XCD on a few
+// of the L2's channels when a row of the weight is a multiple of 4 KiB).
+__device__ __forceinline__ void tile_origin(const GemmArgs& g, uint32_t bm, uint32_t bn, bool pairs, uint32_t& m0, uint32_t& n0) {
+  const uint32_t tm = (g.M + bm - 1) / bm, tn = (g.N + bn - 1) / bn;
+  const uint32_t G = umin(tm, 8) * (pairs ? 2 : 1), b = blockIdx.x, whole = gridDim.x / (8 * G) * (8 * G);
+  const uint32_t L = b < whole ? ((b >> 3) / G * 8 + (b & 7)) * G + (b >> 3) % G : b;
+  const uint32_t band = L / (8 * tn), r = L - band * 8 * tn, rows = umin(8, tm - 8 * band);
+  n0 = r / rows * bn;
+  m0 = (8 * band + r % rows) * bm;
+}
+
+// The partial sums of the P wavefronts added in the order of the wavefronts and written to Y.  acc[i][j][e] is row
+// 16 i + 4 (lane / 16) + e, column 16 j + lane % 16.
+template <int MT, int NT, int P>
+__device__ __forceinline__ void reduce_store(const f32x4 (&acc)[MT][NT], float* red, const GemmArgs& g, uint32_t m0,
+                                             uint32_t n0) {
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) red[(((wave * MT + i) * 4 + e) * NT + j) * 64 + lane] = acc[i][j][e];
+  __syncthreads();
+  for (uint32_t it = tid; it < MT * 4 * 64; it += P * 64) {
+    const uint32_t l = it & 63, ie = it >> 6;   // ie = 4 i + e
+    float s[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) s[j] = red[(ie * NT + j) * 64 + l];
+#pragma unroll
+    for (int w = 1; w < P; ++w)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) s[j] = __fadd_rn(s[j], red[((w * MT * 4 + ie) * NT + j) * 64 + l]);
+    const uint32_t row = m0 + 16 * (ie >> 2) + 4 * (l >> 4) + (ie & 3), o = l & 15;
+    if (row >= g.M) continue;
+    uint16_t* yr = g.y + (size_t)row * g.ldy + n0;
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+      if (n0 + 16 * j + o < g.N) yr[16 * j + o] = (uint16_t)pack_bf16_rne(s[j], 0.0f);
+  }
+}
+}  // namespace stream
+
+// A wavefront keeps D units of 64 k on their way into its own ring of LDS stages (global_load_lds_dwordx4, 8 rows x 128
+// contiguous bytes per instruction).  Loaded straight into the MFMA's register layout instead (16 rows x 64 bytes: a
+// quarter-wavefront touches 16 cache lines for 16 bytes each) a compute unit takes 39 B/ns whatever is in flight; in this
+// form 130-180 B/ns (L2-resident operands, one workgroup per compute unit).  Layouts as in gws_gemm256_core.h: rows of 128
+// bytes with chunk c of row r in slot c ^ ((r / 2) % 8); a [K x N] weight as 64 k-rows of 32 NT bytes, read with the
+// transposing LDS load, chunk c of row k in slot c ^ swizzle(k).
+template <int MT, int NT, int P, int D, bool W_NK>
+__global__ __launch_bounds__(64 * P) void gemm_stream_kernel(const GemmArgs g) {
+  using namespace stream;
+  constexpr int BM = 16 * MT, BN = 16 * NT;
+  constexpr int XS = BM * 64, WS = BN * 64, STG = XS + WS;          // elements of a stage
+  constexpr int QX = BM / 8, QW = BN / 8, LOADS = QX + QW;          // load instructions of a unit
+  static_assert(LOADS * (D - 1) <= 63, "the wait for a unit counts the loads behind it");
+  static_assert(W_NK || NT == 2 || NT == 4, "swizzle of the [K x N] stage");
+  constexpr int kRing = P * D * STG * 2, kRed = P * MT * NT * 256 * 4;
+  __shared__ __attribute__((aligned(1024))) char lds[kRing > kRed ? kRing : kRed];
+  const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint16_t* ring = (uint16_t*)lds + wave * (D * STG);
+  uint32_t m0, n0;
+  tile_origin(g, BM, BN, !W_NK && NT == 2, m0, n0);
+  uint32_t u0, u1;
+  unit_range(g.K, wave, P, u0, u1);
+
+  // lane offsets in bytes; rows and columns past the edge are read from the last ones and not stored
+  uint32_t xo[QX], wo[W_NK ? QW : 1];
+#pragma unroll
+  for (int q = 0; q < QX; ++q)
+    xo[q] = (umin(8u * q + (lane >> 3), g.M - 1 - m0) * g.ldx + ((lane & 7) ^ (4 * (q & 1) + (lane >> 4))) * 8) * 2;
+  if (W_NK) {
+#pragma unroll
+    for (int q = 0; q < QW; ++q)
+      wo[q] = (umin(8u * q + (lane >> 3), g.N - 1 - n0) * g.ldw + ((lane & 7) ^ (4 * (q & 1) + (lane >> 4))) * 8) * 2;
+  }
+  // [K x N]: an instruction covers RPI k-rows of 2 NT chunks
+  constexpr uint32_t CPR = 2 * NT, RPI = 64 / CPR;
+  auto swz = [](uint32_t k) { return NT == 2 ? 2 * ((k >> 3) & 1) : 4 * ((k >> 1) & 1) + 2 * ((k >> 3) & 1); };
+  const uint32_t wk = lane / CPR, ws = lane % CPR;
+  const GWS_GLOBAL char* xb = (const GWS_GLOBAL char*)(g.x + (size_t)m0 * g.ldx);
+  const GWS_GLOBAL char* wb = (const GWS_GLOBAL char*)(W_NK ? g.w + (size_t)n0 * g.ldw : g.w + n0);
+  const uint32_t last_chunk = (g.N - n0) / 8 - 1;
+  uint32_t wv[2];   // the swizzle depends on k % 16: the same for every instruction of 16 rows, two cases with 8 rows
+  if (!W_NK) {
+#pragma unroll
+    for (int v = 0; v < 2; ++v) wv[v] = (wk * g.ldw + umin(ws ^ swz(wk + RPI * v), last_chunk) * 8) * 2;
+  }
+  auto direct = [](const GWS_GLOBAL char* base, uint32_t voff, uint16_t* dst) {
+    const uint32_t a = (uint32_t)(uintptr_t)(GWS_LDS void*)dst;
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(a) : "m0", "memory");
+#pragma clang diagnostic pop
+  };
+  auto load = [&](uint32_t u, uint32_t slot) {
+    uint16_t* st = ring + slot * STG;
+    const uint32_t k0 = umin(64 * u, g.K - 64);   // the half unit at the end of K is fetched as the second half of a whole one
+#pragma unroll
+    for (int q = 0; q < QW; ++q) {
+      if (W_NK) direct(wb + (size_t)k0 * 2, wo[q], st + XS + q * 512);
+      else direct(wb + (size_t)(k0 + RPI * q) * g.ldw * 2, wv[RPI == 8 ? (q & 1) : 0], st + XS + q * 512);
+    }
+#pragma unroll
+    for (int q = 0; q < QX; ++q) direct(xb + (size_t)k0 * 2, xo[q], st + q * 512);
+  };
+
+  f32x4 acc[MT][NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const uint32_t n = u1 - u0;
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if ((uint32_t)d < n) load(u0 + d, d);
+  uint32_t slot = 0;
+  for (uint32_t i = 0; i < n; ++i) {
+    if (i + D <= n) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS * (D - 1)) : "memory");   // the unit has landed
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const uint16_t* xs = ring + slot * STG;
+    const uint16_t* wsg = xs + XS;
+    Frag8 fx[2][MT], fw[2][NT];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int r = 0; r < MT; ++r) fx[h][r].u = *(const u32x4*)(xs + (16 * r + li) * 64 + (((4 * h + grp) ^ ((li >> 1) & 7)) * 8));
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        if (W_NK) {
+          fw[h][j].u = *(const u32x4*)(wsg + (16 * j + li) * 64 + (((4 * h + grp) ^ ((li >> 1) & 7)) * 8));
+        } else {
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            const uint32_t k = 32 * h + 8 * grp + 4 * t + (li >> 2), c = 2 * j + ((li >> 1) & 1);
+            fw[h][j].h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((GWS_LDS i16x4*)(wsg + k * BN + (c ^ swz(k)) * 8 + (li & 1) * 4));
+          }
+        }
+      }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read: the stage can be filled again
+    __builtin_amdgcn_sched_barrier(0);
+    if (i + D < n) load(u0 + i + D, slot);
+    slot = slot + 1 == D ? 0 : slot + 1;
+    const bool half = 64 * (u0 + i) + 64 > g.K;   // only the second half of the stage belongs to this unit
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (h == 0 && half) continue;
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int r = 0; r < MT; ++r) acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fx[h][r].v, fw[h][j].v, acc[r][j], 0, 0, 0);
+    }
+  }
+  __syncthreads();   // the rings become the reduction's memory
+  reduce_store<MT, NT, P>(acc, (float*)lds, g, m0, n0);
+}
+
+// The sampling form: a wavefront loads one 32 x 32 block of the weight per step (two 16-byte groups per lane), samples
+// it in registers, turns it through its own 2.5 KiB of LDS and multiplies.  Bound by the vector ALU work of the
+// sampling (about 275 instructions a block), which every 16 MT rows of X repeat.
+template <int MT, int P, int FMT, bool W_NK>
+__global__ __launch_bounds__(64 * P) void gemm_stream_sample_kernel(const GemmArgs g) {
+  using namespace stream;
+  constexpr int LP = 40;   // row pitch of the staged block (elements)
+  constexpr int kRed = P * MT * 2 * 256 * 4, kBlk = P * 32 * LP * 2;
+  __shared__ __attribute__((aligned(16))) char lds[kRed > kBlk ? kRed : kBlk];
+  const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint16_t* blk = (uint16_t*)lds + wave * 32 * LP;
+  uint32_t m0, n0, b0, b1;
+  tile_origin(g, 16 * MT, 32, !W_NK, m0, n0);
+  unit_range(g.K, wave, P, b0, b1);
+  b0 *= 2;
+  b1 = umin(2 * b1, g.K >> 5);
+
+  uint32_t xo[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) xo[i] = (umin(16u * i + li, g.M - 1 - m0) * g.ldx + 8 * grp) * 2;
+  const GWS_GLOBAL char* xb = (const GWS_GLOBAL char*)(g.x + (size_t)m0 * g.ldx);
+  // group i of a lane: storage row lane / 4 + 16 i, columns 8 (lane % 4) .. + 7 of the block
+  const uint32_t q = lane & 3, r = lane >> 2;
+  const uint32_t wo = (r * g.ldw + 8 * q) * 2;
+  const GWS_GLOBAL char* wb = (const GWS_GLOBAL char*)(W_NK ? g.w + (size_t)n0 * g.ldw : g.w + n0);
+  const size_t wstep = W_NK ? 64 : (size_t)g.ldw * 64;   // bytes from a block to the next along K
+  const uint32_t nbc = (W_NK ? g.K : g.N) >> 5;
+  auto block_index = [&](uint32_t b) { return W_NK ? (size_t)(n0 >> 5) * nbc + b : (size_t)b * nbc + (n0 >> 5); };
+
+  f32x4 acc[MT][2];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) acc[i][0] = acc[i][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  u32x4 nxt[2];
+  float bt_nxt = 0.0f;
+  auto load = [&](uint32_t b) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      nxt[i] = *(const GWS_GLOBAL u32x4*)(wb + b * wstep + (size_t)(16 * i) * g.ldw * 2 + wo);
+    bt_nxt = global_ptr<float>(g.bt)[block_index(b)];
+  };
+  if (b0 < b1) load(b0);
+  for (uint32_t b = b0; b < b1; ++b) {
+    u32x4 w[2] = {nxt[0], nxt[1]};
+    const float bt = bt_nxt;
+    load(umin(b + 1, b1 - 1));
+    Frag8 x[MT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) x[i].u = *(const GWS_GLOBAL u32x4*)(xb + (size_t)b * 64 + xo[i]);
+    // Eq. 3 + cast
+    uint32_t m = absmax_pk(w[1], absmax_pk(w[0], 0));
+    m = max(m & 0xFFFFu, m >> 16);
+    m = block_max_u32(m);
+    const uint32_t a16 = max(m, (uint32_t)__shfl_xor((int)m, 4));   // the block is the whole wavefront's here
+    BlockScale s = block_scale(a16, bt);
+    if (FMT == 1) cast_constants<8, -6>(a16, s);
+    if (FMT == 2) cast_constants<4, -2>(a16, s);
+    const bool writer = m0 == 0 && g.w_hat != nullptr;
+    if (writer && lane == 0) g.scale[block_index(b)] = s.s32;
+    const bool hw = (FMT == 1) && s.hw_safe;   // uniform: the wavefront holds one block
+    const uint32_t row0 = W_NK ? n0 : b * 32, col0 = W_NK ? b * 32 : n0;   // the block's storage origin
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const uint32_t srow = row0 + r + 16 * i, scol = col0 + 8 * q;
+      const Noise n = group_noise(g.cg0 + (scol >> 3), g.row0 + srow, g.step_lo, g.step_hi, g.seed_lo, g.seed_hi);
+      const u32x4 v = hw ? sample_group<FMT>(w[i], n, s, true) : sample_group<FMT>(w[i], n, s, false);
+      if (writer) *(u32x4*)(g.w_hat + (size_t)srow * g.ldw + scol) = v;
+      *(u32x4*)(blk + (r + 16 * i) * LP + 8 * q) = v;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wavefront's own writes have landed
+    __builtin_amdgcn_wave_barrier();
+    Frag8 f[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      if (W_NK) {
+        f[j].u = *(const u32x4*)(blk + (16 * j + li) * LP + 8 * grp);
+      } else {   // transposing read: lanes 4 t .. 4 t + 3 of 16 point at 16 outputs of row k0 + t
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          f[j].h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+              (GWS_LDS i16x4*)(blk + (8 * grp + 4 * h + (li >> 2)) * LP + 16 * j + 4 * (li & 3)));
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[i].v, f[j].v, acc[i][j], 0, 0, 0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the reads are done before the block is overwritten
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();   // the staging blocks become the reduction's memory
+  reduce_store<MT, 2, P>(acc, (float*)lds, g, m0, n0);
+}
+
+// ---------------------------------------------------------------------------
+// Which tile and how many parts of K.  The estimate (us) is a launch plus, per round of workgroups (one per compute unit:
+// the rings fill its LDS), a fixed part and the bytes of the tile's operands at the rate a compute unit takes them.
+// Measured on MI355X (weights taken in turn from four copies), us by tile (rows x columns, parts of K):
+//   M x K -> N            16x16,8 16x32,8 32x32,8 32x64,4 64x64,4   before
+//   4 x 5632 -> 2048 NK     6.0     7.2                               103
+//   16 x 2048 -> 5632 KN    -       7.6                                60
+//   64 x 5632 -> 2048 NK                    9.8    13.8    18.3       105
+//   64 x 2048 -> 5632 KN                   12.0     8.9    11.1        60
+//   256 x 2048 -> 5632 KN                  29.4    20.0    18.2        40
+//   1000 x 2304 -> 768 KN                  21.6    15.1    11.3        66
+// ---------------------------------------------------------------------------
+StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk) {
+  StreamPlan best = {0, 0, 0, 1e30};
+  if (K < 64) return best;
+  const int cus = compute_units() > 0 ? compute_units() : 256;
+  // bytes per ns: eight wavefronts keep twice the loads in flight that four do
+  static const struct { int mt, nt, p; double rate; } tiles[] = {{1, 1, 8, 130.0}, {1, 2, 8, 130.0}, {2, 2, 8, 130.0}, {2, 4, 4, 100.0}, {4, 4, 4, 100.0}};
+  for (const auto& t : tiles) {
+    if (t.mt == 1 && M > 16) continue;
+    if (t.nt == 1 && !w_is_nk) continue;   // 32 bytes of a row of a [K x N] weight: a quarter of a cache line
+    const uint64_t wgs = ((M + 16 * t.mt - 1) / (16 * t.mt)) * ((N + 16 * t.nt - 1) / (16 * t.nt));
+    const double rounds = (double)((wgs + cus - 1) / cus);
+    const double us = 3.0 + rounds * (1.5 + (double)K * 2 * 16 * (t.mt + t.nt) / t.rate * 1e-3);
+    if (wgs < 0x7FFFFFFFull && us < best.us) best = {t.mt, t.nt, t.p, us};
+  }
+  return best;
+}
+
+bool stream_applicable(const GemmArgs& g) {
+  return g.K >= 64 && g.K % 32 == 0 && g.N % 32 == 0 && g.M > 0 && g.N > 0 && g.ldx < stream::kMaxLd && g.ldw < stream::kMaxLd;
+}
+
+template <int MT, int NT, int P, int D>
+static void launch_plain(const GemmArgs& g, int w_is_nk, hipStream_t s) {
+  const dim3 grid(((g.M + 16 * MT - 1) / (16 * MT)) * ((g.N + 16 * NT - 1) / (16 * NT)));
+  if (w_is_nk) {
+    hipLaunchKernelGGL((gemm_stream_kernel<MT, NT, P, D, true>), grid, dim3(64 * P), 0, s, g);
+  } else {
+    if constexpr (NT >= 2) hipLaunchKernelGGL((gemm_stream_kernel<MT, NT, P, D, false>), grid, dim3(64 * P), 0, s, g);
+  }
+}
+
+int launch_gemm_stream(const GemmArgs& g, int w_is_nk, const StreamPlan& p, hipStream_t s) {
+  if (p.mt == 1 && p.nt == 1) launch_plain<1, 1, 8, 4>(g, w_is_nk, s);
+  else if (p.mt == 1) launch_plain<1, 2, 8, 2>(g, w_is_nk, s);
+  else if (p.mt == 2 && p.nt == 2) launch_plain<2, 2, 8, 2>(g, w_is_nk, s);
+  else if (p.mt == 2) launch_plain<2, 4, 4, 3>(g, w_is_nk, s);
+  else launch_plain<4, 4, 4, 2>(g, w_is_nk, s);
+  return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
+}
+
+template <int MT, int P, int FMT>
+static void launch_sampled(const GemmArgs& g, int w_is_nk, hipStream_t s) {
+  const dim3 grid(((g.M + 16 * MT - 1) / (16 * MT)) * (g.N / 32));
+  if (w_is_nk) hipLaunchKernelGGL((gemm_stream_sample_kernel<MT, P, FMT, true>), grid, dim3(64 * P), 0, s, g);
+  else hipLaunchKernelGGL((gemm_stream_sample_kernel<MT, P, FMT, false>), grid, dim3(64 * P), 0, s, g);
+}
+
+template <int FMT>
+static void launch_sampled_fmt(const GemmArgs& g, int w_is_nk, int p, hipStream_t s) {
+  if (p == 4) launch_sampled<4, 4, FMT>(g, w_is_nk, s);
+  else if (g.M <= 16) launch_sampled<1, 8, FMT>(g, w_is_nk, s);
+  else if (g.M <= 32) launch_sampled<2, 8, FMT>(g, w_is_nk, s);
+  else launch_sampled<4, 8, FMT>(g, w_is_nk, s);
+}
+
+// The same parts of K as the plain kernel (p), whatever the tile: the sums are the same bits.
+int launch_gemm_stream_sample(const GemmArgs& g, int w_is_nk, int fmt, int p, hipStream_t s) {
+  if ((uint64_t)((g.M + 15) / 16) * (g.N / 32) >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
+  switch (fmt) {
+    case GWS_FMT_BF16: launch_sampled_fmt<0>(g, w_is_nk, p, s); break;
+    case GWS_FMT_FP8_E4M3: launch_sampled_fmt<1>(g, w_is_nk, p, s); break;
+    case GWS_FMT_FP6_E3M2: launch_sampled_fmt<2>(g, w_is_nk, p, s); break;
+    default: return GWS_ERR_FORMAT;
+  }
+  return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
+}
+
+}  // namespace gws

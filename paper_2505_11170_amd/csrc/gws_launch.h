@@ -85,6 +85,18 @@ struct GemmArgs {
 // fused: 0 = plain GEMM on g.w; kFusedInOperand = sampling in the weight operand load of every tile
 constexpr int kFusedInOperand = 2;
 int launch_gemm(const GemmArgs& g, int w_is_nk, int fused, int fmt, hipStream_t stream);
+// few rows of X or few tiles (gws_gemm_stream.hip): the tile in units of 16 rows and 16 columns, the parts of K and the
+// estimated time; p == 0: the shape is not one for it
+struct StreamPlan {
+  int mt, nt, p;
+  double us;
+};
+StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk);
+bool stream_applicable(const GemmArgs& g);
+int launch_gemm_stream(const GemmArgs& g, int w_is_nk, const StreamPlan& p, hipStream_t stream);
+int launch_gemm_stream_sample(const GemmArgs& g, int w_is_nk, int fmt, int p, hipStream_t stream);
+enum class GemmRoute { kStream, kLarge, kSmall };
+GemmRoute gemm_route(const GemmArgs& g, int w_is_nk, StreamPlan& plan);
 bool gemm256_applicable(const GemmArgs& g);
 int launch_gemm256(const GemmArgs& g, int w_is_nk, hipStream_t stream);
 // Weights whose forward sampling rides in a GEMM's launch: descriptors as the forward pass fills them, with

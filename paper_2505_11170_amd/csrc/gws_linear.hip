@@ -11,6 +11,8 @@
 // one block (two 16-byte groups per lane), reduces max|w| across its 64 lanes,
 // samples in registers and writes w_hat to LDS.  Global loads for step k+1 are
 // issued before the MFMAs of step k.
+#include <math.h>
+
 #include "gws_launch.h"
 
 namespace gws {
@@ -181,12 +183,32 @@ static int launch_layout(const GemmArgs& g, int w_is_nk, dim3 grid, hipStream_t 
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
 
+// Which kernel multiplies.  Chosen by the sizes alone, the same for the plain and the sampling form and whether or not a
+// weight rides along, so that the sums over K run in the same order in all of them.  Estimates in us, fitted to MI355X
+// timings: the 256-tile kernel takes about 1.35 per 64 k and round of tiles (57 for 48 tiles x 48, 27 for 192 x 12, 128
+// for 256 x 88), the 128-tile kernel 0.65 per 32 k and round.
+GemmRoute gemm_route(const GemmArgs& g, int w_is_nk, StreamPlan& plan) {
+  const bool large_fits = gemm256_applicable(g);
+  if (stream_applicable(g)) {
+    plan = stream_plan(g.M, g.N, g.K, w_is_nk != 0);
+    const double tiles = (double)((g.M + BM - 1) / BM) * (double)((g.N + BN - 1) / BN);
+    const double cus = compute_units() > 0 ? compute_units() : 256;
+    const double other = large_fits ? 6.0 + ceil(tiles / 4 / cus) * (3.0 + 1.35 * g.K / 64) : 3.0 + ceil(tiles / cus) * (2.0 + 0.65 * g.K / 32);
+    if (plan.p > 0 && plan.us < other) return GemmRoute::kStream;
+  }
+  return large_fits ? GemmRoute::kLarge : GemmRoute::kSmall;
+}
+
 int launch_gemm(const GemmArgs& g, int w_is_nk, int fused, int fmt, hipStream_t stream) {
   const uint64_t tiles = (uint64_t)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   if (tiles == 0) return GWS_OK;
   if (tiles >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
   const dim3 grid((uint32_t)tiles);
-  if (!fused && gemm256_applicable(g)) return launch_gemm256(g, w_is_nk, stream);
+  StreamPlan plan;
+  const GemmRoute route = gemm_route(g, w_is_nk, plan);
+  if (route == GemmRoute::kStream)
+    return fused ? launch_gemm_stream_sample(g, w_is_nk, fmt, plan.p, stream) : launch_gemm_stream(g, w_is_nk, plan, stream);
+  if (!fused && route == GemmRoute::kLarge) return launch_gemm256(g, w_is_nk, stream);
   if (!fused) return launch_layout<false, 0>(g, w_is_nk, grid, stream);
   switch (fmt) {
     case GWS_FMT_BF16: return launch_layout<true, 0>(g, w_is_nk, grid, stream);
