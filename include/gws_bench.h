@@ -48,7 +48,7 @@ int gws_gemm_bf16_ride_probe(const void* x, int64_t M, int64_t K, int64_t ldx, c
                              int extra_workgroups, int rider, void* stream);
 
 /* How many of the weights next[0 .. n_next) gws_gemm_bf16_sample_next_n would let ride in the launch of an
- * M x K x N GEMM on the current device (a prefix of the list); host function, launches nothing.            */
+ * M x K x N GEMM ([K x N] weight) on the current device (a prefix of the list); host function, launches nothing.            */
 int gws_ride_plan(int64_t M, int64_t K, int64_t N, const gws_tensor* next, int n_next);
 
 #ifdef __cplusplus

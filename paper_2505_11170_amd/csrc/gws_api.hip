@@ -601,15 +601,17 @@ int gws_gemm_bf16(const void* x, int64_t M, int64_t K, int64_t ldx, const void* 
 // Ride along when the 256-tile GEMM leaves compute units without a tile in its last round and the sampling fits
 // beside that round.  Measured on MI355X: a riding wavefront (one per SIMD, the GEMM's register allocation) takes
 // about 1.8 us per 32 x 64 tile in ride_tiles and 2.1 us in sample_tiles; a GEMM tile about 1.5 us per K-step of 64.
-static int plan_ride(const GemmArgs& g, bool gemm_empty, int64_t K, const gws_tensor* next, int n_next, int force_extra,
+static int plan_ride(const GemmArgs& g, int w_is_nk, bool gemm_empty, int64_t K, const gws_tensor* next, int n_next, int force_extra,
                      int rider, RideList& r, uint32_t& idle, int& use_rider) {
   memset(&r, 0, sizeof r);
   idle = 0;
   use_rider = 1;
-  // few tiles are left to the kernel that splits K (the layout does not matter to the route of whole 256-row tiles)
-  StreamPlan plan;
+  // whole tiles only; not where the GEMM splits K (another order of its sums than the large tile's: Y would not be the same
+  // bits), and where the middle tile is its kernel only if the sampling's own launch costs more than that tile saves
+  RoutePlan plan;
+  const GemmRoute route = gemm_empty ? GemmRoute::kSmall : gemm_route(g, w_is_nk, plan);
   const bool gemm_rides = force_extra >= 0 ? (gemm_empty || gemm256_applicable(g))
-                                           : (!gemm_empty && gemm_route(g, 0, plan) == GemmRoute::kLarge);
+                                           : gemm256_applicable(g) && (route == GemmRoute::kLarge || route == GemmRoute::kMiddle);
   if (!gemm_rides) return 0;
   const int cus = compute_units();
   const uint64_t tiles = gemm_empty ? 0 : (uint64_t)(g.M / 256) * (uint64_t)(g.N / 256);
@@ -643,6 +645,12 @@ static int plan_ride(const GemmArgs& g, bool gemm_empty, int64_t K, const gws_te
       use_rider = 0;
       break;
     }
+  }
+  if (force_extra < 0 && route == GemmRoute::kMiddle) {
+    // the sampling kernel alone: about 3 us and 4 bytes an element at 5 TB/s (one launch in any case if some do not ride)
+    double elements = 0.0;
+    for (int i = 0; i < n_riding; ++i) elements += (double)next[i].rows * (double)next[i].cols;
+    if (plan.large_us - (elements * 4.0 / 5e6 + (n_riding == n_next ? 3.0 : 0.0)) > plan.middle_us) n_riding = 0;
   }
   for (int j = n_riding; j <= kMaxRide; ++j) r.begin[j] = begin;
   r.n = (uint32_t)n_riding;
@@ -693,7 +701,7 @@ static int gemm_sample_next(const void* x, int64_t M, int64_t K, int64_t ldx, co
   RideList r;
   uint32_t idle = 0;
   int use_rider = 1;
-  const int n_riding = plan_ride(g, gemm_empty, K, next, n_next, force_extra, rider, r, idle, use_rider);   // the first n_riding ride
+  const int n_riding = plan_ride(g, w_is_nk, gemm_empty, K, next, n_next, force_extra, rider, r, idle, use_rider);   // the first n_riding ride
   if (n_riding > 0) {
     int rc = launch_gemm256_ride(g, w_is_nk, r, fmt, step, idle, use_rider, (hipStream_t)stream);
     if (rc != GWS_OK) return rc;
@@ -726,7 +734,7 @@ int gws_ride_plan(int64_t M, int64_t K, int64_t N, const gws_tensor* next, int n
   RideList r;
   uint32_t idle = 0;
   int use_rider = 1;
-  return plan_ride(g, false, K, next, n_next, -1, -1, r, idle, use_rider);
+  return plan_ride(g, 0, false, K, next, n_next, -1, -1, r, idle, use_rider);
 }
 
 int gws_gemm_bf16_ride_probe(const void* x, int64_t M, int64_t K, int64_t ldx, const void* w, int64_t N, int64_t ldw,

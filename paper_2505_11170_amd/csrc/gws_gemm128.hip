@@ -1,0 +1,166 @@
+// Middle-tile BF16 MFMA GEMM for gfx950: Y[M x N] = X[M x K] * W (W stored [K x N] or [N x K]), any M, N and K of whole
+// 32s.  For products with too few 256 x 256 tiles to fill the chip, or with edges that the large tile would pad.
+//
+// Workgroup = 2 x 2 wavefronts, tile 128 x 128, K-steps of 64; a wavefront owns 64 x 64 of the output as 4 x 4
+// v_mfma_f32_16x16x32_bf16 tiles.  Both operand tiles (16 KiB each) go global -> LDS directly into a ring of four stages, in
+// the layouts of gws_gemm256_core.h, three K-steps ahead; one barrier a K-step, between its two 32-deep halves: the second
+// half's fragments are read under the first half's MFMAs, the next step's first ones under the second half's.
+// What bounds it: the operands' bytes (32 KiB per 64 k and compute unit) and the LDS reads, each about as long as the MFMAs.
+#include "gws_gemm256_core.h"
+#include "gws_launch.h"
+
+namespace gws {
+
+namespace g128 {
+constexpr int T = 128, TK = 64, OP = T * TK, STG = 2 * OP, D = 4;   // elements of an operand tile, of a stage; stages
+constexpr int PC = 64 + 8;                                          // pitch of a wavefront's staged rows (elements)
+constexpr uint32_t kMaxLd = 1u << 24;                               // 32-bit lane offsets: 127 rows x 2 bytes
+__device__ __forceinline__ uint32_t umin(uint32_t a, uint32_t b) { return a < b ? a : b; }
+}  // namespace g128
+
+template <bool W_NK>
+__global__ __launch_bounds__(256) void gemm128_kernel(const GemmArgs g) {
+  using namespace g128;
+  __shared__ __attribute__((aligned(1024))) uint16_t lds[D * STG];
+  const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = wave >> 1, wn = wave & 1;
+  uint32_t tile_m, tile_n;
+  tile_of(blockIdx.x, (g.M + T - 1) / T, (g.N + T - 1) / T, tile_m, tile_n);
+  const uint32_t m0 = tile_m * T, n0 = tile_n * T;
+
+  // a wavefront's four load instructions of an operand tile; rows and columns past the edge are read from the last ones
+  uint32_t xo[4], wo[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t row = 32 * wave + 8 * q + (lane >> 3), chunk = (lane & 7) ^ (4 * (q & 1) + (lane >> 4));
+    xo[q] = (umin(row, g.M - 1 - m0) * g.ldx + chunk * 8) * 2;
+    if (W_NK) wo[q] = (umin(row, g.N - 1 - n0) * g.ldw + chunk * 8) * 2;
+    else wo[q] = ((lane >> 4) * g.ldw + umin((lane & 15) ^ ((lane >> 4) << 2) ^ ((q >> 1) << 1), (g.N - n0) / 8 - 1) * 8) * 2;
+  }
+  const GWS_GLOBAL char* xb = (const GWS_GLOBAL char*)(g.x + (size_t)m0 * g.ldx);
+  const GWS_GLOBAL char* wb = (const GWS_GLOBAL char*)(W_NK ? g.w + (size_t)n0 * g.ldw : g.w + n0);
+  auto direct = [](const GWS_GLOBAL char* base, uint32_t voff, uint16_t* dst) {
+    const uint32_t a = (uint32_t)(uintptr_t)(GWS_LDS void*)dst;
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(a) : "m0", "memory");
+#pragma clang diagnostic pop
+  };
+  // load n (0 .. 7) of a K-step: even n -> X, odd n -> W
+  auto load_n = [&](uint32_t kt, int n) {
+    uint16_t* st = lds + (kt % D) * STG + wave * 2048;
+    const uint32_t k0 = umin(TK * kt, g.K - TK);   // the half step at the end of K is fetched as the second half of a whole one
+    const int q = n >> 1;
+    if (!(n & 1)) direct(xb + (size_t)k0 * 2, xo[q], st + q * 512);
+    else direct(W_NK ? wb + (size_t)k0 * 2 : wb + (size_t)(k0 + 16 * wave + 4 * q) * g.ldw * 2, wo[q], st + OP + q * 512);
+  };
+  Frag8 fx[2][4], fw[2][4];
+  // read fragments of half h, step n of NR, in the order the MFMAs need them: X 0, W 0 .. 3, X 1 .. 3
+  constexpr int RW = W_NK ? 1 : 2, NR = 4 + 4 * RW;
+  auto read_n = [&](int h, uint32_t kt, int n) {
+    const uint16_t* xs = lds + (kt % D) * STG;
+    const uint16_t* ws = xs + OP;
+    const uint32_t sl = ((4 * h + grp) ^ ((li >> 1) & 7)) * 8;
+    if (n == 0 || n > 4 * RW) {
+      const int i = n == 0 ? 0 : n - 4 * RW;
+      fx[h][i].u = *(const u32x4*)(xs + (64 * wm + 16 * i + li) * 64 + sl);
+    } else if (W_NK) {
+      fw[h][n - 1].u = *(const u32x4*)(ws + (64 * wn + 16 * (n - 1) + li) * 64 + sl);
+    } else {
+      const int j = (n - 1) >> 1, t = (n - 1) & 1;
+      const uint32_t k = 32 * h + 8 * grp + 4 * t + (li >> 2), c = 8 * wn + 2 * j + ((li >> 1) & 1);
+      fw[h][j].h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+          (GWS_LDS i16x4*)(ws + k * 128 + (c ^ ((li >> 2) << 2) ^ ((grp & 1) << 1)) * 8 + (li & 1) * 4));
+    }
+  };
+  f32x4 acc[4][4];   // row 16 i + lane % 16, columns 16 j + 4 (lane / 16) .. + 3 of the wavefront's part
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  auto mfma_n = [&](int h, int n) {
+    const int i = n >> 2, j = n & 3;
+    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[h][j].v, fx[h][i].v, acc[i][j], 0, 0, 0);
+  };
+  const uint32_t nk = (g.K + TK - 1) / TK;
+#pragma unroll
+  for (int s = 0; s < D; ++s)
+    if ((uint32_t)s < nk) {
+#pragma unroll
+      for (int n = 0; n < 8; ++n) load_n(s, n);
+    }
+  if (nk >= D) asm volatile("s_waitcnt vmcnt(24)\n\ts_barrier" ::: "memory");
+  else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+  for (int n = 0; n < NR; ++n) read_n(0, 0, n);
+  // The order is written out and pinned: a read behind each of the first MFMAs of a half, a load of the step four ahead
+  // behind every second MFMA of the second half (into the stage that the barrier has just released).
+  auto first_half = [&](uint32_t kt) {
+#pragma unroll
+    for (int n = 0; n < 16; ++n) {
+      mfma_n(0, n);
+      __builtin_amdgcn_sched_barrier(0);
+      if (n < NR) read_n(1, kt, n);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto second_half = [&](uint32_t kt, bool more) {
+#pragma unroll
+    for (int n = 0; n < 16; ++n) {
+      mfma_n(1, n);
+      __builtin_amdgcn_sched_barrier(0);
+      if (n < NR) read_n(0, kt + 1, n);
+      if (more && (n & 1)) load_n(kt + D, n >> 1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  uint32_t kt = 0;
+  for (; kt + D < nk; ++kt) {
+    first_half(kt);
+    // this stage is read; the next step has landed when all but the two steps behind it have
+    asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    second_half(kt, true);
+  }
+  for (; kt < nk; ++kt) {   // everything is on its way: the reads past the last step fetch a stage that nobody multiplies
+    if (TK * kt + TK > g.K) {
+      // half a step at the end of K: the stage's first half belongs to the step before
+#pragma unroll
+      for (int i = 0; i < 4; ++i) fx[0][i].u = fw[0][i].u = u32x4{0, 0, 0, 0};
+    }
+    first_half(kt);
+    if (kt + D == nk) asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    second_half(kt, false);
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the ring is read
+
+  // out through LDS, 16 bytes a lane
+  uint16_t* cs = lds + wave * (64 * PC);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      *(u32x2*)(cs + (16 * i + li) * PC + 16 * j + 4 * grp) = u32x2{pack_bf16_rne(acc[i][j][0], acc[i][j][1]), pack_bf16_rne(acc[i][j][2], acc[i][j][3])};
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wavefront's LDS writes have landed
+  __builtin_amdgcn_wave_barrier();
+  const uint32_t row0 = m0 + 64 * wm + (lane >> 3), col = n0 + 64 * wn + 8 * (lane & 7);
+  if (col < g.N) {
+#pragma unroll
+    for (int it = 0; it < 8; ++it)
+      if (row0 + 8 * it < g.M) *(u32x4*)(g.y + (size_t)(row0 + 8 * it) * g.ldy + col) = *(const u32x4*)(cs + ((lane >> 3) + 8 * it) * PC + 8 * (lane & 7));
+  }
+}
+
+bool gemm128_applicable(const GemmArgs& g) {
+  return g.M > 0 && g.N > 0 && g.N % 32 == 0 && g.K % 32 == 0 && g.K >= 64 && g.ldx < g128::kMaxLd && g.ldw < g128::kMaxLd;
+}
+
+int launch_gemm128(const GemmArgs& g, int w_is_nk, hipStream_t stream) {
+  const uint64_t tiles = (uint64_t)((g.M + g128::T - 1) / g128::T) * ((g.N + g128::T - 1) / g128::T);
+  if (tiles >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
+  if (w_is_nk) hipLaunchKernelGGL(gemm128_kernel<true>, dim3((uint32_t)tiles), dim3(256), 0, stream, g);
+  else hipLaunchKernelGGL(gemm128_kernel<false>, dim3((uint32_t)tiles), dim3(256), 0, stream, g);
+  return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
+}
+
+}  // namespace gws

@@ -27,6 +27,17 @@ __global__ __launch_bounds__(256, 1) void gemm256_kernel(const GemmArgs g) {
   gemm256_tile<W_NK>(g, g.w, blockIdx.x);
 }
 
+// The same for any M, N of whole 32s and K of whole 32s: edge tiles do a whole tile's work on repeated rows and columns and
+// store what exists.
+template <bool W_NK>
+__global__ __launch_bounds__(256, 1) void gemm256_edge_kernel(const GemmArgs g) {
+  using namespace g256;
+  uint32_t tile_m, tile_n;
+  tile_of(blockIdx.x, (g.M + TM - 1) / TM, (g.N + TN - 1) / TN, tile_m, tile_n);
+  const uint32_t m0 = tile_m * TM, n0 = tile_n * TN, rows = g.M - m0 < TM ? g.M - m0 : TM, cols = g.N - n0 < TN ? g.N - n0 : TN;
+  gemm256_core<false, !W_NK, true>(g.x, g.ldx, g.w, g.ldw, g.y, g.ldy, (g.K + TK - 1) / TK, m0, n0, NoHook{}, rows, cols, g.K);
+}
+
 // The stored weight seen as the forward kernel sees it: 32-row x 256-column
 // workgroup tiles of four wavefront tiles (32 x 64, two blocks each).  Wavefront
 // tile t covers block row t / (cols/64), columns 64 * (t % (cols/64)).  A batch of
@@ -213,6 +224,18 @@ int compute_units() {
 bool gemm256_applicable(const GemmArgs& g) {
   return g.M % g256::TM == 0 && g.N % g256::TN == 0 && g.K % g256::TK == 0 && g.M > 0 && g.N > 0 && g.K > 0 &&
          g.ldx < g256::kMaxLd && g.ldw < g256::kMaxLd;
+}
+
+bool gemm256_edge_applicable(const GemmArgs& g) {
+  return g.M > 0 && g.N > 0 && g.N % 32 == 0 && g.K >= g256::TK && g.K % 32 == 0 && g.ldx < g256::kMaxLdEdge && g.ldw < g256::kMaxLdEdge;
+}
+
+int launch_gemm256_edge(const GemmArgs& g, int w_is_nk, hipStream_t stream) {
+  const uint64_t tiles = (uint64_t)((g.M + g256::TM - 1) / g256::TM) * ((g.N + g256::TN - 1) / g256::TN);
+  if (tiles >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
+  if (w_is_nk) hipLaunchKernelGGL(gemm256_edge_kernel<true>, dim3((uint32_t)tiles), dim3(256), 0, stream, g);
+  else hipLaunchKernelGGL(gemm256_edge_kernel<false>, dim3((uint32_t)tiles), dim3(256), 0, stream, g);
+  return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
 
 int launch_gemm256(const GemmArgs& g, int w_is_nk, hipStream_t stream) {

@@ -62,6 +62,7 @@ constexpr int TM = 256, TN = 256, TK = 64;
 constexpr int STAGE = 256 * 64;   // elements of one operand tile (32 KiB), either layout
 constexpr int PC = 128 + 8;       // epilogue pitch of a wavefront's staging rows (elements)
 constexpr uint32_t kMaxLd = 1u << 28;   // leading dimensions (elements) the 32-bit lane offsets of the loads reach: 7 rows x 2 bytes
+constexpr uint32_t kMaxLdEdge = 1u << 23;   // the same with edges: 255 rows x 2 bytes
 static_assert(64 * PC <= STAGE, "half a wavefront tile is staged in one stage array");
 }  // namespace g256
 
@@ -91,9 +92,10 @@ __device__ __forceinline__ void tile_of(uint32_t L, uint32_t mt, uint32_t nt, ui
 // then 16-byte groups to yw[(64 h + row) * ldy + col], each also handed to hook(it, row, col, v) with it = 16 h + the
 // 4-row step, row and col relative to the wavefront's part, lane = (row % 4, col / 8).
 // a4[i2][j][e]: row 64 h + 16 i2 + lane % 16, column 16 j + 4 (lane / 16) + e.
-template <class Hook>
+// EDGE: only rows and columns below `rows` and `cols` (of the wavefront's part) exist.
+template <bool EDGE = false, class Hook>
 __device__ __forceinline__ void epilogue_bf16_half(const f32x4 (&a4)[4][8], int h, uint16_t* cs, uint16_t* yw, uint32_t ldy,
-                                                   uint32_t lane, Hook&& hook) {
+                                                   uint32_t lane, Hook&& hook, int rows = 0, int cols = 0) {
   using namespace g256;
   const uint32_t li = lane & 15, grp = lane >> 4, lr = lane >> 4, c = (lane & 15) * 8;
 #pragma unroll
@@ -112,7 +114,7 @@ __device__ __forceinline__ void epilogue_bf16_half(const f32x4 (&a4)[4][8], int 
   for (int it = 0; it < 16; ++it) {
     const uint32_t row = it * 4 + lr;
     const u32x4 v = *(const u32x4*)(cs + row * PC + c);
-    *(u32x4*)(yw + (size_t)(64 * h + row) * ldy + c) = v;
+    if (!EDGE || ((int)(64 * h + row) < rows && (int)c < cols)) *(u32x4*)(yw + (size_t)(64 * h + row) * ldy + c) = v;
     hook(16 * h + it, 64 * h + row, c, v);
   }
   __builtin_amdgcn_s_waitcnt(0xc07f);  // the reads are done before the staging area is written again
@@ -128,10 +130,13 @@ __device__ __forceinline__ void epilogue_bf16_half(const f32x4 (&a4)[4][8], int 
 //   wavefront's own from here on (a stage array nobody reads any more).
 // Requires nk >= 1 and all 256 threads; ends with every wavefront past its last LDS access
 // except its own staging area (callers that loop over tiles put a barrier between tiles).
-template <bool A_OC, bool B_OC, class Finish>
+// EDGE: of the tile only `a_out` rows and `b_out` columns exist (columns a multiple of 32; the operands' last ones are read
+// in the place of the others), and K (>= 64, a multiple of 32) need not be a multiple of 64; nk counts the half step.
+template <bool A_OC, bool B_OC, bool EDGE = false, class Finish>
 __device__ __forceinline__ void gemm256_accumulate(const uint16_t* __restrict__ a, uint32_t lda,
                                                    const uint16_t* __restrict__ b, uint32_t ldb, uint32_t nk, uint32_t m0,
-                                                   uint32_t n0, Finish&& finish) {
+                                                   uint32_t n0, Finish&& finish, uint32_t a_out = 0, uint32_t b_out = 0,
+                                                   uint32_t K = 0) {
   using namespace g256;
   __shared__ __attribute__((aligned(16))) uint16_t A0[STAGE];
   __shared__ __attribute__((aligned(16))) uint16_t A1[STAGE];
@@ -147,13 +152,20 @@ __device__ __forceinline__ void gemm256_accumulate(const uint16_t* __restrict__ 
   // 1 KiB at (wave * 8 + q) * 1 KiB of the stage ----
   struct Src {
     const GWS_GLOBAL char* base;
-    uint32_t voff[4];   // per-lane byte offset; which one an instruction q uses: vsel(oc, q)
+    uint32_t voff[EDGE ? 8 : 4];   // per-lane byte offset; which one an instruction q uses: see load1
     uint32_t ld;
   };
-  auto make_src = [&](bool oc, const uint16_t* p, uint32_t ld, uint32_t o0) {
+  auto make_src = [&](bool oc, const uint16_t* p, uint32_t ld, uint32_t o0, uint32_t out) {
     Src s;
     s.ld = ld;
-    if (!oc) {  // rows 64 wave + 8 q + lane/8; slot lane%8 holds chunk slot ^ ((row / 2) % 8) = slot ^ (4 (q%2) + lane/16)
+    if (EDGE && !oc) {   // as below, with the row's offset in the lane offset: rows past the last one read that one
+      s.base = (const GWS_GLOBAL char*)(p + (size_t)o0 * ld);
+#pragma unroll
+      for (int q = 0; q < (EDGE ? 8 : 4); ++q) {
+        const uint32_t row = 64 * wave + 8 * q + (lane >> 3);
+        s.voff[q] = ((row < out ? row : out - 1) * ld + (((lane & 7) ^ (4 * (q & 1) + (lane >> 4))) * 8)) * 2;
+      }
+    } else if (!oc) {  // rows 64 wave + 8 q + lane/8; slot lane%8 holds chunk slot ^ ((row / 2) % 8) = slot ^ (4 (q%2) + lane/16)
       s.base = (const GWS_GLOBAL char*)(p + (size_t)(o0 + 64 * wave) * ld);
       s.voff[0] = s.voff[2] = ((lane >> 3) * ld + (((lane & 7) ^ (0 + (lane >> 4))) * 8)) * 2;
       s.voff[1] = s.voff[3] = ((lane >> 3) * ld + (((lane & 7) ^ (4 + (lane >> 4))) * 8)) * 2;
@@ -162,14 +174,19 @@ __device__ __forceinline__ void gemm256_accumulate(const uint16_t* __restrict__ 
       const uint32_t kb = lane >> 5;
       s.base = (const GWS_GLOBAL char*)(p + (size_t)(16 * wave) * ld + o0);
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
-        s.voff[v] = (kb * ld + (((lane & 31) ^ ((2 * (v & 1) + kb) << 2) ^ ((v >> 1) << 1)) * 8)) * 2;
+      for (int v = 0; v < 4; ++v) {
+        uint32_t chunk = (lane & 31) ^ ((2 * (v & 1) + kb) << 2) ^ ((v >> 1) << 1);
+        if (EDGE && chunk * 8 >= out) chunk = 0;
+        s.voff[v] = (kb * ld + chunk * 8) * 2;
+      }
     }
     return s;
   };
-  const Src sa = make_src(A_OC, a, lda, m0), sb = make_src(B_OC, b, ldb, n0);
+  const Src sa = make_src(A_OC, a, lda, m0, a_out), sb = make_src(B_OC, b, ldb, n0, b_out);
   auto load1 = [&](bool oc, const Src& s, uint16_t* stage, uint32_t kt, int q) {
-    const size_t uni = oc ? (size_t)(kt * TK + 2 * q) * s.ld : (size_t)(8 * q) * s.ld + kt * TK;   // elements
+    // EDGE: the half step at the end of K is fetched as the second half of a whole one
+    const uint32_t k0 = EDGE ? __builtin_amdgcn_readfirstlane(kt * TK + TK > K ? K - TK : kt * TK) : kt * TK;
+    const size_t uni = oc ? (size_t)(k0 + 2 * q) * s.ld : EDGE ? (size_t)k0 : (size_t)(8 * q) * s.ld + k0;   // elements
     // issued from an assembly statement: the compiler would order every later read of the stage arrays after all
     // direct loads it knows of (vmcnt(0)), and the ring keeps loads in flight across the barrier on purpose; the
     // waits for these loads are the explicit ones in front of the barriers
@@ -179,7 +196,7 @@ __device__ __forceinline__ void gemm256_accumulate(const uint16_t* __restrict__ 
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :: "v"(s.voff[oc ? (q & 1) + 2 * ((q >> 2) & 1) : (q & 1)]), "s"(s.base + uni * 2), "s"(lds_addr) : "m0", "memory");
+                 :: "v"(s.voff[oc ? (q & 1) + 2 * ((q >> 2) & 1) : EDGE ? q : (q & 1)]), "s"(s.base + uni * 2), "s"(lds_addr) : "m0", "memory");
 #pragma clang diagnostic pop
   };
   // load n (0..15) of a K-step: even n -> A, odd n -> B
@@ -303,8 +320,18 @@ __device__ __forceinline__ void gemm256_accumulate(const uint16_t* __restrict__ 
   __builtin_amdgcn_sched_barrier(0);
   asm volatile("s_nop 3");
   __builtin_amdgcn_sched_barrier(0);
+  // EDGE: in front of a half step, whose stage's first half belongs to the step before, that half's fragments become zeros
+  auto half_step = [&](uint32_t k) {
+    if (EDGE && k * TK + TK > K) {
+#pragma unroll
+      for (int f = 0; f < 8; ++f) fa[0][f].u = fb[0][f].u = u32x4{0, 0, 0, 0};
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_nop 7");
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
   uint32_t kt = 0;
-  for (; kt + 6 <= nk; kt += 6) {
+  for (; kt + 6 <= nk - (EDGE ? 1 : 0); kt += 6) {   // EDGE: the last step is never in the unrolled loop
     kstep(A0, B0, A1, B1, cl(kt + 2), cl(kt + 3));
     kstep(A1, B1, A0, B2, cl(kt + 3), cl(kt + 4));
     kstep(A0, B2, A1, B0, cl(kt + 4), cl(kt + 5));
@@ -313,11 +340,17 @@ __device__ __forceinline__ void gemm256_accumulate(const uint16_t* __restrict__ 
     kstep(A1, B2, A0, B0, cl(kt + 7), cl(kt + 8));
   }
   const uint32_t rem = nk - kt;
-  if (rem > 0) kstep(A0, B0, A1, B1, cl(kt + 2), cl(kt + 3));
-  if (rem > 1) kstep(A1, B1, A0, B2, cl(kt + 3), cl(kt + 4));
-  if (rem > 2) kstep(A0, B2, A1, B0, cl(kt + 4), cl(kt + 5));
-  if (rem > 3) kstep(A1, B0, A0, B1, cl(kt + 5), cl(kt + 6));
-  if (rem > 4) kstep(A0, B1, A1, B2, cl(kt + 6), cl(kt + 7));
+  auto step = [&](uint32_t i, uint16_t* Ac, uint16_t* Bc, uint16_t* An, uint16_t* Bn) {
+    if (rem <= i) return;
+    half_step(kt + i);
+    kstep(Ac, Bc, An, Bn, cl(kt + i + 2), cl(kt + i + 3));
+  };
+  step(0, A0, B0, A1, B1);
+  step(1, A1, B1, A0, B2);
+  step(2, A0, B2, A1, B0);
+  step(3, A1, B0, A0, B1);
+  step(4, A0, B1, A1, B2);
+  if (EDGE) step(5, A1, B2, A0, B0);
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the refetches have landed before the epilogue reuses LDS
   // the MFMAs are assembly to the compiler, which therefore does not count their latency: let the last
   // one retire before anything reads an accumulator
@@ -335,15 +368,17 @@ struct NoHook {
 // The tile written as BF16 (one RNE) to y[(m0 + r) * ldy + n0 + c]; hook(it, row, col, v) is called for every
 // 16-byte group on its way out: a wavefront writes its 128 x 128 part in 32 steps `it` of 4 rows,
 // lane = (row % 4, col / 8).
-template <bool A_OC, bool B_OC, class Hook>
+template <bool A_OC, bool B_OC, bool EDGE = false, class Hook>
 __device__ __forceinline__ void gemm256_core(const uint16_t* __restrict__ a, uint32_t lda,
                                              const uint16_t* __restrict__ b, uint32_t ldb, uint16_t* __restrict__ y,
-                                             uint32_t ldy, uint32_t nk, uint32_t m0, uint32_t n0, Hook&& hook) {
-  gemm256_accumulate<A_OC, B_OC>(a, lda, b, ldb, nk, m0, n0, [&](f32x4 (&acc)[8][8], uint16_t* cs, uint32_t wave, uint32_t lane) {
+                                             uint32_t ldy, uint32_t nk, uint32_t m0, uint32_t n0, Hook&& hook,
+                                             uint32_t rows = 0, uint32_t cols = 0, uint32_t K = 0) {
+  gemm256_accumulate<A_OC, B_OC, EDGE>(a, lda, b, ldb, nk, m0, n0, [&](f32x4 (&acc)[8][8], uint16_t* cs, uint32_t wave, uint32_t lane) {
     uint16_t* yw = y + (size_t)(m0 + 128 * (wave >> 1)) * ldy + n0 + 128 * (wave & 1);
-    epilogue_bf16_half(*reinterpret_cast<const f32x4 (*)[4][8]>(&acc[0]), 0, cs, yw, ldy, lane, hook);
-    epilogue_bf16_half(*reinterpret_cast<const f32x4 (*)[4][8]>(&acc[4]), 1, cs, yw, ldy, lane, hook);
-  });
+    const int wr = (int)rows - 128 * (int)(wave >> 1), wc = (int)cols - 128 * (int)(wave & 1);
+    epilogue_bf16_half<EDGE>(*reinterpret_cast<const f32x4 (*)[4][8]>(&acc[0]), 0, cs, yw, ldy, lane, hook, wr, wc);
+    epilogue_bf16_half<EDGE>(*reinterpret_cast<const f32x4 (*)[4][8]>(&acc[4]), 1, cs, yw, ldy, lane, hook, wr, wc);
+  }, rows, cols, K);
 }
 
 }  // namespace gws

@@ -39,34 +39,38 @@ __device__ __forceinline__ void tile_origin(const GemmArgs& g, uint32_t bm, uint
   m0 = (8 * band + r % rows) * bm;
 }
 
-// The partial sums of the P wavefronts added in the order of the wavefronts and written to Y.  acc[i][j][e] is row
-// 16 i + 4 (lane / 16) + e, column 16 j + lane % 16.
-template <int MT, int NT, int P>
-__device__ __forceinline__ void reduce_store(const f32x4 (&acc)[MT][NT], float* red, const GemmArgs& g, uint32_t m0,
+// The partial sums of the P wavefronts added in the order of the wavefronts and written to Y, MC row tiles at a time.
+// acc[i][j][e] is row 16 i + lane % 16, column 16 j + 4 (lane / 16) + e.  In LDS a row of partial sums is 16 NT floats and
+// 16 bytes of padding: written by 16 lanes of as many rows, read along the row.
+constexpr int red_bytes(int mc, int nt, int p) { return p * mc * 16 * (4 * nt + 1) * 16; }
+
+template <int MT, int NT, int P, int MC>
+__device__ __forceinline__ void reduce_store(const f32x4 (&acc)[MT][NT], char* lds, const GemmArgs& g, uint32_t m0,
                                              uint32_t n0) {
+  constexpr uint32_t PITCH = 4 * NT + 1;
+  f32x4* red = (f32x4*)lds;
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 #pragma unroll
-  for (int i = 0; i < MT; ++i)
+  for (int i0 = 0; i0 < MT; i0 += MC) {
+    __syncthreads();   // what was in this memory is read
 #pragma unroll
-    for (int j = 0; j < NT; ++j)
+    for (int i = 0; i < MC; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) red[(((wave * MT + i) * 4 + e) * NT + j) * 64 + lane] = acc[i][j][e];
-  __syncthreads();
-  for (uint32_t it = tid; it < MT * 4 * 64; it += P * 64) {
-    const uint32_t l = it & 63, ie = it >> 6;   // ie = 4 i + e
-    float s[NT];
+      for (int j = 0; j < NT; ++j) red[((wave * MC + i) * 16 + (lane & 15)) * PITCH + 4 * j + (lane >> 4)] = acc[i0 + i][j];
+    __syncthreads();
+    for (uint32_t it = tid; it < MC * 16 * 4 * NT; it += P * 64) {
+      const uint32_t r = it / (4 * NT), c = it % (4 * NT);
+      f32x4 s = red[r * PITCH + c];
 #pragma unroll
-    for (int j = 0; j < NT; ++j) s[j] = red[(ie * NT + j) * 64 + l];
+      for (int w = 1; w < P; ++w) {
+        const f32x4 v = red[(w * MC * 16 + r) * PITCH + c];
 #pragma unroll
-    for (int w = 1; w < P; ++w)
-#pragma unroll
-      for (int j = 0; j < NT; ++j) s[j] = __fadd_rn(s[j], red[((w * MT * 4 + ie) * NT + j) * 64 + l]);
-    const uint32_t row = m0 + 16 * (ie >> 2) + 4 * (l >> 4) + (ie & 3), o = l & 15;
-    if (row >= g.M) continue;
-    uint16_t* yr = g.y + (size_t)row * g.ldy + n0;
-#pragma unroll
-    for (int j = 0; j < NT; ++j)
-      if (n0 + 16 * j + o < g.N) yr[16 * j + o] = (uint16_t)pack_bf16_rne(s[j], 0.0f);
+        for (int e = 0; e < 4; ++e) s[e] = __fadd_rn(s[e], v[e]);
+      }
+      const uint32_t row = m0 + 16 * i0 + r, col = n0 + 4 * c;
+      if (row < g.M && col < g.N)
+        *(u32x2*)(g.y + (size_t)row * g.ldy + col) = u32x2{pack_bf16_rne(s[0], s[1]), pack_bf16_rne(s[2], s[3])};
+    }
   }
 }
 }  // namespace stream
@@ -84,8 +88,9 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_kernel(const GemmArgs g) {
   constexpr int XS = BM * 64, WS = BN * 64, STG = XS + WS;          // elements of a stage
   constexpr int QX = BM / 8, QW = BN / 8, LOADS = QX + QW;          // load instructions of a unit
   static_assert(LOADS * (D - 1) <= 63, "the wait for a unit counts the loads behind it");
-  static_assert(W_NK || NT == 2 || NT == 4, "swizzle of the [K x N] stage");
-  constexpr int kRing = P * D * STG * 2, kRed = P * MT * NT * 256 * 4;
+  static_assert(W_NK || NT == 2 || NT == 4 || NT == 8, "swizzle of the [K x N] stage");
+  constexpr int MC = MT > 4 ? 4 : MT;                               // row tiles of a pass of the reduction
+  constexpr int kRing = P * D * STG * 2, kRed = red_bytes(MC, NT, P);
   __shared__ __attribute__((aligned(1024))) char lds[kRing > kRed ? kRing : kRed];
   const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -107,15 +112,18 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_kernel(const GemmArgs g) {
   }
   // [K x N]: an instruction covers RPI k-rows of 2 NT chunks
   constexpr uint32_t CPR = 2 * NT, RPI = 64 / CPR;
-  auto swz = [](uint32_t k) { return NT == 2 ? 2 * ((k >> 3) & 1) : 4 * ((k >> 1) & 1) + 2 * ((k >> 3) & 1); };
+  auto swz = [](uint32_t k) {
+    return NT == 8 ? 4 * (k & 3) + 2 * ((k >> 3) & 1) : NT == 4 ? 4 * ((k >> 1) & 1) + 2 * ((k >> 3) & 1) : 2 * ((k >> 3) & 1);
+  };
   const uint32_t wk = lane / CPR, ws = lane % CPR;
   const GWS_GLOBAL char* xb = (const GWS_GLOBAL char*)(g.x + (size_t)m0 * g.ldx);
   const GWS_GLOBAL char* wb = (const GWS_GLOBAL char*)(W_NK ? g.w + (size_t)n0 * g.ldw : g.w + n0);
   const uint32_t last_chunk = (g.N - n0) / 8 - 1;
-  uint32_t wv[2];   // the swizzle depends on k % 16: the same for every instruction of 16 rows, two cases with 8 rows
+  constexpr int NV = W_NK ? 1 : 16 / RPI;   // the swizzle depends on k % 16
+  uint32_t wv[NV];
   if (!W_NK) {
 #pragma unroll
-    for (int v = 0; v < 2; ++v) wv[v] = (wk * g.ldw + umin(ws ^ swz(wk + RPI * v), last_chunk) * 8) * 2;
+    for (int v = 0; v < NV; ++v) wv[v] = (wk * g.ldw + umin(ws ^ swz(wk + RPI * v), last_chunk) * 8) * 2;
   }
   auto direct = [](const GWS_GLOBAL char* base, uint32_t voff, uint16_t* dst) {
     const uint32_t a = (uint32_t)(uintptr_t)(GWS_LDS void*)dst;
@@ -130,7 +138,7 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_kernel(const GemmArgs g) {
 #pragma unroll
     for (int q = 0; q < QW; ++q) {
       if (W_NK) direct(wb + (size_t)k0 * 2, wo[q], st + XS + q * 512);
-      else direct(wb + (size_t)(k0 + RPI * q) * g.ldw * 2, wv[RPI == 8 ? (q & 1) : 0], st + XS + q * 512);
+      else direct(wb + (size_t)(k0 + RPI * q) * g.ldw * 2, wv[q % NV], st + XS + q * 512);
     }
 #pragma unroll
     for (int q = 0; q < QX; ++q) direct(xb + (size_t)k0 * 2, xo[q], st + q * 512);
@@ -180,11 +188,10 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_kernel(const GemmArgs g) {
 #pragma unroll
       for (int j = 0; j < NT; ++j)
 #pragma unroll
-        for (int r = 0; r < MT; ++r) acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fx[h][r].v, fw[h][j].v, acc[r][j], 0, 0, 0);
+        for (int r = 0; r < MT; ++r) acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[h][j].v, fx[h][r].v, acc[r][j], 0, 0, 0);
     }
   }
-  __syncthreads();   // the rings become the reduction's memory
-  reduce_store<MT, NT, P>(acc, (float*)lds, g, m0, n0);
+  reduce_store<MT, NT, P, MC>(acc, lds, g, m0, n0);
 }
 
 // The sampling form: a wavefront loads one 32 x 32 block of the weight per step (two 16-byte groups per lane), samples
@@ -194,7 +201,7 @@ template <int MT, int P, int FMT, bool W_NK>
 __global__ __launch_bounds__(64 * P) void gemm_stream_sample_kernel(const GemmArgs g) {
   using namespace stream;
   constexpr int LP = 40;   // row pitch of the staged block (elements)
-  constexpr int kRed = P * MT * 2 * 256 * 4, kBlk = P * 32 * LP * 2;
+  constexpr int kRed = red_bytes(MT, 2, P), kBlk = P * 32 * LP * 2;
   __shared__ __attribute__((aligned(16))) char lds[kRed > kBlk ? kRed : kBlk];
   const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -273,38 +280,39 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_sample_kernel(const GemmAr
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[i].v, f[j].v, acc[i][j], 0, 0, 0);
+      for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[j].v, x[i].v, acc[i][j], 0, 0, 0);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the reads are done before the block is overwritten
     __builtin_amdgcn_wave_barrier();
   }
-  __syncthreads();   // the staging blocks become the reduction's memory
-  reduce_store<MT, 2, P>(acc, (float*)lds, g, m0, n0);
+  reduce_store<MT, 2, P, MT>(acc, lds, g, m0, n0);
 }
 
 // ---------------------------------------------------------------------------
 // Which tile and how many parts of K.  The estimate (us) is a launch plus, per round of workgroups (one per compute unit:
-// the rings fill its LDS), a fixed part and the bytes of the tile's operands at the rate a compute unit takes them.
-// Measured on MI355X (weights taken in turn from four copies), us by tile (rows x columns, parts of K):
-//   M x K -> N            16x16,8 16x32,8 32x32,8 32x64,4 64x64,4   before
-//   4 x 5632 -> 2048 NK     6.0     7.2                               103
-//   16 x 2048 -> 5632 KN    -       7.6                                60
-//   64 x 5632 -> 2048 NK                    9.8    13.8    18.3       105
-//   64 x 2048 -> 5632 KN                   12.0     8.9    11.1        60
-//   256 x 2048 -> 5632 KN                  29.4    20.0    18.2        40
-//   1000 x 2304 -> 768 KN                  21.6    15.1    11.3        66
+// the rings fill its LDS), a fixed part (the last round's ends before the next one's loads arrive) and the bytes of the
+// tile's operands at the rate a compute unit takes them.  Measured on MI355X (weights taken in turn from four copies), us by
+// tile (rows x columns, parts of K), and the 128-tile kernel that these products took before:
+//   M x K -> N            16x16,8 16x32,8 32x32,8 32x64,4 64x64,4 128x64,4  before
+//   4 x 5632 -> 2048 NK     6.0     7.2                                      103
+//   16 x 2048 -> 5632 KN    -       7.6                                       60
+//   64 x 5632 -> 2048 NK                    9.8    13.8    18.3              105
+//   64 x 2048 -> 5632 KN                   12.0     8.9    11.1               60
+//   256 x 2048 -> 5632 KN                  29.4    20.0    18.2               40
+//   1000 x 2304 -> 768 KN                  21.6    15.1    11.0    16.1       66
+//   1000 x 5632 -> 2048 NK                                 36.6    29.9      107
 // ---------------------------------------------------------------------------
 StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk) {
   StreamPlan best = {0, 0, 0, 1e30};
   if (K < 64) return best;
   const int cus = compute_units() > 0 ? compute_units() : 256;
   // bytes per ns: eight wavefronts keep twice the loads in flight that four do
-  static const struct { int mt, nt, p; double rate; } tiles[] = {{1, 1, 8, 130.0}, {1, 2, 8, 130.0}, {2, 2, 8, 130.0}, {2, 4, 4, 100.0}, {4, 4, 4, 100.0}};
+  static const struct { int mt, nt, p; double rate; } tiles[] = {{1, 1, 8, 130.0}, {1, 2, 8, 130.0}, {2, 2, 8, 130.0}, {2, 4, 4, 100.0}, {4, 4, 4, 100.0}, {8, 4, 4, 72.0}};
   for (const auto& t : tiles) {
     if (t.mt == 1 && M > 16) continue;
     if (t.nt == 1 && !w_is_nk) continue;   // 32 bytes of a row of a [K x N] weight: a quarter of a cache line
     const uint64_t wgs = ((M + 16 * t.mt - 1) / (16 * t.mt)) * ((N + 16 * t.nt - 1) / (16 * t.nt));
     const double rounds = (double)((wgs + cus - 1) / cus);
-    const double us = 3.0 + rounds * (1.5 + (double)K * 2 * 16 * (t.mt + t.nt) / t.rate * 1e-3);
+    const double us = 1.8 + 2.7 * rounds + rounds * (double)K * 2 * 16 * (t.mt + t.nt) / t.rate * 1e-3;
     if (wgs < 0x7FFFFFFFull && us < best.us) best = {t.mt, t.nt, t.p, us};
   }
   return best;
@@ -329,7 +337,8 @@ int launch_gemm_stream(const GemmArgs& g, int w_is_nk, const StreamPlan& p, hipS
   else if (p.mt == 1) launch_plain<1, 2, 8, 2>(g, w_is_nk, s);
   else if (p.mt == 2 && p.nt == 2) launch_plain<2, 2, 8, 2>(g, w_is_nk, s);
   else if (p.mt == 2) launch_plain<2, 4, 4, 3>(g, w_is_nk, s);
-  else launch_plain<4, 4, 4, 2>(g, w_is_nk, s);
+  else if (p.mt == 4) launch_plain<4, 4, 4, 2>(g, w_is_nk, s);
+  else launch_plain<8, 4, 4, 1>(g, w_is_nk, s);
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
 

@@ -95,8 +95,16 @@ StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk);
 bool stream_applicable(const GemmArgs& g);
 int launch_gemm_stream(const GemmArgs& g, int w_is_nk, const StreamPlan& p, hipStream_t stream);
 int launch_gemm_stream_sample(const GemmArgs& g, int w_is_nk, int fmt, int p, hipStream_t stream);
-enum class GemmRoute { kStream, kLarge, kSmall };
-GemmRoute gemm_route(const GemmArgs& g, int w_is_nk, StreamPlan& plan);
+enum class GemmRoute { kStream, kMiddle, kLarge, kSmall };
+struct RoutePlan {   // estimates in us; 1e30: not a shape for that kernel
+  StreamPlan stream;
+  double middle_us, large_us;
+};
+GemmRoute gemm_route(const GemmArgs& g, int w_is_nk, RoutePlan& plan);
+bool gemm256_edge_applicable(const GemmArgs& g);
+int launch_gemm256_edge(const GemmArgs& g, int w_is_nk, hipStream_t stream);
+bool gemm128_applicable(const GemmArgs& g);
+int launch_gemm128(const GemmArgs& g, int w_is_nk, hipStream_t stream);
 bool gemm256_applicable(const GemmArgs& g);
 int launch_gemm256(const GemmArgs& g, int w_is_nk, hipStream_t stream);
 // Weights whose forward sampling rides in a GEMM's launch: descriptors as the forward pass fills them, with

@@ -349,11 +349,11 @@ def test_forced_riding_gives_the_same_bytes_for_both_riding_loops():
 
 
 # Few rows of X or few tiles: the kernel whose wavefronts split K.  Every tile it has (16 x 16 and 16 x 32 up to 16 rows,
-# 32 x 32, 32 x 64, 64 x 64), one row and one column tile more or less than whole, K of whole and half units of 64, fewer
+# 32 x 32, 32 x 64, 64 x 64, 128 x 64), one row and one column tile more or less than whole, K of whole and half units of 64, fewer
 # units than wavefronts and several per wavefront, padded X and Y; plain and sampled form bit for bit (run_case).
 @pytest.mark.parametrize("w_is_nk", [False, True])
 @pytest.mark.parametrize("M,K,N", [(1, 64, 32), (16, 96, 64), (17, 128, 96), (4, 1632, 32), (32, 544, 4128), (33, 2080, 1056),
-                                   (64, 1024, 2080), (65, 736, 5664), (300, 672, 1056), (511, 1312, 800)])
+                                   (64, 1024, 2080), (65, 736, 5664), (300, 672, 1056), (511, 1312, 800), (400, 3072, 2048), (500, 3072, 2528)])
 def test_gemm_that_splits_k(M, K, N, w_is_nk):
     idx = 40 + (M * 7 + K) % 50
     rows_sel = None if M * K * N < 2e7 else np.array(sorted({0, 15 % M, M // 2, M - 1}))
@@ -364,3 +364,20 @@ def test_gemm_that_splits_k(M, K, N, w_is_nk):
 def test_riding_under_a_gemm_of_many_k_steps():
     # 272 tiles of 256 x 256: the large tile is the faster one and leaves 240 compute units idle in its second round
     run_next_list(4096, 1024, 4352, [(128, 512), (64, 256)], gws.FMT_FP8_E4M3, 7, rows_sel=np.array([0, 255, 256, 4095]))
+
+
+# The middle tile (128 x 128) and the large tile with edges: one row and 32 columns more or less than whole tiles, K of
+# whole and half steps of 64 (the half step at every place in the rings of loads), padded X and Y; the sampling kernel's Y
+# is the same bits.
+@pytest.mark.parametrize("w_is_nk", [False, True])
+@pytest.mark.parametrize("M,K,N", [(1537, 96, 1696), (1920, 160, 1760), (1600, 256, 2080), (2049, 288, 1312), (2000, 1504, 2016)])
+def test_middle_tile_gemm(M, K, N, w_is_nk):
+    run_case(M, K, N, w_is_nk, gws.FMT_FP8_E4M3, seed_id=91, ldx_pad=8, ldy_pad=8, rows_sel=np.array([0, 127, 128, M // 2, M - 1]),
+             mode=gws.LINEAR_IN_OPERAND)
+
+
+@pytest.mark.parametrize("w_is_nk", [False, True])
+@pytest.mark.parametrize("M,K,N", [(8191, 96, 1824), (8193, 512, 1760)] + [(7937, 1024 + 32 * i, 1568) for i in range(1, 13, 2)])
+def test_large_tile_gemm_with_edges(M, K, N, w_is_nk):
+    run_case(M, K, N, w_is_nk, gws.FMT_FP8_E4M3, seed_id=92, ldx_pad=8, ldy_pad=8, rows_sel=np.array([0, 255, 256, M // 2, M - 2, M - 1]),
+             mode=gws.LINEAR_IN_OPERAND)
