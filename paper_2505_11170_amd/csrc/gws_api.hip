@@ -155,10 +155,9 @@ int run_batched(const gws_tensor* t, int n, const gws_bitwidth* bw, const gws_mx
     if (a.n == 0) return GWS_OK;
     const int variant = !whole_tiles ? 0 : tune.variant >= 0 ? tune.variant : 1;
     int rc = (!fwd && fmt == kAbsmaxOnly) ? launch_block_absmax(a, (uint32_t)wgs, stream)
-             : (!fwd && basis != kBasisBits) ? launch_sample_bwd_basis(a, (uint32_t)wgs, basis, stream)
-             : !fwd ? launch_sample_bwd(a, (uint32_t)wgs, variant, stream)
+             : !fwd ? launch_sample_bwd(a, (uint32_t)wgs, basis, variant, stream)
              : fmt == kCopyOnly ? launch_copy_tiles(a, (uint32_t)wgs, stream)
-             : basis != kBasisBits ? launch_sample_fwd_basis(a, (uint32_t)wgs, fmt, keep, basis, stream)
+             : basis != kBasisBits ? launch_sample_fwd_basis(a, (uint32_t)wgs, fmt, keep, basis, variant, stream)
                                    : launch_sample_fwd(a, (uint32_t)wgs, fmt, mx != nullptr, keep, variant, stream);
     a.n = 0;
     wgs = 0;

@@ -200,7 +200,7 @@ __global__ __launch_bounds__(kThreads) void sample_bwd_kernel(const LaunchArgs a
 // The forward pass for tensors of whole tiles only (rows a multiple of 32, columns of 256): a workgroup walks
 // `tiles_per_wg_x` neighbouring column tiles of one block row, straight-line per tile, and keeps the row-only
 // share of its Philox calls across them.
-template <int FMT, bool MX, bool STREAM>
+template <int FMT, bool MX, bool STREAM, int BASIS = kBasisBits>
 __global__ __launch_bounds__(kThreads) void sample_fwd_full_kernel(const LaunchArgs a) {
   uint32_t byg, bxg;
   const TileDesc d = locate(a, byg, bxg);
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(kThreads) void sample_fwd_full_kernel(const LaunchA
   for (uint32_t bx = bx0; bx < bx_end; ++bx) {
     const uint32_t col_base = bx * kTileCols + wave * 64;
     Tile t = load_tile(src, d, byg, col_base, col_base + gc * 8, r0);   // always a whole tile here
-    fwd_tile<FMT, true, STREAM, MX>(a.step_lo, a.step_hi, d, t, byg, col_base, lane, 0.0f, &rp);
+    fwd_tile<FMT, true, STREAM, MX, false, BASIS>(a.step_lo, a.step_hi, d, t, byg, col_base, lane, 0.0f, &rp);
   }
 }
 
@@ -227,6 +227,7 @@ __global__ __launch_bounds__(kThreads) void sample_fwd_full_kernel(const LaunchA
 // tile (288 vector instructions per tile against about 330 in the kernel for any shape).  The next tile's loads
 // are issued after the current tile's arithmetic and complete under the next tile's Philox rounds; issuing them
 // a whole tile ahead was measured slower (16 more registers cost a wavefront of occupancy).
+template <int BASIS = kBasisBits>
 __global__ __launch_bounds__(kThreads) void sample_bwd_full_kernel(const LaunchArgs a) {
   uint32_t byg, bxg;
   const TileDesc d = locate(a, byg, bxg);
@@ -267,8 +268,12 @@ __global__ __launch_bounds__(kThreads) void sample_bwd_full_kernel(const LaunchA
     // sum_{b_l}(g .* R) as sum(g .* 2R) / 2: exact products, fixed order (see bwd_tile)
     float acc = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc = dot_group_2r(v[i], noise_planes(philox_row(pc, rp, i, d.seed_lo, d.seed_hi)), acc);
-    acc = block_sum_f32(acc) * 0.5f;
+    for (int i = 0; i < 4; ++i) {
+      const Philox4 x = philox_row(pc, rp, i, d.seed_lo, d.seed_hi);
+      if constexpr (BASIS == kBasisBits) acc = dot_group_2r(v[i], noise_planes(x), acc);
+      else acc = dot_group_basis<BASIS>(v[i], x, acc);
+    }
+    acc = block_sum_f32(acc) * (BASIS == kBasisBits ? 0.5f : 1.0f);
     if (writer) {
       const size_t blk = (size_t)by * nbc + (col >> 5);
       const float neg_ln2 = __uint_as_float(0xBF317218u);   // -ln 2
@@ -348,38 +353,45 @@ __global__ __launch_bounds__(256) void noise_basis_kernel(u32x4* __restrict__ ou
 // ---------------------------------------------------------------------------
 // Host-side launchers
 // ---------------------------------------------------------------------------
+// the kernel of the call's whole-tile rule (variant 1) or the one for any shape
+template <int BASIS, int FMT, bool STREAM>
+static void launch_fwd_basis(const LaunchArgs& a, uint32_t n_wg, int variant, hipStream_t stream) {
+  if (variant == 1) hipLaunchKernelGGL((sample_fwd_full_kernel<FMT, false, STREAM, BASIS>), dim3(n_wg), dim3(kThreads), 0, stream, a);
+  else hipLaunchKernelGGL((sample_fwd_kernel<FMT, false, STREAM, BASIS>), dim3(n_wg), dim3(kThreads), 0, stream, a);
+}
+
 template <int BASIS>
-static int launch_fwd_basis(const LaunchArgs& a, uint32_t n_wg, int fmt, bool keep, hipStream_t stream) {
-  if (keep) {
-    switch (fmt) {
-      case GWS_FMT_BF16: hipLaunchKernelGGL((sample_fwd_kernel<0, false, false, BASIS>), dim3(n_wg), dim3(kThreads), 0, stream, a); break;
-      case GWS_FMT_FP8_E4M3: hipLaunchKernelGGL((sample_fwd_kernel<1, false, false, BASIS>), dim3(n_wg), dim3(kThreads), 0, stream, a); break;
-      case GWS_FMT_FP6_E3M2: hipLaunchKernelGGL((sample_fwd_kernel<2, false, false, BASIS>), dim3(n_wg), dim3(kThreads), 0, stream, a); break;
-      default: return GWS_ERR_FORMAT;
-    }
-  } else {
-    switch (fmt) {
-      case GWS_FMT_BF16: hipLaunchKernelGGL((sample_fwd_kernel<0, false, true, BASIS>), dim3(n_wg), dim3(kThreads), 0, stream, a); break;
-      case GWS_FMT_FP8_E4M3: hipLaunchKernelGGL((sample_fwd_kernel<1, false, true, BASIS>), dim3(n_wg), dim3(kThreads), 0, stream, a); break;
-      case GWS_FMT_FP6_E3M2: hipLaunchKernelGGL((sample_fwd_kernel<2, false, true, BASIS>), dim3(n_wg), dim3(kThreads), 0, stream, a); break;
-      default: return GWS_ERR_FORMAT;
-    }
+static int launch_fwd_basis_fmt(const LaunchArgs& a, uint32_t n_wg, int fmt, bool keep, int variant, hipStream_t stream) {
+  switch (fmt) {
+    case GWS_FMT_BF16: keep ? launch_fwd_basis<BASIS, 0, false>(a, n_wg, variant, stream) : launch_fwd_basis<BASIS, 0, true>(a, n_wg, variant, stream); break;
+    case GWS_FMT_FP8_E4M3: keep ? launch_fwd_basis<BASIS, 1, false>(a, n_wg, variant, stream) : launch_fwd_basis<BASIS, 1, true>(a, n_wg, variant, stream); break;
+    case GWS_FMT_FP6_E3M2: keep ? launch_fwd_basis<BASIS, 2, false>(a, n_wg, variant, stream) : launch_fwd_basis<BASIS, 2, true>(a, n_wg, variant, stream); break;
+    default: return GWS_ERR_FORMAT;
   }
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
 
-int launch_sample_fwd_basis(const LaunchArgs& a, uint32_t n_wg, int fmt, bool keep, int basis, hipStream_t stream) {
+int launch_sample_fwd_basis(const LaunchArgs& a, uint32_t n_wg, int fmt, bool keep, int basis, int variant, hipStream_t stream) {
   if (n_wg == 0) return GWS_OK;
-  if (basis == kBasisUniform) return launch_fwd_basis<kBasisUniform>(a, n_wg, fmt, keep, stream);
-  if (basis == kBasisBoxMuller) return launch_fwd_basis<kBasisBoxMuller>(a, n_wg, fmt, keep, stream);
+  if (basis == kBasisUniform) return launch_fwd_basis_fmt<kBasisUniform>(a, n_wg, fmt, keep, variant, stream);
+  if (basis == kBasisBoxMuller) return launch_fwd_basis_fmt<kBasisBoxMuller>(a, n_wg, fmt, keep, variant, stream);
   return GWS_ERR_FORMAT;
 }
 
-int launch_sample_bwd_basis(const LaunchArgs& a, uint32_t n_wg, int basis, hipStream_t stream) {
+template <int BASIS>
+static void launch_bwd_any(const LaunchArgs& a, uint32_t n_wg, int variant, hipStream_t stream) {
+  if (variant == 1) hipLaunchKernelGGL(sample_bwd_full_kernel<BASIS>, dim3(n_wg), dim3(kThreads), 0, stream, a);
+  else hipLaunchKernelGGL(sample_bwd_kernel<BASIS>, dim3(n_wg), dim3(kThreads), 0, stream, a);
+}
+
+int launch_sample_bwd(const LaunchArgs& a, uint32_t n_wg, int basis, int variant, hipStream_t stream) {
   if (n_wg == 0) return GWS_OK;
-  if (basis == kBasisUniform) hipLaunchKernelGGL(sample_bwd_kernel<kBasisUniform>, dim3(n_wg), dim3(kThreads), 0, stream, a);
-  else if (basis == kBasisBoxMuller) hipLaunchKernelGGL(sample_bwd_kernel<kBasisBoxMuller>, dim3(n_wg), dim3(kThreads), 0, stream, a);
-  else return GWS_ERR_FORMAT;
+  switch (basis) {
+    case kBasisBits: launch_bwd_any<kBasisBits>(a, n_wg, variant, stream); break;
+    case kBasisUniform: launch_bwd_any<kBasisUniform>(a, n_wg, variant, stream); break;
+    case kBasisBoxMuller: launch_bwd_any<kBasisBoxMuller>(a, n_wg, variant, stream); break;
+    default: return GWS_ERR_FORMAT;
+  }
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
 
@@ -440,13 +452,6 @@ int launch_copy_tiles(const LaunchArgs& a, uint32_t n_wg, hipStream_t stream) {
 int launch_block_absmax(const LaunchArgs& a, uint32_t n_wg, hipStream_t stream) {
   if (n_wg == 0) return GWS_OK;
   hipLaunchKernelGGL(block_absmax_kernel, dim3(n_wg), dim3(kThreads), 0, stream, a);
-  return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
-}
-
-int launch_sample_bwd(const LaunchArgs& a, uint32_t n_wg, int variant, hipStream_t stream) {
-  if (n_wg == 0) return GWS_OK;
-  if (variant == 1) hipLaunchKernelGGL(sample_bwd_full_kernel, dim3(n_wg), dim3(kThreads), 0, stream, a);
-  else hipLaunchKernelGGL(sample_bwd_kernel<kBasisBits>, dim3(n_wg), dim3(kThreads), 0, stream, a);
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
 

@@ -181,11 +181,7 @@ __device__ __forceinline__ void tile_apply(uint32_t step_lo, uint32_t step_hi, c
       pk[2] = sampled_pair<2>(w[2], g, n, b);
       pk[3] = sampled_pair<3>(w[3], g, n, b);
     } else {
-      const Philox4 x = bits_of(row, i);
-      pk[0] = sampled_pair_basis<BASIS, 0>(w[0], x, b);
-      pk[1] = sampled_pair_basis<BASIS, 1>(w[1], x, b);
-      pk[2] = sampled_pair_basis<BASIS, 2>(w[2], x, b);
-      pk[3] = sampled_pair_basis<BASIS, 3>(w[3], x, b);
+      sampled_group_basis<BASIS>(w, bits_of(row, i), b, pk);
     }
   };
   if constexpr (FMT != 2) {

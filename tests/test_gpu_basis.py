@@ -125,3 +125,11 @@ def test_basis_argument_rules():
     with pytest.raises(gws.GwsError) as e:
         gws.gws_noise_basis(out, 8, 12, 1, 0, gws.BASIS_UNIFORM_BF16)              # cols not a multiple of 8
     assert e.value.status == 2
+
+
+@pytest.mark.parametrize("fmt", FMTS)
+@pytest.mark.parametrize("name", list(BASES))
+def test_whole_tiles_with_the_gradient_passed_through(name, fmt):
+    # rows multiples of 32, columns of 256, dL/dw aliased: the whole-tile kernels, one tile and several
+    gb, ob = BASES[name]
+    run_fwd_bwd([(32, 256), (64, 1536), (96, 512)], gb, ob, fmt, 9, copy_dw=False)
