@@ -132,15 +132,31 @@ int run_batched(const gws_tensor* t, int n, const gws_bitwidth* bw, const gws_mx
   for (int i = 0; i < n; ++i)
     if (t[i].rows > 0 && t[i].cols > 0) total += wg_count(t[i], 1, 1);
   uint32_t per_wg = 1, per_x = 1;
-  if (!fwd) {
+  // Where dL/dw is copied the pass is the forward pass's traffic: one tile (75 M parameters in rows of 2000 bytes: 60 us, 69
+  // with two, 78 with three).
+  bool copies = false;
+  for (int i = 0; i < n; ++i) copies = copies || (!fwd && fmt != kAbsmaxOnly && t[i].dw != nullptr && t[i].dw != t[i].g);
+  if (!fwd && !copies) {
     while (per_x < 4 && total / (per_x + 1) >= 3000) ++per_x;
   }
   if (tune.per_x > 0) per_x = (uint32_t)tune.per_x;
-  // Forward stores: a call that writes little (one weight, a few layers) is usually followed by its
-  // consumer, and the whole of w_hat fits in the last-level cache, so it is written with ordinary
-  // stores; a call over a model's worth of weights streams past the caches (non-temporal stores).
-  // A workgroup tile is 32 x 256 elements = 16 KiB of w_hat.
-  if (fwd && total * (16u << 10) <= (32u << 20)) keep = true;
+  // Streaming or not.  A forward call that writes little (one weight, a few layers) is usually followed by its consumer, and
+  // the whole of w_hat fits in the last-level cache: ordinary accesses; a call over a model's worth of weights streams past
+  // the caches (ordinary loads: the 124M model's two passes 87.6 -> 92.7 us together, though each of them alone repeats
+  // faster with its 170 MB in the 256 MB last-level cache; the 1B model's backward pass 303 -> 348 us).
+  // Rows that do not start on cache lines (FP6 codes never do: a tile's row is 1.5 lines): ordinary stores, see load16, and
+  // ordinary loads up to 192 MB (75 M parameters in rows of 2000 bytes, both passes: 125 us, 139 with streaming loads).
+  // A workgroup tile is 32 x 256 elements = 16 KiB.
+  const uint64_t tile_bytes = total * (16u << 10);
+  int mode = kStreamAll;
+  if (keep || tile_bytes <= ((uint64_t)32 << 20)) mode = kKeep;
+  bool whole_lines = !(mx && fmt == GWS_FMT_FP6_E3M2);
+  for (int i = 0; i < n && whole_lines; ++i) {
+    const void* out = fwd ? (mx ? mx[i].codes : t[i].w_hat) : t[i].dw;
+    const int64_t row_bytes = mx ? mx[i].ldc : 2 * t[i].ld;
+    if (t[i].rows > 0 && t[i].cols > 0 && (fwd || copies) && ((row_bytes & 127) != 0 || !aligned(out, 128))) whole_lines = false;
+  }
+  if (!whole_lines && mode == kStreamAll) mode = tile_bytes <= ((uint64_t)192 << 20) ? kKeep : kStreamReads;
 
   LaunchArgs a;
   memset(&a, 0, sizeof a);
@@ -155,10 +171,9 @@ int run_batched(const gws_tensor* t, int n, const gws_bitwidth* bw, const gws_mx
     if (a.n == 0) return GWS_OK;
     const int variant = !whole_tiles ? 0 : tune.variant >= 0 ? tune.variant : 1;
     int rc = (!fwd && fmt == kAbsmaxOnly) ? launch_block_absmax(a, (uint32_t)wgs, stream)
-             : !fwd ? launch_sample_bwd(a, (uint32_t)wgs, basis, variant, stream)
+             : !fwd ? launch_sample_bwd(a, (uint32_t)wgs, basis, mode, variant, stream)
              : fmt == kCopyOnly ? launch_copy_tiles(a, (uint32_t)wgs, stream)
-             : basis != kBasisBits ? launch_sample_fwd_basis(a, (uint32_t)wgs, fmt, keep, basis, variant, stream)
-                                   : launch_sample_fwd(a, (uint32_t)wgs, fmt, mx != nullptr, keep, variant, stream);
+             : launch_sample_fwd(a, (uint32_t)wgs, fmt, mx != nullptr, basis, mode, variant, stream);
     a.n = 0;
     wgs = 0;
     whole_tiles = true;

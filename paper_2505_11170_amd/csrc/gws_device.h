@@ -322,62 +322,53 @@ __device__ __forceinline__ uint32_t cast_pair(uint32_t pk, const BlockScale& b, 
   return cast_scaled_bits<M>(pk & 0xFFFFu, b) | (cast_scaled_bits<M>(pk >> 16, b) << 16);
 }
 
-// Byte i of x as fp32 (v_cvt_f32_ubyte<i>).  The empty asm hides what is known
-// about the other bits of x, so the byte extraction is not rewritten into a
-// shift-and-mask pair.
-__device__ __forceinline__ uint32_t opaque(uint32_t x) {
-  asm volatile("" : "+v"(x));
-  return x;
-}
+// Byte i of x as fp32 (v_cvt_f32_ubyte<i>).
 template <int I>
 __device__ __forceinline__ float byte_to_f32(uint32_t x) {
   return (float)((x >> (8 * I)) & 0xFFu);
 }
 
 // ---------------------------------------------------------------------------
-// Eq. 3 + cast on one 16-byte group (8 BF16 in 4 registers).  PQN = R * s is
-// formed in sign-magnitude: |R| * s is exact and the sign bit is placed as is
-// (R = -0 gives -0.0); the fp32 fused multiply-add followed by one RNE to BF16
-// equals the exact BF16 sum.
+// Eq. 3 + cast on one 16-byte group (8 BF16 in 4 registers).  R is sign-magnitude: |R| * s is
+// exact and the sign is kept on a zero (R = -0 gives -0.0); the fp32 fused multiply-add
+// followed by one RNE to BF16 equals the exact BF16 sum.
 // ---------------------------------------------------------------------------
-struct GroupMagnitudes {
-  float m[8];  // |R| of element k as fp32
+struct GroupR {
+  float r[8];  // R of element k as fp32
 };
 
-__device__ __forceinline__ GroupMagnitudes group_magnitudes(const Noise& n) {
+// A byte sign<<7 | |R| is an FP8-E4M3 number (subnormal), R * 2^-9: the scaled converter makes two elements' R of two
+// bytes, sign of a zero included.  Nine instructions a group behind the planes; taking |R| and the sign apart (eight
+// byte conversions, two instructions an element for the sign) took 26.  The forward pass with MX-FP6 output, which the
+// vector ALU bounds: 352 M parameters 217 -> 211 us.
+__device__ __forceinline__ GroupR group_r(const Noise& n) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
   const uint32_t mag = n.nz + n.m2;  // per nibble: |R| in {0, 1, 2}
-  const uint32_t me = opaque(mag & 0x0F0F0F0Fu);         // byte i: |R| of nibble 2i
-  const uint32_t mo = opaque((mag >> 4) & 0x0F0F0F0Fu);  // byte i: |R| of nibble 2i+1
+  const uint32_t be = __builtin_amdgcn_bitop3_b32(n.x3 << 4, 0x80808080u, mag & 0x03030303u, 0xEA);         // byte i: nibble 2i
+  const uint32_t bo = __builtin_amdgcn_bitop3_b32(n.x3, 0x80808080u, (mag >> 4) & 0x03030303u, 0xEA);       // byte i: nibble 2i+1
+  const f32x2 n02 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(be, 512.0f, false), n46 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(be, 512.0f, true);
+  const f32x2 n13 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(bo, 512.0f, false), n57 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(bo, 512.0f, true);
   // element 2d sits in nibble d, element 2d+1 in nibble d+4
-  return GroupMagnitudes{{byte_to_f32<0>(me), byte_to_f32<2>(me), byte_to_f32<0>(mo), byte_to_f32<2>(mo),
-                          byte_to_f32<1>(me), byte_to_f32<3>(me), byte_to_f32<1>(mo), byte_to_f32<3>(mo)}};
+  return GroupR{{n02[0], n46[0], n13[0], n57[0], n02[1], n46[1], n13[1], n57[1]}};
 }
 
 // bf16_rne(w + R * s) for elements 2d and 2d+1 of a group (register d), packed.
 template <int D>
-__device__ __forceinline__ uint32_t sampled_pair(uint32_t wd, const GroupMagnitudes& g, const Noise& n,
-                                                 const BlockScale& b) {
-  constexpr int n_lo = D, n_hi = D + 4;
-  // s with the sign bit of the nibble: (x3 << sh) & 0x80000000 | s, one shift and one bit-op
-  const uint32_t sh_lo = n.x3 << (28 - 4 * n_lo);
-  const uint32_t sh_hi = (n_hi == 7) ? n.x3 : (n.x3 << (28 - 4 * n_hi));
-  const float s_lo = __uint_as_float(__builtin_amdgcn_bitop3_b32(sh_lo, 0x80000000u, b.s_bits, 0xEA));
-  const float s_hi = __uint_as_float(__builtin_amdgcn_bitop3_b32(sh_hi, 0x80000000u, b.s_bits, 0xEA));
+__device__ __forceinline__ uint32_t sampled_pair(uint32_t wd, const GroupR& g, const BlockScale& b) {
+  const float s = __uint_as_float(b.s_bits);
   const float w_lo = __uint_as_float(wd << 16), w_hi = __uint_as_float(wd & 0xFFFF0000u);
-  const float sum_lo = __fmaf_rn(g.m[2 * D], s_lo, w_lo);
-  const float sum_hi = __fmaf_rn(g.m[2 * D + 1], s_hi, w_hi);
-  return pack_bf16_rne(sum_lo, sum_hi);
+  return pack_bf16_rne(__fmaf_rn(g.r[2 * D], s, w_lo), __fmaf_rn(g.r[2 * D + 1], s, w_hi));
 }
 
 template <int FMT>
 __device__ __forceinline__ u32x4 sample_group(const u32x4 w, const Noise& n, const BlockScale& b, bool hw) {
-  const GroupMagnitudes g = group_magnitudes(n);
+  const GroupR g = group_r(n);
   i16x2 chain = {0, 0};
   u32x4 out;
-  out[0] = cast_pair<FMT>(sampled_pair<0>(w[0], g, n, b), b, hw, chain);
-  out[1] = cast_pair<FMT>(sampled_pair<1>(w[1], g, n, b), b, hw, chain);
-  out[2] = cast_pair<FMT>(sampled_pair<2>(w[2], g, n, b), b, hw, chain);
-  out[3] = cast_pair<FMT>(sampled_pair<3>(w[3], g, n, b), b, hw, chain);
+  out[0] = cast_pair<FMT>(sampled_pair<0>(w[0], g, b), b, hw, chain);
+  out[1] = cast_pair<FMT>(sampled_pair<1>(w[1], g, b), b, hw, chain);
+  out[2] = cast_pair<FMT>(sampled_pair<2>(w[2], g, b), b, hw, chain);
+  out[3] = cast_pair<FMT>(sampled_pair<3>(w[3], g, b), b, hw, chain);
   return out;
 }
 
@@ -411,9 +402,9 @@ __device__ __forceinline__ uint32_t encode_scaled(uint32_t h16, const BlockScale
 // FP8-E4M3 codes of one group.  (FP6-E3M2 codes come from the 32-wide converter, a lane's
 // whole tile at a time: see fwd_tile.)
 __device__ __forceinline__ MxCodes sample_group_mx_fp8(const u32x4 w, const Noise& n, const BlockScale& b, bool hw) {
-  const GroupMagnitudes g = group_magnitudes(n);
-  const uint32_t pk[4] = {sampled_pair<0>(w[0], g, n, b), sampled_pair<1>(w[1], g, n, b),
-                          sampled_pair<2>(w[2], g, n, b), sampled_pair<3>(w[3], g, n, b)};
+  const GroupR g = group_r(n);
+  const uint32_t pk[4] = {sampled_pair<0>(w[0], g, b), sampled_pair<1>(w[1], g, b),
+                          sampled_pair<2>(w[2], g, b), sampled_pair<3>(w[3], g, b)};
   MxCodes c;
   if (hw) {
     // hardware converter: rounds to nearest even under the scale; each call fills one

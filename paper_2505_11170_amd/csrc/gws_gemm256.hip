@@ -66,7 +66,7 @@ __device__ __forceinline__ void sample_tiles(uint32_t step_lo, uint32_t step_hi,
       const uint32_t id = base + j * stride;
       if (id < ntiles) {
         const uint32_t by = id / per_row, cb = (id - by * per_row) * 64;
-        fwd_tile<FMT, true, false, false, true>(step_lo, step_hi, d, t[j], by, cb, lane, bv[j]);
+        fwd_tile<FMT, true, kKeep, false, true>(step_lo, step_hi, d, t[j], by, cb, lane, bv[j]);
       }
     }
   }
@@ -144,12 +144,12 @@ __device__ __forceinline__ void ride_tiles(uint32_t step_lo, uint32_t step_hi, c
     if (FMT == 1 && __builtin_amdgcn_ballot_w64(unsafe) == 0) {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        tile_apply<FMT, true, false, false, kBasisBits, FMT == 1>(step_lo, step_hi, d, cur.t[j], bs[j], by, cb0 + 64 * j, lane,
+        tile_apply<FMT, true, kKeep, false, kBasisBits, FMT == 1>(step_lo, step_hi, d, cur.t[j], bs[j], by, cb0 + 64 * j, lane,
                                                                    &rp, bits[j]);
     } else {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        tile_apply<FMT, true, false, false, kBasisBits, false>(step_lo, step_hi, d, cur.t[j], bs[j], by, cb0 + 64 * j, lane,
+        tile_apply<FMT, true, kKeep, false, kBasisBits, false>(step_lo, step_hi, d, cur.t[j], bs[j], by, cb0 + 64 * j, lane,
                                                                 &rp, bits[j]);
     }
     if (writer) {

@@ -39,6 +39,9 @@ struct TileDesc {
 };
 static_assert(sizeof(TileDesc) == 96, "descriptor layout");
 
+// Streaming (non-temporal) or ordinary accesses of the sampling passes (gws_sample_tile.h, load16).
+constexpr int kKeep = 0, kStreamReads = 1, kStreamAll = 2;
+
 // Passed by value: lives in the kernel-argument segment (about 5.5 KiB; the segment
 // of a gfx950 code object is not limited to 4 KiB).
 struct LaunchArgs {
@@ -52,14 +55,19 @@ struct LaunchArgs {
   uint32_t tiles_per_wg;       // consecutive block rows one workgroup covers (>= 1)
   uint32_t tiles_per_wg_x;     // neighbouring 256-column tiles one workgroup covers (>= 1)
 };
+// The same for one tensor: a hundred bytes instead of five thousand, read in one go.
+struct OneArgs {
+  TileDesc t;
+  uint32_t step_lo, step_hi;
+  uint32_t tiles_per_wg, tiles_per_wg_x;
+};
 static_assert(sizeof(LaunchArgs) <= 6144, "kernel arguments: keep within the size verified on the device");
 
+// basis: kBasisBits, or a comparison basis (no MX output then); mode: kKeep, kStreamReads or kStreamAll
 // variant: 0 = any shape (sample_fwd_kernel); 1 = whole tiles only (sample_fwd_full_kernel)
-int launch_sample_fwd(const LaunchArgs& a, uint32_t n_wg, int fmt, bool mx, bool keep, int variant, hipStream_t stream);
+int launch_sample_fwd(const LaunchArgs& a, uint32_t n_wg, int fmt, bool mx, int basis, int mode, int variant, hipStream_t stream);
 // variant: 0 = any shape (sample_bwd_kernel); 1 = whole tiles and aliased dL/dw only (sample_bwd_full_kernel)
-int launch_sample_bwd(const LaunchArgs& a, uint32_t n_wg, int basis, int variant, hipStream_t stream);
-// the forward pass with R drawn from a comparison basis (kBasisUniform, kBasisBoxMuller); variants as above
-int launch_sample_fwd_basis(const LaunchArgs& a, uint32_t n_wg, int fmt, bool keep, int basis, int variant, hipStream_t stream);
+int launch_sample_bwd(const LaunchArgs& a, uint32_t n_wg, int basis, int mode, int variant, hipStream_t stream);
 int launch_noise_basis(void* out, uint32_t rows, uint32_t ngrp, uint32_t row0, uint32_t cg0, uint64_t seed, uint64_t step,
                        int basis, hipStream_t stream);
 int launch_copy_tiles(const LaunchArgs& a, uint32_t n_wg, hipStream_t stream);

@@ -38,8 +38,31 @@ typedef uint32_t u32x16s __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x8s __attribute__((ext_vector_type(8)));
 static_assert(kMaxTensorsPerLaunch == 56 && sizeof(TileDesc) == 96, "locate() is laid out for this table");
 
+// local / tiles_x by the host's reciprocal: the estimate is at most one too small
+__device__ __forceinline__ void tile_position(const TileDesc& d, uint32_t local, uint32_t& byg, uint32_t& bx) {
+  uint32_t q = __umulhi(local, d.tiles_x_inv);
+  uint32_t r = local - q * d.tiles_x;
+  if (r >= d.tiles_x) {
+    ++q;
+    r -= d.tiles_x;
+  }
+  byg = q;
+  bx = r;
+}
+
+// One tensor: its descriptor is the kernel's argument.
+__device__ __forceinline__ TileDesc locate(const OneArgs& a, uint32_t& byg, uint32_t& bx) {
+  tile_position(a.t, blockIdx.x, byg, bx);
+  return a.t;
+}
+
 __device__ __forceinline__ TileDesc locate(const LaunchArgs& a, uint32_t& byg, uint32_t& bx) {
-  const uint32_t wg = blockIdx.x;
+  // Workgroups are dealt round-robin to the 8 XCDs: sixteen neighbouring tiles go to one XCD, so that a cache line shared by
+  // two of them (rows that do not start on lines) meets in its L2.  Rows of 2000 bytes, w and w_hat of 75 M parameters: with
+  // ordinary stores 62 us forward, like this 59 (streaming stores 93 and 83); whole lines too: the 1B model's forward pass
+  // 667 -> 624 us (8 tiles 644, 32 tiles 630).
+  uint32_t wg = blockIdx.x;
+  if (wg < gridDim.x / 128 * 128) wg = (wg & ~127u) + (wg & 7) * 16 + ((wg >> 3) & 15);
   const uint32_t* tb = a.tile_begin;
   u32x16s t0 = *(const u32x16s*)(tb), t1 = *(const u32x16s*)(tb + 16), t2 = *(const u32x16s*)(tb + 32);
   u32x8s t3 = *(const u32x8s*)(tb + 48);
@@ -63,16 +86,7 @@ __device__ __forceinline__ TileDesc locate(const LaunchArgs& a, uint32_t& byg, u
   TileDesc d;
   __builtin_memcpy(&d, w, sizeof d);
 
-  // local / tiles_x by the host's reciprocal: the estimate is at most one too small
-  const uint32_t local = wg - d.first_wg;
-  uint32_t q = __umulhi(local, d.tiles_x_inv);
-  uint32_t r = local - q * d.tiles_x;
-  if (r >= d.tiles_x) {
-    ++q;
-    r -= d.tiles_x;
-  }
-  byg = q;
-  bx = r;
+  tile_position(d, wg - d.first_wg, byg, bx);
   return d;
 }
 
@@ -81,8 +95,8 @@ __device__ __forceinline__ TileDesc locate(const LaunchArgs& a, uint32_t& byg, u
 // contiguous stretch of the tensor.  Each wavefront handles its 64-column strip of every
 // tile; `body(by, col_base, tile)` is called for strips that exist.  The first tile is
 // loaded ahead of the loop, so the common one-tile case stays straight-line code.
-template <class F>
-__device__ __forceinline__ void walk_tiles(const LaunchArgs& a, const TileDesc& d, uint32_t byg, uint32_t bxg,
+template <int STREAM, class ARGS, class F>
+__device__ __forceinline__ void walk_tiles(const ARGS& a, const TileDesc& d, uint32_t byg, uint32_t bxg,
                                            F&& body) {
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const uint32_t r0 = lane >> 3, gcol = (lane & 7) * 8;
@@ -92,7 +106,7 @@ __device__ __forceinline__ void walk_tiles(const LaunchArgs& a, const TileDesc& 
   const uint32_t bx0 = bxg * a.tiles_per_wg_x, bx_end = min(bx0 + a.tiles_per_wg_x, ntx);
   uint32_t by = by0, bx = bx0;
   uint32_t col_base = bx * kTileCols + wave * 64;
-  Tile t = load_tile(src, d, by, col_base, col_base + gcol, r0);
+  Tile t = load_tile<STREAM>(src, d, by, col_base, col_base + gcol, r0);
   for (;;) {
     if (col_base < d.cols) body(by, col_base, t);
     if (++bx >= bx_end) {
@@ -100,27 +114,26 @@ __device__ __forceinline__ void walk_tiles(const LaunchArgs& a, const TileDesc& 
       if (++by >= by_end) break;
     }
     col_base = bx * kTileCols + wave * 64;
-    t = load_tile(src, d, by, col_base, col_base + gcol, r0);
+    t = load_tile<STREAM>(src, d, by, col_base, col_base + gcol, r0);
   }
 }
 
 // MX: write element codes and E8M0 block scales instead of the BF16 container.
-// STREAM: non-temporal stores of w_hat (right when it is not read again soon); false keeps w_hat in
-// the caches for a GEMM that follows immediately.
+// STREAM: see load16.
 // BASIS: the method's bit-built noise, or one of the two comparison bases.
-template <int FMT, bool MX = false, bool STREAM = true, int BASIS = kBasisBits>
-__global__ __launch_bounds__(kThreads) void sample_fwd_kernel(const LaunchArgs a) {
+template <int FMT, bool MX, int STREAM, int BASIS, class ARGS>
+__global__ __launch_bounds__(kThreads) void sample_fwd_kernel(const ARGS a) {
   uint32_t byg, bxg;
   const TileDesc d = locate(a, byg, bxg);
   const uint32_t lane = threadIdx.x & 63;
-  walk_tiles(a, d, byg, bxg, [&](uint32_t by, uint32_t col_base, Tile& t) {
+  walk_tiles<STREAM>(a, d, byg, bxg, [&](uint32_t by, uint32_t col_base, Tile& t) {
     if (t.full) fwd_tile<FMT, true, STREAM, MX, false, BASIS>(a.step_lo, a.step_hi, d, t, by, col_base, lane);
     else fwd_tile<FMT, false, STREAM, MX, false, BASIS>(a.step_lo, a.step_hi, d, t, by, col_base, lane);
   });
 }
 
-template <bool FULL, bool COPY, int BASIS = kBasisBits>
-__device__ __forceinline__ void bwd_tile(const LaunchArgs& a, const TileDesc& d, const Tile& t, uint32_t by,
+template <bool FULL, bool COPY, int STREAM, int BASIS, class ARGS>
+__device__ __forceinline__ void bwd_tile(const ARGS& a, const TileDesc& d, const Tile& t, uint32_t by,
                                          uint32_t col_base, uint32_t lane) {
   const uint32_t row_base = by * 32;
   const uint32_t gc = lane & 7, r0 = lane >> 3;
@@ -152,7 +165,7 @@ __device__ __forceinline__ void bwd_tile(const LaunchArgs& a, const TileDesc& d,
     const uint32_t row = row_base + r0 + 8 * i;
     if (COPY) {  // dL/dw = dL/dw_hat, bit for bit
       GWS_GLOBAL uint16_t* dst = dw + (size_t)row * d.ld + col;
-      if (FULL || t.nv[i] == 8) store16(dst, t.v[i]);
+      if (FULL || t.nv[i] == 8) store16<STREAM>(dst, t.v[i]);
       else store_partial(dst, t.v[i], t.nv[i]);
     }
     const u32x4 gv = (FULL || t.nv[i] == 8) ? t.v[i] : mask_group(t.v[i], t.nv[i]);
@@ -180,19 +193,19 @@ __device__ __forceinline__ void bwd_tile(const LaunchArgs& a, const TileDesc& d,
   }
 }
 
-template <int BASIS = kBasisBits>
-__global__ __launch_bounds__(kThreads) void sample_bwd_kernel(const LaunchArgs a) {
+template <int STREAM, int BASIS, class ARGS>
+__global__ __launch_bounds__(kThreads) void sample_bwd_kernel(const ARGS a) {
   uint32_t byg, bxg;
   const TileDesc d = locate(a, byg, bxg);
   const uint32_t lane = threadIdx.x & 63;
   const bool copy = d.p1 != nullptr;  // NULL: the pass-through is an alias
-  walk_tiles(a, d, byg, bxg, [&](uint32_t by, uint32_t col_base, Tile& t) {
+  walk_tiles<STREAM>(a, d, byg, bxg, [&](uint32_t by, uint32_t col_base, Tile& t) {
     if (t.full) {
-      if (copy) bwd_tile<true, true, BASIS>(a, d, t, by, col_base, lane);
-      else bwd_tile<true, false, BASIS>(a, d, t, by, col_base, lane);
+      if (copy) bwd_tile<true, true, STREAM, BASIS>(a, d, t, by, col_base, lane);
+      else bwd_tile<true, false, STREAM, BASIS>(a, d, t, by, col_base, lane);
     } else {
-      if (copy) bwd_tile<false, true, BASIS>(a, d, t, by, col_base, lane);
-      else bwd_tile<false, false, BASIS>(a, d, t, by, col_base, lane);
+      if (copy) bwd_tile<false, true, STREAM, BASIS>(a, d, t, by, col_base, lane);
+      else bwd_tile<false, false, STREAM, BASIS>(a, d, t, by, col_base, lane);
     }
   });
 }
@@ -200,8 +213,8 @@ __global__ __launch_bounds__(kThreads) void sample_bwd_kernel(const LaunchArgs a
 // The forward pass for tensors of whole tiles only (rows a multiple of 32, columns of 256): a workgroup walks
 // `tiles_per_wg_x` neighbouring column tiles of one block row, straight-line per tile, and keeps the row-only
 // share of its Philox calls across them.
-template <int FMT, bool MX, bool STREAM, int BASIS = kBasisBits>
-__global__ __launch_bounds__(kThreads) void sample_fwd_full_kernel(const LaunchArgs a) {
+template <int FMT, bool MX, int STREAM, int BASIS, class ARGS>
+__global__ __launch_bounds__(kThreads) void sample_fwd_full_kernel(const ARGS a) {
   uint32_t byg, bxg;
   const TileDesc d = locate(a, byg, bxg);
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -215,7 +228,7 @@ __global__ __launch_bounds__(kThreads) void sample_fwd_full_kernel(const LaunchA
   const PhiloxRows rp = philox_rows(rows, a.step_lo, d.seed_lo);
   for (uint32_t bx = bx0; bx < bx_end; ++bx) {
     const uint32_t col_base = bx * kTileCols + wave * 64;
-    Tile t = load_tile(src, d, byg, col_base, col_base + gc * 8, r0);   // always a whole tile here
+    Tile t = load_tile<STREAM>(src, d, byg, col_base, col_base + gc * 8, r0);   // always a whole tile here
     fwd_tile<FMT, true, STREAM, MX, false, BASIS>(a.step_lo, a.step_hi, d, t, byg, col_base, lane, 0.0f, &rp);
   }
 }
@@ -227,8 +240,8 @@ __global__ __launch_bounds__(kThreads) void sample_fwd_full_kernel(const LaunchA
 // tile (288 vector instructions per tile against about 330 in the kernel for any shape).  The next tile's loads
 // are issued after the current tile's arithmetic and complete under the next tile's Philox rounds; issuing them
 // a whole tile ahead was measured slower (16 more registers cost a wavefront of occupancy).
-template <int BASIS = kBasisBits>
-__global__ __launch_bounds__(kThreads) void sample_bwd_full_kernel(const LaunchArgs a) {
+template <int STREAM, int BASIS, class ARGS>
+__global__ __launch_bounds__(kThreads) void sample_bwd_full_kernel(const ARGS a) {
   uint32_t byg, bxg;
   const TileDesc d = locate(a, byg, bxg);
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -254,7 +267,7 @@ __global__ __launch_bounds__(kThreads) void sample_bwd_full_kernel(const LaunchA
   auto load4 = [&](uint32_t bx) {
     const GWS_GLOBAL uint16_t* p = row_ptr + (size_t)bx * kTileCols;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = load16(p + i * row_step);
+    for (int i = 0; i < 4; ++i) v[i] = load16<STREAM>(p + i * row_step);
     if (writer) {   // the block's writer lane fetches what it needs with the tile
       const size_t blk = (size_t)by * nbc + ((bx * kTileCols + wave * 64) >> 5) + (gc >> 2);
       s32 = scale[blk];
@@ -297,7 +310,7 @@ __global__ __launch_bounds__(kThreads) void copy_tiles_kernel(const LaunchArgs a
   const TileDesc d = locate(a, byg, bxg);
   const uint32_t lane = threadIdx.x & 63;
   GWS_GLOBAL uint16_t* __restrict__ dst = global_ptr<uint16_t>(d.p1);
-  walk_tiles(a, d, byg, bxg, [&](uint32_t by, uint32_t col_base, Tile& t) {
+  walk_tiles<kStreamAll>(a, d, byg, bxg, [&](uint32_t by, uint32_t col_base, Tile& t) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       if (t.nv[i] == 0) continue;
@@ -318,7 +331,7 @@ __global__ __launch_bounds__(kThreads) void block_absmax_kernel(const LaunchArgs
   const uint32_t gc = lane & 7, r0 = lane >> 3;
   GWS_GLOBAL float* __restrict__ out = global_ptr<float>(d.p3);
   const uint32_t nbc = (d.cols + 31) >> 5;
-  walk_tiles(a, d, byg, bxg, [&](uint32_t by, uint32_t col_base, Tile& t) {
+  walk_tiles<kStreamAll>(a, d, byg, bxg, [&](uint32_t by, uint32_t col_base, Tile& t) {
     uint32_t m = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) m = absmax_pk(t.nv[i] < 8 ? mask_group(t.v[i], t.nv[i]) : t.v[i], m);
@@ -353,43 +366,68 @@ __global__ __launch_bounds__(256) void noise_basis_kernel(u32x4* __restrict__ ou
 // ---------------------------------------------------------------------------
 // Host-side launchers
 // ---------------------------------------------------------------------------
-// the kernel of the call's whole-tile rule (variant 1) or the one for any shape
-template <int BASIS, int FMT, bool STREAM>
-static void launch_fwd_basis(const LaunchArgs& a, uint32_t n_wg, int variant, hipStream_t stream) {
-  if (variant == 1) hipLaunchKernelGGL((sample_fwd_full_kernel<FMT, false, STREAM, BASIS>), dim3(n_wg), dim3(kThreads), 0, stream, a);
-  else hipLaunchKernelGGL((sample_fwd_kernel<FMT, false, STREAM, BASIS>), dim3(n_wg), dim3(kThreads), 0, stream, a);
+template <int FMT, bool MX, int STREAM, int BASIS, class ARGS>
+static void launch_fwd(const ARGS& a, uint32_t n_wg, int variant, hipStream_t stream) {
+  if (variant == 1) hipLaunchKernelGGL((sample_fwd_full_kernel<FMT, MX, STREAM, BASIS, ARGS>), dim3(n_wg), dim3(kThreads), 0, stream, a);
+  else hipLaunchKernelGGL((sample_fwd_kernel<FMT, MX, STREAM, BASIS, ARGS>), dim3(n_wg), dim3(kThreads), 0, stream, a);
+}
+
+// One small weight (the call inside every sampled linear): five kilobytes of arguments and two dependent reads of them are
+// a fifth of such a kernel's time, 768 x 768 4.5 -> 3.6 us.
+static OneArgs one_of(const LaunchArgs& a) { return OneArgs{a.t[0], a.step_lo, a.step_hi, a.tiles_per_wg, a.tiles_per_wg_x}; }
+
+template <int FMT, bool MX, int BASIS>
+static void launch_fwd_stream(const LaunchArgs& a, uint32_t n_wg, int mode, int variant, hipStream_t stream) {
+  if (BASIS == kBasisBits && !MX && mode == kKeep && a.n == 1) launch_fwd<FMT, false, kKeep, kBasisBits>(one_of(a), n_wg, variant, stream);
+  else if (mode == kKeep) launch_fwd<FMT, MX, kKeep, BASIS>(a, n_wg, variant, stream);
+  else if (mode == kStreamReads) launch_fwd<FMT, MX, kStreamReads, BASIS>(a, n_wg, variant, stream);
+  else launch_fwd<FMT, MX, kStreamAll, BASIS>(a, n_wg, variant, stream);
 }
 
 template <int BASIS>
-static int launch_fwd_basis_fmt(const LaunchArgs& a, uint32_t n_wg, int fmt, bool keep, int variant, hipStream_t stream) {
+static int launch_fwd_fmt(const LaunchArgs& a, uint32_t n_wg, int fmt, int mode, int variant, hipStream_t stream) {
   switch (fmt) {
-    case GWS_FMT_BF16: keep ? launch_fwd_basis<BASIS, 0, false>(a, n_wg, variant, stream) : launch_fwd_basis<BASIS, 0, true>(a, n_wg, variant, stream); break;
-    case GWS_FMT_FP8_E4M3: keep ? launch_fwd_basis<BASIS, 1, false>(a, n_wg, variant, stream) : launch_fwd_basis<BASIS, 1, true>(a, n_wg, variant, stream); break;
-    case GWS_FMT_FP6_E3M2: keep ? launch_fwd_basis<BASIS, 2, false>(a, n_wg, variant, stream) : launch_fwd_basis<BASIS, 2, true>(a, n_wg, variant, stream); break;
+    case GWS_FMT_BF16: launch_fwd_stream<0, false, BASIS>(a, n_wg, mode, variant, stream); return GWS_OK;
+    case GWS_FMT_FP8_E4M3: launch_fwd_stream<1, false, BASIS>(a, n_wg, mode, variant, stream); return GWS_OK;
+    case GWS_FMT_FP6_E3M2: launch_fwd_stream<2, false, BASIS>(a, n_wg, mode, variant, stream); return GWS_OK;
     default: return GWS_ERR_FORMAT;
   }
+}
+
+int launch_sample_fwd(const LaunchArgs& a, uint32_t n_wg, int fmt, bool mx, int basis, int mode, int variant, hipStream_t stream) {
+  if (n_wg == 0) return GWS_OK;
+  int rc = GWS_OK;
+  if (mx && fmt == GWS_FMT_FP8_E4M3 && basis == kBasisBits) launch_fwd_stream<1, true, kBasisBits>(a, n_wg, mode, variant, stream);
+  else if (mx && fmt == GWS_FMT_FP6_E3M2 && basis == kBasisBits) launch_fwd_stream<2, true, kBasisBits>(a, n_wg, mode, variant, stream);
+  else if (mx) rc = GWS_ERR_FORMAT;
+  else if (basis == kBasisBits) rc = launch_fwd_fmt<kBasisBits>(a, n_wg, fmt, mode, variant, stream);
+  else if (basis == kBasisUniform) rc = launch_fwd_fmt<kBasisUniform>(a, n_wg, fmt, mode, variant, stream);
+  else if (basis == kBasisBoxMuller) rc = launch_fwd_fmt<kBasisBoxMuller>(a, n_wg, fmt, mode, variant, stream);
+  else rc = GWS_ERR_FORMAT;
+  if (rc != GWS_OK) return rc;
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
 
-int launch_sample_fwd_basis(const LaunchArgs& a, uint32_t n_wg, int fmt, bool keep, int basis, int variant, hipStream_t stream) {
-  if (n_wg == 0) return GWS_OK;
-  if (basis == kBasisUniform) return launch_fwd_basis_fmt<kBasisUniform>(a, n_wg, fmt, keep, variant, stream);
-  if (basis == kBasisBoxMuller) return launch_fwd_basis_fmt<kBasisBoxMuller>(a, n_wg, fmt, keep, variant, stream);
-  return GWS_ERR_FORMAT;
+template <int STREAM, int BASIS, class ARGS>
+static void launch_bwd(const ARGS& a, uint32_t n_wg, int variant, hipStream_t stream) {
+  if (variant == 1) hipLaunchKernelGGL((sample_bwd_full_kernel<STREAM, BASIS, ARGS>), dim3(n_wg), dim3(kThreads), 0, stream, a);
+  else hipLaunchKernelGGL((sample_bwd_kernel<STREAM, BASIS, ARGS>), dim3(n_wg), dim3(kThreads), 0, stream, a);
 }
 
 template <int BASIS>
-static void launch_bwd_any(const LaunchArgs& a, uint32_t n_wg, int variant, hipStream_t stream) {
-  if (variant == 1) hipLaunchKernelGGL(sample_bwd_full_kernel<BASIS>, dim3(n_wg), dim3(kThreads), 0, stream, a);
-  else hipLaunchKernelGGL(sample_bwd_kernel<BASIS>, dim3(n_wg), dim3(kThreads), 0, stream, a);
+static void launch_bwd_stream(const LaunchArgs& a, uint32_t n_wg, int mode, int variant, hipStream_t stream) {
+  if (BASIS == kBasisBits && mode == kKeep && a.n == 1) launch_bwd<kKeep, kBasisBits>(one_of(a), n_wg, variant, stream);
+  else if (mode == kKeep) launch_bwd<kKeep, BASIS>(a, n_wg, variant, stream);
+  else if (mode == kStreamReads) launch_bwd<kStreamReads, BASIS>(a, n_wg, variant, stream);
+  else launch_bwd<kStreamAll, BASIS>(a, n_wg, variant, stream);
 }
 
-int launch_sample_bwd(const LaunchArgs& a, uint32_t n_wg, int basis, int variant, hipStream_t stream) {
+int launch_sample_bwd(const LaunchArgs& a, uint32_t n_wg, int basis, int mode, int variant, hipStream_t stream) {
   if (n_wg == 0) return GWS_OK;
   switch (basis) {
-    case kBasisBits: launch_bwd_any<kBasisBits>(a, n_wg, variant, stream); break;
-    case kBasisUniform: launch_bwd_any<kBasisUniform>(a, n_wg, variant, stream); break;
-    case kBasisBoxMuller: launch_bwd_any<kBasisBoxMuller>(a, n_wg, variant, stream); break;
+    case kBasisBits: launch_bwd_stream<kBasisBits>(a, n_wg, mode, variant, stream); break;
+    case kBasisUniform: launch_bwd_stream<kBasisUniform>(a, n_wg, mode, variant, stream); break;
+    case kBasisBoxMuller: launch_bwd_stream<kBasisBoxMuller>(a, n_wg, mode, variant, stream); break;
     default: return GWS_ERR_FORMAT;
   }
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
@@ -408,40 +446,6 @@ int launch_noise_basis(void* out, uint32_t rows, uint32_t ngrp, uint32_t row0, u
   else return GWS_ERR_FORMAT;
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
-
-#define GWS_FWD_CASES(KERNEL)                                                                                             \
-  if (mx) {                                                                                                               \
-    switch (fmt) {                                                                                                        \
-      case GWS_FMT_FP8_E4M3: hipLaunchKernelGGL((KERNEL<1, true, true>), dim3(n_wg), dim3(kThreads), 0, stream, a); break;  \
-      case GWS_FMT_FP6_E3M2: hipLaunchKernelGGL((KERNEL<2, true, true>), dim3(n_wg), dim3(kThreads), 0, stream, a); break;  \
-      default: return GWS_ERR_FORMAT;                                                                                     \
-    }                                                                                                                     \
-  } else if (keep) {                                                                                                      \
-    switch (fmt) {                                                                                                        \
-      case GWS_FMT_BF16: hipLaunchKernelGGL((KERNEL<0, false, false>), dim3(n_wg), dim3(kThreads), 0, stream, a); break;    \
-      case GWS_FMT_FP8_E4M3: hipLaunchKernelGGL((KERNEL<1, false, false>), dim3(n_wg), dim3(kThreads), 0, stream, a); break; \
-      case GWS_FMT_FP6_E3M2: hipLaunchKernelGGL((KERNEL<2, false, false>), dim3(n_wg), dim3(kThreads), 0, stream, a); break; \
-      default: return GWS_ERR_FORMAT;                                                                                     \
-    }                                                                                                                     \
-  } else {                                                                                                                \
-    switch (fmt) {                                                                                                        \
-      case GWS_FMT_BF16: hipLaunchKernelGGL((KERNEL<0, false, true>), dim3(n_wg), dim3(kThreads), 0, stream, a); break;     \
-      case GWS_FMT_FP8_E4M3: hipLaunchKernelGGL((KERNEL<1, false, true>), dim3(n_wg), dim3(kThreads), 0, stream, a); break;  \
-      case GWS_FMT_FP6_E3M2: hipLaunchKernelGGL((KERNEL<2, false, true>), dim3(n_wg), dim3(kThreads), 0, stream, a); break;  \
-      default: return GWS_ERR_FORMAT;                                                                                     \
-    }                                                                                                                     \
-  }
-
-int launch_sample_fwd(const LaunchArgs& a, uint32_t n_wg, int fmt, bool mx, bool keep, int variant, hipStream_t stream) {
-  if (n_wg == 0) return GWS_OK;
-  if (variant == 1) {
-    GWS_FWD_CASES(sample_fwd_full_kernel)
-  } else {
-    GWS_FWD_CASES(sample_fwd_kernel)
-  }
-  return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
-}
-#undef GWS_FWD_CASES
 
 int launch_copy_tiles(const LaunchArgs& a, uint32_t n_wg, hipStream_t stream) {
   if (n_wg == 0) return GWS_OK;

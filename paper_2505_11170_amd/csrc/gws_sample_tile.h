@@ -15,11 +15,18 @@ __device__ __forceinline__ int valid_count(uint32_t row, uint32_t col, uint32_t 
   return left >= 8 ? 8 : (int)left;
 }
 
+// Streaming (non-temporal) or ordinary accesses.  STREAM = kKeep: everything stays in the caches, right for a call whose output
+// is read at once and for rows that do not start on cache lines (a line written in two halves is put together in L2; written
+// past it, each half costs a partial write); kStreamReads: what is read streams past the caches; kStreamAll: writes too.
+template <int STREAM = kStreamAll>
 __device__ __forceinline__ u32x4 load16(const GWS_GLOBAL uint16_t* p) {
-  return __builtin_nontemporal_load((const GWS_GLOBAL u32x4*)p);
+  if (STREAM != kKeep) return __builtin_nontemporal_load((const GWS_GLOBAL u32x4*)p);
+  return *(const GWS_GLOBAL u32x4*)p;
 }
+template <int STREAM = kStreamAll>
 __device__ __forceinline__ void store16(GWS_GLOBAL uint16_t* p, const u32x4 v) {
-  __builtin_nontemporal_store(v, (GWS_GLOBAL u32x4*)p);
+  if (STREAM == kStreamAll) __builtin_nontemporal_store(v, (GWS_GLOBAL u32x4*)p);
+  else *(GWS_GLOBAL u32x4*)p = v;
 }
 
 // Zero the elements of a group that lie past the right edge (nv valid of 8).
@@ -44,6 +51,7 @@ struct Tile {
 };
 
 // A 16-byte load never leaves its row: ld % 8 == 0 and ld >= cols.
+template <int STREAM = kStreamAll>
 __device__ __forceinline__ Tile load_tile(const GWS_GLOBAL uint16_t* __restrict__ src, const TileDesc& d, uint32_t by,
                                           uint32_t col_base, uint32_t col, uint32_t r0) {
   Tile t;
@@ -53,7 +61,7 @@ __device__ __forceinline__ Tile load_tile(const GWS_GLOBAL uint16_t* __restrict_
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       t.nv[i] = 8;
-      t.v[i] = load16(src + (size_t)(row_base + r0 + 8 * i) * d.ld + col);
+      t.v[i] = load16<STREAM>(src + (size_t)(row_base + r0 + 8 * i) * d.ld + col);
     }
   } else {
 #pragma unroll
@@ -61,7 +69,7 @@ __device__ __forceinline__ Tile load_tile(const GWS_GLOBAL uint16_t* __restrict_
       const uint32_t row = row_base + r0 + 8 * i;
       t.nv[i] = valid_count(row, col, d.rows, d.cols);
       t.v[i] = u32x4{0, 0, 0, 0};
-      if (t.nv[i] > 0) t.v[i] = load16(src + (size_t)row * d.ld + col);
+      if (t.nv[i] > 0) t.v[i] = load16<STREAM>(src + (size_t)row * d.ld + col);
     }
   }
   return t;
@@ -70,13 +78,14 @@ __device__ __forceinline__ Tile load_tile(const GWS_GLOBAL uint16_t* __restrict_
 // Element codes of one group to memory.  FP8: 8 bytes at column col.  FP6: 6 bytes at
 // (col / 8) * 6, written as three 2-byte stores (a row of codes is only 2-byte aligned).
 // nv < 8: only the bytes that hold existing elements (unused bits of the last one are 0).
-template <int FMT>
+template <int FMT, int STREAM>
 __device__ __forceinline__ void store_codes(GWS_GLOBAL uint8_t* row, uint32_t col, const MxCodes c, int nv) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
   if (FMT == 1) {
     GWS_GLOBAL uint8_t* dst = row + col;
     if (nv == 8) {
-      typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-      __builtin_nontemporal_store(u32x2{c.lo, c.hi}, (GWS_GLOBAL u32x2*)dst);
+      if (STREAM == kStreamAll) __builtin_nontemporal_store(u32x2{c.lo, c.hi}, (GWS_GLOBAL u32x2*)dst);
+      else *(GWS_GLOBAL u32x2*)dst = u32x2{c.lo, c.hi};
     } else {
 #pragma unroll
       for (int k = 0; k < 8; ++k)
@@ -86,9 +95,9 @@ __device__ __forceinline__ void store_codes(GWS_GLOBAL uint8_t* row, uint32_t co
     GWS_GLOBAL uint8_t* dst = row + (col >> 3) * 6;
     if (nv == 8) {
       GWS_GLOBAL uint16_t* d16 = (GWS_GLOBAL uint16_t*)dst;
-      __builtin_nontemporal_store((uint16_t)c.lo, d16);
-      __builtin_nontemporal_store((uint16_t)(c.lo >> 16), d16 + 1);
-      __builtin_nontemporal_store((uint16_t)c.hi, d16 + 2);
+      d16[0] = (uint16_t)c.lo;
+      d16[1] = (uint16_t)(c.lo >> 16);
+      d16[2] = (uint16_t)c.hi;
     } else {
       // the fields of elements past the edge hold noise: clear them
       const uint64_t bits = (((uint64_t)c.hi << 32) | c.lo) & (((uint64_t)1 << (6 * nv)) - 1);
@@ -100,6 +109,46 @@ __device__ __forceinline__ void store_codes(GWS_GLOBAL uint8_t* row, uint32_t co
   }
 }
 
+// The FP6 codes of a whole tile whose rows of codes are 4-byte aligned.  A lane holds 48 bits of each of its four rows
+// r0 + 8 i; within each quad of lanes (four column groups side by side) the 4 x 4 pieces are exchanged, so that a lane
+// ends up with the 24 consecutive bytes of one row (row r0 + 8 (lane % 4)) and writes them with two stores instead of
+// twelve: 352 M parameters 219 -> 217 us (the vector ALU, not the stores, bounds the pass).
+__device__ __forceinline__ void store_codes_fp6_quad(GWS_GLOBAL uint8_t* tile_row0, uint32_t ldc, uint32_t lane,
+                                                     const uint32_t (&c)[6]) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  // piece i = 32 low bits lo[i] and 16 high bits: of pieces 0, 1 in h01, of pieces 2, 3 in h23
+  uint32_t lo[4] = {c[0], __builtin_amdgcn_alignbit(c[2], c[1], 16), c[3], __builtin_amdgcn_alignbit(c[5], c[4], 16)};
+  const uint32_t h01 = __builtin_amdgcn_perm(c[2], c[1], 0x07060100u), h23 = __builtin_amdgcn_perm(c[5], c[4], 0x07060100u);
+  const bool odd = lane & 1, upper = lane & 2;
+  // lane q of a quad collects piece q of every lane: exchange with lane ^ 1, then with lane ^ 2
+#pragma unroll
+  for (int i = 0; i < 4; i += 2) {
+    const uint32_t a = lo[i], b = lo[i + 1], pa = dpp_u32<0xB1>(a), pb = dpp_u32<0xB1>(b);
+    lo[i] = odd ? pb : a;       // from the even lane of the pair
+    lo[i + 1] = odd ? b : pa;   // from the odd one
+  }
+  // now lo[i + j] is piece i + lane % 2 of lane (pair base) + j, i = 0, 2
+  uint32_t l[4];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const uint32_t a = lo[j], b = lo[2 + j], pa = dpp_u32<0x4E>(a), pb = dpp_u32<0x4E>(b);
+    l[j] = upper ? pb : a;       // lane j of the quad
+    l[2 + j] = upper ? b : pa;   // lane 2 + j
+  }
+  const uint32_t p01 = dpp_u32<0x4E>(h01), p23 = dpp_u32<0x4E>(h23);
+  const uint32_t first = upper ? p23 : h01, second = upper ? h23 : p01;   // pieces of the lower and the upper lane of {q, q ^ 2}
+  const uint32_t pf = dpp_u32<0xB1>(first), ps = dpp_u32<0xB1>(second);
+  // halves of this lane's and its neighbour's word, the even lane's first: bytes 0-3 of v_perm are the second operand's
+  const uint32_t sel = odd ? 0x07060302u : 0x05040100u;
+  const uint32_t g01 = odd ? __builtin_amdgcn_perm(first, pf, sel) : __builtin_amdgcn_perm(pf, first, sel);
+  const uint32_t g23 = odd ? __builtin_amdgcn_perm(second, ps, sel) : __builtin_amdgcn_perm(ps, second, sel);
+  GWS_GLOBAL uint8_t* dst = tile_row0 + (size_t)((lane >> 3) + 8 * (lane & 3)) * ldc + (lane & 4) * 6;
+  typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
+  typedef uint32_t u32x2a4 __attribute__((ext_vector_type(2), aligned(4)));
+  *(GWS_GLOBAL u32x4a4*)dst = u32x4{l[0], __builtin_amdgcn_perm(l[1], g01, 0x05040100u), __builtin_amdgcn_perm(g01, l[1], 0x07060302u), l[2]};
+  *(GWS_GLOBAL u32x2a4*)(dst + 16) = u32x2{__builtin_amdgcn_perm(l[3], g23, 0x05040100u), __builtin_amdgcn_perm(g23, l[3], 0x07060302u)};
+}
+
 // The forward pass on one wavefront tile, in two phases.
 //
 // tile_scale: a = max|w| of the lane's block (exact), the block's scale and cast constants.
@@ -107,8 +156,7 @@ __device__ __forceinline__ void store_codes(GWS_GLOBAL uint8_t* row, uint32_t co
 //   through several tiles alone does together with the tile loads, so that its latency is not paid per tile.
 //   STORE: the block's writer lane stores scale (and, MX, the E8M0 block scale) here; off, the caller does.
 // tile_apply: noise, add, round, cast, store.
-//   STREAM: w_hat is written with streaming (non-temporal) stores, right for a pass that is not consumed at
-//   once; off, the stores stay in cache for a reader that follows.
+//   STREAM: see load16.
 //   MX: the output is element codes (p1, row stride ldc) and E8M0 block scales (p4) instead of the BF16 container.
 //   BASIS: kBasisBits is the method's noise (Sec. 3.4); the other two are the comparison bases (no MX form).
 //   USE_HW: FP8-E4M3 through the hardware converters (the caller has shown that no block of the wavefront can
@@ -153,7 +201,7 @@ __device__ __forceinline__ BlockScale tile_scale(const TileDesc& d, Tile& t, uin
   return b;
 }
 
-template <int FMT, bool FULL, bool STREAM, bool MX, int BASIS, bool USE_HW>
+template <int FMT, bool FULL, int STREAM, bool MX, int BASIS, bool USE_HW>
 __device__ __forceinline__ void tile_apply(uint32_t step_lo, uint32_t step_hi, const TileDesc& d, const Tile& t,
                                            const BlockScale& b, uint32_t by, uint32_t col_base, uint32_t lane,
                                            const PhiloxRows* rows_part, const Philox4* bits) {
@@ -175,11 +223,11 @@ __device__ __forceinline__ void tile_apply(uint32_t step_lo, uint32_t step_hi, c
   auto sampled_group = [&](const u32x4 w, uint32_t row, int i, uint32_t (&pk)[4]) {
     if constexpr (BASIS == kBasisBits) {
       const Noise n = noise_planes(bits_of(row, i));
-      const GroupMagnitudes g = group_magnitudes(n);
-      pk[0] = sampled_pair<0>(w[0], g, n, b);
-      pk[1] = sampled_pair<1>(w[1], g, n, b);
-      pk[2] = sampled_pair<2>(w[2], g, n, b);
-      pk[3] = sampled_pair<3>(w[3], g, n, b);
+      const GroupR g = group_r(n);
+      pk[0] = sampled_pair<0>(w[0], g, b);
+      pk[1] = sampled_pair<1>(w[1], g, b);
+      pk[2] = sampled_pair<2>(w[2], g, b);
+      pk[3] = sampled_pair<3>(w[3], g, b);
     } else {
       sampled_group_basis<BASIS>(w, bits_of(row, i), b, pk);
     }
@@ -192,7 +240,7 @@ __device__ __forceinline__ void tile_apply(uint32_t step_lo, uint32_t step_hi, c
       if constexpr (MX) {
         const Noise n = noise_planes(bits_of(d.row0 + row, i));
         const MxCodes c = sample_group_mx_fp8(t.v[i], n, b, USE_HW);
-        store_codes<FMT>(global_ptr<uint8_t>(d.p1) + (size_t)row * d.ldc, col, c, FULL ? 8 : t.nv[i]);
+        store_codes<FMT, STREAM>(global_ptr<uint8_t>(d.p1) + (size_t)row * d.ldc, col, c, FULL ? 8 : t.nv[i]);
       } else {
         uint32_t pk[4];
         sampled_group(t.v[i], d.row0 + row, i, pk);
@@ -201,8 +249,7 @@ __device__ __forceinline__ void tile_apply(uint32_t step_lo, uint32_t step_hi, c
                          cast_pair<FMT>(pk[2], b, USE_HW, chain), cast_pair<FMT>(pk[3], b, USE_HW, chain)};
         GWS_GLOBAL uint16_t* dst = w_hat + (size_t)row * d.ld + col;
         if (FULL || t.nv[i] == 8) {
-          if (STREAM) store16(dst, o);
-          else *(GWS_GLOBAL u32x4*)dst = o;
+          store16<STREAM>(dst, o);
         } else {
           store_partial(dst, o, t.nv[i]);
         }
@@ -232,7 +279,10 @@ __device__ __forceinline__ void tile_apply(uint32_t step_lo, uint32_t step_hi, c
     bf16x32 v;
     __builtin_memcpy(&v, pk, 64);
     const u32x6 c = __builtin_amdgcn_cvt_scalef32_pk32_bf6_bf16(v, b.x_scale);
-    if constexpr (MX) {
+    if (MX && FULL && (((uint32_t)(uintptr_t)d.p1 | d.ldc) & 3) == 0) {   // uniform
+      const uint32_t cw[6] = {c[0], c[1], c[2], c[3], c[4], c[5]};
+      store_codes_fp6_quad(global_ptr<uint8_t>(d.p1) + (size_t)row_base * d.ldc + (col_base >> 3) * 6, d.ldc, lane, cw);
+    } else if constexpr (MX) {
       // element k of the lane's 32 sits in bits [6k, 6k + 6): 48 bits per group
       const MxCodes gc4[4] = {{c[0], c[1] & 0xFFFFu},
                               {(c[1] >> 16) | (c[2] << 16), c[2] >> 16},
@@ -242,7 +292,7 @@ __device__ __forceinline__ void tile_apply(uint32_t step_lo, uint32_t step_hi, c
       for (int i = 0; i < 4; ++i) {
         if (!FULL && t.nv[i] == 0) continue;
         const uint32_t row = row_base + r0 + 8 * i;
-        store_codes<FMT>(global_ptr<uint8_t>(d.p1) + (size_t)row * d.ldc, col, gc4[i], FULL ? 8 : t.nv[i]);
+        store_codes<FMT, STREAM>(global_ptr<uint8_t>(d.p1) + (size_t)row * d.ldc, col, gc4[i], FULL ? 8 : t.nv[i]);
       }
     } else {
       const bf16x32 q = __builtin_amdgcn_cvt_scalef32_pk32_bf16_bf6(c, b.x_scale);
@@ -255,8 +305,7 @@ __device__ __forceinline__ void tile_apply(uint32_t step_lo, uint32_t step_hi, c
         const u32x4 og = {o[4 * i], o[4 * i + 1], o[4 * i + 2], o[4 * i + 3]};
         GWS_GLOBAL uint16_t* dst = w_hat + (size_t)row * d.ld + col;
         if (FULL || t.nv[i] == 8) {
-          if (STREAM) store16(dst, og);
-          else *(GWS_GLOBAL u32x4*)dst = og;
+          store16<STREAM>(dst, og);
         } else {
           store_partial(dst, og, t.nv[i]);
         }
@@ -267,7 +316,7 @@ __device__ __forceinline__ void tile_apply(uint32_t step_lo, uint32_t step_hi, c
 
 // Both phases for one tile; FP8-E4M3 takes the hardware converters only if neither block of this wavefront can
 // overflow (they give NaN where the cast saturates).
-template <int FMT, bool FULL, bool STREAM = true, bool MX = false, bool BT_PRE = false, int BASIS = kBasisBits>
+template <int FMT, bool FULL, int STREAM = kStreamAll, bool MX = false, bool BT_PRE = false, int BASIS = kBasisBits>
 __device__ __forceinline__ void fwd_tile(uint32_t step_lo, uint32_t step_hi, const TileDesc& d, Tile& t,
                                          uint32_t by, uint32_t col_base, uint32_t lane, float bt_pre = 0.0f,
                                          const PhiloxRows* rows_part = nullptr) {

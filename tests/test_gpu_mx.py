@@ -156,3 +156,9 @@ def test_random_mix_of_many_small_and_ragged_tensors(fmt):
     shapes[3] = (0, 17)
     shapes[9] = (32, 256)
     check_mx(make_items(shapes, 2000 + 100 * fmt, user_seed=fmt), fmt, 6, pad=1)
+
+
+@pytest.mark.parametrize("pad", [0, 1, 2, 3])
+def test_fp6_codes_of_whole_tiles_at_every_row_alignment(pad):
+    # whole 32 x 64 tiles leave as 24 bytes a lane where rows of codes are 4-byte aligned (pad 0, 2), else in 2-byte pieces
+    check_mx(make_items([(32, 64), (64, 256), (96, 832), (160, 512)], 460), gws.FMT_FP6_E3M2, 4, pad=pad)

@@ -307,3 +307,35 @@ def test_launch_shape_choices_give_the_same_bytes():
     d = descs[1]
     ref_q, ref_s = oracle.sample_fwd(synth.bits(d.w), d.bt.cpu().numpy(), oracle.FMT_FP8_E4M3, d.seed, 4, cols=d.cols, row0=d.row0, col0=d.col0)
     assert (synth.bits(d.w_hat) == ref_q).all()
+
+
+@pytest.mark.parametrize("shape", [(768, 768), (32, 256), (96, 300), (1000, 1000), (1, 8)])
+def test_one_weight_alone(shape):
+    # a small call of one tensor has kernels of its own (descriptor in the kernel's arguments); whole tiles and ragged
+    items = make_items([shape], base=880)
+    (_, items[0]["scale"]), = check_forward(items, gws.FMT_FP8_E4M3, 6)
+    check_backward(items, 6, dw_mode="alias")
+    check_backward(items, 6)
+
+
+def test_large_calls_give_the_bytes_of_small_ones():
+    # 7 x 33.6 MB in rows of 8200 bytes (not whole cache lines: ordinary stores, streaming loads) and in rows of 8320
+    # (whole lines, streaming both ways) against the same weights one at a time (ordinary accesses)
+    for ld in (4104, 4160):
+        gen = torch.Generator(device=DEV).manual_seed(ld)
+        w = [(torch.randn(4100, ld, generator=gen, device=DEV) * 0.02).to(torch.bfloat16) for _ in range(7)]
+        bt = 4 + 5 * torch.rand(129, 129, generator=gen, device=DEV)
+
+        def descs():
+            return [gws.TensorDesc(rows=4100, cols=4100, ld=ld, seed=30 + i, w=w[i], bt=bt, w_hat=torch.zeros_like(w[i]), scale=torch.zeros_like(bt),
+                                   g=w[i], dw=torch.zeros_like(w[i]), dbt=torch.zeros_like(bt)) for i in range(7)]
+        a, b = descs(), descs()
+        gws.gws_sample_fwd(a, gws.FMT_FP6_E3M2, 3)
+        gws.gws_sample_bwd(a, 3)
+        for d in b:
+            gws.gws_sample_fwd([d], gws.FMT_FP6_E3M2, 3)
+            gws.gws_sample_bwd([d], 3)
+        torch.cuda.synchronize()
+        for x, y in zip(a, b):
+            assert torch.equal(x.w_hat.view(torch.int16), y.w_hat.view(torch.int16)) and torch.equal(x.scale, y.scale)
+            assert torch.equal(x.dw[:, :4100].view(torch.int16), x.g[:, :4100].view(torch.int16)) and torch.equal(x.dbt, y.dbt)
