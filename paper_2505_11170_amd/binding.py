@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from dataclasses import dataclass
 from typing import Optional, Sequence
 
@@ -174,13 +175,21 @@ def status_string(status: int) -> str:
 
 
 def _p(t) -> Optional[int]:
-    return None if t is None else int(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_current_raw_stream = None   # torch's getters of the current device and its stream's handle, once torch is there
 
 
 def _stream(stream) -> Optional[int]:
+    global _current_raw_stream
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
+        if _current_raw_stream is None:
+            import torch
+            torch.cuda.current_stream()   # initialises the device runtime
+            device, raw = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+            _current_raw_stream = lambda: raw(device())
+        return _current_raw_stream() or None
     if isinstance(stream, int):
         return stream or None
     return int(stream.cuda_stream) or None
@@ -209,18 +218,26 @@ def _as_c(t):
     return _marshal(t), len(t)
 
 
+_CTensor1 = _CTensor * 1
+_pack_tensor = struct.Struct("=7Q5qQ").pack   # the fields of _CTensor in one go (field by field takes four times as long)
+assert struct.calcsize("=7Q5qQ") == ctypes.sizeof(_CTensor)
+
+
 def _marshal(descs: Sequence[TensorDesc]):
-    arr = (_CTensor * max(1, len(descs)))()
-    for c, d in zip(arr, descs):
+    if not descs:
+        return _CTensor1()
+    parts = []
+    for d in descs:
+        w, g, dw = d.w, d.g, d.dw
         ld = d.ld
         if ld is None:
-            ref = next((t for t in (d.w, d.g, d.dw) if t is not None), None)
-            ld = int(ref.stride(0)) if ref is not None and ref.dim() == 2 else d.cols
-        c.w, c.w_hat, c.bt, c.scale = _p(d.w), _p(d.w_hat), _p(d.bt), _p(d.scale)
-        c.g, c.dw, c.dbt = _p(d.g), _p(d.dw), _p(d.dbt)
-        c.rows, c.cols, c.ld, c.row0, c.col0 = d.rows, d.cols, ld, d.row0, d.col0
-        c.seed = d.seed & (2 ** 64 - 1)
-    return arr
+            ref = w if w is not None else g if g is not None else dw
+            ld = ref.stride(0) if ref is not None and ref.dim() == 2 else d.cols
+        parts.append(_pack_tensor(_p(w) or 0, _p(d.w_hat) or 0, _p(d.bt) or 0, _p(d.scale) or 0, _p(g) or 0, _p(dw) or 0, _p(d.dbt) or 0,
+                                  d.rows, d.cols, ld, d.row0, d.col0, d.seed & 0xFFFFFFFFFFFFFFFF))
+    if len(parts) == 1:
+        return _CTensor1.from_buffer_copy(parts[0])
+    return (_CTensor * len(parts)).from_buffer_copy(b"".join(parts))
 
 
 def _check(rc: int, what: str):
