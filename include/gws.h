@@ -172,8 +172,8 @@ int gws_sample_fwd_mx(const gws_tensor* t, const gws_mx_out* o, int n, int fmt, 
  *                           wavefronts, else 128).  Any shape; w_hat/scale optional.
  *   GWS_LINEAR_TWO_KERNELS  the sampling kernel of gws_sample_fwd, then the plain GEMM on w_hat.
  *                           Needs w_hat/scale (GWS_ERR_NULL otherwise).
- *   GWS_LINEAR_AUTO         two kernels when w_hat/scale are given (the faster choice at every M
- *                           as measured on MI355X), else in-operand.
+ *   GWS_LINEAR_AUTO         when w_hat/scale are given the faster of the two by an estimate on the
+ *                           sizes (in-operand for a few rows of X, else two kernels), else in-operand.
  * (Mode value 1 belonged to a retired kernel and is rejected with GWS_ERR_FORMAT.)
  * gws_linear_fwd is gws_linear_fwd_mode with GWS_LINEAR_AUTO.                              */
 #define GWS_LINEAR_AUTO 0
@@ -188,7 +188,8 @@ int gws_linear_fwd_mode(const void* x, int64_t M, int64_t K, int64_t ldx,
 
 /* gws_linear_fwd for a caller that wants Y only and many rows of X (Sec. 3.5 keeps sampling and
  * matmul apart; so does this): w_hat and scale are staged in `workspace` instead of the caller's
- * buffers (w->w_hat and w->scale are not used), then the plain GEMM runs on the staged w_hat.
+ * buffers (w->w_hat and w->scale are not used), then the plain GEMM runs on the staged w_hat (for a few
+ * rows of X the sampling may sit in the operand load instead and nothing is staged).
  * Y is bit-identical to gws_linear_fwd's.
  *   workspace       : device, 256-byte aligned, owned by the caller; contents undefined afterwards;
  *                     must not overlap x, y or w->w (GWS_ERR_ALIAS)

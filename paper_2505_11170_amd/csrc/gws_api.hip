@@ -270,9 +270,10 @@ int linear_staged(const void* x, int64_t M, int64_t K, int64_t ldx, const gws_te
   const size_t w_bytes = (size_t)w->rows * w->ld * 2, need = staged_bytes(*w) + (size_t)((w->rows + 31) / 32) * ((w->cols + 31) / 32) * 4;
   if (overlap2(staging, need, w->w, w_bytes) || overlap2(staging, need, x, (size_t)M * ldx * 2) ||
       overlap2(staging, need, y, (size_t)M * ldy * 2)) return GWS_ERR_ALIAS;
+  GemmArgs g = linear_args(x, M, K, ldx, w, w_is_nk, step, y, ldy);
+  if (sample_in_operand(g, w_is_nk)) return launch_gemm(g, w_is_nk, kFusedInOperand, fmt, stream);   // nothing to stage
   int rc = run_batched(&t, 1, nullptr, nullptr, true, fmt, step, stream, /*keep=*/true);
   if (rc != GWS_OK) return rc;
-  GemmArgs g = linear_args(x, M, K, ldx, w, w_is_nk, step, y, ldy);
   g.w = (const uint16_t*)staging;
   return launch_gemm(g, w_is_nk, 0, GWS_FMT_BF16, stream);
 }
@@ -469,10 +470,9 @@ int gws_linear_fwd_mode(const void* x, int64_t M, int64_t K, int64_t ldx, const 
   GemmArgs g = linear_args(x, M, K, ldx, w, w_is_nk, step, y, ldy);
   g.scale = w->scale; g.w_hat = (uint16_t*)w->w_hat;
   if (mode == GWS_LINEAR_AUTO) {
-    // Measured on MI355X: sampling the weight once with the streaming kernel and running the plain GEMM on
-    // w_hat beats the kernel that samples in its operand load at every M (8192 tokens: 0.155 against 0.61 ms;
-    // 16 .. 128 tokens: 28 .. 76 us against 40 .. 125 us for weights of 768 x 768 .. 2048 x 5632).
-    mode = w->w_hat ? GWS_LINEAR_TWO_KERNELS : GWS_LINEAR_IN_OPERAND;
+    // Measured on MI355X: sampling the weight once with the streaming kernel and running the plain GEMM on w_hat beats the
+    // kernel that samples in its operand load (8192 tokens: 0.155 against 0.61 ms) except for a few tokens.
+    mode = w->w_hat && !sample_in_operand(g, w_is_nk) ? GWS_LINEAR_TWO_KERNELS : GWS_LINEAR_IN_OPERAND;
   }
   if (mode == GWS_LINEAR_TWO_KERNELS) {
     if (!w->w_hat) return GWS_ERR_NULL;

@@ -108,6 +108,7 @@ struct RoutePlan {   // estimates in us; 1e30: not a shape for that kernel
   double middle_us, large_us;
 };
 GemmRoute gemm_route(const GemmArgs& g, int w_is_nk, RoutePlan& plan);
+bool sample_in_operand(const GemmArgs& g, int w_is_nk);   // the faster way to a sampled product (same bits either way)
 bool gemm256_edge_applicable(const GemmArgs& g);
 int launch_gemm256_edge(const GemmArgs& g, int w_is_nk, hipStream_t stream);
 bool gemm128_applicable(const GemmArgs& g);

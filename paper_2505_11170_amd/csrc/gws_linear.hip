@@ -211,6 +211,20 @@ GemmRoute gemm_route(const GemmArgs& g, int w_is_nk, RoutePlan& plan) {
   return plan.middle_us < plan.large_us ? GemmRoute::kMiddle : GemmRoute::kLarge;
 }
 
+// Whether sampling in the operand load beats the sampling kernel and the GEMM behind it: one tile of rows of X (every block
+// is then sampled once in either form), where the vector ALU work on the N / 32 workgroups' compute units is shorter than a
+// kernel over all of them plus a launch.  Estimates in us from MI355X timings (M = 16 / 64, in-operand and two kernels):
+// 512 x 512 7.0 / 6.5 and 9.5; 1024 x 3072 8.3 / 10.0 and 10.6 / 11.1; 2304 x 800 14.8 / 17.0 and 11.3 / 12.5; 2048 x 5632
+// 14.7 / 20.1 and 19.0 / 19.7.  A wavefront takes 1.2 a block, with more than 16 rows 1.6; the sampling kernel 3.4 and 0.65
+// a million elements, the gap to the next launch 1.5.
+bool sample_in_operand(const GemmArgs& g, int w_is_nk) {
+  RoutePlan plan;
+  if (g.M > 64 || gemm_route(g, w_is_nk, plan) != GemmRoute::kStream) return false;
+  const double cus = compute_units() > 0 ? compute_units() : 256;
+  const double fused = 3.3 + (g.M <= 16 ? 1.2 : 1.6) * ceil(g.K / 32.0 / plan.stream.p) * ceil(g.N / 32.0 / cus);
+  return fused < 0.95 * (3.4 + 0.65e-6 * g.K * g.N + 1.5 + plan.stream.us);
+}
+
 int launch_gemm(const GemmArgs& g, int w_is_nk, int fused, int fmt, hipStream_t stream) {
   const uint64_t tiles = (uint64_t)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   if (tiles == 0) return GWS_OK;

@@ -359,6 +359,7 @@ def test_gemm_that_splits_k(M, K, N, w_is_nk):
     rows_sel = None if M * K * N < 2e7 else np.array(sorted({0, 15 % M, M // 2, M - 1}))
     run_case(M, K, N, w_is_nk, gws.FMT_FP8_E4M3, seed_id=idx, ldx_pad=8, ldy_pad=8, rows_sel=rows_sel, mode=gws.LINEAR_IN_OPERAND)
     run_case(M, K, N, w_is_nk, gws.FMT_FP6_E3M2 if M % 2 else gws.FMT_BF16, seed_id=idx, step=2, rows_sel=rows_sel, mode=gws.LINEAR_IN_OPERAND)
+    run_case(M, K, N, w_is_nk, gws.FMT_FP8_E4M3, seed_id=idx, step=4, rows_sel=rows_sel)   # the library's choice between the two forms
 
 
 def test_riding_under_a_gemm_of_many_k_steps():
