@@ -102,36 +102,66 @@ __global__ __launch_bounds__(256, 1) void gemm256_tn_part_kernel(const GemmArgs 
   });
 }
 
-// One wavefront per workgroup, one half (64 x 128) of a wavefront's part of a tile each: eight workgroups per tile,
-// so that a weight of 64 tiles spreads over the chip here too (the work is loads and little else).
+// One wavefront per 32 x 32 block of the weight: it takes the block's four registers of every part's slab (all of them
+// requested before the first is added), so that a few dozen tiles still make thousands of wavefronts.  Bound by the slabs'
+// bytes out of the last-level cache; with one wavefront per 64 x 128 (288 for 36 tiles) the loads' latency was: 768 x 3072,
+// seven parts, 66 MB: 19.0 us, 12.3 like this.
+constexpr uint32_t kMaxParts = 8;
+
 template <bool DBT>
-__global__ __launch_bounds__(64) void gemm256_tn_sum_kernel(const GemmArgs g, const float* __restrict__ ws, const uint32_t parts) {
+__global__ __launch_bounds__(256) void gemm256_tn_sum_kernel(const GemmArgs g, const float* __restrict__ ws, const uint32_t parts) {
   using namespace g256;
-  __shared__ __attribute__((aligned(16))) uint16_t stage[64 * PC];
-  const uint32_t tiles = (g.M / TM) * (g.N / TN);
-  const uint32_t L = blockIdx.x >> 3, wave = (blockIdx.x >> 1) & 3, h = blockIdx.x & 1, lane = threadIdx.x;
+  constexpr uint32_t PB = 32 + 8;   // pitch of a block's staged rows (elements)
+  __shared__ __attribute__((aligned(16))) uint16_t stage[4 * 32 * PB];
+  const uint32_t tiles = (g.M / TM) * (g.N / TN), lane = threadIdx.x & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // workgroup: 32 rows (br) of one 128-column half (wn) of a tile; wavefront: 32 columns of it
+  const uint32_t L = blockIdx.x >> 4, br = (blockIdx.x >> 1) & 7, wn = blockIdx.x & 1;
   uint32_t tile_m, tile_n;
   tile_of(L, g.M / TM, g.N / TN, tile_m, tile_n);
-  const uint32_t p0 = tile_m * TM + 128 * (wave >> 1), q0 = tile_n * TN + 128 * (wave & 1);
-  f32x4 a4[4][8];
+  const uint32_t p0 = tile_m * TM + 32 * br, q0 = tile_n * TN + 128 * wn + 32 * wave;
+  // register (i, j) of the accumulating wavefront 2 (br / 4) + wn: i = 2 (br % 4) + ii, j = 2 wave + jj
+  const f32x4* in = reinterpret_cast<const f32x4*>(ws) + ((size_t)L * 4 + 2 * (br >> 2) + wn) * 4096 + (2 * (br & 3) * 8 + 2 * wave) * 64 + lane;
+  const size_t step = (size_t)tiles * (kSlabFloats / 4);
+  f32x4 v[kMaxParts][4];
 #pragma unroll
-  for (int i2 = 0; i2 < 4; ++i2)
+  for (uint32_t s = 0; s < kMaxParts; ++s)
+    if (s < parts) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) a4[i2][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  for (uint32_t s = 0; s < parts; ++s) {
-    const f32x4* in = reinterpret_cast<const f32x4*>(ws + ((size_t)s * tiles + L) * kSlabFloats) + (size_t)wave * 64 * 64 + lane;
+      for (int r = 0; r < 4; ++r) v[s][r] = in[s * step + ((r >> 1) * 8 + (r & 1)) * 64];
+    }
+  uint16_t* cs = stage + wave * 32 * PB;
 #pragma unroll
-    for (int i2 = 0; i2 < 4; ++i2)
+  for (int r = 0; r < 4; ++r) {
+    f32x4 a = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const f32x4 v = in[((4 * h + i2) * 8 + j) * 64];
+    for (uint32_t s = 0; s < kMaxParts; ++s)
+      if (s < parts) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) a4[i2][j][e] = __fadd_rn(a4[i2][j][e], v[e]);
+        for (int e = 0; e < 4; ++e) a[e] = __fadd_rn(a[e], v[s][r][e]);
       }
+    *(u32x2*)(cs + (16 * (r >> 1) + (lane & 15)) * PB + 16 * (r & 1) + 4 * (lane >> 4)) = u32x2{pack_bf16_rne(a[0], a[1]), pack_bf16_rne(a[2], a[3])};
   }
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wavefront's LDS writes have landed
+  __builtin_amdgcn_wave_barrier();
+  // out: lane = (row % 16, 16-byte column group); dL/db_t as in tn_write_half
+  const uint32_t row = lane >> 2, c = (lane & 3) * 8;
   float part = 0.0f;
-  if (h == 0) tn_write_half<DBT>(g, a4, 0, stage, p0, q0, lane, part);
-  else tn_write_half<DBT>(g, a4, 1, stage, p0, q0, lane, part);
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const u32x4 o = *(const u32x4*)(cs + (row + 16 * t) * PB + c);
+    *(u32x4*)(g.y + (size_t)(p0 + row + 16 * t) * g.ldy + q0 + c) = o;
+    if (DBT) part = dot_group_2r(o, group_noise(g.cg0 + ((q0 + c) >> 3), g.row0 + p0 + row + 16 * t, g.step_lo, g.step_hi, g.seed_lo, g.seed_hi), part);
+  }
+  if (DBT) {
+    part = block_sum_f32(part);
+    part += __shfl_xor(part, 4);   // the block is the whole wavefront's here
+    if (lane == 0) {
+      const size_t blk = (size_t)(p0 >> 5) * (g.N >> 5) + (q0 >> 5);
+      const float neg_ln2 = __uint_as_float(0xBF317218u);  // -ln 2
+      g.dbt[blk] = (neg_ln2 * g.scale[blk]) * (part * 0.5f);
+    }
+  }
 }
 
 bool gemm256_tn_applicable(const GemmArgs& g) {
@@ -153,11 +183,11 @@ size_t gemm256_tn_split_bytes(const GemmArgs& g, uint32_t parts) {
 
 int launch_gemm256_tn_split(const GemmArgs& g, bool with_dbt, float* ws, uint32_t parts, hipStream_t stream) {
   const uint64_t tiles = (uint64_t)(g.M / g256::TM) * (g.N / g256::TN);
-  if (parts < 2 || parts > g.K / g256::TK || tiles * parts >= 0x7FFFFFFFull || tiles * 8 >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
+  if (parts < 2 || parts > kMaxParts || parts > g.K / g256::TK || tiles * 16 >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
   hipLaunchKernelGGL(gemm256_tn_part_kernel, dim3((uint32_t)(tiles * parts)), dim3(256), 0, stream, g, ws, parts);
   if (hipGetLastError() != hipSuccess) return GWS_ERR_LAUNCH;
-  if (with_dbt) hipLaunchKernelGGL(gemm256_tn_sum_kernel<true>, dim3((uint32_t)(tiles * 8)), dim3(64), 0, stream, g, (const float*)ws, parts);
-  else hipLaunchKernelGGL(gemm256_tn_sum_kernel<false>, dim3((uint32_t)(tiles * 8)), dim3(64), 0, stream, g, (const float*)ws, parts);
+  if (with_dbt) hipLaunchKernelGGL(gemm256_tn_sum_kernel<true>, dim3((uint32_t)(tiles * 16)), dim3(256), 0, stream, g, (const float*)ws, parts);
+  else hipLaunchKernelGGL(gemm256_tn_sum_kernel<false>, dim3((uint32_t)(tiles * 16)), dim3(256), 0, stream, g, (const float*)ws, parts);
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
 
