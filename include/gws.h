@@ -240,7 +240,9 @@ int gws_linear_bwd_w(const void* x, const void* dy, int64_t M, int64_t ldx, int6
  * fp32 partial tile in `workspace`, and a second kernel adds a tile's parts in a fixed order,
  * rounds once to BF16 and writes dW and dL/db_t as above.  Same arguments, results within the
  * same bounds (the fp32 additions are grouped by part; nothing depends on timing).
- *   gws_linear_bwd_w_workspace_bytes(w, M): bytes the split would use for this weight and M
+ * Where another form is faster for the sizes (a whole tile per workgroup, or small pieces of the
+ * gradient whose tokens are split inside a workgroup) it is taken and the workspace left alone.
+ *   gws_linear_bwd_w_workspace_bytes(w, M): bytes the split may use for this weight and M
  *     (host call; 0 when the one-kernel form is used: enough tiles, M too small, bad shape).
  *   workspace : device memory, 16-byte aligned, workspace_bytes long, not overlapping x, dy or
  *     dw (GWS_ERR_ALIGN / GWS_ERR_ALIAS); the library's only use of it is during this call's

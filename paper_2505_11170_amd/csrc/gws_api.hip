@@ -1,5 +1,6 @@
 // C ABI of libgws: argument validation and launch planning.  Declarations and
 // the meaning of every argument are in include/gws.h.
+#include <math.h>
 #include <string.h>
 
 #include <atomic>
@@ -561,12 +562,36 @@ static uint32_t bwd_w_parts(int64_t rows, int64_t cols, int64_t M) {
   return parts < 2 ? 1u : (uint32_t)parts;
 }
 
+// The fastest way by an estimate in us, with workspace for `max_parts` parts: one workgroup per 256 x 256 tile, the tokens of
+// a tile split over workgroups (2 .. max_parts), or small pieces of the gradient with the tokens split over a workgroup's
+// wavefronts (no workspace).  Fitted to MI355X timings, e.g. tokens x rows x cols 512 x 4096 x 4096 one tile each 26; 1024 x
+// 2048 x 4096 30, in two parts 39; 4096 x 2048 x 2048 92, in four parts 52, in small pieces 54; 2048 x 1024 x 1024 in four
+// parts 26, in small pieces 12.
+static int launch_bwd_w(const GemmArgs& g, bool with_dbt, uint32_t max_parts, void* workspace, hipStream_t stream) {
+  const double cus = compute_units() > 0 ? compute_units() : 256;
+  const double tiles = (double)(g.M / 256) * (double)(g.N / 256), nk = (double)(g.K / 64);
+  double us = 6.0 + ceil(tiles / cus) * (3.0 + nk * (1.2 + 0.2 * fmin(1.0, tiles / cus)));
+  uint32_t parts = 1;
+  for (uint32_t p = 2; p <= max_parts; ++p) {
+    const double slabs = (double)gemm256_tn_split_bytes(g, p);   // written at about 5 MB/us, read again at 5.4
+    const double t = 12.0 + nk / p * 1.3 + slabs * (1.0 / 5.0e6 + 1.0 / 5.4e6);
+    if (t < us) {
+      us = t;
+      parts = p;
+    }
+  }
+  const TnPlan small = stream_tn_plan(g);
+  if (small.us < us) return launch_gemm_stream_tn(g, with_dbt, small, stream);
+  if (parts < 2) return launch_gemm256_tn(g, with_dbt, stream);
+  return launch_gemm256_tn_split(g, with_dbt, (float*)workspace, parts, stream);
+}
+
 int gws_linear_bwd_w(const void* x, const void* dy, int64_t M, int64_t ldx, int64_t ldy, const gws_tensor* w,
                      int w_is_nk, uint64_t step, void* stream) {
   GemmArgs g;
   const int rc = bwd_w_args(x, dy, M, ldx, ldy, w, w_is_nk, step, g);
   if (rc != GWS_OK) return rc;
-  return launch_gemm256_tn(g, w->dbt != nullptr, (hipStream_t)stream);
+  return launch_bwd_w(g, w->dbt != nullptr, 1, nullptr, (hipStream_t)stream);
 }
 
 size_t gws_linear_bwd_w_workspace_bytes(const gws_tensor* w, int64_t M) {
@@ -584,12 +609,12 @@ int gws_linear_bwd_w_ws(const void* x, const void* dy, int64_t M, int64_t ldx, i
   const size_t per_part = gemm256_tn_split_bytes(g, 1);
   if (workspace == nullptr) workspace_bytes = 0;
   if (parts > workspace_bytes / per_part) parts = (uint32_t)(workspace_bytes / per_part);   // as many parts as the workspace holds
-  if (parts < 2) return launch_gemm256_tn(g, w->dbt != nullptr, (hipStream_t)stream);
+  if (parts < 2) return launch_bwd_w(g, w->dbt != nullptr, 1, nullptr, (hipStream_t)stream);
   if (!aligned(workspace, 16)) return GWS_ERR_ALIGN;
   const size_t ws_bytes = gemm256_tn_split_bytes(g, parts);
   if (overlap2(workspace, ws_bytes, w->dw, (size_t)w->rows * w->ld * 2) || overlap2(workspace, ws_bytes, x, (size_t)M * ldx * 2) ||
       overlap2(workspace, ws_bytes, dy, (size_t)M * ldy * 2)) return GWS_ERR_ALIAS;
-  return launch_gemm256_tn_split(g, w->dbt != nullptr, (float*)workspace, parts, (hipStream_t)stream);
+  return launch_bwd_w(g, w->dbt != nullptr, parts, workspace, (hipStream_t)stream);
 }
 
 int gws_gemm_bf16(const void* x, int64_t M, int64_t K, int64_t ldx, const void* w, int64_t N, int64_t ldw,

@@ -9,71 +9,9 @@
 // Operands go from global memory straight to the MFMA's registers: a lane of v_mfma_f32_16x16x32_bf16 holds 8
 // consecutive k of one output.  [N x K] weights and X are stored like that; of a [K x N] weight a lane loads the same
 // NT outputs of 8 rows and turns the 8 x NT piece with byte permutes.
-#include "gws_gemm256_core.h"
-#include "gws_launch.h"
+#include "gws_gemm_stream_core.h"
 
 namespace gws {
-
-namespace stream {
-constexpr uint32_t kMaxLd = 1u << 24;   // leading dimensions the 32-bit lane offsets reach (63 rows x 2 bytes)
-
-__device__ __forceinline__ uint32_t umin(uint32_t a, uint32_t b) { return a < b ? a : b; }
-
-// The units of 64 k that wavefront w of P takes, as even as they go (the last unit of K may be half a one).
-__device__ __forceinline__ void unit_range(uint32_t K, uint32_t w, uint32_t P, uint32_t& u0, uint32_t& u1) {
-  const uint32_t nu = (K + 63) >> 6;
-  u0 = nu * w / P;
-  u1 = nu * (w + 1) / P;
-}
-
-// Tiles in bands of eight row tiles, row tiles first.  Workgroups are dealt round-robin to the 8 XCDs: tiles that share a
-// piece of the weight, and with narrow [K x N] tiles the two that share its cache lines, go to one XCD (its L2) as a
-// group, and the groups round-robin over the XCDs (a contiguous range per XCD would put the columns of one XCD on a few
-// of the L2's channels when a row of the weight is a multiple of 4 KiB).
-__device__ __forceinline__ void tile_origin(const GemmArgs& g, uint32_t bm, uint32_t bn, bool pairs, uint32_t& m0, uint32_t& n0) {
-  const uint32_t tm = (g.M + bm - 1) / bm, tn = (g.N + bn - 1) / bn;
-  const uint32_t G = umin(tm, 8) * (pairs ? 2 : 1), b = blockIdx.x, whole = gridDim.x / (8 * G) * (8 * G);
-  const uint32_t L = b < whole ? ((b >> 3) / G * 8 + (b & 7)) * G + (b >> 3) % G : b;
-  const uint32_t band = L / (8 * tn), r = L - band * 8 * tn, rows = umin(8, tm - 8 * band);
-  n0 = r / rows * bn;
-  m0 = (8 * band + r % rows) * bm;
-}
-
-// The partial sums of the P wavefronts added in the order of the wavefronts and written to Y, MC row tiles at a time.
-// acc[i][j][e] is row 16 i + lane % 16, column 16 j + 4 (lane / 16) + e.  In LDS a row of partial sums is 16 NT floats and
-// 16 bytes of padding: written by 16 lanes of as many rows, read along the row.
-constexpr int red_bytes(int mc, int nt, int p) { return p * mc * 16 * (4 * nt + 1) * 16; }
-
-template <int MT, int NT, int P, int MC>
-__device__ __forceinline__ void reduce_store(const f32x4 (&acc)[MT][NT], char* lds, const GemmArgs& g, uint32_t m0,
-                                             uint32_t n0) {
-  constexpr uint32_t PITCH = 4 * NT + 1;
-  f32x4* red = (f32x4*)lds;
-  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-#pragma unroll
-  for (int i0 = 0; i0 < MT; i0 += MC) {
-    __syncthreads();   // what was in this memory is read
-#pragma unroll
-    for (int i = 0; i < MC; ++i)
-#pragma unroll
-      for (int j = 0; j < NT; ++j) red[((wave * MC + i) * 16 + (lane & 15)) * PITCH + 4 * j + (lane >> 4)] = acc[i0 + i][j];
-    __syncthreads();
-    for (uint32_t it = tid; it < MC * 16 * 4 * NT; it += P * 64) {
-      const uint32_t r = it / (4 * NT), c = it % (4 * NT);
-      f32x4 s = red[r * PITCH + c];
-#pragma unroll
-      for (int w = 1; w < P; ++w) {
-        const f32x4 v = red[(w * MC * 16 + r) * PITCH + c];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s[e] = __fadd_rn(s[e], v[e]);
-      }
-      const uint32_t row = m0 + 16 * i0 + r, col = n0 + 4 * c;
-      if (row < g.M && col < g.N)
-        *(u32x2*)(g.y + (size_t)row * g.ldy + col) = u32x2{pack_bf16_rne(s[0], s[1]), pack_bf16_rne(s[2], s[3])};
-    }
-  }
-}
-}  // namespace stream
 
 // A wavefront keeps D units of 64 k on their way into its own ring of LDS stages (global_load_lds_dwordx4, 8 rows x 128
 // contiguous bytes per instruction).  Loaded straight into the MFMA's register layout instead (16 rows x 64 bytes: a
@@ -112,9 +50,6 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_kernel(const GemmArgs g) {
   }
   // [K x N]: an instruction covers RPI k-rows of 2 NT chunks
   constexpr uint32_t CPR = 2 * NT, RPI = 64 / CPR;
-  auto swz = [](uint32_t k) {
-    return NT == 8 ? 4 * (k & 3) + 2 * ((k >> 3) & 1) : NT == 4 ? 4 * ((k >> 1) & 1) + 2 * ((k >> 3) & 1) : 2 * ((k >> 3) & 1);
-  };
   const uint32_t wk = lane / CPR, ws = lane % CPR;
   const GWS_GLOBAL char* xb = (const GWS_GLOBAL char*)(g.x + (size_t)m0 * g.ldx);
   const GWS_GLOBAL char* wb = (const GWS_GLOBAL char*)(W_NK ? g.w + (size_t)n0 * g.ldw : g.w + n0);
@@ -123,15 +58,8 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_kernel(const GemmArgs g) {
   uint32_t wv[NV];
   if (!W_NK) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) wv[v] = (wk * g.ldw + umin(ws ^ swz(wk + RPI * v), last_chunk) * 8) * 2;
+    for (int v = 0; v < NV; ++v) wv[v] = (wk * g.ldw + umin(ws ^ oc_swizzle<W_NK ? 2 : NT>(wk + RPI * v), last_chunk) * 8) * 2;
   }
-  auto direct = [](const GWS_GLOBAL char* base, uint32_t voff, uint16_t* dst) {
-    const uint32_t a = (uint32_t)(uintptr_t)(GWS_LDS void*)dst;
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(a) : "m0", "memory");
-#pragma clang diagnostic pop
-  };
   auto load = [&](uint32_t u, uint32_t slot) {
     uint16_t* st = ring + slot * STG;
     const uint32_t k0 = umin(64 * u, g.K - 64);   // the half unit at the end of K is fetched as the second half of a whole one
@@ -169,11 +97,7 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_kernel(const GemmArgs g) {
         if (W_NK) {
           fw[h][j].u = *(const u32x4*)(wsg + (16 * j + li) * 64 + (((4 * h + grp) ^ ((li >> 1) & 7)) * 8));
         } else {
-#pragma unroll
-          for (int t = 0; t < 2; ++t) {
-            const uint32_t k = 32 * h + 8 * grp + 4 * t + (li >> 2), c = 2 * j + ((li >> 1) & 1);
-            fw[h][j].h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((GWS_LDS i16x4*)(wsg + k * BN + (c ^ swz(k)) * 8 + (li & 1) * 4));
-          }
+          fw[h][j] = read_oc<W_NK ? 2 : NT>(wsg, h, j, li, grp);
         }
       }
     }

@@ -382,3 +382,18 @@ def test_middle_tile_gemm(M, K, N, w_is_nk):
 def test_large_tile_gemm_with_edges(M, K, N, w_is_nk):
     run_case(M, K, N, w_is_nk, gws.FMT_FP8_E4M3, seed_id=92, ldx_pad=8, ldy_pad=8, rows_sel=np.array([0, 255, 256, M // 2, M - 2, M - 1]),
              mode=gws.LINEAR_IN_OPERAND)
+
+
+@pytest.mark.parametrize("w_is_nk", [False, True])
+def test_whole_large_tiles_at_every_number_of_k_steps(w_is_nk):
+    # 256 tiles of 256 x 256, 1 to 14 K-steps (the rings' common period is six): against fp32 on the GPU
+    for steps in range(1, 15):
+        K = 64 * steps
+        gen = torch.Generator(device=DEV).manual_seed(steps)
+        x = torch.randn(8192, K, generator=gen, device=DEV).to(torch.bfloat16)
+        w = (torch.randn(*((2048, K) if w_is_nk else (K, 2048)), generator=gen, device=DEV) * 0.02).to(torch.bfloat16)
+        y = torch.zeros(8192, 2048, dtype=torch.bfloat16, device=DEV)
+        gws.gws_gemm_bf16(x, w, y, w_is_nk=w_is_nk)
+        kn = (w.t().contiguous() if w_is_nk else w).float()
+        ref, mag = x.float() @ kn, x.float().abs() @ kn.abs()
+        assert bool(((y.float() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2 * K * 2.0 ** -24 * mag).all()), steps

@@ -174,3 +174,34 @@ def test_random_shapes():
         K, N = 256 * int(rng.integers(1, 4)), 256 * int(rng.integers(1, 4))
         M = 64 * int(rng.integers(1, 10))
         run_case(M, K, N, bool(case & 1), 830 + 2 * case, pad=8 * int(rng.integers(0, 3)))
+
+
+def fp32_product(a, b):
+    """a^T b in fp32 on the GPU (a, b [tokens x n])."""
+    return a.float().t().contiguous() @ b.float()
+
+
+@pytest.mark.parametrize("tokens,rows,cols", [(64 * i, 4096, 4096) for i in range(1, 15)] + [(8192, 2048, 2048), (4096, 768, 3072), (8192, 512, 512)]
+                         + [(64, 256, 256), (128, 256, 512), (320, 512, 768), (576, 1536, 1024), (1600, 1280, 1024)])
+def test_every_form_of_the_weight_gradient(tokens, rows, cols):
+    # one workgroup per 256 x 256 tile (256 tiles, every number of K-steps around the rings' period), the tokens split over
+    # workgroups (all the workspace, room for two parts), small pieces with the tokens split over wavefronts (fewer units of
+    # 64 tokens than wavefronts, uneven numbers of them): dW to its rounding and the order of fp32 sums, and dL/db_t to the
+    # separate kernel's on the same bytes
+    gen = torch.Generator(device=DEV).manual_seed(tokens + rows)
+    x = torch.randn(tokens, rows, generator=gen, device=DEV).to(torch.bfloat16)
+    dy = (torch.randn(tokens, cols, generator=gen, device=DEV) * 1e-3).to(torch.bfloat16)
+    d = gws.TensorDesc(rows=rows, cols=cols, seed=77, scale=torch.rand(rows // 32, cols // 32, generator=gen, device=DEV),
+                       dw=torch.zeros(rows, cols, dtype=torch.bfloat16, device=DEV), dbt=torch.zeros(rows // 32, cols // 32, device=DEV))
+    ref, mag = fp32_product(x, dy), fp32_product(x.abs(), dy.abs())
+    need = gws.gws_linear_bwd_w_workspace_bytes(d, tokens)
+    for nbytes in {0, need, min(need, 2 * rows * cols * 4)}:
+        d.dw.zero_()
+        d.dbt.zero_()
+        gws.gws_linear_bwd_w_ws(x, dy, d, 5, torch.empty(nbytes, dtype=torch.uint8, device=DEV) if nbytes else None)
+        # one rounding to BF16 and two fp32 sums of `tokens` terms in different orders
+        assert bool(((d.dw.float() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2 * tokens * 2.0 ** -24 * mag).all()), nbytes
+        back = gws.TensorDesc(rows=rows, cols=cols, seed=77, scale=d.scale, g=d.dw, dw=None, dbt=torch.zeros_like(d.dbt), ld=cols)
+        gws.gws_sample_bwd([back], 5)
+        terms = 0.6932 * d.scale * d.dw.float().abs().view(rows // 32, 32, cols // 32, 32).sum((1, 3)) * 2
+        assert bool(((d.dbt - back.dbt).abs() <= 1e-5 * back.dbt.abs() + 1e-6 * terms).all()), nbytes
