@@ -562,15 +562,17 @@ static uint32_t bwd_w_parts(int64_t rows, int64_t cols, int64_t M) {
   return parts < 2 ? 1u : (uint32_t)parts;
 }
 
-// The fastest way by an estimate in us, with workspace for `max_parts` parts: one workgroup per 256 x 256 tile, the tokens of
-// a tile split over workgroups (2 .. max_parts), or small pieces of the gradient with the tokens split over a workgroup's
+// The fastest way by an estimate in us, with workspace for `max_parts` parts: one workgroup per tile of 256 x 256 or of 256 x
+// 192 (four fifths of the time each: 2048 x 5632 over 8192 tokens 163 against 188), the tokens of a tile split over workgroups (2 .. max_parts), or small pieces of the gradient with the tokens split over a workgroup's
 // wavefronts (no workspace).  Fitted to MI355X timings, e.g. tokens x rows x cols 512 x 4096 x 4096 one tile each 26; 1024 x
 // 2048 x 4096 30, in two parts 39; 4096 x 2048 x 2048 92, in four parts 52, in small pieces 54; 2048 x 1024 x 1024 in four
 // parts 26, in small pieces 12.
 static int launch_bwd_w(const GemmArgs& g, bool with_dbt, uint32_t max_parts, void* workspace, hipStream_t stream) {
   const double cus = compute_units() > 0 ? compute_units() : 256;
   const double tiles = (double)(g.M / 256) * (double)(g.N / 256), nk = (double)(g.K / 64);
-  double us = 6.0 + ceil(tiles / cus) * (3.0 + nk * (1.2 + 0.2 * fmin(1.0, tiles / cus)));
+  auto whole = [&](double n, double k_step) { return 6.0 + ceil(n / cus) * (3.0 + nk * k_step * (1.2 + 0.2 * fmin(1.0, n / cus))); };
+  const double wide_us = whole(tiles, 1.0), narrow_us = whole((double)(g.M / 256) * ceil(g.N / 192.0), 0.8);
+  double us = fmin(wide_us, narrow_us);
   uint32_t parts = 1;
   for (uint32_t p = 2; p <= max_parts; ++p) {
     const double slabs = (double)gemm256_tn_split_bytes(g, p);   // written at about 5 MB/us, read again at 5.4
@@ -582,7 +584,7 @@ static int launch_bwd_w(const GemmArgs& g, bool with_dbt, uint32_t max_parts, vo
   }
   const TnPlan small = stream_tn_plan(g);
   if (small.us < us) return launch_gemm_stream_tn(g, with_dbt, small, stream);
-  if (parts < 2) return launch_gemm256_tn(g, with_dbt, stream);
+  if (parts < 2) return narrow_us < wide_us ? launch_gemm256_tn_narrow(g, with_dbt, stream) : launch_gemm256_tn(g, with_dbt, stream);
   return launch_gemm256_tn_split(g, with_dbt, (float*)workspace, parts, stream);
 }
 
@@ -646,11 +648,11 @@ static int plan_ride(const GemmArgs& g, int w_is_nk, bool gemm_empty, int64_t K,
   idle = 0;
   use_rider = 1;
   // whole tiles only; not where the GEMM splits K (another order of its sums than the large tile's: Y would not be the same
-  // bits), and where the middle tile is its kernel only if the sampling's own launch costs more than that tile saves
+  // bits), and where the middle or the narrow tile is its kernel only if the sampling's own launch costs more than that saves
   RoutePlan plan;
   const GemmRoute route = gemm_empty ? GemmRoute::kSmall : gemm_route(g, w_is_nk, plan);
   const bool gemm_rides = force_extra >= 0 ? (gemm_empty || gemm256_applicable(g))
-                                           : gemm256_applicable(g) && (route == GemmRoute::kLarge || route == GemmRoute::kMiddle);
+                                           : gemm256_applicable(g) && route != GemmRoute::kStream && route != GemmRoute::kSmall;
   if (!gemm_rides) return 0;
   const int cus = compute_units();
   const uint64_t tiles = gemm_empty ? 0 : (uint64_t)(g.M / 256) * (uint64_t)(g.N / 256);
@@ -685,11 +687,11 @@ static int plan_ride(const GemmArgs& g, int w_is_nk, bool gemm_empty, int64_t K,
       break;
     }
   }
-  if (force_extra < 0 && route == GemmRoute::kMiddle) {
+  if (force_extra < 0 && route != GemmRoute::kLarge) {
     // the sampling kernel alone: about 3 us and 4 bytes an element at 5 TB/s (one launch in any case if some do not ride)
     double elements = 0.0;
     for (int i = 0; i < n_riding; ++i) elements += (double)next[i].rows * (double)next[i].cols;
-    if (plan.large_us - (elements * 4.0 / 5e6 + (n_riding == n_next ? 3.0 : 0.0)) > plan.middle_us) n_riding = 0;
+    if (plan.large_us - (elements * 4.0 / 5e6 + (n_riding == n_next ? 3.0 : 0.0)) > fmin(plan.middle_us, plan.narrow_us)) n_riding = 0;
   }
   for (int j = n_riding; j <= kMaxRide; ++j) r.begin[j] = begin;
   r.n = (uint32_t)n_riding;

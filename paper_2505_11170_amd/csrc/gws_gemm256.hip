@@ -226,6 +226,34 @@ bool gemm256_applicable(const GemmArgs& g) {
          g.ldx < g256::kMaxLd && g.ldw < g256::kMaxLd;
 }
 
+// Tiles of 256 x 192, with the edges of gemm256_edge_kernel: for products whose 256 x 256 tiles leave the last round of
+// compute units emptier than these do.
+template <bool W_NK>
+__global__ __launch_bounds__(256, 1) void gemm256_narrow_kernel(const GemmArgs g) {
+  using namespace g256;
+  uint32_t tile_m, tile_n;
+  tile_of(blockIdx.x, (g.M + TM - 1) / TM, (g.N + kNarrow - 1) / kNarrow, tile_m, tile_n);
+  const uint32_t m0 = tile_m * TM, n0 = tile_n * kNarrow, rows = g.M - m0 < TM ? g.M - m0 : TM, cols = g.N - n0 < kNarrow ? g.N - n0 : kNarrow;
+  gemm256_accumulate<false, !W_NK, true, 6>(g.x, g.ldx, g.w, g.ldw, (g.K + TK - 1) / TK, m0, n0,
+                                            [&](f32x4 (&acc)[8][6], uint16_t* cs, uint32_t wave, uint32_t lane) {
+    const uint32_t p0 = 128 * (wave >> 1), q0 = 96 * (wave & 1);
+    uint16_t* yw = g.y + (size_t)(m0 + p0) * g.ldy + n0 + q0;
+    const int wr = (int)rows - (int)p0, wc = (int)cols - (int)q0;
+    auto hook = [](uint32_t, uint32_t, const u32x4&) {};
+    auto done = [](int, int) {};
+    epilogue_narrow_half(*reinterpret_cast<const f32x4 (*)[4][6]>(&acc[0]), 0, cs, yw, g.ldy, lane, wr, wc, hook, done);
+    epilogue_narrow_half(*reinterpret_cast<const f32x4 (*)[4][6]>(&acc[4]), 1, cs, yw, g.ldy, lane, wr, wc, hook, done);
+  }, rows, cols, g.K);
+}
+
+int launch_gemm256_narrow(const GemmArgs& g, int w_is_nk, hipStream_t stream) {
+  const uint64_t tiles = (uint64_t)((g.M + g256::TM - 1) / g256::TM) * ((g.N + g256::kNarrow - 1) / g256::kNarrow);
+  if (tiles >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
+  if (w_is_nk) hipLaunchKernelGGL(gemm256_narrow_kernel<true>, dim3((uint32_t)tiles), dim3(256), 0, stream, g);
+  else hipLaunchKernelGGL(gemm256_narrow_kernel<false>, dim3((uint32_t)tiles), dim3(256), 0, stream, g);
+  return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
+}
+
 bool gemm256_edge_applicable(const GemmArgs& g) {
   return g.M > 0 && g.N > 0 && g.N % 32 == 0 && g.K >= g256::TK && g.K % 32 == 0 && g.ldx < g256::kMaxLdEdge && g.ldw < g256::kMaxLdEdge;
 }

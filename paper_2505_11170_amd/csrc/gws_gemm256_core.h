@@ -60,6 +60,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 namespace g256 {
 constexpr int TM = 256, TN = 256, TK = 64;
 constexpr int STAGE = 256 * 64;   // elements of one operand tile (32 KiB), either layout
+constexpr uint32_t kNarrow = 192; // columns of a narrow tile
 constexpr int PC = 128 + 8;       // epilogue pitch of a wavefront's staging rows (elements)
 constexpr uint32_t kMaxLd = 1u << 28;   // leading dimensions (elements) the 32-bit lane offsets of the loads reach: 7 rows x 2 bytes
 constexpr uint32_t kMaxLdEdge = 1u << 23;   // the same with edges: 255 rows x 2 bytes
@@ -132,7 +133,9 @@ __device__ __forceinline__ void epilogue_bf16_half(const f32x4 (&a4)[4][8], int 
 // except its own staging area (callers that loop over tiles put a barrier between tiles).
 // EDGE: of the tile only `a_out` rows and `b_out` columns exist (columns a multiple of 32; the operands' last ones are read
 // in the place of the others), and K (>= 64, a multiple of 32) need not be a multiple of 64; nk counts the half step.
-template <bool A_OC, bool B_OC, bool EDGE = false, class Finish>
+// NJ: column tiles of 16 of a wavefront: 8, or 6 for a tile of 256 x 192 (b and acc are that much narrower; its output-
+// contiguous B stage is 64 k-rows of 128 columns, as 256 of them are swizzled, and 64 k-rows of 64 behind it).
+template <bool A_OC, bool B_OC, bool EDGE = false, int NJ = 8, class Finish>
 __device__ __forceinline__ void gemm256_accumulate(const uint16_t* __restrict__ a, uint32_t lda,
                                                    const uint16_t* __restrict__ b, uint32_t ldb, uint32_t nk, uint32_t m0,
                                                    uint32_t n0, Finish&& finish, uint32_t a_out = 0, uint32_t b_out = 0,
@@ -140,33 +143,47 @@ __device__ __forceinline__ void gemm256_accumulate(const uint16_t* __restrict__ 
   using namespace g256;
   __shared__ __attribute__((aligned(16))) uint16_t A0[STAGE];
   __shared__ __attribute__((aligned(16))) uint16_t A1[STAGE];
-  __shared__ __attribute__((aligned(16))) uint16_t B0[STAGE];
-  __shared__ __attribute__((aligned(16))) uint16_t B1[STAGE];
-  __shared__ __attribute__((aligned(16))) uint16_t B2[STAGE];
+  static_assert(NJ == 8 || NJ == 6, "");
+  constexpr int STAGE_B = STAGE / 8 * NJ;
+  __shared__ __attribute__((aligned(16))) uint16_t B0[STAGE_B];
+  __shared__ __attribute__((aligned(16))) uint16_t B1[STAGE_B];
+  __shared__ __attribute__((aligned(16))) uint16_t B2[STAGE_B];
 
   const uint32_t tid = threadIdx.x, lane = tid & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t wm = wave >> 1, wn = wave & 1;
 
-  // ---- loads: wave-uniform base + per-lane byte offset; instruction q (0..7) of a wavefront fills
-  // 1 KiB at (wave * 8 + q) * 1 KiB of the stage ----
+  // ---- loads: wave-uniform base + per-lane byte offset; instruction q (0..7, of a narrow B 0..5) of a wavefront
+  // fills 1 KiB at (wave * 8 + q) * 1 KiB of the stage (narrow: see load1) ----
   struct Src {
     const GWS_GLOBAL char* base;
     uint32_t voff[EDGE ? 8 : 4];   // per-lane byte offset; which one an instruction q uses: see load1
     uint32_t ld;
   };
-  auto make_src = [&](bool oc, const uint16_t* p, uint32_t ld, uint32_t o0, uint32_t out) {
+  auto make_src = [&](bool oc, bool narrow, const uint16_t* p, uint32_t ld, uint32_t o0, uint32_t out) {
     Src s;
     s.ld = ld;
-    if (EDGE && !oc) {   // as below, with the row's offset in the lane offset: rows past the last one read that one
+    if (narrow && oc) {
+      // columns 0 .. 127: k-rows 16 wave + 4 q + lane / 16, q = 0 .. 3, chunk ^ 4 (k % 4) ^ 2 (k / 8 % 2);
+      // columns 128 .. 191: k-rows 16 wave + 8 (q - 4) + lane / 8, chunk ^ 4 (k / 2 % 2) ^ 2 (k / 8 % 2)
+      s.base = (const GWS_GLOBAL char*)(p + (size_t)(16 * wave) * ld + o0);
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {
+        uint32_t c = (lane & 15) ^ ((lane >> 4) << 2) ^ (v << 1), d = 16 + ((lane & 7) ^ (((lane >> 4) & 1) << 2) ^ (v << 1));
+        if (EDGE && c * 8 >= out) c = 0;
+        if (EDGE && d * 8 >= out) d = 0;
+        s.voff[v] = ((lane >> 4) * ld + c * 8) * 2;
+        s.voff[2 + v] = ((lane >> 3) * ld + d * 8) * 2;
+      }
+    } else if (EDGE && !oc) {   // as below, with the row's offset in the lane offset: rows past the last one read that one
       s.base = (const GWS_GLOBAL char*)(p + (size_t)o0 * ld);
 #pragma unroll
       for (int q = 0; q < (EDGE ? 8 : 4); ++q) {
-        const uint32_t row = 64 * wave + 8 * q + (lane >> 3);
+        const uint32_t row = (narrow ? 48 : 64) * wave + 8 * q + (lane >> 3);   // 48 wave is even too: the same swizzle
         s.voff[q] = ((row < out ? row : out - 1) * ld + (((lane & 7) ^ (4 * (q & 1) + (lane >> 4))) * 8)) * 2;
       }
     } else if (!oc) {  // rows 64 wave + 8 q + lane/8; slot lane%8 holds chunk slot ^ ((row / 2) % 8) = slot ^ (4 (q%2) + lane/16)
-      s.base = (const GWS_GLOBAL char*)(p + (size_t)(o0 + 64 * wave) * ld);
+      s.base = (const GWS_GLOBAL char*)(p + (size_t)(o0 + (narrow ? 48 : 64) * wave) * ld);
       s.voff[0] = s.voff[2] = ((lane >> 3) * ld + (((lane & 7) ^ (0 + (lane >> 4))) * 8)) * 2;
       s.voff[1] = s.voff[3] = ((lane >> 3) * ld + (((lane & 7) ^ (4 + (lane >> 4))) * 8)) * 2;
     } else {    // k-rows k = 16 wave + 2 q + lane/32; slot lane%32 holds chunk slot ^ 4 (k % 4) ^ 2 (k/8 % 2),
@@ -182,34 +199,36 @@ __device__ __forceinline__ void gemm256_accumulate(const uint16_t* __restrict__ 
     }
     return s;
   };
-  const Src sa = make_src(A_OC, a, lda, m0, a_out), sb = make_src(B_OC, b, ldb, n0, b_out);
-  auto load1 = [&](bool oc, const Src& s, uint16_t* stage, uint32_t kt, int q) {
+  constexpr bool NARROW = NJ != 8;
+  const Src sa = make_src(A_OC, false, a, lda, m0, a_out), sb = make_src(B_OC, NARROW, b, ldb, n0, b_out);
+  auto load1 = [&](bool oc, bool narrow, const Src& s, uint16_t* stage, uint32_t kt, int q) {
     // EDGE: the half step at the end of K is fetched as the second half of a whole one
     const uint32_t k0 = EDGE ? __builtin_amdgcn_readfirstlane(kt * TK + TK > K ? K - TK : kt * TK) : kt * TK;
-    const size_t uni = oc ? (size_t)(k0 + 2 * q) * s.ld : EDGE ? (size_t)k0 : (size_t)(8 * q) * s.ld + k0;   // elements
+    const size_t uni = narrow && oc ? (size_t)(k0 + (q < 4 ? 4 * q : 8 * (q - 4))) * s.ld
+                       : oc         ? (size_t)(k0 + 2 * q) * s.ld
+                       : EDGE       ? (size_t)k0
+                                    : (size_t)(8 * q) * s.ld + k0;   // elements
     // issued from an assembly statement: the compiler would order every later read of the stage arrays after all
     // direct loads it knows of (vmcnt(0)), and the ring keeps loads in flight across the barrier on purpose; the
     // waits for these loads are the explicit ones in front of the barriers
-    const uint32_t lds_addr = (uint32_t)(uintptr_t)(GWS_LDS void*)(stage + (wave * 8 + q) * 512);
+    const uint32_t slot = !narrow ? wave * 8 + q : !oc ? wave * 6 + q : q < 4 ? wave * 4 + q : 16 + wave * 2 + (q - 4);
+    const uint32_t lds_addr = (uint32_t)(uintptr_t)(GWS_LDS void*)(stage + slot * 512);
     // (m0, the LDS address register of such a load, is reserved to the compiler, which warns when told that it is
     // overwritten; it has to be told)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :: "v"(s.voff[oc ? (q & 1) + 2 * ((q >> 2) & 1) : EDGE ? q : (q & 1)]), "s"(s.base + uni * 2), "s"(lds_addr) : "m0", "memory");
+                 :: "v"(s.voff[narrow && oc ? (q < 4 ? q >> 1 : 2 + (q & 1)) : oc ? (q & 1) + 2 * ((q >> 2) & 1) : EDGE ? q : (q & 1)]), "s"(s.base + uni * 2), "s"(lds_addr) : "m0", "memory");
 #pragma clang diagnostic pop
   };
-  // load n (0..15) of a K-step: even n -> A, odd n -> B
-  auto load_n = [&](uint16_t* As, uint16_t* Bs, uint32_t kt, int n) {
-    if (!(n & 1)) load1(A_OC, sa, As, kt, n >> 1);
-    else load1(B_OC, sb, Bs, kt, n >> 1);
-  };
+  auto load_a = [&](uint16_t* st, uint32_t kt, int q) { load1(A_OC, false, sa, st, kt, q); };
+  auto load_b = [&](uint16_t* st, uint32_t kt, int q) { load1(B_OC, NARROW, sb, st, kt, q); };
 
   // ---- fragment reads: per-lane element offsets into a stage ----
   // A fragment of the 16x16x32 MFMA is 16 outputs x 32 k: lane l holds output l % 16, k = 8 (l / 16) .. + 7.
   const uint32_t li = lane & 15, grp = lane >> 4, sw = (li >> 2) & 3;
-  uint32_t a_off[4], b_off[4];   // contraction-contiguous: [ks] (2 used); output-contiguous: [fragment / 2]
-  auto make_off = [&](bool oc, uint32_t w, uint32_t (&off)[4]) {
+  uint32_t a_off[4], b_off[NARROW ? 6 : 4];   // contraction-contiguous: [ks] (2 used); output-contiguous: [fragment / 2], narrow: [fragment]
+  auto make_off = [&](bool oc, uint32_t w, uint32_t* off) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       if (!oc) off[t] = (128 * w + li) * 64 + (((4 * (t & 1) + grp) ^ ((lane >> 1) & 7)) * 8);
@@ -217,10 +236,28 @@ __device__ __forceinline__ void gemm256_accumulate(const uint16_t* __restrict__ 
     }
   };
   make_off(A_OC, wm, a_off);
-  make_off(B_OC, wn, b_off);
+  if (NARROW && B_OC) {
+#pragma unroll
+    for (int f = 0; f < NJ; ++f) {   // 16-column tile t of the stage; k = 8 grp + li / 4 (+ 4 half + 32 ks)
+      const uint32_t t = NJ * wn + f, k = 8 * grp + (li >> 2), c = 2 * t + ((li >> 1) & 1);
+      b_off[f] = t < 8 ? k * 128 + (c ^ ((k & 3) << 2) ^ (((k >> 3) & 1) << 1)) * 8 + (li & 1) * 4
+                       : 8192 + k * 64 + ((c - 16) ^ (((k >> 1) & 1) << 2) ^ (((k >> 3) & 1) << 1)) * 8 + (li & 1) * 4;
+    }
+  } else if (NARROW) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) b_off[t] = (16 * NJ * wn + li) * 64 + (((4 * t + grp) ^ ((lane >> 1) & 7)) * 8);
+  } else {
+    make_off(B_OC, wn, b_off);
+  }
   // read `half` of fragment f (0..7) of slice ks (0, 1) from a stage
-  auto read_frag = [&](bool oc, const uint32_t (&off)[4], Frag8& fr, const uint16_t* stage, int ks, int f, int half) {
-    if (!oc) {
+  auto read_frag = [&](bool oc, bool narrow, const uint32_t* off, Frag8& fr, const uint16_t* stage, int ks, int f, int half) {
+    if (narrow && oc) {
+      // rows of 256 or 128 bytes (which part a fragment lies in depends on the wavefront); the 4 rows of `half` change
+      // neither k % 4, k / 8 % 2 nor, by 4, k / 2 % 2
+      const uint32_t w = NJ * wn + f < 8 ? 128 : 64;
+      const uint16_t* p = stage + off[f] + (ks * 32 + half * 4) * w;
+      fr.h[half] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((GWS_LDS i16x4*)p);
+    } else if (!oc) {
       fr.u = *(const u32x4*)(stage + off[ks] + f * 16 * 64);
     } else {
       const uint16_t* p = stage + (off[f >> 1] ^ ((f & 1) * 16)) + ks * 32 * 256 + half * 4 * 256;
@@ -228,38 +265,41 @@ __device__ __forceinline__ void gemm256_accumulate(const uint16_t* __restrict__ 
     }
   };
   constexpr int RA = A_OC ? 2 : 1, RB = B_OC ? 2 : 1;   // LDS reads per fragment
-  constexpr int NR = 8 * RA + 8 * RB;                   // reads per slice: 16, 24 or 32
-  constexpr int RSTRIDE = 2;                            // one read every second MFMA: the last one is issued well before
-                                                        // the wait in front of the barrier (measured: 2-3 % on the
-                                                        // 16-read form against a read every fourth MFMA)
-  static_assert(RSTRIDE * NR <= 64, "the reads of a slice fit behind its MFMAs");
-  Frag8 fa[2][8], fb[2][8];
+  constexpr int NR = 8 * RA + NJ * RB, NM = 8 * NJ;     // reads (16, 24 or 32; narrow 14, 20 or 28) and MFMAs of a slice
+  // One read every second MFMA: the last one is issued well before the wait in front of the barrier (measured: 2-3 % on
+  // the 16-read form against a read every fourth MFMA).  Where they do not fit like that they are spread over all but the
+  // last MFMAs.
+  constexpr bool SPREAD = 2 * NR > NM;
+  constexpr int LAST = NM - 4;
+  auto read_here = [](int n) { return SPREAD ? n < LAST && (n + 1) * NR / LAST > n * NR / LAST : n % 2 == 0 && n / 2 < NR; };
+  auto read_no = [](int n) { return SPREAD ? n * NR / LAST : n / 2; };
+  Frag8 fa[2][8], fb[2][NJ];
   // read n (0..NR-1) of slice (stage, ks) into fragment buffer `buf`, in the order the MFMAs need them:
-  // A fragment 0, B fragments 0..7, A fragments 1..7
+  // A fragment 0, the B fragments, A fragments 1..7
   auto read_n = [&](int buf, const uint16_t* As, const uint16_t* Bs, int ks, int n) {
     if (n < RA) {
-      read_frag(A_OC, a_off, fa[buf][0], As, ks, 0, n);
-    } else if (n < RA + 8 * RB) {
+      read_frag(A_OC, false, a_off, fa[buf][0], As, ks, 0, n);
+    } else if (n < RA + NJ * RB) {
       const int m = n - RA;
-      read_frag(B_OC, b_off, fb[buf][m / RB], Bs, ks, m / RB, m % RB);
+      read_frag(B_OC, NARROW, b_off, fb[buf][m / RB], Bs, ks, m / RB, m % RB);
     } else {
-      const int m = n - RA - 8 * RB;
-      read_frag(A_OC, a_off, fa[buf][1 + m / RA], As, ks, 1 + m / RA, m % RA);
+      const int m = n - RA - NJ * RB;
+      read_frag(A_OC, false, a_off, fa[buf][1 + m / RA], As, ks, 1 + m / RA, m % RA);
     }
   };
 
   // acc[i][j]: the MFMA takes the B fragment as its first operand, so that a lane ends up with four
   // consecutive columns of one row: row 16 i + lane % 16, columns 16 j + 4 (lane / 16) .. + 3 of the wavefront tile
-  f32x4 acc[8][8];
+  f32x4 acc[8][NJ];
 #pragma unroll
   for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.0f;
   auto mfma_n = [&](int buf, int n) {
     // the B fragments go up and down again: at a change of the A fragment the other operand stays
-    const int i = n >> 3, j = (i & 1) ? 7 - (n & 7) : (n & 7);
+    const int i = n / NJ, j = (i & 1) ? NJ - 1 - n % NJ : n % NJ;
     // written as assembly so that the accumulator is one register tuple, tied in and out: with the builtin the
     // compiler moves accumulators between registers at every turn of the loop
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(fb[buf][j].u), "v"(fa[buf][i].u));
@@ -268,32 +308,33 @@ __device__ __forceinline__ void gemm256_accumulate(const uint16_t* __restrict__ 
   // One K-step on the stages (Ac, Bc).  The A operand lives in a ring of two stages, the B operand (the weight,
   // which comes from HBM where the activations come from the caches) in a ring of three: K-step k computes on
   // A[k % 2], B[k % 3]; its second slice requests A of K-step k + 2 (`ka`) into Ac and B of K-step k + 3 (`kb`) into Bc,
-  // the A loads first.  Loads complete in order, so "all but the last 8" at the barrier means: A and B of the next
+  // the A loads first.  Loads complete in order, so "all but the last 8" (NJ) at the barrier means: A and B of the next
   // K-step have landed, the B loads of the K-step after it may still be in flight.
   auto kstep = [&](uint16_t* Ac, uint16_t* Bc, uint16_t* An, uint16_t* Bn, uint32_t ka, uint32_t kb) {
 #pragma unroll
-    for (int n = 0; n < 64; ++n) {
+    for (int n = 0; n < NM; ++n) {
       mfma_n(0, n);
       __builtin_amdgcn_sched_barrier(0);
-      if (n % RSTRIDE == 0 && n / RSTRIDE < NR) {
-        read_n(1, Ac, Bc, 1, n / RSTRIDE);
+      if (read_here(n)) {
+        read_n(1, Ac, Bc, 1, read_no(n));
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NJ) : "memory");
     __builtin_amdgcn_sched_barrier(0);
+    constexpr int LSTRIDE = NM / 16;   // a load every fourth MFMA (narrow: every third)
 #pragma unroll
-    for (int n = 0; n < 64; ++n) {
+    for (int n = 0; n < NM; ++n) {
       mfma_n(1, n);
       __builtin_amdgcn_sched_barrier(0);
-      if (n % 4 == 1) {
-        const int idx = n / 4;
-        if (idx < 8) load1(A_OC, sa, Ac, ka, idx);
-        else load1(B_OC, sb, Bc, kb, idx - 8);
+      if (n % LSTRIDE == 1) {
+        const int idx = n / LSTRIDE;
+        if (idx < 8) load_a(Ac, ka, idx);
+        else if (idx < 8 + NJ) load_b(Bc, kb, idx - 8);
         __builtin_amdgcn_sched_barrier(0);
       }
-      if (n % RSTRIDE == 0 && n / RSTRIDE < NR) {
-        read_n(0, An, Bn, 0, n / RSTRIDE);
+      if (read_here(n)) {
+        read_n(0, An, Bn, 0, read_no(n));
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -305,14 +346,17 @@ __device__ __forceinline__ void gemm256_accumulate(const uint16_t* __restrict__ 
   auto cl = [&](uint32_t k) { return k < last ? k : last; };
   // everything the rings hold is requested at once (one memory round trip in front of the first MFMA)
 #pragma unroll
-  for (int n = 0; n < 16; ++n) load_n(A0, B0, 0, n);
+  for (int q = 0; q < 8; ++q) {
+    load_a(A0, 0, q);
+    if (q < NJ) load_b(B0, 0, q);
+  }
 #pragma unroll
-  for (int q = 0; q < 8; ++q) load1(A_OC, sa, A1, cl(1), q);
+  for (int q = 0; q < 8; ++q) load_a(A1, cl(1), q);
 #pragma unroll
-  for (int q = 0; q < 8; ++q) load1(B_OC, sb, B1, cl(1), q);
+  for (int q = 0; q < NJ; ++q) load_b(B1, cl(1), q);
 #pragma unroll
-  for (int q = 0; q < 8; ++q) load1(B_OC, sb, B2, cl(2), q);
-  asm volatile("s_waitcnt vmcnt(24)\n\ts_barrier" ::: "memory");   // the first stages have landed
+  for (int q = 0; q < NJ; ++q) load_b(B2, cl(2), q);
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(8 + 2 * NJ) : "memory");   // the first stages have landed
 #pragma unroll
   for (int n = 0; n < NR; ++n) read_n(0, A0, B0, 0, n);
   // the compiler does not know that the assembly statements are MFMAs: keep the zeroing of the accumulators
@@ -324,7 +368,9 @@ __device__ __forceinline__ void gemm256_accumulate(const uint16_t* __restrict__ 
   auto half_step = [&](uint32_t k) {
     if (EDGE && k * TK + TK > K) {
 #pragma unroll
-      for (int f = 0; f < 8; ++f) fa[0][f].u = fb[0][f].u = u32x4{0, 0, 0, 0};
+      for (int f = 0; f < 8; ++f) fa[0][f].u = u32x4{0, 0, 0, 0};
+#pragma unroll
+      for (int f = 0; f < NJ; ++f) fb[0][f].u = u32x4{0, 0, 0, 0};
       __builtin_amdgcn_sched_barrier(0);
       asm volatile("s_nop 7");
       __builtin_amdgcn_sched_barrier(0);
@@ -359,6 +405,38 @@ __device__ __forceinline__ void gemm256_accumulate(const uint16_t* __restrict__ 
   __builtin_amdgcn_sched_barrier(0);
 
   finish(acc, wave == 0 ? A0 : wave == 1 ? A1 : wave == 2 ? B0 : B1, wave, lane);
+}
+
+// The way out of half h (64 rows) of a wavefront's 128 x 96 part of a narrow tile: as epilogue_bf16_half, but by 32 x 32
+// blocks: lane = (row % 16, 16-byte column group) of a block; hook(row, col, v) for every group (row and col relative to the
+// wavefront's part), and block_done(block row, block column) behind a block's two.  Only rows and columns below `rows` and `cols` (a multiple of 32) exist.
+template <class Hook, class Done>
+__device__ __forceinline__ void epilogue_narrow_half(const f32x4 (&a4)[4][6], int h, uint16_t* cs, uint16_t* yw, uint32_t ldy,
+                                                     uint32_t lane, int rows, int cols, Hook&& hook, Done&& block_done) {
+  constexpr int PN = 96 + 8;
+  static_assert(64 * PN <= g256::STAGE / 8 * 6, "half a wavefront tile is staged in one stage array");
+#pragma unroll
+  for (int i2 = 0; i2 < 4; ++i2)
+#pragma unroll
+    for (int j = 0; j < 6; ++j)
+      *(u32x2*)(cs + (16 * i2 + (lane & 15)) * PN + 16 * j + 4 * (lane >> 4)) =
+          u32x2{pack_bf16_rne(a4[i2][j][0], a4[i2][j][1]), pack_bf16_rne(a4[i2][j][2], a4[i2][j][3])};
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wavefront's LDS writes have landed
+  __builtin_amdgcn_wave_barrier();
+  const uint32_t r = lane >> 2, c = (lane & 3) * 8;
+  for (int rb = 0; rb < 2; ++rb)
+    for (int cb = 0; cb < 3 && 32 * cb < cols; ++cb) {   // uniform
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const uint32_t row = 32 * rb + r + 16 * t, col = 32 * cb + c;
+        const u32x4 v = *(const u32x4*)(cs + row * PN + col);
+        if ((int)(64 * h + row) < rows) *(u32x4*)(yw + (size_t)(64 * h + row) * ldy + col) = v;
+        hook(64 * h + row, col, v);
+      }
+      block_done(2 * h + rb, cb);
+    }
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // the reads are done before the staging area is written again
+  __builtin_amdgcn_wave_barrier();
 }
 
 struct NoHook {

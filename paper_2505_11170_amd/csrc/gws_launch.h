@@ -102,15 +102,16 @@ StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk);
 bool stream_applicable(const GemmArgs& g);
 int launch_gemm_stream(const GemmArgs& g, int w_is_nk, const StreamPlan& p, hipStream_t stream);
 int launch_gemm_stream_sample(const GemmArgs& g, int w_is_nk, int fmt, int p, hipStream_t stream);
-enum class GemmRoute { kStream, kMiddle, kLarge, kSmall };
+enum class GemmRoute { kStream, kMiddle, kLarge, kNarrow, kSmall };
 struct RoutePlan {   // estimates in us; 1e30: not a shape for that kernel
   StreamPlan stream;
-  double middle_us, large_us;
+  double middle_us, large_us, narrow_us;
 };
 GemmRoute gemm_route(const GemmArgs& g, int w_is_nk, RoutePlan& plan);
 bool sample_in_operand(const GemmArgs& g, int w_is_nk);   // the faster way to a sampled product (same bits either way)
 bool gemm256_edge_applicable(const GemmArgs& g);
 int launch_gemm256_edge(const GemmArgs& g, int w_is_nk, hipStream_t stream);
+int launch_gemm256_narrow(const GemmArgs& g, int w_is_nk, hipStream_t stream);   // shapes as gemm256_edge_applicable
 bool gemm128_applicable(const GemmArgs& g);
 int launch_gemm128(const GemmArgs& g, int w_is_nk, hipStream_t stream);
 bool gemm256_applicable(const GemmArgs& g);
@@ -134,6 +135,7 @@ int compute_units();   // of the current device; 0 if the query fails
 // row-major (K = the contraction length); with_dbt adds Eq. 4's block reduction on y.
 bool gemm256_tn_applicable(const GemmArgs& g);
 int launch_gemm256_tn(const GemmArgs& g, bool with_dbt, hipStream_t stream);
+int launch_gemm256_tn_narrow(const GemmArgs& g, bool with_dbt, hipStream_t stream);   // the same with tiles of 256 x 192
 // weights of few tiles (gws_gemm_stream_tn.hip): a 16 mt x 64 piece a workgroup, the tokens split over its wavefronts
 struct TnPlan {
   int mt;

@@ -184,31 +184,38 @@ static int launch_layout(const GemmArgs& g, int w_is_nk, dim3 grid, hipStream_t 
 }
 
 // Which kernel multiplies.  Chosen by the sizes alone, the same for the plain and the sampling form and whether or not a
-// weight rides along, so that the sums over K run in the same order in all of them (the middle and large tiles and the
-// sampling kernel above walk K from end to end; the stream kernels split it).  Estimates in us, fitted to MI355X timings
+// weight rides along, so that the sums over K run in the same order in all of them (the middle, large and narrow tiles and
+// the sampling kernel above walk K from end to end; the stream kernels split it).  Estimates in us, fitted to MI355X timings
 // of all of them at some thirty sizes.  Rounds are rounds of workgroups, one per compute unit; a K-step is 64 deep.
 //   middle: 0.42 a K-step ([K x N] 0.45), more in several rounds.  1000 x 800 -> 2304: 10 (stream 17, large 20); 2048 x 2048 -> 2048: 19 (31, 38);
 //     4096 x 3072 -> 768: 27 (45, 54); 4096 x 768 -> 3072: 25 (52, 22)
 //   large: 1.05 to 1.25 a K-step, the card's power limit with all compute units at work.  5000 x 2048 -> 2560: 43 (middle 66);
 //     8192 x 2048 -> 2048: 50 (69); 8000 x 768 -> 2304: 41 (39); 6000 x 512 -> 1536: 17 (19)
+//   narrow (256 x 192): four fifths of the large tile's K-step for three quarters of its columns, where that takes fewer or
+//     fuller rounds.  4100 x 4096 -> 4096: 129 (large 161); 8192 x 2048 -> 2560: 77 (94); 8000 x 768 -> 2304: 36 (43);
+//     4096 x 768 -> 3072: 22 (25); 8192 x 2048 -> 2048: 71 (54)
 GemmRoute gemm_route(const GemmArgs& g, int w_is_nk, RoutePlan& plan) {
   const double cus = compute_units() > 0 ? compute_units() : 256;
   const double nk = ceil(g.K / 64.0);
   auto tiles = [&](double t) { return ceil(g.M / t) * ceil(g.N / t); };
-  plan = RoutePlan{{0, 0, 0, 1e30}, 1e30, 1e30};
+  plan = RoutePlan{{0, 0, 0, 1e30}, 1e30, 1e30, 1e30};
   if (gemm256_edge_applicable(g) || gemm256_applicable(g)) {
     const double n = tiles(256.0);
     plan.large_us = 6.0 + ceil(n / cus) * (3.0 + nk * (1.05 + 0.2 * fmin(1.0, n / cus)));
+  }
+  if (gemm256_edge_applicable(g)) {
+    const double n = ceil(g.M / 256.0) * ceil(g.N / 192.0);
+    plan.narrow_us = 6.0 + ceil(n / cus) * (3.0 + nk * 0.8 * (1.05 + 0.2 * fmin(1.0, n / cus)));
   }
   if (gemm128_applicable(g)) {
     const double n = tiles(128.0), busy = n > cus ? 1.0 : 0.0;
     plan.middle_us = 3.3 + ceil(n / cus) * (2.0 + nk * (w_is_nk ? 0.42 + 0.05 * busy : 0.45 + 0.07 * busy));
   }
   if (stream_applicable(g)) plan.stream = stream_plan(g.M, g.N, g.K, w_is_nk != 0);
-  const double sequential = fmin(plan.large_us, plan.middle_us);
+  const double sequential = fmin(plan.large_us, fmin(plan.narrow_us, plan.middle_us));
   if (plan.stream.p > 0 && plan.stream.us < sequential) return GemmRoute::kStream;
   if (sequential > 1e29) return GemmRoute::kSmall;
-  return plan.middle_us < plan.large_us ? GemmRoute::kMiddle : GemmRoute::kLarge;
+  return plan.large_us <= sequential ? GemmRoute::kLarge : plan.narrow_us <= sequential ? GemmRoute::kNarrow : GemmRoute::kMiddle;
 }
 
 // Whether sampling in the operand load beats the sampling kernel and the GEMM behind it: one tile of rows of X (every block
@@ -235,6 +242,7 @@ int launch_gemm(const GemmArgs& g, int w_is_nk, int fused, int fmt, hipStream_t 
   if (route == GemmRoute::kStream)
     return fused ? launch_gemm_stream_sample(g, w_is_nk, fmt, plan.stream.p, stream) : launch_gemm_stream(g, w_is_nk, plan.stream, stream);
   if (!fused && route == GemmRoute::kMiddle) return launch_gemm128(g, w_is_nk, stream);
+  if (!fused && route == GemmRoute::kNarrow) return launch_gemm256_narrow(g, w_is_nk, stream);
   if (!fused && route == GemmRoute::kLarge) return gemm256_applicable(g) ? launch_gemm256(g, w_is_nk, stream) : launch_gemm256_edge(g, w_is_nk, stream);
   if (!fused) return launch_layout<false, 0>(g, w_is_nk, grid, stream);
   switch (fmt) {

@@ -397,3 +397,19 @@ def test_whole_large_tiles_at_every_number_of_k_steps(w_is_nk):
         kn = (w.t().contiguous() if w_is_nk else w).float()
         ref, mag = x.float() @ kn, x.float().abs() @ kn.abs()
         assert bool(((y.float() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2 * K * 2.0 ** -24 * mag).all()), steps
+
+
+@pytest.mark.parametrize("w_is_nk", [False, True])
+@pytest.mark.parametrize("M,N", [(8192, 2560), (8000, 2336), (4100, 4096)])
+def test_narrow_large_tiles_at_every_number_of_k_steps(M, N, w_is_nk):
+    # sizes whose 256 x 192 tiles fill the rounds better; whole and ragged edges, K of whole and half steps of 64
+    for K in [64 * i + 32 * (i % 2 if i > 1 else 0) for i in range(4, 17)]:
+        gen = torch.Generator(device=DEV).manual_seed(K)
+        x = torch.randn(M, K, generator=gen, device=DEV).to(torch.bfloat16)
+        w = (torch.randn(*((N, K) if w_is_nk else (K, N)), generator=gen, device=DEV) * 0.02).to(torch.bfloat16)
+        y = torch.zeros(M, N + 8, dtype=torch.bfloat16, device=DEV)
+        gws.gws_gemm_bf16(x, w, y[:, :N], w_is_nk=w_is_nk)
+        kn = (w.t().contiguous() if w_is_nk else w).float()
+        ref, mag = x.float() @ kn, x.float().abs() @ kn.abs()
+        assert bool(((y[:, :N].float() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2 * K * 2.0 ** -24 * mag).all()), K
+        assert bool((y[:, N:] == 0).all())

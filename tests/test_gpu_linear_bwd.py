@@ -181,10 +181,10 @@ def fp32_product(a, b):
     return a.float().t().contiguous() @ b.float()
 
 
-@pytest.mark.parametrize("tokens,rows,cols", [(64 * i, 4096, 4096) for i in range(1, 15)] + [(8192, 2048, 2048), (4096, 768, 3072), (8192, 512, 512)]
+@pytest.mark.parametrize("tokens,rows,cols", [(64 * i, 4096, 4096) for i in range(1, 15)] + [(64 * i, 2048, 5632) for i in range(6, 20)] + [(8192, 2048, 2048), (4096, 768, 3072), (8192, 512, 512)]
                          + [(64, 256, 256), (128, 256, 512), (320, 512, 768), (576, 1536, 1024), (1600, 1280, 1024)])
 def test_every_form_of_the_weight_gradient(tokens, rows, cols):
-    # one workgroup per 256 x 256 tile (256 tiles, every number of K-steps around the rings' period), the tokens split over
+    # one workgroup per 256 x 256 or 256 x 192 tile (256 and 240 tiles, every number of K-steps around the rings' period), the tokens split over
     # workgroups (all the workspace, room for two parts), small pieces with the tokens split over wavefronts (fewer units of
     # 64 tokens than wavefronts, uneven numbers of them): dW to its rounding and the order of fp32 sums, and dL/db_t to the
     # separate kernel's on the same bytes
