@@ -118,13 +118,52 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_kernel(const GemmArgs g) {
   reduce_store<MT, NT, P, MC>(acc, lds, g, m0, n0);
 }
 
+// Eq. 3 + cast on one 32 x 32 block of the weight, the wavefront's (group i of a lane: storage row lane / 4 + 16 i, columns
+// 8 (lane % 4) .. + 7), turned through `blk`, 32 x LP elements of the wavefront's own LDS, into the two fragments (16 outputs,
+// 32 k) the MFMA takes.  row0, col0: the block's storage origin; writer: this wavefront stores w_hat and scale (if wanted).
+constexpr int LP = 40;   // row pitch of the staged block (elements)
+template <int FMT, bool W_NK>
+__device__ __forceinline__ void sampled_block(const GemmArgs& g, const u32x4 (&w)[2], float bt, uint32_t row0, uint32_t col0,
+                                              size_t block, bool writer, uint16_t* blk, Frag8 (&f)[2]) {
+  const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4, q = lane & 3, r = lane >> 2;
+  uint32_t m = absmax_pk(w[1], absmax_pk(w[0], 0));
+  m = max(m & 0xFFFFu, m >> 16);
+  m = block_max_u32(m);
+  const uint32_t a16 = max(m, (uint32_t)__shfl_xor((int)m, 4));   // the block is the whole wavefront's here
+  BlockScale s = block_scale(a16, bt);
+  if (FMT == 1) cast_constants<8, -6>(a16, s);
+  if (FMT == 2) cast_constants<4, -2>(a16, s);
+  writer = writer && g.w_hat != nullptr;
+  if (writer && lane == 0) g.scale[block] = s.s32;
+  const bool hw = (FMT == 1) && s.hw_safe;   // uniform: the wavefront holds one block
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const uint32_t srow = row0 + r + 16 * i, scol = col0 + 8 * q;
+    const Noise n = group_noise(g.cg0 + (scol >> 3), g.row0 + srow, g.step_lo, g.step_hi, g.seed_lo, g.seed_hi);
+    const u32x4 v = hw ? sample_group<FMT>(w[i], n, s, true) : sample_group<FMT>(w[i], n, s, false);
+    if (writer) *(u32x4*)(g.w_hat + (size_t)srow * g.ldw + scol) = v;
+    *(u32x4*)(blk + (r + 16 * i) * LP + 8 * q) = v;
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wavefront's own writes have landed
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    if (W_NK) {
+      f[j].u = *(const u32x4*)(blk + (16 * j + li) * LP + 8 * grp);
+    } else {   // transposing read: lanes 4 t .. 4 t + 3 of 16 point at 16 outputs of row k0 + t
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        f[j].h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((GWS_LDS i16x4*)(blk + (8 * grp + 4 * h + (li >> 2)) * LP + 16 * j + 4 * (li & 3)));
+    }
+  }
+}
+
 // The sampling form: a wavefront loads one 32 x 32 block of the weight per step (two 16-byte groups per lane), samples
 // it in registers, turns it through its own 2.5 KiB of LDS and multiplies.  Bound by the vector ALU work of the
 // sampling (about 275 instructions a block), which every 16 MT rows of X repeat.
 template <int MT, int P, int FMT, bool W_NK>
 __global__ __launch_bounds__(64 * P) void gemm_stream_sample_kernel(const GemmArgs g) {
   using namespace stream;
-  constexpr int LP = 40;   // row pitch of the staged block (elements)
   constexpr int kRed = red_bytes(MT, 2, P), kBlk = P * 32 * LP * 2;
   __shared__ __attribute__((aligned(16))) char lds[kRed > kBlk ? kRed : kBlk];
   const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4;
@@ -167,40 +206,8 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_sample_kernel(const GemmAr
     Frag8 x[MT];
 #pragma unroll
     for (int i = 0; i < MT; ++i) x[i].u = *(const GWS_GLOBAL u32x4*)(xb + (size_t)b * 64 + xo[i]);
-    // Eq. 3 + cast
-    uint32_t m = absmax_pk(w[1], absmax_pk(w[0], 0));
-    m = max(m & 0xFFFFu, m >> 16);
-    m = block_max_u32(m);
-    const uint32_t a16 = max(m, (uint32_t)__shfl_xor((int)m, 4));   // the block is the whole wavefront's here
-    BlockScale s = block_scale(a16, bt);
-    if (FMT == 1) cast_constants<8, -6>(a16, s);
-    if (FMT == 2) cast_constants<4, -2>(a16, s);
-    const bool writer = m0 == 0 && g.w_hat != nullptr;
-    if (writer && lane == 0) g.scale[block_index(b)] = s.s32;
-    const bool hw = (FMT == 1) && s.hw_safe;   // uniform: the wavefront holds one block
-    const uint32_t row0 = W_NK ? n0 : b * 32, col0 = W_NK ? b * 32 : n0;   // the block's storage origin
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const uint32_t srow = row0 + r + 16 * i, scol = col0 + 8 * q;
-      const Noise n = group_noise(g.cg0 + (scol >> 3), g.row0 + srow, g.step_lo, g.step_hi, g.seed_lo, g.seed_hi);
-      const u32x4 v = hw ? sample_group<FMT>(w[i], n, s, true) : sample_group<FMT>(w[i], n, s, false);
-      if (writer) *(u32x4*)(g.w_hat + (size_t)srow * g.ldw + scol) = v;
-      *(u32x4*)(blk + (r + 16 * i) * LP + 8 * q) = v;
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wavefront's own writes have landed
-    __builtin_amdgcn_wave_barrier();
     Frag8 f[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      if (W_NK) {
-        f[j].u = *(const u32x4*)(blk + (16 * j + li) * LP + 8 * grp);
-      } else {   // transposing read: lanes 4 t .. 4 t + 3 of 16 point at 16 outputs of row k0 + t
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-          f[j].h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-              (GWS_LDS i16x4*)(blk + (8 * grp + 4 * h + (li >> 2)) * LP + 16 * j + 4 * (li & 3)));
-      }
-    }
+    sampled_block<FMT, W_NK>(g, w, bt, W_NK ? n0 : b * 32, W_NK ? b * 32 : n0, block_index(b), m0 == 0, blk, f);
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -209,6 +216,97 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_sample_kernel(const GemmAr
     __builtin_amdgcn_wave_barrier();
   }
   reduce_store<MT, 2, P, MT>(acc, lds, g, m0, n0);
+}
+
+// Many rows of X, the weight sampled on its way in, K from end to end (the order of the middle and large tiles' sums, so Y is
+// their Y): a workgroup owns 16 MT rows x 128 columns, a wavefront 32 of the columns.  X comes through LDS in units of 64 k, a
+// ring of two stages that the four wavefronts share, one barrier a unit; the weight's blocks go from a wavefront's
+// registers through its own LDS as above.  Bound by the vector ALU work of the sampling, which every 16 MT rows repeat
+// (2.3 us a unit with one workgroup on a compute unit, 2.6 with two; a third needs spills: a quarter slower).  Against
+// gemm_kernel (gws_linear.hip), us, [K x N] and [N x K]: 1107 x 2528 -> 3104 148, 130 -> 101, 94; 4000 x 512 -> 512 29, 28 ->
+// 16, 15; 8192 x 2048 -> 5632 610, 544 -> 519, 500; 5683 x 608 -> 1792 61, 54 -> 56, 57.
+template <int MT, int FMT, bool W_NK>
+__global__ __launch_bounds__(256, 2) void gemm_rows_sample_kernel(const GemmArgs g) {
+  using namespace stream;
+  constexpr int BM = 16 * MT, D = 2, XS = BM * 64, LX = BM / 32;   // load instructions of a wavefront and unit
+  static_assert(MT == 4 || MT == 8, "");
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[D * XS];
+  __shared__ __attribute__((aligned(16))) uint16_t blocks[4 * 32 * LP];
+  const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4, q = lane & 3, r = lane >> 2;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint16_t* blk = blocks + wave * 32 * LP;
+  uint32_t m0, n0;
+  tile_origin(g, BM, 128, false, m0, n0);
+  n0 += 32 * wave;
+  const bool live = n0 < g.N;   // N is a multiple of 32: a wavefront's columns exist or do not
+  const uint32_t nu = (g.K + 63) >> 6, nb = g.K >> 5;
+
+  uint32_t xo[LX];
+#pragma unroll
+  for (int i = 0; i < LX; ++i) {   // rows BM / 4 wave + 8 i + lane / 8
+    const uint32_t row = BM / 4 * wave + 8 * i + (lane >> 3);
+    xo[i] = (umin(row, g.M - 1 - m0) * g.ldx + ((lane & 7) ^ ((row >> 1) & 7)) * 8) * 2;
+  }
+  const GWS_GLOBAL char* xb = (const GWS_GLOBAL char*)(g.x + (size_t)m0 * g.ldx);
+  auto load_x = [&](uint32_t u) {
+    const uint32_t k0 = umin(64 * u, g.K - 64);   // the half unit at the end of K is fetched as the second half of a whole one
+#pragma unroll
+    for (int i = 0; i < LX; ++i) direct(xb + (size_t)k0 * 2, xo[i], ring + (u % D) * XS + (wave * LX + i) * 512);
+  };
+  const uint32_t nw = live ? n0 : 0;   // a wavefront past the edge reads the first columns and multiplies nothing
+  const uint32_t wo = (r * g.ldw + 8 * q) * 2;
+  const GWS_GLOBAL char* wb = (const GWS_GLOBAL char*)(W_NK ? g.w + (size_t)nw * g.ldw : g.w + nw);
+  const size_t wstep = W_NK ? 64 : (size_t)g.ldw * 64;   // bytes from a block to the next along K
+  const uint32_t nbc = (W_NK ? g.K : g.N) >> 5;
+  auto block_index = [&](uint32_t b) { return W_NK ? (size_t)(nw >> 5) * nbc + b : (size_t)b * nbc + (nw >> 5); };
+  u32x4 nxt[2];
+  float bt_nxt = 0.0f;
+  auto load_w = [&](uint32_t b) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) nxt[i] = *(const GWS_GLOBAL u32x4*)(wb + b * wstep + (size_t)(16 * i) * g.ldw * 2 + wo);
+    bt_nxt = global_ptr<float>(g.bt)[block_index(b)];
+  };
+
+  f32x4 acc[MT][2];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) acc[i][0] = acc[i][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  load_w(0);
+  load_x(0);
+  for (uint32_t u = 0; u < nu; ++u) {
+    // this unit, requested a unit's sampling ago, has landed, and every wavefront is past its reads of the other stage
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (u + 1 < nu) load_x(u + 1);
+    if (!live) continue;
+    const uint16_t* xs = ring + (u % D) * XS;
+    const bool half = 64 * u + 64 > g.K;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (h == 0 && half) continue;   // only the second half of the stage belongs to this unit
+      const uint32_t b = half ? nb - 1 : 2 * u + h;
+      const u32x4 w[2] = {nxt[0], nxt[1]};
+      const float bt = bt_nxt;
+      load_w(umin(b + 1, nb - 1));
+      Frag8 f[2];
+      sampled_block<FMT, W_NK>(g, w, bt, W_NK ? n0 : b * 32, W_NK ? b * 32 : n0, block_index(b), m0 == 0, blk, f);
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        Frag8 x;
+        x.u = *(const u32x4*)(xs + (16 * i + li) * 64 + (((4 * h + grp) ^ ((li >> 1) & 7)) * 8));
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[j].v, x.v, acc[i][j], 0, 0, 0);
+      }
+    }
+  }
+  if (!live) return;
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {   // row 16 i + lane % 16, columns 16 j + 4 (lane / 16) .. + 3
+    const uint32_t row = m0 + 16 * i + li;
+    if (row < g.M) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        *(u32x2*)(g.y + (size_t)row * g.ldy + n0 + 16 * j + 4 * grp) = u32x2{pack_bf16_rne(acc[i][j][0], acc[i][j][1]), pack_bf16_rne(acc[i][j][2], acc[i][j][3])};
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -279,6 +377,39 @@ static void launch_sampled_fmt(const GemmArgs& g, int w_is_nk, int p, hipStream_
   else if (g.M <= 16) launch_sampled<1, 8, FMT>(g, w_is_nk, s);
   else if (g.M <= 32) launch_sampled<2, 8, FMT>(g, w_is_nk, s);
   else launch_sampled<4, 8, FMT>(g, w_is_nk, s);
+}
+
+template <int MT, int FMT>
+static void launch_rows(const GemmArgs& g, int w_is_nk, hipStream_t s) {
+  const dim3 grid(((g.M + 16 * MT - 1) / (16 * MT)) * ((g.N + 127) / 128));
+  if (w_is_nk) hipLaunchKernelGGL((gemm_rows_sample_kernel<MT, FMT, true>), grid, dim3(256), 0, s, g);
+  else hipLaunchKernelGGL((gemm_rows_sample_kernel<MT, FMT, false>), grid, dim3(256), 0, s, g);
+}
+
+// 128 rows a workgroup (fewer samplings of a block) where that still gives half of the compute units one.
+template <int FMT>
+static void launch_rows_fmt(const GemmArgs& g, int w_is_nk, hipStream_t s) {
+  const uint64_t cus = compute_units() > 0 ? compute_units() : 256, tn = (g.N + 127) / 128;
+  if ((uint64_t)((g.M + 127) / 128) * tn >= cus / 2) launch_rows<8, FMT>(g, w_is_nk, s);
+  else launch_rows<4, FMT>(g, w_is_nk, s);
+}
+
+// Two workgroups run on a compute unit: between one and one and a half rounds of them the 128 x 128 x 32 kernel, which packs
+// them closer, is as fast for [N x K] weights, which it need not transpose.
+bool rows_sample_applicable(const GemmArgs& g, int w_is_nk) {
+  const uint64_t cus = compute_units() > 0 ? compute_units() : 256, n = (uint64_t)((g.M + 127) / 128) * ((g.N + 127) / 128);
+  return stream_applicable(g) && !(w_is_nk && n > 2 * cus && n <= 3 * cus);
+}
+
+int launch_gemm_rows_sample(const GemmArgs& g, int w_is_nk, int fmt, hipStream_t s) {
+  if ((uint64_t)((g.M + 63) / 64) * ((g.N + 127) / 128) >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
+  switch (fmt) {
+    case GWS_FMT_BF16: launch_rows_fmt<0>(g, w_is_nk, s); break;
+    case GWS_FMT_FP8_E4M3: launch_rows_fmt<1>(g, w_is_nk, s); break;
+    case GWS_FMT_FP6_E3M2: launch_rows_fmt<2>(g, w_is_nk, s); break;
+    default: return GWS_ERR_FORMAT;
+  }
+  return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
 
 // The same parts of K as the plain kernel (p), whatever the tile: the sums are the same bits.

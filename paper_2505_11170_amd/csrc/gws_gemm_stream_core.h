@@ -8,7 +8,7 @@
 namespace gws {
 
 namespace stream {
-constexpr uint32_t kMaxLd = 1u << 24;   // leading dimensions the 32-bit lane offsets reach (63 rows x 2 bytes)
+constexpr uint32_t kMaxLd = 1u << 23;   // leading dimensions the 32-bit lane offsets reach (255 rows x 2 bytes)
 
 __device__ __forceinline__ uint32_t umin(uint32_t a, uint32_t b) { return a < b ? a : b; }
 

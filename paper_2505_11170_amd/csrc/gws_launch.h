@@ -102,6 +102,9 @@ StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk);
 bool stream_applicable(const GemmArgs& g);
 int launch_gemm_stream(const GemmArgs& g, int w_is_nk, const StreamPlan& p, hipStream_t stream);
 int launch_gemm_stream_sample(const GemmArgs& g, int w_is_nk, int fmt, int p, hipStream_t stream);
+// many rows, the weight sampled on its way in, K from end to end
+bool rows_sample_applicable(const GemmArgs& g, int w_is_nk);
+int launch_gemm_rows_sample(const GemmArgs& g, int w_is_nk, int fmt, hipStream_t stream);
 enum class GemmRoute { kStream, kMiddle, kLarge, kNarrow, kSmall };
 struct RoutePlan {   // estimates in us; 1e30: not a shape for that kernel
   StreamPlan stream;

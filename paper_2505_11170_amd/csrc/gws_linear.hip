@@ -1,5 +1,6 @@
-// BF16 MFMA GEMM for gfx950 with an optional GaussWS sampling stage in the
-// weight-operand path: Y = X * w_hat (fused; paper Eq. 3 + cast applied to each
+// The choice of the GEMM's kernel, and the one for every shape that the others (gws_gemm_stream.hip, gws_gemm128.hip,
+// gws_gemm256.hip) do not take or are not faster for: a BF16 MFMA GEMM for gfx950 with an optional GaussWS sampling stage in
+// the weight-operand path: Y = X * w_hat (fused; paper Eq. 3 + cast applied to each
 // 32x32 block of W on its way from global memory to LDS) or Y = X * W (plain
 // twin, same tiling, used as the reference point for the fused overhead).
 //
@@ -244,6 +245,7 @@ int launch_gemm(const GemmArgs& g, int w_is_nk, int fused, int fmt, hipStream_t 
   if (!fused && route == GemmRoute::kMiddle) return launch_gemm128(g, w_is_nk, stream);
   if (!fused && route == GemmRoute::kNarrow) return launch_gemm256_narrow(g, w_is_nk, stream);
   if (!fused && route == GemmRoute::kLarge) return gemm256_applicable(g) ? launch_gemm256(g, w_is_nk, stream) : launch_gemm256_edge(g, w_is_nk, stream);
+  if (fused && rows_sample_applicable(g, w_is_nk)) return launch_gemm_rows_sample(g, w_is_nk, fmt, stream);
   if (!fused) return launch_layout<false, 0>(g, w_is_nk, grid, stream);
   switch (fmt) {
     case GWS_FMT_BF16: return launch_layout<true, 0>(g, w_is_nk, grid, stream);

@@ -413,3 +413,11 @@ def test_narrow_large_tiles_at_every_number_of_k_steps(M, N, w_is_nk):
         ref, mag = x.float() @ kn, x.float().abs() @ kn.abs()
         assert bool(((y[:, :N].float() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2 * K * 2.0 ** -24 * mag).all()), K
         assert bool((y[:, N:] == 0).all())
+
+
+@pytest.mark.parametrize("w_is_nk", [False, True])
+@pytest.mark.parametrize("M,K,N", [(1500, 160, 1760), (2049, 288, 1312), (1537, 96, 4128), (4160, 64, 544)])
+def test_sampling_in_the_operand_load_of_many_rows(M, K, N, w_is_nk):
+    # 64 and 128 rows a workgroup, a last column tile of one wavefront, K of whole and half units; Y and w_hat bit for bit
+    for fmt in (gws.FMT_BF16, gws.FMT_FP8_E4M3, gws.FMT_FP6_E3M2):
+        run_case(M, K, N, w_is_nk, fmt, seed_id=93, ldx_pad=8, ldy_pad=8, rows_sel=np.array([0, 63, 64, M // 2, M - 1]), mode=gws.LINEAR_IN_OPERAND)
