@@ -142,7 +142,8 @@ int run_batched(const gws_tensor* t, int n, const gws_bitwidth* bw, const gws_mx
   }
   if (tune.per_x > 0) per_x = (uint32_t)tune.per_x;
   // Streaming or not.  A forward call that writes little (one weight, a few layers) is usually followed by its consumer, and
-  // the whole of w_hat fits in the last-level cache: ordinary accesses; a call over a model's worth of weights streams past
+  // the whole of w_hat fits in the last-level cache: ordinary stores, with ordinary loads up to 8 MB (2048 x 5632, 23 MB:
+  // 12.4 us with streaming loads, 13.9 without); a call over a model's worth of weights streams past
   // the caches (ordinary loads: the 124M model's two passes 87.6 -> 92.7 us together, though each of them alone repeats
   // faster with its 170 MB in the 256 MB last-level cache; the 1B model's backward pass 303 -> 348 us).
   // Rows that do not start on cache lines (FP6 codes never do: a tile's row is 1.5 lines): ordinary stores, see load16, and
@@ -150,14 +151,14 @@ int run_batched(const gws_tensor* t, int n, const gws_bitwidth* bw, const gws_mx
   // A workgroup tile is 32 x 256 elements = 16 KiB.
   const uint64_t tile_bytes = total * (16u << 10);
   int mode = kStreamAll;
-  if (keep || tile_bytes <= ((uint64_t)32 << 20)) mode = kKeep;
+  if (keep || tile_bytes <= ((uint64_t)32 << 20)) mode = tile_bytes <= ((uint64_t)8 << 20) ? kKeep : kStreamReads;
   bool whole_lines = !(mx && fmt == GWS_FMT_FP6_E3M2);
   for (int i = 0; i < n && whole_lines; ++i) {
     const void* out = fwd ? (mx ? mx[i].codes : t[i].w_hat) : t[i].dw;
     const int64_t row_bytes = mx ? mx[i].ldc : 2 * t[i].ld;
     if (t[i].rows > 0 && t[i].cols > 0 && (fwd || copies) && ((row_bytes & 127) != 0 || !aligned(out, 128))) whole_lines = false;
   }
-  if (!whole_lines && mode == kStreamAll) mode = tile_bytes <= ((uint64_t)192 << 20) ? kKeep : kStreamReads;
+  if (!whole_lines) mode = tile_bytes <= ((uint64_t)192 << 20) ? kKeep : kStreamReads;
 
   LaunchArgs a;
   memset(&a, 0, sizeof a);

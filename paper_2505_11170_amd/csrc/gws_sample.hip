@@ -379,6 +379,7 @@ static OneArgs one_of(const LaunchArgs& a) { return OneArgs{a.t[0], a.step_lo, a
 template <int FMT, bool MX, int BASIS>
 static void launch_fwd_stream(const LaunchArgs& a, uint32_t n_wg, int mode, int variant, hipStream_t stream) {
   if (BASIS == kBasisBits && !MX && mode == kKeep && a.n == 1) launch_fwd<FMT, false, kKeep, kBasisBits>(one_of(a), n_wg, variant, stream);
+  else if (BASIS == kBasisBits && !MX && mode == kStreamReads && a.n == 1) launch_fwd<FMT, false, kStreamReads, kBasisBits>(one_of(a), n_wg, variant, stream);
   else if (mode == kKeep) launch_fwd<FMT, MX, kKeep, BASIS>(a, n_wg, variant, stream);
   else if (mode == kStreamReads) launch_fwd<FMT, MX, kStreamReads, BASIS>(a, n_wg, variant, stream);
   else launch_fwd<FMT, MX, kStreamAll, BASIS>(a, n_wg, variant, stream);
