@@ -240,8 +240,8 @@ int gws_linear_bwd_w(const void* x, const void* dy, int64_t M, int64_t ldx, int6
  * fp32 partial tile in `workspace`, and a second kernel adds a tile's parts in a fixed order,
  * rounds once to BF16 and writes dW and dL/db_t as above.  Same arguments, results within the
  * same bounds (the fp32 additions are grouped by part; nothing depends on timing).
- * Where another form is faster for the sizes (a whole tile per workgroup, or small pieces of the
- * gradient whose tokens are split inside a workgroup) it is taken and the workspace left alone.
+ * Where small pieces of the gradient, whose tokens are split inside a workgroup, are faster for the sizes
+ * they are taken and the workspace left alone; no fp32 sum then runs over more tokens than a part's.
  *   gws_linear_bwd_w_workspace_bytes(w, M): bytes the split may use for this weight and M
  *     (host call; 0 when the one-kernel form is used: enough tiles, M too small, bad shape).
  *   workspace : device memory, 16-byte aligned, workspace_bytes long, not overlapping x, dy or

@@ -563,30 +563,29 @@ static uint32_t bwd_w_parts(int64_t rows, int64_t cols, int64_t M) {
   return parts < 2 ? 1u : (uint32_t)parts;
 }
 
-// The fastest way by an estimate in us, with workspace for `max_parts` parts: one workgroup per tile of 256 x 256 or of 256 x
-// 192 (four fifths of the time each: 2048 x 5632 over 8192 tokens 163 against 188), the tokens of a tile split over workgroups (2 .. max_parts), or small pieces of the gradient with the tokens split over a workgroup's
-// wavefronts (no workspace).  Fitted to MI355X timings, e.g. tokens x rows x cols 512 x 4096 x 4096 one tile each 26; 1024 x
-// 2048 x 4096 30, in two parts 39; 4096 x 2048 x 2048 92, in four parts 52, in small pieces 54; 2048 x 1024 x 1024 in four
-// parts 26, in small pieces 12.
-static int launch_bwd_w(const GemmArgs& g, bool with_dbt, uint32_t max_parts, void* workspace, hipStream_t stream) {
-  const double cus = compute_units() > 0 ? compute_units() : 256;
-  const double tiles = (double)(g.M / 256) * (double)(g.N / 256), nk = (double)(g.K / 64);
-  auto whole = [&](double n, double k_step) { return 6.0 + ceil(n / cus) * (3.0 + nk * k_step * (1.2 + 0.2 * fmin(1.0, n / cus))); };
-  const double wide_us = whole(tiles, 1.0), narrow_us = whole((double)(g.M / 256) * ceil(g.N / 192.0), 0.8);
-  double us = fmin(wide_us, narrow_us);
-  uint32_t parts = 1;
-  for (uint32_t p = 2; p <= max_parts; ++p) {
-    const double slabs = (double)gemm256_tn_split_bytes(g, p);   // written at about 5 MB/us, read again at 5.4
-    const double t = 12.0 + nk / p * 1.3 + slabs * (1.0 / 5.0e6 + 1.0 / 5.4e6);
-    if (t < us) {
-      us = t;
-      parts = p;
-    }
-  }
+// The fastest way by an estimate in us, among those whose fp32 sums run over no more tokens than a part's when the tokens are
+// split into `parts` (as many as the workspace holds): a longer sum has a larger error.  Elements of dW that are not the
+// rounded 64-bit value, 768 x 3072 over 4096 tokens: 2.6e-4 in one sum, 2.0e-4 in five, 1.7e-4 in seven.
+//  - With workspace: the tokens of a tile split over that many workgroups, or small pieces of the gradient with the tokens in
+//    four sums or (parts > 4) eight.
+//  - Without (parts < 2): one workgroup per tile of 256 x 256 or of 256 x 192 (four fifths of the time each: 2048 x 5632 over
+//    8192 tokens 163 against 188), or small pieces.
+// Fitted to MI355X timings, tokens x rows x cols: 512 x 4096 x 4096 one tile each 26; in parts and in small pieces 4096 x
+// 768 x 3072 40 and 50, 4096 x 768 x 2304 35 and 29, 4096 x 2048 x 2048 50 and 53, 2048 x 2048 x 2048 42 and 34, 8192 x
+// 512 x 512 29 and 32, 2048 x 1024 x 1024 26 and 12.
+static int launch_bwd_w(const GemmArgs& g, bool with_dbt, uint32_t parts, void* workspace, hipStream_t stream) {
   const TnPlan small = stream_tn_plan(g);
-  if (small.us < us) return launch_gemm_stream_tn(g, with_dbt, small, stream);
-  if (parts < 2) return narrow_us < wide_us ? launch_gemm256_tn_narrow(g, with_dbt, stream) : launch_gemm256_tn(g, with_dbt, stream);
-  return launch_gemm256_tn_split(g, with_dbt, (float*)workspace, parts, stream);
+  const double nk = (double)(g.K / 64);
+  if (parts >= 2) {
+    const double split_us = 8.2 + nk / parts * 1.19 + (double)gemm256_tn_split_bytes(g, parts) * 0.317e-6;
+    if (small.us < split_us) return launch_gemm_stream_tn(g, with_dbt, small, parts > 4, stream);
+    return launch_gemm256_tn_split(g, with_dbt, (float*)workspace, parts, stream);
+  }
+  const double cus = compute_units() > 0 ? compute_units() : 256;
+  auto whole = [&](double n, double k_step) { return 6.0 + ceil(n / cus) * (3.0 + nk * k_step * (1.2 + 0.2 * fmin(1.0, n / cus))); };
+  const double wide_us = whole((double)(g.M / 256) * (double)(g.N / 256), 1.0), narrow_us = whole((double)(g.M / 256) * ceil(g.N / 192.0), 0.8);
+  if (small.us < fmin(wide_us, narrow_us)) return launch_gemm_stream_tn(g, with_dbt, small, false, stream);
+  return narrow_us < wide_us ? launch_gemm256_tn_narrow(g, with_dbt, stream) : launch_gemm256_tn(g, with_dbt, stream);
 }
 
 int gws_linear_bwd_w(const void* x, const void* dy, int64_t M, int64_t ldx, int64_t ldy, const gws_tensor* w,

@@ -14,7 +14,8 @@
 
 namespace gws {
 
-template <int MT, int NT, int D, bool DBT>
+// HALVES: every wavefront sums its tokens in two halves, eight fp32 sums an element instead of four.
+template <int MT, int NT, int D, bool DBT, bool HALVES>
 __global__ __launch_bounds__(256) void gemm_stream_tn_kernel(const GemmArgs g) {
   using namespace stream;
   constexpr int P = 4, BM = 16 * MT, BN = 16 * NT, PB = 64 + 8;
@@ -63,28 +64,51 @@ __global__ __launch_bounds__(256) void gemm_stream_tn_kernel(const GemmArgs g) {
   for (int d = 0; d < D; ++d)
     if ((uint32_t)d < n) load(u0 + d, d);
   uint32_t slot = 0;
-  for (uint32_t i = 0; i < n; ++i) {
-    if (i + D <= n) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS * (D - 1)) : "memory");   // the unit has landed
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    const uint16_t* xs = ring + slot * STG;
-    Frag8 fx[2][MT], fw[2][NT];
+  auto units = [&](uint32_t i, uint32_t end) {
+    for (; i < end; ++i) {
+      if (i + D <= n) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS * (D - 1)) : "memory");   // the unit has landed
+      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      const uint16_t* xs = ring + slot * STG;
+      Frag8 fx[2][MT], fw[2][NT];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < 2; ++h) {
 #pragma unroll
-      for (int r = 0; r < MT; ++r) fx[h][r] = read_oc<MT>(xs, h, r, li, grp);
+        for (int r = 0; r < MT; ++r) fx[h][r] = read_oc<MT>(xs, h, r, li, grp);
 #pragma unroll
-      for (int j = 0; j < NT; ++j) fw[h][j] = read_oc<NT>(xs + XS, h, j, li, grp);
+        for (int j = 0; j < NT; ++j) fw[h][j] = read_oc<NT>(xs + XS, h, j, li, grp);
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read: the stage can be filled again
+      __builtin_amdgcn_sched_barrier(0);
+      if (i + D < n) load(u0 + i + D, slot);
+      slot = slot + 1 == D ? 0 : slot + 1;
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+          for (int r = 0; r < MT; ++r) acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[h][j].v, fx[h][r].v, acc[r][j], 0, 0, 0);
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read: the stage can be filled again
-    __builtin_amdgcn_sched_barrier(0);
-    if (i + D < n) load(u0 + i + D, slot);
-    slot = slot + 1 == D ? 0 : slot + 1;
+  };
+  if (!HALVES) {
+    units(0, n);
+  } else {
+    const uint32_t half = (n + 1) >> 1;
+    units(0, half);
+    f32x4 first[MT][NT];
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        first[i][j] = acc[i][j];
+        acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      }
+    units(half, n);
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
       for (int j = 0; j < NT; ++j)
 #pragma unroll
-        for (int r = 0; r < MT; ++r) acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[h][j].v, fx[h][r].v, acc[r][j], 0, 0, 0);
+        for (int e = 0; e < 4; ++e) acc[i][j][e] = __fadd_rn(first[i][j][e], acc[i][j][e]);
   }
 
   uint16_t* cs = (uint16_t*)(lds + kRed);
@@ -114,30 +138,33 @@ __global__ __launch_bounds__(256) void gemm_stream_tn_kernel(const GemmArgs g) {
   }
 }
 
-template <int MT, int D>
+template <int MT, int D, bool HALVES>
 static void launch_tn(const GemmArgs& g, bool with_dbt, hipStream_t s) {
   const dim3 grid((g.M / (16 * MT)) * (g.N / 64));
-  if (with_dbt) hipLaunchKernelGGL((gemm_stream_tn_kernel<MT, 4, D, true>), grid, dim3(256), 0, s, g);
-  else hipLaunchKernelGGL((gemm_stream_tn_kernel<MT, 4, D, false>), grid, dim3(256), 0, s, g);
+  if (with_dbt) hipLaunchKernelGGL((gemm_stream_tn_kernel<MT, 4, D, true, HALVES>), grid, dim3(256), 0, s, g);
+  else hipLaunchKernelGGL((gemm_stream_tn_kernel<MT, 4, D, false, HALVES>), grid, dim3(256), 0, s, g);
 }
 
 // mt: row tiles of 16 of the piece (4 or 8); us: the estimate as in stream_plan.
 TnPlan stream_tn_plan(const GemmArgs& g) {
   const double cus = compute_units() > 0 ? compute_units() : 256;
   TnPlan best = {0, 1e30};
-  static const struct { int mt; double rate; } tiles[] = {{4, 82.0}, {8, 65.0}};   // bytes per ns a compute unit takes
+  // the fixed part of a round, and the bytes per ns a compute unit takes; tokens x rows x cols 1024 x 2048 x 4096: 48.7 and
+  // 44.2 us (8 and 4 rounds), 4096 x 2048 x 2048 63.7 and 52.6 (4 and 2)
+  static const struct { int mt; double round, rate; } tiles[] = {{4, 2.7, 82.0}, {8, 4.5, 74.0}};
   for (const auto& t : tiles) {
     const double rounds = ceil((double)(g.M / (16 * t.mt)) * (double)(g.N / 64) / cus);
-    const double us = 2.8 + 2.7 * rounds + rounds * (double)g.K * 2 * 16 * (t.mt + 4) / t.rate * 1e-3;
+    const double us = 2.8 + rounds * (t.round + (double)g.K * 2 * 16 * (t.mt + 4) / t.rate * 1e-3);
     if (us < best.us) best = {t.mt, us};
   }
   return best;
 }
 
-int launch_gemm_stream_tn(const GemmArgs& g, bool with_dbt, const TnPlan& p, hipStream_t stream) {
+// halves: eight fp32 sums an element (512 x 512 over 1024 tokens 6.7 -> 7.9 us, 768 x 2304 over 4096 27.6 -> 29.0).
+int launch_gemm_stream_tn(const GemmArgs& g, bool with_dbt, const TnPlan& p, bool halves, hipStream_t stream) {
   if ((uint64_t)(g.M / 64) * (g.N / 64) >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
-  if (p.mt == 4) launch_tn<4, 2>(g, with_dbt, stream);
-  else launch_tn<8, 1>(g, with_dbt, stream);
+  if (p.mt == 4) halves ? launch_tn<4, 2, true>(g, with_dbt, stream) : launch_tn<4, 2, false>(g, with_dbt, stream);
+  else halves ? launch_tn<8, 1, true>(g, with_dbt, stream) : launch_tn<8, 1, false>(g, with_dbt, stream);
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
 

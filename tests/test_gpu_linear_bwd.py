@@ -205,3 +205,27 @@ def test_every_form_of_the_weight_gradient(tokens, rows, cols):
         gws.gws_sample_bwd([back], 5)
         terms = 0.6932 * d.scale * d.dw.float().abs().view(rows // 32, 32, cols // 32, 32).sum((1, 3)) * 2
         assert bool(((d.dbt - back.dbt).abs() <= 1e-5 * back.dbt.abs() + 1e-6 * terms).all()), nbytes
+
+
+@pytest.mark.parametrize("tokens,rows,cols", [(4096, 768, 3072), (1024, 2048, 4096), (8192, 1024, 1024), (8192, 512, 512), (1536, 1536, 1024), (8192, 2048, 2048)])
+def test_no_fp32_sum_runs_over_more_tokens_than_a_part_of_the_workspace(tokens, rows, cols):
+    # Every element of dW is 2^27 (first token) + ones - 2^27 (last token).  In fp32 the 2^27 (spacing 16) swallows the
+    # ones that the same sum meets after it, at most eight of 32 tokens at once; 16 of 64 tokens are ones, so sums that
+    # have not met it add to it exactly.  The ones that are missing say over how many tokens the first sum ran.
+    units = tokens // 64
+    one = (torch.arange(tokens) % 4 == 1) & (torch.arange(tokens) >= 32) & (torch.arange(tokens) < tokens - 32)
+    x = torch.zeros(tokens, rows, dtype=torch.bfloat16)
+    dy = torch.zeros(tokens, cols, dtype=torch.bfloat16)
+    x[one], dy[one] = 1.0, 1.0
+    x[0], x[-1], dy[0], dy[-1] = 2.0 ** 14, 2.0 ** 14, 2.0 ** 13, -2.0 ** 13
+    d = gws.TensorDesc(rows=rows, cols=cols, seed=3, dw=torch.zeros(rows, cols, dtype=torch.bfloat16, device=DEV))
+    part_bytes = rows * cols * 4
+    need = gws.gws_linear_bwd_w_workspace_bytes(d, tokens)
+    assert need >= 2 * part_bytes
+    for parts in sorted({2, need // part_bytes}):
+        gws.gws_linear_bwd_w_ws(x.to(DEV), dy.to(DEV), d, 5, torch.empty(parts * part_bytes, dtype=torch.uint8, device=DEV))
+        got = d.dw.float()
+        total, run = int(one.sum()), -(-units // parts)
+        assert float(got.max()) <= total
+        lost = total - float(got.min())
+        assert lost <= 16 * run + 2.0 ** -8 * total, (parts, lost / 16, run)   # what the rounding to BF16 may add
