@@ -174,6 +174,7 @@ int gws_sample_fwd_mx(const gws_tensor* t, const gws_mx_out* o, int n, int fmt, 
  *                           Needs w_hat/scale (GWS_ERR_NULL otherwise).
  *   GWS_LINEAR_AUTO         when w_hat/scale are given the faster of the two by an estimate on the
  *                           sizes (in-operand for a few rows of X, else two kernels), else in-operand.
+ *                           Two kernels where y lies on w->w, which the first has then read.
  * (Mode value 1 belonged to a retired kernel and is rejected with GWS_ERR_FORMAT.)
  * gws_linear_fwd is gws_linear_fwd_mode with GWS_LINEAR_AUTO.                              */
 #define GWS_LINEAR_AUTO 0

@@ -258,6 +258,23 @@ GemmArgs linear_args(const void* x, int64_t M, int64_t K, int64_t ldx, const gws
   return g;
 }
 
+// Whether one kernel may sample and multiply for a caller with room for w_hat, for whom a kernel of its own can sample first
+// (w and bt are then read before anything of Y is written, and w_hat and scale written before X is read): nothing that the
+// one kernel writes lies on what it reads or writes elsewhere.
+bool outputs_apart(const GemmArgs& g, const gws_tensor& w) {
+  struct Span { const void* p; size_t n; };
+  const size_t w_bytes = (size_t)w.rows * w.ld * 2, blocks = (size_t)(w.rows >> 5) * (w.cols >> 5) * 4;
+  const Span in[] = {{g.x, (size_t)g.M * g.ldx * 2}, {w.w, w_bytes}, {w.bt, blocks}}, y = {g.y, (size_t)g.M * g.ldy * 2};
+  const Span out[] = {y, {g.w_hat, g.w_hat ? w_bytes : 0}, {g.scale, g.scale ? blocks : 0}};
+  for (const Span& o : out) {
+    if (o.n == 0) continue;
+    for (const Span& i : in)
+      if (overlap2(o.p, o.n, i.p, i.n)) return false;
+    if (o.p != y.p && overlap2(o.p, o.n, y.p, y.n)) return false;
+  }
+  return true;
+}
+
 // Bytes of the staged w_hat of a weight, rounded up so that the block scales behind it stay aligned.
 inline size_t staged_bytes(const gws_tensor& w) { return (((size_t)w.rows * (size_t)w.ld * 2) + 255) & ~(size_t)255; }
 
@@ -273,7 +290,7 @@ int linear_staged(const void* x, int64_t M, int64_t K, int64_t ldx, const gws_te
   if (overlap2(staging, need, w->w, w_bytes) || overlap2(staging, need, x, (size_t)M * ldx * 2) ||
       overlap2(staging, need, y, (size_t)M * ldy * 2)) return GWS_ERR_ALIAS;
   GemmArgs g = linear_args(x, M, K, ldx, w, w_is_nk, step, y, ldy);
-  if (sample_in_operand(g, w_is_nk)) return launch_gemm(g, w_is_nk, kFusedInOperand, fmt, stream);   // nothing to stage
+  if (sample_in_operand(g, w_is_nk) && outputs_apart(g, *w)) return launch_gemm(g, w_is_nk, kFusedInOperand, fmt, stream);   // nothing to stage
   int rc = run_batched(&t, 1, nullptr, nullptr, true, fmt, step, stream, /*keep=*/true);
   if (rc != GWS_OK) return rc;
   g.w = (const uint16_t*)staging;
@@ -474,7 +491,7 @@ int gws_linear_fwd_mode(const void* x, int64_t M, int64_t K, int64_t ldx, const 
   if (mode == GWS_LINEAR_AUTO) {
     // Measured on MI355X: sampling the weight once with the streaming kernel and running the plain GEMM on w_hat beats the
     // kernel that samples in its operand load (8192 tokens: 0.155 against 0.61 ms) except for a few tokens.
-    mode = w->w_hat && !sample_in_operand(g, w_is_nk) ? GWS_LINEAR_TWO_KERNELS : GWS_LINEAR_IN_OPERAND;
+    mode = w->w_hat && !(sample_in_operand(g, w_is_nk) && outputs_apart(g, *w)) ? GWS_LINEAR_TWO_KERNELS : GWS_LINEAR_IN_OPERAND;
   }
   if (mode == GWS_LINEAR_TWO_KERNELS) {
     if (!w->w_hat) return GWS_ERR_NULL;

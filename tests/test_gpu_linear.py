@@ -421,3 +421,34 @@ def test_sampling_in_the_operand_load_of_many_rows(M, K, N, w_is_nk):
     # 64 and 128 rows a workgroup, a last column tile of one wavefront, K of whole and half units; Y and w_hat bit for bit
     for fmt in (gws.FMT_BF16, gws.FMT_FP8_E4M3, gws.FMT_FP6_E3M2):
         run_case(M, K, N, w_is_nk, fmt, seed_id=93, ldx_pad=8, ldy_pad=8, rows_sel=np.array([0, 63, 64, M // 2, M - 1]), mode=gws.LINEAR_IN_OPERAND)
+
+
+@pytest.mark.parametrize("w_is_nk", [False, True])
+@pytest.mark.parametrize("M", [1, 16, 64])
+def test_y_on_top_of_the_weight(M, w_is_nk):
+    # a caller with room for w_hat (its own, a workspace, the library's buffer) may be done with w: the weight is then
+    # sampled by a kernel of its own, at row counts that otherwise sample in the operand load
+    K, N, fmt, step = 1024, 3072, gws.FMT_FP8_E4M3, 6
+    t = synth.make_tensor(95, *((N, K) if w_is_nk else (K, N)), with_grad=False)
+    rows, cols = t["w"].shape
+    x, bt = synth.make_activation(96, M, K).to(DEV), t["bt"].to(DEV)
+
+    def run(form, on_weight):
+        w = t["w"].to(DEV)
+        y = w.view(-1)[:M * N].view(M, N) if on_weight else torch.zeros(M, N, dtype=torch.bfloat16, device=DEV)
+        d = gws.TensorDesc(rows=rows, cols=cols, seed=4, w=w, bt=bt)
+        if form == "hat":
+            d.w_hat, d.scale = torch.zeros_like(w), torch.zeros_like(bt)
+            gws.gws_linear_fwd(x, d, y, fmt, step, w_is_nk=w_is_nk)
+        elif form == "ws":
+            ws = torch.zeros(gws.gws_linear_fwd_workspace_bytes(d), dtype=torch.uint8, device=DEV)
+            gws.gws_linear_fwd_ws(x, d, y, fmt, step, ws, w_is_nk=w_is_nk)
+        else:
+            gws.gws_linear_fwd_static(x, d, y, fmt, step, w_is_nk=w_is_nk)
+        torch.cuda.synchronize()
+        return synth.bits(y)
+
+    ref = run("hat", False)
+    for form in ("hat", "ws", "static"):
+        assert (run(form, False) == ref).all(), form
+        assert (run(form, True) == ref).all(), form
