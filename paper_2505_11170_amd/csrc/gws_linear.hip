@@ -233,19 +233,32 @@ bool sample_in_operand(const GemmArgs& g, int w_is_nk) {
   return fused < 0.95 * (3.4 + 0.65e-6 * g.K * g.N + 1.5 + plan.stream.us);
 }
 
+// Y on top of an operand.  Where one workgroup makes all of Y it has read the operands before it writes, so a product of one
+// tile may be computed in place; the kernels below of smaller tiles would give it to several.
+static bool in_place(const GemmArgs& g, int w_is_nk, int fused) {
+  const uintptr_t y0 = (uintptr_t)g.y, y1 = y0 + ((size_t)(g.M - 1) * g.ldy + g.N) * 2;
+  auto on_y = [&](const void* p, size_t bytes) { return (uintptr_t)p < y1 && y0 < (uintptr_t)p + bytes; };
+  const uint32_t rows = w_is_nk ? g.N : g.K, cols = w_is_nk ? g.K : g.N;
+  return on_y(g.x, ((size_t)(g.M - 1) * g.ldx + g.K) * 2) || on_y(g.w, ((size_t)(rows - 1) * g.ldw + cols) * 2) ||
+         (fused && on_y(g.bt, (size_t)(rows >> 5) * (cols >> 5) * sizeof(float)));
+}
+
 int launch_gemm(const GemmArgs& g, int w_is_nk, int fused, int fmt, hipStream_t stream) {
   const uint64_t tiles = (uint64_t)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   if (tiles == 0) return GWS_OK;
   if (tiles >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
   const dim3 grid((uint32_t)tiles);
   RoutePlan plan;
-  const GemmRoute route = gemm_route(g, w_is_nk, plan);
+  GemmRoute route = gemm_route(g, w_is_nk, plan);
+  const bool one_tile = tiles == 1 || (!fused && g.M == 256 && g.N == 256 && gemm256_applicable(g));
+  const bool one_workgroup = one_tile && in_place(g, w_is_nk, fused);
+  if (one_workgroup) route = tiles == 1 ? GemmRoute::kSmall : GemmRoute::kLarge;
   if (route == GemmRoute::kStream)
     return fused ? launch_gemm_stream_sample(g, w_is_nk, fmt, plan.stream.p, stream) : launch_gemm_stream(g, w_is_nk, plan.stream, stream);
   if (!fused && route == GemmRoute::kMiddle) return launch_gemm128(g, w_is_nk, stream);
   if (!fused && route == GemmRoute::kNarrow) return launch_gemm256_narrow(g, w_is_nk, stream);
   if (!fused && route == GemmRoute::kLarge) return gemm256_applicable(g) ? launch_gemm256(g, w_is_nk, stream) : launch_gemm256_edge(g, w_is_nk, stream);
-  if (fused && rows_sample_applicable(g, w_is_nk)) return launch_gemm_rows_sample(g, w_is_nk, fmt, stream);
+  if (fused && !one_workgroup && rows_sample_applicable(g, w_is_nk)) return launch_gemm_rows_sample(g, w_is_nk, fmt, stream);
   if (!fused) return launch_layout<false, 0>(g, w_is_nk, grid, stream);
   switch (fmt) {
     case GWS_FMT_BF16: return launch_layout<true, 0>(g, w_is_nk, grid, stream);

@@ -452,3 +452,33 @@ def test_y_on_top_of_the_weight(M, w_is_nk):
     for form in ("hat", "ws", "static"):
         assert (run(form, False) == ref).all(), form
         assert (run(form, True) == ref).all(), form
+
+
+@pytest.mark.parametrize("w_is_nk", [False, True])
+@pytest.mark.parametrize("M,K,N", [(1, 64, 32), (128, 128, 128), (37, 96, 96), (100, 1024, 128), (256, 256, 256)])
+def test_a_product_of_one_tile_in_place(M, K, N, w_is_nk):
+    # Y on top of X or of the weight where one workgroup computes all of it: plain, with the weight sampled on its way in,
+    # and (up to 128 rows and columns) with it sampled in the operand load
+    fmt, step = gws.FMT_FP6_E3M2, 2
+    t = synth.make_tensor(97, *((N, K) if w_is_nk else (K, N)), with_grad=False)
+    rows, cols = t["w"].shape
+    bt, seed = t["bt"].to(DEV), oracle.derive_seed(1, 97)
+    xb = synth.make_activation(98, M, K)
+    q, _ = oracle.sample_fwd(synth.bits(t["w"]), t["bt"].numpy(), fmt, seed, step)
+
+    def run(on, sampled):
+        x, w = xb.to(DEV), t["w"].to(DEV)
+        y = (x.view(-1)[:M * N] if on == "x" else w.view(-1)[:M * N]).view(M, N)
+        if sampled:
+            gws.gws_linear_fwd(x, gws.TensorDesc(rows=rows, cols=cols, seed=seed, w=w, bt=bt), y, fmt, step, w_is_nk=w_is_nk)
+        else:
+            gws.gws_gemm_bf16(x, w, y, w_is_nk=w_is_nk)
+        torch.cuda.synchronize()
+        return synth.bits(y)
+
+    for on in ("x", "w"):
+        if M * N > (M * K if on == "x" else K * N):
+            continue
+        check_y(run(on, False), synth.bits(xb), synth.bits(t["w"]), w_is_nk)
+        if M <= 128:
+            check_y(run(on, True), synth.bits(xb), q, w_is_nk)
