@@ -233,8 +233,12 @@ def _marshal(descs: Sequence[TensorDesc]):
         if ld is None:
             ref = w if w is not None else g if g is not None else dw
             ld = ref.stride(0) if ref is not None and ref.dim() == 2 else d.cols
-        parts.append(_pack_tensor(_p(w) or 0, _p(d.w_hat) or 0, _p(d.bt) or 0, _p(d.scale) or 0, _p(g) or 0, _p(dw) or 0, _p(d.dbt) or 0,
-                                  d.rows, d.cols, ld, d.row0, d.col0, d.seed & 0xFFFFFFFFFFFFFFFF))
+        fields = (_p(w) or 0, _p(d.w_hat) or 0, _p(d.bt) or 0, _p(d.scale) or 0, _p(g) or 0, _p(dw) or 0, _p(d.dbt) or 0,
+                  d.rows, d.cols, ld, d.row0, d.col0, d.seed & 0xFFFFFFFFFFFFFFFF)
+        try:
+            parts.append(_pack_tensor(*fields))
+        except struct.error:   # not 64-bit whole numbers: as ctypes takes them, field by field (wrapped) or not at all (TypeError)
+            parts.append(bytes(_CTensor(*fields)))
     if len(parts) == 1:
         return _CTensor1.from_buffer_copy(parts[0])
     return (_CTensor * len(parts)).from_buffer_copy(b"".join(parts))

@@ -128,6 +128,19 @@ def test_argument_validation_launches_nothing(lib):
         assert lib.gws_status_string(s)
 
 
+def test_descriptor_fields_that_are_no_64_bit_whole_numbers():
+    # as ctypes treats its fields: too large wraps (and the library refuses what comes out), no whole number is a TypeError
+    d = binding.TensorDesc(rows=2 ** 63 + 64, cols=64, ld=64, seed=-1)
+    c = binding._marshal([d, binding.TensorDesc(rows=32, cols=64, ld=64, seed=2 ** 64 + 5)])
+    assert (c[0].rows, c[0].cols, c[0].seed) == (64 - 2 ** 63, 64, 2 ** 64 - 1) and (c[1].rows, c[1].seed, c[1].w) == (32, 5, None)
+    with pytest.raises(binding.GwsError) as e:
+        binding._check(binding.load_library().gws_sample_fwd(binding._marshal([d]), 1, 1, 0, None), "gws_sample_fwd")
+    assert e.value.status == 2
+    for bad in (1.5, None, "64"):
+        with pytest.raises(TypeError):
+            binding._marshal([binding.TensorDesc(rows=bad, cols=64, ld=64, seed=1)])
+
+
 def test_bitwidth_and_mx_entry_points_validate_before_any_launch(lib):
     OK, NULL, SHAPE, ALIGN, FORMAT, LAUNCH, ALIAS = range(7)
     fake = 0x10000  # never dereferenced: every case below fails validation first
