@@ -48,8 +48,35 @@ int gws_gemm_bf16_ride_probe(const void* x, int64_t M, int64_t K, int64_t ldx, c
                              int extra_workgroups, int rider, void* stream);
 
 /* How many of the weights next[0 .. n_next) gws_gemm_bf16_sample_next_n would let ride in the launch of an
- * M x K x N GEMM ([K x N] weight) on the current device (a prefix of the list); host function, launches nothing.            */
+ * M x K x N GEMM with a [K x N] weight on the current device (a prefix of the list); host function, launches nothing.
+ * _layout: the same for either layout of the weight.                                                          */
 int gws_ride_plan(int64_t M, int64_t K, int64_t N, const gws_tensor* next, int n_next);
+int gws_ride_plan_layout(int64_t M, int64_t K, int64_t N, int w_is_nk, const gws_tensor* next, int n_next);
+
+/* Which kernel a call takes on the current device (without one: on 256 compute units), so that a test can aim at one.
+ * Host functions, launch nothing; 0 for sizes that the call refuses.  The choice goes by sizes and leading dimensions,
+ * and may change from one version of the library to the next.
+ * gws_gemm_form: of gws_gemm_bf16 (sampled 0), of gws_linear_fwd_mode with GWS_LINEAR_IN_OPERAND (1), and of
+ * gws_linear_fwd with w_hat (2: a GEMM that is not a _SAMPLE one is preceded by the sampling kernel), Y lying apart from
+ * the operands.                                                                                                */
+#define GWS_GEMM_STREAM 1           /* 16 .. 128 x 16 .. 64 tiles, K split over wavefronts */
+#define GWS_GEMM_MIDDLE 2           /* 128 x 128 tiles, any edge */
+#define GWS_GEMM_LARGE 3            /* 256 x 256 tiles, whole ones */
+#define GWS_GEMM_LARGE_EDGE 4       /* 256 x 256 tiles, any edge */
+#define GWS_GEMM_NARROW 5           /* 256 x 192 tiles, any edge */
+#define GWS_GEMM_ANY_SHAPE 6        /* 128 x 128 tiles, K-steps of 32 */
+#define GWS_GEMM_STREAM_SAMPLE 7    /* K split as in 1, the weight sampled in the operand load */
+#define GWS_GEMM_ROWS_SAMPLE 8      /* 128 x 128 tiles, the weight sampled in the operand load */
+#define GWS_GEMM_ANY_SHAPE_SAMPLE 9 /* the same on the tiles of 6 */
+int gws_gemm_form(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled);
+
+/* gws_linear_bwd_w_form: of gws_linear_bwd_w_ws for this weight (rows, cols) over M tokens with that much workspace. */
+#define GWS_BWD_W_WIDE 1            /* a workgroup per 256 x 256 tile */
+#define GWS_BWD_W_NARROW 2          /* a workgroup per 256 x 192 tile */
+#define GWS_BWD_W_PIECES_64 3       /* a workgroup per 64 x 64 piece, the tokens split over its wavefronts */
+#define GWS_BWD_W_PIECES_128 4      /* the same with pieces of 128 x 64 */
+#define GWS_BWD_W_SPLIT 16          /* + parts: the tokens of a 256 x 256 tile split over so many workgroups */
+int gws_linear_bwd_w_form(const gws_tensor* w, int64_t M, size_t workspace_bytes);
 
 #ifdef __cplusplus
 }

@@ -24,7 +24,11 @@ EXPORTS = ("gws_sample_fwd", "gws_sample_bwd", "gws_sample_fwd_bi", "gws_sample_
            "gws_linear_fwd_ws", "gws_linear_fwd_workspace_bytes", "gws_linear_fwd_static", "gws_linear_bwd_w", "gws_linear_bwd_w_ws", "gws_linear_bwd_w_workspace_bytes", "gws_gemm_bf16", "gws_gemm_bf16_sample_next", "gws_gemm_bf16_sample_next_n", "gws_noise_packed",
            "gws_sample_fwd_basis", "gws_sample_bwd_basis", "gws_noise_basis",
            "gws_derive_seed", "gws_status_string", "gws_version")
-BENCH_EXPORTS = ("gws_copy_tiles", "gws_block_absmax", "gws_sample_bwd_tuned", "gws_sample_fwd_tuned", "gws_gemm_bf16_ride_probe", "gws_ride_plan")
+BENCH_EXPORTS = ("gws_copy_tiles", "gws_block_absmax", "gws_sample_bwd_tuned", "gws_sample_fwd_tuned", "gws_gemm_bf16_ride_probe", "gws_ride_plan",
+                 "gws_ride_plan_layout", "gws_gemm_form", "gws_linear_bwd_w_form")
+# kernels as gws_gemm_form and gws_linear_bwd_w_form name them
+GEMM_STREAM, GEMM_MIDDLE, GEMM_LARGE, GEMM_LARGE_EDGE, GEMM_NARROW, GEMM_ANY_SHAPE, GEMM_STREAM_SAMPLE, GEMM_ROWS_SAMPLE, GEMM_ANY_SHAPE_SAMPLE = range(1, 10)
+BWD_W_WIDE, BWD_W_NARROW, BWD_W_PIECES_64, BWD_W_PIECES_128, BWD_W_SPLIT = 1, 2, 3, 4, 16
 
 
 class GwsError(RuntimeError):
@@ -133,6 +137,12 @@ def load_library() -> ctypes.CDLL:
     L.gws_gemm_bf16_sample_next_n.restype = ci
     L.gws_ride_plan.argtypes = [i64, i64, i64, tp, ci]
     L.gws_ride_plan.restype = ci
+    L.gws_ride_plan_layout.argtypes = [i64, i64, i64, ci, tp, ci]
+    L.gws_ride_plan_layout.restype = ci
+    L.gws_gemm_form.argtypes = [i64, i64, i64, i64, i64, ci, ci]
+    L.gws_gemm_form.restype = ci
+    L.gws_linear_bwd_w_form.argtypes = [tp, i64, ctypes.c_size_t]
+    L.gws_linear_bwd_w_form.restype = ci
     L.gws_gemm_bf16_ride_probe.argtypes = [vp, i64, i64, i64, vp, i64, i64, ci, vp, i64, tp, ci, u64, ci, ci, vp]
     L.gws_gemm_bf16_ride_probe.restype = ci
     L.gws_sample_fwd_tuned.argtypes = [tp, ci, ci, u64, ci, ci, vp]
@@ -424,10 +434,21 @@ def gws_gemm_bf16_sample_next_n(x, w, y, nxt, fmt: int, step: int, w_is_nk: bool
            "gws_gemm_bf16_sample_next_n")
 
 
-def gws_ride_plan(M: int, K: int, N: int, nxt) -> int:
+def gws_ride_plan(M: int, K: int, N: int, nxt, w_is_nk: bool = False) -> int:
     """How many of ``nxt`` would ride in the launch of an M x K x N GEMM (a measurement aid)."""
     arr, n = _as_c(nxt)
-    return int(load_library().gws_ride_plan(int(M), int(K), int(N), arr, n))
+    return int(load_library().gws_ride_plan_layout(int(M), int(K), int(N), int(bool(w_is_nk)), arr, n))
+
+
+def gws_gemm_form(M: int, K: int, N: int, w_is_nk: bool = False, sampled: int = 0, ldx: Optional[int] = None, ldw: Optional[int] = None) -> int:
+    """The kernel (``GEMM_*``) of ``gws_gemm_bf16`` (``sampled`` 0), of ``LINEAR_IN_OPERAND`` (1) or of ``gws_linear_fwd`` with w_hat (2)."""
+    return int(load_library().gws_gemm_form(int(M), int(K), K if ldx is None else int(ldx), int(N), (K if w_is_nk else N) if ldw is None else int(ldw),
+                                            int(bool(w_is_nk)), int(sampled)))
+
+
+def gws_linear_bwd_w_form(w: TensorDesc, M: int, workspace_bytes: int = 0) -> int:
+    """The form (``BWD_W_*``) that ``gws_linear_bwd_w_ws`` takes with that much workspace; ``BWD_W_SPLIT`` plus the number of parts."""
+    return int(load_library().gws_linear_bwd_w_form(_marshal([w]), int(M), int(workspace_bytes)))
 
 
 def gws_gemm_bf16_ride_probe(x, w, y, nxt: TensorDesc, fmt: int, step: int, extra_workgroups: int, rider: int = 1,

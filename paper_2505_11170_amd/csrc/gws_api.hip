@@ -570,14 +570,20 @@ static int bwd_w_args(const void* x, const void* dy, int64_t M, int64_t ldx, int
 // Into how many parts the tokens are split so that a weight of few 256 x 256 tiles still fills the chip: as many
 // as keep all workgroups in one round, at least 8 K-steps of 64 tokens each, at most 8 (every part costs a pass
 // over an fp32 copy of the gradient in the second kernel).
-static uint32_t bwd_w_parts(int64_t rows, int64_t cols, int64_t M) {
+static uint32_t bwd_w_parts(int64_t rows, int64_t cols, int64_t M, int cus) {
   const int64_t tiles = (rows / 256) * (cols / 256);
-  const int cus = compute_units();
   if (tiles <= 0 || cus <= 0) return 1;
   int64_t parts = cus / tiles;
   if (parts > 8) parts = 8;
   if (parts > M / 64 / 8) parts = M / 64 / 8;
   return parts < 2 ? 1u : (uint32_t)parts;
+}
+
+// As many parts as a workspace holds.
+static uint32_t parts_within(const GemmArgs& g, size_t workspace_bytes, int cus) {
+  const uint32_t parts = bwd_w_parts(g.M, g.N, g.K, cus);
+  const size_t held = workspace_bytes / gemm256_tn_split_bytes(g, 1);
+  return held < parts ? (uint32_t)held : parts;
 }
 
 // The fastest way by an estimate in us, among those whose fp32 sums run over no more tokens than a part's when the tokens are
@@ -590,19 +596,29 @@ static uint32_t bwd_w_parts(int64_t rows, int64_t cols, int64_t M) {
 // Fitted to MI355X timings, tokens x rows x cols: 512 x 4096 x 4096 one tile each 26; in parts and in small pieces 4096 x
 // 768 x 3072 40 and 50, 4096 x 768 x 2304 35 and 29, 4096 x 2048 x 2048 50 and 53, 2048 x 2048 x 2048 42 and 34, 8192 x
 // 512 x 512 29 and 32, 2048 x 1024 x 1024 26 and 12.
-static int launch_bwd_w(const GemmArgs& g, bool with_dbt, uint32_t parts, void* workspace, hipStream_t stream) {
-  const TnPlan small = stream_tn_plan(g);
+static int bwd_w_form(const GemmArgs& g, uint32_t parts, TnPlan& small) {
+  small = stream_tn_plan(g);
+  const int pieces = small.mt == 4 ? GWS_BWD_W_PIECES_64 : GWS_BWD_W_PIECES_128;
   const double nk = (double)(g.K / 64);
   if (parts >= 2) {
     const double split_us = 8.2 + nk / parts * 1.19 + (double)gemm256_tn_split_bytes(g, parts) * 0.317e-6;
-    if (small.us < split_us) return launch_gemm_stream_tn(g, with_dbt, small, parts > 4, stream);
-    return launch_gemm256_tn_split(g, with_dbt, (float*)workspace, parts, stream);
+    return small.us < split_us ? pieces : GWS_BWD_W_SPLIT;
   }
   const double cus = compute_units() > 0 ? compute_units() : 256;
   auto whole = [&](double n, double k_step) { return 6.0 + ceil(n / cus) * (3.0 + nk * k_step * (1.2 + 0.2 * fmin(1.0, n / cus))); };
   const double wide_us = whole((double)(g.M / 256) * (double)(g.N / 256), 1.0), narrow_us = whole((double)(g.M / 256) * ceil(g.N / 192.0), 0.8);
-  if (small.us < fmin(wide_us, narrow_us)) return launch_gemm_stream_tn(g, with_dbt, small, false, stream);
-  return narrow_us < wide_us ? launch_gemm256_tn_narrow(g, with_dbt, stream) : launch_gemm256_tn(g, with_dbt, stream);
+  if (small.us < fmin(wide_us, narrow_us)) return pieces;
+  return narrow_us < wide_us ? GWS_BWD_W_NARROW : GWS_BWD_W_WIDE;
+}
+
+static int launch_bwd_w(const GemmArgs& g, bool with_dbt, uint32_t parts, void* workspace, hipStream_t stream) {
+  TnPlan small;
+  switch (bwd_w_form(g, parts, small)) {
+    case GWS_BWD_W_WIDE: return launch_gemm256_tn(g, with_dbt, stream);
+    case GWS_BWD_W_NARROW: return launch_gemm256_tn_narrow(g, with_dbt, stream);
+    case GWS_BWD_W_SPLIT: return launch_gemm256_tn_split(g, with_dbt, (float*)workspace, parts, stream);
+    default: return launch_gemm_stream_tn(g, with_dbt, small, parts > 4, stream);
+  }
 }
 
 int gws_linear_bwd_w(const void* x, const void* dy, int64_t M, int64_t ldx, int64_t ldy, const gws_tensor* w,
@@ -615,7 +631,7 @@ int gws_linear_bwd_w(const void* x, const void* dy, int64_t M, int64_t ldx, int6
 
 size_t gws_linear_bwd_w_workspace_bytes(const gws_tensor* w, int64_t M) {
   if (!w || w->rows <= 0 || w->cols <= 0 || (w->rows & 255) != 0 || (w->cols & 255) != 0 || M <= 0 || (M & 63) != 0) return 0;
-  const uint32_t parts = bwd_w_parts(w->rows, w->cols, M);
+  const uint32_t parts = bwd_w_parts(w->rows, w->cols, M, compute_units());
   return parts < 2 ? 0 : (size_t)parts * (size_t)(w->rows / 256) * (size_t)(w->cols / 256) * 256 * 256 * sizeof(float);
 }
 
@@ -624,16 +640,35 @@ int gws_linear_bwd_w_ws(const void* x, const void* dy, int64_t M, int64_t ldx, i
   GemmArgs g;
   const int rc = bwd_w_args(x, dy, M, ldx, ldy, w, w_is_nk, step, g);
   if (rc != GWS_OK) return rc;
-  uint32_t parts = bwd_w_parts(w->rows, w->cols, M);
-  const size_t per_part = gemm256_tn_split_bytes(g, 1);
-  if (workspace == nullptr) workspace_bytes = 0;
-  if (parts > workspace_bytes / per_part) parts = (uint32_t)(workspace_bytes / per_part);   // as many parts as the workspace holds
+  const uint32_t parts = parts_within(g, workspace == nullptr ? 0 : workspace_bytes, compute_units());
   if (parts < 2) return launch_bwd_w(g, w->dbt != nullptr, 1, nullptr, (hipStream_t)stream);
   if (!aligned(workspace, 16)) return GWS_ERR_ALIGN;
   const size_t ws_bytes = gemm256_tn_split_bytes(g, parts);
   if (overlap2(workspace, ws_bytes, w->dw, (size_t)w->rows * w->ld * 2) || overlap2(workspace, ws_bytes, x, (size_t)M * ldx * 2) ||
       overlap2(workspace, ws_bytes, dy, (size_t)M * ldy * 2)) return GWS_ERR_ALIAS;
   return launch_bwd_w(g, w->dbt != nullptr, parts, workspace, (hipStream_t)stream);
+}
+
+int gws_linear_bwd_w_form(const gws_tensor* w, int64_t M, size_t workspace_bytes) {
+  if (!w || w->rows <= 0 || w->cols <= 0 || (w->rows & 255) != 0 || (w->cols & 255) != 0 || M <= 0 || (M & 63) != 0 ||
+      w->rows >= (int64_t)1 << 31 || w->cols >= (int64_t)1 << 31 || M >= (int64_t)1 << 31) return 0;
+  GemmArgs g;
+  memset(&g, 0, sizeof g);
+  g.M = (uint32_t)w->rows; g.N = (uint32_t)w->cols; g.K = (uint32_t)M;
+  const uint32_t parts = parts_within(g, workspace_bytes, compute_units() > 0 ? compute_units() : 256);
+  TnPlan small;
+  const int form = bwd_w_form(g, parts, small);
+  return form == GWS_BWD_W_SPLIT ? form + (int)parts : form;
+}
+
+int gws_gemm_form(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled) {
+  if (M <= 0 || N <= 0 || K <= 0 || ((K | N) & 31) != 0 || ldx < K || ldw < (w_is_nk ? K : N) || ((ldx | ldw) & 7) != 0 ||
+      M >= (int64_t)1 << 31 || N >= (int64_t)1 << 31 || ldx >= (int64_t)1 << 31 || ldw >= (int64_t)1 << 31) return 0;
+  GemmArgs g;
+  memset(&g, 0, sizeof g);
+  g.M = (uint32_t)M; g.N = (uint32_t)N; g.K = (uint32_t)K; g.ldx = (uint32_t)ldx; g.ldw = (uint32_t)ldw;
+  RoutePlan plan;
+  return (int)gemm_form(g, w_is_nk, sampled == 1 || (sampled == 2 && sample_in_operand(g, w_is_nk)) ? kFusedInOperand : 0, plan);
 }
 
 int gws_gemm_bf16(const void* x, int64_t M, int64_t K, int64_t ldx, const void* w, int64_t N, int64_t ldw,
@@ -671,9 +706,9 @@ static int plan_ride(const GemmArgs& g, int w_is_nk, bool gemm_empty, int64_t K,
   const bool gemm_rides = force_extra >= 0 ? (gemm_empty || gemm256_applicable(g))
                                            : gemm256_applicable(g) && route != GemmRoute::kStream && route != GemmRoute::kSmall;
   if (!gemm_rides) return 0;
-  const int cus = compute_units();
+  const int cus = compute_units() > 0 ? compute_units() : 256;
   const uint64_t tiles = gemm_empty ? 0 : (uint64_t)(g.M / 256) * (uint64_t)(g.N / 256);
-  idle = cus > 0 ? (uint32_t)((cus - tiles % cus) % cus) : 0u;
+  idle = (uint32_t)((cus - tiles % cus) % cus);
   if (force_extra >= 0) idle = (uint32_t)force_extra;
   if (idle == 0) return 0;
   const double t_tile_us = (double)(K / 64) * 1.5 + 5.0;
@@ -785,6 +820,10 @@ int gws_gemm_bf16_sample_next_n(const void* x, int64_t M, int64_t K, int64_t ldx
 }
 
 int gws_ride_plan(int64_t M, int64_t K, int64_t N, const gws_tensor* next, int n_next) {
+  return gws_ride_plan_layout(M, K, N, 0, next, n_next);
+}
+
+int gws_ride_plan_layout(int64_t M, int64_t K, int64_t N, int w_is_nk, const gws_tensor* next, int n_next) {
   if (!next || n_next <= 0 || M <= 0 || N <= 0 || K <= 0) return 0;
   GemmArgs g;
   memset(&g, 0, sizeof g);
@@ -792,7 +831,7 @@ int gws_ride_plan(int64_t M, int64_t K, int64_t N, const gws_tensor* next, int n
   RideList r;
   uint32_t idle = 0;
   int use_rider = 1;
-  return plan_ride(g, 0, false, K, next, n_next, -1, -1, r, idle, use_rider);
+  return plan_ride(g, w_is_nk, false, K, next, n_next, -1, -1, r, idle, use_rider);
 }
 
 int gws_gemm_bf16_ride_probe(const void* x, int64_t M, int64_t K, int64_t ldx, const void* w, int64_t N, int64_t ldw,

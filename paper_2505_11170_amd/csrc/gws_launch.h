@@ -111,6 +111,9 @@ struct RoutePlan {   // estimates in us; 1e30: not a shape for that kernel
   double middle_us, large_us, narrow_us;
 };
 GemmRoute gemm_route(const GemmArgs& g, int w_is_nk, RoutePlan& plan);
+// the kernel that launch_gemm takes (Y apart from the operands); the values are GWS_GEMM_* of gws_bench.h
+enum class GemmForm { kStream = 1, kMiddle, kLarge, kLargeEdge, kNarrow, kAnyShape, kStreamSample, kRowsSample, kAnyShapeSample };
+GemmForm gemm_form(const GemmArgs& g, int w_is_nk, int fused, RoutePlan& plan);
 bool sample_in_operand(const GemmArgs& g, int w_is_nk);   // the faster way to a sampled product (same bits either way)
 bool gemm256_edge_applicable(const GemmArgs& g);
 int launch_gemm256_edge(const GemmArgs& g, int w_is_nk, hipStream_t stream);

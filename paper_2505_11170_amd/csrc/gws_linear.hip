@@ -243,23 +243,39 @@ static bool in_place(const GemmArgs& g, int w_is_nk, int fused) {
          (fused && on_y(g.bt, (size_t)(rows >> 5) * (cols >> 5) * sizeof(float)));
 }
 
+GemmForm gemm_form(const GemmArgs& g, int w_is_nk, int fused, RoutePlan& plan) {
+  const GemmRoute route = gemm_route(g, w_is_nk, plan);
+  if (route == GemmRoute::kStream) return fused ? GemmForm::kStreamSample : GemmForm::kStream;
+  if (fused) return rows_sample_applicable(g, w_is_nk) ? GemmForm::kRowsSample : GemmForm::kAnyShapeSample;
+  switch (route) {
+    case GemmRoute::kMiddle: return GemmForm::kMiddle;
+    case GemmRoute::kNarrow: return GemmForm::kNarrow;
+    case GemmRoute::kLarge: return gemm256_applicable(g) ? GemmForm::kLarge : GemmForm::kLargeEdge;
+    default: return GemmForm::kAnyShape;
+  }
+}
+
 int launch_gemm(const GemmArgs& g, int w_is_nk, int fused, int fmt, hipStream_t stream) {
   const uint64_t tiles = (uint64_t)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   if (tiles == 0) return GWS_OK;
   if (tiles >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
   const dim3 grid((uint32_t)tiles);
   RoutePlan plan;
-  GemmRoute route = gemm_route(g, w_is_nk, plan);
-  const bool one_tile = tiles == 1 || (!fused && g.M == 256 && g.N == 256 && gemm256_applicable(g));
-  const bool one_workgroup = one_tile && in_place(g, w_is_nk, fused);
-  if (one_workgroup) route = tiles == 1 ? GemmRoute::kSmall : GemmRoute::kLarge;
-  if (route == GemmRoute::kStream)
-    return fused ? launch_gemm_stream_sample(g, w_is_nk, fmt, plan.stream.p, stream) : launch_gemm_stream(g, w_is_nk, plan.stream, stream);
-  if (!fused && route == GemmRoute::kMiddle) return launch_gemm128(g, w_is_nk, stream);
-  if (!fused && route == GemmRoute::kNarrow) return launch_gemm256_narrow(g, w_is_nk, stream);
-  if (!fused && route == GemmRoute::kLarge) return gemm256_applicable(g) ? launch_gemm256(g, w_is_nk, stream) : launch_gemm256_edge(g, w_is_nk, stream);
-  if (fused && !one_workgroup && rows_sample_applicable(g, w_is_nk)) return launch_gemm_rows_sample(g, w_is_nk, fmt, stream);
-  if (!fused) return launch_layout<false, 0>(g, w_is_nk, grid, stream);
+  GemmForm form = gemm_form(g, w_is_nk, fused, plan);
+  const bool large_tile = !fused && g.M == 256 && g.N == 256 && gemm256_applicable(g);
+  if ((tiles == 1 || large_tile) && in_place(g, w_is_nk, fused))
+    form = large_tile ? GemmForm::kLarge : fused ? GemmForm::kAnyShapeSample : GemmForm::kAnyShape;
+  switch (form) {
+    case GemmForm::kStream: return launch_gemm_stream(g, w_is_nk, plan.stream, stream);
+    case GemmForm::kMiddle: return launch_gemm128(g, w_is_nk, stream);
+    case GemmForm::kLarge: return launch_gemm256(g, w_is_nk, stream);
+    case GemmForm::kLargeEdge: return launch_gemm256_edge(g, w_is_nk, stream);
+    case GemmForm::kNarrow: return launch_gemm256_narrow(g, w_is_nk, stream);
+    case GemmForm::kAnyShape: return launch_layout<false, 0>(g, w_is_nk, grid, stream);
+    case GemmForm::kStreamSample: return launch_gemm_stream_sample(g, w_is_nk, fmt, plan.stream.p, stream);
+    case GemmForm::kRowsSample: return launch_gemm_rows_sample(g, w_is_nk, fmt, stream);
+    case GemmForm::kAnyShapeSample: break;
+  }
   switch (fmt) {
     case GWS_FMT_BF16: return launch_layout<true, 0>(g, w_is_nk, grid, stream);
     case GWS_FMT_FP8_E4M3: return launch_layout<true, 1>(g, w_is_nk, grid, stream);

@@ -141,6 +141,20 @@ def test_descriptor_fields_that_are_no_64_bit_whole_numbers():
             binding._marshal([binding.TensorDesc(rows=bad, cols=64, ld=64, seed=1)])
 
 
+def test_queries_of_the_chosen_kernel(lib):
+    # host functions: what rides and which kernel a call takes, by layout; without a device for 256 compute units
+    nxt = [binding.TensorDesc(rows=1024, cols=1024, ld=1024, seed=1)]
+    assert [binding.gws_ride_plan(1280, 1024, 3328, nxt, w_is_nk=nk) for nk in (False, True)] == [1, 0]
+    assert lib.gws_ride_plan(1280, 1024, 3328, binding._marshal(nxt), 1) == 1           # the [K x N] weight's
+    assert binding.gws_gemm_form(1024, 48, 64) == 0 and binding.gws_gemm_form(0, 64, 64) == 0   # what the GEMM refuses, and an empty one
+    assert binding.gws_gemm_form(4, 5632, 2048, w_is_nk=True) == binding.GEMM_STREAM
+    assert binding.gws_gemm_form(8192, 2048, 5632) == binding.GEMM_LARGE
+    assert [binding.gws_gemm_form(m, 2048, 5632, sampled=2) for m in (16, 8192)] == [binding.GEMM_STREAM_SAMPLE, binding.GEMM_LARGE]
+    wide = binding.TensorDesc(rows=4096, cols=4096, ld=4096, seed=1)
+    assert binding.gws_linear_bwd_w_form(wide, 512) == binding.BWD_W_WIDE and binding.gws_linear_bwd_w_form(wide, 63) == 0
+    assert binding.gws_linear_bwd_w_form(binding.TensorDesc(rows=768, cols=3072, ld=3072, seed=1), 4096, 1 << 30) == binding.BWD_W_SPLIT + 7
+
+
 def test_bitwidth_and_mx_entry_points_validate_before_any_launch(lib):
     OK, NULL, SHAPE, ALIGN, FORMAT, LAUNCH, ALIAS = range(7)
     fake = 0x10000  # never dereferenced: every case below fails validation first
