@@ -219,17 +219,16 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_sample_kernel(const GemmAr
 }
 
 // Many rows of X, the weight sampled on its way in, K from end to end (the order of the middle and large tiles' sums, so Y is
-// their Y): a workgroup owns 16 MT rows x 128 columns, a wavefront 32 of the columns.  X comes through LDS in units of 64 k, a
+// their Y): a workgroup owns 128 rows x 128 columns, a wavefront 32 of the columns.  X comes through LDS in units of 64 k, a
 // ring of two stages that the four wavefronts share, one barrier a unit; the weight's blocks go from a wavefront's
-// registers through its own LDS as above.  Bound by the vector ALU work of the sampling, which every 16 MT rows repeat
+// registers through its own LDS as above.  Bound by the vector ALU work of the sampling, which every 128 rows repeat
 // (2.3 us a unit with one workgroup on a compute unit, 2.6 with two; a third needs spills: a quarter slower).  Against
 // gemm_kernel (gws_linear.hip), us, [K x N] and [N x K]: 1107 x 2528 -> 3104 148, 130 -> 101, 94; 4000 x 512 -> 512 29, 28 ->
 // 16, 15; 8192 x 2048 -> 5632 610, 544 -> 519, 500; 5683 x 608 -> 1792 61, 54 -> 56, 57.
-template <int MT, int FMT, bool W_NK>
+template <int FMT, bool W_NK>
 __global__ __launch_bounds__(256, 2) void gemm_rows_sample_kernel(const GemmArgs g) {
   using namespace stream;
-  constexpr int BM = 16 * MT, D = 2, XS = BM * 64, LX = BM / 32;   // load instructions of a wavefront and unit
-  static_assert(MT == 4 || MT == 8, "");
+  constexpr int MT = 8, BM = 16 * MT, D = 2, XS = BM * 64, LX = BM / 32;   // load instructions of a wavefront and unit
   __shared__ __attribute__((aligned(1024))) uint16_t ring[D * XS];
   __shared__ __attribute__((aligned(16))) uint16_t blocks[4 * 32 * LP];
   const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4, q = lane & 3, r = lane >> 2;
@@ -379,19 +378,11 @@ static void launch_sampled_fmt(const GemmArgs& g, int w_is_nk, int p, hipStream_
   else launch_sampled<4, 8, FMT>(g, w_is_nk, s);
 }
 
-template <int MT, int FMT>
-static void launch_rows(const GemmArgs& g, int w_is_nk, hipStream_t s) {
-  const dim3 grid(((g.M + 16 * MT - 1) / (16 * MT)) * ((g.N + 127) / 128));
-  if (w_is_nk) hipLaunchKernelGGL((gemm_rows_sample_kernel<MT, FMT, true>), grid, dim3(256), 0, s, g);
-  else hipLaunchKernelGGL((gemm_rows_sample_kernel<MT, FMT, false>), grid, dim3(256), 0, s, g);
-}
-
-// 128 rows a workgroup (fewer samplings of a block) where that still gives half of the compute units one.
 template <int FMT>
-static void launch_rows_fmt(const GemmArgs& g, int w_is_nk, hipStream_t s) {
-  const uint64_t cus = compute_units() > 0 ? compute_units() : 256, tn = (g.N + 127) / 128;
-  if ((uint64_t)((g.M + 127) / 128) * tn >= cus / 2) launch_rows<8, FMT>(g, w_is_nk, s);
-  else launch_rows<4, FMT>(g, w_is_nk, s);
+static void launch_rows(const GemmArgs& g, int w_is_nk, hipStream_t s) {
+  const dim3 grid(((g.M + 127) / 128) * ((g.N + 127) / 128));
+  if (w_is_nk) hipLaunchKernelGGL((gemm_rows_sample_kernel<FMT, true>), grid, dim3(256), 0, s, g);
+  else hipLaunchKernelGGL((gemm_rows_sample_kernel<FMT, false>), grid, dim3(256), 0, s, g);
 }
 
 // Two workgroups run on a compute unit: between one and one and a half rounds of them the 128 x 128 x 32 kernel, which packs
@@ -402,11 +393,10 @@ bool rows_sample_applicable(const GemmArgs& g, int w_is_nk) {
 }
 
 int launch_gemm_rows_sample(const GemmArgs& g, int w_is_nk, int fmt, hipStream_t s) {
-  if ((uint64_t)((g.M + 63) / 64) * ((g.N + 127) / 128) >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
   switch (fmt) {
-    case GWS_FMT_BF16: launch_rows_fmt<0>(g, w_is_nk, s); break;
-    case GWS_FMT_FP8_E4M3: launch_rows_fmt<1>(g, w_is_nk, s); break;
-    case GWS_FMT_FP6_E3M2: launch_rows_fmt<2>(g, w_is_nk, s); break;
+    case GWS_FMT_BF16: launch_rows<0>(g, w_is_nk, s); break;
+    case GWS_FMT_FP8_E4M3: launch_rows<1>(g, w_is_nk, s); break;
+    case GWS_FMT_FP6_E3M2: launch_rows<2>(g, w_is_nk, s); break;
     default: return GWS_ERR_FORMAT;
   }
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;

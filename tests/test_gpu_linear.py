@@ -121,8 +121,17 @@ def test_plain_gemm_vs_fp64():
 
 @pytest.mark.parametrize("w_is_nk", [False, True])
 def test_plain_gemm_large_tile_path(w_is_nk):
-    # M, N multiples of 256 and K of 64 take the 256x256x64 kernel; 768 x 1280 = 3 x 5 tiles
-    # exercises the XCD / patch tile numbering with a short last band
+    # whole 256 x 256 tiles but few of them: the kernel that splits K (the large tile itself: 10 x 19 tiles below, which
+    # exercise the XCD / patch tile numbering with a short last band)
+    large = (2560, 64, 4864)
+    assert gws.gws_gemm_form(*large, w_is_nk) == gws.GEMM_LARGE
+    x = synth.make_activation(9, large[0], large[1])
+    w = synth.make_tensor(9, large[1], large[2], with_grad=False)["w"]
+    wd = (w.t().contiguous() if w_is_nk else w).to(DEV)
+    y = torch.zeros(large[0], large[2], dtype=torch.bfloat16, device=DEV)
+    gws.gws_gemm_bf16(x.to(DEV), wd, y, w_is_nk=w_is_nk)
+    torch.cuda.synchronize()
+    check_y(synth.bits(y), synth.bits(x), synth.bits(wd.cpu()), w_is_nk, tile_rows(large[0], np.random.default_rng(9)))
     M, K, N = 768, 192, 1280
     x = synth.make_activation(2, M, K)
     w = synth.make_tensor(2, K, N, with_grad=False)["w"]
@@ -145,7 +154,9 @@ def test_plain_gemm_large_tile_path(w_is_nk):
 @pytest.mark.parametrize("w_is_nk", [False, True])
 @pytest.mark.parametrize("fmt", [gws.FMT_BF16, gws.FMT_FP8_E4M3, gws.FMT_FP6_E3M2])
 def test_linear_on_the_large_tile(w_is_nk, fmt):
-    # M, N multiples of 256, K of 64 and w_hat requested: sampling kernel + the 256-tile GEMM on w_hat
+    # w_hat requested: sampling kernel + the 256-tile GEMM on w_hat; with few tiles the GEMM that splits K
+    assert gws.gws_gemm_form(2560, 64, 4864, w_is_nk, sampled=2) == gws.GEMM_LARGE
+    run_case(2560, 64, 4864, w_is_nk, fmt, seed_id=10, step=3, rows_sel=tile_rows(2560, np.random.default_rng(10)))
     run_case(512, 128, 768, w_is_nk, fmt, seed_id=7, step=2)
     run_case(256, 64, 256, w_is_nk, fmt, bt=3.0, seed_id=8)
 
@@ -200,8 +211,8 @@ def test_linear_mode_errors():
 
 
 def test_large_tile_gemm_random_shapes_and_strides():
-    # the 256x256x64 tile at seeded random shapes: odd and even numbers of K-steps (1 .. 11), padded
-    # leading dimensions, both weight layouts; every element against the fp64 GEMM
+    # whole 256 x 256 tiles, few of them (the kernel that splits K), at seeded random shapes: odd and even numbers of
+    # K-steps (1 .. 11), padded leading dimensions, both weight layouts; every element against the fp64 GEMM
     rng = np.random.default_rng(2505)
     for case in range(10):
         M, N = 256 * int(rng.integers(1, 4)), 256 * int(rng.integers(1, 4))
@@ -223,8 +234,8 @@ def test_large_tile_gemm_random_shapes_and_strides():
 
 @pytest.mark.parametrize("w_is_nk", [False, True])
 def test_large_tile_gemm_every_number_of_k_steps(w_is_nk):
-    # the main loop is unrolled six K-steps with a tail of up to five, and the operand rings are primed for the
-    # first three: 1 .. 14 K-steps take every path through prologue, loop and tail; every element against fp64
+    # two whole 256 x 256 tiles, 1 .. 14 K-steps of 64: fewer units of K than wavefronts that split it, and several each;
+    # every element against fp64 (the large tile's own loop: test_whole_large_tiles_at_every_number_of_k_steps)
     M, N = 256, 512
     for nk in range(1, 15):
         K = 64 * nk
@@ -237,8 +248,9 @@ def test_large_tile_gemm_every_number_of_k_steps(w_is_nk):
         check_y(synth.bits(y), synth.bits(x), synth.bits(w), w_is_nk)
 
 
-def run_next_case(M, K, N, w_is_nk, next_rows, next_cols, fmt, idx, step=3, next_pad=0, rows_sel=None):
-    """gws_gemm_bf16_sample_next: Y against the fp64 GEMM, the riding forward pass against the oracle."""
+def run_next_case(M, K, N, w_is_nk, next_rows, next_cols, fmt, idx, step=3, next_pad=0, rows_sel=None, rides=0):
+    """gws_gemm_bf16_sample_next: Y against the fp64 GEMM, the forward pass of the next weight, which rides or does not,
+    against the oracle."""
     x = synth.make_activation(500 + idx, M, K).to(DEV)
     wr, wc = (N, K) if w_is_nk else (K, N)
     w = synth.make_tensor(500 + idx, wr, wc, with_grad=False)["w"].to(DEV)
@@ -250,6 +262,7 @@ def run_next_case(M, K, N, w_is_nk, next_rows, next_cols, fmt, idx, step=3, next
     n_scale = torch.full((nbr, nbc), float("nan"), device=DEV)
     seed = oracle.derive_seed(7, idx)
     nxt = gws.TensorDesc(rows=next_rows, cols=next_cols, ld=next_cols + next_pad, seed=seed, w=nw, w_hat=n_hat, bt=nbt, scale=n_scale)
+    assert gws.gws_ride_plan(M, K, N, [nxt], w_is_nk) == rides
     gws.gws_gemm_bf16_sample_next(x, w, y, nxt, fmt, step, w_is_nk=w_is_nk)
     torch.cuda.synchronize()
     check_y(synth.bits(y), synth.bits(x), synth.bits(w), w_is_nk, rows_sel)
@@ -261,8 +274,12 @@ def run_next_case(M, K, N, w_is_nk, next_rows, next_cols, fmt, idx, step=3, next
 
 @pytest.mark.parametrize("fmt", [gws.FMT_BF16, gws.FMT_FP8_E4M3, gws.FMT_FP6_E3M2])
 def test_gemm_with_the_next_weight_sampled_alongside(fmt):
-    run_next_case(768, 192, 1280, False, 128, 320, fmt, 0)                   # 15 tiles: the sampling rides in the same launch
-    run_next_case(512, 128, 512, True, 256, 1024, fmt, 1, next_pad=8)        # [N x K] weight, padded next weight
+    rows_sel = np.array([0, 255, 256, 1279])
+    for w_is_nk in (False, True):                                            # 65 tiles: the sampling rides in the same launch
+        run_next_case(1280, 64, 3328, w_is_nk, 128, 320, fmt, 8, rows_sel=rows_sel, rides=1)                # next weight of whole 32 x 64 tiles
+        run_next_case(1280, 64, 3328, w_is_nk, 256, 1024, fmt, 9, next_pad=8, rows_sel=rows_sel, rides=1)   # of whole 32 x 256 tiles, padded
+    run_next_case(768, 192, 1280, False, 128, 320, fmt, 0)                   # a GEMM that splits K: separate launch
+    run_next_case(512, 128, 512, True, 256, 1024, fmt, 1, next_pad=8)
     run_next_case(768, 192, 1280, False, 96, 300, fmt, 2, next_pad=4)        # ragged next weight: separate launch
     run_next_case(200, 96, 160, False, 128, 320, fmt, 3)                     # GEMM not on the large tile: separate launch
     run_next_case(256, 64, 256, False, 4096, 4096, fmt, 4)                   # sampling far longer than the GEMM: separate launch
@@ -284,14 +301,17 @@ def test_gemm_next_without_idle_compute_units_and_without_next():
 
 def test_config5_gemm_with_the_next_weight_sampled_alongside():
     rows_sel = tile_rows(8192, np.random.default_rng(6))
-    run_next_case(8192, 2048, 5632, False, 2048, 5632, gws.FMT_FP8_E4M3, 6, rows_sel=rows_sel)   # too much to ride: two launches
-    run_next_case(8192, 2048, 5632, False, 2048, 2048, gws.FMT_FP8_E4M3, 7, rows_sel=rows_sel)   # rides beside the last round of tiles
+    run_next_case(8192, 2048, 5632, False, 2048, 8192, gws.FMT_FP8_E4M3, 6, rows_sel=rows_sel)   # too much to ride: two launches
+    run_next_case(8192, 2048, 5632, False, 2048, 5632, gws.FMT_FP8_E4M3, 6, rows_sel=rows_sel, rides=1)   # as long as the last round of tiles
+    run_next_case(8192, 2048, 5632, False, 2048, 2048, gws.FMT_FP8_E4M3, 7, rows_sel=rows_sel, rides=1)   # rides beside the last round of tiles
 
 
-def run_next_list(M, K, N, next_shapes, fmt, idx, step=5, rows_sel=None):
-    """gws_gemm_bf16_sample_next_n: Y against the fp64 GEMM, every listed weight against the oracle's forward pass."""
+def run_next_list(M, K, N, next_shapes, fmt, idx, step=5, rows_sel=None, w_is_nk=False, rides=0):
+    """gws_gemm_bf16_sample_next_n: Y against the fp64 GEMM, every listed weight, of which the first `rides` ride, against the
+    oracle's forward pass."""
     x = synth.make_activation(700 + idx, M, K).to(DEV)
-    w = synth.make_tensor(700 + idx, K, N, with_grad=False)["w"].to(DEV)
+    wr, wc = (N, K) if w_is_nk else (K, N)
+    w = synth.make_tensor(700 + idx, wr, wc, with_grad=False)["w"].to(DEV)
     y = torch.zeros(M, N, dtype=torch.bfloat16, device=DEV)
     descs, host = [], []
     for k, (r, c) in enumerate(next_shapes):
@@ -302,9 +322,10 @@ def run_next_list(M, K, N, next_shapes, fmt, idx, step=5, rows_sel=None):
         descs.append(gws.TensorDesc(rows=r, cols=c, ld=ld, seed=oracle.derive_seed(9, 10 * idx + k), w=nw, w_hat=nw.clone(),
                                     bt=t["bt"].to(DEV), scale=torch.full((nbr, nbc), float("nan"), device=DEV)))
         host.append(t)
-    gws.gws_gemm_bf16_sample_next_n(x, w, y, descs, fmt, step)
+    assert gws.gws_ride_plan(M, K, N, descs, w_is_nk) == rides
+    gws.gws_gemm_bf16_sample_next_n(x, w, y, descs, fmt, step, w_is_nk=w_is_nk)
     torch.cuda.synchronize()
-    check_y(synth.bits(y), synth.bits(x), synth.bits(w), False, rows_sel)
+    check_y(synth.bits(y), synth.bits(x), synth.bits(w), w_is_nk, rows_sel)
     for d, t in zip(descs, host):
         ref_q, ref_s = oracle.sample_fwd(synth.bits(t["w"]), t["bt"].numpy(), fmt, d.seed, step, cols=d.cols)
         assert (synth.bits(d.w_hat) == ref_q).all(), ("w_hat", idx, d.rows, d.cols)
@@ -313,24 +334,31 @@ def run_next_list(M, K, N, next_shapes, fmt, idx, step=5, rows_sel=None):
 
 @pytest.mark.parametrize("fmt", [gws.FMT_BF16, gws.FMT_FP8_E4M3, gws.FMT_FP6_E3M2])
 def test_gemm_with_several_next_weights_sampled_alongside(fmt):
-    run_next_list(768, 192, 1280, [(128, 512), (64, 256), (96, 768)], fmt, 0)           # all three ride (whole 32 x 256 tiles)
-    run_next_list(768, 192, 1280, [(128, 512), (96, 300)], fmt, 1)                       # the ragged one: separate launch
-    run_next_list(768, 192, 1280, [(32, 256)] * 5 + [(64, 512)], fmt, 2)                 # more than ride at once: the rest after the GEMM
-    run_next_list(768, 192, 1280, [(96, 320), (128, 512)], fmt, 3)                       # first not of whole 32 x 256 tiles: rides alone
-    run_next_list(200, 96, 160, [(128, 512), (64, 256)], fmt, 4)                         # GEMM not on the large tile: all separate
-    run_next_list(768, 192, 1280, [(256, 512), (0, 256), (64, 256)], fmt, 5)             # an empty weight in the list
+    rows_sel = np.array([0, 255, 256, 2559])
+    for w_is_nk in (False, True):
+        for lst, rides in [([(128, 512), (64, 256), (96, 768)], 3),                  # all three ride (whole 32 x 256 tiles)
+                           ([(128, 512), (96, 300)], 1),                             # the ragged one: separate launch
+                           ([(32, 256)] * 5 + [(64, 512)], 4),                       # more than ride at once: the rest after the GEMM
+                           ([(96, 320), (128, 512)], 1),                             # first not of whole 32 x 256 tiles: rides alone
+                           ([(256, 512), (0, 256), (64, 256)], 1)]:                  # an empty weight in the list
+            run_next_list(2560, 64, 4864, lst, fmt, 8, rows_sel=rows_sel, w_is_nk=w_is_nk, rides=rides)
+        run_next_list(1280, 64, 3328, [(128, 512), (64, 256), (96, 768)], fmt, 9, rows_sel=rows_sel[:3], w_is_nk=w_is_nk, rides=3)   # under a product of the middle tile
+    run_next_list(768, 192, 1280, [(128, 512), (64, 256), (96, 768)], fmt, 0)            # a GEMM that splits K: all separate
+    run_next_list(200, 96, 160, [(128, 512), (64, 256)], fmt, 4)                         # of no whole tiles: all separate
     run_next_list(256, 64, 256, [(2048, 2048), (1024, 1024)], fmt, 6)                    # too much to ride beside one short tile
 
 
-def test_forced_riding_gives_the_same_bytes_for_both_riding_loops():
+@pytest.mark.parametrize("w_is_nk", [False, True])
+@pytest.mark.parametrize("fmt", [gws.FMT_BF16, gws.FMT_FP8_E4M3, gws.FMT_FP6_E3M2])
+def test_forced_riding_gives_the_same_bytes_for_both_riding_loops(fmt, w_is_nk):
     # include/gws_bench.h, gws_gemm_bf16_ride_probe: riders alone (no GEMM) and beside a GEMM, both riding loops
-    fmt, step = gws.FMT_FP8_E4M3, 8
+    step = 8
     t = synth.make_tensor(790, 512, 1280, with_grad=False)
     seed = oracle.derive_seed(3, 790)
     ref_q, ref_s = oracle.sample_fwd(synth.bits(t["w"]), t["bt"].numpy(), fmt, seed, step)
     nw, nbt = t["w"].to(DEV), t["bt"].to(DEV)
     x = synth.make_activation(791, 512, 128).to(DEV)
-    w = synth.make_tensor(791, 128, 768, with_grad=False)["w"].to(DEV)
+    w = synth.make_tensor(791, *((768, 128) if w_is_nk else (128, 768)), with_grad=False)["w"].to(DEV)
     for rider in (0, 1):
         for with_gemm in (False, True):
             for extra in (1, 7, 64):
@@ -338,14 +366,14 @@ def test_forced_riding_gives_the_same_bytes_for_both_riding_loops():
                                    scale=torch.zeros(16, 40, device=DEV))
                 y = torch.zeros(512, 768, dtype=torch.bfloat16, device=DEV)
                 if with_gemm:
-                    gws.gws_gemm_bf16_ride_probe(x, w, y, d, fmt, step, extra, rider)
+                    gws.gws_gemm_bf16_ride_probe(x, w, y, d, fmt, step, extra, rider, w_is_nk=w_is_nk)
                 else:
                     gws.gws_gemm_bf16_ride_probe(None, None, None, d, fmt, step, extra, rider)
                 torch.cuda.synchronize()
                 assert (synth.bits(d.w_hat) == ref_q).all(), (rider, with_gemm, extra)
                 assert (d.scale.cpu().numpy().view(np.uint32) == ref_s.view(np.uint32)).all()
                 if with_gemm:
-                    check_y(synth.bits(y), synth.bits(x), synth.bits(w), False)
+                    check_y(synth.bits(y), synth.bits(x), synth.bits(w), w_is_nk)
 
 
 # Few rows of X or few tiles: the kernel whose wavefronts split K.  Every tile it has (16 x 16 and 16 x 32 up to 16 rows,
@@ -355,6 +383,7 @@ def test_forced_riding_gives_the_same_bytes_for_both_riding_loops():
 @pytest.mark.parametrize("M,K,N", [(1, 64, 32), (16, 96, 64), (17, 128, 96), (4, 1632, 32), (32, 544, 4128), (33, 2080, 1056),
                                    (64, 1024, 2080), (65, 736, 5664), (300, 672, 1056), (511, 1312, 800), (400, 3072, 2048), (500, 3072, 2528)])
 def test_gemm_that_splits_k(M, K, N, w_is_nk):
+    assert [gws.gws_gemm_form(M, K, N, w_is_nk, k, ldx=K + 8) for k in (0, 1)] == [gws.GEMM_STREAM, gws.GEMM_STREAM_SAMPLE]
     idx = 40 + (M * 7 + K) % 50
     rows_sel = None if M * K * N < 2e7 else np.array(sorted({0, 15 % M, M // 2, M - 1}))
     run_case(M, K, N, w_is_nk, gws.FMT_FP8_E4M3, seed_id=idx, ldx_pad=8, ldy_pad=8, rows_sel=rows_sel, mode=gws.LINEAR_IN_OPERAND)
@@ -363,7 +392,11 @@ def test_gemm_that_splits_k(M, K, N, w_is_nk):
 
 
 def test_riding_under_a_gemm_of_many_k_steps():
-    # 272 tiles of 256 x 256: the large tile is the faster one and leaves 240 compute units idle in its second round
+    # 182 tiles of 256 x 256: the large tile is the faster one and leaves 74 compute units idle
+    assert gws.gws_gemm_form(6656, 1024, 1792) == gws.GEMM_LARGE
+    run_next_list(6656, 1024, 1792, [(128, 512), (64, 256), (96, 768)], gws.FMT_FP8_E4M3, 7, rows_sel=np.array([0, 255, 256, 6655]), rides=3)
+    # 272 tiles of 256 x 256, 368 of 256 x 192: the narrow tile is the faster one by more than a launch, and nothing rides
+    assert gws.gws_gemm_form(4096, 1024, 4352) == gws.GEMM_NARROW
     run_next_list(4096, 1024, 4352, [(128, 512), (64, 256)], gws.FMT_FP8_E4M3, 7, rows_sel=np.array([0, 255, 256, 4095]))
 
 
@@ -373,6 +406,7 @@ def test_riding_under_a_gemm_of_many_k_steps():
 @pytest.mark.parametrize("w_is_nk", [False, True])
 @pytest.mark.parametrize("M,K,N", [(1537, 96, 1696), (1920, 160, 1760), (1600, 256, 2080), (2049, 288, 1312), (2000, 1504, 2016)])
 def test_middle_tile_gemm(M, K, N, w_is_nk):
+    assert [gws.gws_gemm_form(M, K, N, w_is_nk, k, ldx=K + 8) for k in (0, 1)] == [gws.GEMM_MIDDLE, gws.GEMM_ROWS_SAMPLE]
     run_case(M, K, N, w_is_nk, gws.FMT_FP8_E4M3, seed_id=91, ldx_pad=8, ldy_pad=8, rows_sel=np.array([0, 127, 128, M // 2, M - 1]),
              mode=gws.LINEAR_IN_OPERAND)
 
@@ -380,6 +414,7 @@ def test_middle_tile_gemm(M, K, N, w_is_nk):
 @pytest.mark.parametrize("w_is_nk", [False, True])
 @pytest.mark.parametrize("M,K,N", [(8191, 96, 1824), (8193, 512, 1760)] + [(7937, 1024 + 32 * i, 1568) for i in range(1, 13, 2)])
 def test_large_tile_gemm_with_edges(M, K, N, w_is_nk):
+    assert [gws.gws_gemm_form(M, K, N, w_is_nk, k, ldx=K + 8) for k in (0, 1)] == [gws.GEMM_LARGE_EDGE, gws.GEMM_ROWS_SAMPLE]
     run_case(M, K, N, w_is_nk, gws.FMT_FP8_E4M3, seed_id=92, ldx_pad=8, ldy_pad=8, rows_sel=np.array([0, 255, 256, M // 2, M - 2, M - 1]),
              mode=gws.LINEAR_IN_OPERAND)
 
@@ -389,6 +424,7 @@ def test_whole_large_tiles_at_every_number_of_k_steps(w_is_nk):
     # 256 tiles of 256 x 256, 1 to 14 K-steps (the rings' common period is six): against fp32 on the GPU
     for steps in range(1, 15):
         K = 64 * steps
+        assert gws.gws_gemm_form(8192, K, 2048, w_is_nk) == gws.GEMM_LARGE
         gen = torch.Generator(device=DEV).manual_seed(steps)
         x = torch.randn(8192, K, generator=gen, device=DEV).to(torch.bfloat16)
         w = (torch.randn(*((2048, K) if w_is_nk else (K, 2048)), generator=gen, device=DEV) * 0.02).to(torch.bfloat16)
@@ -404,6 +440,7 @@ def test_whole_large_tiles_at_every_number_of_k_steps(w_is_nk):
 def test_narrow_large_tiles_at_every_number_of_k_steps(M, N, w_is_nk):
     # sizes whose 256 x 192 tiles fill the rounds better; whole and ragged edges, K of whole and half steps of 64
     for K in [64 * i + 32 * (i % 2 if i > 1 else 0) for i in range(4, 17)]:
+        assert gws.gws_gemm_form(M, K, N, w_is_nk) == gws.GEMM_NARROW
         gen = torch.Generator(device=DEV).manual_seed(K)
         x = torch.randn(M, K, generator=gen, device=DEV).to(torch.bfloat16)
         w = (torch.randn(*((N, K) if w_is_nk else (K, N)), generator=gen, device=DEV) * 0.02).to(torch.bfloat16)
@@ -418,7 +455,8 @@ def test_narrow_large_tiles_at_every_number_of_k_steps(M, N, w_is_nk):
 @pytest.mark.parametrize("w_is_nk", [False, True])
 @pytest.mark.parametrize("M,K,N", [(1500, 160, 1760), (2049, 288, 1312), (1537, 96, 4128), (4160, 64, 544)])
 def test_sampling_in_the_operand_load_of_many_rows(M, K, N, w_is_nk):
-    # 64 and 128 rows a workgroup, a last column tile of one wavefront, K of whole and half units; Y and w_hat bit for bit
+    assert gws.gws_gemm_form(M, K, N, w_is_nk, sampled=1, ldx=K + 8) == gws.GEMM_ROWS_SAMPLE
+    # a last row tile of 1 to 128 rows, a last column tile of one wavefront, K of whole and half units; Y and w_hat bit for bit
     for fmt in (gws.FMT_BF16, gws.FMT_FP8_E4M3, gws.FMT_FP6_E3M2):
         run_case(M, K, N, w_is_nk, fmt, seed_id=93, ldx_pad=8, ldy_pad=8, rows_sel=np.array([0, 63, 64, M // 2, M - 1]), mode=gws.LINEAR_IN_OPERAND)
 
@@ -429,6 +467,7 @@ def test_y_on_top_of_the_weight(M, w_is_nk):
     # a caller with room for w_hat (its own, a workspace, the library's buffer) may be done with w: the weight is then
     # sampled by a kernel of its own, at row counts that otherwise sample in the operand load
     K, N, fmt, step = 1024, 3072, gws.FMT_FP8_E4M3, 6
+    assert gws.gws_gemm_form(M, K, N, w_is_nk, sampled=2) == gws.GEMM_STREAM_SAMPLE
     t = synth.make_tensor(95, *((N, K) if w_is_nk else (K, N)), with_grad=False)
     rows, cols = t["w"].shape
     x, bt = synth.make_activation(96, M, K).to(DEV), t["bt"].to(DEV)
@@ -482,3 +521,60 @@ def test_a_product_of_one_tile_in_place(M, K, N, w_is_nk):
         check_y(run(on, False), synth.bits(xb), synth.bits(t["w"]), w_is_nk)
         if M <= 128:
             check_y(run(on, True), synth.bits(xb), q, w_is_nk)
+
+
+@pytest.mark.parametrize("w_is_nk", [False, True])
+@pytest.mark.parametrize("form,M,K,N", [(gws.GEMM_STREAM, 300, 672, 1056), (gws.GEMM_MIDDLE, 1537, 96, 1696), (gws.GEMM_MIDDLE, 1280, 320, 3328),
+                                        (gws.GEMM_LARGE, 8192, 320, 2048), (gws.GEMM_LARGE, 6656, 832, 1792), (gws.GEMM_LARGE_EDGE, 8191, 96, 1824),
+                                        (gws.GEMM_LARGE_EDGE, 7937, 1056, 1568), (gws.GEMM_NARROW, 8192, 448, 2560), (gws.GEMM_NARROW, 8000, 352, 2336),
+                                        (gws.GEMM_ANY_SHAPE, 300, 32, 416)])
+def test_every_gemm_with_padded_operands(form, M, K, N, w_is_nk):
+    # X, the weight and Y all in wider buffers, NaN in what the product must not read; against fp32 on the GPU
+    padx, padw, pady = 24, 40, 8
+    gen = torch.Generator(device=DEV).manual_seed(M + K)
+    wr, wc = (N, K) if w_is_nk else (K, N)
+    x = torch.full((M, K + padx), float("nan"), dtype=torch.bfloat16, device=DEV)
+    w = torch.full((wr, wc + padw), float("nan"), dtype=torch.bfloat16, device=DEV)
+    y = torch.zeros(M, N + pady, dtype=torch.bfloat16, device=DEV)
+    x[:, :K] = torch.randn(M, K, generator=gen, device=DEV)
+    w[:, :wc] = torch.randn(wr, wc, generator=gen, device=DEV) * 0.02
+    assert gws.gws_gemm_form(M, K, N, w_is_nk, ldx=K + padx, ldw=wc + padw) == form
+    gws.gws_gemm_bf16(x[:, :K], w[:, :wc], y[:, :N], w_is_nk=w_is_nk)
+    kn = (w[:, :wc].t().contiguous() if w_is_nk else w[:, :wc]).float()
+    xf = x[:, :K].float()
+    ref, mag = xf @ kn, xf.abs() @ kn.abs()
+    # one rounding to BF16 and two fp32 sums of K terms in different orders
+    assert bool(((y[:, :N].float() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2 * K * 2.0 ** -24 * mag).all())
+    assert bool((y[:, N:] == 0).all())
+
+
+@pytest.mark.parametrize("M,K,N", [(4224, 96, 2048), (4096, 160, 2176), (4001, 544, 2144)])
+def test_sampling_in_the_operand_load_on_the_tiles_of_any_shape(M, K, N):
+    # the [N x K] weights of 513 to 768 tiles of 128 x 128, which keep the kernel of the 32x32x16 MFMA and K-steps of 32:
+    # Y bit for bit that of the GEMM behind the sampling kernel, which takes another (16x16x32, steps of 64)
+    assert [gws.gws_gemm_form(M, K, N, True, k, ldx=K + 8) for k in (0, 1)] == [gws.GEMM_NARROW, gws.GEMM_ANY_SHAPE_SAMPLE]
+    for fmt in (gws.FMT_BF16, gws.FMT_FP8_E4M3, gws.FMT_FP6_E3M2):
+        run_case(M, K, N, True, fmt, seed_id=94, ldx_pad=8, ldy_pad=8, rows_sel=np.array([0, 127, 128, M // 2, M - 1]), mode=gws.LINEAR_IN_OPERAND)
+
+
+@pytest.mark.parametrize("w_is_nk", [False, True])
+@pytest.mark.parametrize("M,K,N,ldx,plain", [(130, 96, 160, 1 << 23, gws.GEMM_MIDDLE), (100, 160, 96, 1 << 24, gws.GEMM_ANY_SHAPE), (256, 320, 256, 1 << 24, gws.GEMM_LARGE)])
+def test_rows_of_x_far_apart(M, K, N, ldx, plain, w_is_nk):
+    # leading dimensions beyond the 32-bit lane offsets of some kernels: the others take over, and the two forms of the
+    # sampled linear still give the same bits
+    assert [gws.gws_gemm_form(M, K, N, w_is_nk, k, ldx=ldx) for k in (0, 1)] == [plain, gws.GEMM_ANY_SHAPE_SAMPLE]
+    fmt, step, seed = gws.FMT_FP8_E4M3, 3, oracle.derive_seed(0, 99)
+    t = synth.make_tensor(99, *((N, K) if w_is_nk else (K, N)), with_grad=False)
+    rows, cols = t["w"].shape
+    xs = synth.make_activation(99, M, K)
+    x = torch.empty(M, ldx, dtype=torch.bfloat16, device=DEV)[:, :K]
+    x.copy_(xs)
+    w, bt = t["w"].to(DEV), t["bt"].to(DEV)
+    d = gws.TensorDesc(rows=rows, cols=cols, seed=seed, w=w, bt=bt, w_hat=torch.zeros_like(w), scale=torch.zeros_like(bt))
+    y = [torch.zeros(M, N, dtype=torch.bfloat16, device=DEV) for _ in range(2)]
+    gws.gws_linear_fwd_mode(x, d, y[0], fmt, step, gws.LINEAR_TWO_KERNELS, w_is_nk=w_is_nk)
+    gws.gws_linear_fwd_mode(x, d, y[1], fmt, step, gws.LINEAR_IN_OPERAND, w_is_nk=w_is_nk)
+    torch.cuda.synchronize()
+    q, _ = oracle.sample_fwd(synth.bits(t["w"]), t["bt"].numpy(), fmt, seed, step)
+    check_y(synth.bits(y[0]), synth.bits(xs), q, w_is_nk)
+    assert (synth.bits(y[0]) == synth.bits(y[1])).all()
