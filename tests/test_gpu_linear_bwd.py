@@ -66,14 +66,15 @@ def run_case(M, K, N, w_is_nk, idx, step=4, rows_sel=None, pad=0, row0=0, col0=0
 
 @pytest.mark.parametrize("w_is_nk", [False, True])
 def test_single_tile_and_several_tiles(w_is_nk):
+    # few tiles of 256 x 256: small pieces (the other forms: test_each_form_padded_sharded_and_without_the_reduction)
     run_case(64, 256, 256, w_is_nk, 800)
     run_case(192, 512, 768, w_is_nk, 802, pad=8)
     run_case(128, 768, 256, w_is_nk, 804, row0=256, col0=512)     # a shard: the origin enters the noise counter
 
 
 def test_every_number_of_k_steps():
-    # tokens are the contraction here: 1 .. 13 K-steps of 64 tokens take every path through the prologue, the
-    # six-fold unrolled loop and its tail
+    # tokens are the contraction here: 1 .. 13 units of 64 tokens for the four wavefronts of a small piece (the tiles' own
+    # loops: test_every_form_of_the_weight_gradient)
     for nk in range(1, 14):
         run_case(64 * nk, 256, 256, bool(nk & 1), 840 + 2 * nk)
 
@@ -107,21 +108,26 @@ def test_epilogue_agrees_with_the_separate_backward_kernel_and_plain_form():
 
 @pytest.mark.parametrize("w_is_nk", [False, True])
 def test_tokens_split_into_parts(w_is_nk):
-    # few tiles: the contraction over the tokens is split (2 .. 8 parts, uneven where the K-steps do not divide),
-    # partial tiles go through the workspace and are added in a fixed order; dW and dL/db_t to the same bars
-    run_case(1024, 256, 256, w_is_nk, 860, split=-1)                  # 1 tile, 16 K-steps: 2 parts
-    run_case(2048, 512, 768, w_is_nk, 862, pad=8, split=-1)           # 6 tiles, 32 K-steps: 4 parts
-    run_case(4352, 768, 256, w_is_nk, 864, row0=256, col0=512, split=-1)   # 3 tiles, 68 K-steps: 8 parts of 8 or 9
+    # few tokens: small pieces of the gradient, with as many sums as the workspace holds parts or more
+    run_case(1024, 256, 256, w_is_nk, 860, split=-1)                  # 1 tile, room for 2 parts: four sums
+    run_case(2048, 512, 768, w_is_nk, 862, pad=8, split=-1)           # 6 tiles, room for 4 parts: four sums
+    run_case(4352, 768, 256, w_is_nk, 864, row0=256, col0=512, split=-1)   # 3 tiles, room for 8 parts: eight sums of 8 or 9 units
     # a workspace with room for three parts where eight were planned, and none at all
     per_part = 3 * 256 * 256 * 4
     run_case(4352, 768, 256, w_is_nk, 866, split=3 * per_part + 100)
     run_case(1024, 256, 256, w_is_nk, 868, split=0)
+    # many tokens: the contraction is split (partial tiles go through the workspace and are added in a fixed order), uneven
+    # where the units do not divide; dW and dL/db_t to the same bars
+    for tokens, K, N, idx in [(8192, 512, 512, 870), (5184, 256, 256, 872)]:
+        assert gws.gws_linear_bwd_w_form(gws.TensorDesc(rows=K, cols=N, ld=N, seed=0), tokens, 8 * K * N * 4) == gws.BWD_W_SPLIT + 8
+        run_case(tokens, K, N, w_is_nk, idx, pad=8, row0=256, col0=512, split=-1)
 
 
 def test_config5_sized_weights_split_over_tokens():
     # the 2048 x 2048 weight of the 1B layer over 8192 tokens: 64 tiles in 4 parts; a row in every 256-row tile
     rng = np.random.default_rng(870)
     sel = sorted({0, 2047} | {t * 256 + int(rng.integers(0, 256)) for t in range(8)})
+    assert gws.gws_linear_bwd_w_form(gws.TensorDesc(rows=2048, cols=2048, ld=2048, seed=0), 8192, 1 << 30) == gws.BWD_W_SPLIT + 4
     run_case(8192, 2048, 2048, False, 870, rows_sel=sel, split=-1)
     d = gws.TensorDesc(rows=2048, cols=5632, seed=1)
     assert gws.gws_linear_bwd_w_workspace_bytes(d, 8192) == 0          # 176 tiles: the one-kernel form
@@ -229,3 +235,42 @@ def test_no_fp32_sum_runs_over_more_tokens_than_a_part_of_the_workspace(tokens, 
         assert float(got.max()) <= total
         lost = total - float(got.min())
         assert lost <= 16 * run + 2.0 ** -8 * total, (parts, lost / 16, run)   # what the rounding to BF16 may add
+
+
+PIECES, SPLIT = {gws.BWD_W_PIECES_64, gws.BWD_W_PIECES_128}, gws.BWD_W_SPLIT
+
+
+@pytest.mark.parametrize("w_is_nk", [False, True])
+@pytest.mark.parametrize("form,tokens,rows,cols,room", [
+    ({gws.BWD_W_WIDE}, 64, 4096, 4096, 0), ({gws.BWD_W_WIDE}, 448, 4096, 4096, 0), ({gws.BWD_W_NARROW}, 384, 2048, 5632, 0), ({gws.BWD_W_NARROW}, 832, 2048, 5632, 0),
+    (PIECES, 192, 512, 768, 0), (PIECES, 576, 1536, 1024, 0), (PIECES, 2048, 1024, 1024, 4), (PIECES, 4096, 768, 768, 8), (PIECES, 4096, 768, 2304, 8),
+    ({SPLIT + 2}, 3584, 2048, 2816, 2), (PIECES, 4096, 768, 3072, 2), ({SPLIT + 3}, 2560, 1536, 2816, 3), ({SPLIT + 5}, 2624, 768, 2816, 5), ({SPLIT + 6}, 3072, 768, 2816, 6), ({SPLIT + 7}, 4096, 768, 3072, 7),
+    ({SPLIT + 8}, 6656, 512, 2304, 8), ({SPLIT + 8}, 8192, 512, 512, 8)])
+def test_each_form_padded_sharded_and_without_the_reduction(form, tokens, rows, cols, room, w_is_nk):
+    # X and dY in wider buffers with NaN beside them, dW in a wider buffer, the weight a shard of a larger one; room: the
+    # parts that the workspace holds.  With dL/db_t and without, the same dW
+    gen = torch.Generator(device=DEV).manual_seed(tokens + rows)
+    K, N = (cols, rows) if w_is_nk else (rows, cols)
+    x = torch.full((tokens, K + 24), float("nan"), dtype=torch.bfloat16, device=DEV)
+    dy = torch.full((tokens, N + 8), float("nan"), dtype=torch.bfloat16, device=DEV)
+    x[:, :K] = torch.randn(tokens, K, generator=gen, device=DEV)
+    dy[:, :N] = torch.randn(tokens, N, generator=gen, device=DEV) * 1e-3
+    dw = torch.full((rows, cols + 16), 7.0, dtype=torch.bfloat16, device=DEV)
+    shard = dict(rows=rows, cols=cols, ld=cols + 16, row0=320, col0=96, seed=41)
+    d = gws.TensorDesc(**shard, dw=dw, scale=torch.rand(rows // 32, cols // 32, generator=gen, device=DEV), dbt=torch.full((rows // 32, cols // 32), float("nan"), device=DEV))
+    ws = torch.full((room * rows * cols,), float("nan"), device=DEV) if room else None
+    assert gws.gws_linear_bwd_w_form(d, tokens, room * rows * cols * 4) in form
+    gws.gws_linear_bwd_w_ws(x[:, :K], dy[:, :N], d, 5, ws, w_is_nk=w_is_nk)
+    a, b = (dy[:, :N], x[:, :K]) if w_is_nk else (x[:, :K], dy[:, :N])
+    ref, mag = fp32_product(a, b), fp32_product(a.abs(), b.abs())
+    # one rounding to BF16 and two fp32 sums of `tokens` terms in different orders
+    assert bool(((dw[:, :cols].float() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2 * tokens * 2.0 ** -24 * mag).all())
+    assert bool((dw[:, cols:] == 7.0).all())
+    back = gws.TensorDesc(**shard, scale=d.scale, g=dw, dw=None, dbt=torch.zeros_like(d.dbt))
+    gws.gws_sample_bwd([back], 5)
+    terms = 0.6932 * d.scale * dw[:, :cols].float().abs().view(rows // 32, 32, cols // 32, 32).sum((1, 3)) * 2
+    assert bool(((d.dbt - back.dbt).abs() <= 1e-5 * back.dbt.abs() + 1e-6 * terms).all())
+    with_dbt = dw.clone()
+    dw.fill_(7.0)
+    gws.gws_linear_bwd_w_ws(x[:, :K], dy[:, :N], gws.TensorDesc(**shard, dw=dw), 5, ws, w_is_nk=w_is_nk)
+    assert torch.equal(dw.view(torch.int16), with_dbt.view(torch.int16))
