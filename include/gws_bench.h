@@ -78,6 +78,15 @@ int gws_gemm_form(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int
 #define GWS_BWD_W_SPLIT 16          /* + parts: the tokens of a 256 x 256 tile split over so many workgroups */
 int gws_linear_bwd_w_form(const gws_tensor* w, int64_t M, size_t workspace_bytes);
 
+/* The Box-Muller basis draws R of a word of noise by thresholds on z^2 (hardware logarithm and cosine) unless z^2 comes
+ * near one, and by its defined sequence of fp32 operations there.  Both ways over the words first .. first + n - 1 (at most
+ * 2^32 of them), added to out (device, three uint64 that the caller clears):
+ *   out[0]  words for which the thresholds alone decide and give another R than the sequence
+ *   out[1]  words that are left to the sequence
+ *   out[2]  (maximum) of those that the thresholds would decide wrongly, the distance from the threshold, in units of
+ *           2^-24 of the window's width: how much of the half window, 2^23, the hardware's errors need              */
+int gws_box_muller_check(uint64_t first, uint64_t n, void* out, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -25,7 +25,7 @@ EXPORTS = ("gws_sample_fwd", "gws_sample_bwd", "gws_sample_fwd_bi", "gws_sample_
            "gws_sample_fwd_basis", "gws_sample_bwd_basis", "gws_noise_basis",
            "gws_derive_seed", "gws_status_string", "gws_version")
 BENCH_EXPORTS = ("gws_copy_tiles", "gws_block_absmax", "gws_sample_bwd_tuned", "gws_sample_fwd_tuned", "gws_gemm_bf16_ride_probe", "gws_ride_plan",
-                 "gws_ride_plan_layout", "gws_gemm_form", "gws_linear_bwd_w_form")
+                 "gws_ride_plan_layout", "gws_gemm_form", "gws_linear_bwd_w_form", "gws_box_muller_check")
 # kernels as gws_gemm_form and gws_linear_bwd_w_form name them
 GEMM_STREAM, GEMM_MIDDLE, GEMM_LARGE, GEMM_LARGE_EDGE, GEMM_NARROW, GEMM_ANY_SHAPE, GEMM_STREAM_SAMPLE, GEMM_ROWS_SAMPLE, GEMM_ANY_SHAPE_SAMPLE = range(1, 10)
 BWD_W_WIDE, BWD_W_NARROW, BWD_W_PIECES_64, BWD_W_PIECES_128, BWD_W_SPLIT = 1, 2, 3, 4, 16
@@ -143,6 +143,8 @@ def load_library() -> ctypes.CDLL:
     L.gws_gemm_form.restype = ci
     L.gws_linear_bwd_w_form.argtypes = [tp, i64, ctypes.c_size_t]
     L.gws_linear_bwd_w_form.restype = ci
+    L.gws_box_muller_check.argtypes = [u64, u64, vp, vp]
+    L.gws_box_muller_check.restype = ci
     L.gws_gemm_bf16_ride_probe.argtypes = [vp, i64, i64, i64, vp, i64, i64, ci, vp, i64, tp, ci, u64, ci, ci, vp]
     L.gws_gemm_bf16_ride_probe.restype = ci
     L.gws_sample_fwd_tuned.argtypes = [tp, ci, ci, u64, ci, ci, vp]
@@ -514,6 +516,11 @@ def gws_noise_basis(out, rows: int, cols: int, seed: int, step: int, basis: int,
     L = load_library()
     _check(L.gws_noise_basis(_p(out), rows, cols, row0, col0, seed & (2 ** 64 - 1), int(step), int(basis),
                              _stream(stream)), "gws_noise_basis")
+
+
+def gws_box_muller_check(out, first: int = 0, n: int = 2 ** 32, stream=None) -> None:
+    """Both ways to R of the Box-Muller basis over ``n`` words of noise, compared; ``out``: three int64 on the device, added to."""
+    _check(load_library().gws_box_muller_check(int(first), int(n), _p(out), _stream(stream)), "gws_box_muller_check")
 
 
 def gws_noise_packed(out, rows: int, cols: int, seed: int, step: int, row0: int = 0, col0: int = 0,

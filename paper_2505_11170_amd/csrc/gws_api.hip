@@ -410,6 +410,14 @@ int gws_copy_tiles(const gws_tensor* t, int n, void* stream) {
   return run_batched(t, n, nullptr, nullptr, true, kCopyOnly, 0, (hipStream_t)stream);
 }
 
+int gws_box_muller_check(uint64_t first, uint64_t n, void* out, void* stream) {
+  if (first > (uint64_t)1 << 32 || n > ((uint64_t)1 << 32) - first) return GWS_ERR_SHAPE;
+  if (n == 0) return GWS_OK;
+  if (!out) return GWS_ERR_NULL;
+  if (!aligned(out, 8)) return GWS_ERR_ALIGN;
+  return launch_box_muller_check(first, n, (uint64_t*)out, (hipStream_t)stream);
+}
+
 int gws_block_absmax(const gws_tensor* t, int n, void* stream) {
   if (n < 0) return GWS_ERR_SHAPE;
   if (n == 0) return GWS_OK;

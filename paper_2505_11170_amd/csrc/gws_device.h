@@ -513,9 +513,10 @@ __device__ __forceinline__ void box_muller_pair(uint32_t word, float& r_lo, floa
 // hardware cosine (of revolutions) a pair say so for all but the words near a threshold.  Each comparison is a multiply-add
 // clamped to [0, 1] that is fractional within 2^-15 of the threshold (in units of z^2 / (2 ln 2)); a group with such an
 // element in any lane (about one group in a hundred) takes the exact sequence above for all of its pairs.  The hardware
-// functions are off by at most a fortieth of that half window there: over all 2^32 words both ways give the same bits.  The
-// sign is the quadrant's: bits of the word.  About 24 vector instructions a pair where the exact sequence takes 90: both passes over a
-// 2048 x 8192 weight 43.8 -> 29.0 us (the bytes take 17).
+// functions need 2.5 % of that half window, 4.1e-5 of the words lie within it, and over all 2^32 words both ways give the
+// same bits (gws_box_muller_check counts all three).  The sign is the quadrant's: bits of the word.  About 24 vector
+// instructions a pair where the exact sequence takes 90: both passes over a 2048 x 8192 weight 43.8 -> 29.0 us (the bytes
+// take 17).
 __device__ __forceinline__ void box_muller_pair_fast(uint32_t word, float& r_lo, float& r_hi, float& near) {
   constexpr float W = 16384.0f, T1 = 0.72134752f, T9 = 6.49212768f;   // 1 / window, 1 / (2 ln 2), 9 / (2 ln 2)
   // 2^23 + half word: the conversion to fp32 is a byte permute; (x - 2^23 + 0.5) / 2^16 is exact

@@ -70,6 +70,7 @@ int launch_sample_fwd(const LaunchArgs& a, uint32_t n_wg, int fmt, bool mx, int 
 int launch_sample_bwd(const LaunchArgs& a, uint32_t n_wg, int basis, int mode, int variant, hipStream_t stream);
 int launch_noise_basis(void* out, uint32_t rows, uint32_t ngrp, uint32_t row0, uint32_t cg0, uint64_t seed, uint64_t step,
                        int basis, hipStream_t stream);
+int launch_box_muller_check(uint64_t first, uint64_t n, uint64_t* out, hipStream_t stream);
 int launch_copy_tiles(const LaunchArgs& a, uint32_t n_wg, hipStream_t stream);
 int launch_block_absmax(const LaunchArgs& a, uint32_t n_wg, hipStream_t stream);
 int launch_noise_packed(uint32_t* out, uint32_t rows, uint32_t ngrp, uint32_t row0, uint32_t cg0,

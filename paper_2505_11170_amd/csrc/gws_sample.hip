@@ -363,6 +363,31 @@ __global__ __launch_bounds__(256) void noise_basis_kernel(u32x4* __restrict__ ou
   out[idx] = basis_group_bf16<BASIS>(philox4x32_10(cg0 + cgl, row0 + row, step_lo, step_hi, seed_lo, seed_hi));
 }
 
+// Both ways to R of the Box-Muller basis over the words first .. first + n - 1 (gws_box_muller_check of gws_bench.h).
+__global__ __launch_bounds__(256) void box_muller_check_kernel(uint64_t first, uint64_t n, unsigned long long* __restrict__ out) {
+  uint32_t differ = 0, exact = 0, worst = 0;
+  for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (uint64_t)gridDim.x * 256) {
+    const uint32_t word = (uint32_t)(first + i);
+    float r[2], e[2], near = 0.0f;
+    box_muller_pair_fast(word, r[0], r[1], near);
+    box_muller_pair(word, e[0], e[1]);
+    if (near == 0.0f) {
+      differ += __float_as_uint(r[0]) != __float_as_uint(e[0]) || __float_as_uint(r[1]) != __float_as_uint(e[1]) ? 1 : 0;
+      continue;
+    }
+    ++exact;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const float m = __builtin_fabsf(r[k]), f = m - __builtin_floorf(m);   // 0.5: on the threshold
+      if (f != 0.0f && __builtin_floorf(m) + (f >= 0.5f ? 1.0f : 0.0f) != __builtin_fabsf(e[k]))
+        worst = max(worst, (uint32_t)(__builtin_fabsf(f - 0.5f) * 0x1p24f));
+    }
+  }
+  if (differ) atomicAdd(&out[0], (unsigned long long)differ);
+  if (exact) atomicAdd(&out[1], (unsigned long long)exact);
+  if (worst) atomicMax(&out[2], (unsigned long long)worst);
+}
+
 // ---------------------------------------------------------------------------
 // Host-side launchers
 // ---------------------------------------------------------------------------
@@ -445,6 +470,13 @@ int launch_noise_basis(void* out, uint32_t rows, uint32_t ngrp, uint32_t row0, u
   else if (basis == kBasisBoxMuller)
     hipLaunchKernelGGL(noise_basis_kernel<kBasisBoxMuller>, dim3(grid), dim3(256), 0, stream, (u32x4*)out, rows, ngrp, row0, cg0, slo, shi, tlo, thi);
   else return GWS_ERR_FORMAT;
+  return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
+}
+
+int launch_box_muller_check(uint64_t first, uint64_t n, uint64_t* out, hipStream_t stream) {
+  if (n == 0) return GWS_OK;
+  hipLaunchKernelGGL(box_muller_check_kernel, dim3((uint32_t)(n < 4096 * 256 ? (n + 255) / 256 : 4096)), dim3(256), 0, stream, first, n,
+                     (unsigned long long*)out);
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
 

@@ -133,3 +133,15 @@ def test_whole_tiles_with_the_gradient_passed_through(name, fmt):
     # rows multiples of 32, columns of 256, dL/dw aliased: the whole-tile kernels, one tile and several
     gb, ob = BASES[name]
     run_fwd_bwd([(32, 256), (64, 1536), (96, 512)], gb, ob, fmt, 9, copy_dw=False)
+
+
+def test_box_muller_thresholds_and_defined_sequence_agree_for_every_word():
+    # all 2^32 words of noise: R by thresholds is the defined sequence's wherever the thresholds decide, few words are left
+    # to the sequence, and the hardware functions' errors need a small part of the half window (2^23) around a threshold
+    out = torch.zeros(3, dtype=torch.int64, device=DEV)
+    gws.gws_box_muller_check(out)
+    torch.cuda.synchronize()
+    differ, left, worst = out.tolist()
+    assert differ == 0
+    assert 0 < left < 1e-4 * 2 ** 32
+    assert 0 < worst <= 2 ** 23 // 20
