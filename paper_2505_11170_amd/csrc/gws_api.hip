@@ -599,22 +599,27 @@ static uint32_t parts_within(const GemmArgs& g, size_t workspace_bytes, int cus)
 // rounded 64-bit value, 768 x 3072 over 4096 tokens: 2.6e-4 in one sum, 2.0e-4 in five, 1.7e-4 in seven.
 //  - With workspace: the tokens of a tile split over that many workgroups, or small pieces of the gradient with the tokens in
 //    four sums or (parts > 4) eight.
-//  - Without (parts < 2): one workgroup per tile of 256 x 256 or of 256 x 192 (four fifths of the time each: 2048 x 5632 over
-//    8192 tokens 163 against 188), or small pieces.
-// Fitted to MI355X timings, tokens x rows x cols: 512 x 4096 x 4096 one tile each 26; in parts and in small pieces 4096 x
-// 768 x 3072 40 and 50, 4096 x 768 x 2304 35 and 29, 4096 x 2048 x 2048 50 and 53, 2048 x 2048 x 2048 42 and 34, 8192 x
-// 512 x 512 29 and 32, 2048 x 1024 x 1024 26 and 12.
+//  - Without (parts < 2): one workgroup per tile of 256 x 256 or of 256 x 192, or small pieces.
+// Fitted to MI355X timings; in parts and in small pieces, tokens x rows x cols: 4096 x 768 x 3072 40 and 50, 4096 x 768 x 2304
+// 35 and 29, 4096 x 2048 x 2048 50 and 53, 2048 x 2048 x 2048 42 and 34, 8192 x 512 x 512 29 and 32, 2048 x 1024 x 1024 26 and
+// 12, 1024 x 2048 x 4096 39 and 44.
 static int bwd_w_form(const GemmArgs& g, uint32_t parts, TnPlan& small) {
-  small = stream_tn_plan(g);
+  small = stream_tn_plan(g, parts > 4);
   const int pieces = small.mt == 4 ? GWS_BWD_W_PIECES_64 : GWS_BWD_W_PIECES_128;
   const double nk = (double)(g.K / 64);
   if (parts >= 2) {
-    const double split_us = 8.2 + nk / parts * 1.19 + (double)gemm256_tn_split_bytes(g, parts) * 0.317e-6;
+    const double split_us = 9.0 + nk / parts * 1.15 + (double)gemm256_tn_split_bytes(g, parts) * 0.317e-6;
     return small.us < split_us ? pieces : GWS_BWD_W_SPLIT;
   }
   const double cus = compute_units() > 0 ? compute_units() : 256;
-  auto whole = [&](double n, double k_step) { return 6.0 + ceil(n / cus) * (3.0 + nk * k_step * (1.2 + 0.2 * fmin(1.0, n / cus))); };
-  const double wide_us = whole((double)(g.M / 256) * (double)(g.N / 256), 1.0), narrow_us = whole((double)(g.M / 256) * ceil(g.N / 192.0), 0.8);
+  // Fixed: a launch, and with the tiles in flight the stores and the noise on the way out; the narrow tile's way out is by
+  // blocks.  Wide and narrow, us: 2048 x 4096 over 64 tokens 14.1 and 15.5, 448 21.3 and 21.6, 960 30.4 and 28.8; 2048 x 5632
+  // over 192 tokens 15.9 and 17.0, 640 24.2 and 24.2, 8192 188 and 163; 4096 x 4096 (one round and two) over 960 32.8 and 53.5.
+  auto whole = [&](double n, double way_out, double k_step) {
+    const double busy = fmin(1.0, n / cus);
+    return 7.5 + ceil(n / cus) * (3.0 + 3.0 * busy + way_out + nk * k_step * (1.0 + 0.35 * busy));
+  };
+  const double wide_us = whole((double)(g.M / 256) * (double)(g.N / 256), 0.0, 1.0), narrow_us = whole((double)(g.M / 256) * ceil(g.N / 192.0), 0.8, 0.83);
   if (small.us < fmin(wide_us, narrow_us)) return pieces;
   return narrow_us < wide_us ? GWS_BWD_W_NARROW : GWS_BWD_W_WIDE;
 }

@@ -145,16 +145,17 @@ static void launch_tn(const GemmArgs& g, bool with_dbt, hipStream_t s) {
   else hipLaunchKernelGGL((gemm_stream_tn_kernel<MT, 4, D, false, HALVES>), grid, dim3(256), 0, s, g);
 }
 
-// mt: row tiles of 16 of the piece (4 or 8); us: the estimate as in stream_plan.
-TnPlan stream_tn_plan(const GemmArgs& g) {
+// mt: row tiles of 16 of the piece (4 or 8); us: the estimate as in stream_plan.  The larger piece's fixed part of a round
+// grows with the rounds (a round's reductions and stores meet the next one's loads): 1024 tokens in one, three and four rounds
+// 10, 36 and 44 us.
+TnPlan stream_tn_plan(const GemmArgs& g, bool halves) {
   const double cus = compute_units() > 0 ? compute_units() : 256;
   TnPlan best = {0, 1e30};
-  // the fixed part of a round, and the bytes per ns a compute unit takes; tokens x rows x cols 1024 x 2048 x 4096: 48.7 and
-  // 44.2 us (8 and 4 rounds), 4096 x 2048 x 2048 63.7 and 52.6 (4 and 2)
-  static const struct { int mt; double round, rate; } tiles[] = {{4, 2.7, 82.0}, {8, 4.5, 74.0}};
+  // fixed part of a round, what it grows by, bytes per ns that a compute unit takes, what the halves cost
+  static const struct { int mt; double round, more, rate, halves; } tiles[] = {{4, 2.7, 0.0, 82.0, 0.6}, {8, 3.5, 0.7, 75.0, 1.8}};
   for (const auto& t : tiles) {
     const double rounds = ceil((double)(g.M / (16 * t.mt)) * (double)(g.N / 64) / cus);
-    const double us = 2.8 + rounds * (t.round + (double)g.K * 2 * 16 * (t.mt + 4) / t.rate * 1e-3);
+    const double us = 2.8 + rounds * (t.round + t.more * fmin(rounds - 1.0, 2.0) + (double)g.K * 2 * 16 * (t.mt + 4) / t.rate * 1e-3) + (halves ? t.halves : 0.0);
     if (us < best.us) best = {t.mt, us};
   }
   return best;

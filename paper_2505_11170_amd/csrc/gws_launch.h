@@ -149,7 +149,7 @@ struct TnPlan {
   int mt;
   double us;
 };
-TnPlan stream_tn_plan(const GemmArgs& g);
+TnPlan stream_tn_plan(const GemmArgs& g, bool halves);
 int launch_gemm_stream_tn(const GemmArgs& g, bool with_dbt, const TnPlan& p, bool halves, hipStream_t stream);
 // the same result with the contraction of every tile split over `parts` (2 .. 8, at most K / 64) workgroups: fp32 partial tiles in
 // `ws` (gemm256_tn_split_bytes, 16-byte aligned), added in a fixed order by a second kernel

@@ -242,7 +242,7 @@ PIECES, SPLIT = {gws.BWD_W_PIECES_64, gws.BWD_W_PIECES_128}, gws.BWD_W_SPLIT
 
 @pytest.mark.parametrize("w_is_nk", [False, True])
 @pytest.mark.parametrize("form,tokens,rows,cols,room", [
-    ({gws.BWD_W_WIDE}, 64, 4096, 4096, 0), ({gws.BWD_W_WIDE}, 448, 4096, 4096, 0), ({gws.BWD_W_NARROW}, 384, 2048, 5632, 0), ({gws.BWD_W_NARROW}, 832, 2048, 5632, 0),
+    ({gws.BWD_W_WIDE}, 64, 4096, 4096, 0), ({gws.BWD_W_WIDE}, 448, 4096, 4096, 0), ({gws.BWD_W_WIDE}, 192, 2048, 5632, 0), ({gws.BWD_W_NARROW}, 832, 2048, 5632, 0), ({gws.BWD_W_NARROW}, 1088, 2048, 5632, 0),
     (PIECES, 192, 512, 768, 0), (PIECES, 576, 1536, 1024, 0), (PIECES, 2048, 1024, 1024, 4), (PIECES, 4096, 768, 768, 8), (PIECES, 4096, 768, 2304, 8),
     ({SPLIT + 2}, 3584, 2048, 2816, 2), (PIECES, 4096, 768, 3072, 2), ({SPLIT + 3}, 2560, 1536, 2816, 3), ({SPLIT + 5}, 2624, 768, 2816, 5), ({SPLIT + 6}, 3072, 768, 2816, 6), ({SPLIT + 7}, 4096, 768, 3072, 7),
     ({SPLIT + 8}, 6656, 512, 2304, 8), ({SPLIT + 8}, 8192, 512, 512, 8)])
