@@ -163,7 +163,10 @@ int gws_sample_fwd_mx(const gws_tensor* t, const gws_mx_out* o, int n, int fmt, 
  *       w_is_nk != 0, [N x K] (rows = N, cols = K; Y = X * w_hat^T).
  *       w->w_hat and w->scale are written if non-NULL (both or neither).
  *   y : device BF16 [M x N], leading dimension ldy; fp32 accumulation, one
- *       round-to-nearest-even to BF16.
+ *       round-to-nearest-even to BF16.  The order of the fp32 sums goes by M, N, K, the layout and
+ *       the device's number of compute units: a row of Y need not be the same bits for another M.
+ *       y may lie on x or w->w only where one workgroup makes all of it (M and N up to 128), and on
+ *       w->w also where the weight is sampled by a kernel of its own (see GWS_LINEAR_AUTO).
  * K and N must be multiples of 32; ldx, ldy multiples of 8.
  * Two ways to the same bytes (w_hat, scale and Y are bit-identical between them):
  *   GWS_LINEAR_IN_OPERAND   one kernel; the sampling sits in the weight operand load of every
@@ -257,7 +260,9 @@ int gws_linear_bwd_w_ws(const void* x, const void* dy, int64_t M, int64_t ldx, i
 
 /* Plain BF16 GEMM with the same tiling as gws_linear_fwd and no sampling:
  * Y = X * W (or X * W^T when w_is_nk).  The reference point the fused kernel's
- * overhead is measured against.  w is device BF16 with leading dimension ldw.     */
+ * overhead is measured against.  w is device BF16 with leading dimension ldw.
+ * y may lie on x or w only where one workgroup makes all of it (M and N up to 128, or
+ * both 256 with K a multiple of 64 and ldx, ldw below 2^28).                       */
 int gws_gemm_bf16(const void* x, int64_t M, int64_t K, int64_t ldx,
                   const void* w, int64_t N, int64_t ldw, int w_is_nk,
                   void* y, int64_t ldy, void* stream);

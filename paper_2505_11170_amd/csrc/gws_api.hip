@@ -619,7 +619,8 @@ static int bwd_w_form(const GemmArgs& g, uint32_t parts, TnPlan& small) {
     const double busy = fmin(1.0, n / cus);
     return 7.5 + ceil(n / cus) * (3.0 + 3.0 * busy + way_out + nk * k_step * (1.0 + 0.35 * busy));
   };
-  const double wide_us = whole((double)(g.M / 256) * (double)(g.N / 256), 0.0, 1.0), narrow_us = whole((double)(g.M / 256) * ceil(g.N / 192.0), 0.8, 0.83);
+  const double wide_us = whole((double)(g.M / 256) * (double)(g.N / 256), 0.0, 1.0);
+  const double narrow_us = whole((double)(g.M / 256) * ceil(g.N / 192.0), 0.8, 0.83);
   if (small.us < fmin(wide_us, narrow_us)) return pieces;
   return narrow_us < wide_us ? GWS_BWD_W_NARROW : GWS_BWD_W_WIDE;
 }

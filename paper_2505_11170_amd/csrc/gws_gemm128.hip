@@ -140,14 +140,16 @@ __global__ __launch_bounds__(256) void gemm128_kernel(const GemmArgs g) {
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      *(u32x2*)(cs + (16 * i + li) * PC + 16 * j + 4 * grp) = u32x2{pack_bf16_rne(acc[i][j][0], acc[i][j][1]), pack_bf16_rne(acc[i][j][2], acc[i][j][3])};
+      *(u32x2*)(cs + (16 * i + li) * PC + 16 * j + 4 * grp) =
+          u32x2{pack_bf16_rne(acc[i][j][0], acc[i][j][1]), pack_bf16_rne(acc[i][j][2], acc[i][j][3])};
   __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wavefront's LDS writes have landed
   __builtin_amdgcn_wave_barrier();
   const uint32_t row0 = m0 + 64 * wm + (lane >> 3), col = n0 + 64 * wn + 8 * (lane & 7);
   if (col < g.N) {
 #pragma unroll
     for (int it = 0; it < 8; ++it)
-      if (row0 + 8 * it < g.M) *(u32x4*)(g.y + (size_t)(row0 + 8 * it) * g.ldy + col) = *(const u32x4*)(cs + ((lane >> 3) + 8 * it) * PC + 8 * (lane & 7));
+      if (row0 + 8 * it < g.M)
+        *(u32x4*)(g.y + (size_t)(row0 + 8 * it) * g.ldy + col) = *(const u32x4*)(cs + ((lane >> 3) + 8 * it) * PC + 8 * (lane & 7));
   }
 }
 

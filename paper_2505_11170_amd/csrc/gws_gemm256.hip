@@ -1,8 +1,8 @@
 // Large-tile BF16 MFMA GEMM for gfx950: Y[M x N] = X[M x K] * W, W stored [K x N] or
-// [N x K].  Used when M, N are multiples of 256 and K of 64.  The tile itself (direct
-// global -> LDS loads, swizzled stages, pinned MFMA / LDS-read / load interleave) is in
-// gws_gemm256_core.h; here are the plain kernel and the plain kernel with another weight's
-// sampling riding at the end of its grid.
+// [N x K].  The tile itself (direct global -> LDS loads, swizzled stages, pinned MFMA / LDS-read / load interleave) is in
+// gws_gemm256_core.h; here are the kernels on it: whole 256 x 256 tiles (M, N multiples of 256 and K of 64), the same with
+// other weights' sampling riding at the end of its grid, 256 x 256 tiles with edges (any M, N and K of whole 32s) and
+// 256 x 192 tiles with edges.
 // Tiles are numbered so that the 32 workgroups running together on one XCD
 // (workgroups are dealt round-robin to the 8 XCDs, each with its own L2) form an
 // 8 x 4 patch that shares 8 X panels and 4 W panels.

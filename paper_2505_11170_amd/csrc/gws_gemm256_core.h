@@ -217,8 +217,9 @@ __device__ __forceinline__ void gemm256_accumulate(const uint16_t* __restrict__ 
     // overwritten; it has to be told)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
+    const int v = narrow && oc ? (q < 4 ? q >> 1 : 2 + (q & 1)) : oc ? (q & 1) + 2 * ((q >> 2) & 1) : EDGE ? q : (q & 1);
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :: "v"(s.voff[narrow && oc ? (q < 4 ? q >> 1 : 2 + (q & 1)) : oc ? (q & 1) + 2 * ((q >> 2) & 1) : EDGE ? q : (q & 1)]), "s"(s.base + uni * 2), "s"(lds_addr) : "m0", "memory");
+                 :: "v"(s.voff[v]), "s"(s.base + uni * 2), "s"(lds_addr) : "m0", "memory");
 #pragma clang diagnostic pop
   };
   auto load_a = [&](uint16_t* st, uint32_t kt, int q) { load1(A_OC, false, sa, st, kt, q); };
@@ -409,7 +410,8 @@ __device__ __forceinline__ void gemm256_accumulate(const uint16_t* __restrict__ 
 
 // The way out of half h (64 rows) of a wavefront's 128 x 96 part of a narrow tile: as epilogue_bf16_half, but by 32 x 32
 // blocks: lane = (row % 16, 16-byte column group) of a block; hook(row, col, v) for every group (row and col relative to the
-// wavefront's part), and block_done(block row, block column) behind a block's two.  Only rows and columns below `rows` and `cols` (a multiple of 32) exist.
+// wavefront's part), and block_done(block row, block column) behind a block's two.  Only rows and columns below `rows` and
+// `cols` (a multiple of 32) exist.
 template <class Hook, class Done>
 __device__ __forceinline__ void epilogue_narrow_half(const f32x4 (&a4)[4][6], int h, uint16_t* cs, uint16_t* yw, uint32_t ldy,
                                                      uint32_t lane, int rows, int cols, Hook&& hook, Done&& block_done) {

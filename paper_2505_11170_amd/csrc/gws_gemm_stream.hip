@@ -3,12 +3,11 @@
 //
 // What bounds it: the weight's bytes.  A tile of the output that walks all of K alone waits for memory K / 64 times, and
 // a few rows of X make a few tiles.  So a workgroup owns a small piece of Y (16 MT rows x 16 NT columns) and its
-// wavefronts split K: wavefront w takes a contiguous range of 64-deep units of K, keeps several blocks of loads in
-// flight, and needs neither barrier nor LDS until the partial sums meet in LDS, where they are added in the order of
-// the wavefronts (one defined order; the plain and the sampling kernel split K alike, so their Y is the same bits).
-// Operands go from global memory straight to the MFMA's registers: a lane of v_mfma_f32_16x16x32_bf16 holds 8
-// consecutive k of one output.  [N x K] weights and X are stored like that; of a [K x N] weight a lane loads the same
-// NT outputs of 8 rows and turns the 8 x NT piece with byte permutes.
+// wavefronts split K: wavefront w takes a contiguous range of 64-deep units of K, keeps several units of loads on their way
+// into its own ring of LDS stages, and meets the others at a barrier only for the partial sums, which are added in LDS in
+// the order of the wavefronts (one defined order; the plain and the sampling kernel split K alike, so their Y is the same
+// bits).  How many wavefronts split K goes by M, N, K and the number of compute units (stream_plan), so a row of Y is not
+// the same bits for every number of rows beside it.
 #include "gws_gemm_stream_core.h"
 
 namespace gws {
@@ -303,7 +302,8 @@ __global__ __launch_bounds__(256, 2) void gemm_rows_sample_kernel(const GemmArgs
     if (row < g.M) {
 #pragma unroll
       for (int j = 0; j < 2; ++j)
-        *(u32x2*)(g.y + (size_t)row * g.ldy + n0 + 16 * j + 4 * grp) = u32x2{pack_bf16_rne(acc[i][j][0], acc[i][j][1]), pack_bf16_rne(acc[i][j][2], acc[i][j][3])};
+        *(u32x2*)(g.y + (size_t)row * g.ldy + n0 + 16 * j + 4 * grp) =
+            u32x2{pack_bf16_rne(acc[i][j][0], acc[i][j][1]), pack_bf16_rne(acc[i][j][2], acc[i][j][3])};
     }
   }
 }
@@ -327,7 +327,8 @@ StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk) {
   if (K < 64) return best;
   const int cus = compute_units() > 0 ? compute_units() : 256;
   // bytes per ns: eight wavefronts keep twice the loads in flight that four do
-  static const struct { int mt, nt, p; double rate; } tiles[] = {{1, 1, 8, 130.0}, {1, 2, 8, 130.0}, {2, 2, 8, 130.0}, {2, 4, 4, 100.0}, {4, 4, 4, 100.0}, {8, 4, 4, 72.0}};
+  static const struct { int mt, nt, p; double rate; } tiles[] = {{1, 1, 8, 130.0}, {1, 2, 8, 130.0}, {2, 2, 8, 130.0},
+                                                                 {2, 4, 4, 100.0}, {4, 4, 4, 100.0}, {8, 4, 4, 72.0}};
   for (const auto& t : tiles) {
     if (t.mt == 1 && M > 16) continue;
     if (t.nt == 1 && !w_is_nk) continue;   // 32 bytes of a row of a [K x N] weight: a quarter of a cache line

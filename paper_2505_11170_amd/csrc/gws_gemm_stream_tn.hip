@@ -6,7 +6,8 @@
 // 1024 12.1, 16.7, 25.6; 1536 x 1536 x 1024 17.6, 15.3, 25.9; 4096 x 768 x 768 17.1, 26.6, 23.9; 8192 x 1024 x 1024 34, 45,
 // 37; 4096 x 768 x 3072 48, 49, 40.
 // Both operands lie output-contiguous, so both stages are k-rows of 32 MT and 32 NT bytes and both fragments come from the
-// transposing LDS load.  On the way out the sums are rounded to BF16 in LDS and each wavefront takes one 32 x 32 block of the
+// transposing LDS load.  Where the workspace at hand would hold more than four parts, a wavefront sums its tokens in two
+// halves, so that no fp32 sum is longer than in that form.  On the way out the sums are rounded to BF16 in LDS and each wavefront takes one 32 x 32 block of the
 // weight: 16 bytes a lane, one Philox group each, and the reduction of Eq. 4 over the wavefront.
 #include <math.h>
 
@@ -155,7 +156,8 @@ TnPlan stream_tn_plan(const GemmArgs& g, bool halves) {
   static const struct { int mt; double round, more, rate, halves; } tiles[] = {{4, 2.7, 0.0, 82.0, 0.6}, {8, 3.5, 0.7, 75.0, 1.8}};
   for (const auto& t : tiles) {
     const double rounds = ceil((double)(g.M / (16 * t.mt)) * (double)(g.N / 64) / cus);
-    const double us = 2.8 + rounds * (t.round + t.more * fmin(rounds - 1.0, 2.0) + (double)g.K * 2 * 16 * (t.mt + 4) / t.rate * 1e-3) + (halves ? t.halves : 0.0);
+    const double a_round = t.round + t.more * fmin(rounds - 1.0, 2.0) + (double)g.K * 2 * 16 * (t.mt + 4) / t.rate * 1e-3;
+    const double us = 2.8 + rounds * a_round + (halves ? t.halves : 0.0);
     if (us < best.us) best = {t.mt, us};
   }
   return best;
