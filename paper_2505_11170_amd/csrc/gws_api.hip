@@ -168,10 +168,11 @@ int run_batched(const gws_tensor* t, int n, const gws_bitwidth* bw, const gws_mx
   a.tiles_per_wg_x = per_x;
   for (int i = 0; i < kMaxTensorsPerLaunch; ++i) a.tile_begin[i] = 0x7FFFFFFFu;
   uint64_t wgs = 0;
-  bool whole_tiles = true;   // every tensor of the pending launch: rows % 32 == 0, cols % 256 == 0, nothing to copy
+  // every tensor of the pending launch: rows % 32 == 0, cols % 256 == 0, rows below kMaxLaneLd, nothing to copy
+  bool whole_tiles = true;
   auto flush = [&]() -> int {
     if (a.n == 0) return GWS_OK;
-    const int variant = !whole_tiles ? 0 : tune.variant >= 0 ? tune.variant : 1;
+    const int variant = !whole_tiles || (fwd && per_x != 1) ? 0 : tune.variant >= 0 ? tune.variant : 1;
     int rc = (!fwd && fmt == kAbsmaxOnly) ? launch_block_absmax(a, (uint32_t)wgs, stream)
              : !fwd ? launch_sample_bwd(a, (uint32_t)wgs, basis, mode, variant, stream)
              : fmt == kCopyOnly ? launch_copy_tiles(a, (uint32_t)wgs, stream)
@@ -193,14 +194,14 @@ int run_batched(const gws_tensor* t, int n, const gws_bitwidth* bw, const gws_mx
     a.tile_begin[a.n] = (uint32_t)wgs;
     TileDesc& d = a.t[a.n++];
     d.first_wg = (uint32_t)wgs;
+    if ((t[i].rows & 31) != 0 || (t[i].cols & (kTileCols - 1)) != 0 || t[i].ld >= kMaxLaneLd || (mx && mx[i].ldc >= kMaxLaneLd)) whole_tiles = false;
     if (fwd) {
       d.p0 = t[i].w; d.p1 = t[i].w_hat; d.p2 = (void*)t[i].bt; d.p3 = t[i].scale;
-      if ((t[i].rows & 31) != 0 || (t[i].cols & (kTileCols - 1)) != 0) whole_tiles = false;
     } else if (fmt == kAbsmaxOnly) {
       d.p0 = t[i].w; d.p1 = nullptr; d.p2 = nullptr; d.p3 = t[i].scale;
     } else {
       d.p0 = t[i].g; d.p1 = (t[i].dw == t[i].g) ? nullptr : t[i].dw; d.p2 = t[i].dbt; d.p3 = t[i].scale;
-      if (d.p1 != nullptr || (t[i].rows & 31) != 0 || (t[i].cols & (kTileCols - 1)) != 0) whole_tiles = false;
+      if (d.p1 != nullptr) whole_tiles = false;
     }
     fill_common(d, t[i], per_x);
     d.p4 = nullptr;
@@ -731,7 +732,7 @@ static int plan_ride(const GemmArgs& g, int w_is_nk, bool gemm_empty, int64_t K,
   uint32_t begin = 0;
   for (int i = 0; i < n_next && n_riding < kMaxRide; ++i) {
     const gws_tensor& t = next[i];
-    if (t.rows == 0 || t.cols == 0 || (t.rows & 31) != 0 || (t.cols & 63) != 0) break;
+    if (t.rows == 0 || t.cols == 0 || (t.rows & 31) != 0 || (t.cols & 63) != 0 || t.ld >= kMaxLaneLd) break;
     const bool wide = (t.cols & 255) == 0 && rider != 0;
     if (!wide && i > 0) break;                                                      // sample_tiles takes one weight
     const double units = (double)(t.rows / 32) * (double)(t.cols / 64);             // wavefront tiles

@@ -48,7 +48,7 @@ template <int FMT, int kDepth = 3>
 __device__ __forceinline__ void sample_tiles(uint32_t step_lo, uint32_t step_hi, const TileDesc& d, uint32_t first,
                                              uint32_t stride, uint32_t lane) {
   const uint32_t per_row = d.cols >> 6, ntiles = (d.rows >> 5) * per_row;
-  const uint32_t gc = lane & 7, r0 = lane >> 3;
+  const uint32_t gc = lane & 7;
   for (uint32_t base = first; base < ntiles; base += kDepth * stride) {
     Tile t[kDepth];
     float bv[kDepth];   // the lane's block parameter, fetched with the tile instead of once the tile is reduced
@@ -57,7 +57,7 @@ __device__ __forceinline__ void sample_tiles(uint32_t step_lo, uint32_t step_hi,
       const uint32_t id = base + j * stride;
       if (id < ntiles) {
         const uint32_t by = id / per_row, cb = (id - by * per_row) * 64;
-        t[j] = load_tile(global_ptr<uint16_t>(d.p0), d, by, cb, cb + gc * 8, r0);
+        t[j] = load_full_tile(global_ptr<uint16_t>(d.p0), d, by, cb, lane);
         bv[j] = global_ptr<float>(d.p2)[(size_t)by * (d.cols >> 5) + (cb >> 5) + (gc >> 2)];
       }
     }
@@ -66,7 +66,9 @@ __device__ __forceinline__ void sample_tiles(uint32_t step_lo, uint32_t step_hi,
       const uint32_t id = base + j * stride;
       if (id < ntiles) {
         const uint32_t by = id / per_row, cb = (id - by * per_row) * 64;
-        fwd_tile<FMT, true, kKeep, false, true>(step_lo, step_hi, d, t[j], by, cb, lane, bv[j]);
+        TileNoise<kBasisBits> n[1];
+        draw_noise(step_lo, step_hi, d, tile_rows(d, by, lane, step_lo), cb, lane, n);
+        fwd_tile<FMT, true, kKeep, false, true>(d, t[j], n[0], by, cb, lane, bv[j]);
       }
     }
   }
@@ -77,7 +79,7 @@ __device__ __forceinline__ void sample_tiles(uint32_t step_lo, uint32_t step_hi,
 // step and the grid's wavefronts take tiles round-robin.  A riding wavefront has its SIMD to itself and the GEMM's
 // register allocation, so it keeps two tiles' worth of loads in flight (the next 32 x 256 tile is fetched before
 // the current one is computed), and since nothing else hides its vector ALU latency the Philox rounds of two
-// wavefront tiles are advanced together (philox_two_tiles) and the four wavefront tiles are straight-line code; the
+// wavefront tiles are advanced together (philox_tiles) and the four wavefront tiles are straight-line code; the
 // row-only rounds are shared by the four.
 template <int FMT>
 __device__ __forceinline__ void ride_tiles(uint32_t step_lo, uint32_t step_hi, const RideList& r, uint32_t first,
@@ -102,7 +104,7 @@ __device__ __forceinline__ void ride_tiles(uint32_t step_lo, uint32_t step_hi, c
     const uint32_t by = local / per_row, cb0 = (local - by * per_row) * 256;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      b.t[j] = load_tile(global_ptr<uint16_t>(d.p0), d, by, cb0 + 64 * j, cb0 + 64 * j + gc * 8, r0);
+      b.t[j] = load_full_tile(global_ptr<uint16_t>(d.p0), d, by, cb0 + 64 * j, lane);
       b.bv[j] = global_ptr<float>(d.p2)[(size_t)by * nbc + ((cb0 + 64 * j) >> 5) + (gc >> 2)];
     }
   };
@@ -116,10 +118,7 @@ __device__ __forceinline__ void ride_tiles(uint32_t step_lo, uint32_t step_hi, c
     const TileDesc& d = r.d[weight_of(id)];
     const uint32_t local = id - d.first_wg, per_row = d.cols >> 8, nbc = d.cols >> 5;
     const uint32_t by = local / per_row, cb0 = (local - by * per_row) * 256;
-    uint32_t rows[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) rows[i] = d.row0 + by * 32 + r0 + 8 * i;
-    const PhiloxRows rp = philox_rows(rows, step_lo, d.seed_lo);
+    const PhiloxRows rp = tile_rows(d, by, lane, step_lo);
     BlockScale bs[4];
     bool unsafe = false;
 #pragma unroll
@@ -127,30 +126,18 @@ __device__ __forceinline__ void ride_tiles(uint32_t step_lo, uint32_t step_hi, c
       bs[j] = tile_scale<FMT, true, false, true, false>(d, cur.t[j], by, cb0 + 64 * j, lane, cur.bv[j]);
       unsafe |= !bs[j].hw_safe;
     }
-    Philox4 bits[4][4];
+    TileNoise<kBasisBits> noise[2][2];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const PhiloxCols pc[2] = {philox_cols(d.cg0 + ((cb0 + 128 * h) >> 3) + gc, step_lo, step_hi, d.seed_lo, d.seed_hi),
-                                philox_cols(d.cg0 + ((cb0 + 128 * h + 64) >> 3) + gc, step_lo, step_hi, d.seed_lo, d.seed_hi)};
-      Philox4 two[2][4];
-      philox_two_tiles(pc, rp, d.seed_lo, d.seed_hi, two);
+    for (int h = 0; h < 2; ++h) draw_noise(step_lo, step_hi, d, rp, cb0 + 128 * h, lane, noise[h]);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        bits[2 * h][i] = two[0][i];
-        bits[2 * h + 1][i] = two[1][i];
-      }
-    }
+    for (int j = 0; j < 4; ++j) tile_sum<true, kBasisBits>(cur.t[j], bs[j], noise[j >> 1][j & 1]);
     // FP8-E4M3: the hardware converters if no block of the four tiles can overflow
     if (FMT == 1 && __builtin_amdgcn_ballot_w64(unsafe) == 0) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        tile_apply<FMT, true, kKeep, false, kBasisBits, FMT == 1>(step_lo, step_hi, d, cur.t[j], bs[j], by, cb0 + 64 * j, lane,
-                                                                   &rp, bits[j]);
+      for (int j = 0; j < 4; ++j) tile_store<FMT, true, kKeep, false, FMT == 1>(d, cur.t[j], bs[j], by, cb0 + 64 * j, lane);
     } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        tile_apply<FMT, true, kKeep, false, kBasisBits, false>(step_lo, step_hi, d, cur.t[j], bs[j], by, cb0 + 64 * j, lane,
-                                                                &rp, bits[j]);
+      for (int j = 0; j < 4; ++j) tile_store<FMT, true, kKeep, false, false>(d, cur.t[j], bs[j], by, cb0 + 64 * j, lane);
     }
     if (writer) {
       GWS_GLOBAL float* sc = global_ptr<float>(d.p3) + (size_t)by * nbc + (cb0 >> 5) + (gc >> 2);

@@ -39,6 +39,10 @@ struct TileDesc {
 };
 static_assert(sizeof(TileDesc) == 96, "descriptor layout");
 
+// Rows (ld in elements, ldc in bytes) whose full tiles the sampling code addresses with 32-bit lane offsets: 7 rows of elements
+// and 31 rows of codes below 2^32 bytes.
+constexpr uint32_t kMaxLaneLd = 1u << 27;
+
 // Streaming (non-temporal) or ordinary accesses of the sampling passes (gws_sample_tile.h, load16).
 constexpr int kKeep = 0, kStreamReads = 1, kStreamAll = 2;
 

@@ -9,9 +9,8 @@
 // (absmax, sum of g.*R) stay inside one wavefront: no LDS, no barrier.
 // A workgroup covers one such 32 x 256 tile in the forward pass and up to four
 // neighbouring column tiles in the lighter backward pass, where the per-wavefront
-// set-up would otherwise show.  Latency is hidden by occupancy: measured on
-// MI355X, keeping the next tile's loads in flight inside a wavefront costs more
-// in registers than it gains.
+// set-up would otherwise show.  Latency is hidden by occupancy, and four wavefronts
+// a SIMD are the right number (GWS_FOUR_WAVES).
 // One Philox4x32-10 call yields the 16 bits x 8 elements of one 16-byte group,
 // so the noise lives only in registers (2 bytes per parameter of HBM traffic per
 // operand, Sec. 3.5; the 0.5 byte per parameter temporary of the paper is gone).
@@ -98,15 +97,14 @@ __device__ __forceinline__ TileDesc locate(const LaunchArgs& a, uint32_t& byg, u
 template <int STREAM, class ARGS, class F>
 __device__ __forceinline__ void walk_tiles(const ARGS& a, const TileDesc& d, uint32_t byg, uint32_t bxg,
                                            F&& body) {
-  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const uint32_t r0 = lane >> 3, gcol = (lane & 7) * 8;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const GWS_GLOBAL uint16_t* __restrict__ src = global_ptr<uint16_t>(d.p0);
   const uint32_t nbr = (d.rows + 31) >> 5, ntx = (d.cols + kTileCols - 1) / kTileCols;
   const uint32_t by0 = byg * a.tiles_per_wg, by_end = min(by0 + a.tiles_per_wg, nbr);
   const uint32_t bx0 = bxg * a.tiles_per_wg_x, bx_end = min(bx0 + a.tiles_per_wg_x, ntx);
   uint32_t by = by0, bx = bx0;
   uint32_t col_base = bx * kTileCols + wave * 64;
-  Tile t = load_tile<STREAM>(src, d, by, col_base, col_base + gcol, r0);
+  Tile t = load_tile<STREAM>(src, d, by, col_base, lane);
   for (;;) {
     if (col_base < d.cols) body(by, col_base, t);
     if (++bx >= bx_end) {
@@ -114,26 +112,34 @@ __device__ __forceinline__ void walk_tiles(const ARGS& a, const TileDesc& d, uin
       if (++by >= by_end) break;
     }
     col_base = bx * kTileCols + wave * 64;
-    t = load_tile<STREAM>(src, d, by, col_base, col_base + gcol, r0);
+    t = load_tile<STREAM>(src, d, by, col_base, lane);
   }
 }
+
+// Exactly four wavefronts a SIMD, whatever the registers would allow.  64 KiB of loads in flight on a compute unit cover the
+// latency of memory, and more tiles under way spread the accesses over more DRAM pages: forward and backward of the 1B model
+// with 8, 7, 6, 5, 4 and 2 wavefronts a SIMD 927, 923, 891, 891, 876 and 1004 us, of the 124M model 87, 87, 85, 85, 83, 95.
+// The registers that this leaves (128) let the compiler interleave a tile's groups: MX-FP6 of 352 M parameters 195 -> 182 us.
+#define GWS_FOUR_WAVES __attribute__((amdgpu_waves_per_eu(4, 4)))
 
 // MX: write element codes and E8M0 block scales instead of the BF16 container.
 // STREAM: see load16.
 // BASIS: the method's bit-built noise, or one of the two comparison bases.
 template <int FMT, bool MX, int STREAM, int BASIS, class ARGS>
-__global__ __launch_bounds__(kThreads) void sample_fwd_kernel(const ARGS a) {
+__global__ __launch_bounds__(kThreads) GWS_FOUR_WAVES void sample_fwd_kernel(const ARGS a) {
   uint32_t byg, bxg;
   const TileDesc d = locate(a, byg, bxg);
   const uint32_t lane = threadIdx.x & 63;
   walk_tiles<STREAM>(a, d, byg, bxg, [&](uint32_t by, uint32_t col_base, Tile& t) {
-    if (t.full) fwd_tile<FMT, true, STREAM, MX, false, BASIS>(a.step_lo, a.step_hi, d, t, by, col_base, lane);
-    else fwd_tile<FMT, false, STREAM, MX, false, BASIS>(a.step_lo, a.step_hi, d, t, by, col_base, lane);
+    TileNoise<BASIS> n[1];
+    draw_noise(a.step_lo, a.step_hi, d, tile_rows(d, by, lane, a.step_lo), col_base, lane, n);
+    if (t.full) fwd_tile<FMT, true, STREAM, MX, false, BASIS>(d, t, n[0], by, col_base, lane);
+    else fwd_tile<FMT, false, STREAM, MX, false, BASIS>(d, t, n[0], by, col_base, lane);
   });
 }
 
-template <bool FULL, bool COPY, int STREAM, int BASIS, class ARGS>
-__device__ __forceinline__ void bwd_tile(const ARGS& a, const TileDesc& d, const Tile& t, uint32_t by,
+template <bool FULL, bool COPY, int STREAM, int BASIS>
+__device__ __forceinline__ void bwd_tile(const TileDesc& d, const Tile& t, const TileNoise<BASIS>& noise, uint32_t by,
                                          uint32_t col_base, uint32_t lane) {
   const uint32_t row_base = by * 32;
   const uint32_t gc = lane & 7, r0 = lane >> 3;
@@ -141,10 +147,9 @@ __device__ __forceinline__ void bwd_tile(const ARGS& a, const TileDesc& d, const
   GWS_GLOBAL uint16_t* __restrict__ dw = global_ptr<uint16_t>(d.p1);
   GWS_GLOBAL float* __restrict__ dbt = global_ptr<float>(d.p2);
   const GWS_GLOBAL float* __restrict__ scale = global_ptr<float>(d.p3);
-  const uint32_t cg = d.cg0 + (col >> 3);
+  const uint32_t off = lane_offset(d.ld, lane);   // full tiles
 
-  // the block's lane that writes the gradient fetches what it needs first, so the
-  // loads are in flight while the noise is regenerated
+  // the block's lane that writes the gradient fetches what it needs first
   const uint32_t nbc = (d.cols + 31) >> 5;
   const uint32_t bcol = (col_base >> 5) + (gc >> 2);
   const bool writer = (FULL || bcol < nbc) && (gc & 3) == 0 && r0 == 0;
@@ -164,18 +169,13 @@ __device__ __forceinline__ void bwd_tile(const ARGS& a, const TileDesc& d, const
     if (!FULL && t.nv[i] == 0) continue;
     const uint32_t row = row_base + r0 + 8 * i;
     if (COPY) {  // dL/dw = dL/dw_hat, bit for bit
-      GWS_GLOBAL uint16_t* dst = dw + (size_t)row * d.ld + col;
-      if (FULL || t.nv[i] == 8) store16<STREAM>(dst, t.v[i]);
-      else store_partial(dst, t.v[i], t.nv[i]);
+      if (FULL) store16<STREAM>(at_byte(dw + ((size_t)(row_base + 8 * i) * d.ld + col_base), off), t.v[i]);
+      else if (t.nv[i] == 8) store16<STREAM>(dw + (size_t)row * d.ld + col, t.v[i]);
+      else store_partial(dw + (size_t)row * d.ld + col, t.v[i], t.nv[i]);
     }
     const u32x4 gv = (FULL || t.nv[i] == 8) ? t.v[i] : mask_group(t.v[i], t.nv[i]);
-    if constexpr (BASIS == kBasisBits) {
-      const Noise n = group_noise(cg, d.row0 + row, a.step_lo, a.step_hi, d.seed_lo, d.seed_hi);
-      acc = dot_group_2r(gv, n, acc);
-    } else {
-      const Philox4 x = philox4x32_10(cg, d.row0 + row, a.step_lo, a.step_hi, d.seed_lo, d.seed_hi);
-      acc = dot_group_basis<BASIS>(gv, x, acc);
-    }
+    if constexpr (BASIS == kBasisBits) acc = dot_group_2r(gv, noise.x[i], acc);
+    else acc = dot_group_basis<BASIS>(gv, noise.x[i], acc);
   }
   acc = block_sum_f32(acc) * (BASIS == kBasisBits ? 0.5f : 1.0f);
 
@@ -194,101 +194,84 @@ __device__ __forceinline__ void bwd_tile(const ARGS& a, const TileDesc& d, const
 }
 
 template <int STREAM, int BASIS, class ARGS>
-__global__ __launch_bounds__(kThreads) void sample_bwd_kernel(const ARGS a) {
+__global__ __launch_bounds__(kThreads) GWS_FOUR_WAVES void sample_bwd_kernel(const ARGS a) {
   uint32_t byg, bxg;
   const TileDesc d = locate(a, byg, bxg);
   const uint32_t lane = threadIdx.x & 63;
   const bool copy = d.p1 != nullptr;  // NULL: the pass-through is an alias
   walk_tiles<STREAM>(a, d, byg, bxg, [&](uint32_t by, uint32_t col_base, Tile& t) {
+    TileNoise<BASIS> n[1];
+    draw_noise(a.step_lo, a.step_hi, d, tile_rows(d, by, lane, a.step_lo), col_base, lane, n);
     if (t.full) {
-      if (copy) bwd_tile<true, true, STREAM, BASIS>(a, d, t, by, col_base, lane);
-      else bwd_tile<true, false, STREAM, BASIS>(a, d, t, by, col_base, lane);
+      if (copy) bwd_tile<true, true, STREAM, BASIS>(d, t, n[0], by, col_base, lane);
+      else bwd_tile<true, false, STREAM, BASIS>(d, t, n[0], by, col_base, lane);
     } else {
-      if (copy) bwd_tile<false, true, STREAM, BASIS>(a, d, t, by, col_base, lane);
-      else bwd_tile<false, false, STREAM, BASIS>(a, d, t, by, col_base, lane);
+      if (copy) bwd_tile<false, true, STREAM, BASIS>(d, t, n[0], by, col_base, lane);
+      else bwd_tile<false, false, STREAM, BASIS>(d, t, n[0], by, col_base, lane);
     }
   });
 }
 
-// The forward pass for tensors of whole tiles only (rows a multiple of 32, columns of 256): a workgroup walks
-// `tiles_per_wg_x` neighbouring column tiles of one block row, straight-line per tile, and keeps the row-only
-// share of its Philox calls across them.
+// The forward pass for tensors of whole tiles only (rows a multiple of 32, columns of 256), one tile a workgroup, straight
+// through: the loads are issued, the noise is drawn while they are in flight (it depends on none of them) and kept as a
+// register a group, the rest follows.
 template <int FMT, bool MX, int STREAM, int BASIS, class ARGS>
-__global__ __launch_bounds__(kThreads) void sample_fwd_full_kernel(const ARGS a) {
+__global__ __launch_bounds__(kThreads) GWS_FOUR_WAVES void sample_fwd_full_kernel(const ARGS a) {
   uint32_t byg, bxg;
   const TileDesc d = locate(a, byg, bxg);
-  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const uint32_t gc = lane & 7, r0 = lane >> 3;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const GWS_GLOBAL uint16_t* __restrict__ src = global_ptr<uint16_t>(d.p0);
-  const uint32_t ntx = d.cols / kTileCols;
-  const uint32_t bx0 = bxg * a.tiles_per_wg_x, bx_end = min(bx0 + a.tiles_per_wg_x, ntx);
-  uint32_t rows[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) rows[i] = d.row0 + byg * 32 + r0 + 8 * i;
-  const PhiloxRows rp = philox_rows(rows, a.step_lo, d.seed_lo);
-  for (uint32_t bx = bx0; bx < bx_end; ++bx) {
-    const uint32_t col_base = bx * kTileCols + wave * 64;
-    Tile t = load_tile<STREAM>(src, d, byg, col_base, col_base + gc * 8, r0);   // always a whole tile here
-    fwd_tile<FMT, true, STREAM, MX, false, BASIS>(a.step_lo, a.step_hi, d, t, byg, col_base, lane, 0.0f, &rp);
-  }
+  const uint32_t col_base = bxg * kTileCols + wave * 64;
+  Tile t = load_full_tile<STREAM>(src, d, byg, col_base, lane);
+  const float bt = *at_byte(global_ptr<float>(d.p2) + ((size_t)byg * (d.cols >> 5) + (col_base >> 5)), lane & 4);
+  TileNoise<BASIS> n[1];
+  draw_noise(a.step_lo, a.step_hi, d, tile_rows(d, byg, lane, a.step_lo), col_base, lane, n);
+  __builtin_amdgcn_sched_barrier(0);   // the noise is drawn while the loads are in flight
+  fwd_tile<FMT, true, STREAM, MX, true, BASIS>(d, t, n[0], byg, col_base, lane, bt);
 }
 
 // The backward pass for the shape the method meets in a model: every tensor of the launch has whole tiles only
 // (rows a multiple of 32, columns of 256) and dL/dw is an alias (nothing to copy).  Straight-line per tile, and
 // the vector ALU work is cut where it can be: the Philox rounds that depend on the row alone are computed once
 // per wavefront and reused for every column tile it walks, those that depend on the column group alone once per
-// tile (288 vector instructions per tile against about 330 in the kernel for any shape).  The next tile's loads
-// are issued after the current tile's arithmetic and complete under the next tile's Philox rounds; issuing them
-// a whole tile ahead was measured slower (16 more registers cost a wavefront of occupancy).
+// tile.  The next tile's loads are issued after the current tile's arithmetic and complete under the next tile's
+// Philox rounds.
 template <int STREAM, int BASIS, class ARGS>
-__global__ __launch_bounds__(kThreads) void sample_bwd_full_kernel(const ARGS a) {
+__global__ __launch_bounds__(kThreads) GWS_FOUR_WAVES void sample_bwd_full_kernel(const ARGS a) {
   uint32_t byg, bxg;
   const TileDesc d = locate(a, byg, bxg);
-  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const uint32_t gc = lane & 7, r0 = lane >> 3;
   const GWS_GLOBAL uint16_t* __restrict__ src = global_ptr<uint16_t>(d.p0);
-  GWS_GLOBAL float* __restrict__ dbt = global_ptr<float>(d.p2);
-  const GWS_GLOBAL float* __restrict__ scale = global_ptr<float>(d.p3);
   const uint32_t ntx = d.cols / kTileCols, nbc = d.cols >> 5;
   const uint32_t by = byg;                                                  // one block row per workgroup
   const uint32_t bx0 = bxg * a.tiles_per_wg_x, bx_end = min(bx0 + a.tiles_per_wg_x, ntx);
-  const uint32_t row_base = by * 32;
   const bool writer = (gc & 3) == 0 && r0 == 0;
+  const PhiloxRows rp = tile_rows(d, by, lane, a.step_lo);
 
-  uint32_t rows[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) rows[i] = d.row0 + row_base + r0 + 8 * i;
-  const PhiloxRows rp = philox_rows(rows, a.step_lo, d.seed_lo);
-
-  const GWS_GLOBAL uint16_t* row_ptr = src + (size_t)(row_base + r0) * d.ld + wave * 64 + gc * 8;
-  const size_t row_step = (size_t)8 * d.ld;
-  u32x4 v[4];
+  Tile t;
   float s32 = 0.0f, bi = 0.0f;
-  auto load4 = [&](uint32_t bx) {
-    const GWS_GLOBAL uint16_t* p = row_ptr + (size_t)bx * kTileCols;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = load16<STREAM>(p + i * row_step);
+  auto block0 = [&](uint32_t bx) { return (size_t)by * nbc + ((bx * kTileCols + wave * 64) >> 5); };   // of the tile's left block
+  auto load = [&](uint32_t bx) {
+    t = load_full_tile<STREAM>(src, d, by, bx * kTileCols + wave * 64, lane);
     if (writer) {   // the block's writer lane fetches what it needs with the tile
-      const size_t blk = (size_t)by * nbc + ((bx * kTileCols + wave * 64) >> 5) + (gc >> 2);
-      s32 = scale[blk];
-      if (d.p4 != nullptr) bi = global_ptr<float>(d.p4)[blk];
+      s32 = *at_byte(global_ptr<float>(d.p3) + block0(bx), gc);   // gc is 0 or 4 here
+      if (d.p4 != nullptr) bi = *at_byte(global_ptr<float>(d.p4) + block0(bx), gc);
     }
   };
-  load4(bx0);
+  load(bx0);
   for (uint32_t bx = bx0; bx < bx_end; ++bx) {
-    const uint32_t col = bx * kTileCols + wave * 64 + gc * 8;
-    const PhiloxCols pc = philox_cols(d.cg0 + (col >> 3), a.step_lo, a.step_hi, d.seed_lo, d.seed_hi);
+    TileNoise<BASIS> n[1];
+    draw_noise(a.step_lo, a.step_hi, d, rp, bx * kTileCols + wave * 64, lane, n);
     // sum_{b_l}(g .* R) as sum(g .* 2R) / 2: exact products, fixed order (see bwd_tile)
     float acc = 0.0f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const Philox4 x = philox_row(pc, rp, i, d.seed_lo, d.seed_hi);
-      if constexpr (BASIS == kBasisBits) acc = dot_group_2r(v[i], noise_planes(x), acc);
-      else acc = dot_group_basis<BASIS>(v[i], x, acc);
+      if constexpr (BASIS == kBasisBits) acc = dot_group_2r(t.v[i], n[0].x[i], acc);
+      else acc = dot_group_basis<BASIS>(t.v[i], n[0].x[i], acc);
     }
     acc = block_sum_f32(acc) * (BASIS == kBasisBits ? 0.5f : 1.0f);
     if (writer) {
-      const size_t blk = (size_t)by * nbc + (col >> 5);
       const float neg_ln2 = __uint_as_float(0xBF317218u);   // -ln 2
       float grad = (neg_ln2 * s32) * acc;                   // dL/db_t, Eq. 4
       if (d.p4 != nullptr) {                                // dL'/db_i, Eq. 11 and Eq. 12 (as in bwd_tile)
@@ -296,16 +279,16 @@ __global__ __launch_bounds__(kThreads) void sample_bwd_full_kernel(const ARGS a)
         const float sgn = btv > d.b_target ? 1.0f : (btv < d.b_target ? -1.0f : 0.0f);
         grad = d.b_delta * (grad + d.lambda_m * sgn);
       }
-      dbt[blk] = grad;
+      *at_byte(global_ptr<float>(d.p2) + block0(bx), gc) = grad;
     }
-    if (bx + 1 < bx_end) load4(bx + 1);
+    if (bx + 1 < bx_end) load(bx + 1);
   }
 }
 
 // The forward kernel's memory traffic without its arithmetic: every tile is loaded and
 // stored back unchanged, same workgroup shape, same loads and stores.  What this kernel
 // reaches is the ceiling the memory system sets for the access pattern.
-__global__ __launch_bounds__(kThreads) void copy_tiles_kernel(const LaunchArgs a) {
+__global__ __launch_bounds__(kThreads) GWS_FOUR_WAVES void copy_tiles_kernel(const LaunchArgs a) {
   uint32_t byg, bxg;
   const TileDesc d = locate(a, byg, bxg);
   const uint32_t lane = threadIdx.x & 63;
@@ -324,7 +307,7 @@ __global__ __launch_bounds__(kThreads) void copy_tiles_kernel(const LaunchArgs a
 // Step one of the forward pass alone: a = max|w| per 32x32 block (exact), written as fp32.
 // Reads every element once and writes 4 bytes per block, the traffic profile of the backward
 // pass: its rate is the ceiling the memory system sets for a read-only pass of this shape.
-__global__ __launch_bounds__(kThreads) void block_absmax_kernel(const LaunchArgs a) {
+__global__ __launch_bounds__(kThreads) GWS_FOUR_WAVES void block_absmax_kernel(const LaunchArgs a) {
   uint32_t byg, bxg;
   const TileDesc d = locate(a, byg, bxg);
   const uint32_t lane = threadIdx.x & 63;

@@ -50,29 +50,95 @@ struct Tile {
   bool full;   // the 32x64 tile lies inside the tensor: no validity tests needed
 };
 
+// A full tile is addressed by a scalar base per group of eight rows and one 32-bit byte offset of the lane for all of them
+// (15 of 454 vector instructions of a BF16 tile were 64-bit address additions); tensors with longer rows go tile by tile as
+// edges do, with 64-bit addresses (kMaxLaneLd).
+__device__ __forceinline__ uint32_t lane_offset(uint32_t ld, uint32_t lane) { return ((lane >> 3) * ld + (lane & 7) * 8) * 2; }
+
+// A uniform pointer plus the lane's bytes.  The empty asm statement keeps the compiler from adding the lane's share first and
+// the scalar one to each row's address in vector registers, and from widening the lane's share ahead of time.
+template <class T>
+__device__ __forceinline__ GWS_GLOBAL T* at_byte(GWS_GLOBAL T* p, uint32_t byte) {
+  uint64_t base = (uint64_t)(uintptr_t)p;
+  asm("" : "+s"(base), "+v"(byte));
+  return (GWS_GLOBAL T*)((GWS_GLOBAL char*)(uintptr_t)base + byte);
+}
+
+template <int STREAM = kStreamAll>
+__device__ __forceinline__ Tile load_full_tile(const GWS_GLOBAL uint16_t* __restrict__ src, const TileDesc& d, uint32_t by,
+                                               uint32_t col_base, uint32_t lane) {
+  Tile t;
+  t.full = true;
+  const uint32_t off = lane_offset(d.ld, lane);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    t.nv[i] = 8;
+    t.v[i] = load16<STREAM>(at_byte(src + ((size_t)(by * 32 + 8 * i) * d.ld + col_base), off));
+  }
+  return t;
+}
+
 // A 16-byte load never leaves its row: ld % 8 == 0 and ld >= cols.
 template <int STREAM = kStreamAll>
 __device__ __forceinline__ Tile load_tile(const GWS_GLOBAL uint16_t* __restrict__ src, const TileDesc& d, uint32_t by,
-                                          uint32_t col_base, uint32_t col, uint32_t r0) {
+                                          uint32_t col_base, uint32_t lane) {
+  const uint32_t row_base = by * 32, col = col_base + (lane & 7) * 8;
+  if (row_base + 32 <= d.rows && col_base + 64 <= d.cols && d.ld < kMaxLaneLd && d.ldc < kMaxLaneLd)
+    return load_full_tile<STREAM>(src, d, by, col_base, lane);
   Tile t;
-  const uint32_t row_base = by * 32;
-  t.full = (row_base + 32 <= d.rows) && (col_base + 64 <= d.cols);
-  if (t.full) {
+  t.full = false;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      t.nv[i] = 8;
-      t.v[i] = load16<STREAM>(src + (size_t)(row_base + r0 + 8 * i) * d.ld + col);
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t row = row_base + r0 + 8 * i;
-      t.nv[i] = valid_count(row, col, d.rows, d.cols);
-      t.v[i] = u32x4{0, 0, 0, 0};
-      if (t.nv[i] > 0) t.v[i] = load16<STREAM>(src + (size_t)row * d.ld + col);
-    }
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t row = row_base + (lane >> 3) + 8 * i;
+    t.nv[i] = valid_count(row, col, d.rows, d.cols);
+    t.v[i] = u32x4{0, 0, 0, 0};
+    if (t.nv[i] > 0) t.v[i] = load16<STREAM>(src + (size_t)row * d.ld + col);
   }
   return t;
+}
+
+// What the noise of a lane's four groups is kept as until it is applied: the bit basis as codes (a register a group), the
+// comparison bases as the random words.  It depends on no load, so it is drawn while the tile is on its way.
+template <int BASIS>
+struct TileNoise {
+  Philox4 x[4];
+};
+template <>
+struct TileNoise<kBasisBits> {
+  Noise x[4];
+};
+
+__device__ __forceinline__ PhiloxRows tile_rows(const TileDesc& d, uint32_t by, uint32_t lane, uint32_t step_lo) {
+  uint32_t rows[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) rows[i] = d.row0 + by * 32 + (lane >> 3) + 8 * i;
+  return philox_rows(rows, step_lo, d.seed_lo);
+}
+
+// T tiles of one block row, 64 columns apart from col_base on
+template <int BASIS, int T>
+__device__ __forceinline__ void draw_noise(uint32_t step_lo, uint32_t step_hi, const TileDesc& d, const PhiloxRows& rp,
+                                           uint32_t col_base, uint32_t lane, TileNoise<BASIS> (&n)[T]) {
+  PhiloxCols pc[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) pc[t] = philox_cols(d.cg0 + ((col_base + 64 * t) >> 3) + (lane & 7), step_lo, step_hi, d.seed_lo, d.seed_hi);
+  Philox4 x[T][4];
+  philox_tiles(pc, rp, d.seed_lo, d.seed_hi, x);
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (BASIS == kBasisBits) n[t].x[i] = noise_codes(x[t][i]);
+      else n[t].x[i] = x[t][i];
+    }
+  // here and now: the compiler would sink the noise to its use, behind the wait for the tile
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (BASIS == kBasisBits) asm volatile("" : "+v"(n[t].x[i].c));
+      else asm volatile("" : "+v"(n[t].x[i].x0), "+v"(n[t].x[i].x1), "+v"(n[t].x[i].x2), "+v"(n[t].x[i].x3));
+    }
 }
 
 // Element codes of one group to memory.  FP8: 8 bytes at column col.  FP6: 6 bytes at
@@ -112,7 +178,7 @@ __device__ __forceinline__ void store_codes(GWS_GLOBAL uint8_t* row, uint32_t co
 // The FP6 codes of a whole tile whose rows of codes are 4-byte aligned.  A lane holds 48 bits of each of its four rows
 // r0 + 8 i; within each quad of lanes (four column groups side by side) the 4 x 4 pieces are exchanged, so that a lane
 // ends up with the 24 consecutive bytes of one row (row r0 + 8 (lane % 4)) and writes them with two stores instead of
-// twelve: 352 M parameters 219 -> 217 us (the vector ALU, not the stores, bounds the pass).
+// twelve.
 __device__ __forceinline__ void store_codes_fp6_quad(GWS_GLOBAL uint8_t* tile_row0, uint32_t ldc, uint32_t lane,
                                                      const uint32_t (&c)[6]) {
   typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -142,36 +208,35 @@ __device__ __forceinline__ void store_codes_fp6_quad(GWS_GLOBAL uint8_t* tile_ro
   const uint32_t sel = odd ? 0x07060302u : 0x05040100u;
   const uint32_t g01 = odd ? __builtin_amdgcn_perm(first, pf, sel) : __builtin_amdgcn_perm(pf, first, sel);
   const uint32_t g23 = odd ? __builtin_amdgcn_perm(second, ps, sel) : __builtin_amdgcn_perm(ps, second, sel);
-  GWS_GLOBAL uint8_t* dst = tile_row0 + (size_t)((lane >> 3) + 8 * (lane & 3)) * ldc + (lane & 4) * 6;
+  GWS_GLOBAL uint8_t* dst = at_byte(tile_row0, ((lane >> 3) + 8 * (lane & 3)) * ldc + (lane & 4) * 6);
   typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
   typedef uint32_t u32x2a4 __attribute__((ext_vector_type(2), aligned(4)));
   *(GWS_GLOBAL u32x4a4*)dst = u32x4{l[0], __builtin_amdgcn_perm(l[1], g01, 0x05040100u), __builtin_amdgcn_perm(g01, l[1], 0x07060302u), l[2]};
   *(GWS_GLOBAL u32x2a4*)(dst + 16) = u32x2{__builtin_amdgcn_perm(l[3], g23, 0x05040100u), __builtin_amdgcn_perm(g23, l[3], 0x07060302u)};
 }
 
-// The forward pass on one wavefront tile, in two phases.
+// The forward pass on one wavefront tile, in three phases.
 //
 // tile_scale: a = max|w| of the lane's block (exact), the block's scale and cast constants.
-//   BT_PRE: the caller has already fetched this lane's block parameter (bt_pre), as a wavefront that works
-//   through several tiles alone does together with the tile loads, so that its latency is not paid per tile.
+//   BT_PRE: the caller has already fetched this lane's block parameter (bt_pre), together with the tile.
 //   STORE: the block's writer lane stores scale (and, MX, the E8M0 block scale) here; off, the caller does.
-// tile_apply: noise, add, round, cast, store.
+// tile_sum: noise times scale added, rounded to BF16 (the tile's registers are overwritten with the sums).
+//   n: the noise of the tile (draw_noise).
+// tile_store: cast, store.
 //   STREAM: see load16.
 //   MX: the output is element codes (p1, row stride ldc) and E8M0 block scales (p4) instead of the BF16 container.
 //   BASIS: kBasisBits is the method's noise (Sec. 3.4); the other two are the comparison bases (no MX form).
 //   USE_HW: FP8-E4M3 through the hardware converters (the caller has shown that no block of the wavefront can
 //   overflow); off, the arithmetic cast.  Same bits either way where both apply.
-//   rows_part: the row-only share of the lane's four Philox calls, when the caller keeps it across column tiles
-//   (philox_rows of the rows d.row0 + 32 by + lane / 8 + 8 i); bits: the four calls' results themselves, when
-//   the caller has them already; both NULL: every call is computed on its own.
-// Neither phase branches when FULL and !STORE, so a caller that works on several tiles at once gets straight-line
+// No phase branches when FULL and !STORE, so a caller that works on several tiles at once gets straight-line
 // code it can interleave.
 template <int FMT, bool FULL, bool MX, bool BT_PRE, bool STORE>
 __device__ __forceinline__ BlockScale tile_scale(const TileDesc& d, Tile& t, uint32_t by, uint32_t col_base, uint32_t lane,
                                                  float bt_pre) {
   const uint32_t gc = lane & 7, r0 = lane >> 3;
-  const GWS_GLOBAL float* __restrict__ bt = global_ptr<float>(d.p2);
-  GWS_GLOBAL float* __restrict__ scale = global_ptr<float>(d.p3);
+  const uint32_t nbc = (d.cols + 31) >> 5;
+  const size_t blk0 = (size_t)by * nbc + (col_base >> 5);   // of the left block
+  const GWS_GLOBAL float* __restrict__ bt = global_ptr<float>(d.p2) + blk0;
   if (!FULL) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -184,98 +249,82 @@ __device__ __forceinline__ BlockScale tile_scale(const TileDesc& d, Tile& t, uin
   m = max(m & 0xFFFFu, m >> 16);
   const uint32_t a16 = block_max_u32(m);
   // ---- per-block scale ----
-  const uint32_t nbc = (d.cols + 31) >> 5;
-  const uint32_t bcol = (col_base >> 5) + (gc >> 2);
-  const bool block_exists = FULL || bcol < nbc;
-  const float bv = BT_PRE ? bt_pre : (block_exists ? bt[(size_t)by * nbc + bcol] : 0.0f);
+  const bool block_exists = FULL || (col_base >> 5) + (gc >> 2) < nbc;
+  const float bv = BT_PRE ? bt_pre : (block_exists ? bt[gc >> 2] : 0.0f);
   // Eq. 11 (the product and the sum rounded separately); identity for a plain b_t
   const float btv = __fadd_rn(d.b_target, __fmul_rn(bv, d.b_delta));
   BlockScale b = block_scale(a16, btv);
   if (FMT == 1) cast_constants<8, -6>(a16, b);
   if (FMT == 2) cast_constants<4, -2>(a16, b);
   if (STORE && block_exists && (gc & 3) == 0 && r0 == 0) {
-    scale[(size_t)by * nbc + bcol] = b.s32;
+    *at_byte(global_ptr<float>(d.p3) + blk0, gc) = b.s32;   // gc is 0 or 4 here
     // shared exponent of the block: biased exponent of X; X = 1 for an all-zero block
-    if (MX) global_ptr<uint8_t>(d.p4)[(size_t)by * nbc + bcol] = a16 ? (uint8_t)(__float_as_uint(b.x_scale) >> 23) : (uint8_t)127;
+    if (MX) *at_byte(global_ptr<uint8_t>(d.p4) + blk0, gc >> 2) = a16 ? (uint8_t)(__float_as_uint(b.x_scale) >> 23) : (uint8_t)127;
   }
   return b;
 }
 
-template <int FMT, bool FULL, int STREAM, bool MX, int BASIS, bool USE_HW>
-__device__ __forceinline__ void tile_apply(uint32_t step_lo, uint32_t step_hi, const TileDesc& d, const Tile& t,
-                                           const BlockScale& b, uint32_t by, uint32_t col_base, uint32_t lane,
-                                           const PhiloxRows* rows_part, const Philox4* bits) {
-  static_assert(BASIS == kBasisBits || !MX, "the comparison bases have no MX output");
-  static_assert(!USE_HW || FMT == 1, "hardware converters by choice exist for FP8-E4M3 only");
-  const uint32_t row_base = by * 32;
-  const uint32_t gc = lane & 7, r0 = lane >> 3;
-  const uint32_t col = col_base + gc * 8;
-  GWS_GLOBAL uint16_t* __restrict__ w_hat = global_ptr<uint16_t>(d.p1);
-  const uint32_t cg = d.cg0 + (col >> 3);
-  PhiloxCols pc = {};
-  if (bits == nullptr && rows_part != nullptr) pc = philox_cols(cg, step_lo, step_hi, d.seed_lo, d.seed_hi);
-  auto bits_of = [&](uint32_t row, int i) {   // the 128 bits of the lane's group i (row = its global row)
-    return bits != nullptr         ? bits[i]
-           : rows_part != nullptr ? philox_row(pc, *rows_part, i, d.seed_lo, d.seed_hi)
-                                   : philox4x32_10(cg, row, step_lo, step_hi, d.seed_lo, d.seed_hi);
-  };
-  // the four BF16 sums of group i (before the cast), whatever the basis
-  auto sampled_group = [&](const u32x4 w, uint32_t row, int i, uint32_t (&pk)[4]) {
+template <bool FULL, int BASIS>
+__device__ __forceinline__ void tile_sum(Tile& t, const BlockScale& b, const TileNoise<BASIS>& n) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (!FULL && t.nv[i] == 0) continue;
+    const u32x4 w = t.v[i];
+    uint32_t pk[4];
     if constexpr (BASIS == kBasisBits) {
-      const Noise n = noise_planes(bits_of(row, i));
-      const GroupR g = group_r(n);
+      const GroupR g = group_r(n.x[i]);
       pk[0] = sampled_pair<0>(w[0], g, b);
       pk[1] = sampled_pair<1>(w[1], g, b);
       pk[2] = sampled_pair<2>(w[2], g, b);
       pk[3] = sampled_pair<3>(w[3], g, b);
     } else {
-      sampled_group_basis<BASIS>(w, bits_of(row, i), b, pk);
+      sampled_group_basis<BASIS>(w, n.x[i], b, pk);
     }
+    t.v[i] = u32x4{pk[0], pk[1], pk[2], pk[3]};
+  }
+}
+
+template <int FMT, bool FULL, int STREAM, bool MX, bool USE_HW>
+__device__ __forceinline__ void tile_store(const TileDesc& d, const Tile& t, const BlockScale& b, uint32_t by, uint32_t col_base,
+                                           uint32_t lane) {
+  static_assert(!USE_HW || FMT == 1, "hardware converters by choice exist for FP8-E4M3 only");
+  const uint32_t row_base = by * 32;
+  const uint32_t gc = lane & 7, r0 = lane >> 3;
+  const uint32_t col = col_base + gc * 8;
+  GWS_GLOBAL uint16_t* __restrict__ w_hat = global_ptr<uint16_t>(d.p1);
+  const uint32_t off = lane_offset(d.ld, lane);   // full tiles
+  auto store_group = [&](int i, const u32x4& o) {
+    if (FULL) store16<STREAM>(at_byte(w_hat + ((size_t)(row_base + 8 * i) * d.ld + col_base), off), o);
+    else if (t.nv[i] == 8) store16<STREAM>(w_hat + (size_t)(row_base + r0 + 8 * i) * d.ld + col, o);
+    else store_partial(w_hat + (size_t)(row_base + r0 + 8 * i) * d.ld + col, o, t.nv[i]);
   };
   if constexpr (FMT != 2) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       if (!FULL && t.nv[i] == 0) continue;
-      const uint32_t row = row_base + r0 + 8 * i;
+      const uint32_t pk[4] = {t.v[i][0], t.v[i][1], t.v[i][2], t.v[i][3]};
       if constexpr (MX) {
-        const Noise n = noise_planes(bits_of(d.row0 + row, i));
-        const MxCodes c = sample_group_mx_fp8(t.v[i], n, b, USE_HW);
-        store_codes<FMT, STREAM>(global_ptr<uint8_t>(d.p1) + (size_t)row * d.ldc, col, c, FULL ? 8 : t.nv[i]);
+        const MxCodes c = mx_fp8_codes(pk, b, USE_HW);
+        if (FULL) store_codes<FMT, STREAM>(at_byte(global_ptr<uint8_t>(d.p1) + ((size_t)(row_base + 8 * i) * d.ldc + col_base), r0 * d.ldc + gc * 8), 0, c, 8);
+        else store_codes<FMT, STREAM>(global_ptr<uint8_t>(d.p1) + (size_t)(row_base + r0 + 8 * i) * d.ldc, col, c, t.nv[i]);
       } else {
-        uint32_t pk[4];
-        sampled_group(t.v[i], d.row0 + row, i, pk);
         i16x2 chain = {0, 0};
-        const u32x4 o = {cast_pair<FMT>(pk[0], b, USE_HW, chain), cast_pair<FMT>(pk[1], b, USE_HW, chain),
-                         cast_pair<FMT>(pk[2], b, USE_HW, chain), cast_pair<FMT>(pk[3], b, USE_HW, chain)};
-        GWS_GLOBAL uint16_t* dst = w_hat + (size_t)row * d.ld + col;
-        if (FULL || t.nv[i] == 8) {
-          store16<STREAM>(dst, o);
-        } else {
-          store_partial(dst, o, t.nv[i]);
-        }
+        store_group(i, u32x4{cast_pair<FMT>(pk[0], b, USE_HW, chain), cast_pair<FMT>(pk[1], b, USE_HW, chain),
+                             cast_pair<FMT>(pk[2], b, USE_HW, chain), cast_pair<FMT>(pk[3], b, USE_HW, chain)});
       }
-    }
+      }
   } else {
     // FP6-E3M2: the 32-wide hardware converters (v_cvt_scalef32_pk32_bf6_bf16 and back) take
     // a lane's whole tile at once, round to nearest even with gradual underflow and saturate
     // at 28 * X (checked against the cast's definition on every finite BF16 input at several
-    // scales), so all four groups are sampled first and converted together.
+    // scales).
     typedef __bf16 bf16x32 __attribute__((ext_vector_type(32)));
     typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
     uint32_t pk[16];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (!FULL && t.nv[i] == 0) {
-        pk[4 * i] = pk[4 * i + 1] = pk[4 * i + 2] = pk[4 * i + 3] = 0;
-        continue;
-      }
-      uint32_t p4[4];
-      sampled_group(t.v[i], d.row0 + row_base + r0 + 8 * i, i, p4);
-      pk[4 * i] = p4[0];
-      pk[4 * i + 1] = p4[1];
-      pk[4 * i + 2] = p4[2];
-      pk[4 * i + 3] = p4[3];
-    }
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) pk[4 * i + k] = !FULL && t.nv[i] == 0 ? 0 : t.v[i][k];
     bf16x32 v;
     __builtin_memcpy(&v, pk, 64);
     const u32x6 c = __builtin_amdgcn_cvt_scalef32_pk32_bf6_bf16(v, b.x_scale);
@@ -301,33 +350,25 @@ __device__ __forceinline__ void tile_apply(uint32_t step_lo, uint32_t step_hi, c
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         if (!FULL && t.nv[i] == 0) continue;
-        const uint32_t row = row_base + r0 + 8 * i;
-        const u32x4 og = {o[4 * i], o[4 * i + 1], o[4 * i + 2], o[4 * i + 3]};
-        GWS_GLOBAL uint16_t* dst = w_hat + (size_t)row * d.ld + col;
-        if (FULL || t.nv[i] == 8) {
-          store16<STREAM>(dst, og);
-        } else {
-          store_partial(dst, og, t.nv[i]);
-        }
+        store_group(i, u32x4{o[4 * i], o[4 * i + 1], o[4 * i + 2], o[4 * i + 3]});
       }
     }
   }
 }
 
-// Both phases for one tile; FP8-E4M3 takes the hardware converters only if neither block of this wavefront can
+// The phases for one tile; FP8-E4M3 takes the hardware converters only if neither block of this wavefront can
 // overflow (they give NaN where the cast saturates).
 template <int FMT, bool FULL, int STREAM = kStreamAll, bool MX = false, bool BT_PRE = false, int BASIS = kBasisBits>
-__device__ __forceinline__ void fwd_tile(uint32_t step_lo, uint32_t step_hi, const TileDesc& d, Tile& t,
-                                         uint32_t by, uint32_t col_base, uint32_t lane, float bt_pre = 0.0f,
-                                         const PhiloxRows* rows_part = nullptr) {
+__device__ __forceinline__ void fwd_tile(const TileDesc& d, Tile& t, const TileNoise<BASIS>& n, uint32_t by, uint32_t col_base,
+                                         uint32_t lane, float bt_pre = 0.0f) {
+  static_assert(BASIS == kBasisBits || !MX, "the comparison bases have no MX output");
   const BlockScale b = tile_scale<FMT, FULL, MX, BT_PRE, true>(d, t, by, col_base, lane, bt_pre);
+  tile_sum<FULL, BASIS>(t, b, n);
   if constexpr (FMT == 1) {
-    if (__builtin_amdgcn_ballot_w64(!b.hw_safe) == 0)
-      tile_apply<FMT, FULL, STREAM, MX, BASIS, true>(step_lo, step_hi, d, t, b, by, col_base, lane, rows_part, nullptr);
-    else
-      tile_apply<FMT, FULL, STREAM, MX, BASIS, false>(step_lo, step_hi, d, t, b, by, col_base, lane, rows_part, nullptr);
+    if (__builtin_amdgcn_ballot_w64(!b.hw_safe) == 0) tile_store<FMT, FULL, STREAM, MX, true>(d, t, b, by, col_base, lane);
+    else tile_store<FMT, FULL, STREAM, MX, false>(d, t, b, by, col_base, lane);
   } else {
-    tile_apply<FMT, FULL, STREAM, MX, BASIS, false>(step_lo, step_hi, d, t, b, by, col_base, lane, rows_part, nullptr);
+    tile_store<FMT, FULL, STREAM, MX, false>(d, t, b, by, col_base, lane);
   }
 }
 

@@ -339,3 +339,25 @@ def test_large_calls_give_the_bytes_of_small_ones():
         for x, y in zip(a, b):
             assert torch.equal(x.w_hat.view(torch.int16), y.w_hat.view(torch.int16)) and torch.equal(x.scale, y.scale)
             assert torch.equal(x.dw[:, :4100].view(torch.int16), x.g[:, :4100].view(torch.int16)) and torch.equal(x.dbt, y.dbt)
+
+
+def test_rows_longer_than_the_lane_offsets_reach():
+    """Full tiles are addressed by 32-bit lane offsets where ld < 2^27; longer rows go the way of the edges, same bits."""
+    ld, rows, cols, step = 1 << 27, 40, 512, 5
+    t = synth.make_tensor(1700, rows, cols, device=DEV)
+    far = {k: torch.empty(rows * ld, dtype=torch.bfloat16, device=DEV).view(rows, ld) for k in ("w", "w_hat")}
+    far["w"][:, :cols] = t["w"]
+    nb = synth.n_blocks(rows, cols)
+    out = []
+    for w, w_hat, g in ((t["w"], torch.zeros_like(t["w"]), t["g"]), (far["w"], far["w_hat"], None)):
+        d = gws.TensorDesc(rows=rows, cols=cols, ld=w.stride(0), seed=3, w=w, w_hat=w_hat, bt=t["bt"], scale=torch.zeros(*nb, device=DEV))
+        gws.gws_sample_fwd([d], gws.FMT_FP8_E4M3, step)
+        if g is None:
+            far["w"][:, :cols] = t["g"]
+            g = far["w"]
+        d.g, d.dw, d.dbt = g, g, torch.zeros(*nb, device=DEV)
+        gws.gws_sample_bwd([d], step)
+        torch.cuda.synchronize()
+        out.append([w_hat[:, :cols].contiguous().view(torch.int16), d.scale.view(torch.int32), d.dbt.view(torch.int32)])
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
