@@ -25,10 +25,11 @@ EXPORTS = ("gws_sample_fwd", "gws_sample_bwd", "gws_sample_fwd_bi", "gws_sample_
            "gws_sample_fwd_basis", "gws_sample_bwd_basis", "gws_noise_basis",
            "gws_derive_seed", "gws_status_string", "gws_version")
 BENCH_EXPORTS = ("gws_copy_tiles", "gws_block_absmax", "gws_sample_bwd_tuned", "gws_sample_fwd_tuned", "gws_gemm_bf16_ride_probe", "gws_ride_plan",
-                 "gws_ride_plan_layout", "gws_gemm_form", "gws_linear_bwd_w_form", "gws_box_muller_check")
+                 "gws_ride_plan_layout", "gws_gemm_form", "gws_linear_bwd_w_form", "gws_linear_bwd_w_form_rows", "gws_box_muller_check")
 # kernels as gws_gemm_form and gws_linear_bwd_w_form name them
 GEMM_STREAM, GEMM_MIDDLE, GEMM_LARGE, GEMM_LARGE_EDGE, GEMM_NARROW, GEMM_ANY_SHAPE, GEMM_STREAM_SAMPLE, GEMM_ROWS_SAMPLE, GEMM_ANY_SHAPE_SAMPLE = range(1, 10)
 BWD_W_WIDE, BWD_W_NARROW, BWD_W_PIECES_64, BWD_W_PIECES_128, BWD_W_SPLIT = 1, 2, 3, 4, 16
+BWD_W_PIECES_96, BWD_W_PIECES_128_128, BWD_W_PIECES_32 = 5, 6, 7
 
 
 class GwsError(RuntimeError):
@@ -143,6 +144,8 @@ def load_library() -> ctypes.CDLL:
     L.gws_gemm_form.restype = ci
     L.gws_linear_bwd_w_form.argtypes = [tp, i64, ctypes.c_size_t]
     L.gws_linear_bwd_w_form.restype = ci
+    L.gws_linear_bwd_w_form_rows.argtypes = [tp, i64, ctypes.c_size_t, ci]
+    L.gws_linear_bwd_w_form_rows.restype = ci
     L.gws_box_muller_check.argtypes = [u64, u64, vp, vp]
     L.gws_box_muller_check.restype = ci
     L.gws_gemm_bf16_ride_probe.argtypes = [vp, i64, i64, i64, vp, i64, i64, ci, vp, i64, tp, ci, u64, ci, ci, vp]
@@ -448,9 +451,10 @@ def gws_gemm_form(M: int, K: int, N: int, w_is_nk: bool = False, sampled: int = 
                                             int(bool(w_is_nk)), int(sampled)))
 
 
-def gws_linear_bwd_w_form(w: TensorDesc, M: int, workspace_bytes: int = 0) -> int:
-    """The form (``BWD_W_*``) that ``gws_linear_bwd_w_ws`` takes with that much workspace; ``BWD_W_SPLIT`` plus the number of parts."""
-    return int(load_library().gws_linear_bwd_w_form(_marshal([w]), int(M), int(workspace_bytes)))
+def gws_linear_bwd_w_form(w: TensorDesc, M: int, workspace_bytes: int = 0, on_lines: bool = False) -> int:
+    """The form (``BWD_W_*``) that ``gws_linear_bwd_w_ws`` takes with that much workspace; ``BWD_W_SPLIT`` plus the number of parts.
+    ``on_lines``: every row of X, dY and dW starts on a 128-byte line."""
+    return int(load_library().gws_linear_bwd_w_form_rows(_marshal([w]), int(M), int(workspace_bytes), int(on_lines)))
 
 
 def gws_gemm_bf16_ride_probe(x, w, y, nxt: TensorDesc, fmt: int, step: int, extra_workgroups: int, rider: int = 1,

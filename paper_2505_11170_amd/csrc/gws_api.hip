@@ -601,18 +601,20 @@ static uint32_t parts_within(const GemmArgs& g, size_t workspace_bytes, int cus)
 //  - With workspace: the tokens of a tile split over that many workgroups, or small pieces of the gradient with the tokens in
 //    four sums or (parts > 4) eight.
 //  - Without (parts < 2): one workgroup per tile of 256 x 256 or of 256 x 192, or small pieces.
-// Fitted to MI355X timings; in parts and in small pieces, tokens x rows x cols: 4096 x 768 x 3072 40 and 50, 4096 x 768 x 2304
-// 35 and 29, 4096 x 2048 x 2048 50 and 53, 2048 x 2048 x 2048 42 and 34, 8192 x 512 x 512 29 and 32, 2048 x 1024 x 1024 26 and
-// 12, 1024 x 2048 x 4096 39 and 44.
-static int bwd_w_form(const GemmArgs& g, uint32_t parts, TnPlan& small) {
-  small = stream_tn_plan(g, parts > 4);
-  const int pieces = small.mt == 4 ? GWS_BWD_W_PIECES_64 : GWS_BWD_W_PIECES_128;
-  const double nk = (double)(g.K / 64);
+// Fitted to MI355X timings; in parts and in small pieces, tokens x rows x cols: 4096 x 768 x 3072 42 and 30, 4096 x 768 x 2304
+// 35 and 27, 8192 x 2048 x 2048 75 and 68, 2048 x 2048 x 2048 41 and 26, 8192 x 512 x 512 29 and 29, 8192 x 1024 x 1024 37 and
+// 37, 2048 x 1024 x 1024 25 and 13, 1024 x 2048 x 4096 40 and 34 (a K-step of a part: 1.05 to 1.38 with all compute units at work).
+// lines: see stream_tn_plan.
+static int bwd_w_form(const GemmArgs& g, uint32_t parts, bool lines, TnPlan& small) {
+  small = stream_tn_plan(g, lines, parts > 4);
+  const int pieces = small.nt == 2 ? GWS_BWD_W_PIECES_32 : small.nt == 6 ? GWS_BWD_W_PIECES_96 : small.nt == 8 ? GWS_BWD_W_PIECES_128_128
+                     : small.mt == 4 ? GWS_BWD_W_PIECES_64 : GWS_BWD_W_PIECES_128;
+  const double nk = (double)(g.K / 64), cus = compute_units() > 0 ? compute_units() : 256;
   if (parts >= 2) {
-    const double split_us = 9.0 + nk / parts * 1.15 + (double)gemm256_tn_split_bytes(g, parts) * 0.317e-6;
+    const double busy = fmin(1.0, (double)parts * (g.M / 256) * (g.N / 256) / cus);
+    const double split_us = 9.0 + nk / parts * (1.0 + 0.33 * busy) + (double)gemm256_tn_split_bytes(g, parts) * 0.317e-6;
     return small.us < split_us ? pieces : GWS_BWD_W_SPLIT;
   }
-  const double cus = compute_units() > 0 ? compute_units() : 256;
   // Fixed: a launch, and with the tiles in flight the stores and the noise on the way out; the narrow tile's way out is by
   // blocks.  Wide and narrow, us: 2048 x 4096 over 64 tokens 14.1 and 15.5, 448 21.3 and 21.6, 960 30.4 and 28.8; 2048 x 5632
   // over 192 tokens 15.9 and 17.0, 640 24.2 and 24.2, 8192 188 and 163; 4096 x 4096 (one round and two) over 960 32.8 and 53.5.
@@ -628,7 +630,8 @@ static int bwd_w_form(const GemmArgs& g, uint32_t parts, TnPlan& small) {
 
 static int launch_bwd_w(const GemmArgs& g, bool with_dbt, uint32_t parts, void* workspace, hipStream_t stream) {
   TnPlan small;
-  switch (bwd_w_form(g, parts, small)) {
+  const bool lines = ((g.ldx | g.ldw | g.ldy) & 63) == 0 && aligned(g.x, 128) && aligned(g.w, 128) && aligned(g.y, 128);
+  switch (bwd_w_form(g, parts, lines, small)) {
     case GWS_BWD_W_WIDE: return launch_gemm256_tn(g, with_dbt, stream);
     case GWS_BWD_W_NARROW: return launch_gemm256_tn_narrow(g, with_dbt, stream);
     case GWS_BWD_W_SPLIT: return launch_gemm256_tn_split(g, with_dbt, (float*)workspace, parts, stream);
@@ -664,7 +667,7 @@ int gws_linear_bwd_w_ws(const void* x, const void* dy, int64_t M, int64_t ldx, i
   return launch_bwd_w(g, w->dbt != nullptr, parts, workspace, (hipStream_t)stream);
 }
 
-int gws_linear_bwd_w_form(const gws_tensor* w, int64_t M, size_t workspace_bytes) {
+int gws_linear_bwd_w_form_rows(const gws_tensor* w, int64_t M, size_t workspace_bytes, int on_lines) {
   if (!w || w->rows <= 0 || w->cols <= 0 || (w->rows & 255) != 0 || (w->cols & 255) != 0 || M <= 0 || (M & 63) != 0 ||
       w->rows >= (int64_t)1 << 31 || w->cols >= (int64_t)1 << 31 || M >= (int64_t)1 << 31) return 0;
   GemmArgs g;
@@ -672,8 +675,12 @@ int gws_linear_bwd_w_form(const gws_tensor* w, int64_t M, size_t workspace_bytes
   g.M = (uint32_t)w->rows; g.N = (uint32_t)w->cols; g.K = (uint32_t)M;
   const uint32_t parts = parts_within(g, workspace_bytes, compute_units() > 0 ? compute_units() : 256);
   TnPlan small;
-  const int form = bwd_w_form(g, parts, small);
+  const int form = bwd_w_form(g, parts, on_lines != 0, small);
   return form == GWS_BWD_W_SPLIT ? form + (int)parts : form;
+}
+
+int gws_linear_bwd_w_form(const gws_tensor* w, int64_t M, size_t workspace_bytes) {
+  return gws_linear_bwd_w_form_rows(w, M, workspace_bytes, 0);
 }
 
 int gws_gemm_form(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled) {

@@ -22,12 +22,12 @@ __device__ __forceinline__ void direct(const GWS_GLOBAL char* base, uint32_t vof
 }
 
 // Slot of a 16-byte chunk of k-row k in a stage stored output-contiguous, 16 T outputs wide: chunk ^ swizzle.  The 32 lanes
-// that a transposing read serves together take four rows k % 4 of two row groups k / 8; with 256, 128 and 64 bytes a row
+// that a transposing read serves together take four rows k % 4 of two row groups k / 8; with 256, 192, 128 and 64 bytes a row
 // this puts them on different banks.
 template <int T>
 __device__ __forceinline__ uint32_t oc_swizzle(uint32_t k) {
-  static_assert(T == 2 || T == 4 || T == 8, "");
-  return T == 8 ? 4 * (k & 3) + 2 * ((k >> 3) & 1) : T == 4 ? 4 * ((k >> 1) & 1) + 2 * ((k >> 3) & 1) : 2 * ((k >> 3) & 1);
+  static_assert(T == 2 || T == 4 || T == 6 || T == 8, "");
+  return T == 6 ? 2 * ((k >> 3) & 1) : T == 8 ? 4 * (k & 3) + 2 * ((k >> 3) & 1) : T == 4 ? 4 * ((k >> 1) & 1) + 2 * ((k >> 3) & 1) : 2 * ((k >> 3) & 1);
 }
 
 // Fragment (16 outputs from 16 j, 32 k from 32 h) of such a stage for lane (li = lane % 16, grp = lane / 16).

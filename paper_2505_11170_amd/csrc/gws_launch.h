@@ -147,13 +147,13 @@ int compute_units();   // of the current device; 0 if the query fails
 bool gemm256_tn_applicable(const GemmArgs& g);
 int launch_gemm256_tn(const GemmArgs& g, bool with_dbt, hipStream_t stream);
 int launch_gemm256_tn_narrow(const GemmArgs& g, bool with_dbt, hipStream_t stream);   // the same with tiles of 256 x 192
-// weights of few tiles (gws_gemm_stream_tn.hip): a 16 mt x 64 piece a workgroup, the tokens split over its four wavefronts
-// (halves: and each wavefront's in two)
+// weights of few tiles (gws_gemm_stream_tn.hip): a 16 mt x 16 nt piece a workgroup, the tokens split over its four wavefronts
+// (halves: and each wavefront's in two); us 1e30: no piece takes the leading dimensions
 struct TnPlan {
-  int mt;
+  int mt, nt;
   double us;
 };
-TnPlan stream_tn_plan(const GemmArgs& g, bool halves);
+TnPlan stream_tn_plan(const GemmArgs& g, bool lines, bool halves);
 int launch_gemm_stream_tn(const GemmArgs& g, bool with_dbt, const TnPlan& p, bool halves, hipStream_t stream);
 // the same result with the contraction of every tile split over `parts` (2 .. 8, at most K / 64) workgroups: fp32 partial tiles in
 // `ws` (gemm256_tn_split_bytes, 16-byte aligned), added in a fixed order by a second kernel

@@ -274,3 +274,38 @@ def test_each_form_padded_sharded_and_without_the_reduction(form, tokens, rows, 
     dw.fill_(7.0)
     gws.gws_linear_bwd_w_ws(x[:, :K], dy[:, :N], gws.TensorDesc(**shard, dw=dw), 5, ws, w_is_nk=w_is_nk)
     assert torch.equal(dw.view(torch.int16), with_dbt.view(torch.int16))
+
+
+@pytest.mark.parametrize("w_is_nk", [False, True])
+@pytest.mark.parametrize("form,tokens,rows,cols,room", [
+    (gws.BWD_W_PIECES_32, 64, 256, 256, 0), (gws.BWD_W_PIECES_32, 448, 256, 512, 0), (gws.BWD_W_PIECES_32, 8192, 256, 2048, 8),
+    (gws.BWD_W_PIECES_96, 64, 768, 2816, 0), (gws.BWD_W_PIECES_96, 448, 1280, 3328, 0), (gws.BWD_W_PIECES_96, 2624, 768, 2816, 5), (gws.BWD_W_PIECES_96, 4096, 768, 3072, 7),
+    (gws.BWD_W_PIECES_128_128, 64, 1280, 1792, 0), (gws.BWD_W_PIECES_128_128, 832, 2048, 2048, 0), (gws.BWD_W_PIECES_128_128, 1088, 2048, 4096, 2)])
+def test_pieces_for_rows_on_cache_lines(form, tokens, rows, cols, room, w_is_nk):
+    # fewer units of tokens than wavefronts, uneven numbers of them, pieces past the weight's edge, sums in two halves; X and
+    # dY in wider buffers with NaN beside them, the weight a shard of a larger one, dW in a wider buffer
+    gen = torch.Generator(device=DEV).manual_seed(tokens + cols)
+    K, N = (cols, rows) if w_is_nk else (rows, cols)
+    x = torch.full((tokens, K + 64), float("nan"), dtype=torch.bfloat16, device=DEV)
+    dy = torch.full((tokens, N + 64), float("nan"), dtype=torch.bfloat16, device=DEV)
+    x[:, :K] = torch.randn(tokens, K, generator=gen, device=DEV)
+    dy[:, :N] = torch.randn(tokens, N, generator=gen, device=DEV) * 1e-3
+    dw = torch.full((rows, cols + 64), 7.0, dtype=torch.bfloat16, device=DEV)
+    shard = dict(rows=rows, cols=cols, ld=cols + 64, row0=320, col0=96, seed=41)
+    d = gws.TensorDesc(**shard, dw=dw, scale=torch.rand(rows // 32, cols // 32, generator=gen, device=DEV), dbt=torch.full((rows // 32, cols // 32), float("nan"), device=DEV))
+    ws = torch.full((room * rows * cols,), float("nan"), device=DEV) if room else None
+    assert gws.gws_linear_bwd_w_form(d, tokens, room * rows * cols * 4, on_lines=True) == form
+    gws.gws_linear_bwd_w_ws(x[:, :K], dy[:, :N], d, 5, ws, w_is_nk=w_is_nk)
+    a, b = (dy[:, :N], x[:, :K]) if w_is_nk else (x[:, :K], dy[:, :N])
+    ref, mag = fp32_product(a, b), fp32_product(a.abs(), b.abs())
+    # one rounding to BF16 and two fp32 sums of `tokens` terms in different orders
+    assert bool(((dw[:, :cols].float() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2 * tokens * 2.0 ** -24 * mag).all())
+    assert bool((dw[:, cols:] == 7.0).all())
+    back = gws.TensorDesc(**shard, scale=d.scale, g=dw, dw=None, dbt=torch.zeros_like(d.dbt))
+    gws.gws_sample_bwd([back], 5)
+    terms = 0.6932 * d.scale * dw[:, :cols].float().abs().view(rows // 32, 32, cols // 32, 32).sum((1, 3)) * 2
+    assert bool(((d.dbt - back.dbt).abs() <= 1e-5 * back.dbt.abs() + 1e-6 * terms).all())
+    with_dbt = dw.clone()
+    dw.fill_(7.0)
+    gws.gws_linear_bwd_w_ws(x[:, :K], dy[:, :N], gws.TensorDesc(**shard, dw=dw), 5, ws, w_is_nk=w_is_nk)
+    assert torch.equal(dw.view(torch.int16), with_dbt.view(torch.int16))
