@@ -102,26 +102,26 @@ __device__ __forceinline__ uint32_t in_vgpr(uint32_t v) {
   return v;
 }
 
-// The 4 T calls of T tiles (column groups pc[0 .. T-1]; the same four rows) advanced round by round together: independent
-// multiplies keep the vector ALU fed where few wavefronts share it, and the round keys, in vector registers, are stepped
-// once for all calls.
-template <int T>
+// The R T calls of T tiles (column groups pc[0 .. T-1]; the same R rows, four or the first two) advanced round by round
+// together: independent multiplies keep the vector ALU fed where few wavefronts share it, and the round keys, in vector
+// registers, are stepped once for all calls.
+template <int T, int R>
 __device__ __forceinline__ void philox_tiles(const PhiloxCols (&pc)[T], const PhiloxRows& rp, uint32_t k0, uint32_t k1,
-                                             Philox4 (&out)[T][4]) {
+                                             Philox4 (&out)[T][R]) {
   constexpr uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u, W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;
-  constexpr int N = 4 * T;
+  constexpr int N = R * T;
   uint32_t c0[N], c1[N], c2[N], c3[N];
   uint32_t ka = in_vgpr(k0 + 2 * W0), kb = in_vgpr(k1 + W1);
   uint64_t e[N];
 #pragma unroll
-  for (int k = 0; k < N; ++k) e[k] = (uint64_t)M1 * xor3(rp.hi[k & 3], pc[k >> 2].c3_1, kb);   // rounds 1 and 2
+  for (int k = 0; k < N; ++k) e[k] = (uint64_t)M1 * xor3(rp.hi[k % R], pc[k / R].c3_1, kb);   // rounds 1 and 2
   kb += W1;
 #pragma unroll
   for (int k = 0; k < N; ++k) {
-    c0[k] = xor3((uint32_t)(e[k] >> 32), pc[k >> 2].c1_2, ka);
+    c0[k] = xor3((uint32_t)(e[k] >> 32), pc[k / R].c1_2, ka);
     c1[k] = (uint32_t)e[k];
-    c2[k] = xor3(pc[k >> 2].hi_f, rp.lo[k & 3], kb);
-    c3[k] = pc[k >> 2].c3_3;
+    c2[k] = xor3(pc[k / R].hi_f, rp.lo[k % R], kb);
+    c3[k] = pc[k / R].c3_3;
   }
 #pragma unroll
   for (int r = 3; r < 10; ++r) {
@@ -142,7 +142,7 @@ __device__ __forceinline__ void philox_tiles(const PhiloxCols (&pc)[T], const Ph
     }
   }
 #pragma unroll
-  for (int k = 0; k < N; ++k) out[k >> 2][k & 3] = Philox4{c0[k], c1[k], c2[k], c3[k]};
+  for (int k = 0; k < N; ++k) out[k / R][k % R] = Philox4{c0[k], c1[k], c2[k], c3[k]};
 }
 
 // ---------------------------------------------------------------------------

@@ -117,101 +117,177 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_kernel(const GemmArgs g) {
   reduce_store<MT, NT, P, MC>(acc, lds, g, m0, n0);
 }
 
-// Eq. 3 + cast on one 32 x 32 block of the weight, the wavefront's (group i of a lane: storage row lane / 4 + 16 i, columns
-// 8 (lane % 4) .. + 7), turned through `blk`, 32 x LP elements of the wavefront's own LDS, into the two fragments (16 outputs,
-// 32 k) the MFMA takes.  row0, col0: the block's storage origin; writer: this wavefront stores w_hat and scale (if wanted).
-constexpr int LP = 40;   // row pitch of the staged block (elements)
-template <int FMT, bool W_NK>
-__device__ __forceinline__ void sampled_block(const GemmArgs& g, const u32x4 (&w)[2], float bt, uint32_t row0, uint32_t col0,
-                                              size_t block, bool writer, uint16_t* blk, Frag8 (&f)[2]) {
-  const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4, q = lane & 3, r = lane >> 2;
-  uint32_t m = absmax_pk(w[1], absmax_pk(w[0], 0));
-  m = max(m & 0xFFFFu, m >> 16);
-  m = block_max_u32(m);
-  const uint32_t a16 = max(m, (uint32_t)__shfl_xor((int)m, 4));   // the block is the whole wavefront's here
-  BlockScale s = block_scale(a16, bt);
-  if (FMT == 1) cast_constants<8, -6>(a16, s);
-  if (FMT == 2) cast_constants<4, -2>(a16, s);
-  writer = writer && g.w_hat != nullptr;
-  if (writer && lane == 0) g.scale[block] = s.s32;
-  const bool hw = (FMT == 1) && s.hw_safe;   // uniform: the wavefront holds one block
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const uint32_t srow = row0 + r + 16 * i, scol = col0 + 8 * q;
-    const Noise n = group_noise(g.cg0 + (scol >> 3), g.row0 + srow, g.step_lo, g.step_hi, g.seed_lo, g.seed_hi);
-    const u32x4 v = hw ? sample_group<FMT>(w[i], n, s, true) : sample_group<FMT>(w[i], n, s, false);
-    if (writer) *(u32x4*)(g.w_hat + (size_t)srow * g.ldw + scol) = v;
-    *(u32x4*)(blk + (r + 16 * i) * LP + 8 * q) = v;
-  }
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wavefront's own writes have landed
-  __builtin_amdgcn_wave_barrier();
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
+// Eq. 3 + cast on the weight's blocks on their way into the MFMA, B (1 or 2) at a time: the wavefront's 32 columns of Y and the
+// 32 B k of step s.  Group i of block h of a lane: storage row lane / 4 + 16 i, columns 8 (lane % 4) .. + 7 of the block.  Two
+// blocks together are two independent chains (maximum over the wavefront, scale, sums, cast), which one or two wavefronts a
+// SIMD need; one at a time takes half the registers.  The noise depends on none of the loads and comes first, its Philox
+// calls round by round with what they share drawn once (a column group of a [K x N] weight, two rows of an [N x K] one).
+constexpr int LP = 40;   // row pitch of a staged block (elements)
+template <int FMT, bool W_NK, int B>
+struct Blocks {
+  uint32_t n0, nbc;          // the wavefront's columns of Y; blocks per storage row
+  uint32_t q, r;             // lane % 4, lane / 4
+  PhiloxCols cols;           // [K x N]
+  PhiloxRows rows;           // [N x K], two of them
+  const GWS_GLOBAL char* base;
+  uint32_t off;
+
+  __device__ __forceinline__ Blocks(const GemmArgs& g, uint32_t n) : n0(n), nbc((W_NK ? g.K : g.N) >> 5) {
+    const uint32_t lane = threadIdx.x & 63;
+    q = lane & 3;
+    r = lane >> 2;
     if (W_NK) {
-      f[j].u = *(const u32x4*)(blk + (16 * j + li) * LP + 8 * grp);
-    } else {   // transposing read: lanes 4 t .. 4 t + 3 of 16 point at 16 outputs of row k0 + t
+      const uint32_t row[4] = {g.row0 + n0 + r, g.row0 + n0 + r + 16, 0, 0};
+      rows = philox_rows(row, g.step_lo, g.seed_lo);
+    } else {
+      cols = philox_cols(g.cg0 + (n0 >> 3) + q, g.step_lo, g.step_hi, g.seed_lo, g.seed_hi);
+    }
+    base = (const GWS_GLOBAL char*)(W_NK ? g.w + (size_t)n0 * g.ldw : g.w + n0);
+    off = (r * g.ldw + 8 * q) * 2;
+  }
+  // block b along K: its first storage row and column, its number
+  __device__ __forceinline__ uint32_t row_of(uint32_t b) const { return W_NK ? n0 : 32 * b; }
+  __device__ __forceinline__ uint32_t col_of(uint32_t b) const { return W_NK ? 32 * b : n0; }
+  __device__ __forceinline__ size_t number(uint32_t b) const { return W_NK ? (size_t)(n0 >> 5) * nbc + b : (size_t)b * nbc + (n0 >> 5); }
+
+  struct Raw {
+    u32x4 w[B][2];
+    float bt[B];
+  };
+  // blocks B s ..; of half a step at the end of K the first one twice
+  __device__ __forceinline__ void load(const GemmArgs& g, uint32_t s, Raw& x) const {
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
-        f[j].h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((GWS_LDS i16x4*)(blk + (8 * grp + 4 * h + (li >> 2)) * LP + 16 * j + 4 * (li & 3)));
+    for (int h = 0; h < B; ++h) {
+      const uint32_t b = stream::umin(B * s + h, (g.K >> 5) - 1);
+      const GWS_GLOBAL char* p = base + (W_NK ? (size_t)b * 64 : (size_t)b * 64 * g.ldw);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) x.w[h][i] = *(const GWS_GLOBAL u32x4*)(p + (size_t)(16 * i) * g.ldw * 2 + off);
+      x.bt[h] = global_ptr<float>(g.bt)[number(b)];
     }
   }
-}
 
-// The sampling form: a wavefront loads one 32 x 32 block of the weight per step (two 16-byte groups per lane), samples
-// it in registers, turns it through its own 2.5 KiB of LDS and multiplies.  Bound by the vector ALU work of the
-// sampling (about 275 instructions a block), which every 16 MT rows of X repeat.
+  // The sampled blocks as fragments f[block][column half] (16 outputs, 32 k), turned through `blk`, B x 32 x LP elements of the
+  // wavefront's own LDS; writer: this wavefront stores w_hat and scale (if wanted).
+  __device__ __forceinline__ void sample(const GemmArgs& g, uint32_t step, const Raw& x, bool writer, uint16_t* blk, Frag8 (&f)[B][2]) const {
+    const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4;
+    Noise n[B][2];   // [block][group]
+    if (W_NK) {
+      PhiloxCols pc[B];
+#pragma unroll
+      for (int h = 0; h < B; ++h) pc[h] = philox_cols(g.cg0 + 4 * (B * step + h) + q, g.step_lo, g.step_hi, g.seed_lo, g.seed_hi);
+      Philox4 p[B][2];
+      philox_tiles(pc, rows, g.seed_lo, g.seed_hi, p);
+#pragma unroll
+      for (int k = 0; k < 2 * B; ++k) n[k >> 1][k & 1] = noise_codes(p[k >> 1][k & 1]);
+    } else {
+      const uint32_t k0 = g.row0 + 32 * B * step + r, row[4] = {k0, k0 + 16, k0 + 32, k0 + 48};
+      const PhiloxCols pc[1] = {cols};
+      Philox4 p[1][2 * B];
+      philox_tiles(pc, philox_rows(row, g.step_lo, g.seed_lo), g.seed_lo, g.seed_hi, p);
+#pragma unroll
+      for (int k = 0; k < 2 * B; ++k) n[k >> 1][k & 1] = noise_codes(p[0][k]);
+    }
+#pragma unroll
+    for (int k = 0; k < 2 * B; ++k) asm volatile("" : "+v"(n[k >> 1][k & 1].c));   // here, while the weight is on its way
+    BlockScale s[B];
+#pragma unroll
+    for (int h = 0; h < B; ++h) {
+      uint32_t m = absmax_pk(x.w[h][1], absmax_pk(x.w[h][0], 0));
+      m = max(m & 0xFFFFu, m >> 16);
+      m = block_max_u32(m);
+      const uint32_t a16 = max(m, (uint32_t)__shfl_xor((int)m, 4));   // the block is the whole wavefront's here
+      s[h] = block_scale(a16, x.bt[h]);
+      if (FMT == 1) cast_constants<8, -6>(a16, s[h]);
+      if (FMT == 2) cast_constants<4, -2>(a16, s[h]);
+    }
+    u32x4 v[B][2];
+    if (FMT == 1 && s[0].hw_safe && s[B - 1].hw_safe) {   // uniform: the wavefront holds the blocks
+#pragma unroll
+      for (int k = 0; k < 2 * B; ++k) v[k >> 1][k & 1] = sample_group<FMT>(x.w[k >> 1][k & 1], n[k >> 1][k & 1], s[k >> 1], true);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 2 * B; ++k) v[k >> 1][k & 1] = sample_group<FMT>(x.w[k >> 1][k & 1], n[k >> 1][k & 1], s[k >> 1], false);
+    }
+    if (writer && g.w_hat != nullptr) {
+#pragma unroll
+      for (int h = 0; h < B; ++h) {
+        const uint32_t b = B * step + h;
+        if (b >= g.K >> 5) break;
+        if (lane == 0) g.scale[number(b)] = s[h].s32;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) *(u32x4*)(g.w_hat + (size_t)(row_of(b) + r + 16 * i) * g.ldw + col_of(b) + 8 * q) = v[h][i];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 2 * B; ++k) *(u32x4*)(blk + ((k >> 1) * 32 + r + 16 * (k & 1)) * LP + 8 * q) = v[k >> 1][k & 1];
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wavefront's own writes have landed
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int h = 0; h < B; ++h)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const uint16_t* p = blk + h * 32 * LP;
+        if (W_NK) {
+          f[h][j].u = *(const u32x4*)(p + (16 * j + li) * LP + 8 * grp);
+        } else {   // transposing read: lanes 4 t .. 4 t + 3 of 16 point at 16 outputs of row k0 + t
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+            f[h][j].h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((GWS_LDS i16x4*)(p + (8 * grp + 4 * t + (li >> 2)) * LP + 16 * j + 4 * (li & 3)));
+        }
+      }
+  }
+};
+
+// The sampling form: a wavefront keeps a step's blocks on their way into registers while it samples those of the step before,
+// turns them through its own 2.5 KiB of LDS a block and multiplies.  Bound by the vector ALU work of the sampling, which every
+// 16 MT rows of X repeat.  Two blocks a step where a compute unit has only one such workgroup's wavefronts (16 rows: 16 x 2048
+// -> 5632 11.6 -> 11.4 us, 16 x 768 -> 3072 8.0 -> 7.6), one where it may have several (300 x 2048 -> 5632 41 us, two blocks 46).
 template <int MT, int P, int FMT, bool W_NK>
 __global__ __launch_bounds__(64 * P) void gemm_stream_sample_kernel(const GemmArgs g) {
   using namespace stream;
-  constexpr int kRed = red_bytes(MT, 2, P), kBlk = P * 32 * LP * 2;
+  constexpr int B = MT == 1 ? 2 : 1;
+  constexpr int kRed = red_bytes(MT, 2, P), kBlk = P * B * 32 * LP * 2;
   __shared__ __attribute__((aligned(16))) char lds[kRed > kBlk ? kRed : kBlk];
   const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  uint16_t* blk = (uint16_t*)lds + wave * 32 * LP;
-  uint32_t m0, n0, b0, b1;
+  uint16_t* blk = (uint16_t*)lds + wave * B * 32 * LP;
+  uint32_t m0, n0, s0, s1;
   tile_origin(g, 16 * MT, 32, !W_NK, m0, n0);
-  unit_range(g.K, wave, P, b0, b1);
-  b0 *= 2;
-  b1 = umin(2 * b1, g.K >> 5);
+  unit_range(g.K, wave, P, s0, s1);
+  if (B == 1) {
+    s0 *= 2;
+    s1 = umin(2 * s1, g.K >> 5);
+  }
 
   uint32_t xo[MT];
 #pragma unroll
   for (int i = 0; i < MT; ++i) xo[i] = (umin(16u * i + li, g.M - 1 - m0) * g.ldx + 8 * grp) * 2;
   const GWS_GLOBAL char* xb = (const GWS_GLOBAL char*)(g.x + (size_t)m0 * g.ldx);
-  // group i of a lane: storage row lane / 4 + 16 i, columns 8 (lane % 4) .. + 7 of the block
-  const uint32_t q = lane & 3, r = lane >> 2;
-  const uint32_t wo = (r * g.ldw + 8 * q) * 2;
-  const GWS_GLOBAL char* wb = (const GWS_GLOBAL char*)(W_NK ? g.w + (size_t)n0 * g.ldw : g.w + n0);
-  const size_t wstep = W_NK ? 64 : (size_t)g.ldw * 64;   // bytes from a block to the next along K
-  const uint32_t nbc = (W_NK ? g.K : g.N) >> 5;
-  auto block_index = [&](uint32_t b) { return W_NK ? (size_t)(n0 >> 5) * nbc + b : (size_t)b * nbc + (n0 >> 5); };
+  const Blocks<FMT, W_NK, B> w(g, n0);
 
   f32x4 acc[MT][2];
 #pragma unroll
   for (int i = 0; i < MT; ++i) acc[i][0] = acc[i][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  u32x4 nxt[2];
-  float bt_nxt = 0.0f;
-  auto load = [&](uint32_t b) {
+  typename Blocks<FMT, W_NK, B>::Raw nxt;
+  if (s0 < s1) w.load(g, s0, nxt);
+  for (uint32_t s = s0; s < s1; ++s) {
+    const typename Blocks<FMT, W_NK, B>::Raw cur = nxt;
+    w.load(g, umin(s + 1, s1 - 1), nxt);
+    Frag8 x[B][MT], f[B][2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-      nxt[i] = *(const GWS_GLOBAL u32x4*)(wb + b * wstep + (size_t)(16 * i) * g.ldw * 2 + wo);
-    bt_nxt = global_ptr<float>(g.bt)[block_index(b)];
-  };
-  if (b0 < b1) load(b0);
-  for (uint32_t b = b0; b < b1; ++b) {
-    u32x4 w[2] = {nxt[0], nxt[1]};
-    const float bt = bt_nxt;
-    load(umin(b + 1, b1 - 1));
-    Frag8 x[MT];
+    for (int h = 0; h < B; ++h)
 #pragma unroll
-    for (int i = 0; i < MT; ++i) x[i].u = *(const GWS_GLOBAL u32x4*)(xb + (size_t)b * 64 + xo[i]);
-    Frag8 f[2];
-    sampled_block<FMT, W_NK>(g, w, bt, W_NK ? n0 : b * 32, W_NK ? b * 32 : n0, block_index(b), m0 == 0, blk, f);
+      for (int i = 0; i < MT; ++i) x[h][i].u = *(const GWS_GLOBAL u32x4*)(xb + (size_t)umin(B * s + h, (g.K >> 5) - 1) * 64 + xo[i]);
+    w.sample(g, s, cur, m0 == 0, blk, f);
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
+    for (int h = 0; h < B; ++h) {
+      if (h > 0 && B * s + h >= g.K >> 5) break;   // half a step at the end of K (uniform)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[j].v, x[i].v, acc[i][j], 0, 0, 0);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the reads are done before the block is overwritten
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[h][j].v, x[h][i].v, acc[i][j], 0, 0, 0);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the reads are done before the blocks are overwritten
     __builtin_amdgcn_wave_barrier();
   }
   reduce_store<MT, 2, P, MT>(acc, lds, g, m0, n0);
@@ -220,24 +296,24 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_sample_kernel(const GemmAr
 // Many rows of X, the weight sampled on its way in, K from end to end (the order of the middle and large tiles' sums, so Y is
 // their Y): a workgroup owns 128 rows x 128 columns, a wavefront 32 of the columns.  X comes through LDS in units of 64 k, a
 // ring of two stages that the four wavefronts share, one barrier a unit; the weight's blocks go from a wavefront's
-// registers through its own LDS as above.  Bound by the vector ALU work of the sampling, which every 128 rows repeat
-// (2.3 us a unit with one workgroup on a compute unit, 2.6 with two; a third needs spills: a quarter slower).  Against
-// gemm_kernel (gws_linear.hip), us, [K x N] and [N x K]: 1107 x 2528 -> 3104 148, 130 -> 101, 94; 4000 x 512 -> 512 29, 28 ->
-// 16, 15; 8192 x 2048 -> 5632 610, 544 -> 519, 500; 5683 x 608 -> 1792 61, 54 -> 56, 57.
+// registers through its own LDS as above, two a unit.  Bound by the vector ALU work of the sampling, which every 128 rows
+// repeat (about 2 us a unit with one workgroup on a compute unit).  FP8, [K x N] and [N x K], us, with one block at a time before:
+// 4000 x 2304 -> 800 92, 92 -> 70, 72; 4000 x 3072 -> 1024 122, 121 -> 93, 94; 8192 x 512 -> 512 28, 28 -> 23, 23;
+// 8192 x 2048 -> 5632 494, 498 -> 450, 436.
 template <int FMT, bool W_NK>
 __global__ __launch_bounds__(256, 2) void gemm_rows_sample_kernel(const GemmArgs g) {
   using namespace stream;
   constexpr int MT = 8, BM = 16 * MT, D = 2, XS = BM * 64, LX = BM / 32;   // load instructions of a wavefront and unit
   __shared__ __attribute__((aligned(1024))) uint16_t ring[D * XS];
-  __shared__ __attribute__((aligned(16))) uint16_t blocks[4 * 32 * LP];
-  const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4, q = lane & 3, r = lane >> 2;
+  __shared__ __attribute__((aligned(16))) uint16_t blocks[4 * 2 * 32 * LP];
+  const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  uint16_t* blk = blocks + wave * 32 * LP;
+  uint16_t* blk = blocks + wave * 2 * 32 * LP;
   uint32_t m0, n0;
   tile_origin(g, BM, 128, false, m0, n0);
   n0 += 32 * wave;
   const bool live = n0 < g.N;   // N is a multiple of 32: a wavefront's columns exist or do not
-  const uint32_t nu = (g.K + 63) >> 6, nb = g.K >> 5;
+  const uint32_t nu = (g.K + 63) >> 6;
 
   uint32_t xo[LX];
 #pragma unroll
@@ -251,24 +327,13 @@ __global__ __launch_bounds__(256, 2) void gemm_rows_sample_kernel(const GemmArgs
 #pragma unroll
     for (int i = 0; i < LX; ++i) direct(xb + (size_t)k0 * 2, xo[i], ring + (u % D) * XS + (wave * LX + i) * 512);
   };
-  const uint32_t nw = live ? n0 : 0;   // a wavefront past the edge reads the first columns and multiplies nothing
-  const uint32_t wo = (r * g.ldw + 8 * q) * 2;
-  const GWS_GLOBAL char* wb = (const GWS_GLOBAL char*)(W_NK ? g.w + (size_t)nw * g.ldw : g.w + nw);
-  const size_t wstep = W_NK ? 64 : (size_t)g.ldw * 64;   // bytes from a block to the next along K
-  const uint32_t nbc = (W_NK ? g.K : g.N) >> 5;
-  auto block_index = [&](uint32_t b) { return W_NK ? (size_t)(nw >> 5) * nbc + b : (size_t)b * nbc + (nw >> 5); };
-  u32x4 nxt[2];
-  float bt_nxt = 0.0f;
-  auto load_w = [&](uint32_t b) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) nxt[i] = *(const GWS_GLOBAL u32x4*)(wb + b * wstep + (size_t)(16 * i) * g.ldw * 2 + wo);
-    bt_nxt = global_ptr<float>(g.bt)[block_index(b)];
-  };
+  const Blocks<FMT, W_NK, 2> w(g, live ? n0 : 0);   // a wavefront past the edge reads the first columns and multiplies nothing
+  typename Blocks<FMT, W_NK, 2>::Raw nxt;
 
   f32x4 acc[MT][2];
 #pragma unroll
   for (int i = 0; i < MT; ++i) acc[i][0] = acc[i][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  load_w(0);
+  w.load(g, 0, nxt);
   load_x(0);
   for (uint32_t u = 0; u < nu; ++u) {
     // this unit, requested a unit's sampling ago, has landed, and every wavefront is past its reads of the other stage
@@ -277,21 +342,20 @@ __global__ __launch_bounds__(256, 2) void gemm_rows_sample_kernel(const GemmArgs
     if (!live) continue;
     const uint16_t* xs = ring + (u % D) * XS;
     const bool half = 64 * u + 64 > g.K;
+    const typename Blocks<FMT, W_NK, 2>::Raw cur = nxt;
+    w.load(g, umin(u + 1, nu - 1), nxt);
+    Frag8 f[2][2];
+    w.sample(g, u, cur, m0 == 0, blk, f);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      if (h == 0 && half) continue;   // only the second half of the stage belongs to this unit
-      const uint32_t b = half ? nb - 1 : 2 * u + h;
-      const u32x4 w[2] = {nxt[0], nxt[1]};
-      const float bt = bt_nxt;
-      load_w(umin(b + 1, nb - 1));
-      Frag8 f[2];
-      sampled_block<FMT, W_NK>(g, w, bt, W_NK ? n0 : b * 32, W_NK ? b * 32 : n0, block_index(b), m0 == 0, blk, f);
+      if (h == 1 && half) break;   // one block, whose k are the second half of the stage
+      const int hx = half ? 1 : h;
 #pragma unroll
       for (int i = 0; i < MT; ++i) {
         Frag8 x;
-        x.u = *(const u32x4*)(xs + (16 * i + li) * 64 + (((4 * h + grp) ^ ((li >> 1) & 7)) * 8));
+        x.u = *(const u32x4*)(xs + (16 * i + li) * 64 + (((4 * hx + grp) ^ ((li >> 1) & 7)) * 8));
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[j].v, x.v, acc[i][j], 0, 0, 0);
+        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[h][j].v, x.v, acc[i][j], 0, 0, 0);
       }
     }
   }

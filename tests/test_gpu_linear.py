@@ -578,3 +578,25 @@ def test_rows_of_x_far_apart(M, K, N, ldx, plain, w_is_nk):
     q, _ = oracle.sample_fwd(synth.bits(t["w"]), t["bt"].numpy(), fmt, seed, step)
     check_y(synth.bits(y[0]), synth.bits(xs), q, w_is_nk)
     assert (synth.bits(y[0]) == synth.bits(y[1])).all()
+
+
+@pytest.mark.parametrize("w_is_nk", [False, True])
+@pytest.mark.parametrize("fmt", [gws.FMT_BF16, gws.FMT_FP8_E4M3, gws.FMT_FP6_E3M2])
+@pytest.mark.parametrize("M,K,N", [(1, 64, 32), (5, 96, 64), (16, 992, 160), (17, 96, 32), (40, 544, 96), (200, 96, 96), (3000, 96, 160), (3000, 160, 2208), (2900, 352, 992)])
+def test_blocks_sampled_by_one_and_by_pairs(M, K, N, fmt, w_is_nk):
+    # few rows take two blocks a step, more take one, many two again: one, two, three blocks of K and odd numbers of them
+    # (half a step at the end), wavefronts without any, a shard; w_hat, scale and Y to the bits of the sampling kernel and the
+    # plain product
+    r, c = (N, K) if w_is_nk else (K, N)
+    t = synth.make_tensor(60 + M % 7, r, c, device=DEV, bt=3.0 if M == 40 else None)     # b_t = 3: blocks beyond the hardware cast
+    x = synth.make_activation(61 + M % 5, M, K, device=DEV)
+    nb = synth.n_blocks(r, c)
+    shard = dict(rows=r, cols=c, seed=9, row0=64, col0=96)
+    one, two = (gws.TensorDesc(**shard, w=t["w"], bt=t["bt"], w_hat=torch.zeros_like(t["w"]), scale=torch.zeros(*nb, device=DEV)) for _ in range(2))
+    y, ref = (torch.zeros(M, N, dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    gws.gws_linear_fwd_mode(x, one, y, fmt, 4, gws.LINEAR_IN_OPERAND, w_is_nk=w_is_nk)
+    gws.gws_sample_fwd([two], fmt, 4)
+    gws.gws_gemm_bf16(x, two.w_hat, ref, w_is_nk=w_is_nk)
+    torch.cuda.synchronize()
+    assert torch.equal(one.w_hat.view(torch.int16), two.w_hat.view(torch.int16)) and torch.equal(one.scale, two.scale)
+    assert torch.equal(y.view(torch.int16), ref.view(torch.int16))
