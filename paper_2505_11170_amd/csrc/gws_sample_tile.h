@@ -175,13 +175,13 @@ __device__ __forceinline__ void store_codes(GWS_GLOBAL uint8_t* row, uint32_t co
   }
 }
 
-// The FP6 codes of a whole tile whose rows of codes are 4-byte aligned.  A lane holds 48 bits of each of its four rows
-// r0 + 8 i; within each quad of lanes (four column groups side by side) the 4 x 4 pieces are exchanged, so that a lane
-// ends up with the 24 consecutive bytes of one row (row r0 + 8 (lane % 4)) and writes them with two stores instead of
-// twelve.
-__device__ __forceinline__ void store_codes_fp6_quad(GWS_GLOBAL uint8_t* tile_row0, uint32_t ldc, uint32_t lane,
-                                                     const uint32_t (&c)[6]) {
-  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// The FP6 codes of a whole tile.  A lane holds 48 bits of each of its four rows r0 + 8 i; within each quad of lanes (four
+// column groups side by side) the 4 x 4 pieces are exchanged, so that a lane ends up with the 24 consecutive bytes of one
+// row: row r0 + 8 (lane % 4), byte (lane & 4) * 6 of the tile's 48.
+struct Codes24 {
+  uint32_t w[6];
+};
+__device__ __forceinline__ Codes24 codes_fp6_quad(uint32_t lane, const uint32_t (&c)[6]) {
   // piece i = 32 low bits lo[i] and 16 high bits: of pieces 0, 1 in h01, of pieces 2, 3 in h23
   uint32_t lo[4] = {c[0], __builtin_amdgcn_alignbit(c[2], c[1], 16), c[3], __builtin_amdgcn_alignbit(c[5], c[4], 16)};
   const uint32_t h01 = __builtin_amdgcn_perm(c[2], c[1], 0x07060100u), h23 = __builtin_amdgcn_perm(c[5], c[4], 0x07060100u);
@@ -208,11 +208,27 @@ __device__ __forceinline__ void store_codes_fp6_quad(GWS_GLOBAL uint8_t* tile_ro
   const uint32_t sel = odd ? 0x07060302u : 0x05040100u;
   const uint32_t g01 = odd ? __builtin_amdgcn_perm(first, pf, sel) : __builtin_amdgcn_perm(pf, first, sel);
   const uint32_t g23 = odd ? __builtin_amdgcn_perm(second, ps, sel) : __builtin_amdgcn_perm(ps, second, sel);
-  GWS_GLOBAL uint8_t* dst = at_byte(tile_row0, ((lane >> 3) + 8 * (lane & 3)) * ldc + (lane & 4) * 6);
-  typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
-  typedef uint32_t u32x2a4 __attribute__((ext_vector_type(2), aligned(4)));
-  *(GWS_GLOBAL u32x4a4*)dst = u32x4{l[0], __builtin_amdgcn_perm(l[1], g01, 0x05040100u), __builtin_amdgcn_perm(g01, l[1], 0x07060302u), l[2]};
-  *(GWS_GLOBAL u32x2a4*)(dst + 16) = u32x2{__builtin_amdgcn_perm(l[3], g23, 0x05040100u), __builtin_amdgcn_perm(g23, l[3], 0x07060302u)};
+  return Codes24{{l[0], __builtin_amdgcn_perm(l[1], g01, 0x05040100u), __builtin_amdgcn_perm(g01, l[1], 0x07060302u), l[2],
+                  __builtin_amdgcn_perm(l[3], g23, 0x05040100u), __builtin_amdgcn_perm(g23, l[3], 0x07060302u)}};
+}
+
+typedef __bf16 bf16x32 __attribute__((ext_vector_type(32)));
+typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
+
+// FP6-E3M2: the 32-wide hardware converters (v_cvt_scalef32_pk32_bf6_bf16 and back) take
+// a lane's whole tile at once, round to nearest even with gradual underflow and saturate
+// at 28 * X (checked against the cast's definition on every finite BF16 input at several
+// scales).
+template <bool FULL>
+__device__ __forceinline__ u32x6 tile_codes_fp6(const Tile& t, const BlockScale& b) {
+  uint32_t pk[16];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) pk[4 * i + k] = !FULL && t.nv[i] == 0 ? 0 : t.v[i][k];
+  bf16x32 v;
+  __builtin_memcpy(&v, pk, 64);
+  return __builtin_amdgcn_cvt_scalef32_pk32_bf6_bf16(v, b.x_scale);
 }
 
 // The forward pass on one wavefront tile, in three phases.
@@ -314,23 +330,16 @@ __device__ __forceinline__ void tile_store(const TileDesc& d, const Tile& t, con
       }
       }
   } else {
-    // FP6-E3M2: the 32-wide hardware converters (v_cvt_scalef32_pk32_bf6_bf16 and back) take
-    // a lane's whole tile at once, round to nearest even with gradual underflow and saturate
-    // at 28 * X (checked against the cast's definition on every finite BF16 input at several
-    // scales).
-    typedef __bf16 bf16x32 __attribute__((ext_vector_type(32)));
-    typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
-    uint32_t pk[16];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) pk[4 * i + k] = !FULL && t.nv[i] == 0 ? 0 : t.v[i][k];
-    bf16x32 v;
-    __builtin_memcpy(&v, pk, 64);
-    const u32x6 c = __builtin_amdgcn_cvt_scalef32_pk32_bf6_bf16(v, b.x_scale);
+    const u32x6 c = tile_codes_fp6<FULL>(t, b);
     if (MX && FULL && (((uint32_t)(uintptr_t)d.p1 | d.ldc) & 3) == 0) {   // uniform
       const uint32_t cw[6] = {c[0], c[1], c[2], c[3], c[4], c[5]};
-      store_codes_fp6_quad(global_ptr<uint8_t>(d.p1) + (size_t)row_base * d.ldc + (col_base >> 3) * 6, d.ldc, lane, cw);
+      const Codes24 q = codes_fp6_quad(lane, cw);
+      GWS_GLOBAL uint8_t* dst = at_byte(global_ptr<uint8_t>(d.p1) + (size_t)row_base * d.ldc + (col_base >> 3) * 6, (r0 + 8 * (lane & 3)) * d.ldc + (lane & 4) * 6);
+      typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
+      typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+      typedef uint32_t u32x2a4 __attribute__((ext_vector_type(2), aligned(4)));
+      *(GWS_GLOBAL u32x4a4*)dst = u32x4{q.w[0], q.w[1], q.w[2], q.w[3]};
+      *(GWS_GLOBAL u32x2a4*)(dst + 16) = u32x2{q.w[4], q.w[5]};
     } else if constexpr (MX) {
       // element k of the lane's 32 sits in bits [6k, 6k + 6): 48 bits per group
       const MxCodes gc4[4] = {{c[0], c[1] & 0xFFFFu},

@@ -162,3 +162,10 @@ def test_random_mix_of_many_small_and_ragged_tensors(fmt):
 def test_fp6_codes_of_whole_tiles_at_every_row_alignment(pad):
     # whole 32 x 64 tiles leave as 24 bytes a lane where rows of codes are 4-byte aligned (pad 0, 2), else in 2-byte pieces
     check_mx(make_items([(32, 64), (64, 256), (96, 832), (160, 512)], 460), gws.FMT_FP6_E3M2, 4, pad=pad)
+
+
+@pytest.mark.parametrize("fmt", MX_FMTS)
+@pytest.mark.parametrize("pad", [0, 1, 7])
+def test_codes_that_leave_by_rows_of_the_workgroup(fmt, pad):
+    # tensors of whole 32 x 256 tiles only: the codes are staged; rows at the least alignment (FP8 8 bytes, FP6 2)
+    check_mx(make_items([(32, 256), (64, 768), (320, 512)], 470), fmt, 5, pad=pad)
