@@ -5,7 +5,8 @@
 // v_mfma_f32_16x16x32_bf16 tiles.  Both operand tiles (16 KiB each) go global -> LDS directly into a ring of four stages, in
 // the layouts of gws_gemm256_core.h, three K-steps ahead; one barrier a K-step, between its two 32-deep halves: the second
 // half's fragments are read under the first half's MFMAs, the next step's first ones under the second half's.
-// What bounds it: the operands' bytes (32 KiB per 64 k and compute unit) and the LDS reads, each about as long as the MFMAs.
+// What bounds it: a K-step takes 0.41 us (W [N x K]; 0.43 for [K x N]), of which the operands' 32 KiB from L2 alone 0.34, the
+// MFMAs alone 0.25 and the LDS reads alone 0.17; misses in L2 are not it (0.39 without any).  A launch starts and ends in 6 us.
 #include "gws_gemm256_core.h"
 #include "gws_launch.h"
 
@@ -35,42 +36,66 @@ __global__ __launch_bounds__(256) void gemm128_kernel(const GemmArgs g) {
     const uint32_t row = 32 * wave + 8 * q + (lane >> 3), chunk = (lane & 7) ^ (4 * (q & 1) + (lane >> 4));
     xo[q] = (umin(row, g.M - 1 - m0) * g.ldx + chunk * 8) * 2;
     if (W_NK) wo[q] = (umin(row, g.N - 1 - n0) * g.ldw + chunk * 8) * 2;
-    else wo[q] = ((lane >> 4) * g.ldw + umin((lane & 15) ^ ((lane >> 4) << 2) ^ ((q >> 1) << 1), (g.N - n0) / 8 - 1) * 8) * 2;
+    else
+      wo[q] = ((16 * wave + 4 * q + (lane >> 4)) * g.ldw +
+               umin((lane & 15) ^ ((lane >> 4) << 2) ^ ((q >> 1) << 1), (g.N - n0) / 8 - 1) * 8) * 2;
+    // an instruction's offset counts on both sides: 1 KiB a load in LDS, taken back here
+    xo[q] += 1024 * (3 - q);
+    wo[q] += 1024 * (3 - q);
   }
-  const GWS_GLOBAL char* xb = (const GWS_GLOBAL char*)(g.x + (size_t)m0 * g.ldx);
-  const GWS_GLOBAL char* wb = (const GWS_GLOBAL char*)(W_NK ? g.w + (size_t)n0 * g.ldw : g.w + n0);
-  auto direct = [](const GWS_GLOBAL char* base, uint32_t voff, uint16_t* dst) {
-    const uint32_t a = (uint32_t)(uintptr_t)(GWS_LDS void*)dst;
+  const GWS_GLOBAL char* xb = (const GWS_GLOBAL char*)(g.x + (size_t)m0 * g.ldx) - 3072;
+  const GWS_GLOBAL char* wb = (const GWS_GLOBAL char*)(W_NK ? g.w + (size_t)n0 * g.ldw : g.w + n0) - 3072;
+  uint32_t k_next = 0;                   // first k of the step that is fetched next
+  const uint32_t lds_wave = (uint32_t)(uintptr_t)(GWS_LDS void*)lds + wave * 4096;
+  // two of a step's eight loads (n = 0 .. 3): X, W, X, W.  One wavefront a SIMD issues an instruction in about five cycles, an
+  // MFMA takes sixteen: the loop has room for two instructions beside each MFMA, so addresses are kept as running scalars and
+  // two loads share one setting of M0.
+  auto load_n = [&](uint32_t stage, int n) {
+    const uint32_t dst = lds_wave + stage + (n & 1) * (OP * 2);
+    const uint32_t v0 = n & 1 ? wo[n & 2] : xo[n & 2], v1 = n & 1 ? wo[(n & 2) + 1] : xo[(n & 2) + 1];
+    const GWS_GLOBAL char* base = n & 1 ? wb : xb;
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(a) : "m0", "memory");
+    if (n < 2)
+      asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2\n\tglobal_load_lds_dwordx4 %1, %2 offset:1024"
+                   ::"v"(v0), "v"(v1), "s"(base), "s"(dst) : "m0", "memory");
+    else
+      asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 offset:2048\n\tglobal_load_lds_dwordx4 %1, %2 offset:3072"
+                   ::"v"(v0), "v"(v1), "s"(base), "s"(dst) : "m0", "memory");
 #pragma clang diagnostic pop
   };
-  // load n (0 .. 7) of a K-step: even n -> X, odd n -> W
-  auto load_n = [&](uint32_t kt, int n) {
-    uint16_t* st = lds + (kt % D) * STG + wave * 2048;
-    const uint32_t k0 = umin(TK * kt, g.K - TK);   // the half step at the end of K is fetched as the second half of a whole one
-    const int q = n >> 1;
-    if (!(n & 1)) direct(xb + (size_t)k0 * 2, xo[q], st + q * 512);
-    else direct(W_NK ? wb + (size_t)k0 * 2 : wb + (size_t)(k0 + 16 * wave + 4 * q) * g.ldw * 2, wo[q], st + OP + q * 512);
+  auto load_advance = [&]() {   // the half step at the end of K is fetched as the second half of a whole one
+    const uint32_t k = umin(k_next + TK, g.K - TK), d = __builtin_amdgcn_readfirstlane(k - k_next);
+    xb += d * 2;
+    wb += W_NK ? d * 2 : d * (g.ldw * 2);
+    k_next = k;
   };
   Frag8 fx[2][4], fw[2][4];
   // read fragments of half h, step n of NR, in the order the MFMAs need them: X 0, W 0 .. 3, X 1 .. 3
   constexpr int RW = W_NK ? 1 : 2, NR = 4 + 4 * RW;
-  auto read_n = [&](int h, uint32_t kt, int n) {
-    const uint16_t* xs = lds + (kt % D) * STG;
-    const uint16_t* ws = xs + OP;
-    const uint32_t sl = ((4 * h + grp) ^ ((li >> 1) & 7)) * 8;
+  uint32_t xr[2], wr[W_NK ? 2 : 4];   // byte offsets in a stage
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const uint32_t sl = ((4 * h + grp) ^ ((li >> 1) & 7)) * 16;
+    xr[h] = (64 * wm + li) * 128 + sl;
+    if (W_NK) wr[h] = OP * 2 + (64 * wn + li) * 128 + sl;
+  }
+  if (!W_NK)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t k = 8 * grp + (li >> 2), c = 8 * wn + 2 * j + ((li >> 1) & 1);
+      wr[j] = OP * 2 + k * 256 + (c ^ ((li >> 2) << 2) ^ ((grp & 1) << 1)) * 16 + (li & 1) * 8;
+    }
+  auto read_n = [&](int h, uint32_t stage, int n) {
+    const char* st = (const char*)lds + stage;
     if (n == 0 || n > 4 * RW) {
       const int i = n == 0 ? 0 : n - 4 * RW;
-      fx[h][i].u = *(const u32x4*)(xs + (64 * wm + 16 * i + li) * 64 + sl);
+      fx[h][i].u = *(const u32x4*)(st + xr[h] + 2048 * i);
     } else if (W_NK) {
-      fw[h][n - 1].u = *(const u32x4*)(ws + (64 * wn + 16 * (n - 1) + li) * 64 + sl);
+      fw[h][n - 1].u = *(const u32x4*)(st + wr[h] + 2048 * (n - 1));
     } else {
       const int j = (n - 1) >> 1, t = (n - 1) & 1;
-      const uint32_t k = 32 * h + 8 * grp + 4 * t + (li >> 2), c = 8 * wn + 2 * j + ((li >> 1) & 1);
-      fw[h][j].h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-          (GWS_LDS i16x4*)(ws + k * 128 + (c ^ ((li >> 2) << 2) ^ ((grp & 1) << 1)) * 8 + (li & 1) * 4));
+      fw[h][j].h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((GWS_LDS i16x4*)(st + wr[j] + 8192 * h + 1024 * t));
     }
   };
   f32x4 acc[4][4];   // row 16 i + lane % 16, columns 16 j + 4 (lane / 16) .. + 3 of the wavefront's part
@@ -87,50 +112,61 @@ __global__ __launch_bounds__(256) void gemm128_kernel(const GemmArgs g) {
   for (int s = 0; s < D; ++s)
     if ((uint32_t)s < nk) {
 #pragma unroll
-      for (int n = 0; n < 8; ++n) load_n(s, n);
+      for (int n = 0; n < 4; ++n) load_n(s * STG * 2, n);
+      load_advance();
     }
   if (nk >= D) asm volatile("s_waitcnt vmcnt(24)\n\ts_barrier" ::: "memory");
   else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
   for (int n = 0; n < NR; ++n) read_n(0, 0, n);
-  // The order is written out and pinned: a read behind each of the first MFMAs of a half, a load of the step four ahead
-  // behind every second MFMA of the second half (into the stage that the barrier has just released).
-  auto first_half = [&](uint32_t kt) {
+  // The order is written out and pinned: a read behind each of the first MFMAs of a half, two loads of the step four ahead
+  // behind every fourth MFMA of the second half (into the stage that the barrier has just released).
+  auto first_half = [&](uint32_t stage) {
 #pragma unroll
     for (int n = 0; n < 16; ++n) {
       mfma_n(0, n);
       __builtin_amdgcn_sched_barrier(0);
-      if (n < NR) read_n(1, kt, n);
+      if (n < NR) read_n(1, stage, n);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  auto second_half = [&](uint32_t kt, bool more) {
+  auto second_half = [&](uint32_t stage, uint32_t next, bool more) {
 #pragma unroll
     for (int n = 0; n < 16; ++n) {
       mfma_n(1, n);
       __builtin_amdgcn_sched_barrier(0);
-      if (n < NR) read_n(0, kt + 1, n);
-      if (more && (n & 1)) load_n(kt + D, n >> 1);
+      if (n < NR) read_n(0, next, n);
+      if (more && (n & 3) == 3) load_n(stage, n >> 2);
       __builtin_amdgcn_sched_barrier(0);
     }
+    if (more) load_advance();
   };
-  uint32_t kt = 0;
+  uint32_t kt = 0, stage = 0;   // of the ring, in bytes
+  auto after = [](uint32_t s) { return (s + STG * 2) & (D * STG * 2 - 1); };
   for (; kt + D < nk; ++kt) {
-    first_half(kt);
+    first_half(stage);
     // this stage is read; the next step has landed when all but the two steps behind it have
     asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    second_half(kt, true);
+    second_half(stage, after(stage), true);
+    stage = after(stage);
   }
+  // without this the register allocator passes the last accumulators on from register to register in the loop above (20 moves a
+  // K-step and the waits for the MFMAs before them)
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) asm("" : "+a"(acc[i][j]));
   for (; kt < nk; ++kt) {   // everything is on its way: the reads past the last step fetch a stage that nobody multiplies
     if (TK * kt + TK > g.K) {
       // half a step at the end of K: the stage's first half belongs to the step before
 #pragma unroll
       for (int i = 0; i < 4; ++i) fx[0][i].u = fw[0][i].u = u32x4{0, 0, 0, 0};
     }
-    first_half(kt);
+    first_half(stage);
     if (kt + D == nk) asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    second_half(kt, false);
+    second_half(stage, after(stage), false);
+    stage = after(stage);
   }
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the ring is read
 
