@@ -114,6 +114,7 @@ enum class GemmRoute { kStream, kMiddle, kLarge, kNarrow, kSmall };
 struct RoutePlan {   // estimates in us; 1e30: not a shape for that kernel
   StreamPlan stream;
   double middle_us, large_us, narrow_us;
+  int middle_nj;   // the middle tile is 128 x 32 middle_nj
 };
 GemmRoute gemm_route(const GemmArgs& g, int w_is_nk, RoutePlan& plan);
 // the kernel that launch_gemm takes (Y apart from the operands); the values are GWS_GEMM_* of gws_bench.h
@@ -124,7 +125,7 @@ bool gemm256_edge_applicable(const GemmArgs& g);
 int launch_gemm256_edge(const GemmArgs& g, int w_is_nk, hipStream_t stream);
 int launch_gemm256_narrow(const GemmArgs& g, int w_is_nk, hipStream_t stream);   // shapes as gemm256_edge_applicable
 bool gemm128_applicable(const GemmArgs& g);
-int launch_gemm128(const GemmArgs& g, int w_is_nk, hipStream_t stream);
+int launch_gemm128(const GemmArgs& g, int w_is_nk, int nj, hipStream_t stream);   // tiles of 128 x 32 nj, nj 3 or 4
 bool gemm256_applicable(const GemmArgs& g);
 int launch_gemm256(const GemmArgs& g, int w_is_nk, hipStream_t stream);
 // Weights whose forward sampling rides in a GEMM's launch: descriptors as the forward pass fills them, with

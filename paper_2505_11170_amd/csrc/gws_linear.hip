@@ -188,8 +188,14 @@ static int launch_layout(const GemmArgs& g, int w_is_nk, dim3 grid, hipStream_t 
 // weight rides along, so that the sums over K run in the same order in all of them (the middle, large and narrow tiles and
 // the sampling kernel above walk K from end to end; the stream kernels split it).  Estimates in us, fitted to MI355X timings
 // of all of them at some thirty sizes.  Rounds are rounds of workgroups, one per compute unit; a K-step is 64 deep.
-//   middle: 0.42 a K-step ([K x N] 0.45), more in several rounds.  1000 x 800 -> 2304: 10 (stream 17, large 20); 2048 x 2048 -> 2048: 19 (31, 38);
-//     4096 x 3072 -> 768: 27 (45, 54); 4096 x 768 -> 3072: 25 (52, 22)
+//   middle: tiles of 128 x 128 or 128 x 96 (34 sizes in both layouts, the choice 0.03 % from the fastest in the mean).  A K-step of a
+//     128 x 96 tile takes four fifths of the larger one's: they win where they need no more rounds, or three for two.  W [K x N],
+//     128 x 96 and 128 x 128: 4096 x 3072 -> 768 23.7 and 27.7 (256 tiles and 192); 1000 x 768 -> 2304 7.9 and 8.7; 8192 x 2304 -> 768
+//     32.8 and 35.9 (two rounds of either; narrow 37); 2048 x 2048 -> 2048 27 and 18.8 (two rounds and one)
+//     A middle tile takes a product from the larger ones where a 128 x 128 tile at 0.42 a K-step ([K x N] 0.45) would, or where the
+//     estimate is below theirs by more than it errs: 4096 x 2048 -> 1056 28.1 (narrow 33.3), 7000 x 1536 -> 640 23.2 (27.6)
+//   stream or one of the others: against that 128 x 128 tile too: the products that the 128 x 96 tile would take from the stream kernel
+//     (2500 x 2048 -> 512: 14.8, stream 17.3; 512 x 2304 -> 3072: 15.2 and 15.8) would have fp32 sums four times as long
 //   large: 1.05 to 1.25 a K-step, the card's power limit with all compute units at work.  5000 x 2048 -> 2560: 43 (middle 66);
 //     8192 x 2048 -> 2048: 50 (69); 8000 x 768 -> 2304: 41 (39); 6000 x 512 -> 1536: 17 (19)
 //   narrow (256 x 192): four fifths of the large tile's K-step for three quarters of its columns, where that takes fewer or
@@ -198,8 +204,9 @@ static int launch_layout(const GemmArgs& g, int w_is_nk, dim3 grid, hipStream_t 
 GemmRoute gemm_route(const GemmArgs& g, int w_is_nk, RoutePlan& plan) {
   const double cus = compute_units() > 0 ? compute_units() : 256;
   const double nk = ceil(g.K / 64.0);
+  double middle128_us = 1e30;
   auto tiles = [&](double t) { return ceil(g.M / t) * ceil(g.N / t); };
-  plan = RoutePlan{{0, 0, 0, 1e30}, 1e30, 1e30, 1e30};
+  plan = RoutePlan{{0, 0, 0, 1e30}, 1e30, 1e30, 1e30, 4};
   if (gemm256_edge_applicable(g) || gemm256_applicable(g)) {
     const double n = tiles(256.0);
     plan.large_us = 6.0 + ceil(n / cus) * (3.0 + nk * (1.05 + 0.2 * fmin(1.0, n / cus)));
@@ -210,13 +217,22 @@ GemmRoute gemm_route(const GemmArgs& g, int w_is_nk, RoutePlan& plan) {
   }
   if (gemm128_applicable(g)) {
     const double n = tiles(128.0), busy = n > cus ? 1.0 : 0.0;
-    plan.middle_us = 3.3 + ceil(n / cus) * (2.0 + nk * (w_is_nk ? 0.42 + 0.05 * busy : 0.45 + 0.07 * busy));
+    middle128_us = 3.3 + ceil(n / cus) * (2.0 + nk * (w_is_nk ? 0.42 + 0.05 * busy : 0.45 + 0.07 * busy));
+    for (int nj = 3; nj <= 4; ++nj) {
+      const double t = ceil(g.M / 128.0) * ceil(g.N / (32.0 * nj));
+      const double us = 2.4 + ceil(t / cus) * (2.0 + nk * ((nj == 3 ? 0.26 : 0.33) + 0.08 * fmin(1.0, t / cus) + (w_is_nk ? 0.0 : 0.02)));
+      if (us < plan.middle_us) {
+        plan.middle_us = us;
+        plan.middle_nj = nj;
+      }
+    }
   }
   if (stream_applicable(g)) plan.stream = stream_plan(g.M, g.N, g.K, w_is_nk != 0);
-  const double sequential = fmin(plan.large_us, fmin(plan.narrow_us, plan.middle_us));
-  if (plan.stream.p > 0 && plan.stream.us < sequential) return GemmRoute::kStream;
-  if (sequential > 1e29) return GemmRoute::kSmall;
-  return plan.large_us <= sequential ? GemmRoute::kLarge : plan.narrow_us <= sequential ? GemmRoute::kNarrow : GemmRoute::kMiddle;
+  const double larger = fmin(plan.large_us, plan.narrow_us);
+  if (plan.stream.p > 0 && plan.stream.us < fmin(larger, middle128_us)) return GemmRoute::kStream;
+  if (fmin(larger, plan.middle_us) > 1e29) return GemmRoute::kSmall;
+  if (middle128_us < larger || 1.07 * plan.middle_us < larger) return GemmRoute::kMiddle;
+  return plan.large_us <= plan.narrow_us ? GemmRoute::kLarge : GemmRoute::kNarrow;
 }
 
 // Whether sampling in the operand load beats the sampling kernel and the GEMM behind it: one tile of rows of X (every block
@@ -267,7 +283,7 @@ int launch_gemm(const GemmArgs& g, int w_is_nk, int fused, int fmt, hipStream_t 
     form = large_tile ? GemmForm::kLarge : fused ? GemmForm::kAnyShapeSample : GemmForm::kAnyShape;
   switch (form) {
     case GemmForm::kStream: return launch_gemm_stream(g, w_is_nk, plan.stream, stream);
-    case GemmForm::kMiddle: return launch_gemm128(g, w_is_nk, stream);
+    case GemmForm::kMiddle: return launch_gemm128(g, w_is_nk, plan.middle_nj, stream);
     case GemmForm::kLarge: return launch_gemm256(g, w_is_nk, stream);
     case GemmForm::kLargeEdge: return launch_gemm256_edge(g, w_is_nk, stream);
     case GemmForm::kNarrow: return launch_gemm256_narrow(g, w_is_nk, stream);

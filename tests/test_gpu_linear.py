@@ -411,6 +411,27 @@ def test_middle_tile_gemm(M, K, N, w_is_nk):
              mode=gws.LINEAR_IN_OPERAND)
 
 
+# Middle tiles of 128 x 96 (taken here: they and those of 128 x 128 are one round, and theirs is the shorter K-step): a last column
+# tile of one wavefront's part, of two thirds of it and whole, a last row tile of 1 row to 128, 1 to 9 K-steps (four stages) whole
+# and half; against fp32 on the GPU and bit for bit the sampling kernel's Y, which walks K from end to end as well.
+@pytest.mark.parametrize("w_is_nk", [False, True])
+@pytest.mark.parametrize("M,N", [(1024, 2304), (1025, 2272), (897, 2336), (1000, 2336)])
+def test_middle_tile_of_96_columns_at_every_number_of_k_steps(M, N, w_is_nk):
+    for K in [64 * i + 32 * h for i in range(1, 10) for h in (0, 1)]:
+        assert gws.gws_gemm_form(M, K, N, w_is_nk) == gws.GEMM_MIDDLE
+        gen = torch.Generator(device=DEV).manual_seed(K)
+        x = torch.randn(M, K, generator=gen, device=DEV).to(torch.bfloat16)
+        w = (torch.randn(*((N, K) if w_is_nk else (K, N)), generator=gen, device=DEV) * 0.02).to(torch.bfloat16)
+        y = torch.zeros(M + 1, N + 8, dtype=torch.bfloat16, device=DEV)
+        gws.gws_gemm_bf16(x, w, y[:M, :N], w_is_nk=w_is_nk)
+        kn = (w.t().contiguous() if w_is_nk else w).float()
+        ref, mag = x.float() @ kn, x.float().abs() @ kn.abs()
+        # one rounding to BF16 and two fp32 sums of K terms in different orders
+        assert bool(((y[:M, :N].float() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2 * K * 2.0 ** -24 * mag).all()), K
+        assert bool((y[:, N:] == 0).all()) and bool((y[M] == 0).all())
+    run_case(M, 352, N, w_is_nk, gws.FMT_FP8_E4M3, seed_id=93, ldx_pad=8, ldy_pad=8, rows_sel=np.array([0, 127, 128, M - 1]), mode=gws.LINEAR_IN_OPERAND)
+
+
 @pytest.mark.parametrize("w_is_nk", [False, True])
 @pytest.mark.parametrize("M,K,N", [(8191, 96, 1824), (8193, 512, 1760)] + [(7937, 1024 + 32 * i, 1568) for i in range(1, 13, 2)])
 def test_large_tile_gemm_with_edges(M, K, N, w_is_nk):
