@@ -294,38 +294,40 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_sample_kernel(const GemmAr
 }
 
 // Many rows of X, the weight sampled on its way in, K from end to end (the order of the middle and large tiles' sums, so Y is
-// their Y): a workgroup owns 128 rows x 128 columns, a wavefront 32 of the columns.  X comes through LDS in units of 64 k, a
-// ring of two stages that the four wavefronts share, one barrier a unit; the weight's blocks go from a wavefront's
-// registers through its own LDS as above, two a unit.  Bound by the vector ALU work of the sampling, which every 128 rows
-// repeat (about 2 us a unit with one workgroup on a compute unit).  FP8, [K x N] and [N x K], us, with one block at a time before:
-// 4000 x 2304 -> 800 92, 92 -> 70, 72; 4000 x 3072 -> 1024 122, 121 -> 93, 94; 8192 x 512 -> 512 28, 28 -> 23, 23;
-// 8192 x 2048 -> 5632 494, 498 -> 450, 436.
-template <int FMT, bool W_NK>
-__global__ __launch_bounds__(256, 2) void gemm_rows_sample_kernel(const GemmArgs g) {
+// their Y): a workgroup owns 16 MT rows x 32 NW columns (128 x 128 or 256 x 256), a wavefront 32 of the columns.  X comes through
+// LDS in units of 64 k, a ring of stages that the wavefronts share, one barrier a unit; the weight's blocks go from a wavefront's
+// registers through its own LDS as above, two a unit.  Bound by the vector ALU work of the sampling, which every tile of rows
+// repeats: 256 rows halve it.  Of a 256-row workgroup's eight wavefronts two share a SIMD, and the barrier keeps them abreast: the
+// later four multiply a unit after the next barrier (hence a third stage), before they sample, so that one's MFMAs run under the
+// other's sampling.  FP8, [K x N] and [N x K], us, two blocks at a time (one before): 4000 x 2304 -> 800 92, 92 -> 70, 72;
+// 4000 x 3072 -> 1024 122, 121 -> 93, 94; 8192 x 512 -> 512 28, 28 -> 23, 23.  128 x 128 and 256 x 256: 8192 x 2048 -> 5632
+// 462, 424 -> 290, 304 (FP6 548, 508 -> 359, 368; BF16 385, 373 -> 288, 285); 8192 x 2048 -> 2048 160, 161 -> 99, 106.
+template <int MT, int NW, int FMT, bool W_NK>
+__global__ __launch_bounds__(64 * NW, 2) void gemm_rows_sample_kernel(const GemmArgs g) {
   using namespace stream;
-  constexpr int MT = 8, BM = 16 * MT, D = 2, XS = BM * 64, LX = BM / 32;   // load instructions of a wavefront and unit
+  constexpr int BM = 16 * MT, D = NW == 8 ? 3 : 2, XS = BM * 64, LX = BM / (8 * NW);   // load instructions of a wavefront and unit
   __shared__ __attribute__((aligned(1024))) uint16_t ring[D * XS];
-  __shared__ __attribute__((aligned(16))) uint16_t blocks[4 * 2 * 32 * LP];
+  __shared__ __attribute__((aligned(16))) uint16_t blocks[NW * 2 * 32 * LP];
   const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint16_t* blk = blocks + wave * 2 * 32 * LP;
   uint32_t m0, n0;
-  tile_origin(g, BM, 128, false, m0, n0);
+  tile_origin(g, BM, 32 * NW, false, m0, n0);
   n0 += 32 * wave;
   const bool live = n0 < g.N;   // N is a multiple of 32: a wavefront's columns exist or do not
   const uint32_t nu = (g.K + 63) >> 6;
 
   uint32_t xo[LX];
 #pragma unroll
-  for (int i = 0; i < LX; ++i) {   // rows BM / 4 wave + 8 i + lane / 8
-    const uint32_t row = BM / 4 * wave + 8 * i + (lane >> 3);
+  for (int i = 0; i < LX; ++i) {   // rows 8 LX wave + 8 i + lane / 8
+    const uint32_t row = 8 * LX * wave + 8 * i + (lane >> 3);
     xo[i] = (umin(row, g.M - 1 - m0) * g.ldx + ((lane & 7) ^ ((row >> 1) & 7)) * 8) * 2;
   }
   const GWS_GLOBAL char* xb = (const GWS_GLOBAL char*)(g.x + (size_t)m0 * g.ldx);
-  auto load_x = [&](uint32_t u) {
+  auto load_x = [&](uint32_t u, uint32_t slot) {
     const uint32_t k0 = umin(64 * u, g.K - 64);   // the half unit at the end of K is fetched as the second half of a whole one
 #pragma unroll
-    for (int i = 0; i < LX; ++i) direct(xb + (size_t)k0 * 2, xo[i], ring + (u % D) * XS + (wave * LX + i) * 512);
+    for (int i = 0; i < LX; ++i) direct(xb + (size_t)k0 * 2, xo[i], ring + slot * XS + (wave * LX + i) * 512);
   };
   const Blocks<FMT, W_NK, 2> w(g, live ? n0 : 0);   // a wavefront past the edge reads the first columns and multiplies nothing
   typename Blocks<FMT, W_NK, 2>::Raw nxt;
@@ -334,18 +336,12 @@ __global__ __launch_bounds__(256, 2) void gemm_rows_sample_kernel(const GemmArgs
 #pragma unroll
   for (int i = 0; i < MT; ++i) acc[i][0] = acc[i][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   w.load(g, 0, nxt);
-  load_x(0);
-  for (uint32_t u = 0; u < nu; ++u) {
-    // this unit, requested a unit's sampling ago, has landed, and every wavefront is past its reads of the other stage
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    if (u + 1 < nu) load_x(u + 1);
-    if (!live) continue;
-    const uint16_t* xs = ring + (u % D) * XS;
+  load_x(0, 0);
+  uint32_t slot = 0, next = 1, last = D - 1;   // of this unit, the next one and the one before
+  Frag8 f[2][2];
+  auto multiply = [&](uint32_t u, uint32_t at) __attribute__((always_inline)) {
+    const uint16_t* xs = ring + at * XS;
     const bool half = 64 * u + 64 > g.K;
-    const typename Blocks<FMT, W_NK, 2>::Raw cur = nxt;
-    w.load(g, umin(u + 1, nu - 1), nxt);
-    Frag8 f[2][2];
-    w.sample(g, u, cur, m0 == 0, blk, f);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       if (h == 1 && half) break;   // one block, whose k are the second half of the stage
@@ -358,8 +354,25 @@ __global__ __launch_bounds__(256, 2) void gemm_rows_sample_kernel(const GemmArgs
         for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[h][j].v, x.v, acc[i][j], 0, 0, 0);
       }
     }
+  };
+  const bool late = NW == 8 && wave >= 4;   // uniform
+  for (uint32_t u = 0; u < nu; ++u) {
+    // this unit, requested a unit's sampling ago, has landed, and every wavefront is past its reads of the stage filled next
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (u + 1 < nu) load_x(u + 1, next);
+    if (live) {
+      if (late && u > 0) multiply(u - 1, last);
+      const typename Blocks<FMT, W_NK, 2>::Raw cur = nxt;
+      w.load(g, umin(u + 1, nu - 1), nxt);
+      w.sample(g, u, cur, m0 == 0, blk, f);
+      if (!late) multiply(u, slot);
+    }
+    last = slot;
+    slot = next;
+    next = next + 1 == D ? 0 : next + 1;
   }
   if (!live) return;
+  if (late) multiply(nu - 1, last);
 #pragma unroll
   for (int i = 0; i < MT; ++i) {   // row 16 i + lane % 16, columns 16 j + 4 (lane / 16) .. + 3
     const uint32_t row = m0 + 16 * i + li;
@@ -443,18 +456,36 @@ static void launch_sampled_fmt(const GemmArgs& g, int w_is_nk, int p, hipStream_
   else launch_sampled<4, 8, FMT>(g, w_is_nk, s);
 }
 
+template <int MT, int NW, int FMT>
+static void launch_rows_tile(const GemmArgs& g, int w_is_nk, hipStream_t s) {
+  const dim3 grid(((g.M + 16 * MT - 1) / (16 * MT)) * ((g.N + 32 * NW - 1) / (32 * NW)));
+  if (w_is_nk) hipLaunchKernelGGL((gemm_rows_sample_kernel<MT, NW, FMT, true>), grid, dim3(64 * NW), 0, s, g);
+  else hipLaunchKernelGGL((gemm_rows_sample_kernel<MT, NW, FMT, false>), grid, dim3(64 * NW), 0, s, g);
+}
+// 256 x 256 tiles (a workgroup of eight wavefronts has the compute unit) or 128 x 128 (two of four share it, or one has it).  us a
+// unit of 64 k and round, FP8: 3.1; 2.45 with two and 1.85 with one.  FP6 and BF16 stand in the same proportion.  8192 x 2048 -> 2048
+// (1 round, 2 of two) 99 and 160 us; 5479 x 1184 -> 1920 (1, 1 and one of one) 65 and 87; 6000 x 1536 -> 3072 (2, 2 and one of one) 161
+// and 169; 4096 x 1024 -> 2048 (1, 1) 56 and 51; 2946 x 2592 -> 2112 (1, 1) 121 and 112; 4000 x 2304 -> 800 (1, one of one) 102 and 67.
+static bool rows_large(const GemmArgs& g) {
+  const uint64_t cus = compute_units() > 0 ? compute_units() : 256;
+  const uint64_t n = (uint64_t)((g.M + 127) / 128) * ((g.N + 127) / 128), rest = n % (2 * cus);
+  const uint64_t n256 = (uint64_t)((g.M + 255) / 256) * ((g.N + 255) / 256);
+  const double small = 2.45 * (double)(n / (2 * cus)) + (rest == 0 ? 0.0 : rest <= cus ? 1.85 : 2.45);
+  return g.K > 64 && 3.1 * (double)((n256 + cus - 1) / cus) < small;   // one unit: 14.3 and 14.1 us for 4224 x 64 -> 2048
+}
 template <int FMT>
 static void launch_rows(const GemmArgs& g, int w_is_nk, hipStream_t s) {
-  const dim3 grid(((g.M + 127) / 128) * ((g.N + 127) / 128));
-  if (w_is_nk) hipLaunchKernelGGL((gemm_rows_sample_kernel<FMT, true>), grid, dim3(256), 0, s, g);
-  else hipLaunchKernelGGL((gemm_rows_sample_kernel<FMT, false>), grid, dim3(256), 0, s, g);
+  if (rows_large(g)) launch_rows_tile<16, 8, FMT>(g, w_is_nk, s);
+  else launch_rows_tile<8, 4, FMT>(g, w_is_nk, s);
 }
 
-// Two workgroups run on a compute unit: between one and one and a half rounds of them the 128 x 128 x 32 kernel, which packs
-// them closer, is as fast for [N x K] weights, which it need not transpose.
+// Two workgroups of 128 rows run on a compute unit: between one and one and a half rounds of them the 128 x 128 x 32 kernel, which
+// packs them closer, is faster for [N x K] weights, which it need not transpose, where K is short.  4001 x K -> 2144, that kernel and
+// 256 x 256 here: K = 160 17.5 and 17.9 us, 320 27.6 and 24.0, 544 43 and 36, 768 57 and 44, 2048 139 and 100.  The line is not at
+// the crossing but where the difference is worth more than a launch.
 bool rows_sample_applicable(const GemmArgs& g, int w_is_nk) {
   const uint64_t cus = compute_units() > 0 ? compute_units() : 256, n = (uint64_t)((g.M + 127) / 128) * ((g.N + 127) / 128);
-  return stream_applicable(g) && !(w_is_nk && n > 2 * cus && n <= 3 * cus);
+  return stream_applicable(g) && !(w_is_nk && n > 2 * cus && n <= 3 * cus && g.K < 576);
 }
 
 int launch_gemm_rows_sample(const GemmArgs& g, int w_is_nk, int fmt, hipStream_t s) {
