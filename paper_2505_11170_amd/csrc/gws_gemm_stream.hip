@@ -166,10 +166,9 @@ struct Blocks {
     }
   }
 
-  // The sampled blocks as fragments f[block][column half] (16 outputs, 32 k), turned through `blk`, B x 32 x LP elements of the
-  // wavefront's own LDS; writer: this wavefront stores w_hat and scale (if wanted).
-  __device__ __forceinline__ void sample(const GemmArgs& g, uint32_t step, const Raw& x, bool writer, uint16_t* blk, Frag8 (&f)[B][2]) const {
-    const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4;
+  // The sampled blocks to `blk`, B x 32 x LP elements of LDS; writer: this wavefront stores w_hat and scale (if wanted).
+  __device__ __forceinline__ void stage(const GemmArgs& g, uint32_t step, const Raw& x, bool writer, uint16_t* blk) const {
+    const uint32_t lane = threadIdx.x & 63;
     Noise n[B][2];   // [block][group]
     if (W_NK) {
       PhiloxCols pc[B];
@@ -220,21 +219,29 @@ struct Blocks {
     }
 #pragma unroll
     for (int k = 0; k < 2 * B; ++k) *(u32x4*)(blk + ((k >> 1) * 32 + r + 16 * (k & 1)) * LP + 8 * q) = v[k >> 1][k & 1];
+  }
+  // column half j of a staged block
+  static __device__ __forceinline__ Frag8 fragment(const uint16_t* p, int j) {
+    const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4;
+    Frag8 f;
+    if (W_NK) {
+      f.u = *(const u32x4*)(p + (16 * j + li) * LP + 8 * grp);
+    } else {   // transposing read: lanes 4 t .. 4 t + 3 of 16 point at 16 outputs of row k0 + t
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+        f.h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((GWS_LDS i16x4*)(p + (8 * grp + 4 * t + (li >> 2)) * LP + 16 * j + 4 * (li & 3)));
+    }
+    return f;
+  }
+  // the sampled blocks as fragments f[block][column half] (16 outputs, 32 k)
+  __device__ __forceinline__ void sample(const GemmArgs& g, uint32_t step, const Raw& x, bool writer, uint16_t* blk, Frag8 (&f)[B][2]) const {
+    stage(g, step, x, writer, blk);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wavefront's own writes have landed
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int h = 0; h < B; ++h)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const uint16_t* p = blk + h * 32 * LP;
-        if (W_NK) {
-          f[h][j].u = *(const u32x4*)(p + (16 * j + li) * LP + 8 * grp);
-        } else {   // transposing read: lanes 4 t .. 4 t + 3 of 16 point at 16 outputs of row k0 + t
-#pragma unroll
-          for (int t = 0; t < 2; ++t)
-            f[h][j].h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((GWS_LDS i16x4*)(p + (8 * grp + 4 * t + (li >> 2)) * LP + 16 * j + 4 * (li & 3)));
-        }
-      }
+      for (int j = 0; j < 2; ++j) f[h][j] = fragment(blk + h * 32 * LP, j);
   }
 };
 
@@ -294,18 +301,17 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_sample_kernel(const GemmAr
 }
 
 // Many rows of X, the weight sampled on its way in, K from end to end (the order of the middle and large tiles' sums, so Y is
-// their Y): a workgroup owns 16 MT rows x 32 NW columns (128 x 128 or 256 x 256), a wavefront 32 of the columns.  X comes through
-// LDS in units of 64 k, a ring of stages that the wavefronts share, one barrier a unit; the weight's blocks go from a wavefront's
-// registers through its own LDS as above, two a unit.  Bound by the vector ALU work of the sampling, which every tile of rows
-// repeats: 256 rows halve it.  Of a 256-row workgroup's eight wavefronts two share a SIMD, and the barrier keeps them abreast: the
-// later four multiply a unit after the next barrier (hence a third stage), before they sample, so that one's MFMAs run under the
-// other's sampling.  FP8, [K x N] and [N x K], us, two blocks at a time (one before): 4000 x 2304 -> 800 92, 92 -> 70, 72;
-// 4000 x 3072 -> 1024 122, 121 -> 93, 94; 8192 x 512 -> 512 28, 28 -> 23, 23.  128 x 128 and 256 x 256: 8192 x 2048 -> 5632
-// 462, 424 -> 290, 304 (FP6 548, 508 -> 359, 368; BF16 385, 373 -> 288, 285); 8192 x 2048 -> 2048 160, 161 -> 99, 106.
-template <int MT, int NW, int FMT, bool W_NK>
-__global__ __launch_bounds__(64 * NW, 2) void gemm_rows_sample_kernel(const GemmArgs g) {
+// their Y): a workgroup owns 256 rows x 256 columns, a wavefront 32 of the columns.  X comes through LDS in units of 64 k, a ring of
+// stages that the wavefronts share, one barrier a unit; the weight's blocks go from a wavefront's registers through its own LDS as
+// above, two a unit.  Bound by the vector ALU work of the sampling, which every tile of rows repeats (128 rows a tile: twice of
+// it).  Two of the eight wavefronts share a SIMD, and the barrier keeps them abreast: the later four multiply a unit after the next
+// barrier (hence a third stage), before they sample, so that one's MFMAs run under the other's sampling.  FP8, [K x N] and [N x K],
+// us, tiles of 128 x 128 by four wavefronts and this: 8192 x 2048 -> 5632 462, 424 -> 290, 304 (FP6 548, 508 -> 359, 368; BF16 385,
+// 373 -> 288, 285); 8192 x 2048 -> 2048 160, 161 -> 99, 106.
+template <int FMT, bool W_NK>
+__global__ __launch_bounds__(512, 2) void gemm_rows_sample_kernel(const GemmArgs g) {
   using namespace stream;
-  constexpr int BM = 16 * MT, D = NW == 8 ? 3 : 2, XS = BM * 64, LX = BM / (8 * NW);   // load instructions of a wavefront and unit
+  constexpr int MT = 16, NW = 8, BM = 16 * MT, D = 3, XS = BM * 64, LX = BM / (8 * NW);   // LX: load instructions of a wavefront and unit
   __shared__ __attribute__((aligned(1024))) uint16_t ring[D * XS];
   __shared__ __attribute__((aligned(16))) uint16_t blocks[NW * 2 * 32 * LP];
   const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4;
@@ -355,7 +361,7 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_rows_sample_kernel(const Gemm
       }
     }
   };
-  const bool late = NW == 8 && wave >= 4;   // uniform
+  const bool late = wave >= 4;   // uniform
   for (uint32_t u = 0; u < nu; ++u) {
     // this unit, requested a unit's sampling ago, has landed, and every wavefront is past its reads of the stage filled next
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -376,6 +382,87 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_rows_sample_kernel(const Gemm
 #pragma unroll
   for (int i = 0; i < MT; ++i) {   // row 16 i + lane % 16, columns 16 j + 4 (lane / 16) .. + 3
     const uint32_t row = m0 + 16 * i + li;
+    if (row < g.M) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        *(u32x2*)(g.y + (size_t)row * g.ldy + n0 + 16 * j + 4 * grp) =
+            u32x2{pack_bf16_rne(acc[i][j][0], acc[i][j][1]), pack_bf16_rne(acc[i][j][2], acc[i][j][3])};
+    }
+  }
+}
+
+// The same with tiles of 128 x 128, for fewer of them.  Of the eight wavefronts two share the columns: each samples one block of a
+// unit and multiplies half of the rows by both blocks, a unit later, past the barrier that makes both visible.  Of the two
+// wavefronts of a SIMD one multiplies first, one samples first.  Four wavefronts that sampled and multiplied for themselves waited
+// for their own serial chains.  us, four wavefronts and this, one workgroup on a compute unit: 4000 x 2304 -> 800 68 -> 53 (FP6 84 ->
+// 66, BF16 63 -> 47; [N x K] 69 -> 54), 4000 x 3072 -> 1024 91 -> 72, 8192 x 512 -> 512 19.5 -> 16.8; two: 4096 x 1024 -> 2048 47 -> 44,
+// 2862 x 1184 -> 1920 53 -> 50; several rounds of two: 8192 x 2048 -> 2048 160 -> 147.
+template <int FMT, bool W_NK>
+__global__ __launch_bounds__(512, 2) void gemm_rows_pair_sample_kernel(const GemmArgs g) {
+  using namespace stream;
+  constexpr int MT = 4, BM = 128, XS = BM * 64, LX = 2;   // row tiles of a wavefront; elements of a stage; load instructions of a wavefront
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[2 * XS];
+  __shared__ __attribute__((aligned(16))) uint16_t blocks[2][4][2][32 * LP];   // [unit][32 columns][block]
+  const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rm = wave >> 2, cn = wave & 3;
+  uint32_t m0, n0;
+  tile_origin(g, BM, 128, false, m0, n0);
+  n0 += 32 * cn;
+  const bool live = n0 < g.N;   // N is a multiple of 32: a wavefront's columns exist or do not
+  const uint32_t nu = (g.K + 63) >> 6;
+
+  uint32_t xo[LX];
+#pragma unroll
+  for (int i = 0; i < LX; ++i) {   // rows 16 wave + 8 i + lane / 8
+    const uint32_t row = 16 * wave + 8 * i + (lane >> 3);
+    xo[i] = (umin(row, g.M - 1 - m0) * g.ldx + ((lane & 7) ^ ((row >> 1) & 7)) * 8) * 2;
+  }
+  const GWS_GLOBAL char* xb = (const GWS_GLOBAL char*)(g.x + (size_t)m0 * g.ldx);
+  const Blocks<FMT, W_NK, 1> w(g, live ? n0 : 0);   // a wavefront past the edge reads the first columns and multiplies nothing
+  typename Blocks<FMT, W_NK, 1>::Raw nxt;
+  f32x4 acc[MT][2];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) acc[i][0] = acc[i][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+  auto multiply = [&](uint32_t u) __attribute__((always_inline)) {
+    const uint16_t* xs = ring + (u & 1) * XS;
+    const bool half = 64 * u + 64 > g.K;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (h == 1 && half) break;   // one block, whose k are the second half of the stage
+      const int hx = half ? 1 : h;
+      Frag8 f[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) f[j] = Blocks<FMT, W_NK, 1>::fragment(blocks[u & 1][cn][h], j);
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        Frag8 x;
+        x.u = *(const u32x4*)(xs + (64 * rm + 16 * i + li) * 64 + (((4 * hx + grp) ^ ((li >> 1) & 7)) * 8));
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[j].v, x.v, acc[i][j], 0, 0, 0);
+      }
+    }
+  };
+  w.load(g, rm, nxt);
+  for (uint32_t u = 0; u < nu; ++u) {
+    // the unit before has landed and is sampled, and every wavefront is past its reads of the stages filled next
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    const uint32_t k0 = umin(64 * u, g.K - 64);   // the half unit at the end of K is fetched as the second half of a whole one
+#pragma unroll
+    for (int i = 0; i < LX; ++i) direct(xb + (size_t)k0 * 2, xo[i], ring + (u & 1) * XS + (wave * LX + i) * 512);
+    if (!live) continue;
+    if (rm == 1 && u > 0) multiply(u - 1);
+    const typename Blocks<FMT, W_NK, 1>::Raw cur = nxt;
+    w.load(g, 2 * umin(u + 1, nu - 1) + rm, nxt);
+    w.stage(g, 2 * u + rm, cur, m0 == 0, blocks[u & 1][cn][rm]);
+    if (rm == 0 && u > 0) multiply(u - 1);
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  if (!live) return;
+  multiply(nu - 1);
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {   // row 16 i + lane % 16, columns 16 j + 4 (lane / 16) .. + 3
+    const uint32_t row = m0 + 64 * rm + 16 * i + li;
     if (row < g.M) {
 #pragma unroll
       for (int j = 0; j < 2; ++j)
@@ -456,27 +543,25 @@ static void launch_sampled_fmt(const GemmArgs& g, int w_is_nk, int p, hipStream_
   else launch_sampled<4, 8, FMT>(g, w_is_nk, s);
 }
 
-template <int MT, int NW, int FMT>
-static void launch_rows_tile(const GemmArgs& g, int w_is_nk, hipStream_t s) {
-  const dim3 grid(((g.M + 16 * MT - 1) / (16 * MT)) * ((g.N + 32 * NW - 1) / (32 * NW)));
-  if (w_is_nk) hipLaunchKernelGGL((gemm_rows_sample_kernel<MT, NW, FMT, true>), grid, dim3(64 * NW), 0, s, g);
-  else hipLaunchKernelGGL((gemm_rows_sample_kernel<MT, NW, FMT, false>), grid, dim3(64 * NW), 0, s, g);
-}
-// 256 x 256 tiles (a workgroup of eight wavefronts has the compute unit) or 128 x 128 (two of four share it, or one has it).  us a
-// unit of 64 k and round, FP8: 3.1; 2.45 with two and 1.85 with one.  FP6 and BF16 stand in the same proportion.  8192 x 2048 -> 2048
-// (1 round, 2 of two) 99 and 160 us; 5479 x 1184 -> 1920 (1, 1 and one of one) 65 and 87; 6000 x 1536 -> 3072 (2, 2 and one of one) 161
-// and 169; 4096 x 1024 -> 2048 (1, 1) 56 and 51; 2946 x 2592 -> 2112 (1, 1) 121 and 112; 4000 x 2304 -> 800 (1, one of one) 102 and 67.
+// 256 x 256 tiles (one on a compute unit) or 128 x 128 (two share it, or one has it).  us a unit of 64 k and round, FP8: 3.1; 2.25 with
+// two and 1.45 with one.  FP6 and BF16 stand in the same proportion.  8192 x 2048 -> 2048 (1 round, 2 of two) 99 and 147 us; 5113 x
+// 2592 -> 1664 (1, 1 and one of one) 132 and 146; 5497 x 1248 -> 4096 (2, 3 of two) 136 and 140; 6000 x 1536 -> 3072 (2, 2 and one of one)
+// 159 and 141; 4096 x 1024 -> 2048 (1, 1) 56 and 44; 4000 x 2304 -> 800 (1, one of one) 102 and 53.
 static bool rows_large(const GemmArgs& g) {
   const uint64_t cus = compute_units() > 0 ? compute_units() : 256;
   const uint64_t n = (uint64_t)((g.M + 127) / 128) * ((g.N + 127) / 128), rest = n % (2 * cus);
   const uint64_t n256 = (uint64_t)((g.M + 255) / 256) * ((g.N + 255) / 256);
-  const double small = 2.45 * (double)(n / (2 * cus)) + (rest == 0 ? 0.0 : rest <= cus ? 1.85 : 2.45);
+  const double small = 2.25 * (double)(n / (2 * cus)) + (rest == 0 ? 0.0 : rest <= cus ? 1.45 : 2.25);
   return g.K > 64 && 3.1 * (double)((n256 + cus - 1) / cus) < small;   // one unit: 14.3 and 14.1 us for 4224 x 64 -> 2048
 }
 template <int FMT>
 static void launch_rows(const GemmArgs& g, int w_is_nk, hipStream_t s) {
-  if (rows_large(g)) launch_rows_tile<16, 8, FMT>(g, w_is_nk, s);
-  else launch_rows_tile<8, 4, FMT>(g, w_is_nk, s);
+  const uint32_t t = rows_large(g) ? 256 : 128;
+  const dim3 grid(((g.M + t - 1) / t) * ((g.N + t - 1) / t));
+  if (t == 256 && w_is_nk) hipLaunchKernelGGL((gemm_rows_sample_kernel<FMT, true>), grid, dim3(512), 0, s, g);
+  else if (t == 256) hipLaunchKernelGGL((gemm_rows_sample_kernel<FMT, false>), grid, dim3(512), 0, s, g);
+  else if (w_is_nk) hipLaunchKernelGGL((gemm_rows_pair_sample_kernel<FMT, true>), grid, dim3(512), 0, s, g);
+  else hipLaunchKernelGGL((gemm_rows_pair_sample_kernel<FMT, false>), grid, dim3(512), 0, s, g);
 }
 
 // Two workgroups of 128 rows run on a compute unit: between one and one and a half rounds of them the 128 x 128 x 32 kernel, which

@@ -475,10 +475,11 @@ def test_narrow_large_tiles_at_every_number_of_k_steps(M, N, w_is_nk):
 
 # Tiles of 256 x 256 of the same (more than two 128 x 128 workgroups a compute unit, one round of these): a last row tile of 1 and 255
 # rows, a last column tile of one wavefront, six and eight, 2 to 10 units whole and half, the [N x K] weights that K brings here;
-# Y and w_hat bit for bit
+# Y and w_hat bit for bit.  The first four: tiles of 128 x 128 (one workgroup a compute unit and two), last row tiles of one
+# wavefront's half and one row, a last column tile of one wavefront, 1 to 11 units whole and half.
 @pytest.mark.parametrize("w_is_nk", [False, True])
-@pytest.mark.parametrize("M,K,N", [(4097, 96, 3616), (7935, 128, 1984), (7937, 160, 2016), (8192, 416, 2048), (4097, 576, 2144), (4001, 608, 2208)])
-def test_sampling_in_the_operand_load_of_256_rows(M, K, N, w_is_nk):
+@pytest.mark.parametrize("M,K,N", [(2240, 96, 1056), (2241, 672, 1120), (3969, 64, 1952), (7937, 160, 416), (4097, 96, 3616), (7935, 128, 1984), (7937, 160, 2016), (8192, 416, 2048), (4097, 576, 2144), (4001, 608, 2208)])
+def test_sampling_in_the_operand_load_of_256_rows_and_by_pairs(M, K, N, w_is_nk):
     assert gws.gws_gemm_form(M, K, N, w_is_nk, sampled=1, ldx=K + 8) == gws.GEMM_ROWS_SAMPLE
     for fmt in (gws.FMT_BF16, gws.FMT_FP8_E4M3, gws.FMT_FP6_E3M2):
         run_case(M, K, N, w_is_nk, fmt, seed_id=95, ldx_pad=8, ldy_pad=8, rows_sel=np.array([0, 127, 128, 255, 256, M // 2, M - 1]), mode=gws.LINEAR_IN_OPERAND)
