@@ -121,12 +121,14 @@ __device__ __forceinline__ void walk_tiles(const ARGS& a, const TileDesc& d, uin
 // with 8, 7, 6, 5, 4 and 2 wavefronts a SIMD 927, 923, 891, 891, 876 and 1004 us, of the 124M model 87, 87, 85, 85, 83, 95.
 // The registers that this leaves (128) let the compiler interleave a tile's groups: MX-FP6 of 352 M parameters 195 -> 182 us.
 #define GWS_FOUR_WAVES __attribute__((amdgpu_waves_per_eu(4, 4)))
+// The uniform basis on weights of any shape: up to eight, as measured: 45 M parameters in FP8 49 us with as many as fit, 54 with four; 67 M 77 and 83; 147 M 182 either way.
+#define GWS_WAVES_ANY_SHAPE(basis) __attribute__((amdgpu_waves_per_eu(4, (basis) == kBasisUniform ? 8 : 4)))
 
 // MX: write element codes and E8M0 block scales instead of the BF16 container.
 // STREAM: see load16.
 // BASIS: the method's bit-built noise, or one of the two comparison bases.
 template <int FMT, bool MX, int STREAM, int BASIS, class ARGS>
-__global__ __launch_bounds__(kThreads) GWS_FOUR_WAVES void sample_fwd_kernel(const ARGS a) {
+__global__ __launch_bounds__(kThreads) GWS_WAVES_ANY_SHAPE(BASIS) void sample_fwd_kernel(const ARGS a) {
   uint32_t byg, bxg;
   const TileDesc d = locate(a, byg, bxg);
   const uint32_t lane = threadIdx.x & 63;
@@ -194,7 +196,7 @@ __device__ __forceinline__ void bwd_tile(const TileDesc& d, const Tile& t, const
 }
 
 template <int STREAM, int BASIS, class ARGS>
-__global__ __launch_bounds__(kThreads) GWS_FOUR_WAVES void sample_bwd_kernel(const ARGS a) {
+__global__ __launch_bounds__(kThreads) GWS_WAVES_ANY_SHAPE(BASIS) void sample_bwd_kernel(const ARGS a) {
   uint32_t byg, bxg;
   const TileDesc d = locate(a, byg, bxg);
   const uint32_t lane = threadIdx.x & 63;
