@@ -68,7 +68,7 @@ __device__ __forceinline__ void sample_tiles(uint32_t step_lo, uint32_t step_hi,
         const uint32_t by = id / per_row, cb = (id - by * per_row) * 64;
         TileNoise<kBasisBits> n[1];
         draw_noise(step_lo, step_hi, d, tile_rows(d, by, lane, step_lo), cb, lane, n);
-        fwd_tile<FMT, true, kKeep, false, true>(d, t[j], n[0], by, cb, lane, bv[j]);
+        fwd_tile<FMT, true, kKeep>(d, t[j], n[0], by, cb, lane, bv[j]);
       }
     }
   }
@@ -123,7 +123,7 @@ __device__ __forceinline__ void ride_tiles(uint32_t step_lo, uint32_t step_hi, c
     bool unsafe = false;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      bs[j] = tile_scale<FMT, true, false, true, false>(d, cur.t[j], by, cb0 + 64 * j, lane, cur.bv[j]);
+      bs[j] = tile_scale<FMT, true, false, false>(d, cur.t[j], by, cb0 + 64 * j, lane, cur.bv[j]);
       unsafe |= !bs[j].hw_safe;
     }
     TileNoise<kBasisBits> noise[2][2];

@@ -134,9 +134,15 @@ __global__ __launch_bounds__(kThreads) GWS_WAVES_ANY_SHAPE(BASIS) void sample_fw
   const uint32_t lane = threadIdx.x & 63;
   walk_tiles<STREAM>(a, d, byg, bxg, [&](uint32_t by, uint32_t col_base, Tile& t) {
     TileNoise<BASIS> n[1];
-    draw_noise(a.step_lo, a.step_hi, d, tile_rows(d, by, lane, a.step_lo), col_base, lane, n);
-    if (t.full) fwd_tile<FMT, true, STREAM, MX, false, BASIS>(d, t, n[0], by, col_base, lane);
-    else fwd_tile<FMT, false, STREAM, MX, false, BASIS>(d, t, n[0], by, col_base, lane);
+    if (t.full) {   // the block's parameter with the tile: behind the noise, its latency would be paid in full
+      const float bt = *at_byte(global_ptr<float>(d.p2) + ((size_t)by * ((d.cols + 31) >> 5) + (col_base >> 5)), lane & 4);
+      draw_noise(a.step_lo, a.step_hi, d, tile_rows(d, by, lane, a.step_lo), col_base, lane, n);
+      fwd_tile<FMT, true, STREAM, MX, BASIS>(d, t, n[0], by, col_base, lane, bt);
+    } else {
+      const float bt = lane_bt(d, by, col_base, lane);
+      draw_noise_edge(a.step_lo, a.step_hi, d, by, col_base, lane, n[0]);
+      fwd_tile<FMT, false, STREAM, MX, BASIS>(d, t, n[0], by, col_base, lane, bt);
+    }
   });
 }
 
@@ -203,11 +209,12 @@ __global__ __launch_bounds__(kThreads) GWS_WAVES_ANY_SHAPE(BASIS) void sample_bw
   const bool copy = d.p1 != nullptr;  // NULL: the pass-through is an alias
   walk_tiles<STREAM>(a, d, byg, bxg, [&](uint32_t by, uint32_t col_base, Tile& t) {
     TileNoise<BASIS> n[1];
-    draw_noise(a.step_lo, a.step_hi, d, tile_rows(d, by, lane, a.step_lo), col_base, lane, n);
     if (t.full) {
+      draw_noise(a.step_lo, a.step_hi, d, tile_rows(d, by, lane, a.step_lo), col_base, lane, n);
       if (copy) bwd_tile<true, true, STREAM, BASIS>(d, t, n[0], by, col_base, lane);
       else bwd_tile<true, false, STREAM, BASIS>(d, t, n[0], by, col_base, lane);
     } else {
+      draw_noise_edge(a.step_lo, a.step_hi, d, by, col_base, lane, n[0]);
       if (copy) bwd_tile<false, true, STREAM, BASIS>(d, t, n[0], by, col_base, lane);
       else bwd_tile<false, false, STREAM, BASIS>(d, t, n[0], by, col_base, lane);
     }
@@ -224,7 +231,7 @@ __device__ __forceinline__ void store_mx_rows(const TileDesc& d, Tile& t, const 
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, gc = lane & 7, r0 = lane >> 3;
   constexpr uint32_t kRow = FMT == 1 ? kTileCols : kTileCols / 8 * 6, kPitch = kRow + 16, kChunks = kRow / 16;
   __shared__ __attribute__((aligned(16))) char staged[32 * kPitch];
-  const BlockScale b = tile_scale<FMT, true, true, true, true>(d, t, by, bx * kTileCols + wave * 64, lane, bt);
+  const BlockScale b = tile_scale<FMT, true, true, true>(d, t, by, bx * kTileCols + wave * 64, lane, bt);
   tile_sum<true>(t, b, n);
   if constexpr (FMT == 1) {
     const bool hw = __builtin_amdgcn_ballot_w64(!b.hw_safe) == 0;
@@ -273,7 +280,7 @@ __global__ __launch_bounds__(kThreads) GWS_FOUR_WAVES void sample_fwd_full_kerne
   draw_noise(a.step_lo, a.step_hi, d, tile_rows(d, byg, lane, a.step_lo), col_base, lane, n);
   __builtin_amdgcn_sched_barrier(0);   // the noise is drawn while the loads are in flight
   if constexpr (MX) store_mx_rows<FMT, STREAM>(d, t, n[0], byg, bxg, bt);
-  else fwd_tile<FMT, true, STREAM, MX, true, BASIS>(d, t, n[0], byg, col_base, lane, bt);
+  else fwd_tile<FMT, true, STREAM, MX, BASIS>(d, t, n[0], byg, col_base, lane, bt);
 }
 
 // The backward pass for the shape the method meets in a model: every tensor of the launch has whole tiles only

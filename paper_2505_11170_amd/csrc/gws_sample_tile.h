@@ -47,6 +47,7 @@ __device__ __forceinline__ void store_partial(GWS_GLOBAL uint16_t* dst, const u3
 struct Tile {
   u32x4 v[4];
   int nv[4];   // valid elements per group (8 everywhere on a full tile)
+  uint32_t rows;   // of the tile that exist (unset on a full tile)
   bool full;   // the 32x64 tile lies inside the tensor: no validity tests needed
 };
 
@@ -87,6 +88,7 @@ __device__ __forceinline__ Tile load_tile(const GWS_GLOBAL uint16_t* __restrict_
     return load_full_tile<STREAM>(src, d, by, col_base, lane);
   Tile t;
   t.full = false;
+  t.rows = d.rows - row_base;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const uint32_t row = row_base + (lane >> 3) + 8 * i;
@@ -107,6 +109,21 @@ template <>
 struct TileNoise<kBasisBits> {
   Noise x[4];
 };
+
+// The lane's block parameter, 0 for a block past the right edge.
+__device__ __forceinline__ float lane_bt(const TileDesc& d, uint32_t by, uint32_t col_base, uint32_t lane) {
+  const uint32_t nbc = (d.cols + 31) >> 5, bcol = (col_base >> 5) + ((lane >> 2) & 1);
+  return bcol < nbc ? global_ptr<float>(d.p2)[(size_t)by * nbc + bcol] : 0.0f;
+}
+
+// Pins the noise where it is drawn; of the random words those that the basis uses (the uniform basis two of four: the others are
+// then not computed).
+__device__ __forceinline__ void pin_noise(Noise& n) { asm volatile("" : "+v"(n.c)); }
+template <int BASIS>
+__device__ __forceinline__ void pin_noise(Philox4& x) {
+  asm volatile("" : "+v"(x.x0), "+v"(x.x1));
+  if (BASIS != kBasisUniform) asm volatile("" : "+v"(x.x2), "+v"(x.x3));
+}
 
 __device__ __forceinline__ PhiloxRows tile_rows(const TileDesc& d, uint32_t by, uint32_t lane, uint32_t step_lo) {
   uint32_t rows[4];
@@ -136,9 +153,39 @@ __device__ __forceinline__ void draw_noise(uint32_t step_lo, uint32_t step_hi, c
   for (int t = 0; t < T; ++t)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      if constexpr (BASIS == kBasisBits) asm volatile("" : "+v"(n[t].x[i].c));
-      else asm volatile("" : "+v"(n[t].x[i].x0), "+v"(n[t].x[i].x1), "+v"(n[t].x[i].x2), "+v"(n[t].x[i].x3));
+      if constexpr (BASIS == kBasisBits) pin_noise(n[t].x[i]);
+      else pin_noise<BASIS>(n[t].x[i]);
     }
+}
+
+// The noise of a tile at an edge: two groups of eight rows together, one alone, none for rows past the tensor's (eight weights of 16
+// rows of 312128, backward: 33 us with all four groups, 24 like this).
+template <int BASIS>
+__device__ __forceinline__ void draw_noise_edge(uint32_t step_lo, uint32_t step_hi, const TileDesc& d, uint32_t by, uint32_t col_base,
+                                                uint32_t lane, TileNoise<BASIS>& n) {
+  const PhiloxCols pc[1] = {philox_cols(d.cg0 + (col_base >> 3) + (lane & 7), step_lo, step_hi, d.seed_lo, d.seed_hi)};
+  const uint32_t rows = d.rows - by * 32;
+  auto groups = [&](auto& x, int i) __attribute__((always_inline)) {   // as many as x holds from group i on
+    constexpr int R = sizeof(x[0]) / sizeof(Philox4);
+    const uint32_t r = d.row0 + by * 32 + (lane >> 3) + 8 * i, row[4] = {r, r + 8, 0, 0};
+    philox_tiles(pc, philox_rows(row, step_lo, d.seed_lo), d.seed_lo, d.seed_hi, x);
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      if constexpr (BASIS == kBasisBits) n.x[i + k] = noise_codes(x[0][k]);
+      else n.x[i + k] = x[0][k];
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < 4; i += 2) {   // uniform branches
+    n.x[i] = n.x[i + 1] = {};
+    if (rows > 8u * i + 8) {
+      Philox4 x[1][2];
+      groups(x, i);
+    } else if (rows > 8u * i) {
+      Philox4 x[1][1];
+      groups(x, i);
+    }
+  }
 }
 
 // Element codes of one group to memory.  FP8: 8 bytes at column col.  FP6: 6 bytes at
@@ -234,7 +281,7 @@ __device__ __forceinline__ u32x6 tile_codes_fp6(const Tile& t, const BlockScale&
 // The forward pass on one wavefront tile, in three phases.
 //
 // tile_scale: a = max|w| of the lane's block (exact), the block's scale and cast constants.
-//   BT_PRE: the caller has already fetched this lane's block parameter (bt_pre), together with the tile.
+//   bt: this lane's block parameter, which the caller fetches with the tile.
 //   STORE: the block's writer lane stores scale (and, MX, the E8M0 block scale) here; off, the caller does.
 // tile_sum: noise times scale added, rounded to BF16 (the tile's registers are overwritten with the sums).
 //   n: the noise of the tile (draw_noise).
@@ -246,13 +293,12 @@ __device__ __forceinline__ u32x6 tile_codes_fp6(const Tile& t, const BlockScale&
 //   overflow); off, the arithmetic cast.  Same bits either way where both apply.
 // No phase branches when FULL and !STORE, so a caller that works on several tiles at once gets straight-line
 // code it can interleave.
-template <int FMT, bool FULL, bool MX, bool BT_PRE, bool STORE>
+template <int FMT, bool FULL, bool MX, bool STORE>
 __device__ __forceinline__ BlockScale tile_scale(const TileDesc& d, Tile& t, uint32_t by, uint32_t col_base, uint32_t lane,
-                                                 float bt_pre) {
+                                                 float bt) {
   const uint32_t gc = lane & 7, r0 = lane >> 3;
   const uint32_t nbc = (d.cols + 31) >> 5;
   const size_t blk0 = (size_t)by * nbc + (col_base >> 5);   // of the left block
-  const GWS_GLOBAL float* __restrict__ bt = global_ptr<float>(d.p2) + blk0;
   if (!FULL) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -266,9 +312,8 @@ __device__ __forceinline__ BlockScale tile_scale(const TileDesc& d, Tile& t, uin
   const uint32_t a16 = block_max_u32(m);
   // ---- per-block scale ----
   const bool block_exists = FULL || (col_base >> 5) + (gc >> 2) < nbc;
-  const float bv = BT_PRE ? bt_pre : (block_exists ? bt[gc >> 2] : 0.0f);
   // Eq. 11 (the product and the sum rounded separately); identity for a plain b_t
-  const float btv = __fadd_rn(d.b_target, __fmul_rn(bv, d.b_delta));
+  const float btv = __fadd_rn(d.b_target, __fmul_rn(bt, d.b_delta));
   BlockScale b = block_scale(a16, btv);
   if (FMT == 1) cast_constants<8, -6>(a16, b);
   if (FMT == 2) cast_constants<4, -2>(a16, b);
@@ -284,7 +329,7 @@ template <bool FULL, int BASIS>
 __device__ __forceinline__ void tile_sum(Tile& t, const BlockScale& b, const TileNoise<BASIS>& n) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    if (!FULL && t.nv[i] == 0) continue;
+    if (!FULL && t.rows <= 8 * i) continue;   // uniform
     const u32x4 w = t.v[i];
     uint32_t pk[4];
     if constexpr (BASIS == kBasisBits) {
@@ -367,11 +412,11 @@ __device__ __forceinline__ void tile_store(const TileDesc& d, const Tile& t, con
 
 // The phases for one tile; FP8-E4M3 takes the hardware converters only if neither block of this wavefront can
 // overflow (they give NaN where the cast saturates).
-template <int FMT, bool FULL, int STREAM = kStreamAll, bool MX = false, bool BT_PRE = false, int BASIS = kBasisBits>
+template <int FMT, bool FULL, int STREAM = kStreamAll, bool MX = false, int BASIS = kBasisBits>
 __device__ __forceinline__ void fwd_tile(const TileDesc& d, Tile& t, const TileNoise<BASIS>& n, uint32_t by, uint32_t col_base,
-                                         uint32_t lane, float bt_pre = 0.0f) {
+                                         uint32_t lane, float bt) {
   static_assert(BASIS == kBasisBits || !MX, "the comparison bases have no MX output");
-  const BlockScale b = tile_scale<FMT, FULL, MX, BT_PRE, true>(d, t, by, col_base, lane, bt_pre);
+  const BlockScale b = tile_scale<FMT, FULL, MX, true>(d, t, by, col_base, lane, bt);
   tile_sum<FULL, BASIS>(t, b, n);
   if constexpr (FMT == 1) {
     if (__builtin_amdgcn_ballot_w64(!b.hw_safe) == 0) tile_store<FMT, FULL, STREAM, MX, true>(d, t, b, by, col_base, lane);

@@ -145,3 +145,10 @@ def test_box_muller_thresholds_and_defined_sequence_agree_for_every_word():
     assert differ == 0
     assert 0 < left < 1e-4 * 2 ** 32
     assert 0 < worst <= 2 ** 23 // 20
+
+
+@pytest.mark.parametrize("name", list(BASES))
+def test_every_number_of_rows_of_a_last_block(name):
+    gb, ob = BASES[name]
+    for i, rows in enumerate((1, 8, 9, 17, 24, 25, 31, 40, 49)):
+        run_fwd_bwd([(rows, 256), (rows, 77)], gb, ob, FMTS[i % 3], step=6, copy_dw=bool(i & 1))

@@ -169,3 +169,8 @@ def test_fp6_codes_of_whole_tiles_at_every_row_alignment(pad):
 def test_codes_that_leave_by_rows_of_the_workgroup(fmt, pad):
     # tensors of whole 32 x 256 tiles only: the codes are staged; rows at the least alignment (FP8 8 bytes, FP6 2)
     check_mx(make_items([(32, 256), (64, 768), (320, 512)], 470), fmt, 5, pad=pad)
+
+
+@pytest.mark.parametrize("fmt", MX_FMTS)
+def test_codes_of_every_number_of_rows_of_a_last_block(fmt):
+    check_mx(make_items([(rows, cols) for rows in (1, 8, 9, 17, 24, 25, 31, 40, 49) for cols in (256, 77)], 480), fmt, 6, pad=1)

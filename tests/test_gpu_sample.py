@@ -318,6 +318,18 @@ def test_one_weight_alone(shape):
     check_backward(items, 6)
 
 
+@pytest.mark.parametrize("rows", [1, 7, 8, 9, 16, 17, 24, 25, 31, 40, 49, 88])
+def test_every_number_of_rows_of_a_last_block(rows):
+    # at an edge the noise is drawn for as many groups of eight rows as exist, two together or one alone; the columns whole
+    # tiles, a part of one and of a group
+    for fmt in FMTS:
+        items = make_items([(rows, 256), (rows, 300), (rows, 5)], base=1800 + rows)
+        for it, (_, scale) in zip(items, check_forward(items, fmt, 6)):
+            it["scale"] = scale
+    check_backward(items, 6, dw_mode="alias")
+    check_backward(items, 6)
+
+
 def test_large_calls_give_the_bytes_of_small_ones():
     # 7 x 33.6 MB in rows of 8200 bytes (not whole cache lines: ordinary stores, streaming loads) and in rows of 8320
     # (whole lines, streaming both ways) against the same weights one at a time (ordinary accesses)
