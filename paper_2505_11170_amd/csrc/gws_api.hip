@@ -115,7 +115,7 @@ constexpr int kAbsmaxOnly = -2;  // the backward launch shape, block-maximum ker
 // `mx` (one per tensor, forward only) switches the output to MX element codes and block scales.
 // Launch-shape choices of a sampling pass; the defaults (-1, 0) let run_batched decide.
 struct Tuning {
-  int variant = -1;   // launch_sample_fwd's / launch_sample_bwd's variant; above 0 only where every tensor qualifies
+  int variant = -1;   // launch_sample_fwd's / launch_sample_bwd's variant; 1 only where every tensor qualifies
   int per_x = 0;      // column tiles per workgroup
 };
 
@@ -159,6 +159,12 @@ int run_batched(const gws_tensor* t, int n, const gws_bitwidth* bw, const gws_mx
     if (t[i].rows > 0 && t[i].cols > 0 && (fwd || copies) && ((row_bytes & 127) != 0 || !aligned(out, 128))) whole_lines = false;
   }
   if (!whole_lines) mode = tile_bytes <= ((uint64_t)192 << 20) ? kKeep : kStreamReads;
+  // The kernels for any shape: up to eight wavefronts a SIMD while what a pass reads and writes fits in the 256 MB last-level cache,
+  // and in any size where it only reads; four beyond (gws_sample.hip).  Ragged weights of the bit basis, ratio to four: forward
+  // 4 - 12 M parameters 0.97, 25 - 45 M 0.98, 64 - 96 M 1.04, 260 - 500 M 1.10; backward 25 - 45 M 0.87, 260 - 500 M 0.95; with dL/dw
+  // copied 25 - 45 M 0.98, 64 - 96 M 1.05.
+  const uint64_t written = !fwd ? (copies ? tile_bytes : 0) : !mx ? tile_bytes : fmt == GWS_FMT_FP8_E4M3 ? tile_bytes / 2 : tile_bytes / 8 * 3;
+  const int any_shape = written == 0 || tile_bytes + written <= ((uint64_t)224 << 20) ? 2 : 0;
 
   LaunchArgs a;
   memset(&a, 0, sizeof a);
@@ -172,7 +178,7 @@ int run_batched(const gws_tensor* t, int n, const gws_bitwidth* bw, const gws_mx
   bool whole_tiles = true;
   auto flush = [&]() -> int {
     if (a.n == 0) return GWS_OK;
-    const int variant = !whole_tiles || (fwd && per_x != 1) ? 0 : tune.variant >= 0 ? tune.variant : 1;
+    const int variant = tune.variant == 0 || tune.variant == 2 ? tune.variant : !whole_tiles || (fwd && per_x != 1) ? any_shape : 1;
     int rc = (!fwd && fmt == kAbsmaxOnly) ? launch_block_absmax(a, (uint32_t)wgs, stream)
              : !fwd ? launch_sample_bwd(a, (uint32_t)wgs, basis, mode, variant, stream)
              : fmt == kCopyOnly ? launch_copy_tiles(a, (uint32_t)wgs, stream)
@@ -368,7 +374,7 @@ int gws_noise_basis(void* out, int64_t rows, int64_t cols, int64_t row0, int64_t
 }
 
 int gws_sample_bwd_tuned(const gws_tensor* t, int n, uint64_t step, int variant, int per_x, void* stream) {
-  if (n < 0 || variant < -1 || variant > 1 || per_x < 0 || per_x > 64) return GWS_ERR_SHAPE;
+  if (n < 0 || variant < -1 || variant > 2 || per_x < 0 || per_x > 64) return GWS_ERR_SHAPE;
   if (n == 0) return GWS_OK;
   if (!t) return GWS_ERR_NULL;
   for (int i = 0; i < n; ++i) {
@@ -382,7 +388,7 @@ int gws_sample_bwd_tuned(const gws_tensor* t, int n, uint64_t step, int variant,
 }
 
 int gws_sample_fwd_tuned(const gws_tensor* t, int n, int fmt, uint64_t step, int variant, int per_x, void* stream) {
-  if (n < 0 || variant < -1 || variant > 1 || per_x < 0 || per_x > 64) return GWS_ERR_SHAPE;
+  if (n < 0 || variant < -1 || variant > 2 || per_x < 0 || per_x > 64) return GWS_ERR_SHAPE;
   if (n == 0) return GWS_OK;
   if (!t) return GWS_ERR_NULL;
   if (fmt != GWS_FMT_BF16 && fmt != GWS_FMT_FP8_E4M3 && fmt != GWS_FMT_FP6_E3M2) return GWS_ERR_FORMAT;

@@ -68,9 +68,10 @@ struct OneArgs {
 static_assert(sizeof(LaunchArgs) <= 6144, "kernel arguments: keep within the size verified on the device");
 
 // basis: kBasisBits, or a comparison basis (no MX output then); mode: kKeep, kStreamReads or kStreamAll
-// variant: 0 = any shape (sample_fwd_kernel); 1 = whole tiles only (sample_fwd_full_kernel)
+// variant: any shape (sample_fwd_kernel) with 0 = four, 2 = up to eight wavefronts a SIMD; 1 = whole tiles only, one a workgroup
+// (sample_fwd_full_kernel)
 int launch_sample_fwd(const LaunchArgs& a, uint32_t n_wg, int fmt, bool mx, int basis, int mode, int variant, hipStream_t stream);
-// variant: 0 = any shape (sample_bwd_kernel); 1 = whole tiles and aliased dL/dw only (sample_bwd_full_kernel)
+// variant: any shape (sample_bwd_kernel) as above; 1 = whole tiles and aliased dL/dw only (sample_bwd_full_kernel)
 int launch_sample_bwd(const LaunchArgs& a, uint32_t n_wg, int basis, int mode, int variant, hipStream_t stream);
 int launch_noise_basis(void* out, uint32_t rows, uint32_t ngrp, uint32_t row0, uint32_t cg0, uint64_t seed, uint64_t step,
                        int basis, hipStream_t stream);

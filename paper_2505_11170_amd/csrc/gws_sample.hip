@@ -121,14 +121,16 @@ __device__ __forceinline__ void walk_tiles(const ARGS& a, const TileDesc& d, uin
 // with 8, 7, 6, 5, 4 and 2 wavefronts a SIMD 927, 923, 891, 891, 876 and 1004 us, of the 124M model 87, 87, 85, 85, 83, 95.
 // The registers that this leaves (128) let the compiler interleave a tile's groups: MX-FP6 of 352 M parameters 195 -> 182 us.
 #define GWS_FOUR_WAVES __attribute__((amdgpu_waves_per_eu(4, 4)))
-// The uniform basis on weights of any shape: up to eight, as measured: 45 M parameters in FP8 49 us with as many as fit, 54 with four; 67 M 77 and 83; 147 M 182 either way.
-#define GWS_WAVES_ANY_SHAPE(basis) __attribute__((amdgpu_waves_per_eu(4, (basis) == kBasisUniform ? 8 : 4)))
+// Weights of any shape: up to eight (EIGHT) while what the pass reads and writes fits in the last-level cache, and wherever it only
+// reads (run_batched).  Backward pass of the uniform basis on whole tiles: up to eight too, as that basis has more left to do when the
+// tile has come (34.7 M parameters 11.3 us, 12.0 with four).
+#define GWS_WAVES(eight) __attribute__((amdgpu_waves_per_eu(4, (eight) ? 8 : 4)))
 
 // MX: write element codes and E8M0 block scales instead of the BF16 container.
 // STREAM: see load16.
 // BASIS: the method's bit-built noise, or one of the two comparison bases.
-template <int FMT, bool MX, int STREAM, int BASIS, class ARGS>
-__global__ __launch_bounds__(kThreads) GWS_WAVES_ANY_SHAPE(BASIS) void sample_fwd_kernel(const ARGS a) {
+template <int FMT, bool MX, int STREAM, int BASIS, bool EIGHT, class ARGS>
+__global__ __launch_bounds__(kThreads) GWS_WAVES(EIGHT) void sample_fwd_kernel(const ARGS a) {
   uint32_t byg, bxg;
   const TileDesc d = locate(a, byg, bxg);
   const uint32_t lane = threadIdx.x & 63;
@@ -201,8 +203,8 @@ __device__ __forceinline__ void bwd_tile(const TileDesc& d, const Tile& t, const
   }
 }
 
-template <int STREAM, int BASIS, class ARGS>
-__global__ __launch_bounds__(kThreads) GWS_WAVES_ANY_SHAPE(BASIS) void sample_bwd_kernel(const ARGS a) {
+template <int STREAM, int BASIS, bool EIGHT, class ARGS>
+__global__ __launch_bounds__(kThreads) GWS_WAVES(EIGHT) void sample_bwd_kernel(const ARGS a) {
   uint32_t byg, bxg;
   const TileDesc d = locate(a, byg, bxg);
   const uint32_t lane = threadIdx.x & 63;
@@ -290,7 +292,7 @@ __global__ __launch_bounds__(kThreads) GWS_FOUR_WAVES void sample_fwd_full_kerne
 // tile.  The next tile's loads are issued after the current tile's arithmetic and complete under the next tile's
 // Philox rounds.
 template <int STREAM, int BASIS, class ARGS>
-__global__ __launch_bounds__(kThreads) GWS_FOUR_WAVES void sample_bwd_full_kernel(const ARGS a) {
+__global__ __launch_bounds__(kThreads) GWS_WAVES(BASIS == kBasisUniform) void sample_bwd_full_kernel(const ARGS a) {
   uint32_t byg, bxg;
   const TileDesc d = locate(a, byg, bxg);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -430,7 +432,8 @@ __global__ __launch_bounds__(256) void box_muller_check_kernel(uint64_t first, u
 template <int FMT, bool MX, int STREAM, int BASIS, class ARGS>
 static void launch_fwd(const ARGS& a, uint32_t n_wg, int variant, hipStream_t stream) {
   if (variant == 1) hipLaunchKernelGGL((sample_fwd_full_kernel<FMT, MX, STREAM, BASIS, ARGS>), dim3(n_wg), dim3(kThreads), 0, stream, a);
-  else hipLaunchKernelGGL((sample_fwd_kernel<FMT, MX, STREAM, BASIS, ARGS>), dim3(n_wg), dim3(kThreads), 0, stream, a);
+  else if (variant == 2) hipLaunchKernelGGL((sample_fwd_kernel<FMT, MX, STREAM, BASIS, true, ARGS>), dim3(n_wg), dim3(kThreads), 0, stream, a);
+  else hipLaunchKernelGGL((sample_fwd_kernel<FMT, MX, STREAM, BASIS, false, ARGS>), dim3(n_wg), dim3(kThreads), 0, stream, a);
 }
 
 // One small weight (the call inside every sampled linear): five kilobytes of arguments and two dependent reads of them are
@@ -473,7 +476,8 @@ int launch_sample_fwd(const LaunchArgs& a, uint32_t n_wg, int fmt, bool mx, int 
 template <int STREAM, int BASIS, class ARGS>
 static void launch_bwd(const ARGS& a, uint32_t n_wg, int variant, hipStream_t stream) {
   if (variant == 1) hipLaunchKernelGGL((sample_bwd_full_kernel<STREAM, BASIS, ARGS>), dim3(n_wg), dim3(kThreads), 0, stream, a);
-  else hipLaunchKernelGGL((sample_bwd_kernel<STREAM, BASIS, ARGS>), dim3(n_wg), dim3(kThreads), 0, stream, a);
+  else if (variant == 2) hipLaunchKernelGGL((sample_bwd_kernel<STREAM, BASIS, true, ARGS>), dim3(n_wg), dim3(kThreads), 0, stream, a);
+  else hipLaunchKernelGGL((sample_bwd_kernel<STREAM, BASIS, false, ARGS>), dim3(n_wg), dim3(kThreads), 0, stream, a);
 }
 
 template <int BASIS>

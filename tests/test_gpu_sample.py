@@ -275,9 +275,10 @@ def test_random_mixes_of_many_small_and_ragged_tensors(seed):
 
 
 def test_launch_shape_choices_give_the_same_bytes():
-    # include/gws_bench.h: the kernel variant (any-shape kernel, whole-tile kernel) and the column tiles a
-    # workgroup walks are launch-shape choices; forward and backward results may not depend on them.
-    # Whole-tile tensors (the whole-tile kernels run), a ragged one mixed in (the launch falls back to the
+    # include/gws_bench.h: the kernel variant (any-shape kernel with four and eight wavefronts a SIMD, whole-tile
+    # kernel) and the column tiles a workgroup walks are launch-shape choices; forward and backward results may
+    # not depend on them.  Whole-tile tensors (the whole-tile kernels run, forward at one column tile a workgroup:
+    # the any-shape kernel at more), a ragged one mixed in (the launch falls back to the
     # any-shape kernel), a shard origin, and the bitwidth left per block.
     shapes = [(64, 512), (96, 1280), (32, 256), (128, 768)]
     for mix in (shapes, shapes + [(40, 300)]):
@@ -293,7 +294,7 @@ def test_launch_shape_choices_give_the_same_bytes():
         gws.gws_sample_bwd(descs, 4)
         torch.cuda.synchronize()
         ref = outs()
-        for variant in (0, 1):
+        for variant in (0, 1, 2):
             for per_x in (1, 2, 3, 5):
                 for d in descs:
                     d.w_hat.zero_(), d.scale.zero_(), d.dbt.zero_()
