@@ -280,9 +280,11 @@ def test_each_form_padded_sharded_and_without_the_reduction(form, tokens, rows, 
 @pytest.mark.parametrize("form,tokens,rows,cols,room", [
     (gws.BWD_W_PIECES_32, 64, 256, 256, 0), (gws.BWD_W_PIECES_32, 448, 256, 512, 0), (gws.BWD_W_PIECES_32, 8192, 256, 2048, 8),
     (gws.BWD_W_PIECES_96, 64, 768, 2816, 0), (gws.BWD_W_PIECES_96, 448, 1280, 3328, 0), (gws.BWD_W_PIECES_96, 2624, 768, 2816, 5), (gws.BWD_W_PIECES_96, 4096, 768, 3072, 7),
-    (gws.BWD_W_PIECES_128_128, 64, 1280, 1792, 0), (gws.BWD_W_PIECES_128_128, 832, 2048, 2048, 0), (gws.BWD_W_PIECES_128_128, 1088, 2048, 4096, 2)])
+    (gws.BWD_W_PIECES_128_128, 64, 1280, 1792, 0), (gws.BWD_W_PIECES_128_128, 832, 2048, 2048, 0), (gws.BWD_W_PIECES_128_128, 1088, 2048, 4096, 2),
+    (gws.BWD_W_PIECES_32, 448, 512, 256, 0), (gws.BWD_W_PIECES_32, 2240, 1792, 256, 0), (gws.BWD_W_PIECES_96, 64, 2816, 768, 0), (gws.BWD_W_PIECES_96, 448, 3328, 1280, 0),
+    (gws.BWD_W_PIECES_128_128, 832, 2304, 1792, 0), (gws.BWD_W_PIECES_128, 1344, 3072, 512, 0), (gws.BWD_W_PIECES_64, 4096, 1280, 512, 0)])
 def test_pieces_for_rows_on_cache_lines(form, tokens, rows, cols, room, w_is_nk):
-    # fewer units of tokens than wavefronts, uneven numbers of them, pieces past the weight's edge, sums in two halves; X and
+    # weights wider and taller than square (the pieces are dealt along the longer side), fewer units of tokens than wavefronts, uneven numbers of them, pieces past the weight's edge, sums in two halves; X and
     # dY in wider buffers with NaN beside them, the weight a shard of a larger one, dW in a wider buffer
     gen = torch.Generator(device=DEV).manual_seed(tokens + cols)
     K, N = (cols, rows) if w_is_nk else (rows, cols)
