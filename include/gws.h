@@ -246,6 +246,9 @@ int gws_linear_bwd_w(const void* x, const void* dy, int64_t M, int64_t ldx, int6
  * same bounds (the fp32 additions are grouped by part; nothing depends on timing).
  * Where small pieces of the gradient, whose tokens are split inside a workgroup, are faster for the sizes
  * they are taken and the workspace left alone; no fp32 sum then runs over more tokens than a part's.
+ * Which of these runs, and with it how the fp32 additions are grouped, goes by the sizes, the workspace, the device's
+ * number of compute units and whether every row of x, dy and dw starts on a 128-byte line: the same call on other
+ * buffers may differ in dW's last bits, the same call on the same buffers does not.  (So may gws_linear_bwd_w.)
  *   gws_linear_bwd_w_workspace_bytes(w, M): bytes the split may use for this weight and M
  *     (host call; 0 when the one-kernel form is used: enough tiles, M too small, bad shape).
  *   workspace : device memory, 16-byte aligned, workspace_bytes long, not overlapping x, dy or

@@ -72,13 +72,13 @@ int gws_ride_plan_layout(int64_t M, int64_t K, int64_t N, int w_is_nk, const gws
 #define GWS_GEMM_ANY_SHAPE_SAMPLE 9 /* the same on the tiles of 6 */
 int gws_gemm_form(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled);
 
-/* gws_linear_bwd_w_form: of gws_linear_bwd_w_ws for this weight (rows, cols) over M tokens with that much workspace, X, dY
- * or dW being rows that do not start on 128-byte lines; gws_linear_bwd_w_form_rows: where they all do (on_lines != 0). */
+/* gws_linear_bwd_w_form: of gws_linear_bwd_w_ws for this weight (rows, cols) over M tokens with that much workspace, X, dY and
+ * dW being rows that start on 128-byte lines (contiguous ones do); _rows: the same for either, on_lines = 0 where some do not. */
 #define GWS_BWD_W_WIDE 1            /* a workgroup per 256 x 256 tile */
 #define GWS_BWD_W_NARROW 2          /* a workgroup per 256 x 192 tile */
 #define GWS_BWD_W_PIECES_64 3       /* a workgroup per 64 x 64 piece, the tokens split over its wavefronts */
 #define GWS_BWD_W_PIECES_128 4      /* the same with pieces of 128 x 64 */
-#define GWS_BWD_W_PIECES_96 5       /* of 96 x 96 (this and the next two: rows on lines only) */
+#define GWS_BWD_W_PIECES_96 5       /* of 96 x 96 */
 #define GWS_BWD_W_PIECES_128_128 6  /* of 128 x 128 */
 #define GWS_BWD_W_PIECES_32 7       /* of 64 x 32 */
 #define GWS_BWD_W_SPLIT 16          /* + parts: the tokens of a 256 x 256 tile split over so many workgroups */

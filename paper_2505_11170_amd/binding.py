@@ -451,9 +451,9 @@ def gws_gemm_form(M: int, K: int, N: int, w_is_nk: bool = False, sampled: int = 
                                             int(bool(w_is_nk)), int(sampled)))
 
 
-def gws_linear_bwd_w_form(w: TensorDesc, M: int, workspace_bytes: int = 0, on_lines: bool = False) -> int:
+def gws_linear_bwd_w_form(w: TensorDesc, M: int, workspace_bytes: int = 0, on_lines: bool = True) -> int:
     """The form (``BWD_W_*``) that ``gws_linear_bwd_w_ws`` takes with that much workspace; ``BWD_W_SPLIT`` plus the number of parts.
-    ``on_lines``: every row of X, dY and dW starts on a 128-byte line."""
+    ``on_lines``: every row of X, dY and dW starts on a 128-byte line, as contiguous ones do."""
     return int(load_library().gws_linear_bwd_w_form_rows(_marshal([w]), int(M), int(workspace_bytes), int(on_lines)))
 
 

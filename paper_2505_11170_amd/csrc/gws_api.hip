@@ -605,12 +605,13 @@ static uint32_t parts_within(const GemmArgs& g, size_t workspace_bytes, int cus)
 // split into `parts` (as many as the workspace holds): a longer sum has a larger error.  Elements of dW that are not the
 // rounded 64-bit value, 768 x 3072 over 4096 tokens: 2.6e-4 in one sum, 2.0e-4 in five, 1.7e-4 in seven.
 //  - With workspace: the tokens of a tile split over that many workgroups, or small pieces of the gradient with the tokens in
-//    four sums or (parts > 4) eight.
+//    four sums or (parts > 4) eight.  Where the parts are fewer sums than the pieces make, they must be faster by more than the
+//    estimates err.
 //  - Without (parts < 2): one workgroup per tile of 256 x 256 or of 256 x 192, or small pieces.
-// Fitted to MI355X timings; in parts and in small pieces, tokens x rows x cols: 4096 x 768 x 3072 42 and 30, 4096 x 768 x 2304
-// 35 and 27, 8192 x 2048 x 2048 75 and 68, 2048 x 2048 x 2048 41 and 26, 8192 x 512 x 512 29 and 29, 8192 x 1024 x 1024 37 and
-// 37, 2048 x 1024 x 1024 25 and 13, 1024 x 2048 x 4096 40 and 34 (a K-step of a part: 1.05 to 1.38 with all compute units at work).
-// lines: see stream_tn_plan.
+// Fitted to MI355X timings; in parts and in small pieces, tokens x rows x cols: 4096 x 768 x 3072 41 and 30, 4096 x 768 x 2304
+// 35 and 27, 8192 x 2048 x 2048 76 and 72, 2048 x 2048 x 2048 40 and 26, 8192 x 512 x 512 29 and 29, 8192 x 1024 x 1024 37 and
+// 39, 2048 x 1024 x 1024 25 and 13, 1024 x 2048 x 4096 40 and 35, 2816 x 1280 x 2304 37 and 42, 3584 x 2048 x 2816 56 and 66.
+// lines: see stream_tn_plan; the other forms take rows off the lines as fast (4096 x 768 x 3072 in parts 40.7 and 41.2).
 static int bwd_w_form(const GemmArgs& g, uint32_t parts, bool lines, TnPlan& small) {
   small = stream_tn_plan(g, lines, parts > 4);
   const int pieces = small.nt == 2 ? GWS_BWD_W_PIECES_32 : small.nt == 6 ? GWS_BWD_W_PIECES_96 : small.nt == 8 ? GWS_BWD_W_PIECES_128_128
@@ -618,8 +619,8 @@ static int bwd_w_form(const GemmArgs& g, uint32_t parts, bool lines, TnPlan& sma
   const double nk = (double)(g.K / 64), cus = compute_units() > 0 ? compute_units() : 256;
   if (parts >= 2) {
     const double busy = fmin(1.0, (double)parts * (g.M / 256) * (g.N / 256) / cus);
-    const double split_us = 9.0 + nk / parts * (1.0 + 0.33 * busy) + (double)gemm256_tn_split_bytes(g, parts) * 0.317e-6;
-    return small.us < split_us ? pieces : GWS_BWD_W_SPLIT;
+    const double split_us = 11.5 + nk / parts * (0.985 + 0.43 * busy) + (double)gemm256_tn_split_bytes(g, parts) * 0.24e-6;
+    return small.us < split_us * (parts == 4 || parts == 8 ? 1.0 : 1.05) ? pieces : GWS_BWD_W_SPLIT;
   }
   // Fixed: a launch, and with the tiles in flight the stores and the noise on the way out; the narrow tile's way out is by
   // blocks.  Wide and narrow, us: 2048 x 4096 over 64 tokens 14.1 and 15.5, 448 21.3 and 21.6, 960 30.4 and 28.8; 2048 x 5632
@@ -686,7 +687,7 @@ int gws_linear_bwd_w_form_rows(const gws_tensor* w, int64_t M, size_t workspace_
 }
 
 int gws_linear_bwd_w_form(const gws_tensor* w, int64_t M, size_t workspace_bytes) {
-  return gws_linear_bwd_w_form_rows(w, M, workspace_bytes, 0);
+  return gws_linear_bwd_w_form_rows(w, M, workspace_bytes, 1);
 }
 
 int gws_gemm_form(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled) {

@@ -6,9 +6,9 @@
 // workgroups, no fp32 slabs go through memory and there is no second kernel.  Which piece: a whole number of rounds of workgroups,
 // and few bytes.  Measured on MI355X with dL/db_t, us (tokens x P x Q; 64 x 32, 64 x 64, 128 x 64, 96 x 96, 128 x 128, and the
 // 256-tile form that the sizes would take otherwise):
-//   512 x 512 x 512 5.4, 6.3, 8.9, 9.1, 12, 19;       2048 x 1024 x 1024 18, 13.3, 17.4, 19.7, 23, 25;   4096 x 768 x 768 31, 19, 27, 30, -, 24
-//   4096 x 768 x 3072 70, 48, 51, 30, -, 42;          2048 x 2048 x 2048 62, 41, 33, 37, 25.5, 41;       4096 x 768 x 2304 59, 35, 27, 29, -, 35
-//   8192 x 2048 x 2048 258, 121, 90, 118, 68, 75;     1024 x 2048 x 4096 79, 50, 43, 46, 34, 40;         8192 x 512 x 512 29, 36, 47, 54, -, 29
+//   512 x 512 x 512 5.4, 6.2, 8.7, 9.7, 12, 19;       2048 x 1024 x 1024 18, 13.1, 16.9, 19.3, 23, 25;   4096 x 768 x 768 31, 19, 26, 30, -, 24
+//   4096 x 768 x 3072 71, 49, 52, 30, -, 41;          2048 x 2048 x 2048 62, 41, 33, 37, 26, 40;         4096 x 768 x 2304 60, 36, 27, 29, -, 35
+//   8192 x 2048 x 2048 272, 127, 97, 119, 72, 76;     1024 x 2048 x 4096 80, 52, 44, 47, 35, 40;         8192 x 512 x 512 29, 36, 48, 54, -, 29
 // Both operands lie output-contiguous, so both stages are rows of 32 MT and 32 NT bytes a token and both fragments come from the
 // transposing LDS load.  Where the workspace at hand would hold more than four parts, a wavefront sums its tokens in two
 // halves, so that no fp32 sum is longer than in that form (not in 128 x 128 pieces, whose sums fill the registers).  On the way
@@ -234,32 +234,35 @@ static void launch_tn(const GemmArgs& g, bool with_dbt, hipStream_t s) {
 }
 
 // The piece with the smallest estimate in us: a launch, and per round of workgroups (one per compute unit: the rings fill its
-// LDS) a fixed part and the bytes of the piece's operands at the rate a compute unit takes them, which falls with the share of
-// them at work.  The larger pieces' fixed part grows with the rounds (a round's way out meets the next one's loads).
-// lines: every row of X, dY and dW starts on a cache line (as they do in a model's own buffers).  64 x 32, 96 x 96 and 128 x 128
-// pieces then only: the estimates are fitted to such operands, and others cost each piece differently (4096 x 768 x 3072 over
-// rows 16 bytes off the lines: 64 x 64 48 -> 66 us, 128 x 64 51 -> 59, 96 x 96 30 -> 34, the 256-tile form 42 -> 43), so for them
-// the choice is between the other two and the 256-tile form.
+// LDS) a fixed part that grows with the rounds (a round's way out meets the next one's loads), and the bytes of the piece's
+// operands at the rate a compute unit takes them, which falls with the share of them at work.
+// lines: every row of X, dY and dW starts on a cache line (as they do in a model's own buffers).  Others touch one line more a row of
+// a piece: the same fixed parts, lower rates, the lowest for the narrowest pieces (4096 x 768 x 3072, rows on lines and off: 64 x 64
+// 48.5 and 67.5 us, 128 x 64 52 and 61, 96 x 96 30 and 33; 8192 x 2048 x 2048 in 128 x 128 72 and 76).
+// Fitted to MI355X timings of every piece at 330 sizes either way, operands in turn from copies beyond the L2 (4 to 6 % off at one
+// size), the choice between them, the 256-tile forms and the parts 0.05 % from the fastest in the mean, 0.2 % for rows off the lines.
 TnPlan stream_tn_plan(const GemmArgs& g, bool lines, bool halves) {
   const double cus = compute_units() > 0 ? compute_units() : 256;
   TnPlan best = {0, 0, 1e30};
   if (g.ldx >= kTnMaxLd || g.ldw >= kTnMaxLd) return best;
-  // fixed part of a round, what it grows by, bytes per ns with few and with all compute units at work, what the halves cost
-  static const struct { int mt, nt; bool lines; double round, more, rate, rate_full, halves; } tiles[] = {
-      {4, 4, false, 2.7, 0.0, 82.0, 82.0, 0.6}, {8, 4, false, 3.5, 1.0, 75.0, 75.0, 1.8},
-      {4, 2, true, 1.0, 0.5, 61.0, 61.0, 0.4}, {6, 6, true, 5.0, 0.5, 75.0, 75.0, 1.0}, {8, 8, true, 8.2, 0.0, 96.0, 67.0, 0.0}};
+  // fixed part of a round, what it grows by, bytes per ns with few and with all compute units at work (on lines, off), what the
+  // halves cost
+  static const struct { int mt, nt; double round, more, rate[2][2], halves; } tiles[] = {
+      {4, 2, 0.9, 0.52, {{67.0, 65.0}, {52.5, 49.5}}, 0.1}, {4, 4, 1.45, 0.58, {{81.0, 70.0}, {57.5, 52.5}}, 0.5},
+      {8, 4, 3.3, 0.64, {{85.0, 73.0}, {67.0, 60.0}}, 1.0}, {6, 6, 4.0, 0.61, {{80.0, 66.0}, {68.0, 60.5}}, 0.8},
+      {8, 8, 6.3, 0.68, {{83.5, 68.0}, {73.0, 59.5}}, 0.0}};
   for (const auto& t : tiles) {
-    if ((t.lines && !lines) || (halves && t.mt * t.nt == 64)) continue;
+    if (halves && t.mt * t.nt == 64) continue;
     const double n = ceil(g.M / (16.0 * t.mt)) * ceil(g.N / (16.0 * t.nt)), rounds = ceil(n / cus);
-    const double rate = t.rate + (t.rate_full - t.rate) * fmin(1.0, n / cus);
-    const double a_round = t.round + t.more * fmin(rounds - 1.0, 2.0) + (double)g.K * 2 * 16 * (t.mt + t.nt) / rate * 1e-3;
+    const double* r = t.rate[lines ? 0 : 1];
+    const double a_round = t.round + t.more * fmin(rounds - 1.0, 2.0) + (double)g.K * 2 * 16 * (t.mt + t.nt) / (r[0] + (r[1] - r[0]) * fmin(1.0, n / cus)) * 1e-3;
     const double us = 2.8 + rounds * a_round + (halves ? t.halves : 0.0);
     if (us < best.us) best = {t.mt, t.nt, us};
   }
   return best;
 }
 
-// halves: eight fp32 sums an element (512 x 512 over 1024 tokens 6.7 -> 7.9 us, 768 x 2304 over 4096 27.6 -> 29.0).
+// halves: eight fp32 sums an element (768 x 768 over 4096 tokens 18.4 -> 18.9 us, 768 x 2304 26.4 -> 27.5).
 int launch_gemm_stream_tn(const GemmArgs& g, bool with_dbt, const TnPlan& p, bool halves, hipStream_t stream) {
   if ((uint64_t)((g.M + 31) / 32) * ((g.N + 31) / 32) >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
   if (p.mt == 4 && p.nt == 2) halves ? launch_tn<4, 2, 4, true>(g, with_dbt, stream) : launch_tn<4, 2, 4, false>(g, with_dbt, stream);

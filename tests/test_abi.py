@@ -152,7 +152,32 @@ def test_queries_of_the_chosen_kernel(lib):
     assert [binding.gws_gemm_form(m, 2048, 5632, sampled=2) for m in (16, 8192)] == [binding.GEMM_STREAM_SAMPLE, binding.GEMM_LARGE]
     wide = binding.TensorDesc(rows=4096, cols=4096, ld=4096, seed=1)
     assert binding.gws_linear_bwd_w_form(wide, 512) == binding.BWD_W_WIDE and binding.gws_linear_bwd_w_form(wide, 63) == 0
-    assert binding.gws_linear_bwd_w_form(binding.TensorDesc(rows=768, cols=3072, ld=3072, seed=1), 4096, 1 << 30) == binding.BWD_W_SPLIT + 7
+
+
+# Weight gradient: the form that was fastest by more than 8 % when every one was timed (MI355X, operands in turn from copies beyond the
+# L2), rows on cache lines and off; parts that the workspace has room for.
+@pytest.mark.parametrize("tokens,rows,cols,parts,on,off", [
+    (512, 512, 512, 0, "32", "32"), (4096, 512, 256, 8, "32", None), (4096, 768, 768, 8, "64", None), (2048, 1024, 1024, 4, "64", "64"),
+    (4096, 768, 3072, 7, "96", "96"), (4096, 768, 3072, 0, "96", "96"), (2048, 768, 3072, 4, "96", "96"), (8192, 768, 3072, 0, "96", "96"),
+    (2048, 2048, 2048, 4, "128x128", "128x128"), (2816, 1280, 2304, 0, "128x128", "128x128"), (1920, 4352, 512, 3, "128x128", "128x128"),
+    (8192, 2048, 2048, 0, "128x128", "128x128"), (8192, 2048, 2048, 4, "128x128", None), (4032, 256, 256, 7, "32", "32"),
+    (2816, 1280, 2304, 5, "parts", "parts"), (3584, 2048, 2816, 2, "parts", "parts"), (5760, 3072, 2048, 2, "parts", "parts"),
+    (8192, 512, 512, 8, None, "parts"), (8128, 1792, 256, 8, None, "parts"), (1024, 2048, 4096, 0, "narrow", "narrow"), (512, 4096, 4096, 0, "wide", "wide")])
+def test_the_form_of_a_weight_gradient_is_the_one_that_measured_fastest(lib, tokens, rows, cols, parts, on, off):
+    forms = {"32": binding.BWD_W_PIECES_32, "64": binding.BWD_W_PIECES_64, "96": binding.BWD_W_PIECES_96, "128x128": binding.BWD_W_PIECES_128_128,
+             "parts": binding.BWD_W_SPLIT + parts, "narrow": binding.BWD_W_NARROW, "wide": binding.BWD_W_WIDE}
+    d = binding.TensorDesc(rows=rows, cols=cols, ld=cols, seed=1)
+    for on_lines, name in ((True, on), (False, off)):
+        if name is not None:
+            assert binding.gws_linear_bwd_w_form(d, tokens, parts * rows * cols * 4, on_lines=on_lines) == forms[name]
+    # without the flag the query is of an ordinary call: contiguous operands, rows on lines
+    assert lib.gws_linear_bwd_w_form(binding._marshal([d]), tokens, parts * rows * cols * 4) == binding.gws_linear_bwd_w_form(d, tokens, parts * rows * cols * 4)
+
+
+def test_pieces_of_a_weight_gradient_are_not_given_up_for_longer_sums():
+    # off the lines, where four or eight sums an element are as fast as three or seven parts
+    for tokens, rows, cols, parts in [(1920, 4352, 512, 3), (4032, 256, 256, 7)]:
+        assert binding.gws_linear_bwd_w_form(binding.TensorDesc(rows=rows, cols=cols, ld=cols, seed=1), tokens, parts * rows * cols * 4, on_lines=False) < binding.BWD_W_SPLIT
 
 
 def test_bitwidth_and_mx_entry_points_validate_before_any_launch(lib):

@@ -70,12 +70,12 @@ def test_forward_backward_and_linear_entry_points_replay_from_a_graph():
     assert gws_bytes > 0
     gwork = torch.zeros(gws_bytes // 4, device=DEV)
     outs += [dgrad[0].dw, dgrad[0].dbt, dgrad[1].dw, dgrad[1].dbt]
-    # and with the tokens split through a workspace
-    dys = (synth.make_activation(719, 5184, 256, device=DEV).float() * 1e-3).to(torch.bfloat16)
-    xs = synth.make_activation(720, 5184, 256, device=DEV)
+    # and with the tokens split through a workspace (operands in wider buffers, their rows off the cache lines)
+    dys = (synth.make_activation(719, 5184, 264, device=DEV).float() * 1e-3).to(torch.bfloat16)[:, :256]
+    xs = synth.make_activation(720, 5184, 264, device=DEV)[:, :256]
     dsplit = gws.TensorDesc(rows=256, cols=256, seed=9, scale=torch.full((8, 8), 1e-3, device=DEV), dw=torch.zeros(256, 256, dtype=torch.bfloat16, device=DEV), dbt=torch.zeros(8, 8, device=DEV))
     swork = torch.zeros(gws.gws_linear_bwd_w_workspace_bytes(dsplit, 5184) // 4, device=DEV)
-    assert gws.gws_linear_bwd_w_form(dsplit, 5184, swork.numel() * 4) == gws.BWD_W_SPLIT + 8
+    assert gws.gws_linear_bwd_w_form(dsplit, 5184, swork.numel() * 4, on_lines=False) == gws.BWD_W_SPLIT + 8
     outs += [dsplit.dw, dsplit.dbt]
 
     def run():

@@ -119,16 +119,20 @@ def test_tokens_split_into_parts(w_is_nk):
     # many tokens: the contraction is split (partial tiles go through the workspace and are added in a fixed order), uneven
     # where the units do not divide; dW and dL/db_t to the same bars
     for tokens, K, N, idx in [(8192, 512, 512, 870), (5184, 256, 256, 872)]:
-        assert gws.gws_linear_bwd_w_form(gws.TensorDesc(rows=K, cols=N, ld=N, seed=0), tokens, 8 * K * N * 4) == gws.BWD_W_SPLIT + 8
+        assert gws.gws_linear_bwd_w_form(gws.TensorDesc(rows=K, cols=N, ld=N, seed=0), tokens, 8 * K * N * 4, on_lines=False) == gws.BWD_W_SPLIT + 8
         run_case(tokens, K, N, w_is_nk, idx, pad=8, row0=256, col0=512, split=-1)
 
 
 def test_config5_sized_weights_split_over_tokens():
-    # the 2048 x 2048 weight of the 1B layer over 8192 tokens: 64 tiles in 4 parts; a row in every 256-row tile
+    # the 2048 x 2048 weight of the 1B layer over 8192 tokens: in pieces of 128 x 128, and with rows off the cache lines
+    # 64 tiles in 4 parts; a row in every 256-row tile
     rng = np.random.default_rng(870)
     sel = sorted({0, 2047} | {t * 256 + int(rng.integers(0, 256)) for t in range(8)})
-    assert gws.gws_linear_bwd_w_form(gws.TensorDesc(rows=2048, cols=2048, ld=2048, seed=0), 8192, 1 << 30) == gws.BWD_W_SPLIT + 4
+    d = gws.TensorDesc(rows=2048, cols=2048, ld=2048, seed=0)
+    assert gws.gws_linear_bwd_w_form(d, 8192, 1 << 30) == gws.BWD_W_PIECES_128_128
     run_case(8192, 2048, 2048, False, 870, rows_sel=sel, split=-1)
+    assert gws.gws_linear_bwd_w_form(d, 8192, 1 << 30, on_lines=False) == gws.BWD_W_SPLIT + 4
+    run_case(8192, 2048, 2048, False, 871, pad=8, rows_sel=sel, split=-1)
     d = gws.TensorDesc(rows=2048, cols=5632, seed=1)
     assert gws.gws_linear_bwd_w_workspace_bytes(d, 8192) == 0          # 176 tiles: the one-kernel form
     assert gws.gws_linear_bwd_w_workspace_bytes(gws.TensorDesc(rows=2048, cols=2048, seed=1), 8192) == 4 * 64 * 256 * 256 * 4
@@ -237,14 +241,14 @@ def test_no_fp32_sum_runs_over_more_tokens_than_a_part_of_the_workspace(tokens, 
         assert lost <= 16 * run + 2.0 ** -8 * total, (parts, lost / 16, run)   # what the rounding to BF16 may add
 
 
-PIECES, SPLIT = {gws.BWD_W_PIECES_64, gws.BWD_W_PIECES_128}, gws.BWD_W_SPLIT
+PIECES, SPLIT = {gws.BWD_W_PIECES_32, gws.BWD_W_PIECES_64, gws.BWD_W_PIECES_96, gws.BWD_W_PIECES_128, gws.BWD_W_PIECES_128_128}, gws.BWD_W_SPLIT
 
 
 @pytest.mark.parametrize("w_is_nk", [False, True])
 @pytest.mark.parametrize("form,tokens,rows,cols,room", [
     ({gws.BWD_W_WIDE}, 64, 4096, 4096, 0), ({gws.BWD_W_WIDE}, 448, 4096, 4096, 0), ({gws.BWD_W_WIDE}, 192, 2048, 5632, 0), ({gws.BWD_W_NARROW}, 832, 2048, 5632, 0), ({gws.BWD_W_NARROW}, 1088, 2048, 5632, 0),
     (PIECES, 192, 512, 768, 0), (PIECES, 576, 1536, 1024, 0), (PIECES, 2048, 1024, 1024, 4), (PIECES, 4096, 768, 768, 8), (PIECES, 4096, 768, 2304, 8),
-    ({SPLIT + 2}, 3584, 2048, 2816, 2), (PIECES, 4096, 768, 3072, 2), ({SPLIT + 3}, 2560, 1536, 2816, 3), ({SPLIT + 5}, 2624, 768, 2816, 5), ({SPLIT + 6}, 3072, 768, 2816, 6), ({SPLIT + 7}, 4096, 768, 3072, 7),
+    ({SPLIT + 2}, 3584, 2048, 2816, 2), (PIECES, 4096, 768, 3072, 2), ({SPLIT + 3}, 2560, 1536, 2816, 3), ({SPLIT + 5}, 2560, 1280, 1792, 5), ({SPLIT + 6}, 3072, 1280, 1792, 6), ({SPLIT + 7}, 3584, 1280, 1792, 7), (PIECES, 1088, 2048, 4096, 2),
     ({SPLIT + 8}, 6656, 512, 2304, 8), ({SPLIT + 8}, 8192, 512, 512, 8)])
 def test_each_form_padded_sharded_and_without_the_reduction(form, tokens, rows, cols, room, w_is_nk):
     # X and dY in wider buffers with NaN beside them, dW in a wider buffer, the weight a shard of a larger one; room: the
@@ -259,7 +263,7 @@ def test_each_form_padded_sharded_and_without_the_reduction(form, tokens, rows, 
     shard = dict(rows=rows, cols=cols, ld=cols + 16, row0=320, col0=96, seed=41)
     d = gws.TensorDesc(**shard, dw=dw, scale=torch.rand(rows // 32, cols // 32, generator=gen, device=DEV), dbt=torch.full((rows // 32, cols // 32), float("nan"), device=DEV))
     ws = torch.full((room * rows * cols,), float("nan"), device=DEV) if room else None
-    assert gws.gws_linear_bwd_w_form(d, tokens, room * rows * cols * 4) in form
+    assert gws.gws_linear_bwd_w_form(d, tokens, room * rows * cols * 4, on_lines=False) in form
     gws.gws_linear_bwd_w_ws(x[:, :K], dy[:, :N], d, 5, ws, w_is_nk=w_is_nk)
     a, b = (dy[:, :N], x[:, :K]) if w_is_nk else (x[:, :K], dy[:, :N])
     ref, mag = fp32_product(a, b), fp32_product(a.abs(), b.abs())
