@@ -249,10 +249,12 @@ struct Blocks {
 // turns them through its own 2.5 KiB of LDS a block and multiplies.  Bound by the vector ALU work of the sampling, which every
 // 16 MT rows of X repeat.  Two blocks a step where a compute unit has only one such workgroup's wavefronts (16 rows: 16 x 2048
 // -> 5632 11.6 -> 11.4 us, 16 x 768 -> 3072 8.0 -> 7.6), one where it may have several (300 x 2048 -> 5632 41 us, two blocks 46).
-template <int MT, int P, int FMT, bool W_NK>
-__global__ __launch_bounds__(64 * P) void gemm_stream_sample_kernel(const GemmArgs g) {
+// TAIL: K ends with half a step of two blocks.  W: wavefronts a SIMD that the registers have to leave room for.
+template <int MT, int P, int FMT, bool W_NK, int B, bool TAIL, int W>
+__global__ __launch_bounds__(64 * P) __attribute__((amdgpu_waves_per_eu(W)))
+void gemm_stream_sample_kernel(const GemmArgs g) {
   using namespace stream;
-  constexpr int B = MT == 1 ? 2 : 1;
+  static_assert(B == 2 || !TAIL, "half a step is one of two blocks");
   constexpr int kRed = red_bytes(MT, 2, P), kBlk = P * B * 32 * LP * 2;
   __shared__ __attribute__((aligned(16))) char lds[kRed > kBlk ? kRed : kBlk];
   const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4;
@@ -277,7 +279,8 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_sample_kernel(const GemmAr
   for (int i = 0; i < MT; ++i) acc[i][0] = acc[i][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   typename Blocks<FMT, W_NK, B>::Raw nxt;
   if (s0 < s1) w.load(g, s0, nxt);
-  for (uint32_t s = s0; s < s1; ++s) {
+  const uint32_t whole = TAIL ? umin(s1, g.K >> 6) : s1;
+  for (uint32_t s = s0; s < whole; ++s) {
     const typename Blocks<FMT, W_NK, B>::Raw cur = nxt;
     w.load(g, umin(s + 1, s1 - 1), nxt);
     Frag8 x[B][MT], f[B][2];
@@ -287,15 +290,26 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_sample_kernel(const GemmAr
       for (int i = 0; i < MT; ++i) x[h][i].u = *(const GWS_GLOBAL u32x4*)(xb + (size_t)umin(B * s + h, (g.K >> 5) - 1) * 64 + xo[i]);
     w.sample(g, s, cur, m0 == 0, blk, f);
 #pragma unroll
-    for (int h = 0; h < B; ++h) {
-      if (h > 0 && B * s + h >= g.K >> 5) break;   // half a step at the end of K (uniform)
+    for (int h = 0; h < B; ++h)
 #pragma unroll
       for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[h][j].v, x[h][i].v, acc[i][j], 0, 0, 0);
-    }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the reads are done before the blocks are overwritten
     __builtin_amdgcn_wave_barrier();
+  }
+  if (TAIL && whole < s1) {
+    // half a step at the end of K: one block, as the wavefront beside this one on the SIMD has work of its own
+    const Blocks<FMT, W_NK, 1> last(g, n0);
+    const typename Blocks<FMT, W_NK, 1>::Raw one = {{{nxt.w[0][0], nxt.w[0][1]}}, {nxt.bt[0]}};
+    Frag8 x[MT], f[1][2];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) x[i].u = *(const GWS_GLOBAL u32x4*)(xb + (size_t)(2 * whole) * 64 + xo[i]);
+    last.sample(g, 2 * whole, one, m0 == 0, blk, f);
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[0][j].v, x[i].v, acc[i][j], 0, 0, 0);
   }
   reduce_store<MT, 2, P, MT>(acc, lds, g, m0, n0);
 }
@@ -528,19 +542,30 @@ int launch_gemm_stream(const GemmArgs& g, int w_is_nk, const StreamPlan& p, hipS
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
 
-template <int MT, int P, int FMT>
+template <int MT, int P, int FMT, int B, bool TAIL>
 static void launch_sampled(const GemmArgs& g, int w_is_nk, hipStream_t s) {
   const dim3 grid(((g.M + 16 * MT - 1) / (16 * MT)) * (g.N / 32));
-  if (w_is_nk) hipLaunchKernelGGL((gemm_stream_sample_kernel<MT, P, FMT, true>), grid, dim3(64 * P), 0, s, g);
-  else hipLaunchKernelGGL((gemm_stream_sample_kernel<MT, P, FMT, false>), grid, dim3(64 * P), 0, s, g);
+  const uint32_t cus = compute_units() > 0 ? compute_units() : 256;
+  // [N x K] in FP8 at 64 rows is 131 registers, three wavefronts a SIMD; with more workgroups than those hold, four and two registers
+  // in scratch: 755 x 96 -> 2592 8.0 -> 6.8 us (with one workgroup a compute unit 61 x 160 -> 672 4.8 -> 5.0)
+  constexpr bool kTight = MT == 4 && FMT == 1;
+  if (w_is_nk && kTight && grid.x > (P == 4 ? 3 : 1) * cus)
+    hipLaunchKernelGGL((gemm_stream_sample_kernel<MT, P, FMT, true, B, TAIL, kTight ? 4 : P / 4>), grid, dim3(64 * P), 0, s, g);
+  else if (w_is_nk) hipLaunchKernelGGL((gemm_stream_sample_kernel<MT, P, FMT, true, B, TAIL, P / 4>), grid, dim3(64 * P), 0, s, g);
+  else hipLaunchKernelGGL((gemm_stream_sample_kernel<MT, P, FMT, false, B, TAIL, P / 4>), grid, dim3(64 * P), 0, s, g);
 }
 
+// Up to 16 rows: two blocks a step where a compute unit has one workgroup, one where it has several, which then fit (16 x 96 -> 3232
+// in FP6 5.6 us with a half step as a whole one, 4.9 as half; 1 x 2176 -> 20736 in FP8 36.5 us by two blocks, 28.1 by one).
 template <int FMT>
 static void launch_sampled_fmt(const GemmArgs& g, int w_is_nk, int p, hipStream_t s) {
-  if (p == 4) launch_sampled<4, 4, FMT>(g, w_is_nk, s);
-  else if (g.M <= 16) launch_sampled<1, 8, FMT>(g, w_is_nk, s);
-  else if (g.M <= 32) launch_sampled<2, 8, FMT>(g, w_is_nk, s);
-  else launch_sampled<4, 8, FMT>(g, w_is_nk, s);
+  const uint32_t cus = compute_units() > 0 ? compute_units() : 256;
+  if (p == 4) launch_sampled<4, 4, FMT, 1, false>(g, w_is_nk, s);
+  else if (g.M <= 16 && g.N / 32 > cus) launch_sampled<1, 8, FMT, 1, false>(g, w_is_nk, s);
+  else if (g.M <= 16 && (g.K & 32)) launch_sampled<1, 8, FMT, 2, true>(g, w_is_nk, s);
+  else if (g.M <= 16) launch_sampled<1, 8, FMT, 2, false>(g, w_is_nk, s);
+  else if (g.M <= 32) launch_sampled<2, 8, FMT, 1, false>(g, w_is_nk, s);
+  else launch_sampled<4, 8, FMT, 1, false>(g, w_is_nk, s);
 }
 
 // 256 x 256 tiles (one on a compute unit) or 128 x 128 (two share it, or one has it).  us a unit of 64 k and round, FP8: 3.1; 2.25 with

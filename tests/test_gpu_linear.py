@@ -615,10 +615,11 @@ def test_rows_of_x_far_apart(M, K, N, ldx, plain, w_is_nk):
 
 @pytest.mark.parametrize("w_is_nk", [False, True])
 @pytest.mark.parametrize("fmt", [gws.FMT_BF16, gws.FMT_FP8_E4M3, gws.FMT_FP6_E3M2])
-@pytest.mark.parametrize("M,K,N", [(1, 64, 32), (5, 96, 64), (16, 992, 160), (17, 96, 32), (40, 544, 96), (200, 96, 96), (3000, 96, 160), (3000, 160, 2208), (2900, 352, 992)])
+@pytest.mark.parametrize("M,K,N", [(1, 64, 32), (5, 96, 64), (16, 992, 160), (17, 96, 32), (40, 544, 96), (200, 96, 96), (3000, 96, 160), (3000, 160, 2208), (2900, 352, 992),
+                                   (5, 96, 8288), (16, 64, 8224), (40, 544, 8224), (755, 96, 2592), (1700, 64, 3104)])
 def test_blocks_sampled_by_one_and_by_pairs(M, K, N, fmt, w_is_nk):
-    # few rows take two blocks a step, more take one, many two again: one, two, three blocks of K and odd numbers of them
-    # (half a step at the end), wavefronts without any, a shard; w_hat, scale and Y to the bits of the sampling kernel and the
+    # few rows take two blocks a step, with more than one workgroup a compute unit one, more rows one, many two again: one, two,
+    # three blocks of K and odd numbers of them (half a step at the end), wavefronts without any, a shard; w_hat, scale and Y to the bits of the sampling kernel and the
     # plain product
     r, c = (N, K) if w_is_nk else (K, N)
     t = synth.make_tensor(60 + M % 7, r, c, device=DEV, bt=3.0 if M == 40 else None)     # b_t = 3: blocks beyond the hardware cast
