@@ -411,7 +411,9 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_sample_kernel(const GemmArgs
 // for their own serial chains.  us, four wavefronts and this, one workgroup on a compute unit: 4000 x 2304 -> 800 68 -> 53 (FP6 84 ->
 // 66, BF16 63 -> 47; [N x K] 69 -> 54), 4000 x 3072 -> 1024 91 -> 72, 8192 x 512 -> 512 19.5 -> 16.8; two: 4096 x 1024 -> 2048 47 -> 44,
 // 2862 x 1184 -> 1920 53 -> 50; several rounds of two: 8192 x 2048 -> 2048 160 -> 147.
-template <int FMT, bool W_NK>
+// HALF: K ends with half a unit, of which one wavefront samples its block and the other nothing (4000 x 160 -> 1664 in FP6 17.1 ->
+// 16.3).  The first unit's X comes with the weight: 1678 x 64 -> 3104 in FP6 10.9 -> 10.2.
+template <int FMT, bool W_NK, bool HALF>
 __global__ __launch_bounds__(512, 2) void gemm_rows_pair_sample_kernel(const GemmArgs g) {
   using namespace stream;
   constexpr int MT = 4, BM = 128, XS = BM * 64, LX = 2;   // row tiles of a wavefront; elements of a stage; load instructions of a wavefront
@@ -440,7 +442,7 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_pair_sample_kernel(const Gem
 
   auto multiply = [&](uint32_t u) __attribute__((always_inline)) {
     const uint16_t* xs = ring + (u & 1) * XS;
-    const bool half = 64 * u + 64 > g.K;
+    const bool half = HALF && 64 * u + 64 > g.K;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       if (h == 1 && half) break;   // one block, whose k are the second half of the stage
@@ -459,8 +461,9 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_pair_sample_kernel(const Gem
   };
   w.load(g, rm, nxt);
   for (uint32_t u = 0; u < nu; ++u) {
-    // the unit before has landed and is sampled, and every wavefront is past its reads of the stages filled next
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    // the unit before has landed and is sampled, and every wavefront is past its reads of the stages filled next (the first unit
+    // waits for nothing: X comes with the weight)
+    if (u > 0) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     const uint32_t k0 = umin(64 * u, g.K - 64);   // the half unit at the end of K is fetched as the second half of a whole one
 #pragma unroll
     for (int i = 0; i < LX; ++i) direct(xb + (size_t)k0 * 2, xo[i], ring + (u & 1) * XS + (wave * LX + i) * 512);
@@ -468,7 +471,7 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_pair_sample_kernel(const Gem
     if (rm == 1 && u > 0) multiply(u - 1);
     const typename Blocks<FMT, W_NK, 1>::Raw cur = nxt;
     w.load(g, 2 * umin(u + 1, nu - 1) + rm, nxt);
-    w.stage(g, 2 * u + rm, cur, m0 == 0, blocks[u & 1][cn][rm]);
+    if (!HALF || 2 * u + rm < g.K >> 5) w.stage(g, 2 * u + rm, cur, m0 == 0, blocks[u & 1][cn][rm]);   // of half a unit one block
     if (rm == 0 && u > 0) multiply(u - 1);
   }
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -585,8 +588,10 @@ static void launch_rows(const GemmArgs& g, int w_is_nk, hipStream_t s) {
   const dim3 grid(((g.M + t - 1) / t) * ((g.N + t - 1) / t));
   if (t == 256 && w_is_nk) hipLaunchKernelGGL((gemm_rows_sample_kernel<FMT, true>), grid, dim3(512), 0, s, g);
   else if (t == 256) hipLaunchKernelGGL((gemm_rows_sample_kernel<FMT, false>), grid, dim3(512), 0, s, g);
-  else if (w_is_nk) hipLaunchKernelGGL((gemm_rows_pair_sample_kernel<FMT, true>), grid, dim3(512), 0, s, g);
-  else hipLaunchKernelGGL((gemm_rows_pair_sample_kernel<FMT, false>), grid, dim3(512), 0, s, g);
+  else if (w_is_nk && (g.K & 32)) hipLaunchKernelGGL((gemm_rows_pair_sample_kernel<FMT, true, true>), grid, dim3(512), 0, s, g);
+  else if (w_is_nk) hipLaunchKernelGGL((gemm_rows_pair_sample_kernel<FMT, true, false>), grid, dim3(512), 0, s, g);
+  else if (g.K & 32) hipLaunchKernelGGL((gemm_rows_pair_sample_kernel<FMT, false, true>), grid, dim3(512), 0, s, g);
+  else hipLaunchKernelGGL((gemm_rows_pair_sample_kernel<FMT, false, false>), grid, dim3(512), 0, s, g);
 }
 
 // Two workgroups of 128 rows run on a compute unit: between one and one and a half rounds of them the 128 x 128 x 32 kernel, which
