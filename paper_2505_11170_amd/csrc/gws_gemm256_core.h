@@ -405,7 +405,12 @@ __device__ __forceinline__ void gemm256_accumulate(const uint16_t* __restrict__ 
   asm volatile("s_nop 7\n\ts_nop 7");
   __builtin_amdgcn_sched_barrier(0);
 
-  finish(acc, wave == 0 ? A0 : wave == 1 ? A1 : wave == 2 ? B0 : B1, wave, lane);
+  // The lane anew: kept since the loads were set up, what the way out needs of it went to scratch in the [K x N] kernels (two
+  // registers), and a kernel with scratch starts 0.2 to 0.5 us later.
+  uint32_t all = 0xFFFFFFFFu;
+  asm volatile("" : "+s"(all));
+  const uint32_t lane_out = __builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0));
+  finish(acc, wave == 0 ? A0 : wave == 1 ? A1 : wave == 2 ? B0 : B1, wave, lane_out);
 }
 
 // The way out of half h (64 rows) of a wavefront's 128 x 96 part of a narrow tile: as epilogue_bf16_half, but by 32 x 32
