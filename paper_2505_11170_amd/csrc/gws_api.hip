@@ -769,10 +769,14 @@ static int plan_ride(const GemmArgs& g, int w_is_nk, bool gemm_empty, int64_t K,
     }
   }
   if (force_extra < 0 && route != GemmRoute::kLarge) {
-    // the sampling kernel alone: about 3 us and 4 bytes an element at 5 TB/s (one launch in any case if some do not ride)
+    // apart: the kernel that would run, 0.4 us a million elements and (one launch in any case if some do not ride) the sampling's
+    // launch.  Fitted to 700 products of the middle and narrow tiles whose weights fit, one in six of them faster with the weights
+    // riding: the choice 0.1 % from the faster in the mean, 7 % at worst.  Riding and apart, us, [K x N]: 1280 x 1024 -> 3328 with
+    // 1024 x 1024 25.3 and 21.0, 2304 x 1088 -> 2304 with 768 x 2304 26.8 and 22.2; 1280 x 128 -> 4864 with 256 x 256 10.2 and 11.5.
     double elements = 0.0;
     for (int i = 0; i < n_riding; ++i) elements += (double)next[i].rows * (double)next[i].cols;
-    if (plan.large_us - (elements * 4.0 / 5e6 + (n_riding == n_next ? 3.0 : 0.0)) > fmin(plan.middle_us, plan.narrow_us)) n_riding = 0;
+    const double apart = (route == GemmRoute::kMiddle ? plan.middle_us : plan.narrow_us) + elements * 0.4e-6 + (n_riding == n_next ? 4.0 : 0.0);
+    if (plan.large_us > apart) n_riding = 0;
   }
   for (int j = n_riding; j <= kMaxRide; ++j) r.begin[j] = begin;
   r.n = (uint32_t)n_riding;

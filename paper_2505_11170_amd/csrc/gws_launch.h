@@ -115,7 +115,8 @@ enum class GemmRoute { kStream, kMiddle, kLarge, kNarrow, kSmall };
 struct RoutePlan {   // estimates in us; 1e30: not a shape for that kernel
   StreamPlan stream;
   double middle_us, large_us, narrow_us;
-  int middle_nj;   // the middle tile is 128 x 32 middle_nj
+  int middle_nj;      // the middle tile is 128 x 32 middle_nj
+  double middle_line; // what the stream kernel has to beat of the middle tile
 };
 GemmRoute gemm_route(const GemmArgs& g, int w_is_nk, RoutePlan& plan);
 // the kernel that launch_gemm takes (Y apart from the operands); the values are GWS_GEMM_* of gws_bench.h

@@ -204,9 +204,8 @@ static int launch_layout(const GemmArgs& g, int w_is_nk, dim3 grid, hipStream_t 
 GemmRoute gemm_route(const GemmArgs& g, int w_is_nk, RoutePlan& plan) {
   const double cus = compute_units() > 0 ? compute_units() : 256;
   const double nk = ceil(g.K / 64.0);
-  double middle_us = 1e30;   // the faster middle tile; plan.middle_us, which what rides is weighed against: the 128 x 128 line below
   auto tiles = [&](double t) { return ceil(g.M / t) * ceil(g.N / t); };
-  plan = RoutePlan{{0, 0, 0, 1e30}, 1e30, 1e30, 1e30, 4};
+  plan = RoutePlan{{0, 0, 0, 1e30}, 1e30, 1e30, 1e30, 4, 1e30};
   if (gemm256_edge_applicable(g) || gemm256_applicable(g)) {
     const double n = tiles(256.0);
     plan.large_us = 6.0 + ceil(n / cus) * (3.0 + nk * (1.05 + 0.2 * fmin(1.0, n / cus)));
@@ -217,21 +216,21 @@ GemmRoute gemm_route(const GemmArgs& g, int w_is_nk, RoutePlan& plan) {
   }
   if (gemm128_applicable(g)) {
     const double n = tiles(128.0), busy = n > cus ? 1.0 : 0.0;
-    plan.middle_us = 3.3 + ceil(n / cus) * (2.0 + nk * (w_is_nk ? 0.42 + 0.05 * busy : 0.45 + 0.07 * busy));
+    plan.middle_line = 3.3 + ceil(n / cus) * (2.0 + nk * (w_is_nk ? 0.42 + 0.05 * busy : 0.45 + 0.07 * busy));
     for (int nj = 3; nj <= 4; ++nj) {
       const double t = ceil(g.M / 128.0) * ceil(g.N / (32.0 * nj));
       const double us = 2.4 + ceil(t / cus) * (2.0 + nk * ((nj == 3 ? 0.26 : 0.33) + 0.08 * fmin(1.0, t / cus) + (w_is_nk ? 0.0 : 0.02)));
-      if (us < middle_us) {
-        middle_us = us;
+      if (us < plan.middle_us) {
+        plan.middle_us = us;
         plan.middle_nj = nj;
       }
     }
   }
   if (stream_applicable(g)) plan.stream = stream_plan(g.M, g.N, g.K, w_is_nk != 0);
   const double larger = fmin(plan.large_us, plan.narrow_us);
-  if (plan.stream.p > 0 && plan.stream.us < fmin(larger, plan.middle_us)) return GemmRoute::kStream;
-  if (fmin(larger, plan.middle_us) > 1e29) return GemmRoute::kSmall;
-  if (plan.middle_us < larger || 1.07 * middle_us < larger) return GemmRoute::kMiddle;
+  if (plan.stream.p > 0 && plan.stream.us < fmin(larger, plan.middle_line)) return GemmRoute::kStream;
+  if (fmin(larger, plan.middle_line) > 1e29) return GemmRoute::kSmall;
+  if (plan.middle_line < larger || 1.07 * plan.middle_us < larger) return GemmRoute::kMiddle;
   return plan.large_us <= plan.narrow_us ? GemmRoute::kLarge : GemmRoute::kNarrow;
 }
 

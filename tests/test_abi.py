@@ -143,15 +143,28 @@ def test_descriptor_fields_that_are_no_64_bit_whole_numbers():
 
 def test_queries_of_the_chosen_kernel(lib):
     # host functions: what rides and which kernel a call takes, by layout; without a device for 256 compute units
-    nxt = [binding.TensorDesc(rows=1024, cols=1024, ld=1024, seed=1)]
-    assert [binding.gws_ride_plan(1280, 1024, 3328, nxt, w_is_nk=nk) for nk in (False, True)] == [1, 0]
-    assert lib.gws_ride_plan(1280, 1024, 3328, binding._marshal(nxt), 1) == 1           # the [K x N] weight's
+    nxt = [binding.TensorDesc(rows=512, cols=512, ld=512, seed=1)]
+    assert [binding.gws_ride_plan(1536, 320, 4096, nxt, w_is_nk=nk) for nk in (False, True)] == [1, 0]
+    assert lib.gws_ride_plan(1536, 320, 4096, binding._marshal(nxt), 1) == 1           # the [K x N] weight's
     assert binding.gws_gemm_form(1024, 48, 64) == 0 and binding.gws_gemm_form(0, 64, 64) == 0   # what the GEMM refuses, and an empty one
     assert binding.gws_gemm_form(4, 5632, 2048, w_is_nk=True) == binding.GEMM_STREAM
     assert binding.gws_gemm_form(8192, 2048, 5632) == binding.GEMM_LARGE
     assert [binding.gws_gemm_form(m, 2048, 5632, sampled=2) for m in (16, 8192)] == [binding.GEMM_STREAM_SAMPLE, binding.GEMM_LARGE]
     wide = binding.TensorDesc(rows=4096, cols=4096, ld=4096, seed=1)
     assert binding.gws_linear_bwd_w_form(wide, 512) == binding.BWD_W_WIDE and binding.gws_linear_bwd_w_form(wide, 63) == 0
+
+
+# Under products of the middle and the narrow tile, what was faster by more than 8 % (MI355X): the weights riding under the 256-tile, or
+# sampled behind the product's own kernel.
+@pytest.mark.parametrize("M,K,N,nk,weights,rides", [
+    (1280, 1024, 3328, False, [(1024, 1024)], 0), (1280, 768, 3328, False, [(256, 512)], 0), (2048, 1024, 2304, False, [(1024, 512)], 0),
+    (2304, 1088, 2304, False, [(768, 2304)], 0), (2304, 704, 2048, False, [(512, 256)], 0), (3840, 512, 1280, True, [(512, 512)], 0),
+    (1280, 128, 4864, False, [(256, 256)], 1), (5120, 128, 1536, False, [(256, 512)], 1), (3072, 128, 2048, True, [(256, 256)], 1),
+    (1280, 192, 4608, False, [(256, 256), (2304, 256)], 2)])
+def test_weights_ride_where_that_measured_faster(lib, M, K, N, nk, weights, rides):
+    descs = [binding.TensorDesc(rows=r, cols=c, ld=c, seed=1) for r, c in weights]
+    assert binding.gws_gemm_form(M, K, N, nk) in (binding.GEMM_MIDDLE, binding.GEMM_NARROW)
+    assert binding.gws_ride_plan(M, K, N, descs, w_is_nk=nk) == rides
 
 
 # Weight gradient: the form that was fastest by more than 8 % when every one was timed (MI355X, operands in turn from copies beyond the
