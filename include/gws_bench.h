@@ -62,15 +62,17 @@ int gws_ride_plan_layout(int64_t M, int64_t K, int64_t N, int w_is_nk, const gws
  * gws_linear_fwd with w_hat (2: a GEMM that is not a _SAMPLE one is preceded by the sampling kernel), Y lying apart from
  * the operands.                                                                                                */
 #define GWS_GEMM_STREAM 1           /* 16 .. 128 x 16 .. 64 tiles, K split over wavefronts */
-#define GWS_GEMM_MIDDLE 2           /* 128 x 128 tiles, any edge */
+#define GWS_GEMM_MIDDLE 2           /* 128 x 128 or 128 x 96 tiles, any edge */
 #define GWS_GEMM_LARGE 3            /* 256 x 256 tiles, whole ones */
 #define GWS_GEMM_LARGE_EDGE 4       /* 256 x 256 tiles, any edge */
 #define GWS_GEMM_NARROW 5           /* 256 x 192 tiles, any edge */
 #define GWS_GEMM_ANY_SHAPE 6        /* 128 x 128 tiles, K-steps of 32 */
 #define GWS_GEMM_STREAM_SAMPLE 7    /* K split as in 1, the weight sampled in the operand load */
-#define GWS_GEMM_ROWS_SAMPLE 8      /* 128 x 128 tiles, the weight sampled in the operand load */
+#define GWS_GEMM_ROWS_SAMPLE 8      /* 256 x 256 or 128 x 128 tiles, the weight sampled in the operand load */
 #define GWS_GEMM_ANY_SHAPE_SAMPLE 9 /* the same on the tiles of 6 */
 int gws_gemm_form(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled);
+/* gws_gemm_tile: of the same call, the part of Y that a workgroup of that kernel makes, rows << 16 | columns.                */
+int gws_gemm_tile(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled);
 
 /* gws_linear_bwd_w_form: of gws_linear_bwd_w_ws for this weight (rows, cols) over M tokens with that much workspace, X, dY and
  * dW being rows that start on 128-byte lines (contiguous ones do); _rows: the same for either, on_lines = 0 where some do not. */

@@ -690,14 +690,27 @@ int gws_linear_bwd_w_form(const gws_tensor* w, int64_t M, size_t workspace_bytes
   return gws_linear_bwd_w_form_rows(w, M, workspace_bytes, 1);
 }
 
-int gws_gemm_form(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled) {
+// 0: refused sizes
+static int gemm_query(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled, uint32_t& rows, uint32_t& cols) {
   if (M <= 0 || N <= 0 || K <= 0 || ((K | N) & 31) != 0 || ldx < K || ldw < (w_is_nk ? K : N) || ((ldx | ldw) & 7) != 0 ||
       M >= (int64_t)1 << 31 || N >= (int64_t)1 << 31 || ldx >= (int64_t)1 << 31 || ldw >= (int64_t)1 << 31) return 0;
   GemmArgs g;
   memset(&g, 0, sizeof g);
   g.M = (uint32_t)M; g.N = (uint32_t)N; g.K = (uint32_t)K; g.ldx = (uint32_t)ldx; g.ldw = (uint32_t)ldw;
   RoutePlan plan;
-  return (int)gemm_form(g, w_is_nk, sampled == 1 || (sampled == 2 && sample_in_operand(g, w_is_nk)) ? kFusedInOperand : 0, plan);
+  const GemmForm form = gemm_form(g, w_is_nk, sampled == 1 || (sampled == 2 && sample_in_operand(g, w_is_nk)) ? kFusedInOperand : 0, plan);
+  gemm_tile(g, form, plan, rows, cols);
+  return (int)form;
+}
+
+int gws_gemm_form(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled) {
+  uint32_t rows, cols;
+  return gemm_query(M, K, ldx, N, ldw, w_is_nk, sampled, rows, cols);
+}
+
+int gws_gemm_tile(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled) {
+  uint32_t rows, cols;
+  return gemm_query(M, K, ldx, N, ldw, w_is_nk, sampled, rows, cols) == 0 ? 0 : (int)(rows << 16 | cols);
 }
 
 int gws_gemm_bf16(const void* x, int64_t M, int64_t K, int64_t ldx, const void* w, int64_t N, int64_t ldw,

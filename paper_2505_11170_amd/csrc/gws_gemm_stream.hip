@@ -558,16 +558,19 @@ static void launch_sampled(const GemmArgs& g, int w_is_nk, hipStream_t s) {
   else hipLaunchKernelGGL((gemm_stream_sample_kernel<MT, P, FMT, false, B, TAIL, P / 4>), grid, dim3(64 * P), 0, s, g);
 }
 
+uint32_t stream_sample_rows(const GemmArgs& g, int p) { return p == 4 ? 64 : g.M <= 16 ? 16 : g.M <= 32 ? 32 : 64; }
+
 // Up to 16 rows: two blocks a step where a compute unit has one workgroup, one where it has several, which then fit (16 x 96 -> 3232
 // in FP6 5.6 us with a half step as a whole one, 4.9 as half; 1 x 2176 -> 20736 in FP8 36.5 us by two blocks, 28.1 by one).
 template <int FMT>
 static void launch_sampled_fmt(const GemmArgs& g, int w_is_nk, int p, hipStream_t s) {
   const uint32_t cus = compute_units() > 0 ? compute_units() : 256;
+  const uint32_t rows = stream_sample_rows(g, p);
   if (p == 4) launch_sampled<4, 4, FMT, 1, false>(g, w_is_nk, s);
-  else if (g.M <= 16 && g.N / 32 > cus) launch_sampled<1, 8, FMT, 1, false>(g, w_is_nk, s);
-  else if (g.M <= 16 && (g.K & 32)) launch_sampled<1, 8, FMT, 2, true>(g, w_is_nk, s);
-  else if (g.M <= 16) launch_sampled<1, 8, FMT, 2, false>(g, w_is_nk, s);
-  else if (g.M <= 32) launch_sampled<2, 8, FMT, 1, false>(g, w_is_nk, s);
+  else if (rows == 16 && g.N / 32 > cus) launch_sampled<1, 8, FMT, 1, false>(g, w_is_nk, s);
+  else if (rows == 16 && (g.K & 32)) launch_sampled<1, 8, FMT, 2, true>(g, w_is_nk, s);
+  else if (rows == 16) launch_sampled<1, 8, FMT, 2, false>(g, w_is_nk, s);
+  else if (rows == 32) launch_sampled<2, 8, FMT, 1, false>(g, w_is_nk, s);
   else launch_sampled<4, 8, FMT, 1, false>(g, w_is_nk, s);
 }
 
@@ -575,16 +578,16 @@ static void launch_sampled_fmt(const GemmArgs& g, int w_is_nk, int p, hipStream_
 // two and 1.45 with one.  FP6 and BF16 stand in the same proportion.  8192 x 2048 -> 2048 (1 round, 2 of two) 99 and 147 us; 5113 x
 // 2592 -> 1664 (1, 1 and one of one) 132 and 146; 5497 x 1248 -> 4096 (2, 3 of two) 136 and 140; 6000 x 1536 -> 3072 (2, 2 and one of one)
 // 159 and 141; 4096 x 1024 -> 2048 (1, 1) 56 and 44; 4000 x 2304 -> 800 (1, one of one) 102 and 53.
-static bool rows_large(const GemmArgs& g) {
+uint32_t rows_sample_tile(const GemmArgs& g) {
   const uint64_t cus = compute_units() > 0 ? compute_units() : 256;
   const uint64_t n = (uint64_t)((g.M + 127) / 128) * ((g.N + 127) / 128), rest = n % (2 * cus);
   const uint64_t n256 = (uint64_t)((g.M + 255) / 256) * ((g.N + 255) / 256);
   const double small = 2.25 * (double)(n / (2 * cus)) + (rest == 0 ? 0.0 : rest <= cus ? 1.45 : 2.25);
-  return g.K > 64 && 3.1 * (double)((n256 + cus - 1) / cus) < small;   // one unit: 14.3 and 14.1 us for 4224 x 64 -> 2048
+  return g.K > 64 && 3.1 * (double)((n256 + cus - 1) / cus) < small ? 256 : 128;   // one unit: 14.3 and 14.1 us for 4224 x 64 -> 2048
 }
 template <int FMT>
 static void launch_rows(const GemmArgs& g, int w_is_nk, hipStream_t s) {
-  const uint32_t t = rows_large(g) ? 256 : 128;
+  const uint32_t t = rows_sample_tile(g);
   const dim3 grid(((g.M + t - 1) / t) * ((g.N + t - 1) / t));
   if (t == 256 && w_is_nk) hipLaunchKernelGGL((gemm_rows_sample_kernel<FMT, true>), grid, dim3(512), 0, s, g);
   else if (t == 256) hipLaunchKernelGGL((gemm_rows_sample_kernel<FMT, false>), grid, dim3(512), 0, s, g);

@@ -108,9 +108,11 @@ StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk);
 bool stream_applicable(const GemmArgs& g);
 int launch_gemm_stream(const GemmArgs& g, int w_is_nk, const StreamPlan& p, hipStream_t stream);
 int launch_gemm_stream_sample(const GemmArgs& g, int w_is_nk, int fmt, int p, hipStream_t stream);
+uint32_t stream_sample_rows(const GemmArgs& g, int p);   // of its tile, which is 32 columns wide
 // many rows, the weight sampled on its way in, K from end to end
 bool rows_sample_applicable(const GemmArgs& g, int w_is_nk);
 int launch_gemm_rows_sample(const GemmArgs& g, int w_is_nk, int fmt, hipStream_t stream);
+uint32_t rows_sample_tile(const GemmArgs& g);   // rows and columns of its tile, 256 or 128
 enum class GemmRoute { kStream, kMiddle, kLarge, kNarrow, kSmall };
 struct RoutePlan {   // estimates in us; 1e30: not a shape for that kernel
   StreamPlan stream;
@@ -122,6 +124,7 @@ GemmRoute gemm_route(const GemmArgs& g, int w_is_nk, RoutePlan& plan);
 // the kernel that launch_gemm takes (Y apart from the operands); the values are GWS_GEMM_* of gws_bench.h
 enum class GemmForm { kStream = 1, kMiddle, kLarge, kLargeEdge, kNarrow, kAnyShape, kStreamSample, kRowsSample, kAnyShapeSample };
 GemmForm gemm_form(const GemmArgs& g, int w_is_nk, int fused, RoutePlan& plan);
+void gemm_tile(const GemmArgs& g, GemmForm form, const RoutePlan& plan, uint32_t& rows, uint32_t& cols);   // of a workgroup of it
 bool sample_in_operand(const GemmArgs& g, int w_is_nk);   // the faster way to a sampled product (same bits either way)
 bool gemm256_edge_applicable(const GemmArgs& g);
 int launch_gemm256_edge(const GemmArgs& g, int w_is_nk, hipStream_t stream);

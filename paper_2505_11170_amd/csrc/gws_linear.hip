@@ -270,6 +270,21 @@ GemmForm gemm_form(const GemmArgs& g, int w_is_nk, int fused, RoutePlan& plan) {
   }
 }
 
+void gemm_tile(const GemmArgs& g, GemmForm form, const RoutePlan& plan, uint32_t& rows, uint32_t& cols) {
+  rows = cols = 256;
+  switch (form) {
+    case GemmForm::kStream: rows = 16u * plan.stream.mt; cols = 16u * plan.stream.nt; break;
+    case GemmForm::kMiddle: rows = 128; cols = 32u * plan.middle_nj; break;
+    case GemmForm::kLarge:
+    case GemmForm::kLargeEdge: break;
+    case GemmForm::kNarrow: cols = 192; break;
+    case GemmForm::kStreamSample: rows = stream_sample_rows(g, plan.stream.p); cols = 32; break;
+    case GemmForm::kRowsSample: rows = cols = rows_sample_tile(g); break;
+    case GemmForm::kAnyShape:
+    case GemmForm::kAnyShapeSample: rows = BM; cols = BN; break;
+  }
+}
+
 int launch_gemm(const GemmArgs& g, int w_is_nk, int fused, int fmt, hipStream_t stream) {
   const uint64_t tiles = (uint64_t)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   if (tiles == 0) return GWS_OK;

@@ -150,6 +150,12 @@ def test_queries_of_the_chosen_kernel(lib):
     assert binding.gws_gemm_form(4, 5632, 2048, w_is_nk=True) == binding.GEMM_STREAM
     assert binding.gws_gemm_form(8192, 2048, 5632) == binding.GEMM_LARGE
     assert [binding.gws_gemm_form(m, 2048, 5632, sampled=2) for m in (16, 8192)] == [binding.GEMM_STREAM_SAMPLE, binding.GEMM_LARGE]
+    tile = binding.gws_gemm_tile                                                      # and the part of Y that a workgroup makes
+    assert tile(1024, 48, 64) == (0, 0) and tile(1024, 32, 64) == (128, 128)
+    assert [tile(4, 5632, 2048, nk) for nk in (True, False)] == [(16, 16), (16, 32)] and tile(4, 5632, 2048, sampled=1) == (16, 32)
+    assert [tile(8192, 2048, n) for n in (5632, 2560)] == [(256, 256), (256, 192)]
+    assert [tile(2048, 2048, 2048), tile(1024, 768, 2304)] == [(128, 128), (128, 96)]
+    assert [tile(m, 2048, 2048, sampled=1) for m in (2048, 8192)] == [(128, 128), (256, 256)]
     wide = binding.TensorDesc(rows=4096, cols=4096, ld=4096, seed=1)
     assert binding.gws_linear_bwd_w_form(wide, 512) == binding.BWD_W_WIDE and binding.gws_linear_bwd_w_form(wide, 63) == 0
 

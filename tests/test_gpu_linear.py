@@ -400,12 +400,14 @@ def test_riding_under_a_gemm_of_many_k_steps():
     run_next_list(4096, 1024, 4352, [(128, 512), (64, 256)], gws.FMT_FP8_E4M3, 7, rows_sel=np.array([0, 255, 256, 4095]))
 
 
-# The middle tile (128 x 128) and the large tile with edges: one row and 32 columns more or less than whole tiles, K of
+# The middle tile (128 x 128 and 128 x 96 columns) and the large tile with edges: one row and 32 columns more or less than whole tiles, K of
 # whole and half steps of 64 (the half step at every place in the rings of loads), padded X and Y; the sampling kernel's Y
 # is the same bits.
 @pytest.mark.parametrize("w_is_nk", [False, True])
-@pytest.mark.parametrize("M,K,N", [(1537, 96, 1696), (1920, 160, 1760), (1600, 256, 2080), (2049, 288, 1312), (2000, 1504, 2016)])
-def test_middle_tile_gemm(M, K, N, w_is_nk):
+@pytest.mark.parametrize("M,K,N,cols", [(1537, 96, 1696, 96), (1920, 160, 1760, 128), (1600, 256, 2080, 128), (2049, 288, 1312, 96), (2000, 1504, 2016, 128),
+                                        (3969, 96, 800, 128), (3969, 320, 928, 128), (3841, 288, 1824, 128)])
+def test_middle_tile_gemm(M, K, N, cols, w_is_nk):
+    assert gws.gws_gemm_tile(M, K, N, w_is_nk, ldx=K + 8) == (128, cols)
     assert [gws.gws_gemm_form(M, K, N, w_is_nk, k, ldx=K + 8) for k in (0, 1)] == [gws.GEMM_MIDDLE, gws.GEMM_ROWS_SAMPLE]
     run_case(M, K, N, w_is_nk, gws.FMT_FP8_E4M3, seed_id=91, ldx_pad=8, ldy_pad=8, rows_sel=np.array([0, 127, 128, M // 2, M - 1]),
              mode=gws.LINEAR_IN_OPERAND)
@@ -418,7 +420,7 @@ def test_middle_tile_gemm(M, K, N, w_is_nk):
 @pytest.mark.parametrize("M,N", [(1024, 2304), (1025, 2272), (897, 2336), (1000, 2336)])
 def test_middle_tile_of_96_columns_at_every_number_of_k_steps(M, N, w_is_nk):
     for K in [64 * i + 32 * h for i in range(1, 10) for h in (0, 1)]:
-        assert gws.gws_gemm_form(M, K, N, w_is_nk) == gws.GEMM_MIDDLE
+        assert gws.gws_gemm_form(M, K, N, w_is_nk) == gws.GEMM_MIDDLE and gws.gws_gemm_tile(M, K, N, w_is_nk) == (128, 96)
         gen = torch.Generator(device=DEV).manual_seed(K)
         x = torch.randn(M, K, generator=gen, device=DEV).to(torch.bfloat16)
         w = (torch.randn(*((N, K) if w_is_nk else (K, N)), generator=gen, device=DEV) * 0.02).to(torch.bfloat16)
@@ -473,13 +475,14 @@ def test_narrow_large_tiles_at_every_number_of_k_steps(M, N, w_is_nk):
         assert bool((y[:, N:] == 0).all())
 
 
-# Tiles of 256 x 256 of the same (more than two 128 x 128 workgroups a compute unit, one round of these): a last row tile of 1 and 255
-# rows, a last column tile of one wavefront, six and eight, 2 to 10 units whole and half, the [N x K] weights that K brings here;
-# Y and w_hat bit for bit.  The first four: tiles of 128 x 128 (one workgroup a compute unit and two), last row tiles of one
-# wavefront's half and one row, a last column tile of one wavefront, 1 to 11 units whole and half.
+# Tiles of 256 x 256: a last row tile of 1 and 255 rows, a last column tile of one wavefront, six and eight, 2 to 10 units whole and
+# half, the [N x K] weights that K brings here; Y and w_hat bit for bit.  Tiles of 128 x 128 (one workgroup a compute unit and two):
+# last row tiles of one wavefront's half and one row, a last column tile of one wavefront, 1 to 11 units whole and half.
 @pytest.mark.parametrize("w_is_nk", [False, True])
-@pytest.mark.parametrize("M,K,N", [(2240, 96, 1056), (2241, 672, 1120), (3969, 64, 1952), (7937, 160, 416), (4097, 96, 3616), (7935, 128, 1984), (7937, 160, 2016), (8192, 416, 2048), (4097, 576, 2144), (4001, 608, 2208)])
-def test_sampling_in_the_operand_load_of_256_rows_and_by_pairs(M, K, N, w_is_nk):
+@pytest.mark.parametrize("tile,M,K,N", [(128, 2240, 96, 1056), (128, 2241, 672, 1120), (128, 3969, 64, 1952), (128, 7937, 160, 416), (256, 4097, 96, 3616),
+                                         (256, 7935, 128, 1984), (256, 7937, 160, 2016), (256, 8192, 416, 2048), (256, 4097, 576, 2144), (256, 4001, 608, 2208)])
+def test_sampling_in_the_operand_load_of_256_rows_and_by_pairs(tile, M, K, N, w_is_nk):
+    assert gws.gws_gemm_tile(M, K, N, w_is_nk, sampled=1, ldx=K + 8) == (tile, tile)
     assert gws.gws_gemm_form(M, K, N, w_is_nk, sampled=1, ldx=K + 8) == gws.GEMM_ROWS_SAMPLE
     for fmt in (gws.FMT_BF16, gws.FMT_FP8_E4M3, gws.FMT_FP6_E3M2):
         run_case(M, K, N, w_is_nk, fmt, seed_id=95, ldx_pad=8, ldy_pad=8, rows_sel=np.array([0, 127, 128, 255, 256, M // 2, M - 1]), mode=gws.LINEAR_IN_OPERAND)
@@ -489,6 +492,7 @@ def test_sampling_in_the_operand_load_of_256_rows_and_by_pairs(M, K, N, w_is_nk)
 @pytest.mark.parametrize("M,K,N", [(1500, 160, 1760), (2049, 288, 1312), (1537, 96, 4128), (4160, 64, 544)])
 def test_sampling_in_the_operand_load_of_many_rows(M, K, N, w_is_nk):
     assert gws.gws_gemm_form(M, K, N, w_is_nk, sampled=1, ldx=K + 8) == gws.GEMM_ROWS_SAMPLE
+    assert gws.gws_gemm_tile(M, K, N, w_is_nk, sampled=1, ldx=K + 8) == (128, 128)
     # a last row tile of 1 to 128 rows, a last column tile of one wavefront, K of whole and half units; Y and w_hat bit for bit
     for fmt in (gws.FMT_BF16, gws.FMT_FP8_E4M3, gws.FMT_FP6_E3M2):
         run_case(M, K, N, w_is_nk, fmt, seed_id=93, ldx_pad=8, ldy_pad=8, rows_sel=np.array([0, 63, 64, M // 2, M - 1]), mode=gws.LINEAR_IN_OPERAND)
@@ -557,11 +561,13 @@ def test_a_product_of_one_tile_in_place(M, K, N, w_is_nk):
 
 
 @pytest.mark.parametrize("w_is_nk", [False, True])
-@pytest.mark.parametrize("form,M,K,N", [(gws.GEMM_STREAM, 300, 672, 1056), (gws.GEMM_MIDDLE, 1537, 96, 1696), (gws.GEMM_MIDDLE, 1280, 320, 3328),
-                                        (gws.GEMM_LARGE, 8192, 320, 2048), (gws.GEMM_LARGE, 6656, 832, 1792), (gws.GEMM_LARGE_EDGE, 8191, 96, 1824),
-                                        (gws.GEMM_LARGE_EDGE, 7937, 1056, 1568), (gws.GEMM_NARROW, 8192, 448, 2560), (gws.GEMM_NARROW, 8000, 352, 2336),
-                                        (gws.GEMM_ANY_SHAPE, 300, 32, 416)])
-def test_every_gemm_with_padded_operands(form, M, K, N, w_is_nk):
+@pytest.mark.parametrize("form,cols,M,K,N", [
+    (gws.GEMM_STREAM, 64, 300, 672, 1056), (gws.GEMM_MIDDLE, 96, 1537, 96, 1696), (gws.GEMM_MIDDLE, 96, 1280, 320, 3328),
+    (gws.GEMM_MIDDLE, 128, 3969, 96, 800), (gws.GEMM_MIDDLE, 128, 3969, 320, 1824), (gws.GEMM_MIDDLE, 128, 1920, 256, 1792),
+    (gws.GEMM_LARGE, 256, 8192, 320, 2048), (gws.GEMM_LARGE, 256, 6656, 832, 1792), (gws.GEMM_LARGE_EDGE, 256, 8191, 96, 1824),
+    (gws.GEMM_LARGE_EDGE, 256, 7937, 1056, 1568), (gws.GEMM_NARROW, 192, 8192, 448, 2560), (gws.GEMM_NARROW, 192, 8000, 352, 2336),
+    (gws.GEMM_ANY_SHAPE, 128, 300, 32, 416)])
+def test_every_gemm_with_padded_operands(form, cols, M, K, N, w_is_nk):
     # X, the weight and Y all in wider buffers, NaN in what the product must not read; against fp32 on the GPU
     padx, padw, pady = 24, 40, 8
     gen = torch.Generator(device=DEV).manual_seed(M + K)
@@ -572,6 +578,7 @@ def test_every_gemm_with_padded_operands(form, M, K, N, w_is_nk):
     x[:, :K] = torch.randn(M, K, generator=gen, device=DEV)
     w[:, :wc] = torch.randn(wr, wc, generator=gen, device=DEV) * 0.02
     assert gws.gws_gemm_form(M, K, N, w_is_nk, ldx=K + padx, ldw=wc + padw) == form
+    assert gws.gws_gemm_tile(M, K, N, w_is_nk, ldx=K + padx, ldw=wc + padw)[1] == cols
     gws.gws_gemm_bf16(x[:, :K], w[:, :wc], y[:, :N], w_is_nk=w_is_nk)
     kn = (w[:, :wc].t().contiguous() if w_is_nk else w[:, :wc]).float()
     xf = x[:, :K].float()
@@ -615,10 +622,12 @@ def test_rows_of_x_far_apart(M, K, N, ldx, plain, w_is_nk):
 
 @pytest.mark.parametrize("w_is_nk", [False, True])
 @pytest.mark.parametrize("fmt", [gws.FMT_BF16, gws.FMT_FP8_E4M3, gws.FMT_FP6_E3M2])
-@pytest.mark.parametrize("M,K,N", [(1, 64, 32), (5, 96, 64), (16, 992, 160), (17, 96, 32), (40, 544, 96), (200, 96, 96), (3000, 96, 160), (3000, 160, 2208), (2900, 352, 992),
-                                   (5, 96, 8288), (16, 64, 8224), (40, 544, 8224), (755, 96, 2592), (1700, 64, 3104)])
-def test_blocks_sampled_by_one_and_by_pairs(M, K, N, fmt, w_is_nk):
-    # few rows take two blocks a step, with more than one workgroup a compute unit one, more rows one, many two again: one, two,
+@pytest.mark.parametrize("tile,M,K,N", [(16, 1, 64, 32), (16, 5, 96, 64), (16, 16, 992, 160), (32, 17, 96, 32), (64, 40, 544, 96), (64, 200, 96, 96), (64, 3000, 96, 160),
+                                        (128, 3000, 160, 2208), (128, 2900, 352, 992), (64, 5, 96, 8288), (64, 16, 64, 8224), (64, 40, 544, 8224),
+                                        (64, 755, 96, 2592), (128, 1700, 64, 3104), (16, 5, 1696, 16416), (16, 16, 1664, 16416), (64, 218, 8576, 2336)])
+def test_blocks_sampled_by_one_and_by_pairs(tile, M, K, N, fmt, w_is_nk):
+    assert gws.gws_gemm_tile(M, K, N, w_is_nk, sampled=1)[0] == tile
+    # up to 16 rows two blocks a step, with more than one workgroup a compute unit one, more rows one, many two again: one, two,
     # three blocks of K and odd numbers of them (half a step at the end), wavefronts without any, a shard; w_hat, scale and Y to the bits of the sampling kernel and the
     # plain product
     r, c = (N, K) if w_is_nk else (K, N)
