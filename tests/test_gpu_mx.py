@@ -174,3 +174,22 @@ def test_codes_that_leave_by_rows_of_the_workgroup(fmt, pad):
 @pytest.mark.parametrize("fmt", MX_FMTS)
 def test_codes_of_every_number_of_rows_of_a_last_block(fmt):
     check_mx(make_items([(rows, cols) for rows in (1, 8, 9, 17, 24, 25, 31, 40, 49) for cols in (256, 77)], 480), fmt, 6, pad=1)
+
+
+@pytest.mark.parametrize("fmt", MX_FMTS)
+@pytest.mark.parametrize("ldc,rows", [((1 << 27) - 8, 40), (1 << 27, 40), ((1 << 27) - 8, 64), (1 << 27, 64)])
+def test_rows_of_codes_longer_than_the_lane_offsets_reach(ldc, rows, fmt):
+    # 31 rows of codes within 32-bit lane offsets, or 64-bit addresses; the kernels for any shape (40 rows) and for whole tiles
+    cols, step = 512, 5
+    nbytes = oracle.mx_row_bytes(cols, fmt)
+    t = synth.make_tensor(1710, rows, cols, device=DEV, with_grad=False)
+    out = []
+    for codes in (torch.zeros(rows, nbytes, dtype=torch.uint8, device=DEV), torch.empty(rows * ldc, dtype=torch.uint8, device=DEV).view(rows, ldc)):
+        nb = synth.n_blocks(rows, cols)
+        xscale, scale = torch.zeros(*nb, dtype=torch.uint8, device=DEV), torch.zeros(*nb, device=DEV)
+        gws.gws_sample_fwd_mx([gws.TensorDesc(rows=rows, cols=cols, seed=3, w=t["w"], bt=t["bt"], scale=scale)],
+                              [gws.MxOut(codes=codes, xscale=xscale, ldc=codes.stride(0))], fmt, step)
+        torch.cuda.synchronize()
+        out.append([codes[:, :nbytes].contiguous(), xscale, scale.view(torch.int32)])
+    for a, b in zip(*out):
+        assert torch.equal(a, b)

@@ -354,9 +354,11 @@ def test_large_calls_give_the_bytes_of_small_ones():
             assert torch.equal(x.dw[:, :4100].view(torch.int16), x.g[:, :4100].view(torch.int16)) and torch.equal(x.dbt, y.dbt)
 
 
-def test_rows_longer_than_the_lane_offsets_reach():
-    """Full tiles are addressed by 32-bit lane offsets where ld < 2^27; longer rows go the way of the edges, same bits."""
-    ld, rows, cols, step = 1 << 27, 40, 512, 5
+@pytest.mark.parametrize("ld,rows", [((1 << 27) - 8, 40), (1 << 27, 40), ((1 << 27) - 8, 32), (1 << 27, 32)])
+def test_rows_longer_than_the_lane_offsets_reach(ld, rows):
+    """Full tiles are addressed by 32-bit lane offsets where ld < 2^27; longer rows go the way of the edges, same bits: the longest row
+    of the first way and the shortest of the second, by the kernels for any shape (40 rows) and for whole tiles."""
+    cols, step = 512, 5
     t = synth.make_tensor(1700, rows, cols, device=DEV)
     far = {k: torch.empty(rows * ld, dtype=torch.bfloat16, device=DEV).view(rows, ld) for k in ("w", "w_hat")}
     far["w"][:, :cols] = t["w"]
