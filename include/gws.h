@@ -172,7 +172,7 @@ int gws_sample_fwd_mx(const gws_tensor* t, const gws_mx_out* o, int n, int fmt, 
  *   GWS_LINEAR_IN_OPERAND   one kernel; the sampling sits in the weight operand load of every
  *                           output tile (no w_hat round trip; each block is resampled once per
  *                           tile of rows of X: 16 to 64 where the plain GEMM splits K over
- *                           wavefronts, else 128).  Any shape; w_hat/scale optional.
+ *                           wavefronts, else 128 or 256).  Any shape; w_hat/scale optional.
  *   GWS_LINEAR_TWO_KERNELS  the sampling kernel of gws_sample_fwd, then the plain GEMM on w_hat.
  *                           Needs w_hat/scale (GWS_ERR_NULL otherwise).
  *   GWS_LINEAR_AUTO         when w_hat/scale are given the faster of the two by an estimate on the
@@ -277,7 +277,8 @@ int gws_gemm_bf16(const void* x, int64_t M, int64_t K, int64_t ldx,
  * (the paper keeps sampling and matmul in separate kernels, Sec. 3.5; so does this, in one launch):
  * when the GEMM takes the 256-tile kernel and its last round of tiles leaves compute units idle,
  * that many extra workgroups of the same launch do the sampling there; otherwise the sampling kernel
- * is launched after the GEMM.  Same bytes either way; no state; next->w_hat must not overlap x, w
+ * is launched after the GEMM, as it is where another tile with the sampling behind it is estimated to
+ * be the faster.  Same bytes either way; no state; next->w_hat must not overlap x, w
  * or y (GWS_ERR_ALIAS).                                                                        */
 int gws_gemm_bf16_sample_next(const void* x, int64_t M, int64_t K, int64_t ldx,
                               const void* w, int64_t N, int64_t ldw, int w_is_nk,

@@ -505,7 +505,7 @@ int gws_linear_fwd_mode(const void* x, int64_t M, int64_t K, int64_t ldx, const 
   g.scale = w->scale; g.w_hat = (uint16_t*)w->w_hat;
   if (mode == GWS_LINEAR_AUTO) {
     // Measured on MI355X: sampling the weight once with the streaming kernel and running the plain GEMM on w_hat beats the
-    // kernel that samples in its operand load (8192 tokens: 0.155 against 0.61 ms) except for a few tokens.
+    // kernel that samples in its operand load (8192 x 2048 -> 5632 in FP8: 147 against 291 us) except for a few tokens.
     mode = w->w_hat && !(sample_in_operand(g, w_is_nk) && outputs_apart(g, *w)) ? GWS_LINEAR_TWO_KERNELS : GWS_LINEAR_IN_OPERAND;
   }
   if (mode == GWS_LINEAR_TWO_KERNELS) {

@@ -3,8 +3,9 @@
 //
 // Workgroup = 2 x 2 wavefronts, tile 128 x 32 NJ (NJ 4 or 3), K-steps of 64; a wavefront owns 64 x 16 NJ of the output as 4 x NJ
 // v_mfma_f32_16x16x32_bf16 tiles.  Both operand tiles (16 KiB, and 16 or 12) go global -> LDS directly into a ring of four stages,
-// in the layouts of gws_gemm256_core.h (96 columns of a [K x N] weight as in gws_gemm_stream_core.h), three K-steps ahead; one barrier a K-step, between its two 32-deep halves: the second
-// half's fragments are read under the first half's MFMAs, the next step's first ones under the second half's.
+// in the layouts of gws_gemm256_core.h (96 columns of a [K x N] weight as in gws_gemm_stream_core.h), three K-steps ahead; one
+// barrier a K-step, between its two 32-deep halves: the second half's fragments are read under the first half's MFMAs, the next
+// step's first ones under the second half's.
 // What bounds it: a K-step of 128 x 128 takes 0.41 us (W [N x K]; 0.43 for [K x N]), of which the operands' 32 KiB from L2 alone 0.34, the
 // MFMAs alone 0.25 and the LDS reads alone 0.17; misses in L2 are not it (0.39 without any).  A launch starts and ends in 6 us.
 // 128 x 96 is for the sizes whose 128 x 128 tiles leave compute units idle in their rounds: 4096 x 3072 -> 768 is 256 tiles instead of
@@ -57,9 +58,9 @@ __global__ __launch_bounds__(256) void gemm128_kernel(const GemmArgs g) {
   uint32_t k_next = 0;                   // first k of the step that is fetched next
   const uint32_t lds_x = (uint32_t)(uintptr_t)(GWS_LDS void*)lds + wave * 4096;
   const uint32_t lds_w = (uint32_t)(uintptr_t)(GWS_LDS void*)lds + OP * 2 + wave * (NJ * 1024);
-  // two of a step's loads (n = 0 .. 3): X, W, X, W (of three of W the last one comes alone).  One wavefront a SIMD issues an instruction in about five cycles, an
-  // MFMA takes sixteen: the loop has room for two instructions beside each MFMA, so addresses are kept as running scalars and
-  // two loads share one setting of M0.
+  // two of a step's loads (n = 0 .. 3): X, W, X, W (of three of W the last one comes alone).  One wavefront a SIMD issues an
+  // instruction in about five cycles, an MFMA takes sixteen: the loop has room for two instructions beside each MFMA, so addresses
+  // are kept as running scalars and two loads share one setting of M0.
   auto load_n = [&](uint32_t stage, int n) {
     const uint32_t dst = (n & 1 ? lds_w : lds_x) + stage;
     const bool alone = NJ == 3 && n == 3;

@@ -246,8 +246,9 @@ struct Blocks {
 };
 
 // The sampling form: a wavefront keeps a step's blocks on their way into registers while it samples those of the step before,
-// turns them through its own 2.5 KiB of LDS a block and multiplies.  Bound by the vector ALU work of the sampling, which every
-// 16 MT rows of X repeat.  Two blocks a step where a compute unit has only one such workgroup's wavefronts (16 rows: 16 x 2048
+// turns them through its own 2.5 KiB of LDS a block and multiplies.  Bound by the sampling, which every 16 MT rows of X repeat: with
+// 16 rows, two wavefronts a SIMD, the vector ALU issues in 66 % of a workgroup's cycles, and the rest is the chain from a block's
+// maximum to its MFMA.  Two blocks a step where a compute unit has only one such workgroup's wavefronts (16 rows: 16 x 2048
 // -> 5632 11.6 -> 11.4 us, 16 x 768 -> 3072 8.0 -> 7.6), one where it may have several (300 x 2048 -> 5632 41 us, two blocks 46).
 // TAIL: K ends with half a step of two blocks.  W: wavefronts a SIMD that the registers have to leave room for.
 template <int MT, int P, int FMT, bool W_NK, int B, bool TAIL, int W>
@@ -317,8 +318,8 @@ void gemm_stream_sample_kernel(const GemmArgs g) {
 // Many rows of X, the weight sampled on its way in, K from end to end (the order of the middle and large tiles' sums, so Y is
 // their Y): a workgroup owns 256 rows x 256 columns, a wavefront 32 of the columns.  X comes through LDS in units of 64 k, a ring of
 // stages that the wavefronts share, one barrier a unit; the weight's blocks go from a wavefront's registers through its own LDS as
-// above, two a unit.  Bound by the vector ALU work of the sampling, which every tile of rows repeats (128 rows a tile: twice of
-// it).  Two of the eight wavefronts share a SIMD, and the barrier keeps them abreast: the later four multiply a unit after the next
+// above, two a unit.  Bound by the sampling, which every tile of rows repeats (128 rows a tile: twice of it): the vector ALU issues in
+// 64 % of the cycles, the matrix cores work in 29 %.  Two of the eight wavefronts share a SIMD, and the barrier keeps them abreast: the later four multiply a unit after the next
 // barrier (hence a third stage), before they sample, so that one's MFMAs run under the other's sampling.  FP8, [K x N] and [N x K],
 // us, tiles of 128 x 128 by four wavefronts and this: 8192 x 2048 -> 5632 462, 424 -> 290, 304 (FP6 548, 508 -> 359, 368; BF16 385,
 // 373 -> 288, 285); 8192 x 2048 -> 2048 160, 161 -> 99, 106.

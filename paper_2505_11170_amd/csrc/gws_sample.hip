@@ -6,11 +6,12 @@
 // rows {r, r+8, r+16, r+24}, column group c.  Each load instruction of a wave
 // therefore covers 8 rows x 128 contiguous bytes, the four waves of a workgroup
 // sit side by side (512 contiguous bytes per row), and the per-block reductions
-// (absmax, sum of g.*R) stay inside one wavefront: no LDS, no barrier.
+// (absmax, sum of g.*R) stay inside one wavefront: no LDS and no barrier, except
+// where microscaling codes are gathered into rows of the workgroup (store_mx_rows).
 // A workgroup covers one such 32 x 256 tile in the forward pass and up to four
 // neighbouring column tiles in the lighter backward pass, where the per-wavefront
-// set-up would otherwise show.  Latency is hidden by occupancy, and four wavefronts
-// a SIMD are the right number (GWS_FOUR_WAVES).
+// set-up would otherwise show.  Four wavefronts a SIMD hide the latency of memory,
+// and more are slower where it is memory that bounds a pass (GWS_FOUR_WAVES).
 // One Philox4x32-10 call yields the 16 bits x 8 elements of one 16-byte group,
 // so the noise lives only in registers (2 bytes per parameter of HBM traffic per
 // operand, Sec. 3.5; the 0.5 byte per parameter temporary of the paper is gone).
@@ -226,7 +227,7 @@ __global__ __launch_bounds__(kThreads) GWS_WAVES(EIGHT) void sample_bwd_kernel(c
 // The forward pass on a workgroup's 32 x 256 tile with MX output: the codes are staged in LDS and go to memory by rows, 16 bytes
 // a thread, so that an instruction covers whole rows of the tile (192 bytes of FP6, 256 of FP8) and not each wavefront's quarter
 // of many.  FP6 from the wavefronts' own 48 bytes a row made 3.7 times as many write requests as lines: 352 M parameters 183 us,
-// 159 like this (FP8 173, 170); 809 M in rows of 4096 and 11008 elements 407 us, 351 (FP8 392, 369).  Rows of FP6 codes are
+// 159 like this, 6.3 TB/s with no idle cycle of the vector ALU (FP8 173, 170); 809 M in rows of 4096 and 11008 elements 407 us, 351 (FP8 392, 369).  Rows of FP6 codes are
 // 2-byte aligned, rows of FP8 codes 8-byte aligned.
 template <int FMT, int STREAM>
 __device__ __forceinline__ void store_mx_rows(const TileDesc& d, Tile& t, const TileNoise<kBasisBits>& n, uint32_t by, uint32_t bx, float bt) {
