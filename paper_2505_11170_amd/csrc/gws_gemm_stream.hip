@@ -316,13 +316,14 @@ void gemm_stream_sample_kernel(const GemmArgs g) {
 }
 
 // Many rows of X, the weight sampled on its way in, K from end to end (the order of the middle and large tiles' sums, so Y is
-// their Y): a workgroup owns 256 rows x 256 columns, a wavefront 32 of the columns.  X comes through LDS in units of 64 k, a ring of
-// stages that the wavefronts share, one barrier a unit; the weight's blocks go from a wavefront's registers through its own LDS as
-// above, two a unit.  Bound by the sampling, which every tile of rows repeats (128 rows a tile: twice of it): the vector ALU issues in
-// 64 % of the cycles, the matrix cores work in 29 %.  Two of the eight wavefronts share a SIMD, and the barrier keeps them abreast: the later four multiply a unit after the next
-// barrier (hence a third stage), before they sample, so that one's MFMAs run under the other's sampling.  FP8, [K x N] and [N x K],
-// us, tiles of 128 x 128 by four wavefronts and this: 8192 x 2048 -> 5632 462, 424 -> 290, 304 (FP6 548, 508 -> 359, 368; BF16 385,
-// 373 -> 288, 285); 8192 x 2048 -> 2048 160, 161 -> 99, 106.
+// their Y): a workgroup owns 256 rows x 256 columns, a wavefront 32 of the columns.  X comes through LDS in units of 64 k, a
+// ring of stages that the wavefronts share, one barrier a unit; the weight's blocks go from a wavefront's registers through its
+// own LDS as above, two a unit.  Bound by the sampling, which every tile of rows repeats (128 rows a tile: twice of it): the
+// vector ALU issues in 64 % of the cycles, the matrix cores work in 29 %.  Two of the eight wavefronts share a SIMD, and the
+// barrier keeps them abreast: the later four multiply a unit after the next barrier (hence a third stage), before they sample,
+// so that one's MFMAs run under the other's sampling.  FP8, [K x N] and [N x K], us, tiles of 128 x 128 by four wavefronts and
+// this: 8192 x 2048 -> 5632 462, 424 -> 290, 304 (FP6 548, 508 -> 359, 368; BF16 385, 373 -> 288, 285); 8192 x 2048 -> 2048 160,
+// 161 -> 99, 106.
 template <int FMT, bool W_NK>
 __global__ __launch_bounds__(512, 2) void gemm_rows_sample_kernel(const GemmArgs g) {
   using namespace stream;

@@ -227,8 +227,8 @@ __global__ __launch_bounds__(kThreads) GWS_WAVES(EIGHT) void sample_bwd_kernel(c
 // The forward pass on a workgroup's 32 x 256 tile with MX output: the codes are staged in LDS and go to memory by rows, 16 bytes
 // a thread, so that an instruction covers whole rows of the tile (192 bytes of FP6, 256 of FP8) and not each wavefront's quarter
 // of many.  FP6 from the wavefronts' own 48 bytes a row made 3.7 times as many write requests as lines: 352 M parameters 183 us,
-// 159 like this, 6.3 TB/s with no idle cycle of the vector ALU (FP8 173, 170); 809 M in rows of 4096 and 11008 elements 407 us, 351 (FP8 392, 369).  Rows of FP6 codes are
-// 2-byte aligned, rows of FP8 codes 8-byte aligned.
+// 159 like this, 6.3 TB/s with no idle cycle of the vector ALU (FP8 173, 170); 809 M in rows of 4096 and 11008 elements 407 us,
+// 351 (FP8 392, 369).  Rows of FP6 codes are 2-byte aligned, rows of FP8 codes 8-byte aligned.
 template <int FMT, int STREAM>
 __device__ __forceinline__ void store_mx_rows(const TileDesc& d, Tile& t, const TileNoise<kBasisBits>& n, uint32_t by, uint32_t bx, float bt) {
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, gc = lane & 7, r0 = lane >> 3;
