@@ -129,9 +129,13 @@ int run_batched(const gws_tensor* t, int n, const gws_bitwidth* bw, const gws_mx
   // while at least ~3000 workgroups (12 per compute unit) remain (measured: 3 best on the 85 M parameters
   // of GPT2-124M, 4 on the 1B model; 6 and more lose).  Neighbouring column tiles, not rows: the
   // workgroups in flight then still cover a contiguous stretch of memory, which the memory system rewards.
-  uint64_t total = 0;
+  uint64_t total = 0, present = 0, live = 0;   // workgroup tiles; elements, and those of the 32 x 64 tiles that have any
   for (int i = 0; i < n; ++i)
-    if (t[i].rows > 0 && t[i].cols > 0) total += wg_count(t[i], 1, 1);
+    if (t[i].rows > 0 && t[i].cols > 0) {
+      total += wg_count(t[i], 1, 1);
+      present += (uint64_t)t[i].rows * (uint64_t)t[i].cols;
+      live += (uint64_t)((t[i].rows + 31) / 32) * (uint64_t)((t[i].cols + 63) / 64) * 2048;
+    }
   uint32_t per_wg = 1, per_x = 1;
   // Where dL/dw is copied the pass is the forward pass's traffic: one tile (75 M parameters in rows of 2000 bytes: 60 us, 69
   // with two, 78 with three).
@@ -162,9 +166,14 @@ int run_batched(const gws_tensor* t, int n, const gws_bitwidth* bw, const gws_mx
   // The kernels for any shape: up to eight wavefronts a SIMD while what a pass reads and writes fits in the 256 MB last-level cache,
   // and in any size where it only reads; four beyond (gws_sample.hip).  Ragged weights of the bit basis, ratio to four: forward
   // 4 - 12 M parameters 0.97, 25 - 45 M 0.98, 64 - 96 M 1.04, 260 - 500 M 1.10; backward 25 - 45 M 0.87, 260 - 500 M 0.95; with dL/dw
-  // copied 25 - 45 M 0.98, 64 - 96 M 1.05.
+  // copied 25 - 45 M 0.98, 64 - 96 M 1.05.  Four wavefronts' loads cover the latency of memory where their 32 x 64 tiles are full: up to
+  // eight also where three quarters of them or less exist, or half of the workgroups' tiles (rows of at most 128 elements).  Forward in
+  // FP8 and copying backward, four and eight, us: 8 x 4 M 53, 43 and 49, 40; 16 x 8 M 121, 97 and 113, 103; 40 x 4 M 158, 159 and
+  // 149, 136; 2 M x 40 123, 95 and 155, 138; 24 x 6 M (3/4) 116, 118 and 126, 112; 600 000 x 100 69, 70 and 79, 72; 500 000 x 128 45, 42 and
+  // 46, 45; beyond the lines 400 000 x 200 65, 68 and 67, 68; 300 000 x 264 96, 99 and 96, 99.
   const uint64_t written = !fwd ? (copies ? tile_bytes : 0) : !mx ? tile_bytes : fmt == GWS_FMT_FP8_E4M3 ? tile_bytes / 2 : tile_bytes / 8 * 3;
-  const int any_shape = written == 0 || tile_bytes + written <= ((uint64_t)224 << 20) ? 2 : 0;
+  const int any_shape = written == 0 || tile_bytes + written <= ((uint64_t)224 << 20) ||
+                        4 * present <= 3 * live || 2 * present <= total * (32 * kTileCols) ? 2 : 0;
 
   LaunchArgs a;
   memset(&a, 0, sizeof a);

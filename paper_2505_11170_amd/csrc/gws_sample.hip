@@ -122,8 +122,8 @@ __device__ __forceinline__ void walk_tiles(const ARGS& a, const TileDesc& d, uin
 // with 8, 7, 6, 5, 4 and 2 wavefronts a SIMD 927, 923, 891, 891, 876 and 1004 us, of the 124M model 87, 87, 85, 85, 83, 95.
 // The registers that this leaves (128) let the compiler interleave a tile's groups: MX-FP6 of 352 M parameters 195 -> 182 us.
 #define GWS_FOUR_WAVES __attribute__((amdgpu_waves_per_eu(4, 4)))
-// Weights of any shape: up to eight (EIGHT) while what the pass reads and writes fits in the last-level cache, and wherever it only
-// reads (run_batched).  Backward pass of the uniform basis on whole tiles: up to eight too, as that basis has more left to do when the
+// Weights of any shape: up to eight (EIGHT) while what the pass reads and writes fits in the last-level cache, wherever it only reads
+// and where much of the tiles lies outside the weights (run_batched).  Backward pass of the uniform basis on whole tiles: up to eight too, as that basis has more left to do when the
 // tile has come (34.7 M parameters 11.3 us, 12.0 with four).
 #define GWS_WAVES(eight) __attribute__((amdgpu_waves_per_eu(4, (eight) ? 8 : 4)))
 
