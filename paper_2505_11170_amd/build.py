@@ -22,6 +22,7 @@ OUT = os.path.join(_HERE, "libgws.so")
 
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-mllvm", "-amdgpu-kernarg-preload-count=16",   # plain kernel arguments arrive in scalar registers
          "-Wall", "-Wno-unused-command-line-argument"]
 
 

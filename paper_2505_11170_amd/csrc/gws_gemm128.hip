@@ -22,8 +22,9 @@ __device__ __forceinline__ uint32_t umin(uint32_t a, uint32_t b) { return a < b 
 }  // namespace g128
 
 template <bool W_NK, int NJ>
-__global__ __launch_bounds__(256) void gemm128_kernel(const GemmArgs g) {
+__global__ __launch_bounds__(256) void gemm128_kernel(GWS_GEMM_PARAMS) {
   using namespace g128;
+  const GemmArgs g = GWS_GEMM_GATHER({});
   constexpr int TN = 32 * NJ, OP = T * TK, STG = OP + TN * TK;   // columns of a tile; elements of the X tile, of a stage
   constexpr int PC = 16 * NJ + 8;                                // pitch of a wavefront's staged rows (elements)
   constexpr int LOADS = 4 + NJ;                                  // load instructions of a wavefront and K-step
@@ -31,7 +32,7 @@ __global__ __launch_bounds__(256) void gemm128_kernel(const GemmArgs g) {
   const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = wave >> 1, wn = wave & 1;
   uint32_t tile_m, tile_n;
-  tile_of(blockIdx.x, (g.M + T - 1) / T, (g.N + TN - 1) / TN, tile_m, tile_n);
+  tile_of(TileGrid{(g.M + T - 1) / T, (g.N + TN - 1) / TN, g.inv_band, g.inv_last}, blockIdx.x, tile_m, tile_n);
   const uint32_t m0 = tile_m * T, n0 = tile_n * TN;
 
   // a wavefront's load instructions of an operand tile, four and NJ; rows and columns past the edge are read from the last ones
@@ -208,11 +209,12 @@ bool gemm128_applicable(const GemmArgs& g) {
 }
 
 template <int NJ>
-static int launch_tiles(const GemmArgs& g, int w_is_nk, hipStream_t stream) {
-  const uint64_t tiles = (uint64_t)((g.M + g128::T - 1) / g128::T) * ((g.N + 32 * NJ - 1) / (32 * NJ));
-  if (tiles >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
-  if (w_is_nk) hipLaunchKernelGGL((gemm128_kernel<true, NJ>), dim3((uint32_t)tiles), dim3(256), 0, stream, g);
-  else hipLaunchKernelGGL((gemm128_kernel<false, NJ>), dim3((uint32_t)tiles), dim3(256), 0, stream, g);
+static int launch_tiles(GemmArgs g, int w_is_nk, hipStream_t stream) {
+  const uint32_t mt = (uint32_t)(((uint64_t)g.M + g128::T - 1) / g128::T), nt = (uint32_t)(((uint64_t)g.N + 32 * NJ - 1) / (32 * NJ));
+  if ((uint64_t)mt * nt >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
+  set_tile_grid(g, mt, nt);
+  if (w_is_nk) hipLaunchKernelGGL((gemm128_kernel<true, NJ>), dim3(mt * nt), dim3(256), 0, stream, GWS_GEMM_PASS(g));
+  else hipLaunchKernelGGL((gemm128_kernel<false, NJ>), dim3(mt * nt), dim3(256), 0, stream, GWS_GEMM_PASS(g));
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
 

@@ -17,23 +17,25 @@ namespace gws {
 template <bool W_NK>
 __device__ __forceinline__ void gemm256_tile(const GemmArgs& g, const uint16_t* __restrict__ wsrc, uint32_t L) {
   uint32_t tile_m, tile_n;
-  tile_of(L, g.M / g256::TM, g.N / g256::TN, tile_m, tile_n);
+  tile_of(TileGrid{g.M / g256::TM, g.N / g256::TN, g.inv_band, g.inv_last}, L, tile_m, tile_n);
   gemm256_core<false, !W_NK>(g.x, g.ldx, wsrc, g.ldw, g.y, g.ldy, g.K / g256::TK, tile_m * g256::TM,
                              tile_n * g256::TN, NoHook{});
 }
 
 template <bool W_NK>
-__global__ __launch_bounds__(256, 1) void gemm256_kernel(const GemmArgs g) {
+__global__ __launch_bounds__(256, 1) void gemm256_kernel(GWS_GEMM_PARAMS) {
+  const GemmArgs g = GWS_GEMM_GATHER({});
   gemm256_tile<W_NK>(g, g.w, blockIdx.x);
 }
 
 // The same for any M, N of whole 32s and K of whole 32s: edge tiles do a whole tile's work on repeated rows and columns and
 // store what exists.
 template <bool W_NK>
-__global__ __launch_bounds__(256, 1) void gemm256_edge_kernel(const GemmArgs g) {
+__global__ __launch_bounds__(256, 1) void gemm256_edge_kernel(GWS_GEMM_PARAMS) {
   using namespace g256;
+  const GemmArgs g = GWS_GEMM_GATHER({});
   uint32_t tile_m, tile_n;
-  tile_of(blockIdx.x, (g.M + TM - 1) / TM, (g.N + TN - 1) / TN, tile_m, tile_n);
+  tile_of(TileGrid{(g.M + TM - 1) / TM, (g.N + TN - 1) / TN, g.inv_band, g.inv_last}, blockIdx.x, tile_m, tile_n);
   const uint32_t m0 = tile_m * TM, n0 = tile_n * TN, rows = g.M - m0 < TM ? g.M - m0 : TM, cols = g.N - n0 < TN ? g.N - n0 : TN;
   gemm256_core<false, !W_NK, true>(g.x, g.ldx, g.w, g.ldw, g.y, g.ldy, (g.K + TK - 1) / TK, m0, n0, NoHook{}, rows, cols, g.K);
 }
@@ -154,8 +156,9 @@ __device__ __forceinline__ void ride_tiles(uint32_t step_lo, uint32_t step_hi, c
 // synchronisation, no state.
 // RIDER: 0 = sample_tiles on r.d[0] alone (any weight of whole 32 x 64 tiles), 1 = ride_tiles (whole 32 x 256 tiles)
 template <int FMT, bool W_NK, int RIDER>
-__global__ __launch_bounds__(256, 1) void gemm256_ride_kernel(const GemmArgs g, const RideList r, const uint32_t step_lo,
-                                                              const uint32_t step_hi, const uint32_t tiles) {
+__global__ __launch_bounds__(256, 1) void gemm256_ride_kernel(GWS_GEMM_PARAMS, const uint32_t tiles, const RideList r,
+                                                              const uint32_t step_lo, const uint32_t step_hi) {
+  const GemmArgs g = GWS_GEMM_GATHER({});
   if (blockIdx.x < tiles) {
     gemm256_tile<W_NK>(g, g.w, blockIdx.x);
   } else {
@@ -170,16 +173,18 @@ template <int FMT, int RIDER>
 static int launch_ride_fmt(const GemmArgs& g, int w_is_nk, const RideList& r, uint32_t step_lo, uint32_t step_hi,
                            uint32_t tiles, uint32_t extra, hipStream_t s) {
   if (w_is_nk)
-    hipLaunchKernelGGL((gemm256_ride_kernel<FMT, true, RIDER>), dim3(tiles + extra), dim3(256), 0, s, g, r, step_lo, step_hi, tiles);
+    hipLaunchKernelGGL((gemm256_ride_kernel<FMT, true, RIDER>), dim3(tiles + extra), dim3(256), 0, s, GWS_GEMM_PASS(g), tiles, r, step_lo, step_hi);
   else
-    hipLaunchKernelGGL((gemm256_ride_kernel<FMT, false, RIDER>), dim3(tiles + extra), dim3(256), 0, s, g, r, step_lo, step_hi, tiles);
+    hipLaunchKernelGGL((gemm256_ride_kernel<FMT, false, RIDER>), dim3(tiles + extra), dim3(256), 0, s, GWS_GEMM_PASS(g), tiles, r, step_lo, step_hi);
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
 
-int launch_gemm256_ride(const GemmArgs& g, int w_is_nk, const RideList& r, int fmt, uint64_t step, uint32_t extra,
+int launch_gemm256_ride(const GemmArgs& args, int w_is_nk, const RideList& r, int fmt, uint64_t step, uint32_t extra,
                         int rider, hipStream_t stream) {
+  GemmArgs g = args;
   const uint64_t tiles = (uint64_t)(g.M / g256::TM) * (g.N / g256::TN);
   if (tiles + extra >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
+  if (tiles > 0) set_tile_grid(g, g.M / g256::TM, g.N / g256::TN);
   const uint32_t lo = (uint32_t)step, hi = (uint32_t)(step >> 32);
   if (rider == 1) {
     switch (fmt) {
@@ -216,10 +221,11 @@ bool gemm256_applicable(const GemmArgs& g) {
 // Tiles of 256 x 192, with the edges of gemm256_edge_kernel: for products whose 256 x 256 tiles leave the last round of
 // compute units emptier than these do.
 template <bool W_NK>
-__global__ __launch_bounds__(256, 1) void gemm256_narrow_kernel(const GemmArgs g) {
+__global__ __launch_bounds__(256, 1) void gemm256_narrow_kernel(GWS_GEMM_PARAMS) {
   using namespace g256;
+  const GemmArgs g = GWS_GEMM_GATHER({});
   uint32_t tile_m, tile_n;
-  tile_of(blockIdx.x, (g.M + TM - 1) / TM, (g.N + kNarrow - 1) / kNarrow, tile_m, tile_n);
+  tile_of(TileGrid{(g.M + TM - 1) / TM, (g.N + kNarrow - 1) / kNarrow, g.inv_band, g.inv_last}, blockIdx.x, tile_m, tile_n);
   const uint32_t m0 = tile_m * TM, n0 = tile_n * kNarrow, rows = g.M - m0 < TM ? g.M - m0 : TM, cols = g.N - n0 < kNarrow ? g.N - n0 : kNarrow;
   gemm256_accumulate<false, !W_NK, true, 6>(g.x, g.ldx, g.w, g.ldw, (g.K + TK - 1) / TK, m0, n0,
                                             [&](f32x4 (&acc)[8][6], uint16_t* cs, uint32_t wave, uint32_t lane) {
@@ -233,12 +239,18 @@ __global__ __launch_bounds__(256, 1) void gemm256_narrow_kernel(const GemmArgs g
   }, rows, cols, g.K);
 }
 
-int launch_gemm256_narrow(const GemmArgs& g, int w_is_nk, hipStream_t stream) {
-  const uint64_t tiles = (uint64_t)((g.M + g256::TM - 1) / g256::TM) * ((g.N + g256::kNarrow - 1) / g256::kNarrow);
-  if (tiles >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
-  if (w_is_nk) hipLaunchKernelGGL(gemm256_narrow_kernel<true>, dim3((uint32_t)tiles), dim3(256), 0, stream, g);
-  else hipLaunchKernelGGL(gemm256_narrow_kernel<false>, dim3((uint32_t)tiles), dim3(256), 0, stream, g);
+// A kernel of the three on its grid of tiles of TM x tn.
+template <class K>
+static int launch_tiles(K kernel, GemmArgs g, uint32_t tn, hipStream_t stream) {
+  const uint32_t mt = (uint32_t)(((uint64_t)g.M + g256::TM - 1) / g256::TM), nt = (uint32_t)(((uint64_t)g.N + tn - 1) / tn);
+  if ((uint64_t)mt * nt >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
+  set_tile_grid(g, mt, nt);
+  hipLaunchKernelGGL(kernel, dim3(mt * nt), dim3(256), 0, stream, GWS_GEMM_PASS(g));
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
+}
+
+int launch_gemm256_narrow(const GemmArgs& g, int w_is_nk, hipStream_t stream) {
+  return launch_tiles(w_is_nk ? gemm256_narrow_kernel<true> : gemm256_narrow_kernel<false>, g, g256::kNarrow, stream);
 }
 
 bool gemm256_edge_applicable(const GemmArgs& g) {
@@ -246,19 +258,11 @@ bool gemm256_edge_applicable(const GemmArgs& g) {
 }
 
 int launch_gemm256_edge(const GemmArgs& g, int w_is_nk, hipStream_t stream) {
-  const uint64_t tiles = (uint64_t)((g.M + g256::TM - 1) / g256::TM) * ((g.N + g256::TN - 1) / g256::TN);
-  if (tiles >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
-  if (w_is_nk) hipLaunchKernelGGL(gemm256_edge_kernel<true>, dim3((uint32_t)tiles), dim3(256), 0, stream, g);
-  else hipLaunchKernelGGL(gemm256_edge_kernel<false>, dim3((uint32_t)tiles), dim3(256), 0, stream, g);
-  return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
+  return launch_tiles(w_is_nk ? gemm256_edge_kernel<true> : gemm256_edge_kernel<false>, g, g256::TN, stream);
 }
 
 int launch_gemm256(const GemmArgs& g, int w_is_nk, hipStream_t stream) {
-  const uint64_t tiles = (uint64_t)(g.M / g256::TM) * (g.N / g256::TN);
-  if (tiles >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
-  if (w_is_nk) hipLaunchKernelGGL(gemm256_kernel<true>, dim3((uint32_t)tiles), dim3(256), 0, stream, g);
-  else hipLaunchKernelGGL(gemm256_kernel<false>, dim3((uint32_t)tiles), dim3(256), 0, stream, g);
-  return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
+  return launch_tiles(w_is_nk ? gemm256_kernel<true> : gemm256_kernel<false>, g, g256::TN, stream);
 }
 
 }  // namespace gws

@@ -73,21 +73,6 @@ union Frag8 {
   i16x4 h[2];
 };
 
-// XCD-aware tile numbering: launch-order number L -> (tile_m, tile_n) of an mt x nt grid of
-// tiles.  Workgroups are dealt round-robin to the 8 XCDs, each with its own L2; XCD x gets
-// a contiguous range of an order that walks 8 m-tiles down before moving one n-tile right,
-// so the 32 workgroups running together on an XCD form an 8 x 4 patch sharing 8 + 4 panels.
-__device__ __forceinline__ void tile_of(uint32_t L, uint32_t mt, uint32_t nt, uint32_t& tile_m, uint32_t& tile_n) {
-  const uint32_t total = mt * nt;
-  const uint32_t per = total / 8, rem = total % 8, x = L % 8, j = L / 8;
-  L = x * per + (x < rem ? x : rem) + j;            // XCD x owns `per` tiles (+1 for the first `rem`)
-  const uint32_t band_sz = 8 * nt;                   // tiles in a band of 8 m-tiles
-  const uint32_t band = L / band_sz, r = L % band_sz;
-  const uint32_t mrows = (band * 8 + 8 <= mt) ? 8 : (mt - band * 8);  // last band may be short
-  tile_n = r / mrows;
-  tile_m = band * 8 + r % mrows;
-}
-
 // Half h (rows 64 h .. 64 h + 63) of a wavefront's 128 x 128 part of the result on its way out: fp32 -> BF16 (RNE)
 // into the wavefront's staging area `cs` (64 rows of pitch PC; 8 bytes per lane: its four consecutive columns),
 // then 16-byte groups to yw[(64 h + row) * ldy + col], each also handed to hook(it, row, col, v) with it = 16 h + the

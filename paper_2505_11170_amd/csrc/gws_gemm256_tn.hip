@@ -58,7 +58,7 @@ template <bool DBT>
 __device__ __forceinline__ void gemm256_tn_tile(const GemmArgs& g, uint32_t L) {
   using namespace g256;
   uint32_t tile_m, tile_n;
-  tile_of(L, g.M / TM, g.N / TN, tile_m, tile_n);
+  tile_of(TileGrid{g.M / TM, g.N / TN, g.inv_band, g.inv_last}, L, tile_m, tile_n);
   const uint32_t m0 = tile_m * TM, n0 = tile_n * TN;
   gemm256_accumulate<true, true>(g.x, g.ldx, g.w, g.ldw, g.K / TK, m0, n0,
                                  [&](f32x4 (&acc)[8][8], uint16_t* cs, uint32_t wave, uint32_t lane) {
@@ -70,7 +70,8 @@ __device__ __forceinline__ void gemm256_tn_tile(const GemmArgs& g, uint32_t L) {
 }
 
 template <bool DBT>
-__global__ __launch_bounds__(256, 1) void gemm256_tn_kernel(const GemmArgs g) {
+__global__ __launch_bounds__(256, 1) void gemm256_tn_kernel(GWS_GEMM_PARAMS, const GemmSampling sampling) {
+  const GemmArgs g = GWS_GEMM_GATHER(sampling);
   gemm256_tn_tile<DBT>(g, blockIdx.x);
 }
 
@@ -78,10 +79,11 @@ __global__ __launch_bounds__(256, 1) void gemm256_tn_kernel(const GemmArgs g) {
 // compute units idle in a round that as many narrow ones fill: 2048 x 5632 over 8192 tokens has 176 of the one (188 us) and
 // 240 of the other (163), on 256 compute units.
 template <bool DBT>
-__global__ __launch_bounds__(256, 1) void gemm256_tn_narrow_kernel(const GemmArgs g) {
+__global__ __launch_bounds__(256, 1) void gemm256_tn_narrow_kernel(GWS_GEMM_PARAMS, const GemmSampling sampling) {
   using namespace g256;
+  const GemmArgs g = GWS_GEMM_GATHER(sampling);
   uint32_t tile_m, tile_n;
-  tile_of(blockIdx.x, g.M / TM, (g.N + kNarrow - 1) / kNarrow, tile_m, tile_n);
+  tile_of(TileGrid{g.M / TM, (g.N + kNarrow - 1) / kNarrow, g.inv_band, g.inv_last}, blockIdx.x, tile_m, tile_n);
   const uint32_t m0 = tile_m * TM, n0 = tile_n * kNarrow, cols = g.N - n0 < kNarrow ? g.N - n0 : kNarrow;
   gemm256_accumulate<true, true, true, 6>(g.x, g.ldx, g.w, g.ldw, g.K / TK, m0, n0,
                                           [&](f32x4 (&acc)[8][6], uint16_t* cs, uint32_t wave, uint32_t lane) {
@@ -117,12 +119,13 @@ __global__ __launch_bounds__(256, 1) void gemm256_tn_narrow_kernel(const GemmArg
 // on timing: no atomics, no arrival order.
 constexpr uint32_t kSlabFloats = 256 * 256;
 
-__global__ __launch_bounds__(256, 1) void gemm256_tn_part_kernel(const GemmArgs g, float* __restrict__ ws, const uint32_t parts) {
+__global__ __launch_bounds__(256, 1) void gemm256_tn_part_kernel(GWS_GEMM_PARAMS, const uint32_t parts, float* __restrict__ ws) {
   using namespace g256;
+  const GemmArgs g = GWS_GEMM_GATHER({});
   const uint32_t tiles = (g.M / TM) * (g.N / TN);
   const uint32_t L = blockIdx.x % tiles, s = blockIdx.x / tiles;
   uint32_t tile_m, tile_n;
-  tile_of(L, g.M / TM, g.N / TN, tile_m, tile_n);
+  tile_of(TileGrid{g.M / TM, g.N / TN, g.inv_band, g.inv_last}, L, tile_m, tile_n);
   const uint32_t nk = g.K / TK;
   const uint32_t kb = (uint32_t)((uint64_t)nk * s / parts), ke = (uint32_t)((uint64_t)nk * (s + 1) / parts);
   float* slab = ws + ((size_t)s * tiles + L) * kSlabFloats;
@@ -143,8 +146,9 @@ __global__ __launch_bounds__(256, 1) void gemm256_tn_part_kernel(const GemmArgs 
 constexpr uint32_t kMaxParts = 8;
 
 template <bool DBT>
-__global__ __launch_bounds__(256) void gemm256_tn_sum_kernel(const GemmArgs g, const float* __restrict__ ws, const uint32_t parts) {
+__global__ __launch_bounds__(256) void gemm256_tn_sum_kernel(GWS_GEMM_PARAMS, const uint32_t parts, const float* __restrict__ ws, const GemmSampling sampling) {
   using namespace g256;
+  const GemmArgs g = GWS_GEMM_GATHER(sampling);
   constexpr uint32_t PB = 32 + 8;   // pitch of a block's staged rows (elements)
   __shared__ __attribute__((aligned(16))) uint16_t stage[4 * 32 * PB];
   const uint32_t tiles = (g.M / TM) * (g.N / TN), lane = threadIdx.x & 63;
@@ -152,7 +156,7 @@ __global__ __launch_bounds__(256) void gemm256_tn_sum_kernel(const GemmArgs g, c
   // workgroup: 32 rows (br) of one 128-column half (wn) of a tile; wavefront: 32 columns of it
   const uint32_t L = blockIdx.x >> 4, br = (blockIdx.x >> 1) & 7, wn = blockIdx.x & 1;
   uint32_t tile_m, tile_n;
-  tile_of(L, g.M / TM, g.N / TN, tile_m, tile_n);
+  tile_of(TileGrid{g.M / TM, g.N / TN, g.inv_band, g.inv_last}, L, tile_m, tile_n);
   const uint32_t p0 = tile_m * TM + 32 * br, q0 = tile_n * TN + 128 * wn + 32 * wave;
   // register (i, j) of the accumulating wavefront 2 (br / 4) + wn: i = 2 (br % 4) + ii, j = 2 wave + jj
   const f32x4* in = reinterpret_cast<const f32x4*>(ws) + ((size_t)L * 4 + 2 * (br >> 2) + wn) * 4096 + (2 * (br & 3) * 8 + 2 * wave) * 64 + lane;
@@ -203,19 +207,23 @@ bool gemm256_tn_applicable(const GemmArgs& g) {
          g.ldx < g256::kMaxLd && g.ldw < g256::kMaxLd;
 }
 
-int launch_gemm256_tn(const GemmArgs& g, bool with_dbt, hipStream_t stream) {
+int launch_gemm256_tn(const GemmArgs& args, bool with_dbt, hipStream_t stream) {
+  GemmArgs g = args;
   const uint64_t tiles = (uint64_t)(g.M / g256::TM) * (g.N / g256::TN);
   if (tiles >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
-  if (with_dbt) hipLaunchKernelGGL(gemm256_tn_kernel<true>, dim3((uint32_t)tiles), dim3(256), 0, stream, g);
-  else hipLaunchKernelGGL(gemm256_tn_kernel<false>, dim3((uint32_t)tiles), dim3(256), 0, stream, g);
+  set_tile_grid(g, g.M / g256::TM, g.N / g256::TN);
+  if (with_dbt) hipLaunchKernelGGL(gemm256_tn_kernel<true>, dim3((uint32_t)tiles), dim3(256), 0, stream, GWS_GEMM_PASS(g), (const GemmSampling&)g);
+  else hipLaunchKernelGGL(gemm256_tn_kernel<false>, dim3((uint32_t)tiles), dim3(256), 0, stream, GWS_GEMM_PASS(g), (const GemmSampling&)g);
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
 
-int launch_gemm256_tn_narrow(const GemmArgs& g, bool with_dbt, hipStream_t stream) {
-  const uint64_t tiles = (uint64_t)(g.M / g256::TM) * ((g.N + g256::kNarrow - 1) / g256::kNarrow);
-  if (tiles >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
-  if (with_dbt) hipLaunchKernelGGL(gemm256_tn_narrow_kernel<true>, dim3((uint32_t)tiles), dim3(256), 0, stream, g);
-  else hipLaunchKernelGGL(gemm256_tn_narrow_kernel<false>, dim3((uint32_t)tiles), dim3(256), 0, stream, g);
+int launch_gemm256_tn_narrow(const GemmArgs& args, bool with_dbt, hipStream_t stream) {
+  GemmArgs g = args;
+  const uint32_t mt = g.M / g256::TM, nt = (g.N + g256::kNarrow - 1) / g256::kNarrow;
+  if ((uint64_t)mt * nt >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
+  set_tile_grid(g, mt, nt);
+  if (with_dbt) hipLaunchKernelGGL(gemm256_tn_narrow_kernel<true>, dim3(mt * nt), dim3(256), 0, stream, GWS_GEMM_PASS(g), (const GemmSampling&)g);
+  else hipLaunchKernelGGL(gemm256_tn_narrow_kernel<false>, dim3(mt * nt), dim3(256), 0, stream, GWS_GEMM_PASS(g), (const GemmSampling&)g);
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
 
@@ -223,13 +231,15 @@ size_t gemm256_tn_split_bytes(const GemmArgs& g, uint32_t parts) {
   return (size_t)parts * (g.M / g256::TM) * (g.N / g256::TN) * kSlabFloats * sizeof(float);
 }
 
-int launch_gemm256_tn_split(const GemmArgs& g, bool with_dbt, float* ws, uint32_t parts, hipStream_t stream) {
+int launch_gemm256_tn_split(const GemmArgs& args, bool with_dbt, float* ws, uint32_t parts, hipStream_t stream) {
+  GemmArgs g = args;
   const uint64_t tiles = (uint64_t)(g.M / g256::TM) * (g.N / g256::TN);
   if (parts < 2 || parts > kMaxParts || parts > g.K / g256::TK || tiles * 16 >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
-  hipLaunchKernelGGL(gemm256_tn_part_kernel, dim3((uint32_t)(tiles * parts)), dim3(256), 0, stream, g, ws, parts);
+  set_tile_grid(g, g.M / g256::TM, g.N / g256::TN);
+  hipLaunchKernelGGL(gemm256_tn_part_kernel, dim3((uint32_t)(tiles * parts)), dim3(256), 0, stream, GWS_GEMM_PASS(g), parts, ws);
   if (hipGetLastError() != hipSuccess) return GWS_ERR_LAUNCH;
-  if (with_dbt) hipLaunchKernelGGL(gemm256_tn_sum_kernel<true>, dim3((uint32_t)(tiles * 16)), dim3(256), 0, stream, g, (const float*)ws, parts);
-  else hipLaunchKernelGGL(gemm256_tn_sum_kernel<false>, dim3((uint32_t)(tiles * 16)), dim3(256), 0, stream, g, (const float*)ws, parts);
+  if (with_dbt) hipLaunchKernelGGL(gemm256_tn_sum_kernel<true>, dim3((uint32_t)(tiles * 16)), dim3(256), 0, stream, GWS_GEMM_PASS(g), parts, (const float*)ws, (const GemmSampling&)g);
+  else hipLaunchKernelGGL(gemm256_tn_sum_kernel<false>, dim3((uint32_t)(tiles * 16)), dim3(256), 0, stream, GWS_GEMM_PASS(g), parts, (const float*)ws, (const GemmSampling&)g);
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
 

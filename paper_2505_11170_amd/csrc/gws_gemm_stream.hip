@@ -19,8 +19,9 @@ namespace gws {
 // bytes with chunk c of row r in slot c ^ ((r / 2) % 8); a [K x N] weight as 64 k-rows of 32 NT bytes, read with the
 // transposing LDS load, chunk c of row k in slot c ^ swizzle(k).
 template <int MT, int NT, int P, int D, bool W_NK>
-__global__ __launch_bounds__(64 * P) void gemm_stream_kernel(const GemmArgs g) {
+__global__ __launch_bounds__(64 * P) void gemm_stream_kernel(GWS_GEMM_PARAMS) {
   using namespace stream;
+  const GemmArgs g = GWS_GEMM_GATHER({});
   constexpr int BM = 16 * MT, BN = 16 * NT;
   constexpr int XS = BM * 64, WS = BN * 64, STG = XS + WS;          // elements of a stage
   constexpr int QX = BM / 8, QW = BN / 8, LOADS = QX + QW;          // load instructions of a unit
@@ -253,8 +254,9 @@ struct Blocks {
 // TAIL: K ends with half a step of two blocks.  W: wavefronts a SIMD that the registers have to leave room for.
 template <int MT, int P, int FMT, bool W_NK, int B, bool TAIL, int W>
 __global__ __launch_bounds__(64 * P) __attribute__((amdgpu_waves_per_eu(W)))
-void gemm_stream_sample_kernel(const GemmArgs g) {
+void gemm_stream_sample_kernel(GWS_GEMM_PARAMS, const GemmSampling sampling) {
   using namespace stream;
+  const GemmArgs g = GWS_GEMM_GATHER(sampling);
   static_assert(B == 2 || !TAIL, "half a step is one of two blocks");
   constexpr int kRed = red_bytes(MT, 2, P), kBlk = P * B * 32 * LP * 2;
   __shared__ __attribute__((aligned(16))) char lds[kRed > kBlk ? kRed : kBlk];
@@ -325,8 +327,9 @@ void gemm_stream_sample_kernel(const GemmArgs g) {
 // this: 8192 x 2048 -> 5632 462, 424 -> 290, 304 (FP6 548, 508 -> 359, 368; BF16 385, 373 -> 288, 285); 8192 x 2048 -> 2048 160,
 // 161 -> 99, 106.
 template <int FMT, bool W_NK>
-__global__ __launch_bounds__(512, 2) void gemm_rows_sample_kernel(const GemmArgs g) {
+__global__ __launch_bounds__(512, 2) void gemm_rows_sample_kernel(GWS_GEMM_PARAMS, const GemmSampling sampling) {
   using namespace stream;
+  const GemmArgs g = GWS_GEMM_GATHER(sampling);
   constexpr int MT = 16, NW = 8, BM = 16 * MT, D = 3, XS = BM * 64, LX = BM / (8 * NW);   // LX: load instructions of a wavefront and unit
   __shared__ __attribute__((aligned(1024))) uint16_t ring[D * XS];
   __shared__ __attribute__((aligned(16))) uint16_t blocks[NW * 2 * 32 * LP];
@@ -416,8 +419,9 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_sample_kernel(const GemmArgs
 // HALF: K ends with half a unit, of which one wavefront samples its block and the other nothing (4000 x 160 -> 1664 in FP6 17.1 ->
 // 16.3).  The first unit's X comes with the weight: 1678 x 64 -> 3104 in FP6 10.9 -> 10.2.
 template <int FMT, bool W_NK, bool HALF>
-__global__ __launch_bounds__(512, 2) void gemm_rows_pair_sample_kernel(const GemmArgs g) {
+__global__ __launch_bounds__(512, 2) void gemm_rows_pair_sample_kernel(GWS_GEMM_PARAMS, const GemmSampling sampling) {
   using namespace stream;
+  const GemmArgs g = GWS_GEMM_GATHER(sampling);
   constexpr int MT = 4, BM = 128, XS = BM * 64, LX = 2;   // row tiles of a wavefront; elements of a stage; load instructions of a wavefront
   __shared__ __attribute__((aligned(1024))) uint16_t ring[2 * XS];
   __shared__ __attribute__((aligned(16))) uint16_t blocks[2][4][2][32 * LP];   // [unit][32 columns][block]
@@ -528,12 +532,12 @@ bool stream_applicable(const GemmArgs& g) {
 }
 
 template <int MT, int NT, int P, int D>
-static void launch_plain(const GemmArgs& g, int w_is_nk, hipStream_t s) {
-  const dim3 grid(((g.M + 16 * MT - 1) / (16 * MT)) * ((g.N + 16 * NT - 1) / (16 * NT)));
+static void launch_plain(GemmArgs g, int w_is_nk, hipStream_t s) {
+  const dim3 grid(stream::tile_grid(g, 16 * MT, 16 * NT));
   if (w_is_nk) {
-    hipLaunchKernelGGL((gemm_stream_kernel<MT, NT, P, D, true>), grid, dim3(64 * P), 0, s, g);
+    hipLaunchKernelGGL((gemm_stream_kernel<MT, NT, P, D, true>), grid, dim3(64 * P), 0, s, GWS_GEMM_PASS(g));
   } else {
-    if constexpr (NT >= 2) hipLaunchKernelGGL((gemm_stream_kernel<MT, NT, P, D, false>), grid, dim3(64 * P), 0, s, g);
+    if constexpr (NT >= 2) hipLaunchKernelGGL((gemm_stream_kernel<MT, NT, P, D, false>), grid, dim3(64 * P), 0, s, GWS_GEMM_PASS(g));
   }
 }
 
@@ -548,16 +552,16 @@ int launch_gemm_stream(const GemmArgs& g, int w_is_nk, const StreamPlan& p, hipS
 }
 
 template <int MT, int P, int FMT, int B, bool TAIL>
-static void launch_sampled(const GemmArgs& g, int w_is_nk, hipStream_t s) {
-  const dim3 grid(((g.M + 16 * MT - 1) / (16 * MT)) * (g.N / 32));
+static void launch_sampled(GemmArgs g, int w_is_nk, hipStream_t s) {
+  const dim3 grid(stream::tile_grid(g, 16 * MT, 32));
   const uint32_t cus = compute_units() > 0 ? compute_units() : 256;
   // [N x K] in FP8 at 64 rows is 131 registers, three wavefronts a SIMD; with more workgroups than those hold, four and two registers
   // in scratch: 755 x 96 -> 2592 8.0 -> 6.8 us (with one workgroup a compute unit 61 x 160 -> 672 4.8 -> 5.0)
   constexpr bool kTight = MT == 4 && FMT == 1;
   if (w_is_nk && kTight && grid.x > (P == 4 ? 3 : 1) * cus)
-    hipLaunchKernelGGL((gemm_stream_sample_kernel<MT, P, FMT, true, B, TAIL, kTight ? 4 : P / 4>), grid, dim3(64 * P), 0, s, g);
-  else if (w_is_nk) hipLaunchKernelGGL((gemm_stream_sample_kernel<MT, P, FMT, true, B, TAIL, P / 4>), grid, dim3(64 * P), 0, s, g);
-  else hipLaunchKernelGGL((gemm_stream_sample_kernel<MT, P, FMT, false, B, TAIL, P / 4>), grid, dim3(64 * P), 0, s, g);
+    hipLaunchKernelGGL((gemm_stream_sample_kernel<MT, P, FMT, true, B, TAIL, kTight ? 4 : P / 4>), grid, dim3(64 * P), 0, s, GWS_GEMM_PASS(g), (const GemmSampling&)g);
+  else if (w_is_nk) hipLaunchKernelGGL((gemm_stream_sample_kernel<MT, P, FMT, true, B, TAIL, P / 4>), grid, dim3(64 * P), 0, s, GWS_GEMM_PASS(g), (const GemmSampling&)g);
+  else hipLaunchKernelGGL((gemm_stream_sample_kernel<MT, P, FMT, false, B, TAIL, P / 4>), grid, dim3(64 * P), 0, s, GWS_GEMM_PASS(g), (const GemmSampling&)g);
 }
 
 uint32_t stream_sample_rows(const GemmArgs& g, int p) { return p == 4 ? 64 : g.M <= 16 ? 16 : g.M <= 32 ? 32 : 64; }
@@ -588,15 +592,15 @@ uint32_t rows_sample_tile(const GemmArgs& g) {
   return g.K > 64 && 3.1 * (double)((n256 + cus - 1) / cus) < small ? 256 : 128;   // one unit: 14.3 and 14.1 us for 4224 x 64 -> 2048
 }
 template <int FMT>
-static void launch_rows(const GemmArgs& g, int w_is_nk, hipStream_t s) {
+static void launch_rows(GemmArgs g, int w_is_nk, hipStream_t s) {
   const uint32_t t = rows_sample_tile(g);
-  const dim3 grid(((g.M + t - 1) / t) * ((g.N + t - 1) / t));
-  if (t == 256 && w_is_nk) hipLaunchKernelGGL((gemm_rows_sample_kernel<FMT, true>), grid, dim3(512), 0, s, g);
-  else if (t == 256) hipLaunchKernelGGL((gemm_rows_sample_kernel<FMT, false>), grid, dim3(512), 0, s, g);
-  else if (w_is_nk && (g.K & 32)) hipLaunchKernelGGL((gemm_rows_pair_sample_kernel<FMT, true, true>), grid, dim3(512), 0, s, g);
-  else if (w_is_nk) hipLaunchKernelGGL((gemm_rows_pair_sample_kernel<FMT, true, false>), grid, dim3(512), 0, s, g);
-  else if (g.K & 32) hipLaunchKernelGGL((gemm_rows_pair_sample_kernel<FMT, false, true>), grid, dim3(512), 0, s, g);
-  else hipLaunchKernelGGL((gemm_rows_pair_sample_kernel<FMT, false, false>), grid, dim3(512), 0, s, g);
+  const dim3 grid(stream::tile_grid(g, t, t));
+  if (t == 256 && w_is_nk) hipLaunchKernelGGL((gemm_rows_sample_kernel<FMT, true>), grid, dim3(512), 0, s, GWS_GEMM_PASS(g), (const GemmSampling&)g);
+  else if (t == 256) hipLaunchKernelGGL((gemm_rows_sample_kernel<FMT, false>), grid, dim3(512), 0, s, GWS_GEMM_PASS(g), (const GemmSampling&)g);
+  else if (w_is_nk && (g.K & 32)) hipLaunchKernelGGL((gemm_rows_pair_sample_kernel<FMT, true, true>), grid, dim3(512), 0, s, GWS_GEMM_PASS(g), (const GemmSampling&)g);
+  else if (w_is_nk) hipLaunchKernelGGL((gemm_rows_pair_sample_kernel<FMT, true, false>), grid, dim3(512), 0, s, GWS_GEMM_PASS(g), (const GemmSampling&)g);
+  else if (g.K & 32) hipLaunchKernelGGL((gemm_rows_pair_sample_kernel<FMT, false, true>), grid, dim3(512), 0, s, GWS_GEMM_PASS(g), (const GemmSampling&)g);
+  else hipLaunchKernelGGL((gemm_rows_pair_sample_kernel<FMT, false, false>), grid, dim3(512), 0, s, GWS_GEMM_PASS(g), (const GemmSampling&)g);
 }
 
 // Two workgroups of 128 rows run on a compute unit: between one and one and a half rounds of them the 128 x 128 x 32 kernel, which

@@ -49,21 +49,19 @@ __device__ __forceinline__ void unit_range(uint32_t K, uint32_t w, uint32_t P, u
   u1 = nu * (w + 1) / P;
 }
 
-// Tiles in bands of eight row tiles, row tiles first.  Workgroups are dealt round-robin to the 8 XCDs: tiles that share a
-// piece of the weight, and with narrow [K x N] tiles the two that share its cache lines, go to one XCD (its L2) as a
-// group, and the groups round-robin over the XCDs (a contiguous range per XCD would put the columns of one XCD on a few
-// of the L2's channels when a row of the weight is a multiple of 4 KiB).
-__device__ __forceinline__ void tile_origin(uint32_t M, uint32_t N, uint32_t bm, uint32_t bn, bool pairs, uint32_t& m0, uint32_t& n0) {
-  const uint32_t tm = (M + bm - 1) / bm, tn = (N + bn - 1) / bn;
-  const uint32_t G = umin(tm, 8) * (pairs ? 2 : 1), b = blockIdx.x, whole = gridDim.x / (8 * G) * (8 * G);
-  const uint32_t L = b < whole ? ((b >> 3) / G * 8 + (b & 7)) * G + (b >> 3) % G : b;
-  const uint32_t band = L / (8 * tn), r = L - band * 8 * tn, rows = umin(8, tm - 8 * band);
-  n0 = r / rows * bn;
-  m0 = (8 * band + r % rows) * bm;
-}
-
+// First row and column of the workgroup's tile of bm x bn (tile_of_groups).
 __device__ __forceinline__ void tile_origin(const GemmArgs& g, uint32_t bm, uint32_t bn, bool pairs, uint32_t& m0, uint32_t& n0) {
-  tile_origin(g.M, g.N, bm, bn, pairs, m0, n0);
+  uint32_t tm, tn;
+  tile_of_groups(TileGrid{(g.M + bm - 1) / bm, (g.N + bn - 1) / bn, g.inv_band, g.inv_last}, pairs, blockIdx.x, tm, tn);
+  m0 = tm * bm;
+  n0 = tn * bn;
+}
+// The grid of such tiles, its reciprocals put into g; 0 if it is too large.
+inline uint32_t tile_grid(GemmArgs& g, uint32_t bm, uint32_t bn) {
+  const uint32_t mt = (uint32_t)(((uint64_t)g.M + bm - 1) / bm), nt = (uint32_t)(((uint64_t)g.N + bn - 1) / bn);
+  if ((uint64_t)mt * nt >= 0x7FFFFFFFull) return 0;
+  set_tile_grid(g, mt, nt);
+  return mt * nt;
 }
 
 // The partial sums of the P wavefronts added in the order of the wavefronts, MC row tiles at a time.

@@ -53,8 +53,9 @@ __device__ __forceinline__ void rows_of_block(u32x2 (&pk)[2][2], u32x4 (&o)[2]) 
 // as shallow as the MFMA is deep.
 // HALVES: every wavefront sums its tokens in two halves, eight fp32 sums an element instead of four.
 template <int MT, int NT, int D, bool DBT, bool HALVES>
-__global__ __launch_bounds__(256, 1) void gemm_stream_tn_kernel(const GemmArgs g) {
+__global__ __launch_bounds__(256, 1) void gemm_stream_tn_kernel(GWS_GEMM_PARAMS, const GemmSampling sampling) {
   using namespace stream;
+  const GemmArgs g = GWS_GEMM_GATHER(sampling);
   constexpr int P = 4, U = 32, BM = 16 * MT, BN = 16 * NT;
   constexpr int XS = BM * U, STG = (BM + BN) * U, LOADS = MT + NT;   // elements of a stage; load instructions of a unit
   constexpr int BC = NT / 2, BLOCKS = MT / 2 * BC;                   // 32 x 32 blocks of the weight in the piece
@@ -71,8 +72,11 @@ __global__ __launch_bounds__(256, 1) void gemm_stream_tn_kernel(const GemmArgs g
   // Eight pieces along the longer side of C that share the shorter side's operand go to one XCD, which of the shorter operand then
   // reads its own part.  Along the rows whatever the shape, every XCD read all of the longer operand of a weight of few columns:
   // 1856 tokens x 1792 x 256 in pieces of 64 x 32 11.9 us, like this 10.1; 7680 x 4096 x 256 in 64 x 64 47.2, 30.0.
-  if (g.M > g.N) tile_origin(g.N, g.M, BN, BM, false, n0, m0);
-  else tile_origin(g, BM, BN, false, m0, n0);
+  const uint32_t mt = (g.M + BM - 1) / BM, nt = (g.N + BN - 1) / BN;
+  if (g.M > g.N) tile_of_groups(TileGrid{nt, mt, g.inv_band, g.inv_last}, false, blockIdx.x, n0, m0);
+  else tile_of_groups(TileGrid{mt, nt, g.inv_band, g.inv_last}, false, blockIdx.x, m0, n0);
+  m0 *= BM;
+  n0 *= BN;
   unit_range(g.K, wave, P, u0, u1);
   u0 *= 2;   // in units of 32 (the tokens are whole 64s)
   u1 *= 2;
@@ -228,10 +232,13 @@ __global__ __launch_bounds__(256, 1) void gemm_stream_tn_kernel(const GemmArgs g
 }
 
 template <int MT, int NT, int D, bool HALVES>
-static void launch_tn(const GemmArgs& g, bool with_dbt, hipStream_t s) {
-  const dim3 grid(((g.M + 16 * MT - 1) / (16 * MT)) * ((g.N + 16 * NT - 1) / (16 * NT)));
-  if (with_dbt) hipLaunchKernelGGL((gemm_stream_tn_kernel<MT, NT, D, true, HALVES>), grid, dim3(256), 0, s, g);
-  else hipLaunchKernelGGL((gemm_stream_tn_kernel<MT, NT, D, false, HALVES>), grid, dim3(256), 0, s, g);
+static void launch_tn(GemmArgs g, bool with_dbt, hipStream_t s) {
+  const uint32_t mt = (g.M + 16 * MT - 1) / (16 * MT), nt = (g.N + 16 * NT - 1) / (16 * NT);
+  if (g.M > g.N) set_tile_grid(g, nt, mt);   // the numbering runs along the longer side
+  else set_tile_grid(g, mt, nt);
+  const dim3 grid(mt * nt);
+  if (with_dbt) hipLaunchKernelGGL((gemm_stream_tn_kernel<MT, NT, D, true, HALVES>), grid, dim3(256), 0, s, GWS_GEMM_PASS(g), (const GemmSampling&)g);
+  else hipLaunchKernelGGL((gemm_stream_tn_kernel<MT, NT, D, false, HALVES>), grid, dim3(256), 0, s, GWS_GEMM_PASS(g), (const GemmSampling&)g);
 }
 
 // The piece with the smallest estimate in us: a launch, and per round of workgroups (one per compute unit: the rings fill its

@@ -82,19 +82,81 @@ int launch_noise_packed(uint32_t* out, uint32_t rows, uint32_t ngrp, uint32_t ro
                         uint64_t seed, uint64_t step, hipStream_t stream);
 
 // GEMM launchers (gws_linear.hip)
-struct GemmArgs {
-  const uint16_t* x;   // [M x K], ldx
-  const uint16_t* w;   // [K x N] or [N x K], ldw
-  uint16_t* y;         // [M x N], ldy
-  uint32_t M, N, K;
-  uint32_t ldx, ldw, ldy;
-  // sampling (fused variant only)
+// What only the kernels that sample or reduce Eq. 4 need.
+struct GemmSampling {
   const float* bt;
   float* scale;        // may be NULL
   uint16_t* w_hat;     // may be NULL
   uint32_t row0, cg0, seed_lo, seed_hi, step_lo, step_hi;
   float* dbt;          // weight-gradient GEMM only: dL/db_t per block (with scale as input)
 };
+struct GemmArgs : GemmSampling {
+  const uint16_t* x;   // [M x K], ldx
+  const uint16_t* w;   // [K x N] or [N x K], ldw
+  uint16_t* y;         // [M x N], ldy
+  uint32_t M, N, K;
+  uint32_t ldx, ldw, ldy;
+  uint32_t inv_band, inv_last;   // of the kernel's tile grid (TileGrid), for its numbering of the tiles
+};
+// The kernels take these one by one: the first sixteen scalar registers' worth of plain arguments is in registers when a
+// wavefront starts (the build asks for it), where a structure is fetched from memory first.  With the reciprocals of TileGrid
+// in the place of four divisions: 1 x 768 -> 768 2.85 -> 2.44 us, 4 x 5632 -> 2048 (both [N x K]) 6.35 -> 5.9.
+#define GWS_GEMM_PARAMS                                                                                                        \
+  const uint16_t *px, const uint16_t *pw, uint16_t *py, const uint32_t pM, const uint32_t pN, const uint32_t pK, const uint32_t pldx, \
+      const uint32_t pldw, const uint32_t pldy, const uint32_t pinv_band, const uint32_t pinv_last
+#define GWS_GEMM_GATHER(sampling) \
+  GemmArgs { sampling, px, pw, py, pM, pN, pK, pldx, pldw, pldy, pinv_band, pinv_last }
+#define GWS_GEMM_PASS(g) (g).x, (g).w, (g).y, (g).M, (g).N, (g).K, (g).ldx, (g).ldw, (g).ldy, (g).inv_band, (g).inv_last
+
+// n / d by the host's reciprocal min(floor(2^32 / d), 2^32 - 1): the estimate is at most one too small for any 32-bit n.
+inline uint32_t reciprocal(uint32_t d) {
+  const uint64_t inv = ((uint64_t)1 << 32) / d;
+  return inv > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)inv;
+}
+__host__ __device__ __forceinline__ uint32_t divide(uint32_t n, uint32_t d, uint32_t inv) {
+  const uint32_t q = (uint32_t)(((uint64_t)n * inv) >> 32);
+  return q + (n - q * d >= d ? 1u : 0u);
+}
+// A grid of mt x nt tiles of Y in bands of eight tile rows, the last band of mt % 8 where that is not 0: what its numbering
+// divides by is 8 nt, the tiles of a band, and the last band's rows.
+struct TileGrid {
+  uint32_t mt, nt, inv_band, inv_last;
+};
+inline void set_tile_grid(GemmArgs& g, uint32_t mt, uint32_t nt) {
+  g.inv_band = reciprocal(8 * nt);
+  g.inv_last = reciprocal(mt % 8 ? mt % 8 : 8);
+}
+// Tile L of the order that walks a band's rows down before it moves one tile right.
+__host__ __device__ __forceinline__ void tile_in_bands(const TileGrid& t, uint32_t L, uint32_t& tile_m, uint32_t& tile_n) {
+  const uint32_t band = divide(L, 8 * t.nt, t.inv_band), r = L - band * 8 * t.nt;
+  if (band * 8 + 8 <= t.mt) {
+    tile_n = r >> 3;
+    tile_m = band * 8 + (r & 7);
+  } else {
+    tile_n = divide(r, t.mt & 7, t.inv_last);
+    tile_m = band * 8 + r - tile_n * (t.mt & 7);
+  }
+}
+// XCD-aware tile numbering: launch-order number L -> (tile_m, tile_n).  Workgroups are dealt round-robin to the 8 XCDs, each
+// with its own L2; XCD x gets a contiguous range of that order, so that the 32 workgroups running together on an XCD form an
+// 8 x 4 patch sharing 8 + 4 panels.
+__host__ __device__ __forceinline__ void tile_of(const TileGrid& t, uint32_t L, uint32_t& tile_m, uint32_t& tile_n) {
+  const uint32_t total = t.mt * t.nt, per = total / 8, rem = total % 8, x = L % 8, j = L / 8;
+  tile_in_bands(t, x * per + (x < rem ? x : rem) + j, tile_m, tile_n);   // XCD x owns `per` tiles (+1 for the first `rem`)
+}
+// The same for small tiles: tiles that share a piece of the weight (the rows of a band), and with narrow [K x N] tiles the two
+// that share its cache lines, go to one XCD as a group, and the groups round-robin over the XCDs (a contiguous range per XCD
+// would put the columns of one XCD on a few of the L2's channels when a row of the weight is a multiple of 4 KiB).
+__host__ __device__ __forceinline__ void tile_of_groups(const TileGrid& t, bool pairs, uint32_t b, uint32_t& tile_m, uint32_t& tile_n) {
+  const uint32_t p = pairs ? 1 : 0;   // groups of G = min(mt, 8) << p tiles
+  const uint32_t whole = t.mt < 8 ? (t.nt >> (3 + p) << (3 + p)) * t.mt : t.mt * t.nt >> (6 + p) << (6 + p);   // of rounds of 8 G
+  uint32_t L = b;
+  if (b < whole) {
+    const uint32_t j = b >> 3, q = t.mt < 8 ? divide(j >> p, t.mt, t.inv_last) : j >> (3 + p), G = (t.mt < 8 ? t.mt : 8) << p;
+    L = (q * 8 + (b & 7)) * G + j - q * G;
+  }
+  tile_in_bands(t, L, tile_m, tile_n);
+}
 // fused: 0 = plain GEMM on g.w; kFusedInOperand = sampling in the weight operand load of every tile
 constexpr int kFusedInOperand = 2;
 int launch_gemm(const GemmArgs& g, int w_is_nk, int fused, int fmt, hipStream_t stream);
