@@ -437,14 +437,15 @@ static void launch_fwd(const ARGS& a, uint32_t n_wg, int variant, hipStream_t st
   else hipLaunchKernelGGL((sample_fwd_kernel<FMT, MX, STREAM, BASIS, false, ARGS>), dim3(n_wg), dim3(kThreads), 0, stream, a);
 }
 
-// One small weight (the call inside every sampled linear): five kilobytes of arguments and two dependent reads of them are
-// a fifth of such a kernel's time, 768 x 768 4.5 -> 3.6 us.
+// One weight of up to 32 MB (the call inside every sampled linear): five kilobytes of arguments and two dependent reads of them
+// are a fifth of a small kernel's time, 768 x 768 4.5 -> 3.6 us, and show in larger ones: backward of 2048 x 8192 7.4 -> 6.6,
+// Box-Muller 16.5 -> 15.7 and 10.8 -> 10.2, FP6 codes of 2048 x 5632 8.8 -> 7.7.  Beyond, the order of the tiles (locate) counts more.
 static OneArgs one_of(const LaunchArgs& a) { return OneArgs{a.t[0], a.step_lo, a.step_hi, a.tiles_per_wg, a.tiles_per_wg_x}; }
 
 template <int FMT, bool MX, int BASIS>
 static void launch_fwd_stream(const LaunchArgs& a, uint32_t n_wg, int mode, int variant, hipStream_t stream) {
-  if (BASIS == kBasisBits && !MX && mode == kKeep && a.n == 1) launch_fwd<FMT, false, kKeep, kBasisBits>(one_of(a), n_wg, variant, stream);
-  else if (BASIS == kBasisBits && !MX && mode == kStreamReads && a.n == 1) launch_fwd<FMT, false, kStreamReads, kBasisBits>(one_of(a), n_wg, variant, stream);
+  if (mode == kKeep && a.n == 1) launch_fwd<FMT, MX, kKeep, BASIS>(one_of(a), n_wg, variant, stream);
+  else if (mode == kStreamReads && a.n == 1) launch_fwd<FMT, MX, kStreamReads, BASIS>(one_of(a), n_wg, variant, stream);
   else if (mode == kKeep) launch_fwd<FMT, MX, kKeep, BASIS>(a, n_wg, variant, stream);
   else if (mode == kStreamReads) launch_fwd<FMT, MX, kStreamReads, BASIS>(a, n_wg, variant, stream);
   else launch_fwd<FMT, MX, kStreamAll, BASIS>(a, n_wg, variant, stream);
@@ -483,7 +484,8 @@ static void launch_bwd(const ARGS& a, uint32_t n_wg, int variant, hipStream_t st
 
 template <int BASIS>
 static void launch_bwd_stream(const LaunchArgs& a, uint32_t n_wg, int mode, int variant, hipStream_t stream) {
-  if (BASIS == kBasisBits && mode == kKeep && a.n == 1) launch_bwd<kKeep, kBasisBits>(one_of(a), n_wg, variant, stream);
+  if (mode == kKeep && a.n == 1) launch_bwd<kKeep, BASIS>(one_of(a), n_wg, variant, stream);
+  else if (mode == kStreamReads && a.n == 1) launch_bwd<kStreamReads, BASIS>(one_of(a), n_wg, variant, stream);
   else if (mode == kKeep) launch_bwd<kKeep, BASIS>(a, n_wg, variant, stream);
   else if (mode == kStreamReads) launch_bwd<kStreamReads, BASIS>(a, n_wg, variant, stream);
   else launch_bwd<kStreamAll, BASIS>(a, n_wg, variant, stream);
