@@ -496,35 +496,42 @@ __device__ __forceinline__ void box_muller_pair(uint32_t word, float& r_lo, floa
 // clamped to [0, 1] that is fractional within 2^-15 of the threshold (in units of z^2 / (2 ln 2)); a group with such an
 // element in any lane (about one group in a hundred) takes the exact sequence above for all of its pairs.  The hardware
 // functions need 2.5 % of that half window, 4.1e-5 of the words lie within it, and over all 2^32 words both ways give the
-// same bits (gws_box_muller_check counts all three).  The sign is the quadrant's: bits of the word.  About 24 vector
-// instructions a pair where the exact sequence takes 90: both passes over a 2048 x 8192 weight 43.8 -> 29.0 us (the bytes
-// take 17).
-__device__ __forceinline__ void box_muller_pair_fast(uint32_t word, float& r_lo, float& r_hi, float& near) {
+// same bits (gws_box_muller_check counts all three).  The sign is the quadrant's: the cosine's own, and a bit of the word.
+// Bound by the vector ALU: 18 instructions a pair where the exact sequence takes 90, of what issues in two cycles (constants in
+// vector registers, no permutes, no left shift, fractions collected as bits): backward of 2048 x 8192 10.3 -> 9.6 us, of 4096 x
+// 8192 17.6 -> 16.5 (forward, which its bytes bound, 15.7 -> 15.5 and 24.9 -> 24.3).
+// near: its low 21 bits are not all clear if an element lies within a window.
+__device__ __forceinline__ void box_muller_pair_fast(uint32_t word, float& r_lo, float& r_hi, uint32_t& near) {
   constexpr float W = 16384.0f, T1 = 0.72134752f, T9 = 6.49212768f;   // 1 / window, 1 / (2 ln 2), 9 / (2 ln 2)
-  // 2^23 + half word: the conversion to fp32 is a byte permute; (x - 2^23 + 0.5) / 2^16 is exact
-  const uint32_t magic = 0x4B000000u;
-  const float u1 = __fmaf_rn(__uint_as_float(__builtin_amdgcn_perm(magic, word, 0x07040100u)), 0x1p-16f, -128.0f + 0x1p-17f);
-  const float u2 = __fmaf_rn(__uint_as_float(__builtin_amdgcn_perm(magic, word, 0x07040302u)), 0x1p-16f, -128.0f + 0x1p-17f);
+  constexpr uint32_t kMinusW = 0xC6800000u;
+  // u1: 2^23 + low half, made (low half + 0.5) / 2^16 by an exact multiply-add.  u2: the high half and the half step as mantissa bits
+  // of a number in [1, 2), one revolution more.
+  const float u1 = __fmaf_rn(__uint_as_float(__builtin_amdgcn_bitop3_b32(word, in_vgpr(0xFFFFu), in_vgpr(0x4B000000u), 0xEA)), 0x1p-16f, -128.0f + 0x1p-17f);
+  const float u2 = __uint_as_float(__builtin_amdgcn_bitop3_b32(word >> 9, in_vgpr(0x007FFF80u), in_vgpr(0x3F800040u), 0xEA));
   const float l2 = __builtin_amdgcn_logf(u1), c = __builtin_amdgcn_cosf(u2);
   const float qc = __fmul_rn(l2, __fmul_rn(c, c)), qs = __fsub_rn(l2, qc);   // -z^2 / (2 ln 2) of the two elements
+  const float w = __uint_as_float(in_vgpr(kMinusW));
   auto magnitude = [&](float q) {
-    const float m1 = __builtin_amdgcn_fmed3f(__fmaf_rn(q, -W, 0.5f - T1 * W), 0.0f, 1.0f);
-    const float m9 = __builtin_amdgcn_fmed3f(__fmaf_rn(q, -W, 0.5f - T9 * W), 0.0f, 1.0f);
+    const float m1 = __builtin_amdgcn_fmed3f(__fmaf_rn(q, w, 0.5f - T1 * W), 0.0f, 1.0f);
+    const float m9 = __builtin_amdgcn_fmed3f(__fmaf_rn(q, w, 0.5f - T9 * W), 0.0f, 1.0f);
     return __fadd_rn(m1, m9);
   };
   const float mc = magnitude(qc), ms = magnitude(qs);
-  near = fmaxf(near, fmaxf(__builtin_amdgcn_fractf(mc), __builtin_amdgcn_fractf(ms)));
-  r_lo = __uint_as_float(__builtin_amdgcn_bitop3_b32(word ^ (word << 1), 0x80000000u, __float_as_uint(mc), 0xEA));
-  r_hi = __uint_as_float(__builtin_amdgcn_bitop3_b32(word, 0x80000000u, __float_as_uint(ms), 0xEA));
+  // 4, 5 and 6 have no mantissa bits below bit 21
+  near = __builtin_amdgcn_bitop3_b32(near, __float_as_uint(__fadd_rn(mc, 4.0f)), __float_as_uint(__fadd_rn(ms, 4.0f)), 0xFE);
+  const uint32_t sign = in_vgpr(0x80000000u);
+  r_lo = __uint_as_float(__builtin_amdgcn_bitop3_b32(__float_as_uint(c), sign, __float_as_uint(mc), 0xEA));
+  r_hi = __uint_as_float(__builtin_amdgcn_bitop3_b32(word, sign, __float_as_uint(ms), 0xEA));
 }
+constexpr uint32_t kBoxMullerNear = 0x001FFFFFu;
 
 __device__ __forceinline__ void box_muller_group(const Philox4& x, float (&r)[8]) {
-  float near = 0.0f;
+  uint32_t near = 0;
   box_muller_pair_fast(x.x0, r[0], r[1], near);
   box_muller_pair_fast(x.x1, r[2], r[3], near);
   box_muller_pair_fast(x.x2, r[4], r[5], near);
   box_muller_pair_fast(x.x3, r[6], r[7], near);
-  if (__builtin_amdgcn_ballot_w64(near != 0.0f) != 0) {
+  if (__builtin_amdgcn_ballot_w64((near & kBoxMullerNear) != 0) != 0) {
     box_muller_pair(x.x0, r[0], r[1]);
     box_muller_pair(x.x1, r[2], r[3]);
     box_muller_pair(x.x2, r[4], r[5]);

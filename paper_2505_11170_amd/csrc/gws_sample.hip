@@ -123,8 +123,9 @@ __device__ __forceinline__ void walk_tiles(const ARGS& a, const TileDesc& d, uin
 // The registers that this leaves (128) let the compiler interleave a tile's groups: MX-FP6 of 352 M parameters 195 -> 182 us.
 #define GWS_FOUR_WAVES __attribute__((amdgpu_waves_per_eu(4, 4)))
 // Weights of any shape: up to eight (EIGHT) while what the pass reads and writes fits in the last-level cache, wherever it only reads
-// and where much of the tiles lies outside the weights (run_batched).  Backward pass of the uniform basis on whole tiles: up to eight too, as that basis has more left to do when the
-// tile has come (34.7 M parameters 11.3 us, 12.0 with four).
+// and where much of the tiles lies outside the weights (run_batched).  Backward pass of the comparison bases on whole tiles: up to
+// eight too, as they have more left to do when the tile has come (uniform, 34.7 M parameters 11.3 us, 12.0 with four; Box-Muller, 33.5 M
+// 16.5, 16.9).
 #define GWS_WAVES(eight) __attribute__((amdgpu_waves_per_eu(4, (eight) ? 8 : 4)))
 
 // MX: write element codes and E8M0 block scales instead of the BF16 container.
@@ -293,7 +294,7 @@ __global__ __launch_bounds__(kThreads) GWS_FOUR_WAVES void sample_fwd_full_kerne
 // tile.  The next tile's loads are issued after the current tile's arithmetic and complete under the next tile's
 // Philox rounds.
 template <int STREAM, int BASIS, class ARGS>
-__global__ __launch_bounds__(kThreads) GWS_WAVES(BASIS == kBasisUniform) void sample_bwd_full_kernel(const ARGS a) {
+__global__ __launch_bounds__(kThreads) GWS_WAVES(BASIS != kBasisBits) void sample_bwd_full_kernel(const ARGS a) {
   uint32_t byg, bxg;
   const TileDesc d = locate(a, byg, bxg);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -407,10 +408,11 @@ __global__ __launch_bounds__(256) void box_muller_check_kernel(uint64_t first, u
   uint32_t differ = 0, exact = 0, worst = 0;
   for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (uint64_t)gridDim.x * 256) {
     const uint32_t word = (uint32_t)(first + i);
-    float r[2], e[2], near = 0.0f;
+    float r[2], e[2];
+    uint32_t near = 0;
     box_muller_pair_fast(word, r[0], r[1], near);
     box_muller_pair(word, e[0], e[1]);
-    if (near == 0.0f) {
+    if ((near & kBoxMullerNear) == 0) {
       differ += __float_as_uint(r[0]) != __float_as_uint(e[0]) || __float_as_uint(r[1]) != __float_as_uint(e[1]) ? 1 : 0;
       continue;
     }
