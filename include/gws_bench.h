@@ -71,7 +71,8 @@ int gws_ride_plan_layout(int64_t M, int64_t K, int64_t N, int w_is_nk, const gws
 #define GWS_GEMM_ROWS_SAMPLE 8      /* 256 x 256 or 128 x 128 tiles, the weight sampled in the operand load */
 #define GWS_GEMM_ANY_SHAPE_SAMPLE 9 /* the same on the tiles of 6 */
 int gws_gemm_form(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled);
-/* gws_gemm_tile: of the same call, the part of Y that a workgroup of that kernel makes, rows << 16 | columns.                */
+/* gws_gemm_tile: of the same call, the part of Y that a workgroup of that kernel makes, rows << 16 | columns (of the stream kernel in
+ * whole MFMA tiles of 16 x 16, also where it keeps eight rows or eight columns of one).                                           */
 int gws_gemm_tile(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled);
 
 /* gws_linear_bwd_w_form: of gws_linear_bwd_w_ws for this weight (rows, cols) over M tokens with that much workspace, X, dY and

@@ -18,11 +18,13 @@ namespace gws {
 // form 130-180 B/ns (L2-resident operands, one workgroup per compute unit).  Layouts as in gws_gemm256_core.h: rows of 128
 // bytes with chunk c of row r in slot c ^ ((r / 2) % 8); a [K x N] weight as 64 k-rows of 32 NT bytes, read with the
 // transposing LDS load, chunk c of row k in slot c ^ swizzle(k).
-template <int MT, int NT, int P, int D, bool W_NK>
+// BM x BN is the workgroup's tile: 16 MT x 16 NT, or eight rows, eight columns where one MFMA tile has that many of use (the others
+// are computed on repeated ones and not stored).
+template <int MT, int NT, int P, int D, bool W_NK, int BM = 16 * MT, int BN = 16 * NT>
 __global__ __launch_bounds__(64 * P) void gemm_stream_kernel(GWS_GEMM_PARAMS) {
   using namespace stream;
   const GemmArgs g = GWS_GEMM_GATHER({});
-  constexpr int BM = 16 * MT, BN = 16 * NT;
+  static_assert((BM == 16 * MT || (BM == 8 && MT == 1)) && (BN == 16 * NT || (BN == 8 && NT == 1 && W_NK)), "whole MFMA tiles or half a one");
   constexpr int XS = BM * 64, WS = BN * 64, STG = XS + WS;          // elements of a stage
   constexpr int QX = BM / 8, QW = BN / 8, LOADS = QX + QW;          // load instructions of a unit
   static_assert(LOADS * (D - 1) <= 63, "the wait for a unit counts the loads behind it");
@@ -82,6 +84,7 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_kernel(GWS_GEMM_PARAMS) {
   for (int d = 0; d < D; ++d)
     if ((uint32_t)d < n) load(u0 + d, d);
   uint32_t slot = 0;
+  const uint32_t lx = BM == 8 ? li & 7 : li, lw = BN == 8 ? li & 7 : li;
   for (uint32_t i = 0; i < n; ++i) {
     if (i + D <= n) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS * (D - 1)) : "memory");   // the unit has landed
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -91,11 +94,11 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_kernel(GWS_GEMM_PARAMS) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
-      for (int r = 0; r < MT; ++r) fx[h][r].u = *(const u32x4*)(xs + (16 * r + li) * 64 + (((4 * h + grp) ^ ((li >> 1) & 7)) * 8));
+      for (int r = 0; r < MT; ++r) fx[h][r].u = *(const u32x4*)(xs + (16 * r + lx) * 64 + (((4 * h + grp) ^ ((lx >> 1) & 7)) * 8));
 #pragma unroll
       for (int j = 0; j < NT; ++j) {
         if (W_NK) {
-          fw[h][j].u = *(const u32x4*)(wsg + (16 * j + li) * 64 + (((4 * h + grp) ^ ((li >> 1) & 7)) * 8));
+          fw[h][j].u = *(const u32x4*)(wsg + (16 * j + lw) * 64 + (((4 * h + grp) ^ ((lw >> 1) & 7)) * 8));
         } else {
           fw[h][j] = read_oc<W_NK ? 2 : NT>(wsg, h, j, li, grp);
         }
@@ -115,7 +118,7 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_kernel(GWS_GEMM_PARAMS) {
         for (int r = 0; r < MT; ++r) acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[h][j].v, fx[h][r].v, acc[r][j], 0, 0, 0);
     }
   }
-  reduce_store<MT, NT, P, MC>(acc, lds, g, m0, n0);
+  reduce_store<MT, NT, P, MC, BM, BN>(acc, lds, g, m0, n0);
 }
 
 // Eq. 3 + cast on the weight's blocks on their way into the MFMA, B (1 or 2) at a time: the wavefront's 32 columns of Y and the
@@ -510,7 +513,7 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_pair_sample_kernel(GWS_GEMM_
 //   1000 x 5632 -> 2048 NK                                 36.6    29.9      107
 // ---------------------------------------------------------------------------
 StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk) {
-  StreamPlan best = {0, 0, 0, 1e30};
+  StreamPlan best = {0, 0, 0, 0, 0, 1e30};
   if (K < 64) return best;
   const int cus = compute_units() > 0 ? compute_units() : 256;
   // bytes per ns: eight wavefronts keep twice the loads in flight that four do
@@ -522,8 +525,14 @@ StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk) {
     const uint64_t wgs = ((M + 16 * t.mt - 1) / (16 * t.mt)) * ((N + 16 * t.nt - 1) / (16 * t.nt));
     const double rounds = (double)((wgs + cus - 1) / cus);
     const double us = 1.8 + 2.7 * rounds + rounds * (double)K * 2 * 16 * (t.mt + t.nt) / t.rate * 1e-3;
-    if (wgs < 0x7FFFFFFFull && us < best.us) best = {t.mt, t.nt, t.p, us};
+    if (wgs < 0x7FFFFFFFull && us < best.us) best = {t.mt, t.nt, t.p, 16 * t.mt, 16 * t.nt, us};
   }
+  // Of one MFMA tile's rows and columns those that are wanted.  Up to eight rows of X are one load instruction a unit instead of
+  // two (4 x 5632 -> 2048 6.09 -> 5.64 us).  Eight columns of an [N x K] weight make twice the workgroups: faster where they still
+  // fit one a compute unit and K is long enough for the bytes to count (16 x 5632 -> 2048 6.48 -> 5.95, 4 x 4096 -> 512 3.95 -> 3.89,
+  // 16 x 3072 -> 768 4.32 -> 3.91; short: 16 x 768 -> 768 2.67 -> 2.79, 4 x 768 -> 3072 3.06 -> 3.30).
+  if (best.mt == 1 && M <= 8) best.bm = 8;
+  if (best.nt == 1 && N / 8 <= (uint64_t)cus && K >= 2048) best.bn = 8;
   return best;
 }
 
@@ -531,18 +540,21 @@ bool stream_applicable(const GemmArgs& g) {
   return g.K >= 64 && g.K % 32 == 0 && g.N % 32 == 0 && g.M > 0 && g.N > 0 && g.ldx < stream::kMaxLd && g.ldw < stream::kMaxLd;
 }
 
-template <int MT, int NT, int P, int D>
+template <int MT, int NT, int P, int D, int BM = 16 * MT, int BN = 16 * NT>
 static void launch_plain(GemmArgs g, int w_is_nk, hipStream_t s) {
-  const dim3 grid(stream::tile_grid(g, 16 * MT, 16 * NT));
+  const dim3 grid(stream::tile_grid(g, BM, BN));
   if (w_is_nk) {
-    hipLaunchKernelGGL((gemm_stream_kernel<MT, NT, P, D, true>), grid, dim3(64 * P), 0, s, GWS_GEMM_PASS(g));
+    hipLaunchKernelGGL((gemm_stream_kernel<MT, NT, P, D, true, BM, BN>), grid, dim3(64 * P), 0, s, GWS_GEMM_PASS(g));
   } else {
-    if constexpr (NT >= 2) hipLaunchKernelGGL((gemm_stream_kernel<MT, NT, P, D, false>), grid, dim3(64 * P), 0, s, GWS_GEMM_PASS(g));
+    if constexpr (NT >= 2) hipLaunchKernelGGL((gemm_stream_kernel<MT, NT, P, D, false, BM, BN>), grid, dim3(64 * P), 0, s, GWS_GEMM_PASS(g));
   }
 }
 
 int launch_gemm_stream(const GemmArgs& g, int w_is_nk, const StreamPlan& p, hipStream_t s) {
-  if (p.mt == 1 && p.nt == 1) launch_plain<1, 1, 8, 4>(g, w_is_nk, s);
+  // up to 16 rows: two units on their way a wavefront (four, which take all of the LDS: 4 x 5632 -> 2048 [N x K] 6.1 us, two 5.7)
+  if (p.bn == 8) p.bm == 8 ? launch_plain<1, 1, 8, 2, 8, 8>(g, w_is_nk, s) : launch_plain<1, 1, 8, 2, 16, 8>(g, w_is_nk, s);
+  else if (p.bn == 16) p.bm == 8 ? launch_plain<1, 1, 8, 2, 8, 16>(g, w_is_nk, s) : launch_plain<1, 1, 8, 2>(g, w_is_nk, s);
+  else if (p.bm == 8) launch_plain<1, 2, 8, 2, 8, 32>(g, w_is_nk, s);
   else if (p.mt == 1) launch_plain<1, 2, 8, 2>(g, w_is_nk, s);
   else if (p.mt == 2 && p.nt == 2) launch_plain<2, 2, 8, 2>(g, w_is_nk, s);
   else if (p.mt == 2) launch_plain<2, 4, 4, 3>(g, w_is_nk, s);

@@ -94,14 +94,15 @@ __device__ __forceinline__ void sum_parts(const f32x4 (&acc)[MT][NT], char* lds,
   }
 }
 
-template <int MT, int NT, int P, int MC>
+// BM x BN: the part of the 16 MT x 16 NT that is stored.
+template <int MT, int NT, int P, int MC, int BM = 16 * MT, int BN = 16 * NT>
 __device__ __forceinline__ void reduce_store(const f32x4 (&acc)[MT][NT], char* lds, const GemmArgs& g, uint32_t m0,
                                              uint32_t n0) {
 #pragma unroll
   for (int i0 = 0; i0 < MT; i0 += MC)
     sum_parts<MT, NT, P, MC>(acc, lds, i0, [&](uint32_t r, uint32_t c, const f32x4& s) {
       const uint32_t row = m0 + 16 * i0 + r, col = n0 + 4 * c;
-      if (row < g.M && col < g.N)
+      if (row < g.M && col < g.N && (BM == 16 * MT || r < BM) && (BN == 16 * NT || 4 * c < BN))
         *(u32x2*)(g.y + (size_t)row * g.ldy + col) = u32x2{pack_bf16_rne(s[0], s[1]), pack_bf16_rne(s[2], s[3])};
     });
 }

@@ -160,10 +160,10 @@ __host__ __device__ __forceinline__ void tile_of_groups(const TileGrid& t, bool 
 // fused: 0 = plain GEMM on g.w; kFusedInOperand = sampling in the weight operand load of every tile
 constexpr int kFusedInOperand = 2;
 int launch_gemm(const GemmArgs& g, int w_is_nk, int fused, int fmt, hipStream_t stream);
-// few rows of X or few tiles (gws_gemm_stream.hip): the tile in units of 16 rows and 16 columns, the parts of K and the
-// estimated time; p == 0: the shape is not one for it
+// few rows of X or few tiles (gws_gemm_stream.hip): the tile in units of 16 rows and 16 columns, the parts of K, the rows and
+// columns of it that a workgroup owns and the estimated time; p == 0: the shape is not one for it
 struct StreamPlan {
-  int mt, nt, p;
+  int mt, nt, p, bm, bn;
   double us;
 };
 StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk);

@@ -391,6 +391,17 @@ def test_gemm_that_splits_k(M, K, N, w_is_nk):
     run_case(M, K, N, w_is_nk, gws.FMT_FP8_E4M3, seed_id=idx, step=4, rows_sel=rows_sel)   # the library's choice between the two forms
 
 
+# Up to 16 rows the stream kernel keeps eight or sixteen rows and, of [N x K] weights, eight, sixteen or 32 columns of its MFMA tiles: each
+# of them, at the edges of the choice (8 and 9 rows, K of 2048, as many eight-column tiles as compute units) and at the smallest.  The
+# sampled form, which has one tile for all of these, gives the same bits (run_case).
+@pytest.mark.parametrize("w_is_nk", [False, True])
+@pytest.mark.parametrize("M,K,N", [(1, 64, 32), (7, 2016, 64), (8, 2048, 2048), (8, 2080, 2080), (9, 2048, 2048), (9, 2016, 96), (16, 2080, 2048), (8, 320, 4128)])
+def test_gemm_of_half_an_mfma_tile(M, K, N, w_is_nk):
+    assert gws.gws_gemm_form(M, K, N, w_is_nk, ldx=K + 8) == gws.GEMM_STREAM
+    run_case(M, K, N, w_is_nk, gws.FMT_FP8_E4M3, seed_id=61, ldx_pad=8, ldy_pad=8, mode=gws.LINEAR_IN_OPERAND,
+             rows_sel=None if M * K * N < 2e7 else np.array(sorted({0, M // 2, M - 1})))
+
+
 def test_riding_under_a_gemm_of_many_k_steps():
     # 182 tiles of 256 x 256: the large tile is the faster one and leaves 74 compute units idle
     assert gws.gws_gemm_form(6656, 1024, 1792) == gws.GEMM_LARGE
