@@ -35,8 +35,17 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_kernel(GWS_GEMM_PARAMS) {
   const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint16_t* ring = (uint16_t*)lds + wave * (D * STG);
+  // A contiguous part of the tiles per XCD, eight tile rows high, reads least into its L2, and what the L2s read comes in at 8 TB/s in
+  // all: 1000 x 2304 -> 768 with groups of one tile column dealt round-robin 40 MB, 11.0 us, like this 25 MB, 10.0 ([K x N] 11.6,
+  // 10.6); 2800 x 5184 -> 608 42.6, 30.7; 300 x 768 -> 768 4.9, 4.4; 68 sizes 0.97.  Few tiles or columns of them stay dealt out
+  // ([K x N] 822 x 2816 -> 64 7.2, as a part 7.8, 372 x 4320 -> 128 11.3, 12.1; [N x K] 601 x 5568 -> 128 10.6, 10.3), and few rows of X on
+  // a [K x N] weight (16 x 2048 -> 5632 7.4, 7.7).
+  const TileGrid t = {(g.M + BM - 1) / BM, (g.N + BN - 1) / BN, g.inv_band, g.inv_last};
   uint32_t m0, n0;
-  tile_origin(g, BM, BN, !W_NK && NT == 2, m0, n0);
+  if (t.nt >= (W_NK ? 4 : 6) && t.mt * t.nt >= 32 && (W_NK || t.mt > 1)) tile_of(t, blockIdx.x, m0, n0);
+  else tile_of_groups(t, !W_NK && NT == 2, blockIdx.x, m0, n0);
+  m0 *= BM;
+  n0 *= BN;
   uint32_t u0, u1;
   unit_range(g.K, wave, P, u0, u1);
 

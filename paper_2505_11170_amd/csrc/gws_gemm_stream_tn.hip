@@ -69,12 +69,13 @@ __global__ __launch_bounds__(256, 1) void gemm_stream_tn_kernel(GWS_GEMM_PARAMS,
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   uint16_t* ring = (uint16_t*)lds + wave * (D * STG);
   uint32_t m0, n0, u0, u1;
-  // Eight pieces along the longer side of C that share the shorter side's operand go to one XCD, which of the shorter operand then
-  // reads its own part.  Along the rows whatever the shape, every XCD read all of the longer operand of a weight of few columns:
-  // 1856 tokens x 1792 x 256 in pieces of 64 x 32 11.9 us, like this 10.1; 7680 x 4096 x 256 in 64 x 64 47.2, 30.0.
+  // Each XCD takes a contiguous part of the pieces, in bands of eight along the shorter side of C: neighbouring pieces share lines and an
+  // operand.  Along the rows whatever the shape, every XCD read all of the longer operand of a weight of few columns (1856 tokens
+  // x 1792 x 256 in pieces of 64 x 32 11.9 us, like this 10.1; 7680 x 4096 x 256 in 64 x 64 47.2, 30.0); with groups of eight dealt
+  // round-robin 2048 x 1024 x 1024 12.9, like this 11.0, 3072 x 768 x 256 13.8, 11.9, 8192 x 2048 x 2048 67.7, 66.0; 50 sizes 0.97.
   const uint32_t mt = (g.M + BM - 1) / BM, nt = (g.N + BN - 1) / BN;
-  if (g.M > g.N) tile_of_groups(TileGrid{nt, mt, g.inv_band, g.inv_last}, false, blockIdx.x, n0, m0);
-  else tile_of_groups(TileGrid{mt, nt, g.inv_band, g.inv_last}, false, blockIdx.x, m0, n0);
+  if (g.M > g.N) tile_of(TileGrid{nt, mt, g.inv_band, g.inv_last}, blockIdx.x, n0, m0);
+  else tile_of(TileGrid{mt, nt, g.inv_band, g.inv_last}, blockIdx.x, m0, n0);
   m0 *= BM;
   n0 *= BN;
   unit_range(g.K, wave, P, u0, u1);
