@@ -18,9 +18,24 @@ namespace gws {
 // form 130-180 B/ns (L2-resident operands, one workgroup per compute unit).  Layouts as in gws_gemm256_core.h: rows of 128
 // bytes with chunk c of row r in slot c ^ ((r / 2) % 8); a [K x N] weight as 64 k-rows of 32 NT bytes, read with the
 // transposing LDS load, chunk c of row k in slot c ^ swizzle(k).
+// A wavefront's share of a tile's columns of the weight, fetched into the XCD's L2 and dropped: one load instruction touches 64 pieces
+// of lines, every part-th unit of 64 k.  A compute unit gets about 60 B/ns from beyond its L2, a line every 2 ns whether 64 bytes of it are
+// wanted or 128, so few tiles on few compute units wait for the weight while the others idle; what an idle one has fetched comes at 150.
+template <int BN, bool W_NK>
+__device__ __forceinline__ void warm_l2(const GemmArgs& g, uint32_t n0, uint32_t u0, uint32_t u1, uint32_t part, uint32_t parts) {
+  const uint32_t lane = threadIdx.x & 63;
+  constexpr uint32_t UNITS = W_NK ? 64 / BN : 1;   // of an instruction
+  for (uint32_t u = u0 + part * UNITS; u < u1; u += parts * UNITS) {
+    const uint32_t k = stream::umin(64 * (u + (W_NK ? lane / BN : 0)), g.K - 64);
+    const uint32_t v = *(const uint32_t*)(W_NK ? g.w + (size_t)stream::umin(n0 + lane % BN, g.N - 1) * g.ldw + k : g.w + (size_t)(k + lane) * g.ldw + n0);
+    asm volatile("" ::"v"(v));
+  }
+}
+
+// WARM: the grid has more workgroups a tile (blockIdx.y > 0) that only warm_l2; they share nothing with the others.
 // BM x BN is the workgroup's tile: 16 MT x 16 NT, or eight rows, eight columns where one MFMA tile has that many of use (the others
 // are computed on repeated ones and not stored).
-template <int MT, int NT, int P, int D, bool W_NK, int BM = 16 * MT, int BN = 16 * NT>
+template <int MT, int NT, int P, int D, bool W_NK, int BM = 16 * MT, int BN = 16 * NT, bool WARM = false>
 __global__ __launch_bounds__(64 * P) void gemm_stream_kernel(GWS_GEMM_PARAMS) {
   using namespace stream;
   const GemmArgs g = GWS_GEMM_GATHER({});
@@ -39,15 +54,19 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_kernel(GWS_GEMM_PARAMS) {
   // all: 1000 x 2304 -> 768 with groups of one tile column dealt round-robin 40 MB, 11.0 us, like this 25 MB, 10.0 ([K x N] 11.6,
   // 10.6); 2800 x 5184 -> 608 42.6, 30.7; 300 x 768 -> 768 4.9, 4.4; 68 sizes 0.97.  Few tiles or columns of them stay dealt out
   // ([K x N] 822 x 2816 -> 64 7.2, as a part 7.8, 372 x 4320 -> 128 11.3, 12.1; [N x K] 601 x 5568 -> 128 10.6, 10.3), and few rows of X on
-  // a [K x N] weight (16 x 2048 -> 5632 7.4, 7.7).
+  // a wide [K x N] weight (16 x 2048 -> 5632 7.4, 7.7; 64 x 768 -> 3072 4.1, 4.6; up to eight tile rows an XCD reads all of X in either order).
   const TileGrid t = {(g.M + BM - 1) / BM, (g.N + BN - 1) / BN, g.inv_band, g.inv_last};
   uint32_t m0, n0;
-  if (t.nt >= (W_NK ? 4 : 6) && t.mt * t.nt >= 32 && (W_NK || t.mt > 1)) tile_of(t, blockIdx.x, m0, n0);
+  if (t.nt >= (W_NK ? 4 : 6) && t.mt * t.nt >= 32 && (W_NK || t.mt > 8 || (t.mt > 1 && g.N <= 2304))) tile_of(t, blockIdx.x, m0, n0);
   else tile_of_groups(t, !W_NK && NT == 2, blockIdx.x, m0, n0);
   m0 *= BM;
   n0 *= BN;
   uint32_t u0, u1;
   unit_range(g.K, wave, P, u0, u1);
+  if (WARM && (blockIdx.y > 0 || blockIdx.x >= t.mt * t.nt)) {   // uniform; a row of the grid is whole rounds of the XCDs
+    if (blockIdx.x < t.mt * t.nt) warm_l2<BN, W_NK>(g, n0, u0, u1, blockIdx.y - 1, gridDim.y - 1);
+    return;
+  }
 
   // lane offsets in bytes; rows and columns past the edge are read from the last ones and not stored
   uint32_t xo[QX], wo[W_NK ? QW : 1];
@@ -522,7 +541,7 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_pair_sample_kernel(GWS_GEMM_
 //   1000 x 5632 -> 2048 NK                                 36.6    29.9      107
 // ---------------------------------------------------------------------------
 StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk) {
-  StreamPlan best = {0, 0, 0, 0, 0, 1e30};
+  StreamPlan best = {0, 0, 0, 0, 0, 0, 1e30};
   if (K < 64) return best;
   const int cus = compute_units() > 0 ? compute_units() : 256;
   // bytes per ns: eight wavefronts keep twice the loads in flight that four do
@@ -534,7 +553,7 @@ StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk) {
     const uint64_t wgs = ((M + 16 * t.mt - 1) / (16 * t.mt)) * ((N + 16 * t.nt - 1) / (16 * t.nt));
     const double rounds = (double)((wgs + cus - 1) / cus);
     const double us = 1.8 + 2.7 * rounds + rounds * (double)K * 2 * 16 * (t.mt + t.nt) / t.rate * 1e-3;
-    if (wgs < 0x7FFFFFFFull && us < best.us) best = {t.mt, t.nt, t.p, 16 * t.mt, 16 * t.nt, us};
+    if (wgs < 0x7FFFFFFFull && us < best.us) best = {t.mt, t.nt, t.p, 16 * t.mt, 16 * t.nt, 0, us};
   }
   // Of one MFMA tile's rows and columns those that are wanted.  Up to eight rows of X are one load instruction a unit instead of
   // two (4 x 5632 -> 2048 6.09 -> 5.64 us).  Eight columns of an [N x K] weight make twice the workgroups: faster where they still
@@ -542,6 +561,16 @@ StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk) {
   // 16 x 3072 -> 768 4.32 -> 3.91; short: 16 x 768 -> 768 2.67 -> 2.79, 4 x 768 -> 3072 3.06 -> 3.30).
   if (best.mt == 1 && M <= 8) best.bm = 8;
   if (best.nt == 1 && N / 8 <= (uint64_t)cus && K >= 2048) best.bn = 8;
+  // Idle compute units fetch the weight into the L2s (warm_l2), two or three workgroups a tile that all find one, of an [N x K] weight
+  // one.  [K x N], where a tile takes half of each line: 4 x 5632 -> 2048 13.5 -> 8.0 us, 8 x 4096 -> 512 8.3 -> 5.2, 16 x 5632 -> 2048 14.3 ->
+  // 9.3, 64 x 4096 -> 1024 11.0 -> 7.2; one alone gets no further ahead than the tile's own loads (7 x 2464 -> 3328 7.5 -> 6.6, but 6 x 4896
+  // -> 3936 11.4 -> 13.0).  [N x K], 32 columns a tile: 32 x 5632 -> 2048 9.9 -> 9.1 (with three 10.8), 64 x 4096 -> 1024 7.1 -> 6.5.  More
+  // than the chip holds cost: 4 x 2048 -> 5632 (176 tiles) 7.1 -> 7.7.  Not where the weight is small (1 x 768 -> 768 2.93, 2.97) or X is not
+  // (2000 x 5632 -> 64 12.0, 12.4).
+  if (best.nt == 2 && (!w_is_nk || best.mt == 2) && 4 * M <= N && K >= 512 && K * N >= (uint64_t)1 << 20) {
+    const uint64_t row = ((M + best.bm - 1) / best.bm * ((N + best.bn - 1) / best.bn) + 7) / 8 * 8, spare = (uint64_t)cus / row;
+    best.warm = w_is_nk ? (spare >= 2 ? 1 : 0) : spare >= 4 ? 3 : spare == 3 ? 2 : 0;
+  }
   return best;
 }
 
@@ -549,26 +578,39 @@ bool stream_applicable(const GemmArgs& g) {
   return g.K >= 64 && g.K % 32 == 0 && g.N % 32 == 0 && g.M > 0 && g.N > 0 && g.ldx < stream::kMaxLd && g.ldw < stream::kMaxLd;
 }
 
-template <int MT, int NT, int P, int D, int BM = 16 * MT, int BN = 16 * NT>
-static void launch_plain(GemmArgs g, int w_is_nk, hipStream_t s) {
-  const dim3 grid(stream::tile_grid(g, BM, BN));
+// WARM_KN, WARM_NK: the forms that stream_plan lets warm the L2
+template <int MT, int NT, int P, int D, int BM = 16 * MT, int BN = 16 * NT, bool WARM_KN = false, bool WARM_NK = false>
+static void launch_plain(GemmArgs g, int w_is_nk, int warm, hipStream_t s) {
+  const dim3 tiles(stream::tile_grid(g, BM, BN)), grid(warm ? (tiles.x + 7) / 8 * 8 : tiles.x, 1 + warm), block(64 * P);
+  if constexpr (WARM_NK) {
+    if (w_is_nk && warm) {
+      hipLaunchKernelGGL((gemm_stream_kernel<MT, NT, P, D, true, BM, BN, true>), grid, block, 0, s, GWS_GEMM_PASS(g));
+      return;
+    }
+  }
+  if constexpr (WARM_KN) {
+    if (!w_is_nk && warm) {
+      hipLaunchKernelGGL((gemm_stream_kernel<MT, NT, P, D, false, BM, BN, true>), grid, block, 0, s, GWS_GEMM_PASS(g));
+      return;
+    }
+  }
   if (w_is_nk) {
-    hipLaunchKernelGGL((gemm_stream_kernel<MT, NT, P, D, true, BM, BN>), grid, dim3(64 * P), 0, s, GWS_GEMM_PASS(g));
-  } else {
-    if constexpr (NT >= 2) hipLaunchKernelGGL((gemm_stream_kernel<MT, NT, P, D, false, BM, BN>), grid, dim3(64 * P), 0, s, GWS_GEMM_PASS(g));
+    hipLaunchKernelGGL((gemm_stream_kernel<MT, NT, P, D, true, BM, BN>), tiles, block, 0, s, GWS_GEMM_PASS(g));
+  } else if constexpr (NT >= 2) {
+    hipLaunchKernelGGL((gemm_stream_kernel<MT, NT, P, D, false, BM, BN>), tiles, block, 0, s, GWS_GEMM_PASS(g));
   }
 }
 
 int launch_gemm_stream(const GemmArgs& g, int w_is_nk, const StreamPlan& p, hipStream_t s) {
   // up to 16 rows: two units on their way a wavefront (four, which take all of the LDS: 4 x 5632 -> 2048 [N x K] 6.1 us, two 5.7)
-  if (p.bn == 8) p.bm == 8 ? launch_plain<1, 1, 8, 2, 8, 8>(g, w_is_nk, s) : launch_plain<1, 1, 8, 2, 16, 8>(g, w_is_nk, s);
-  else if (p.bn == 16) p.bm == 8 ? launch_plain<1, 1, 8, 2, 8, 16>(g, w_is_nk, s) : launch_plain<1, 1, 8, 2>(g, w_is_nk, s);
-  else if (p.bm == 8) launch_plain<1, 2, 8, 2, 8, 32>(g, w_is_nk, s);
-  else if (p.mt == 1) launch_plain<1, 2, 8, 2>(g, w_is_nk, s);
-  else if (p.mt == 2 && p.nt == 2) launch_plain<2, 2, 8, 2>(g, w_is_nk, s);
-  else if (p.mt == 2) launch_plain<2, 4, 4, 3>(g, w_is_nk, s);
-  else if (p.mt == 4) launch_plain<4, 4, 4, 2>(g, w_is_nk, s);
-  else launch_plain<8, 4, 4, 1>(g, w_is_nk, s);
+  if (p.bn == 8) p.bm == 8 ? launch_plain<1, 1, 8, 2, 8, 8>(g, w_is_nk, 0, s) : launch_plain<1, 1, 8, 2, 16, 8>(g, w_is_nk, 0, s);
+  else if (p.bn == 16) p.bm == 8 ? launch_plain<1, 1, 8, 2, 8, 16>(g, w_is_nk, 0, s) : launch_plain<1, 1, 8, 2>(g, w_is_nk, 0, s);
+  else if (p.bm == 8) launch_plain<1, 2, 8, 2, 8, 32, true>(g, w_is_nk, p.warm, s);
+  else if (p.mt == 1) launch_plain<1, 2, 8, 2, 16, 32, true>(g, w_is_nk, p.warm, s);
+  else if (p.mt == 2 && p.nt == 2) launch_plain<2, 2, 8, 2, 32, 32, true, true>(g, w_is_nk, p.warm, s);
+  else if (p.mt == 2) launch_plain<2, 4, 4, 3>(g, w_is_nk, 0, s);
+  else if (p.mt == 4) launch_plain<4, 4, 4, 2>(g, w_is_nk, 0, s);
+  else launch_plain<8, 4, 4, 1>(g, w_is_nk, 0, s);
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
 

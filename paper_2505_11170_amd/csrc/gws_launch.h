@@ -161,9 +161,9 @@ __host__ __device__ __forceinline__ void tile_of_groups(const TileGrid& t, bool 
 constexpr int kFusedInOperand = 2;
 int launch_gemm(const GemmArgs& g, int w_is_nk, int fused, int fmt, hipStream_t stream);
 // few rows of X or few tiles (gws_gemm_stream.hip): the tile in units of 16 rows and 16 columns, the parts of K, the rows and
-// columns of it that a workgroup owns and the estimated time; p == 0: the shape is not one for it
+// columns of it that a workgroup owns, the workgroups a tile that warm the L2 and the estimated time; p == 0: the shape is not one for it
 struct StreamPlan {
-  int mt, nt, p, bm, bn;
+  int mt, nt, p, bm, bn, warm;
   double us;
 };
 StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk);

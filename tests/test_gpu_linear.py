@@ -402,6 +402,17 @@ def test_gemm_of_half_an_mfma_tile(M, K, N, w_is_nk):
              rows_sel=None if M * K * N < 2e7 else np.array(sorted({0, M // 2, M - 1})))
 
 
+# Idle compute units fetch the weight into the L2s (up to three workgroups a tile): as many tiles as half, a third, a quarter of the compute
+# units and one more, tiles that do not fill a round of the XCDs, one and two rows of tiles, half a unit at the end of K, K shorter than
+# the wavefronts' ranges are many; bit for bit the sampled form's Y, which has no such workgroups (run_case).
+@pytest.mark.parametrize("w_is_nk", [False, True])
+@pytest.mark.parametrize("M,K,N", [(3, 2080, 2048), (16, 1024, 2080), (8, 2720, 2720), (4, 608, 4096), (5, 544, 4128), (16, 2048, 512), (24, 1056, 1024),
+                                   (64, 1056, 1088), (40, 4096, 256)])
+def test_gemm_whose_weight_is_fetched_by_idle_compute_units(M, K, N, w_is_nk):
+    assert gws.gws_gemm_form(M, K, N, w_is_nk, ldx=K + 8) == gws.GEMM_STREAM
+    run_case(M, K, N, w_is_nk, gws.FMT_FP8_E4M3, seed_id=62, ldx_pad=8, ldy_pad=8, mode=gws.LINEAR_IN_OPERAND, rows_sel=np.array(sorted({0, M // 2, M - 1})))
+
+
 def test_riding_under_a_gemm_of_many_k_steps():
     # 182 tiles of 256 x 256: the large tile is the faster one and leaves 74 compute units idle
     assert gws.gws_gemm_form(6656, 1024, 1792) == gws.GEMM_LARGE
