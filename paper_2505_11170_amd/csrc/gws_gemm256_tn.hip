@@ -211,7 +211,7 @@ int launch_gemm256_tn(const GemmArgs& args, bool with_dbt, hipStream_t stream) {
   GemmArgs g = args;
   const uint64_t tiles = (uint64_t)(g.M / g256::TM) * (g.N / g256::TN);
   if (tiles >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
-  set_tile_grid(g, g.M / g256::TM, g.N / g256::TN);
+  set_tile_grid(g, g.M / g256::TM, g.N / g256::TN, patch_band(g.M / g256::TM, g.N / g256::TN, g256::TM, g256::TN));
   if (with_dbt) hipLaunchKernelGGL(gemm256_tn_kernel<true>, dim3((uint32_t)tiles), dim3(256), 0, stream, GWS_GEMM_PASS(g), (const GemmSampling&)g);
   else hipLaunchKernelGGL(gemm256_tn_kernel<false>, dim3((uint32_t)tiles), dim3(256), 0, stream, GWS_GEMM_PASS(g), (const GemmSampling&)g);
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
@@ -221,7 +221,7 @@ int launch_gemm256_tn_narrow(const GemmArgs& args, bool with_dbt, hipStream_t st
   GemmArgs g = args;
   const uint32_t mt = g.M / g256::TM, nt = (g.N + g256::kNarrow - 1) / g256::kNarrow;
   if ((uint64_t)mt * nt >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
-  set_tile_grid(g, mt, nt);
+  set_tile_grid(g, mt, nt, patch_band(mt, nt, g256::TM, g256::kNarrow));
   if (with_dbt) hipLaunchKernelGGL(gemm256_tn_narrow_kernel<true>, dim3(mt * nt), dim3(256), 0, stream, GWS_GEMM_PASS(g), (const GemmSampling&)g);
   else hipLaunchKernelGGL(gemm256_tn_narrow_kernel<false>, dim3(mt * nt), dim3(256), 0, stream, GWS_GEMM_PASS(g), (const GemmSampling&)g);
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
@@ -235,7 +235,7 @@ int launch_gemm256_tn_split(const GemmArgs& args, bool with_dbt, float* ws, uint
   GemmArgs g = args;
   const uint64_t tiles = (uint64_t)(g.M / g256::TM) * (g.N / g256::TN);
   if (parts < 2 || parts > kMaxParts || parts > g.K / g256::TK || tiles * 16 >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
-  set_tile_grid(g, g.M / g256::TM, g.N / g256::TN);
+  set_tile_grid(g, g.M / g256::TM, g.N / g256::TN, patch_band(g.M / g256::TM, g.N / g256::TN, g256::TM, g256::TN));
   hipLaunchKernelGGL(gemm256_tn_part_kernel, dim3((uint32_t)(tiles * parts)), dim3(256), 0, stream, GWS_GEMM_PASS(g), parts, ws);
   if (hipGetLastError() != hipSuccess) return GWS_ERR_LAUNCH;
   if (with_dbt) hipLaunchKernelGGL(gemm256_tn_sum_kernel<true>, dim3((uint32_t)(tiles * 16)), dim3(256), 0, stream, GWS_GEMM_PASS(g), parts, (const float*)ws, (const GemmSampling&)g);

@@ -69,7 +69,7 @@ __global__ __launch_bounds__(256, 1) void gemm_stream_tn_kernel(GWS_GEMM_PARAMS,
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   uint16_t* ring = (uint16_t*)lds + wave * (D * STG);
   uint32_t m0, n0, u0, u1;
-  // Each XCD takes a contiguous part of the pieces, in bands of eight along the shorter side of C: neighbouring pieces share lines and an
+  // Each XCD takes a contiguous part of the pieces, in bands along the shorter side of C: neighbouring pieces share lines and an
   // operand.  Along the rows whatever the shape, every XCD read all of the longer operand of a weight of few columns (1856 tokens
   // x 1792 x 256 in pieces of 64 x 32 11.9 us, like this 10.1; 7680 x 4096 x 256 in 64 x 64 47.2, 30.0); with groups of eight dealt
   // round-robin 2048 x 1024 x 1024 12.9, like this 11.0, 3072 x 768 x 256 13.8, 11.9, 8192 x 2048 x 2048 67.7, 66.0; 50 sizes 0.97.
@@ -232,11 +232,22 @@ __global__ __launch_bounds__(256, 1) void gemm_stream_tn_kernel(GWS_GEMM_PARAMS,
   }
 }
 
+uint32_t patch_band(uint32_t mt, uint32_t nt, uint32_t rows, uint32_t cols) {
+  const int cus = compute_units();
+  const double per = fmax(1.0, fmin((double)mt * nt, cus > 0 ? cus : 256) / 8);
+  auto patch = [&](double r) {   // what the bands of r rows read, by their tile columns
+    const double c = fmin(fmax(1.0, per / r), nt);
+    return r * fmax(r, per / c) * rows + r * c * cols;
+  };
+  auto reads = [&](uint32_t b) { return mt / b * patch(b) + (mt % b ? patch(mt % b) : 0); };
+  return reads(4) < reads(8) * (1 - 1e-9) ? 4 : 8;
+}
+
 template <int MT, int NT, int D, bool HALVES>
 static void launch_tn(GemmArgs g, bool with_dbt, hipStream_t s) {
   const uint32_t mt = (g.M + 16 * MT - 1) / (16 * MT), nt = (g.N + 16 * NT - 1) / (16 * NT);
-  if (g.M > g.N) set_tile_grid(g, nt, mt);   // the numbering runs along the longer side
-  else set_tile_grid(g, mt, nt);
+  if (g.M > g.N) set_tile_grid(g, nt, mt, patch_band(nt, mt, 16 * NT, 16 * MT));   // the numbering runs along the longer side
+  else set_tile_grid(g, mt, nt, patch_band(mt, nt, 16 * MT, 16 * NT));
   const dim3 grid(mt * nt);
   if (with_dbt) hipLaunchKernelGGL((gemm_stream_tn_kernel<MT, NT, D, true, HALVES>), grid, dim3(256), 0, s, GWS_GEMM_PASS(g), (const GemmSampling&)g);
   else hipLaunchKernelGGL((gemm_stream_tn_kernel<MT, NT, D, false, HALVES>), grid, dim3(256), 0, s, GWS_GEMM_PASS(g), (const GemmSampling&)g);

@@ -108,7 +108,8 @@ struct GemmArgs : GemmSampling {
   GemmArgs { sampling, px, pw, py, pM, pN, pK, pldx, pldw, pldy, pinv_band, pinv_last }
 #define GWS_GEMM_PASS(g) (g).x, (g).w, (g).y, (g).M, (g).N, (g).K, (g).ldx, (g).ldw, (g).ldy, (g).inv_band, (g).inv_last
 
-// n / d by the host's reciprocal min(floor(2^32 / d), 2^32 - 1): the estimate is at most one too small for any 32-bit n.
+// n / d by the host's reciprocal min(floor(2^32 / d), 2^32 - 1): the estimate is at most one too small for any 32-bit n (and, for n
+// below 2^31, with the reciprocal's lowest bit cleared).
 inline uint32_t reciprocal(uint32_t d) {
   const uint64_t inv = ((uint64_t)1 << 32) / d;
   return inv > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)inv;
@@ -117,36 +118,38 @@ __host__ __device__ __forceinline__ uint32_t divide(uint32_t n, uint32_t d, uint
   const uint32_t q = (uint32_t)(((uint64_t)n * inv) >> 32);
   return q + (n - q * d >= d ? 1u : 0u);
 }
-// A grid of mt x nt tiles of Y in bands of eight tile rows, the last band of mt % 8 where that is not 0: what its numbering
-// divides by is 8 nt, the tiles of a band, and the last band's rows.
+// A grid of mt x nt tiles of Y in bands of B = 4 or 8 tile rows, the last band of mt % B where that is not 0: what its numbering
+// divides by is B nt, the tiles of a band, and the last band's rows.  inv_band's lowest bit, which the numbers divided here (below
+// 2^31) do not need, says that B is 4.
 struct TileGrid {
   uint32_t mt, nt, inv_band, inv_last;
+  __host__ __device__ __forceinline__ uint32_t log_band() const { return 3 - (inv_band & 1); }
 };
-inline void set_tile_grid(GemmArgs& g, uint32_t mt, uint32_t nt) {
-  g.inv_band = reciprocal(8 * nt);
-  g.inv_last = reciprocal(mt % 8 ? mt % 8 : 8);
+inline void set_tile_grid(GemmArgs& g, uint32_t mt, uint32_t nt, uint32_t band = 8) {
+  g.inv_band = (reciprocal(band * nt) & ~1u) | (band == 4 ? 1 : 0);
+  g.inv_last = reciprocal(mt % band ? mt % band : band);
 }
 // Tile L of the order that walks a band's rows down before it moves one tile right.
 __host__ __device__ __forceinline__ void tile_in_bands(const TileGrid& t, uint32_t L, uint32_t& tile_m, uint32_t& tile_n) {
-  const uint32_t band = divide(L, 8 * t.nt, t.inv_band), r = L - band * 8 * t.nt;
-  if (band * 8 + 8 <= t.mt) {
-    tile_n = r >> 3;
-    tile_m = band * 8 + (r & 7);
+  const uint32_t s = t.log_band(), b = 1u << s, band = divide(L, t.nt << s, t.inv_band & ~1u), r = L - band * (t.nt << s);
+  if (band * b + b <= t.mt) {
+    tile_n = r >> s;
+    tile_m = band * b + (r & (b - 1));
   } else {
-    tile_n = divide(r, t.mt & 7, t.inv_last);
-    tile_m = band * 8 + r - tile_n * (t.mt & 7);
+    const uint32_t last = t.mt & (b - 1);
+    tile_n = divide(r, last, t.inv_last);
+    tile_m = band * b + r - tile_n * last;
   }
 }
 // XCD-aware tile numbering: launch-order number L -> (tile_m, tile_n).  Workgroups are dealt round-robin to the 8 XCDs, each
-// with its own L2; XCD x gets a contiguous range of that order, so that the 32 workgroups running together on an XCD form an
-// 8 x 4 patch sharing 8 + 4 panels.
+// with its own L2; XCD x gets a contiguous range of that order, so that the 32 workgroups running together on an XCD form a
+// 4 x 8 or 8 x 4 patch sharing 12 panels.
 __host__ __device__ __forceinline__ void tile_of(const TileGrid& t, uint32_t L, uint32_t& tile_m, uint32_t& tile_n) {
   const uint32_t total = t.mt * t.nt, per = total / 8, rem = total % 8, x = L % 8, j = L / 8;
   tile_in_bands(t, x * per + (x < rem ? x : rem) + j, tile_m, tile_n);   // XCD x owns `per` tiles (+1 for the first `rem`)
 }
-// The same for small tiles: tiles that share a piece of the weight (the rows of a band), and with narrow [K x N] tiles the two
-// that share its cache lines, go to one XCD as a group, and the groups round-robin over the XCDs (a contiguous range per XCD
-// would put the columns of one XCD on a few of the L2's channels when a row of the weight is a multiple of 4 KiB).
+// The same for small tiles, dealt out: tiles that share a piece of the weight (the rows of a band of eight), and with narrow [K x N]
+// tiles the two that share its cache lines, go to one XCD as a group, and the groups round-robin over the XCDs.
 __host__ __device__ __forceinline__ void tile_of_groups(const TileGrid& t, bool pairs, uint32_t b, uint32_t& tile_m, uint32_t& tile_n) {
   const uint32_t p = pairs ? 1 : 0;   // groups of G = min(mt, 8) << p tiles
   const uint32_t whole = t.mt < 8 ? (t.nt >> (3 + p) << (3 + p)) * t.mt : t.mt * t.nt >> (6 + p) << (6 + p);   // of rounds of 8 G
@@ -210,6 +213,11 @@ struct RideList {
 int launch_gemm256_ride(const GemmArgs& g, int w_is_nk, const RideList& r, int fmt, uint64_t step, uint32_t extra,
                         int rider, hipStream_t stream);
 int compute_units();   // of the current device; 0 if the query fails
+// The band for mt x nt tiles of the weight gradient: an XCD's workgroups at work form a patch of so many tile rows by the columns that
+// follow, and what it reads into its L2 is the patch's rows of one operand and its columns of the other, over all bands fewer lines with
+// 4 or with 8 (rows, cols: of a tile).  us with 8 and with 4: 4096 x 768 x 768 in 64 x 64 17.9, 16.2, 8192 x 2048 x 2560 81.8, 80.1; on a
+// tie 8: 4096 x 3072 x 768 29.4, 30.0, 4096 x 768 x 3072 30.7, 30.9.
+uint32_t patch_band(uint32_t mt, uint32_t nt, uint32_t rows, uint32_t cols);
 // Weight-gradient GEMM (gws_gemm256_tn.hip): y[M x N] = x^T * w with x [K x M], w [K x N]
 // row-major (K = the contraction length); with_dbt adds Eq. 4's block reduction on y.
 bool gemm256_tn_applicable(const GemmArgs& g);
