@@ -223,8 +223,8 @@ uint32_t patch_band(uint32_t mt, uint32_t nt, uint32_t rows, uint32_t cols);
 bool gemm256_tn_applicable(const GemmArgs& g);
 int launch_gemm256_tn(const GemmArgs& g, bool with_dbt, hipStream_t stream);
 int launch_gemm256_tn_narrow(const GemmArgs& g, bool with_dbt, hipStream_t stream);   // the same with tiles of 256 x 192
-// weights of few tiles (gws_gemm_stream_tn.hip): a 16 mt x 16 nt piece a workgroup, the tokens split over its four wavefronts
-// (halves: and each wavefront's in two); us 1e30: no piece takes the leading dimensions
+// weights of few tiles (gws_gemm_stream_tn.hip): a 16 mt x 16 nt piece a workgroup, the tokens in four fp32 sums (halves: in
+// eight); us 1e30: no piece takes the leading dimensions
 struct TnPlan {
   int mt, nt;
   double us;
