@@ -60,6 +60,14 @@ __device__ __forceinline__ void rows_of_block(u32x2 (&pk)[2][2], u32x4 (&o)[2]) 
   }
 }
 
+// The numbering runs along the longer side of C.  64 x 32 pieces of which an XCD gets at most eight: eight of one row, which read whole
+// lines of dY, rather than four of two columns, which share one (2688 x 256 x 512 11.9 -> 10.7 us, 4096 x 256 x 256 15.8 -> 14.5; with
+// twelve 4096 x 256 x 768 14.4 -> 15.1).
+template <int NT>
+__host__ __device__ __forceinline__ bool along_columns(const GemmArgs& g, uint32_t mt, uint32_t nt) {
+  return g.M > g.N || (NT == 2 && mt * nt <= 64);
+}
+
 // A wavefront keeps D units of 32 tokens on their way into its own ring: both operands are rows of the outputs, so a unit may be
 // as shallow as the MFMA is deep.
 // HALVES: every wavefront sums its tokens in two halves, eight fp32 sums an element instead of four.
@@ -85,7 +93,7 @@ __global__ __launch_bounds__(256, 1) void gemm_stream_tn_kernel(GWS_GEMM_PARAMS,
   // x 1792 x 256 in pieces of 64 x 32 11.9 us, like this 10.1; 7680 x 4096 x 256 in 64 x 64 47.2, 30.0); with groups of eight dealt
   // round-robin 2048 x 1024 x 1024 12.9, like this 11.0, 3072 x 768 x 256 13.8, 11.9, 8192 x 2048 x 2048 67.7, 66.0; 50 sizes 0.97.
   const uint32_t mt = (g.M + BM - 1) / BM, nt = (g.N + BN - 1) / BN;
-  if (g.M > g.N) tile_of(TileGrid{nt, mt, g.inv_band, g.inv_last}, blockIdx.x, n0, m0);
+  if (along_columns<NT>(g, mt, nt)) tile_of(TileGrid{nt, mt, g.inv_band, g.inv_last}, blockIdx.x, n0, m0);
   else tile_of(TileGrid{mt, nt, g.inv_band, g.inv_last}, blockIdx.x, m0, n0);
   m0 *= BM;
   n0 *= BN;
@@ -251,7 +259,7 @@ uint32_t patch_band(uint32_t mt, uint32_t nt, uint32_t rows, uint32_t cols) {
 template <int MT, int NT, int D, bool HALVES>
 static void launch_tn(GemmArgs g, bool with_dbt, hipStream_t s) {
   const uint32_t mt = (g.M + 16 * MT - 1) / (16 * MT), nt = (g.N + 16 * NT - 1) / (16 * NT);
-  if (g.M > g.N) set_tile_grid(g, nt, mt, patch_band(nt, mt, 16 * NT, 16 * MT));   // the numbering runs along the longer side
+  if (along_columns<NT>(g, mt, nt)) set_tile_grid(g, nt, mt, patch_band(nt, mt, 16 * NT, 16 * MT));
   else set_tile_grid(g, mt, nt, patch_band(mt, nt, 16 * MT, 16 * NT));
   const dim3 grid(mt * nt);
   if (with_dbt) hipLaunchKernelGGL((gemm_stream_tn_kernel<MT, NT, D, true, HALVES>), grid, dim3(256), 0, s, GWS_GEMM_PASS(g), (const GemmSampling&)g);
