@@ -7,7 +7,8 @@
 // barrier a K-step, between its two 32-deep halves: the second half's fragments are read under the first half's MFMAs, the next
 // step's first ones under the second half's.
 // What bounds it: a K-step of 128 x 128 takes 0.41 us (W [N x K]; 0.43 for [K x N]), of which the operands' 32 KiB from L2 alone 0.34, the
-// MFMAs alone 0.25 and the LDS reads alone 0.17; misses in L2 are not it (0.39 without any).  A launch starts and ends in 6 us.
+// MFMAs alone 0.25 and the LDS reads alone 0.17; misses in L2 are not it (0.39 without any).  A launch starts and
+// ends in 5.7 us (6.0 with divisions in the tile numbering and the arguments in memory).
 // 128 x 96 is for the sizes whose 128 x 128 tiles leave compute units idle in their rounds: 4096 x 3072 -> 768 is 256 tiles instead of
 // 192, one round of either, 27.7 -> 23.7 us (816 TFLOP/s); 1000 x 768 -> 2304 8.7 -> 7.9; 3500 x 3008 -> 800 24.6 -> 21.2; 8192 x 2304
 // -> 768, two rounds, 35.9 -> 32.8.  All of W [K x N]; [N x K] alike.  Each element's sum runs in the same order in both.
