@@ -50,14 +50,9 @@ __global__ __launch_bounds__(64 * P) void gemm_stream_kernel(GWS_GEMM_PARAMS) {
   const uint32_t lane = threadIdx.x & 63, li = lane & 15, grp = lane >> 4;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint16_t* ring = (uint16_t*)lds + wave * (D * STG);
-  // A contiguous part of the tiles per XCD, eight tile rows high, reads least into its L2, and what the L2s read comes in at 8 TB/s in
-  // all: 1000 x 2304 -> 768 with groups of one tile column dealt round-robin 40 MB, 11.0 us, like this 25 MB, 10.0 ([K x N] 11.6,
-  // 10.6); 2800 x 5184 -> 608 42.6, 30.7; 300 x 768 -> 768 4.9, 4.4; 68 sizes 0.97.  Few tiles or columns of them stay dealt out
-  // ([K x N] 822 x 2816 -> 64 7.2, as a part 7.8, 372 x 4320 -> 128 11.3, 12.1; [N x K] 601 x 5568 -> 128 10.6, 10.3), and few rows of X on
-  // a wide [K x N] weight (16 x 2048 -> 5632 7.4, 7.7; 64 x 768 -> 3072 4.1, 4.6; up to eight tile rows an XCD reads all of X in either order).
   const TileGrid t = {(g.M + BM - 1) / BM, (g.N + BN - 1) / BN, g.inv_band, g.inv_last};
   uint32_t m0, n0;
-  if (t.nt >= (W_NK ? 4 : 6) && t.mt * t.nt >= 32 && (W_NK || t.mt > 8 || (t.mt > 1 && g.N <= 2304))) tile_of(t, blockIdx.x, m0, n0);
+  if (t.joined()) tile_of_joined(t, blockIdx.x, m0, n0);   // StreamPlan::parts
   else tile_of_groups(t, !W_NK && NT == 2, blockIdx.x, m0, n0);
   m0 *= BM;
   n0 *= BN;
@@ -543,7 +538,7 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_pair_sample_kernel(GWS_GEMM_
 // (in the order of the tiles then; as they are dealt now the first 5.6, 1000 x 2304 -> 768 in 64x64 10.6).
 // ---------------------------------------------------------------------------
 StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk) {
-  StreamPlan best = {0, 0, 0, 0, 0, 0, 1e30};
+  StreamPlan best = {0, 0, 0, 0, 0, 0, 0, 1e30};
   if (K < 64) return best;
   const int cus = compute_units() > 0 ? compute_units() : 256;
   // bytes per ns: eight wavefronts keep twice the loads in flight that four do
@@ -555,8 +550,9 @@ StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk) {
     const uint64_t wgs = ((M + 16 * t.mt - 1) / (16 * t.mt)) * ((N + 16 * t.nt - 1) / (16 * t.nt));
     const double rounds = (double)((wgs + cus - 1) / cus);
     const double us = 1.8 + 2.7 * rounds + rounds * (double)K * 2 * 16 * (t.mt + t.nt) / t.rate * 1e-3;
-    if (wgs < 0x7FFFFFFFull && us < best.us) best = {t.mt, t.nt, t.p, 16 * t.mt, 16 * t.nt, 0, us};
+    if (wgs < 0x7FFFFFFFull && us < best.us) best = {t.mt, t.nt, t.p, 16 * t.mt, 16 * t.nt, 0, 0, us};
   }
+  if (best.p == 0) return best;
   // Of one MFMA tile's rows and columns those that are wanted.  Up to eight rows of X are one load instruction a unit instead of
   // two (4 x 5632 -> 2048 6.09 -> 5.64 us).  Eight columns of an [N x K] weight make twice the workgroups: faster where they still
   // fit one a compute unit and K is long enough for the bytes to count (16 x 5632 -> 2048 6.48 -> 5.95, 4 x 4096 -> 512 3.95 -> 3.89,
@@ -573,6 +569,13 @@ StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk) {
     const uint64_t row = ((M + best.bm - 1) / best.bm * ((N + best.bn - 1) / best.bn) + 7) / 8 * 8, spare = (uint64_t)cus / row;
     best.warm = w_is_nk ? (spare >= 2 ? 1 : 0) : spare >= 4 ? 3 : spare == 3 ? 2 : 0;
   }
+  // A contiguous part of the tiles per XCD, eight tile rows high, reads least into its L2, and what the L2s read comes in at 8 TB/s in
+  // all: 1000 x 2304 -> 768 with groups of one tile column dealt round-robin 40 MB, 11.0 us, like this 25 MB, 10.0 ([K x N] 11.6,
+  // 10.6); 2800 x 5184 -> 608 42.6, 30.7; 300 x 768 -> 768 4.9, 4.4; 68 sizes 0.97.  Few tiles or columns of them stay dealt out
+  // ([K x N] 822 x 2816 -> 64 7.2, as a part 7.8, 372 x 4320 -> 128 11.3, 12.1; [N x K] 601 x 5568 -> 128 10.6, 10.3), and few rows of X on
+  // a wide [K x N] weight (16 x 2048 -> 5632 7.4, 7.7; 64 x 768 -> 3072 4.1, 4.6; up to eight tile rows an XCD reads all of X in either order).
+  const uint64_t rows = (M + best.bm - 1) / best.bm, columns = (N + best.bn - 1) / best.bn;
+  best.parts = columns >= (w_is_nk ? 4 : 6) && rows * columns >= 32 && (w_is_nk || rows > 8 || (rows > 1 && N <= 2304));
   return best;
 }
 
@@ -582,8 +585,9 @@ bool stream_applicable(const GemmArgs& g) {
 
 // WARM_KN, WARM_NK: the forms that stream_plan lets warm the L2
 template <int MT, int NT, int P, int D, int BM = 16 * MT, int BN = 16 * NT, bool WARM_KN = false, bool WARM_NK = false>
-static void launch_plain(GemmArgs g, int w_is_nk, int warm, hipStream_t s) {
-  const dim3 tiles(stream::tile_grid(g, BM, BN)), grid(warm ? (tiles.x + 7) / 8 * 8 : tiles.x, 1 + warm), block(64 * P);
+static void launch_plain(GemmArgs g, int w_is_nk, const StreamPlan& p, hipStream_t s) {
+  const int warm = WARM_KN || WARM_NK ? p.warm : 0;
+  const dim3 tiles(stream::tile_grid(g, BM, BN, p.parts != 0)), grid(warm ? (tiles.x + 7) / 8 * 8 : tiles.x, 1 + warm), block(64 * P);
   if constexpr (WARM_NK) {
     if (w_is_nk && warm) {
       hipLaunchKernelGGL((gemm_stream_kernel<MT, NT, P, D, true, BM, BN, true>), grid, block, 0, s, GWS_GEMM_PASS(g));
@@ -605,14 +609,14 @@ static void launch_plain(GemmArgs g, int w_is_nk, int warm, hipStream_t s) {
 
 int launch_gemm_stream(const GemmArgs& g, int w_is_nk, const StreamPlan& p, hipStream_t s) {
   // up to 16 rows: two units on their way a wavefront (four, which take all of the LDS: 4 x 5632 -> 2048 [N x K] 6.1 us, two 5.7)
-  if (p.bn == 8) p.bm == 8 ? launch_plain<1, 1, 8, 2, 8, 8>(g, w_is_nk, 0, s) : launch_plain<1, 1, 8, 2, 16, 8>(g, w_is_nk, 0, s);
-  else if (p.bn == 16) p.bm == 8 ? launch_plain<1, 1, 8, 2, 8, 16>(g, w_is_nk, 0, s) : launch_plain<1, 1, 8, 2>(g, w_is_nk, 0, s);
-  else if (p.bm == 8) launch_plain<1, 2, 8, 2, 8, 32, true>(g, w_is_nk, p.warm, s);
-  else if (p.mt == 1) launch_plain<1, 2, 8, 2, 16, 32, true>(g, w_is_nk, p.warm, s);
-  else if (p.mt == 2 && p.nt == 2) launch_plain<2, 2, 8, 2, 32, 32, true, true>(g, w_is_nk, p.warm, s);
-  else if (p.mt == 2) launch_plain<2, 4, 4, 3>(g, w_is_nk, 0, s);
-  else if (p.mt == 4) launch_plain<4, 4, 4, 2>(g, w_is_nk, 0, s);
-  else launch_plain<8, 4, 4, 1>(g, w_is_nk, 0, s);
+  if (p.bn == 8) p.bm == 8 ? launch_plain<1, 1, 8, 2, 8, 8>(g, w_is_nk, p, s) : launch_plain<1, 1, 8, 2, 16, 8>(g, w_is_nk, p, s);
+  else if (p.bn == 16) p.bm == 8 ? launch_plain<1, 1, 8, 2, 8, 16>(g, w_is_nk, p, s) : launch_plain<1, 1, 8, 2>(g, w_is_nk, p, s);
+  else if (p.bm == 8) launch_plain<1, 2, 8, 2, 8, 32, true>(g, w_is_nk, p, s);
+  else if (p.mt == 1) launch_plain<1, 2, 8, 2, 16, 32, true>(g, w_is_nk, p, s);
+  else if (p.mt == 2 && p.nt == 2) launch_plain<2, 2, 8, 2, 32, 32, true, true>(g, w_is_nk, p, s);
+  else if (p.mt == 2) launch_plain<2, 4, 4, 3>(g, w_is_nk, p, s);
+  else if (p.mt == 4) launch_plain<4, 4, 4, 2>(g, w_is_nk, p, s);
+  else launch_plain<8, 4, 4, 1>(g, w_is_nk, p, s);
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
 

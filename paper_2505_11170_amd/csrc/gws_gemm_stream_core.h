@@ -56,11 +56,11 @@ __device__ __forceinline__ void tile_origin(const GemmArgs& g, uint32_t bm, uint
   m0 = tm * bm;
   n0 = tn * bn;
 }
-// The grid of such tiles, its reciprocals put into g; 0 if it is too large.
-inline uint32_t tile_grid(GemmArgs& g, uint32_t bm, uint32_t bn) {
+// The grid of such tiles, its reciprocals put into g; 0 if it is too large.  parts: for tile_of_joined.
+inline uint32_t tile_grid(GemmArgs& g, uint32_t bm, uint32_t bn, bool parts = false) {
   const uint32_t mt = (uint32_t)(((uint64_t)g.M + bm - 1) / bm), nt = (uint32_t)(((uint64_t)g.N + bn - 1) / bn);
   if ((uint64_t)mt * nt >= 0x7FFFFFFFull) return 0;
-  set_tile_grid(g, mt, nt);
+  set_tile_grid(g, mt, nt, 8, parts);
   return mt * nt;
 }
 

@@ -119,15 +119,17 @@ __host__ __device__ __forceinline__ uint32_t divide(uint32_t n, uint32_t d, uint
   return q + (n - q * d >= d ? 1u : 0u);
 }
 // A grid of mt x nt tiles of Y in bands of B = 4 or 8 tile rows, the last band of mt % B where that is not 0: what its numbering
-// divides by is B nt, the tiles of a band, and the last band's rows.  inv_band's lowest bit, which the numbers divided here (below
-// 2^31) do not need, says that B is 4.
+// divides by is B nt, the tiles of a band, and the last band's rows.  Two bits that the numbers divided here (below 2^31) do not need
+// of the reciprocals: inv_band's lowest says that B is 4, inv_last's that the bands (of 8) are joined (tile_of_joined).
 struct TileGrid {
   uint32_t mt, nt, inv_band, inv_last;
   __host__ __device__ __forceinline__ uint32_t log_band() const { return 3 - (inv_band & 1); }
+  __host__ __device__ __forceinline__ bool joined() const { return (inv_last & 1) != 0; }
 };
-inline void set_tile_grid(GemmArgs& g, uint32_t mt, uint32_t nt, uint32_t band = 8) {
+inline void set_tile_grid(GemmArgs& g, uint32_t mt, uint32_t nt, uint32_t band = 8, bool joined = false) {
+  const uint32_t over = mt % band, last = over == 0 ? band : over <= 2 && joined && mt > band ? band + over : over;
   g.inv_band = (reciprocal(band * nt) & ~1u) | (band == 4 ? 1 : 0);
-  g.inv_last = reciprocal(mt % band ? mt % band : band);
+  g.inv_last = (reciprocal(last) & ~1u) | (joined ? 1 : 0);
 }
 // Tile L of the order that walks a band's rows down before it moves one tile right.
 __host__ __device__ __forceinline__ void tile_in_bands(const TileGrid& t, uint32_t L, uint32_t& tile_m, uint32_t& tile_n) {
@@ -141,12 +143,36 @@ __host__ __device__ __forceinline__ void tile_in_bands(const TileGrid& t, uint32
     tile_m = band * b + r - tile_n * last;
   }
 }
-// XCD-aware tile numbering: launch-order number L -> (tile_m, tile_n).  Workgroups are dealt round-robin to the 8 XCDs, each
-// with its own L2; XCD x gets a contiguous range of that order, so that the 32 workgroups running together on an XCD form a
+// Workgroups are dealt round-robin to the 8 XCDs, each with its own L2: number L of a launch of `total` as the place in an order of
+// which XCD x gets a contiguous range (total / 8, one more for the first total % 8).
+__host__ __device__ __forceinline__ uint32_t xcd_part(uint32_t total, uint32_t L) {
+  const uint32_t per = total / 8, rem = total % 8, x = L % 8, j = L / 8;
+  return x * per + (x < rem ? x : rem) + j;
+}
+// XCD-aware tile numbering: launch-order number L -> (tile_m, tile_n), the 32 workgroups running together on an XCD a
 // 4 x 8 or 8 x 4 patch sharing 12 panels.
 __host__ __device__ __forceinline__ void tile_of(const TileGrid& t, uint32_t L, uint32_t& tile_m, uint32_t& tile_n) {
-  const uint32_t total = t.mt * t.nt, per = total / 8, rem = total % 8, x = L % 8, j = L / 8;
-  tile_in_bands(t, x * per + (x < rem ? x : rem) + j, tile_m, tile_n);   // XCD x owns `per` tiles (+1 for the first `rem`)
+  tile_in_bands(t, xcd_part(t.mt * t.nt, L), tile_m, tile_n);
+}
+// The same for small tiles, in joined bands: a remainder of one or two rows belongs to the band of eight before it.  As a band
+// of its own it is the part of one XCD alone, which then reads every column of the weight: us with nine tile rows, joined and not, the operands
+// in the last-level cache: [N x K] 258 x 2816 -> 1536 8.7, 10.9, 530 x 2816 -> 3584 21.4, 23.6; [K x N] 288 x 1440 -> 1536 7.0, 8.1.  Three
+// rows stay alone (24 sizes of eleven tile rows 0.98 of joined).
+__host__ __device__ __forceinline__ void tile_of_joined(const TileGrid& t, uint32_t L, uint32_t& tile_m, uint32_t& tile_n) {
+  const uint32_t l = xcd_part(t.mt * t.nt, L);
+  uint32_t band = divide(l, 8 * t.nt, t.inv_band), left = t.mt - 8 * band;   // tile rows from here on
+  if (left <= 2 && band > 0) {
+    --band;
+    left += 8;
+  }
+  const uint32_t r = l - band * 8 * t.nt;
+  if (left > 10) {
+    tile_n = r >> 3;
+    tile_m = 8 * band + (r & 7);
+  } else {
+    tile_n = divide(r, left, t.inv_last & ~1u);
+    tile_m = 8 * band + r - tile_n * left;
+  }
 }
 // The same for small tiles, dealt out: tiles that share a piece of the weight (the rows of a band of eight), and with narrow [K x N]
 // tiles the two that share its cache lines, go to one XCD as a group, and the groups round-robin over the XCDs.
@@ -164,9 +190,10 @@ __host__ __device__ __forceinline__ void tile_of_groups(const TileGrid& t, bool 
 constexpr int kFusedInOperand = 2;
 int launch_gemm(const GemmArgs& g, int w_is_nk, int fused, int fmt, hipStream_t stream);
 // few rows of X or few tiles (gws_gemm_stream.hip): the tile in units of 16 rows and 16 columns, the parts of K, the rows and
-// columns of it that a workgroup owns, the workgroups a tile that warm the L2 and the estimated time; p == 0: the shape is not one for it
+// columns of it that a workgroup owns, the workgroups a tile that warm the L2, whether each XCD takes a contiguous part of the tiles,
+// and the estimated time; p == 0: the shape is not one for it
 struct StreamPlan {
-  int mt, nt, p, bm, bn, warm;
+  int mt, nt, p, bm, bn, warm, parts;
   double us;
 };
 StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk);

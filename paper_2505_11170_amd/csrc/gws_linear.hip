@@ -205,7 +205,7 @@ GemmRoute gemm_route(const GemmArgs& g, int w_is_nk, RoutePlan& plan) {
   const double cus = compute_units() > 0 ? compute_units() : 256;
   const double nk = ceil(g.K / 64.0);
   auto tiles = [&](double t) { return ceil(g.M / t) * ceil(g.N / t); };
-  plan = RoutePlan{{0, 0, 0, 0, 0, 0, 1e30}, 1e30, 1e30, 1e30, 4, 1e30};
+  plan = RoutePlan{{0, 0, 0, 0, 0, 0, 0, 1e30}, 1e30, 1e30, 1e30, 4, 1e30};
   if (gemm256_edge_applicable(g) || gemm256_applicable(g)) {
     const double n = tiles(256.0);
     plan.large_us = 6.0 + ceil(n / cus) * (3.0 + nk * (1.05 + 0.2 * fmin(1.0, n / cus)));

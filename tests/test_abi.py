@@ -150,6 +150,7 @@ def test_queries_of_the_chosen_kernel(lib):
     assert binding.gws_gemm_form(4, 5632, 2048, w_is_nk=True) == binding.GEMM_STREAM
     assert binding.gws_gemm_form(8192, 2048, 5632) == binding.GEMM_LARGE
     assert [binding.gws_gemm_form(m, 2048, 5632, sampled=2) for m in (16, 8192)] == [binding.GEMM_STREAM_SAMPLE, binding.GEMM_LARGE]
+    assert binding.gws_gemm_form(2**30, 64, 2**30) == 0 or binding.gws_gemm_tile(2**30, 64, 2**30)[0] > 0   # more tiles than a grid has
     tile = binding.gws_gemm_tile                                                      # and the part of Y that a workgroup makes
     assert tile(1024, 48, 64) == (0, 0) and tile(1024, 32, 64) == (128, 128)
     assert [tile(4, 5632, 2048, nk) for nk in (True, False)] == [(16, 16), (16, 32)] and tile(4, 5632, 2048, sampled=1) == (16, 32)

@@ -391,6 +391,16 @@ def test_gemm_that_splits_k(M, K, N, w_is_nk):
     run_case(M, K, N, w_is_nk, gws.FMT_FP8_E4M3, seed_id=idx, step=4, rows_sel=rows_sel)   # the library's choice between the two forms
 
 
+# Bands of eight tile rows with one and two more, which are joined to the band before, and with three, which are not: every tile against
+# the 64-bit product.
+@pytest.mark.parametrize("w_is_nk", [False, True])
+@pytest.mark.parametrize("M,K,N,rows", [(257, 96, 768, 9), (290, 128, 448, 10), (321, 96, 672, 11), (513, 192, 256, 17), (576, 96, 416, 18)])
+def test_gemm_that_splits_k_of_a_few_tile_rows_over_whole_bands(M, K, N, rows, w_is_nk):
+    assert gws.gws_gemm_form(M, K, N, w_is_nk, ldx=K + 8) == gws.GEMM_STREAM
+    assert -(-M // gws.gws_gemm_tile(M, K, N, w_is_nk, ldx=K + 8)[0]) == rows
+    run_case(M, K, N, w_is_nk, gws.FMT_FP8_E4M3, seed_id=63, ldx_pad=8, ldy_pad=8)
+
+
 # Up to 16 rows the stream kernel keeps eight or sixteen rows and, of [N x K] weights, eight, sixteen or 32 columns of its MFMA tiles: each
 # of them, at the edges of the choice (8 and 9 rows, K of 2048, as many eight-column tiles as compute units) and at the smallest.  The
 # sampled form, which has one tile for all of these, gives the same bits (run_case).

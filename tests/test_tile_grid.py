@@ -51,3 +51,57 @@ def test_every_tile_is_taken_once(tmp_path):
                    check=True, capture_output=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+JOINED = r"""
+#include "gws_launch.h"
+#include <cstdio>
+#include <cstdlib>
+#include <set>
+#include <vector>
+using namespace gws;
+int main() {
+  for (uint32_t mt = 1; mt <= 70; ++mt)
+    for (uint32_t nt = 1; nt <= 60; ++nt)
+      for (int way = 0; way < 1; ++way) {
+        GemmArgs g{};
+        const uint32_t band = 8;
+        set_tile_grid(g, mt, nt, band, way == 0);
+        const TileGrid t{mt, nt, g.inv_band, g.inv_last};
+        std::vector<char> seen((size_t)mt * nt, 0);
+        std::set<uint32_t> columns[8];
+        for (uint32_t L = 0; L < mt * nt; ++L) {
+          uint32_t m, n;
+          if (way == 0) tile_of_joined(t, L, m, n);
+          else tile_of(t, L, m, n);
+          if (m >= mt || n >= nt || seen[(size_t)m * nt + n]++) {
+            printf("%u x %u tiles, way %d: number %u -> %u, %u\n", mt, nt, way, L, m, n);
+            return 1;
+          }
+          columns[L % 8].insert(n);
+        }
+        // one or two tile rows over whole bands: no XCD reads the weight's columns for all the others
+        const uint32_t over = mt % (way == 0 ? 8 : 4);
+        for (uint32_t x = 0; x < 8; ++x)
+          if ((over == 1 || over == 2) && mt > 4 && mt < (way == 0 ? 27 : 8) && columns[x].size() > nt / 2 + 2) {
+            printf("%u x %u tiles, way %d: XCD %u has tiles of %zu columns\n", mt, nt, way, x, columns[x].size());
+            return 1;
+          }
+      }
+  return 0;
+}
+"""
+
+
+def run(tmp_path, source):
+    src, exe = tmp_path / "tiles.hip", tmp_path / "tiles"
+    src.write_text(source)
+    root = os.path.dirname(build.CSRC)
+    subprocess.run([build.hipcc(), *build.FLAGS, "-I", build.CSRC, "-I", os.path.join(os.path.dirname(root), "include"), str(src), "-o", str(exe)],
+                   check=True, capture_output=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+
+
+def test_a_row_or_two_over_whole_bands_is_no_part_of_its_own(tmp_path):
+    run(tmp_path, JOINED)
