@@ -253,7 +253,7 @@ uint32_t patch_band(uint32_t mt, uint32_t nt, uint32_t rows, uint32_t cols) {
     return r * fmax(r, per / c) * rows + r * c * cols;
   };
   auto reads = [&](uint32_t b) { return mt / b * patch(b) + (mt % b ? patch(mt % b) : 0); };
-  return reads(4) < reads(8) * (1 - 1e-9) ? 4 : 8;
+  return !leaves_few(mt) && reads(4) < reads(8) * (1 - 1e-9) ? 4 : 8;
 }
 
 template <int MT, int NT, int D, bool HALVES>

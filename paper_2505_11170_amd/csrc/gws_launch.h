@@ -240,10 +240,14 @@ struct RideList {
 int launch_gemm256_ride(const GemmArgs& g, int w_is_nk, const RideList& r, int fmt, uint64_t step, uint32_t extra,
                         int rider, hipStream_t stream);
 int compute_units();   // of the current device; 0 if the query fails
+// Bands of four that leave one or two tile rows to a band of their own, which is the part of one or two XCDs and reads all of the other
+// operand there.
+inline bool leaves_few(uint32_t mt) { return mt % 4 == 1 || mt % 4 == 2; }
 // The band for mt x nt tiles of the weight gradient: an XCD's workgroups at work form a patch of so many tile rows by the columns that
 // follow, and what it reads into its L2 is the patch's rows of one operand and its columns of the other, over all bands fewer lines with
 // 4 or with 8 (rows, cols: of a tile).  us with 8 and with 4: 4096 x 768 x 768 in 64 x 64 17.9, 16.2, 8192 x 2048 x 2560 81.8, 80.1; on a
-// tie 8: 4096 x 3072 x 768 29.4, 30.0, 4096 x 768 x 3072 30.7, 30.9.
+// tie 8: 4096 x 3072 x 768 29.4, 30.0, 4096 x 768 x 3072 30.7, 30.9.  8 too where bands of four leave one or two rows over (leaves_few):
+// 7040 x 768 x 2560 in 128 x 64, six tile rows, 39.8, 42.5.
 uint32_t patch_band(uint32_t mt, uint32_t nt, uint32_t rows, uint32_t cols);
 // Weight-gradient GEMM (gws_gemm256_tn.hip): y[M x N] = x^T * w with x [K x M], w [K x N]
 // row-major (K = the contraction length); with_dbt adds Eq. 4's block reduction on y.

@@ -63,9 +63,9 @@ using namespace gws;
 int main() {
   for (uint32_t mt = 1; mt <= 70; ++mt)
     for (uint32_t nt = 1; nt <= 60; ++nt)
-      for (int way = 0; way < 1; ++way) {
+      for (int way = 0; way < 2; ++way) {
         GemmArgs g{};
-        const uint32_t band = 8;
+        const uint32_t band = way == 1 && !leaves_few(mt) ? 4 : 8;
         set_tile_grid(g, mt, nt, band, way == 0);
         const TileGrid t{mt, nt, g.inv_band, g.inv_last};
         std::vector<char> seen((size_t)mt * nt, 0);
