@@ -170,13 +170,14 @@ __global__ __launch_bounds__(256, 1) void gemm256_ride_kernel(GWS_GEMM_PARAMS, c
 }
 
 // The band of 256 x 256 tiles: with one for every compute unit or more an XCD's patch is 4 x 8 panels rather than 8 x 4, each piece of X
-// read by half as many XCDs (us with a band of 8 and of 4, after the sampling of the weight: 8192 x 2048 -> 2048 60.0, 58.6, -> 5632
-// 155.5, 154.2, 8192 x 4096 -> 4096 200.0, 198.0).  With fewer tiles, and with narrower ones, what the tiles wait for is the weight that
-// was sampled just before, which then comes to twice as many XCDs (3877 x 832 -> 3488 32.4, 33.2; 256 x 192: 4096 x 768 -> 3072 28.4, 29.2;
-// 128 x 96: 2048 x 768 -> 3072 22.7, 23.6).
-static uint32_t band(uint64_t tiles) {
+// read by half as many XCDs: 8192 x 2048 -> 2048 54.3 -> 53.0 us, after the sampling of the weight 58.7 -> 57.4; for larger weights there is
+// nothing in it (42 products of 256 tiles and more 0.9986, sampled 1.001).  Where it leaves one or two tile rows over it costs (five rows:
+// 1147 x 1120 -> 31072 89.9 -> 93.6, 1188 x 2240 -> 30144 148.2 -> 150.6): bands of eight.  With fewer tiles, and with narrower ones, what the
+// tiles wait for is the weight that was sampled just before, which then comes to twice as many XCDs (3877 x 832 -> 3488 32.4, 33.2;
+// 256 x 192: 4096 x 768 -> 3072 28.4, 29.2; 128 x 96: 2048 x 768 -> 3072 22.7, 23.6).
+static uint32_t band(uint32_t mt, uint32_t nt) {
   const int cus = compute_units();
-  return tiles >= (uint64_t)(cus > 0 ? cus : 256) ? 4 : 8;
+  return (uint64_t)mt * nt >= (uint64_t)(cus > 0 ? cus : 256) && !leaves_few(mt) ? 4 : 8;
 }
 
 template <int FMT, int RIDER>
@@ -194,7 +195,7 @@ int launch_gemm256_ride(const GemmArgs& args, int w_is_nk, const RideList& r, in
   GemmArgs g = args;
   const uint64_t tiles = (uint64_t)(g.M / g256::TM) * (g.N / g256::TN);
   if (tiles + extra >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
-  if (tiles > 0) set_tile_grid(g, g.M / g256::TM, g.N / g256::TN, band(tiles));
+  if (tiles > 0) set_tile_grid(g, g.M / g256::TM, g.N / g256::TN, band(g.M / g256::TM, g.N / g256::TN));
   const uint32_t lo = (uint32_t)step, hi = (uint32_t)(step >> 32);
   if (rider == 1) {
     switch (fmt) {
@@ -254,7 +255,7 @@ template <class K>
 static int launch_tiles(K kernel, GemmArgs g, uint32_t tn, hipStream_t stream) {
   const uint32_t mt = (uint32_t)(((uint64_t)g.M + g256::TM - 1) / g256::TM), nt = (uint32_t)(((uint64_t)g.N + tn - 1) / tn);
   if ((uint64_t)mt * nt >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
-  set_tile_grid(g, mt, nt, tn == g256::TN ? band((uint64_t)mt * nt) : 8);
+  set_tile_grid(g, mt, nt, tn == g256::TN ? band(mt, nt) : 8);
   hipLaunchKernelGGL(kernel, dim3(mt * nt), dim3(256), 0, stream, GWS_GEMM_PASS(g));
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;
 }
