@@ -25,7 +25,7 @@ EXPORTS = ("gws_sample_fwd", "gws_sample_bwd", "gws_sample_fwd_bi", "gws_sample_
            "gws_sample_fwd_basis", "gws_sample_bwd_basis", "gws_noise_basis",
            "gws_derive_seed", "gws_status_string", "gws_version")
 BENCH_EXPORTS = ("gws_copy_tiles", "gws_block_absmax", "gws_sample_bwd_tuned", "gws_sample_fwd_tuned", "gws_gemm_bf16_ride_probe", "gws_ride_plan",
-                 "gws_ride_plan_layout", "gws_gemm_form", "gws_gemm_tile", "gws_linear_bwd_w_form", "gws_linear_bwd_w_form_rows", "gws_box_muller_check")
+                 "gws_ride_plan_layout", "gws_gemm_form", "gws_gemm_tile", "gws_gemm_stream_tile", "gws_linear_bwd_w_form", "gws_linear_bwd_w_form_rows", "gws_box_muller_check")
 # kernels as gws_gemm_form and gws_linear_bwd_w_form name them
 GEMM_STREAM, GEMM_MIDDLE, GEMM_LARGE, GEMM_LARGE_EDGE, GEMM_NARROW, GEMM_ANY_SHAPE, GEMM_STREAM_SAMPLE, GEMM_ROWS_SAMPLE, GEMM_ANY_SHAPE_SAMPLE = range(1, 10)
 BWD_W_WIDE, BWD_W_NARROW, BWD_W_PIECES_64, BWD_W_PIECES_128, BWD_W_SPLIT = 1, 2, 3, 4, 16
@@ -144,6 +144,8 @@ def load_library() -> ctypes.CDLL:
     L.gws_gemm_form.restype = ci
     L.gws_gemm_tile.argtypes = [i64, i64, i64, i64, i64, ci, ci]
     L.gws_gemm_tile.restype = ci
+    L.gws_gemm_stream_tile.argtypes = [i64, i64, i64, i64, i64, ci]
+    L.gws_gemm_stream_tile.restype = ctypes.c_uint32
     L.gws_linear_bwd_w_form.argtypes = [tp, i64, ctypes.c_size_t]
     L.gws_linear_bwd_w_form.restype = ci
     L.gws_linear_bwd_w_form_rows.argtypes = [tp, i64, ctypes.c_size_t, ci]
@@ -458,6 +460,14 @@ def gws_gemm_tile(M: int, K: int, N: int, w_is_nk: bool = False, sampled: int = 
     t = int(load_library().gws_gemm_tile(int(M), int(K), K if ldx is None else int(ldx), int(N), (K if w_is_nk else N) if ldw is None else int(ldw),
                                          int(bool(w_is_nk)), int(sampled)))
     return t >> 16, t & 0xFFFF
+
+
+def gws_gemm_stream_tile(M: int, K: int, N: int, w_is_nk: bool = False, ldx: Optional[int] = None, ldw: Optional[int] = None) -> tuple:
+    """Of ``gws_gemm_bf16`` by ``GEMM_STREAM``: rows and columns that a workgroup stores, workgroups a tile that only fetch the weight into the
+    L2s, whether each XCD takes a contiguous part of the tiles; zeros for another kernel."""
+    t = int(load_library().gws_gemm_stream_tile(int(M), int(K), K if ldx is None else int(ldx), int(N), (K if w_is_nk else N) if ldw is None else int(ldw),
+                                                int(bool(w_is_nk))))
+    return t >> 24, t >> 16 & 0xFF, t >> 8 & 0xFF, t & 0xFF
 
 
 def gws_linear_bwd_w_form(w: TensorDesc, M: int, workspace_bytes: int = 0, on_lines: bool = True) -> int:

@@ -700,13 +700,13 @@ int gws_linear_bwd_w_form(const gws_tensor* w, int64_t M, size_t workspace_bytes
 }
 
 // 0: refused sizes
-static int gemm_query(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled, uint32_t& rows, uint32_t& cols) {
+static int gemm_query(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled, uint32_t& rows, uint32_t& cols,
+                      RoutePlan& plan) {
   if (M <= 0 || N <= 0 || K <= 0 || ((K | N) & 31) != 0 || ldx < K || ldw < (w_is_nk ? K : N) || ((ldx | ldw) & 7) != 0 ||
       M >= (int64_t)1 << 31 || N >= (int64_t)1 << 31 || ldx >= (int64_t)1 << 31 || ldw >= (int64_t)1 << 31) return 0;
   GemmArgs g;
   memset(&g, 0, sizeof g);
   g.M = (uint32_t)M; g.N = (uint32_t)N; g.K = (uint32_t)K; g.ldx = (uint32_t)ldx; g.ldw = (uint32_t)ldw;
-  RoutePlan plan;
   const GemmForm form = gemm_form(g, w_is_nk, sampled == 1 || (sampled == 2 && sample_in_operand(g, w_is_nk)) ? kFusedInOperand : 0, plan);
   gemm_tile(g, form, plan, rows, cols);
   return (int)form;
@@ -714,12 +714,21 @@ static int gemm_query(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw,
 
 int gws_gemm_form(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled) {
   uint32_t rows, cols;
-  return gemm_query(M, K, ldx, N, ldw, w_is_nk, sampled, rows, cols);
+  RoutePlan plan;
+  return gemm_query(M, K, ldx, N, ldw, w_is_nk, sampled, rows, cols, plan);
 }
 
 int gws_gemm_tile(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled) {
   uint32_t rows, cols;
-  return gemm_query(M, K, ldx, N, ldw, w_is_nk, sampled, rows, cols) == 0 ? 0 : (int)(rows << 16 | cols);
+  RoutePlan plan;
+  return gemm_query(M, K, ldx, N, ldw, w_is_nk, sampled, rows, cols, plan) == 0 ? 0 : (int)(rows << 16 | cols);
+}
+
+uint32_t gws_gemm_stream_tile(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk) {
+  uint32_t rows, cols;
+  RoutePlan plan;
+  if (gemm_query(M, K, ldx, N, ldw, w_is_nk, 0, rows, cols, plan) != GWS_GEMM_STREAM) return 0;
+  return (uint32_t)plan.stream.bm << 24 | (uint32_t)plan.stream.bn << 16 | (uint32_t)plan.stream.warm << 8 | (uint32_t)plan.stream.parts;
 }
 
 int gws_gemm_bf16(const void* x, int64_t M, int64_t K, int64_t ldx, const void* w, int64_t N, int64_t ldw,

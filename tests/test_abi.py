@@ -157,6 +157,9 @@ def test_queries_of_the_chosen_kernel(lib):
     assert [tile(8192, 2048, n) for n in (5632, 2560)] == [(256, 256), (256, 192)]
     assert [tile(2048, 2048, 2048), tile(1024, 768, 2304)] == [(128, 128), (128, 96)]
     assert [tile(m, 2048, 2048, sampled=1) for m in (2048, 8192)] == [(128, 128), (256, 256)]
+    launch = binding.gws_gemm_stream_tile                                             # rows, columns, workgroups that fetch, parts
+    assert [launch(m, 2048, 2048, True)[:2] for m in (8, 9, 17)] == [(8, 8), (16, 8), (32, 32)] and launch(8192, 2048, 5632) == (0, 0, 0, 0)
+    assert [launch(8, 2048, n)[2] for n in (2048, 2560, 2592)] == [3, 2, 0] and [launch(20, 544, n, True)[2] for n in (4096, 4128)] == [1, 0]
     wide = binding.TensorDesc(rows=4096, cols=4096, ld=4096, seed=1)
     assert binding.gws_linear_bwd_w_form(wide, 512) == binding.BWD_W_WIDE and binding.gws_linear_bwd_w_form(wide, 63) == 0
 

@@ -396,8 +396,8 @@ def test_gemm_that_splits_k(M, K, N, w_is_nk):
 @pytest.mark.parametrize("w_is_nk", [False, True])
 @pytest.mark.parametrize("M,K,N,rows", [(257, 96, 768, 9), (290, 128, 448, 10), (321, 96, 672, 11), (513, 192, 256, 17), (576, 96, 416, 18)])
 def test_gemm_that_splits_k_of_a_few_tile_rows_over_whole_bands(M, K, N, rows, w_is_nk):
-    assert gws.gws_gemm_form(M, K, N, w_is_nk, ldx=K + 8) == gws.GEMM_STREAM
-    assert -(-M // gws.gws_gemm_tile(M, K, N, w_is_nk, ldx=K + 8)[0]) == rows
+    tile_rows, _, _, parts = gws.gws_gemm_stream_tile(M, K, N, w_is_nk, ldx=K + 8)
+    assert -(-M // tile_rows) == rows and parts
     run_case(M, K, N, w_is_nk, gws.FMT_FP8_E4M3, seed_id=63, ldx_pad=8, ldy_pad=8)
 
 
@@ -405,21 +405,25 @@ def test_gemm_that_splits_k_of_a_few_tile_rows_over_whole_bands(M, K, N, rows, w
 # of them, at the edges of the choice (8 and 9 rows, K of 2048, as many eight-column tiles as compute units) and at the smallest.  The
 # sampled form, which has one tile for all of these, gives the same bits (run_case).
 @pytest.mark.parametrize("w_is_nk", [False, True])
-@pytest.mark.parametrize("M,K,N", [(1, 64, 32), (7, 2016, 64), (8, 2048, 2048), (8, 2080, 2080), (9, 2048, 2048), (9, 2016, 96), (16, 2080, 2048), (8, 320, 4128)])
-def test_gemm_of_half_an_mfma_tile(M, K, N, w_is_nk):
-    assert gws.gws_gemm_form(M, K, N, w_is_nk, ldx=K + 8) == gws.GEMM_STREAM
+@pytest.mark.parametrize("M,K,N,columns", [(1, 64, 32, 16), (7, 2016, 64, 16), (8, 2048, 2048, 8), (8, 2080, 2080, 16), (9, 2048, 2048, 8), (9, 2016, 96, 16), (16, 2080, 2048, 8),
+                                           (16, 2080, 2080, 16), (8, 320, 4128, 32)])
+def test_gemm_of_half_an_mfma_tile(M, K, N, columns, w_is_nk):
+    assert gws.gws_gemm_stream_tile(M, K, N, w_is_nk, ldx=K + 8)[:2] == (8 if M <= 8 else 16, columns if w_is_nk else 32)
     run_case(M, K, N, w_is_nk, gws.FMT_FP8_E4M3, seed_id=61, ldx_pad=8, ldy_pad=8, mode=gws.LINEAR_IN_OPERAND,
              rows_sel=None if M * K * N < 2e7 else np.array(sorted({0, M // 2, M - 1})))
 
 
-# Idle compute units fetch the weight into the L2s (up to three workgroups a tile): as many tiles as half, a third, a quarter of the compute
-# units and one more, tiles that do not fill a round of the XCDs, one and two rows of tiles, half a unit at the end of K, K shorter than
-# the wavefronts' ranges are many; bit for bit the sampled form's Y, which has no such workgroups (run_case).
+# Idle compute units fetch the weight into the L2s.  [K x N] (kn workgroups a tile): as many tiles as a quarter and a third of the compute
+# units, one tile more than each, and where a round of the XCDs more takes the last of them; [N x K] of 17 to 64 rows (nk): up to half of the
+# compute units and one more.  Tiles that do not fill a round, one and two rows of them, half a unit at the end of K, one unit a
+# wavefront and many; bit for bit the sampled form's Y, which has no such workgroups (run_case).
 @pytest.mark.parametrize("w_is_nk", [False, True])
-@pytest.mark.parametrize("M,K,N", [(3, 2080, 2048), (16, 1024, 2080), (8, 2720, 2720), (4, 608, 4096), (5, 544, 4128), (16, 2048, 512), (24, 1056, 1024),
-                                   (64, 1056, 1088), (40, 4096, 256)])
-def test_gemm_whose_weight_is_fetched_by_idle_compute_units(M, K, N, w_is_nk):
-    assert gws.gws_gemm_form(M, K, N, w_is_nk, ldx=K + 8) == gws.GEMM_STREAM
+@pytest.mark.parametrize("M,K,N,kn,nk", [
+    (3, 2080, 2048, 3, 0), (16, 1024, 2080, 2, 0), (6, 544, 2560, 2, 0), (6, 544, 2592, 0, 0), (8, 2720, 2720, 0, 0), (4, 608, 4096, 0, 0), (5, 544, 4128, 0, 0),
+    (8, 512, 2048, 3, 0), (16, 2048, 512, 3, 0), (24, 1056, 1024, 3, 1), (20, 512, 2048, 3, 1), (64, 1056, 1088, 2, 1), (40, 4096, 256, 3, 1), (20, 544, 3840, 0, 1),
+    (20, 544, 4096, 0, 1), (20, 544, 4128, 0, 0)])
+def test_gemm_whose_weight_is_fetched_by_idle_compute_units(M, K, N, kn, nk, w_is_nk):
+    assert gws.gws_gemm_stream_tile(M, K, N, w_is_nk, ldx=K + 8)[2] == (nk if w_is_nk else kn)
     run_case(M, K, N, w_is_nk, gws.FMT_FP8_E4M3, seed_id=62, ldx_pad=8, ldy_pad=8, mode=gws.LINEAR_IN_OPERAND, rows_sel=np.array(sorted({0, M // 2, M - 1})))
 
 
