@@ -572,10 +572,16 @@ StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk) {
   // A contiguous part of the tiles per XCD, eight tile rows high, reads least into its L2, and what the L2s read comes in at 8 TB/s in
   // all: 1000 x 2304 -> 768 with groups of one tile column dealt round-robin 40 MB, 11.0 us, like this 25 MB, 10.0 ([K x N] 11.6,
   // 10.6); 2800 x 5184 -> 608 42.6, 30.7; 300 x 768 -> 768 4.9, 4.4; 68 sizes 0.97.  Few tiles or columns of them stay dealt out
-  // ([K x N] 822 x 2816 -> 64 7.2, as a part 7.8, 372 x 4320 -> 128 11.3, 12.1; [N x K] 601 x 5568 -> 128 10.6, 10.3), and few rows of X on
-  // a wide [K x N] weight (16 x 2048 -> 5632 7.4, 7.7; 64 x 768 -> 3072 4.1, 4.6; up to eight tile rows an XCD reads all of X in either order).
-  const uint64_t rows = (M + best.bm - 1) / best.bm, columns = (N + best.bn - 1) / best.bn;
-  best.parts = columns >= (w_is_nk ? 4 : 6) && rows * columns >= 32 && (w_is_nk || rows > 8 || (rows > 1 && N <= 2304));
+  // ([K x N] 822 x 2816 -> 64 7.2, as a part 7.8, 372 x 4320 -> 128 11.3, 12.1; [N x K] 601 x 5568 -> 128 10.6, 10.3), and one row of them on
+  // a [K x N] weight (16 x 2048 -> 5632 7.4, 7.7).
+  // [K x N] weights of a multiple of 512 columns: the groups are whole rounds of the XCDs there, and beyond 2048 columns in one round of
+  // workgroups they stay too.  The orders differ only for a weight that is multiplied again and again out of the L2s; in turn out of the L2s
+  // and from HBM, groups and parts: 48 x 4096 -> 3072 7.7, 10.9 and 17.4, 17.3, 132 x 4096 -> 2560 10.5, 12.3 and 19.7, 19.7; up to 2048 columns
+  // 48 x 4096 -> 2048 7.1, 7.3 and 16.5, 16.2, 250 x 1440 -> 1024 5.4, 5.4 and 7.9, 7.7; of more than a round 132 x 4096 -> 5632 24.1, 21.8 and 36.1,
+  // 31.4.  Other widths: 48 x 4096 -> 2336 10.0, 7.9 and 13.3, 13.0, 132 x 2816 -> 3104 9.6, 9.1 and 13.1, 13.0; 18 of them beyond 2304 columns
+  // 0.98 out of the L2s, 0.97 from the last-level cache, 0.98 from HBM.
+  const uint64_t rows = (M + best.bm - 1) / best.bm, columns = (N + best.bn - 1) / best.bn, all = rows * columns;
+  best.parts = columns >= (w_is_nk ? 4 : 6) && all >= 32 && (w_is_nk || (rows > 1 && (N % 512 != 0 || N <= 2048 || all > (uint64_t)cus)));
   return best;
 }
 

@@ -160,6 +160,9 @@ def test_queries_of_the_chosen_kernel(lib):
     launch = binding.gws_gemm_stream_tile                                             # rows, columns, workgroups that fetch, parts
     assert [launch(m, 2048, 2048, True)[:2] for m in (8, 9, 17)] == [(8, 8), (16, 8), (32, 32)] and launch(8192, 2048, 5632) == (0, 0, 0, 0)
     assert [launch(8, 2048, n)[2] for n in (2048, 2560, 2592)] == [3, 2, 0] and [launch(20, 544, n, True)[2] for n in (4096, 4128)] == [1, 0]
+    # [K x N], two tile rows and more: parts, unless the columns are a multiple of 512 beyond 2048 and the tiles one round of the compute units
+    assert [launch(100, 2048, n)[3] for n in (2048, 2304, 2336, 2560, 2592, 3072, 5600)] == [1, 1, 1, 0, 1, 0, 1] and launch(132, 4096, 5632)[3] == 1
+    assert [launch(16, 2048, n)[3] for n in (2304, 2336)] == [0, 0] and [launch(100, 2048, n, True)[3] for n in (96, 2560)] == [0, 1]
     wide = binding.TensorDesc(rows=4096, cols=4096, ld=4096, seed=1)
     assert binding.gws_linear_bwd_w_form(wide, 512) == binding.BWD_W_WIDE and binding.gws_linear_bwd_w_form(wide, 63) == 0
 
