@@ -391,6 +391,9 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_sample_kernel(GWS_GEMM_PARAM
   uint32_t slot = 0, next = 1, last = D - 1;   // of this unit, the next one and the one before
   Frag8 f[2][2];
   auto multiply = [&](uint32_t u, uint32_t at) __attribute__((always_inline)) {
+    // MFMAs and LDS reads are 8 bytes each: four bytes off, every eighth one lies on two lines of the instruction cache (BF16 8192 x 2048 ->
+    // 5632 [K x N] 293 -> 281 us; where the loop falls otherwise, [N x K] 296 -> 281)
+    asm volatile(".p2align 3");
     const uint16_t* xs = ring + at * XS;
     const bool half = 64 * u + 64 > g.K;
 #pragma unroll
@@ -407,7 +410,9 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_sample_kernel(GWS_GEMM_PARAM
     }
   };
   const bool late = wave >= 4;   // uniform
-  asm volatile(".p2align 6");   // the loop at a line of the instruction cache: FP8 [K x N] 8192 x 2048 -> 5632 293.4 -> 285.9 us
+  // A shift of the code that measured faster, not an alignment of the loop: its header comes about 140 instructions later, 44 or 48 bytes
+  // past a line of the instruction cache.  FP8 [K x N] 8192 x 2048 -> 5632 with and without 287, 294 us, FP6 358, 360; [N x K] 305, 303 and 369, 367.
+  asm volatile(".p2align 6");
   for (uint32_t u = 0; u < nu; ++u) {
     // this unit, requested a unit's sampling ago, has landed, and every wavefront is past its reads of the stage filled next
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
