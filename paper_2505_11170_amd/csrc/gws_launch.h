@@ -59,12 +59,22 @@ struct LaunchArgs {
   uint32_t tiles_per_wg;       // consecutive block rows one workgroup covers (>= 1)
   uint32_t tiles_per_wg_x;     // neighbouring 256-column tiles one workgroup covers (>= 1)
 };
-// The same for one tensor: a hundred bytes instead of five thousand, read in one go.
+// The same for one tensor: a hundred bytes instead of five thousand, read in one go.  dealt: the first workgroups, whole rounds of 128,
+// of which sixteen neighbouring ones go to one XCD (locate, gws_sample.hip).
 struct OneArgs {
   TileDesc t;
   uint32_t step_lo, step_hi;
   uint32_t tiles_per_wg, tiles_per_wg_x;
+  uint32_t dealt;
 };
+// Weights of more than 32 MB (2048 tiles) are dealt out as several are.  Without that rows off the cache lines, and codes, of one such
+// weight took up to half as long again: 264 M parameters in rows of 408 FP8 343 us, like this 230, uniform basis 203 M 235, 196, MX-FP8 65 M
+// 41.8, 34.9, copying backward with a parametrised bitwidth 270 M 312, 253; MX-FP6 of whole tiles 164 M 73, 70.  Up to 32 MB it goes either way:
+// 9.5 M FP8 10.0, 10.4, 8.4 M copying backward 9.5, 10.0, 6.0 M MX-FP8 7.6, 7.2.
+inline OneArgs one_of(const LaunchArgs& a, uint32_t n_wg) {
+  const uint64_t tiles = (uint64_t)n_wg * a.tiles_per_wg * a.tiles_per_wg_x;
+  return OneArgs{a.t[0], a.step_lo, a.step_hi, a.tiles_per_wg, a.tiles_per_wg_x, tiles > 2048 ? n_wg / 128 * 128 : 0};
+}
 static_assert(sizeof(LaunchArgs) <= 6144, "kernel arguments: keep within the size verified on the device");
 
 // basis: kBasisBits, or a comparison basis (no MX output then); mode: kKeep, kStreamReads or kStreamAll

@@ -50,19 +50,20 @@ __device__ __forceinline__ void tile_position(const TileDesc& d, uint32_t local,
   bx = r;
 }
 
+// Workgroups are dealt round-robin to the 8 XCDs: sixteen neighbouring tiles go to one XCD, so that a cache line shared by
+// two of them (rows that do not start on lines) meets in its L2.  Rows of 2000 bytes, w and w_hat of 75 M parameters: with
+// ordinary stores 62 us forward, like this 59 (streaming stores 93 and 83); whole lines too: the 1B model's forward pass
+// 667 -> 624 us (8 tiles 644, 32 tiles 630).
+__device__ __forceinline__ uint32_t dealt_out(uint32_t wg) { return (wg & ~127u) + (wg & 7) * 16 + ((wg >> 3) & 15); }
+
 // One tensor: its descriptor is the kernel's argument.
 __device__ __forceinline__ TileDesc locate(const OneArgs& a, uint32_t& byg, uint32_t& bx) {
-  tile_position(a.t, blockIdx.x, byg, bx);
+  tile_position(a.t, blockIdx.x < a.dealt ? dealt_out(blockIdx.x) : blockIdx.x, byg, bx);
   return a.t;
 }
 
 __device__ __forceinline__ TileDesc locate(const LaunchArgs& a, uint32_t& byg, uint32_t& bx) {
-  // Workgroups are dealt round-robin to the 8 XCDs: sixteen neighbouring tiles go to one XCD, so that a cache line shared by
-  // two of them (rows that do not start on lines) meets in its L2.  Rows of 2000 bytes, w and w_hat of 75 M parameters: with
-  // ordinary stores 62 us forward, like this 59 (streaming stores 93 and 83); whole lines too: the 1B model's forward pass
-  // 667 -> 624 us (8 tiles 644, 32 tiles 630).
-  uint32_t wg = blockIdx.x;
-  if (wg < gridDim.x / 128 * 128) wg = (wg & ~127u) + (wg & 7) * 16 + ((wg >> 3) & 15);
+  const uint32_t wg = blockIdx.x < gridDim.x / 128 * 128 ? dealt_out(blockIdx.x) : blockIdx.x;
   const uint32_t* tb = a.tile_begin;
   u32x16s t0 = *(const u32x16s*)(tb), t1 = *(const u32x16s*)(tb + 16), t2 = *(const u32x16s*)(tb + 32);
   u32x8s t3 = *(const u32x8s*)(tb + 48);
@@ -439,15 +440,13 @@ static void launch_fwd(const ARGS& a, uint32_t n_wg, int variant, hipStream_t st
   else hipLaunchKernelGGL((sample_fwd_kernel<FMT, MX, STREAM, BASIS, false, ARGS>), dim3(n_wg), dim3(kThreads), 0, stream, a);
 }
 
-// One weight of up to 32 MB (the call inside every sampled linear): five kilobytes of arguments and two dependent reads of them
-// are a fifth of a small kernel's time, 768 x 768 4.5 -> 3.6 us, and show in larger ones: backward of 2048 x 8192 7.4 -> 6.6,
-// Box-Muller 16.5 -> 15.7 and 10.8 -> 10.2, FP6 codes of 2048 x 5632 8.8 -> 7.7.  Beyond, the order of the tiles (locate) counts more.
-static OneArgs one_of(const LaunchArgs& a) { return OneArgs{a.t[0], a.step_lo, a.step_hi, a.tiles_per_wg, a.tiles_per_wg_x}; }
-
+// One weight (the call inside every sampled linear) takes the small argument block: five kilobytes of arguments and two dependent reads of
+// them are a fifth of a small kernel's time, 768 x 768 4.5 -> 3.6 us, and show in larger ones: backward of 2048 x 8192 7.4 -> 6.6, Box-Muller
+// 16.5 -> 15.7 and 10.8 -> 10.2, FP6 codes of 2048 x 5632 8.8 -> 7.7.
 template <int FMT, bool MX, int BASIS>
 static void launch_fwd_stream(const LaunchArgs& a, uint32_t n_wg, int mode, int variant, hipStream_t stream) {
-  if (mode == kKeep && a.n == 1) launch_fwd<FMT, MX, kKeep, BASIS>(one_of(a), n_wg, variant, stream);
-  else if (mode == kStreamReads && a.n == 1) launch_fwd<FMT, MX, kStreamReads, BASIS>(one_of(a), n_wg, variant, stream);
+  if (mode == kKeep && a.n == 1) launch_fwd<FMT, MX, kKeep, BASIS>(one_of(a, n_wg), n_wg, variant, stream);
+  else if (mode == kStreamReads && a.n == 1) launch_fwd<FMT, MX, kStreamReads, BASIS>(one_of(a, n_wg), n_wg, variant, stream);
   else if (mode == kKeep) launch_fwd<FMT, MX, kKeep, BASIS>(a, n_wg, variant, stream);
   else if (mode == kStreamReads) launch_fwd<FMT, MX, kStreamReads, BASIS>(a, n_wg, variant, stream);
   else launch_fwd<FMT, MX, kStreamAll, BASIS>(a, n_wg, variant, stream);
@@ -486,8 +485,8 @@ static void launch_bwd(const ARGS& a, uint32_t n_wg, int variant, hipStream_t st
 
 template <int BASIS>
 static void launch_bwd_stream(const LaunchArgs& a, uint32_t n_wg, int mode, int variant, hipStream_t stream) {
-  if (mode == kKeep && a.n == 1) launch_bwd<kKeep, BASIS>(one_of(a), n_wg, variant, stream);
-  else if (mode == kStreamReads && a.n == 1) launch_bwd<kStreamReads, BASIS>(one_of(a), n_wg, variant, stream);
+  if (mode == kKeep && a.n == 1) launch_bwd<kKeep, BASIS>(one_of(a, n_wg), n_wg, variant, stream);
+  else if (mode == kStreamReads && a.n == 1) launch_bwd<kStreamReads, BASIS>(one_of(a, n_wg), n_wg, variant, stream);
   else if (mode == kKeep) launch_bwd<kKeep, BASIS>(a, n_wg, variant, stream);
   else if (mode == kStreamReads) launch_bwd<kStreamReads, BASIS>(a, n_wg, variant, stream);
   else launch_bwd<kStreamAll, BASIS>(a, n_wg, variant, stream);

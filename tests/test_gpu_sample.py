@@ -376,3 +376,41 @@ def test_rows_longer_than_the_lane_offsets_reach(ld, rows):
         out.append([w_hat[:, :cols].contiguous().view(torch.int16), d.scale.view(torch.int32), d.dbt.view(torch.int32)])
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+# One weight alone in a call has an argument block of its own, and above 2048 workgroup tiles of 32 x 256 its tiles are dealt out: at that line
+# and over it, whole tiles and ragged ones, rounds of 128 workgroups with and without a rest, every kind of pass; the same bits as
+# beside a second weight.
+@pytest.mark.parametrize("rows,cols", [(4096, 4096), (4128, 4096), (4100, 4090), (32 * 2049, 256), (65600, 40), (70, 262200)])
+def test_one_large_weight_alone_and_beside_another(rows, cols):
+    nbr, nbc = synth.n_blocks(rows, cols)
+    ld = (cols + 7) // 8 * 8
+    gen = torch.Generator(device=DEV).manual_seed(rows)
+    w = (torch.randn(rows, ld, device=DEV, generator=gen) * 0.02).to(torch.bfloat16)
+    g = (torch.randn(rows, ld, device=DEV, generator=gen) * 1e-3).to(torch.bfloat16)
+    bt = 4 + 5 * torch.rand(nbr, nbc, device=DEV, generator=gen)
+    small = dict(w=w[:32, :32].contiguous(), bt=bt[:1, :1].contiguous())
+    small_out = lambda: dict(w_hat=torch.zeros_like(small["w"]), scale=torch.ones_like(small["bt"]), g=small["w"], dw=torch.zeros_like(small["w"]), dbt=torch.zeros_like(small["bt"]))
+    ldc = [(cols * 6 + 7) // 8 + 1 & ~1, ld]
+
+    def run(beside):
+        outs = []
+
+        def descs(**out):
+            outs.extend(out.values())
+            return [gws.TensorDesc(rows=rows, cols=cols, ld=ld, seed=5, w=w, bt=bt, g=g, **out)] + \
+                   ([gws.TensorDesc(rows=32, cols=32, ld=32, seed=6, **small, **small_out())] if beside else [])
+        scale = lambda: torch.ones_like(bt)
+        gws.gws_sample_fwd(descs(w_hat=torch.zeros_like(w), scale=scale()), gws.FMT_FP8_E4M3, 3)
+        gws.gws_sample_fwd_basis(descs(w_hat=torch.zeros_like(w), scale=scale()), gws.BASIS_UNIFORM_BF16, gws.FMT_BF16, 3)
+        for fmt, l in ((gws.FMT_FP6_E3M2, ldc[0]), (gws.FMT_FP8_E4M3, ldc[1])):
+            codes, xs = torch.zeros(rows * l, dtype=torch.uint8, device=DEV), torch.zeros(nbr * nbc, dtype=torch.uint8, device=DEV)
+            outs.extend((codes, xs))
+            other = [gws.MxOut(torch.zeros(32 * 32, dtype=torch.uint8, device=DEV), torch.zeros(1, dtype=torch.uint8, device=DEV), 24 if fmt == gws.FMT_FP6_E3M2 else 32)]
+            gws.gws_sample_fwd_mx(descs(scale=scale()), [gws.MxOut(codes, xs, l)] + (other if beside else []), fmt, 3)
+        gws.gws_sample_bwd(descs(scale=scale(), dw=torch.zeros_like(g), dbt=torch.zeros_like(bt)), 3)
+        gws.gws_sample_bwd_basis(descs(scale=scale(), dw=torch.zeros_like(g), dbt=torch.zeros_like(bt)), gws.BASIS_BOX_MULLER, 3)
+        torch.cuda.synchronize()
+        return outs
+    for i, (a, b) in enumerate(zip(run(False), run(True))):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), i

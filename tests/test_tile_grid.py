@@ -105,3 +105,30 @@ def run(tmp_path, source):
 
 def test_a_row_or_two_over_whole_bands_is_no_part_of_its_own(tmp_path):
     run(tmp_path, JOINED)
+
+
+ONE = r"""
+#include "gws_launch.h"
+#include <cstdio>
+#include <cstring>
+using namespace gws;
+int main() {
+  static LaunchArgs a;
+  memset(&a, 0, sizeof a);
+  a.n = a.tiles_per_wg = 1;
+  // workgroups, column tiles of each -> how many are dealt out: above 2048 tiles, whole rounds of 128
+  const uint32_t cases[][3] = {{1, 1, 0}, {2048, 1, 0}, {2049, 1, 2048}, {2176, 1, 2176}, {683, 3, 640}, {682, 3, 0}, {0x7FFFFFEF, 4, 0x7FFFFF80}};
+  for (const auto& c : cases) {
+    a.tiles_per_wg_x = c[1];
+    if (one_of(a, c[0]).dealt != c[2]) {
+      printf("%u workgroups of %u tiles: %u\n", c[0], c[1], one_of(a, c[0]).dealt);
+      return 1;
+    }
+  }
+  return 0;
+}
+"""
+
+
+def test_one_large_weight_is_dealt_out(tmp_path):
+    run(tmp_path, ONE)
