@@ -21,10 +21,11 @@
 //   4096 x 768 x 3072 71, 49, 52, 30, -, 41;          2048 x 2048 x 2048 62, 41, 33, 37, 24, 40;         4096 x 768 x 2304 60, 36, 26, 29, -, 35
 //   8192 x 2048 x 2048 272, 127, 97, 119, 68, 76;     1024 x 2048 x 4096 80, 52, 44, 47, 30, 40;         8192 x 512 x 512 29, 36, 48, 54, -, 29
 // Both operands lie output-contiguous, so both stages are rows of 2 bytes an output a token and both fragments come from the
-// transposing LDS load.  The tokens are summed in four fp32 sums, or in eight where the workspace at hand would hold more than four
-// parts, so that no sum is longer than in that form: a wavefront's share of the tokens, or in two halves, and the tile kernel adds its
-// accumulators to a second set after every quarter or eighth of the tokens (pieces of 128 x 128: four sums only, see stream_tn_plan).  On the way out each wavefront takes 32 x 32 blocks of the
-// weight: 16 bytes a lane, one Philox group each, and the reduction of Eq. 4 over the wavefront.
+// transposing LDS load.  The tokens are summed in four fp32 sums, so that none is longer than in that form with four parts: a wavefront's
+// share of the tokens each, and the tile kernel adds its accumulators to a second set after every quarter of them.  Where the workspace at
+// hand would hold more than four parts (from 2560 tokens on) the wavefronts sum their shares in two halves, eight sums; the tile kernel
+// has no such form: below 2560 tokens nothing asks for it, and pieces of 128 x 128 are not taken then (stream_tn_plan).  On the way out each
+// wavefront takes 32 x 32 blocks of the weight: 16 bytes a lane, one Philox group each, and the reduction of Eq. 4 over the wavefront.
 #include <math.h>
 
 #include "gws_gemm_stream_core.h"
@@ -453,12 +454,12 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_tn_kernel(GWS_GEMM_PARAMS, u
 }
 
 template <int WM, int WN, int D>
-static void launch_tile(GemmArgs g, bool with_dbt, bool halves, hipStream_t s) {
-  const uint32_t mt = (g.M + 32 * WM - 1) / (32 * WM), nt = (g.N + 32 * WN - 1) / (32 * WN), sums = halves ? 8 : 4;
+static void launch_tile(GemmArgs g, bool with_dbt, hipStream_t s) {
+  const uint32_t mt = (g.M + 32 * WM - 1) / (32 * WM), nt = (g.N + 32 * WN - 1) / (32 * WN);
   if (g.M > g.N) set_tile_grid(g, nt, mt, patch_band(nt, mt, 32 * WN, 32 * WM));
   else set_tile_grid(g, mt, nt, patch_band(mt, nt, 32 * WM, 32 * WN));
   const dim3 grid(mt * nt);
-  const uint32_t fold = (g.K / 64 + sums - 1) / sums;
+  const uint32_t fold = (g.K / 64 + 3) / 4;
   if (with_dbt) hipLaunchKernelGGL((gemm_tile_tn_kernel<WM, WN, D, true>), grid, dim3(256), 0, s, GWS_GEMM_PASS(g), fold, (const GemmSampling&)g);
   else hipLaunchKernelGGL((gemm_tile_tn_kernel<WM, WN, D, false>), grid, dim3(256), 0, s, GWS_GEMM_PASS(g), fold, (const GemmSampling&)g);
 }
@@ -501,18 +502,18 @@ int launch_gemm_stream_tn(const GemmArgs& g, bool with_dbt, const TnPlan& p, boo
   if ((uint64_t)((g.M + 31) / 32) * ((g.N + 31) / 32) >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
   const bool tile = g.ldx < kTileMaxLd && g.ldw < kTileMaxLd;   // 2 x 2 wavefronts
   if (p.mt == 8 && p.nt == 8) {
-    launch_tile<4, 4, 5>(g, with_dbt, false, stream);
+    launch_tile<4, 4, 5>(g, with_dbt, stream);
   } else if (p.mt == 6) {
-    if (tile && g.K <= 1408) launch_tile<3, 3, 6>(g, with_dbt, halves, stream);
+    if (tile && g.K <= 1408) launch_tile<3, 3, 6>(g, with_dbt, stream);
     else halves ? launch_tn<6, 6, 3, true>(g, with_dbt, stream) : launch_tn<6, 6, 3, false>(g, with_dbt, stream);
   } else if (p.mt == 8) {
-    if (tile && g.K <= 1216) launch_tile<4, 2, 6>(g, with_dbt, halves, stream);
+    if (tile && g.K <= 1216) launch_tile<4, 2, 6>(g, with_dbt, stream);
     else halves ? launch_tn<8, 4, 3, true>(g, with_dbt, stream) : launch_tn<8, 4, 3, false>(g, with_dbt, stream);
   } else if (p.nt == 4) {
-    if (tile && g.K <= 128) launch_tile<2, 2, 8>(g, with_dbt, halves, stream);
+    if (tile && g.K <= 128) launch_tile<2, 2, 8>(g, with_dbt, stream);
     else halves ? launch_tn<4, 4, 4, true>(g, with_dbt, stream) : launch_tn<4, 4, 4, false>(g, with_dbt, stream);
   } else {
-    if (tile && g.K <= 128) launch_tile<2, 1, 12>(g, with_dbt, halves, stream);
+    if (tile && g.K <= 128) launch_tile<2, 1, 12>(g, with_dbt, stream);
     else halves ? launch_tn<4, 2, 4, true>(g, with_dbt, stream) : launch_tn<4, 2, 4, false>(g, with_dbt, stream);
   }
   return hipGetLastError() == hipSuccess ? GWS_OK : GWS_ERR_LAUNCH;

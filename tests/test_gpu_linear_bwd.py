@@ -318,7 +318,8 @@ def test_pieces_for_rows_on_cache_lines(form, tokens, rows, cols, room, w_is_nk)
 
 
 # pieces by 2 x 2 wavefronts: fewer stages of 64 tokens than the ring holds, as many, one more, and the last token counts before
-# and the first after which a piece's tokens are split over the wavefronts; room: workspace parts, above four in eight sums
+# and the first after which a piece's tokens are split over the wavefronts; room: a workspace of so many parts, of which the tokens make one to
+# three (the kernel has four fp32 sums whatever the workspace holds)
 @pytest.mark.parametrize("form,tokens,rows,cols,room", [
     (gws.BWD_W_PIECES_32, 128, 256, 512, 0), (gws.BWD_W_PIECES_32, 192, 256, 512, 0), (gws.BWD_W_PIECES_64, 64, 768, 768, 0), (gws.BWD_W_PIECES_64, 128, 1024, 768, 8),
     (gws.BWD_W_PIECES_64, 192, 768, 768, 0), (gws.BWD_W_PIECES_128, 320, 1280, 1024, 0), (gws.BWD_W_PIECES_128, 384, 768, 2304, 8), (gws.BWD_W_PIECES_128, 448, 512, 3328, 0),
