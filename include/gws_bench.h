@@ -72,7 +72,7 @@ int gws_ride_plan_layout(int64_t M, int64_t K, int64_t N, int w_is_nk, const gws
 #define GWS_GEMM_ANY_SHAPE_SAMPLE 9 /* the same on the tiles of 6 */
 int gws_gemm_form(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled);
 /* gws_gemm_tile: of the same call, the part of Y that a workgroup of that kernel makes, rows << 16 | columns (of the stream kernel in
- * whole MFMA tiles of 16 x 16, also where it keeps eight rows or eight columns of one).                                           */
+ * whole MFMA tiles of 16 x 16, also where it keeps eight rows or eight columns of one: gws_gemm_stream_tile).                     */
 int gws_gemm_tile(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled);
 /* gws_gemm_stream_tile: of gws_gemm_bf16 where its kernel is GWS_GEMM_STREAM (0 otherwise), how that kernel is launched:
  * rows << 24 | columns << 16 | fetching << 8 | parts, with the rows and columns of Y that a workgroup stores (eight of a tile among

@@ -12,15 +12,11 @@
 
 namespace gws {
 
-// A wavefront keeps D units of 64 k on their way into its own ring of LDS stages (global_load_lds_dwordx4, 8 rows x 128
-// contiguous bytes per instruction).  Loaded straight into the MFMA's register layout instead (16 rows x 64 bytes: a
-// quarter-wavefront touches 16 cache lines for 16 bytes each) a compute unit takes 39 B/ns whatever is in flight; in this
-// form 130-180 B/ns (L2-resident operands, one workgroup per compute unit).  Layouts as in gws_gemm256_core.h: rows of 128
-// bytes with chunk c of row r in slot c ^ ((r / 2) % 8); a [K x N] weight as 64 k-rows of 32 NT bytes, read with the
-// transposing LDS load, chunk c of row k in slot c ^ swizzle(k).
 // A wavefront's share of a tile's columns of the weight, fetched into the XCD's L2 and dropped: one load instruction touches 64 pieces
 // of lines, every part-th unit of 64 k.  A compute unit gets about 60 B/ns from beyond its L2, a line every 2 ns whether 64 bytes of it are
 // wanted or 128, so few tiles on few compute units wait for the weight while the others idle; what an idle one has fetched comes at 150.
+// A wavefront has one load on its way: the empty statement uses its register, so the next one waits for it.  How many workgroups a tile
+// fetch (stream_plan) is fitted to that.
 template <int BN, bool W_NK>
 __device__ __forceinline__ void warm_l2(const GemmArgs& g, uint32_t n0, uint32_t u0, uint32_t u1, uint32_t part, uint32_t parts) {
   const uint32_t lane = threadIdx.x & 63;
@@ -32,6 +28,12 @@ __device__ __forceinline__ void warm_l2(const GemmArgs& g, uint32_t n0, uint32_t
   }
 }
 
+// A wavefront keeps D units of 64 k on their way into its own ring of LDS stages (global_load_lds_dwordx4, 8 rows x 128
+// contiguous bytes per instruction).  Loaded straight into the MFMA's register layout instead (16 rows x 64 bytes: a
+// quarter-wavefront touches 16 cache lines for 16 bytes each) a compute unit takes 39 B/ns whatever is in flight; in this
+// form 130-180 B/ns (L2-resident operands, one workgroup per compute unit).  Layouts as in gws_gemm256_core.h: rows of 128
+// bytes with chunk c of row r in slot c ^ ((r / 2) % 8); a [K x N] weight as 64 k-rows of 32 NT bytes, read with the
+// transposing LDS load, chunk c of row k in slot c ^ swizzle(k).
 // WARM: the grid has more workgroups a tile (blockIdx.y > 0) that only warm_l2; they share nothing with the others.
 // BM x BN is the workgroup's tile: 16 MT x 16 NT, or eight rows, eight columns where one MFMA tile has that many of use (the others
 // are computed on repeated ones and not stored).
@@ -569,7 +571,8 @@ StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk) {
   // 9.3, 64 x 4096 -> 1024 11.0 -> 7.2; one alone gets no further ahead than the tile's own loads (7 x 2464 -> 3328 7.5 -> 6.6, but 6 x 4896
   // -> 3936 11.4 -> 13.0).  [N x K], 32 columns a tile: 32 x 5632 -> 2048 9.9 -> 9.1 (with three 10.8), 64 x 4096 -> 1024 7.1 -> 6.5.  More
   // than the chip holds cost: 4 x 2048 -> 5632 (176 tiles) 7.1 -> 7.7.  Not where the weight is small (1 x 768 -> 768 2.93, 2.97) or X is not
-  // (2000 x 5632 -> 64 12.0, 12.4).
+  // (2000 x 5632 -> 64 12.0, 12.4).  These are of weights in the last-level cache; from HBM 4 x 5632 -> 2048 22.1 -> 10.4, 8 x 4096 -> 512 16.2 -> 7.3;
+  // one weight multiplied again and again out of the L2s pays for it, 6.8 -> 7.1, 16 x 5632 -> 2048 6.9 -> 7.7.
   if (best.nt == 2 && (!w_is_nk || best.mt == 2) && 4 * M <= N && K >= 512 && K * N >= (uint64_t)1 << 20) {
     const uint64_t row = ((M + best.bm - 1) / best.bm * ((N + best.bn - 1) / best.bn) + 7) / 8 * 8, spare = (uint64_t)cus / row;
     best.warm = w_is_nk ? (spare >= 2 ? 1 : 0) : spare >= 4 ? 3 : spare == 3 ? 2 : 0;
@@ -583,7 +586,7 @@ StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk) {
   // workgroups they stay too.  The orders differ only for a weight that is multiplied again and again out of the L2s; in turn out of the L2s
   // and from HBM, groups and parts: 48 x 4096 -> 3072 7.7, 10.9 and 17.4, 17.3, 132 x 4096 -> 2560 10.5, 12.3 and 19.7, 19.7; up to 2048 columns
   // 48 x 4096 -> 2048 7.1, 7.3 and 16.5, 16.2, 250 x 1440 -> 1024 5.4, 5.4 and 7.9, 7.7; of more than a round 132 x 4096 -> 5632 24.1, 21.8 and 36.1,
-  // 31.4.  Other widths: 48 x 4096 -> 2336 10.0, 7.9 and 13.3, 13.0, 132 x 2816 -> 3104 9.6, 9.1 and 13.1, 13.0; 18 of them beyond 2304 columns
+  // 31.4.  Other widths: 48 x 4096 -> 2336 10.0, 7.9 and 13.3, 13.0, 132 x 4096 -> 2336 14.1, 12.4 and 17.4, 17.1; 18 of them beyond 2304 columns
   // 0.98 out of the L2s, 0.97 from the last-level cache, 0.98 from HBM.
   const uint64_t rows = (M + best.bm - 1) / best.bm, columns = (N + best.bn - 1) / best.bn, all = rows * columns;
   best.parts = columns >= (w_is_nk ? 4 : 6) && all >= 32 && (w_is_nk || (rows > 1 && (N % 512 != 0 || N <= 2048 || all > (uint64_t)cus)));
@@ -619,7 +622,9 @@ static void launch_plain(GemmArgs g, int w_is_nk, const StreamPlan& p, hipStream
 }
 
 int launch_gemm_stream(const GemmArgs& g, int w_is_nk, const StreamPlan& p, hipStream_t s) {
-  // up to 16 rows: two units on their way a wavefront (four, which take all of the LDS: 4 x 5632 -> 2048 [N x K] 6.1 us, two 5.7)
+  // Up to 16 rows of X on [N x K] weights: two units on their way a wavefront; more are in the way where the weight is in a cache.  us with two,
+  // three and four, 4 x 5632 -> 2048 (8 x 8) in the last-level cache 5.7, 5.8, 5.9, from HBM 6.8, 6.2, 6.2; 16 x 5632 -> 2048 (16 x 8) 5.9, 6.1, 6.2 and
+  // 7.8, 7.9, 8.0; 16 x 768 -> 768 (16 x 16) 2.6, 2.6, 2.6 and 3.0, 3.1, 3.1.
   if (p.bn == 8) p.bm == 8 ? launch_plain<1, 1, 8, 2, 8, 8>(g, w_is_nk, p, s) : launch_plain<1, 1, 8, 2, 16, 8>(g, w_is_nk, p, s);
   else if (p.bn == 16) p.bm == 8 ? launch_plain<1, 1, 8, 2, 8, 16>(g, w_is_nk, p, s) : launch_plain<1, 1, 8, 2>(g, w_is_nk, p, s);
   else if (p.bm == 8) launch_plain<1, 2, 8, 2, 8, 32, true>(g, w_is_nk, p, s);

@@ -62,8 +62,9 @@ __device__ __forceinline__ void rows_of_block(u32x2 (&pk)[2][2], u32x4 (&o)[2]) 
 }
 
 // The numbering runs along the longer side of C.  64 x 32 pieces of which an XCD gets at most eight: eight of one row, which read whole
-// lines of dY, rather than four of two columns, which share one (2688 x 256 x 512 11.9 -> 10.7 us, 4096 x 256 x 256 15.8 -> 14.5; with
-// twelve 4096 x 256 x 768 14.4 -> 15.1).
+// lines of dY, rather than four of two columns, which share one.  Over 64 to 8192 tokens 32 and 64 pieces 0.81 to 0.99 of along the rows
+// (2688 x 256 x 512 12.0 -> 10.0 us, 4096 x 256 x 256 16.0 -> 14.4, 256 x 256 x 256 4.6 -> 4.5), 96 to 256 of them 0.98 to 1.11 (4096 x 256 x 768
+// 14.4 -> 15.3, 8192 x 256 x 1280 25.0 -> 27.7, 8192 x 512 x 512 26.2, 26.2).
 template <int NT>
 __host__ __device__ __forceinline__ bool along_columns(const GemmArgs& g, uint32_t mt, uint32_t nt) {
   return g.M > g.N || (NT == 2 && mt * nt <= 64);
