@@ -3,13 +3,15 @@
 //  - gemm_stream_tn_kernel: its four wavefronts split the tokens, as in gws_gemm_stream.hip.  No barrier, but every wavefront holds the
 //    whole piece's sums, which are added through LDS at the end (up to 144 KiB through it, 2 to 4 us).
 //  - gemm_tile_tn_kernel: 2 x 2 wavefronts walk the tokens together, each with a quarter of the piece.  No sum to add up and a way
-//    out of bf16 only, but a barrier every 64 tokens.  The faster one for few tokens, and for pieces of 128 x 128 always (there the
-//    other read a unit's fragments for 64 MFMAs with two units in its ring).  us, first and second (tokens x P x Q):
+//    out of bf16 only, but a barrier every 64 tokens, at which all wait for the last line: the faster one for few tokens, and for longer the
+//    nearer the operands lie.  us, first and second, from the last-level cache (tokens x P x Q):
 //      64 x 768 x 768 in 64 x 64 4.9, 4.3, 128 4.9, 4.6, 256 5.1, 5.2, 1024 7.5, 8.1
 //      64 x 768 x 2304 in 128 x 64 6.9, 5.4, 512 9.1, 8.7, 1024 11.7, 11.5, 1536 13.8, 13.8, 4032 x 2304 x 512 25.2, 25.7
 //      64 x 768 x 3072 in 96 x 96 7.7, 6.3, 512 10.2, 10.2, 832 x 1536 x 1536 12.7, 11.9, 1536 x 768 x 3072 15.5, 15.8
-//      64 x 2048 x 2048 in 128 x 128 10.3, 7.8, 512 14.4, 13.2, 1664 x 1536 x 2048 21.9, 20.0, 2624 x 1536 x 2304 27.9, 26.3, 8192 x 2048 x
-//      2048 67.9, 67.9
+//      2048 x 2048 x 2048 in 128 x 128 25.1, 24.2, 3072 32.0, 31.4, 4096 38.0, 38.3, 6144 52.5, 52.8
+//    and from HBM: 2048 x 2048 x 2048 25.0, 26.2, 3072 32.0, 34.8, 4096 39.5, 46.7, 6144 52.3, 62.1; means of four to ten weights by tokens, second to
+//    first, last-level cache, HBM, X from HBM and dY from the cache: 128 x 128 1024 0.95, 1.0, 1.0, 2048 0.97, 1.06, 1.06, 2560 0.98, 1.08, 1.08, 4096 0.99, 1.15,
+//    1.14; 96 x 96 768 0.99, 1.02, 1.01, 1024 1.0, 1.04, 1.07, 1408 0.97, 1.05, 1.08; 128 x 64 896 0.92, 0.96, 0.92, 1216 0.96, 1.0, 0.99.
 // What bounds them: the operands' bytes, which every piece reads for itself.  All wavefronts of an XCD walk the tokens abreast, so
 // most loads wait for a line that is on its way into the L2 (1.4 us), and the 110 to 160 KiB that the rings keep in flight give
 // 72 to 92 B/ns a compute unit; the same loads from the L2 give 150 (96 x 96 pieces of 768 x 3072 over 4096 tokens: 84 % of the requests
@@ -80,10 +82,10 @@ __global__ __launch_bounds__(256, 1) void gemm_stream_tn_kernel(GWS_GEMM_PARAMS,
   constexpr int P = 4, U = 32, BM = 16 * MT, BN = 16 * NT;
   constexpr int XS = BM * U, STG = (BM + BN) * U, LOADS = MT + NT;   // elements of a stage; load instructions of a unit
   constexpr int BC = NT / 2, BLOCKS = MT / 2 * BC;                   // 32 x 32 blocks of the weight in the piece
-  constexpr int OWN = (BLOCKS + P - 1) / P;
-  static_assert(MT % 2 == 0 && NT % 2 == 0, "whole blocks");
+  constexpr int PASS = BLOCKS <= 9 ? BLOCKS : 8, PASSES = BLOCKS / PASS, OWN = (PASS + P - 1) / P;   // blocks of a pass of the way out
+  static_assert(MT % 2 == 0 && NT % 2 == 0 && PASS * PASSES == BLOCKS, "whole blocks");
   static_assert(LOADS * (D - 1) <= 63, "the wait for a unit counts the loads behind it");
-  constexpr int kRing = P * D * STG * 2, kRed = P * BLOCKS * 4 * 64 * 16;
+  constexpr int kRing = P * D * STG * 2, kRed = P * PASS * 4 * 64 * 16;
   static_assert(kRing <= 160 * 1024 && kRed <= 160 * 1024, "LDS");
   __shared__ __attribute__((aligned(1024))) char lds[kRing > kRed ? kRing : kRed];
   const uint32_t tid = threadIdx.x, lane = tid & 63, li = lane & 15, grp = lane >> 4;
@@ -137,23 +139,26 @@ __global__ __launch_bounds__(256, 1) void gemm_stream_tn_kernel(GWS_GEMM_PARAMS,
 #pragma unroll
   for (int d = 0; d < D; ++d)
     if ((uint32_t)d < n) load(u0 + d, d);
-  // Block b = P k + wave leaves through this wavefront.  Its noise is drawn while the first loads are on their way:
+  // Block b = PASS pass + P k + wave leaves through this wavefront.  Its noise is drawn while the first loads are on their way:
   // of each of its rows a lane writes 16 bytes, row lane % 16 + 16 t, column group 0, 2, 1 or 3 for lane / 16 = 0 .. 3.
   const uint32_t cgl = (grp >> 1) | ((grp & 1) << 1);
-  auto exists = [&](uint32_t b) { return b < (uint32_t)BLOCKS && m0 + b / BC * 32 < g.M && n0 + b % BC * 32 < g.N; };   // uniform
-  Noise noise[OWN][2];
-  float scale[OWN];
+  auto block_of = [&](int pass, int k) { return (uint32_t)(PASS * pass + P * k) + wave; };
+  auto exists = [&](int k, uint32_t b) { return P * k + wave < (uint32_t)PASS && m0 + b / BC * 32 < g.M && n0 + b % BC * 32 < g.N; };   // uniform
+  Noise noise[PASSES][OWN][2];
+  float scale[PASSES][OWN];
   if (DBT) {
 #pragma unroll
-    for (int k = 0; k < OWN; ++k) {
-      const uint32_t b = P * k + wave, p0 = m0 + b / BC * 32, q0 = n0 + b % BC * 32;
+    for (int pass = 0; pass < PASSES; ++pass)
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        noise[k][t] = group_noise(g.cg0 + (q0 >> 3) + cgl, g.row0 + p0 + li + 16 * t, g.step_lo, g.step_hi, g.seed_lo, g.seed_hi);
-        asm volatile("" : "+v"(noise[k][t].c));   // here and now
+      for (int k = 0; k < OWN; ++k) {
+        const uint32_t b = block_of(pass, k), p0 = m0 + b / BC * 32, q0 = n0 + b % BC * 32;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          noise[pass][k][t] = group_noise(g.cg0 + (q0 >> 3) + cgl, g.row0 + p0 + li + 16 * t, g.step_lo, g.step_hi, g.seed_lo, g.seed_hi);
+          asm volatile("" : "+v"(noise[pass][k][t].c));   // here and now
+        }
+        scale[pass][k] = exists(k, b) ? g.scale[(size_t)(p0 >> 5) * (g.N >> 5) + (q0 >> 5)] : 0.0f;
       }
-      scale[k] = exists(b) ? g.scale[(size_t)(p0 >> 5) * (g.N >> 5) + (q0 >> 5)] : 0.0f;
-    }
   }
   uint32_t slot = 0;
   auto units = [&](uint32_t i, uint32_t end) __attribute__((always_inline)) {
@@ -202,47 +207,50 @@ __global__ __launch_bounds__(256, 1) void gemm_stream_tn_kernel(GWS_GEMM_PARAMS,
   // consecutive memory), one barrier, and each wavefront adds its blocks' in the order of the wavefronts, rounds, and turns
   // the MFMA's layout into rows by swapping half rows between lanes (v_permlane16_swap): no second trip through LDS.
   f32x4* red = (f32x4*)lds;
-  __syncthreads();   // the rings are read
 #pragma unroll
-  for (int b = 0; b < BLOCKS; ++b) {
-    const int i = b / BC * 2, j = b % BC * 2;
+  for (int pass = 0; pass < PASSES; ++pass) {
+    __syncthreads();   // what was in this memory is read
 #pragma unroll
-    for (int r = 0; r < 4; ++r) red[((b * P + wave) * 4 + r) * 64 + lane] = acc[i + (r >> 1)][j + (r & 1)];
-  }
-  __syncthreads();
+    for (int b = 0; b < PASS; ++b) {
+      const int i = (PASS * pass + b) / BC * 2, j = (PASS * pass + b) % BC * 2;
 #pragma unroll
-  for (int k = 0; k < OWN; ++k) {
-    const uint32_t b = P * k + wave, p0 = m0 + b / BC * 32, q0 = n0 + b % BC * 32;
-    if (!exists(b)) continue;
-    const f32x4* in = red + b * (P * 4 * 64) + lane;
-    f32x4 v[P][4];
-#pragma unroll
-    for (int w = 0; w < P; ++w)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) v[w][r] = in[(w * 4 + r) * 64];
-    u32x2 pk[2][2];   // [row half][column half]: row lane % 16, columns 4 (lane / 16) .. + 3 of the 16 x 16 tile
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      f32x4 s = v[0][r];
-#pragma unroll
-      for (int w = 1; w < P; ++w)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s[e] = __fadd_rn(s[e], v[w][r][e]);
-      pk[r >> 1][r & 1] = u32x2{pack_bf16_rne(s[0], s[1]), pack_bf16_rne(s[2], s[3])};
+      for (int r = 0; r < 4; ++r) red[((b * P + wave) * 4 + r) * 64 + lane] = acc[i + (r >> 1)][j + (r & 1)];
     }
-    u32x4 o[2];
-    rows_of_block(pk, o);
-    float part = 0.0f;
+    __syncthreads();
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      *(u32x4*)(g.y + (size_t)(p0 + li + 16 * t) * g.ldy + q0 + 8 * cgl) = o[t];
-      if (DBT) part = dot_group_2r(o[t], noise[k][t], part);
-    }
-    if (DBT) {
-      part = block_sum_f32(part);
-      part += __shfl_xor(part, 4);   // the block is the whole wavefront's here
-      const float neg_ln2 = __uint_as_float(0xBF317218u);  // -ln 2
-      if (lane == 0) g.dbt[(size_t)(p0 >> 5) * (g.N >> 5) + (q0 >> 5)] = (neg_ln2 * scale[k]) * (part * 0.5f);
+    for (int k = 0; k < OWN; ++k) {
+      const uint32_t b = block_of(pass, k), p0 = m0 + b / BC * 32, q0 = n0 + b % BC * 32;
+      if (!exists(k, b)) continue;
+      const f32x4* in = red + (P * k + wave) * (P * 4 * 64) + lane;
+      f32x4 v[P][4];
+#pragma unroll
+      for (int w = 0; w < P; ++w)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[w][r] = in[(w * 4 + r) * 64];
+      u32x2 pk[2][2];   // [row half][column half]: row lane % 16, columns 4 (lane / 16) .. + 3 of the 16 x 16 tile
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        f32x4 s = v[0][r];
+#pragma unroll
+        for (int w = 1; w < P; ++w)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) s[e] = __fadd_rn(s[e], v[w][r][e]);
+        pk[r >> 1][r & 1] = u32x2{pack_bf16_rne(s[0], s[1]), pack_bf16_rne(s[2], s[3])};
+      }
+      u32x4 o[2];
+      rows_of_block(pk, o);
+      float part = 0.0f;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        *(u32x4*)(g.y + (size_t)(p0 + li + 16 * t) * g.ldy + q0 + 8 * cgl) = o[t];
+        if (DBT) part = dot_group_2r(o[t], noise[pass][k][t], part);
+      }
+      if (DBT) {
+        part = block_sum_f32(part);
+        part += __shfl_xor(part, 4);   // the block is the whole wavefront's here
+        const float neg_ln2 = __uint_as_float(0xBF317218u);  // -ln 2
+        if (lane == 0) g.dbt[(size_t)(p0 >> 5) * (g.N >> 5) + (q0 >> 5)] = (neg_ln2 * scale[pass][k]) * (part * 0.5f);
+      }
     }
   }
 }
@@ -497,15 +505,20 @@ TnPlan stream_tn_plan(const GemmArgs& g, bool lines, bool halves) {
 }
 
 // halves: eight fp32 sums an element (768 x 768 over 4096 tokens 18.4 -> 18.9 us, 768 x 2304 26.4 -> 27.5).
-// The bounds on the tokens are where the two kernels take the same time (head of this file): the smaller the piece, the less there is
-// to add up at the end, and the more a barrier costs.
+// The bounds on the tokens lie where what the second kernel loses on operands from HBM passes what it gains on cached ones (head of this
+// file; an activation that the forward pass kept comes from HBM).  The smaller the piece, the less there is to add up at the end, and the
+// more a barrier costs.  The first kernel's wavefronts take whole units of 64 tokens, so off multiples of 256 the longest of the four
+// shares is up to a tenth more than a quarter, and the bound lies further on (first to second, last-level cache and HBM, 128 x 128: 2112 tokens 1.09,
+// 0.99, 2496 1.05, 0.95, 3136 1.06, 0.95; 2304 1.03, 0.94).
 int launch_gemm_stream_tn(const GemmArgs& g, bool with_dbt, const TnPlan& p, bool halves, hipStream_t stream) {
   if ((uint64_t)((g.M + 31) / 32) * ((g.N + 31) / 32) >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
   const bool tile = g.ldx < kTileMaxLd && g.ldw < kTileMaxLd;   // 2 x 2 wavefronts
+  const bool uneven = g.K % 256 != 0;
   if (p.mt == 8 && p.nt == 8) {
-    launch_tile<4, 4, 5>(g, with_dbt, stream);
+    if (g.K <= 2048 || (uneven && g.K < 4096)) launch_tile<4, 4, 5>(g, with_dbt, stream);
+    else launch_tn<8, 8, 2, false>(g, with_dbt, stream);
   } else if (p.mt == 6) {
-    if (tile && g.K <= 1408) launch_tile<3, 3, 6>(g, with_dbt, stream);
+    if (tile && (g.K <= 960 || (uneven && g.K <= 1408))) launch_tile<3, 3, 6>(g, with_dbt, stream);
     else halves ? launch_tn<6, 6, 3, true>(g, with_dbt, stream) : launch_tn<6, 6, 3, false>(g, with_dbt, stream);
   } else if (p.mt == 8) {
     if (tile && g.K <= 1216) launch_tile<4, 2, 6>(g, with_dbt, stream);

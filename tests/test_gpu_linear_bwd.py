@@ -317,15 +317,17 @@ def test_pieces_for_rows_on_cache_lines(form, tokens, rows, cols, room, w_is_nk)
     assert torch.equal(dw.view(torch.int16), with_dbt.view(torch.int16))
 
 
-# pieces by 2 x 2 wavefronts: fewer stages of 64 tokens than the ring holds, as many, one more, and the last token counts before
-# and the first after which a piece's tokens are split over the wavefronts; room: a workspace of so many parts, of which the tokens make one to
+# pieces by 2 x 2 wavefronts: fewer stages of 64 tokens than the ring holds, as many, one more, and the last token counts before and the
+# first after which a piece's tokens are split over the wavefronts, multiples of 256 and others; room: a workspace of so many parts, of which the tokens make one to
 # three (the kernel has four fp32 sums whatever the workspace holds)
 @pytest.mark.parametrize("form,tokens,rows,cols,room", [
     (gws.BWD_W_PIECES_32, 128, 256, 512, 0), (gws.BWD_W_PIECES_32, 192, 256, 512, 0), (gws.BWD_W_PIECES_64, 64, 768, 768, 0), (gws.BWD_W_PIECES_64, 128, 1024, 768, 8),
     (gws.BWD_W_PIECES_64, 192, 768, 768, 0), (gws.BWD_W_PIECES_128, 320, 1280, 1024, 0), (gws.BWD_W_PIECES_128, 384, 768, 2304, 8), (gws.BWD_W_PIECES_128, 448, 512, 3328, 0),
     (gws.BWD_W_PIECES_128, 1216, 768, 2304, 8), (gws.BWD_W_PIECES_128, 1280, 768, 2304, 0), (gws.BWD_W_PIECES_96, 384, 768, 2816, 8), (gws.BWD_W_PIECES_96, 1408, 2816, 768, 0),
     (gws.BWD_W_PIECES_96, 1472, 768, 2816, 0), (gws.BWD_W_PIECES_128_128, 256, 2048, 1792, 0), (gws.BWD_W_PIECES_128_128, 320, 1280, 1792, 0),
-    (gws.BWD_W_PIECES_128_128, 384, 1024, 3328, 8), (gws.BWD_W_PIECES_128_128, 1664, 1536, 2048, 8)])
+    (gws.BWD_W_PIECES_128_128, 384, 1024, 3328, 8), (gws.BWD_W_PIECES_128_128, 1664, 1536, 2048, 8), (gws.BWD_W_PIECES_96, 960, 768, 2816, 8),
+    (gws.BWD_W_PIECES_96, 1024, 2816, 768, 0), (gws.BWD_W_PIECES_128_128, 2048, 1024, 2304, 8), (gws.BWD_W_PIECES_128_128, 2304, 1280, 1792, 0),
+    (gws.BWD_W_PIECES_128_128, 2240, 1024, 2304, 8), (gws.BWD_W_PIECES_128_128, 4160, 1280, 1792, 0)])
 def test_pieces_by_wavefronts_that_walk_the_tokens_together(form, tokens, rows, cols, room):
     nk = bool(tokens & 64)
     d = gws.TensorDesc(rows=rows, cols=cols, seed=1, dw=torch.empty(rows, cols, dtype=torch.bfloat16, device=DEV))
