@@ -74,10 +74,10 @@ int gws_gemm_form(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int
 /* gws_gemm_tile: of the same call, the part of Y that a workgroup of that kernel makes, rows << 16 | columns (of the stream kernel in
  * whole MFMA tiles of 16 x 16, also where it keeps eight rows or eight columns of one: gws_gemm_stream_tile).                     */
 int gws_gemm_tile(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled);
-/* gws_gemm_stream_tile: of gws_gemm_bf16 where its kernel is GWS_GEMM_STREAM (0 otherwise), how that kernel is launched:
+/* gws_gemm_stream_tile: of the same call where its kernel is GWS_GEMM_STREAM (0 otherwise), how that kernel is launched:
  * rows << 24 | columns << 16 | fetching << 8 | parts, with the rows and columns of Y that a workgroup stores (eight of a tile among
  * them), the workgroups a tile that only fetch the weight into the L2s, and whether each XCD takes a contiguous part of the tiles. */
-uint32_t gws_gemm_stream_tile(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk);
+uint32_t gws_gemm_stream_tile(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled);
 
 /* gws_linear_bwd_w_form: of gws_linear_bwd_w_ws for this weight (rows, cols) over M tokens with that much workspace, X, dY and
  * dW being rows that start on 128-byte lines (contiguous ones do); _rows: the same for either, on_lines = 0 where some do not. */

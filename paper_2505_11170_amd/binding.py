@@ -144,7 +144,7 @@ def load_library() -> ctypes.CDLL:
     L.gws_gemm_form.restype = ci
     L.gws_gemm_tile.argtypes = [i64, i64, i64, i64, i64, ci, ci]
     L.gws_gemm_tile.restype = ci
-    L.gws_gemm_stream_tile.argtypes = [i64, i64, i64, i64, i64, ci]
+    L.gws_gemm_stream_tile.argtypes = [i64, i64, i64, i64, i64, ci, ci]
     L.gws_gemm_stream_tile.restype = ctypes.c_uint32
     L.gws_linear_bwd_w_form.argtypes = [tp, i64, ctypes.c_size_t]
     L.gws_linear_bwd_w_form.restype = ci
@@ -462,11 +462,12 @@ def gws_gemm_tile(M: int, K: int, N: int, w_is_nk: bool = False, sampled: int = 
     return t >> 16, t & 0xFFFF
 
 
-def gws_gemm_stream_tile(M: int, K: int, N: int, w_is_nk: bool = False, ldx: Optional[int] = None, ldw: Optional[int] = None) -> tuple:
-    """Of ``gws_gemm_bf16`` by ``GEMM_STREAM``: rows and columns that a workgroup stores, workgroups a tile that only fetch the weight into the
-    L2s, whether each XCD takes a contiguous part of the tiles; zeros for another kernel."""
+def gws_gemm_stream_tile(M: int, K: int, N: int, w_is_nk: bool = False, ldx: Optional[int] = None, ldw: Optional[int] = None,
+                         sampled: int = 0) -> tuple:
+    """Of the call that ``gws_gemm_form`` with these arguments names, by ``GEMM_STREAM``: rows and columns that a workgroup stores, workgroups a
+    tile that only fetch the weight into the L2s, whether each XCD takes a contiguous part of the tiles; zeros for another kernel."""
     t = int(load_library().gws_gemm_stream_tile(int(M), int(K), K if ldx is None else int(ldx), int(N), (K if w_is_nk else N) if ldw is None else int(ldw),
-                                                int(bool(w_is_nk))))
+                                                int(bool(w_is_nk)), int(sampled)))
     return t >> 24, t >> 16 & 0xFF, t >> 8 & 0xFF, t & 0xFF
 
 

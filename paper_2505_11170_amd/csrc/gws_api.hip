@@ -310,7 +310,7 @@ int linear_staged(const void* x, int64_t M, int64_t K, int64_t ldx, const gws_te
   int rc = run_batched(&t, 1, nullptr, nullptr, true, fmt, step, stream, /*keep=*/true);
   if (rc != GWS_OK) return rc;
   g.w = (const uint16_t*)staging;
-  return launch_gemm(g, w_is_nk, 0, GWS_FMT_BF16, stream);
+  return launch_gemm(g, w_is_nk, kJustSampled, GWS_FMT_BF16, stream);
 }
 
 }  // namespace
@@ -522,7 +522,7 @@ int gws_linear_fwd_mode(const void* x, int64_t M, int64_t K, int64_t ldx, const 
     rc = run_batched(w, 1, nullptr, nullptr, true, fmt, step, (hipStream_t)stream, /*keep=*/true);
     if (rc != GWS_OK) return rc;
     g.w = g.w_hat;
-    return launch_gemm(g, w_is_nk, 0, GWS_FMT_BF16, (hipStream_t)stream);
+    return launch_gemm(g, w_is_nk, kJustSampled, GWS_FMT_BF16, (hipStream_t)stream);
   }
   return launch_gemm(g, w_is_nk, kFusedInOperand, fmt, (hipStream_t)stream);
 }
@@ -708,6 +708,7 @@ static int gemm_query(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw,
   memset(&g, 0, sizeof g);
   g.M = (uint32_t)M; g.N = (uint32_t)N; g.K = (uint32_t)K; g.ldx = (uint32_t)ldx; g.ldw = (uint32_t)ldw;
   const GemmForm form = gemm_form(g, w_is_nk, sampled == 1 || (sampled == 2 && sample_in_operand(g, w_is_nk)) ? kFusedInOperand : 0, plan);
+  if (sampled == 2) stream_after_sampling(g, w_is_nk, plan.stream);
   gemm_tile(g, form, plan, rows, cols);
   return (int)form;
 }
@@ -724,10 +725,10 @@ int gws_gemm_tile(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int
   return gemm_query(M, K, ldx, N, ldw, w_is_nk, sampled, rows, cols, plan) == 0 ? 0 : (int)(rows << 16 | cols);
 }
 
-uint32_t gws_gemm_stream_tile(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk) {
+uint32_t gws_gemm_stream_tile(int64_t M, int64_t K, int64_t ldx, int64_t N, int64_t ldw, int w_is_nk, int sampled) {
   uint32_t rows, cols;
   RoutePlan plan;
-  if (gemm_query(M, K, ldx, N, ldw, w_is_nk, 0, rows, cols, plan) != GWS_GEMM_STREAM) return 0;
+  if (gemm_query(M, K, ldx, N, ldw, w_is_nk, sampled, rows, cols, plan) != GWS_GEMM_STREAM) return 0;
   return (uint32_t)plan.stream.bm << 24 | (uint32_t)plan.stream.bn << 16 | (uint32_t)plan.stream.warm << 8 | (uint32_t)plan.stream.parts;
 }
 

@@ -593,6 +593,15 @@ StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk) {
   return best;
 }
 
+// An [N x K] weight of 8 MB or more that the launch before wrote, and up to four tile rows: the order by groups.  What was written last
+// comes in slower, and by parts that is all one XCD's.  us by parts and by groups, sampling in FP8 (8.1 of 2048 x 5632) and product: 1 x
+// 2048 -> 5632 21.8, 17.3; 1 x 5632 -> 2048 20.3, 18.1; 64 x 2048 -> 5632 23.8, 19.9; 30 x 4096 -> 4096 26.2, 24.0; 203 x 2048 -> 3424 20.5,
+// 18.4; 1 x 2048 -> 2048 10.7, 10.2.  Parts where the weight is smaller (469 x 1440 -> 2272 18.5, 19.2; 1 x 2272 -> 736 8.3, 8.5) or shared by
+// more rows (261 x 2336 -> 5952 32.7, 33.5; 457 x 5792 -> 1792 33.0, 36.3); [K x N] 59 x 4128 -> 1888 18.8, 21.6.
+void stream_after_sampling(const GemmArgs& g, int w_is_nk, StreamPlan& p) {
+  if (p.p > 0 && w_is_nk && ((uint64_t)g.M + p.bm - 1) / p.bm <= 4 && (uint64_t)g.K * g.N >= (uint64_t)1 << 22) p.parts = 0;
+}
+
 bool stream_applicable(const GemmArgs& g) {
   return g.K >= 64 && g.K % 32 == 0 && g.N % 32 == 0 && g.M > 0 && g.N > 0 && g.ldx < stream::kMaxLd && g.ldw < stream::kMaxLd;
 }

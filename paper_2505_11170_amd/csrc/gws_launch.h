@@ -196,8 +196,9 @@ __host__ __device__ __forceinline__ void tile_of_groups(const TileGrid& t, bool 
   }
   tile_in_bands(t, L, tile_m, tile_n);
 }
-// fused: 0 = plain GEMM on g.w; kFusedInOperand = sampling in the weight operand load of every tile
-constexpr int kFusedInOperand = 2;
+// fused: 0 = plain GEMM on g.w; kJustSampled = the same, the launch before writes g.w; kFusedInOperand = sampling in the weight operand
+// load of every tile
+constexpr int kJustSampled = 1, kFusedInOperand = 2;
 int launch_gemm(const GemmArgs& g, int w_is_nk, int fused, int fmt, hipStream_t stream);
 // few rows of X or few tiles (gws_gemm_stream.hip): the tile in units of 16 rows and 16 columns, the parts of K, the rows and
 // columns of it that a workgroup owns, the workgroups a tile that warm the L2, whether each XCD takes a contiguous part of the tiles,
@@ -207,6 +208,7 @@ struct StreamPlan {
   double us;
 };
 StreamPlan stream_plan(uint64_t M, uint64_t N, uint64_t K, bool w_is_nk);
+void stream_after_sampling(const GemmArgs& g, int w_is_nk, StreamPlan& p);   // the plan where the launch before writes the weight
 bool stream_applicable(const GemmArgs& g);
 int launch_gemm_stream(const GemmArgs& g, int w_is_nk, const StreamPlan& p, hipStream_t stream);
 int launch_gemm_stream_sample(const GemmArgs& g, int w_is_nk, int fmt, int p, hipStream_t stream);

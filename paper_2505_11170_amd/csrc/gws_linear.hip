@@ -290,13 +290,17 @@ int launch_gemm(const GemmArgs& g, int w_is_nk, int fused, int fmt, hipStream_t 
   if (tiles == 0) return GWS_OK;
   if (tiles >= 0x7FFFFFFFull) return GWS_ERR_SHAPE;
   const dim3 grid((uint32_t)tiles);
+  const bool just_sampled = fused == kJustSampled;
+  if (just_sampled) fused = 0;
   RoutePlan plan;
   GemmForm form = gemm_form(g, w_is_nk, fused, plan);
   const bool large_tile = !fused && g.M == 256 && g.N == 256 && gemm256_applicable(g);
   if ((tiles == 1 || large_tile) && in_place(g, w_is_nk, fused))
     form = large_tile ? GemmForm::kLarge : fused ? GemmForm::kAnyShapeSample : GemmForm::kAnyShape;
   switch (form) {
-    case GemmForm::kStream: return launch_gemm_stream(g, w_is_nk, plan.stream, stream);
+    case GemmForm::kStream:
+      if (just_sampled) stream_after_sampling(g, w_is_nk, plan.stream);
+      return launch_gemm_stream(g, w_is_nk, plan.stream, stream);
     case GemmForm::kMiddle: return launch_gemm128(g, w_is_nk, plan.middle_nj, stream);
     case GemmForm::kLarge: return launch_gemm256(g, w_is_nk, stream);
     case GemmForm::kLargeEdge: return launch_gemm256_edge(g, w_is_nk, stream);

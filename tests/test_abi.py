@@ -163,6 +163,11 @@ def test_queries_of_the_chosen_kernel(lib):
     # [K x N], two tile rows and more: parts, unless the columns are a multiple of 512 beyond 2048 and the tiles one round of the compute units
     assert [launch(100, 2048, n)[3] for n in (2048, 2304, 2336, 2560, 2592, 3072, 5600)] == [1, 1, 1, 0, 1, 0, 1] and launch(132, 4096, 5632)[3] == 1
     assert [launch(16, 2048, n)[3] for n in (2304, 2336)] == [0, 0] and [launch(100, 2048, n, True)[3] for n in (96, 2560)] == [0, 1]
+    # the launch before writes the weight: [N x K] of 8 MB and more, up to four tile rows, by groups
+    after = lambda m, k, n, nk=True: (launch(m, k, n, nk)[3], launch(m, k, n, nk, sampled=2)[3])
+    assert [after(64, 5632, 2048), after(128, 2048, 2048), after(16, 5632, 2048), after(203, 2048, 3424)] == [(1, 0)] * 4
+    assert [after(129, 2048, 2048), after(128, 2048, 2016), after(261, 2336, 5952), after(64, 5632, 2048, False)] == [(1, 1)] * 4
+    assert launch(64, 5632, 2048, True)[:3] == launch(64, 5632, 2048, True, sampled=2)[:3] and launch(16, 768, 768, True, sampled=2) == (0, 0, 0, 0)
     wide = binding.TensorDesc(rows=4096, cols=4096, ld=4096, seed=1)
     assert binding.gws_linear_bwd_w_form(wide, 512) == binding.BWD_W_WIDE and binding.gws_linear_bwd_w_form(wide, 63) == 0
 

@@ -427,6 +427,15 @@ def test_gemm_whose_weight_is_fetched_by_idle_compute_units(M, K, N, kn, nk, w_i
     run_case(M, K, N, w_is_nk, gws.FMT_FP8_E4M3, seed_id=62, ldx_pad=8, ldy_pad=8, mode=gws.LINEAR_IN_OPERAND, rows_sel=np.array(sorted({0, M // 2, M - 1})))
 
 
+# A large [N x K] weight that the launch before wrote is taken by groups of tiles, kept weights by parts (both in run_case, bit for bit): each
+# tile, with and without fetching workgroups, one and four rows of tiles and a last column that is not whole (the query says zeros where
+# gws_linear_fwd would sample in the operand load; the two kernels are asked for).
+@pytest.mark.parametrize("M,K,N", [(1, 2080, 2048), (16, 1056, 4000), (8, 800, 5280), (33, 2080, 2048), (128, 2080, 2048), (100, 1056, 4000), (203, 2048, 3424)])
+def test_gemm_on_a_weight_that_was_just_sampled(M, K, N):
+    assert gws.gws_gemm_stream_tile(M, K, N, True, ldx=K + 8)[3] == 1 and gws.gws_gemm_stream_tile(M, K, N, True, ldx=K + 8, sampled=2)[3] == 0
+    run_case(M, K, N, True, gws.FMT_FP8_E4M3, seed_id=64, ldx_pad=8, ldy_pad=8, mode=gws.LINEAR_TWO_KERNELS, rows_sel=np.array(sorted({0, M // 2, M - 1})))
+
+
 def test_riding_under_a_gemm_of_many_k_steps():
     # 182 tiles of 256 x 256: the large tile is the faster one and leaves 74 compute units idle
     assert gws.gws_gemm_form(6656, 1024, 1792) == gws.GEMM_LARGE
